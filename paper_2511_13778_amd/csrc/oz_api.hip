@@ -3,6 +3,7 @@
 // the ones after the verdict read the device-resident record and return at once when they are
 // not selected, so no host-device synchronisation is needed to route a call
 // (paper: section "GPU-Resident Integration" and the flowchart of the GEMM decision process).
+#include <algorithm>
 #include <cstring>
 #include <new>
 #include <vector>
@@ -98,6 +99,8 @@ bool make_problem(const oz_handle& h, const oz_opts_t& o, int64_t m, int64_t n, 
     p.np = round_up(n > 0 ? n : 1, kRowPad);
     p.kp = round_up(k > 0 ? k : 1, kKPad);
     p.s_cap = slice_cap(h, o, m, n, k);
+    // fixed modes: the count itself; dynamic: that of an ESC of 1, the smallest there is
+    p.s_min = o.mode == OZ_DYNAMIC ? std::max(1, std::min((o.target_bits + 1 + 1 + kHeadroomBits + 7) / 8, p.s_cap)) : p.s_cap;
     p.kblk = k_block_length(p.s_cap);
     p.nkb = int((p.kp + p.kblk - 1) / p.kblk);
     p.esc_block = o.esc_block > 0 ? o.esc_block : kDefaultEscBlock;

@@ -6,33 +6,52 @@
 //
 //   P_d[j][i] = sum_{s+t=d} sum_{l in k-block kb} As[s][i][l] * Bs[t][j][l],   d = 0..S-1
 //
-// One launch covers all S(S+1)/2 pairs: a workgroup owns a 256x256 tile of C and walks the
-// anti-diagonals d from the least significant (S-1) to the most significant (0); all pairs of one d
-// accumulate into the same int32 registers (their k ranges are simply concatenated).  When an
-// anti-diagonal is complete its sum T is split exactly into a balanced digit (T mod 256 in
-// [-128,127], one byte per element, written out) and a carry (T - digit)/256 that stays in the
-// accumulators as the start value of the next anti-diagonal; the last one (d = 0) is written as an
-// int32 word.  So a k-block leaves the exact integer sum_d P_d 256^(S-1-d) in 4 + (S-1) bytes per
-// element instead of 4S, already aggregated: the FP64 recomposition converts it in one pass.
+// One launch covers all S(S+1)/2 pairs.  A workgroup owns a 128x128 unit of C and takes the
+// anti-diagonals in groups of up to four, from the least significant (S-1) to the most significant
+// (0): four sets of int32 accumulators grow side by side while k is walked once per group.  When a
+// group is complete, its sums are split exactly, least significant first, into a balanced digit
+// (T mod 256 in [-128,127], one byte per element, written out) and a carry (T - digit)/256 added to
+// the next anti-diagonal's sum; the carry out of a group is the start value of the next one, and
+// d = 0 is written as an int32 word.  So a k-block leaves the exact integer sum_d P_d 256^(S-1-d) in
+// 4 + (S-1) bytes per element instead of 4S, already aggregated.
+//
+// What bounds it: power.  An MFMA-only loop on random digits reaches 3.5 POP/s with 32x32x32 and 3.7-4.2
+// with 16x16x64 tiles (4.9 with constant operands, where the clock stays up); every byte moved on the way
+// takes its share of the same budget: one LDS read of 1 KB per two 32x32x32 MFMAs costs 8 %, one
+// direct-to-LDS transfer of 1 KB per four costs another 10 % (loops of the same shape as the one below).
+// Hence the order of the loops.  Four anti-diagonals at a time means that an A fragment read from LDS
+// meets four B slices, and a B fragment that has been read stays in registers for four steps:
+//  * A step is one slice s of A for 64 of k.  With d_hi the group's first anti-diagonal, step s multiplies
+//    A_s with B_t, t = d_hi-s-j, j = 0..3 (as far as t >= 0), accumulator set j.  From one step to
+//    the next the window of B slices moves by one: it lives in four register slots.
+//  * For seven slices a 64 of k thus costs 10 tiles of A and of B for 28 pairs (7 + 3 in the groups
+//    6..3 and 2..0) instead of 28: 29 % fewer bytes through L2, LDS and the fabric than 256x256 tiles that
+//    walk the pairs one by one, at the same 256 accumulator registers per lane.
+//  * v_mfma_i32_16x16x64_i8: per operation it moves a fifth less through the register file than
+//    32x32x32 (16x16 sums are read and written for 64 of k instead of 32).
+// Measured with seven slices, against one pair at a time on 256x256 tiles of 32x32x32: 8192^3 11.2 -> 10.3 ms
+// (2.75 -> 2.99 POP/s; matrix unit busy 75 % of the cycles at 1.83 GHz), 1024x1024x65536 1.85 -> 1.27 ms, and
+// where the quarter of the size lets more CUs work without a k split, 2048^3 0.53 -> 0.19 ms.
 //
 // Mapping to gfx950:
-//  * v_mfma_i32_32x32x32_i8; 4 waves per workgroup, each wave a 128x128 sub-tile (4x4 MFMA
-//    tiles, 256 accumulator registers per lane); one workgroup per CU.
-//  * K step 64 per pipeline stage; 4 LDS stages of 32 KB (128 of the CU's 160 KB).  Tiles go
-//    from HBM/L2 straight into LDS with global_load_lds_dwordx4 (no staging registers, no LDS
-//    store instructions), issued three stages ahead of their use; one workgroup barrier per
-//    stage.  The slice panels are stored [k/16][row][16], so a tile is four contiguous 4 KB
-//    runs per operand and the LDS image [k chunk][row][16 B] is what the MFMA operand loads
-//    read (ds_read_b128 per lane: row = lane%32, k chunk = lane/32) without bank conflicts.
+//  * 4 waves per workgroup, each 64x64 x four anti-diagonals (256 accumulator registers per lane); one
+//    workgroup per CU.
+//  * 10 LDS stages of 16 KB (all 160 KB), one per step.  Tiles go from L2 straight into LDS
+//    with global_load_lds_dwordx4 (no staging registers, no LDS store instructions), issued seven
+//    steps ahead; one workgroup barrier per step.  The slice panels are stored [k/16][row][16], so a
+//    tile is four contiguous 2 KB runs per operand and the LDS image [k chunk][row][16 B] is what
+//    the MFMA operand loads read (ds_read_b128 per lane: row = lane%16, k chunk = lane/16).
 //  * The B-slices feed the MFMA's row operand and the A-slices its column operand, so the lane
-//    index of the result runs along i and the stores to P (i contiguous) coalesce.
-//  * Workgroup ids are remapped so that the tiles resident on one XCD form a compact block and
-//    share their A and B panels in that XCD's L2; the workgroups of such a block wait for each
+//    index of the result runs along i and the four registers of a lane are four consecutive j: one
+//    dword of the digit planes.
+//  * Workgroup ids are remapped so that the units resident on one XCD form a compact block and
+//    share their A and B panels in that XCD's L2; the workgroups of such a round wait for each
 //    other (bounded) so that they stay within what L2 holds.
-//  * One wave per SIMD, so nothing hides an instruction that delays the next MFMA: at most one
-//    LDS read or one tile transfer (three instructions) sits between two MFMAs, tile addresses
-//    advance by one add per K step (the full address is recomputed only when the slice pair
-//    changes), and the workgroup barrier of a K step is followed by four MFMAs that cover it.
+//  * One wave per SIMD, so nothing hides an instruction that delays the next MFMA: LDS reads, transfers and scalar
+//    work are spread over the gaps between a step's MFMAs, and the loops are laid out for few branches.
+#include <algorithm>
+#include <type_traits>
+
 #include "oz_internal.h"
 
 namespace oz {
@@ -40,48 +59,65 @@ namespace oz {
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 
-constexpr int kBM = 256;             // tile extent along i (rows of op(A))
-constexpr int kBN = 256;             // tile extent along j (columns of op(B))
-constexpr int kBK = 64;              // K step per pipeline stage (kKPad is a multiple)
-constexpr int kStages = 4;
-constexpr int kStageBytes = (kBM + kBN) * kBK;   // 32 KB
-constexpr int kGemmLds = kStages * kStageBytes;  // 128 KB
-constexpr int kDmaPerStage = 2 * (kBK / 16);     // DMA instructions per wave per stage (A and B)
-static_assert(kKPad % kBK == 0, "k padding must cover whole K steps");
-static_assert(kBM == kTile && kBN == kTile, "a workgroup tile is one block of C with its own slice count");
-static_assert(kDmaPerStage == 8, "the vmcnt immediates below assume 8 DMA instructions per stage");
+constexpr int kUnit = 128;                       // edge of the unit of C a workgroup owns (four per kTile block)
+constexpr int kDiag = 4;                         // anti-diagonals accumulated side by side
+constexpr int kDiagAtomic = 3;                   // the same in the atomic variant (its 32x32 tiles need more registers in flight)
+constexpr int kBK = 64;                          // k per step (kKPad is a multiple)
+constexpr int kStages = 10;                      // LDS stages; the pipeline below counts on ten
+constexpr int kOperandBytes = kUnit * kBK;       // 8 KB: one operand's tile
+constexpr int kStageBytes = 2 * kOperandBytes;   // A tile, then B tile
+constexpr int kRingBytes = kStages * kStageBytes;
+constexpr int kGemmLds = kRingBytes;             // 160 KB: all of the CU's LDS
+static_assert(kKPad % kBK == 0, "k padding must cover whole steps");
+static_assert(kTile == 2 * kUnit, "a block of C with its own slice count is two by two units");
 
-constexpr int kRoundTiles = 32;       // workgroups an XCD runs at a time: 32 CUs, one workgroup each
+constexpr int kRoundUnits = 32;       // workgroups an XCD runs at a time: 32 CUs, one workgroup each
 constexpr int kMaxSyncSpins = 384;    // upper bound of the wait for the other workgroups of a round
-constexpr int kMidSyncMinK = 12288;   // from this k on, workgroups also wait after every anti-diagonal
-constexpr int kMinSplitSteps = 8;     // a part of a split k range keeps at least this many K steps
+constexpr int kSyncMinK = 2048;       // units of a shorter k run without the in-step waits
+constexpr int kMidSyncMinK = 24576;   // from this k on, workgroups also wait after every group of anti-diagonals
+
+// The streams of tiles run up to nine entries ahead of the multiplication: with at least this many per unit they never
+// need to know more than the next unit.
+constexpr int kMinUnitItems = 12;
+
+// What a launch of the slice GEMM covers.
+struct GemmGrid {
+    int nti, ntj;      // kTile x kTile blocks of the padded C
+    int um, un;        // units with at least one row / column of C
+    int begin, count;  // plain order: units [begin, begin + count); per-block order: as many positions of the order table
+    int zsplit;        // parts of the k range per unit
+    int nkb_part;      // k-blocks a part's slot has room for (parts other than the first)
+    int full_chip;     // 8 XCDs of 32 CUs: the in-step waits make sense
+    int persistent;    // a workgroup takes several units, and every unit has at least kMinUnitItems items
+};
+
+// Where part z > 0 of unit `local` of a launch leaves its aggregated sums: a slot of the raw buffer holding, per
+// k-block the part touches, T [128 j][128 i] int32 and L [s_cap-1][32][128 i][4 j] int8 of the unit alone.
+__host__ __device__ inline int64_t part_slot_bytes(int s_cap) { return int64_t(kUnit) * kUnit * (4 + (s_cap - 1)); }
 
 // Records this workgroup's arrival at *counter and, if `wait`, waits (bounded, about half a
 // millisecond) until `target` workgroups have arrived.  The wait only improves cache locality:
 // correctness does not depend on it, and every wave gets past it whatever the other workgroups do.
-// Returns whether the others were met in time; a workgroup that was not (the chip is shared with
-// another kernel, or workgroups are not placed as assumed) keeps counting its arrivals, which the
-// others rely on, but stops waiting, so the cost of a wrong assumption is paid once per tile.
-__device__ __forceinline__ bool round_sync(int32_t* counter, int target, bool wait) {
-    int met = 0;
+// A workgroup that did not meet the others in time (the chip is shared with another kernel, or workgroups are not
+// placed as assumed) keeps counting its arrivals, which the others rely on, but stops waiting (`wait` of thread 0
+// becomes false), so the cost of a wrong assumption is paid once.
+__device__ __forceinline__ void round_sync(int32_t* counter, int target, bool& wait) {
     if (threadIdx.x == 0) {
         atomicAdd(counter, 1);
         if (wait) {
+            bool met = false;
             for (int spin = 0; spin < kMaxSyncSpins && !met; ++spin) {
                 met = __hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= target;
                 if (!met) __builtin_amdgcn_s_sleep(8);
             }
+            wait = met;
         }
     }
-    return __syncthreads_or(met) != 0;
+    asm volatile("s_barrier" ::: "memory");
 }
 
-__device__ __forceinline__ v4i as_v4i(const uint4& v) { return v4i{int(v.x), int(v.y), int(v.z), int(v.w)}; }
-
-// linear workgroup id -> tile coordinates.  Ids are dealt round-robin to the 8 XCDs by the
-// hardware; each XCD is given a contiguous range of a tile order in which 32 consecutive tiles
-// form a 4 (i) x 8 (j) block.
-// position `lin` of the tile order -> tile coordinates: panels of 8 tile columns, i fastest inside
+// position `lin` of the tile order -> tile coordinates: panels of 8 tile columns, inside a panel row by row,
+// so 32 consecutive tiles form a 4 (i) x 8 (j) block
 __device__ __forceinline__ void lin_to_tile(int lin, int nti, int ntj, int& ti, int& tj) {
     constexpr int GW = 8;
     const int panel = lin / (GW * nti);
@@ -91,393 +127,641 @@ __device__ __forceinline__ void lin_to_tile(int lin, int nti, int ntj, int& ti, 
     tj = panel * GW + in_panel % w;
 }
 
-// A launch covers the tiles [tile_begin, tile_begin + tile_count) of the tile order.  With a k split
-// (zsplit > 1) a work unit is (tile, part of the k range); units are ordered part by part, so the
-// units an XCD runs together still are neighbouring tiles of the same k range.
-// `order` (per-tile mode, else null) maps a position of the tile order to the tile that runs there.
-__device__ __forceinline__ void tile_of(int bid, int nti, int ntj, int tile_begin, int tile_count, int zsplit,
-                                        const int32_t* __restrict__ order,
-                                        int& ti, int& tj, int& z, int& xcd, int& slot, int& xcd_tiles, int& lin) {
-    const int total = tile_count * zsplit;
-    xcd = bid & 7;
-    slot = bid >> 3;
+// Position `slot` of an XCD's range -> unit of C.  Workgroup ids are dealt round-robin to the 8 XCDs by the hardware; each XCD is given a
+// contiguous range.  With a k split (zsplit > 1) a work item is (unit, part of the k range), ordered part by
+// part, so the items an XCD runs together still are neighbours on the same k range.
+// Plain order: the units themselves in the 4 x 8 order of lin_to_tile.  Per-block order (`order` maps a position
+// to a kTile block): an XCD's blocks are taken in groups of 32, and a group in four rounds, one per quadrant, so a
+// round touches one 128-row half of each panel: as many panel bytes as a 4 x 8 block of units.
+// Returns false past the end of the range.
+__device__ __forceinline__ bool unit_of(int xcd, int slot, const GemmGrid& g, const int32_t* __restrict__ order, int& ui,
+                                        int& uj, int& z, int& local, int& xcd_units) {
+    z = 0;
+    if (order && g.zsplit == 1) {
+        const int per = g.count >> 3, rem = g.count & 7;
+        const int blocks = per + (xcd < rem ? 1 : 0);
+        xcd_units = 4 * blocks;
+        local = 0;
+        if (slot >= xcd_units) return false;
+        const int grp = slot / (4 * kRoundUnits), in = slot - grp * 4 * kRoundUnits;
+        const int gsz = min(kRoundUnits, blocks - grp * kRoundUnits);
+        const int q = in / gsz;
+        int ti, tj;
+        lin_to_tile(order[g.begin + xcd * per + min(xcd, rem) + grp * kRoundUnits + in - q * gsz], g.nti, g.ntj, ti, tj);
+        ui = 2 * ti + (q & 1);
+        uj = 2 * tj + (q >> 1);
+        return true;
+    }
+    const int units = order ? 4 * g.count : g.count, total = units * g.zsplit;
     const int per = total >> 3, rem = total & 7;
-    xcd_tiles = per + (xcd < rem ? 1 : 0);
-    const int unit = xcd * per + min(xcd, rem) + slot;
-    z = unit / tile_count;
-    lin = tile_begin + unit - z * tile_count;
-    lin_to_tile(order ? order[lin] : lin, nti, ntj, ti, tj);
+    xcd_units = per + (xcd < rem ? 1 : 0);
+    if (slot >= xcd_units) return false;
+    const int item = xcd * per + min(xcd, rem) + slot;
+    z = item / units;
+    local = item - z * units;
+    if (order) {
+        const int q = local / g.count;
+        int ti, tj;
+        lin_to_tile(order[g.begin + local - q * g.count], g.nti, g.ntj, ti, tj);
+        ui = 2 * ti + (q & 1);
+        uj = 2 * tj + (q >> 1);
+    } else {
+        lin_to_tile(g.begin + local, g.um, g.un, ui, uj);
+    }
+    return true;
 }
 
 // 64 lanes x 16 B from global memory into LDS: lane l's 16 bytes land at lds_addr + LDS_IMM + 16*l.
 // The LDS byte address travels in M0 (set by the scalar add).  The compiler does not see this as a
 // memory access, so completion is awaited with explicit s_waitcnt vmcnt(...) below.
-// The global address is a wave-uniform base (scalar registers) plus a per-lane byte offset
-// (lane position plus the k chunk's distance, loop-invariant), so stepping through the tiles
-// costs two scalar adds per K step.
+// The global address is a wave-uniform base (scalar registers) plus a per-lane byte offset.
 template <int LDS_IMM>
 __device__ __forceinline__ void dma16(const uint8_t* gbase, uint32_t lane_off, uint32_t lds_addr) {
     asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                  :: "s"(lds_addr), "v"(lane_off), "s"(gbase), "n"(LDS_IMM) : "memory", "scc");
 }
 
-// One dword per lane to a wave-uniform base (scalar register pair) plus a 32-bit per-lane byte offset.
+// 16 bytes per lane to a wave-uniform base (scalar register pair) plus a 32-bit per-lane byte offset.
 // Written as assembly so that the address stays in this form: left to itself the compiler builds a
-// 64-bit per-lane address for each of the several hundred stores of an epilogue, hoists them out of
-// the anti-diagonal loop and spills them.
+// 64-bit per-lane address for each of the stores of an epilogue, hoists them out of the loop over the groups
+// and spills them.
 // The s_nop covers the five wait states the hardware needs between a vector-ALU write of a scalar
 // register (a register-allocator reload with v_readlane, say) and a memory instruction that reads
 // it as its base: inside an asm block the compiler does not insert them itself, and a store issued
-// too early takes the stale register value as its address.
-__device__ __forceinline__ void store_lane_dword(void* uniform_base, uint32_t lane_byte_off, uint32_t data) {
-    asm volatile("s_nop 4\n\tglobal_store_dword %0, %1, %2"
+// too early takes the stale register value as its address.  The one behind it keeps the next instruction from
+// overwriting the data before the store has read all four registers.
+__device__ __forceinline__ void store_lane_16(void* uniform_base, uint32_t lane_byte_off, v4i data) {
+    asm volatile("s_nop 4\n\tglobal_store_dwordx4 %0, %1, %2\n\ts_nop 1"
                  :: "v"(lane_byte_off), "v"(data), "s"(uniform_base) : "memory");
 }
 
-// SPLIT: the launch splits the k range of its tiles over several workgroups (zsplit > 1)
-template <bool SPLIT>
-__global__ __launch_bounds__(256) void gemm_i8_kernel(const int8_t* __restrict__ As,
-                                                      const int8_t* __restrict__ Bs,
+template <int N>
+struct Int { static constexpr int v = N; };
+
+// The order of a step's work between its MFMAs: 0..3 fragments of the next A tile (first: the next step starts with
+// them), 10.. the step's NB further LDS reads, 20..23 transfers, 30..33 the streams move on, 34 and 35 the ring.
+constexpr int kOwnPieces = 14;
+template <int NB>
+constexpr int kPieces[kOwnPieces + NB] = {0, 1, 2, 20, 3, 21, 34, 22, 35, 23, 30, 31, 32, 33};
+template <>
+constexpr int kPieces<4>[kOwnPieces + 4] = {0, 1, 2, 20, 3, 10, 21, 11, 12, 22, 13, 34, 23, 35, 30, 31, 32, 33};
+template <>
+constexpr int kPieces<8>[kOwnPieces + 8] = {0, 1, 2, 20, 3, 10, 11, 21, 12, 13, 22, 14, 15, 23, 16, 17, 34, 35, 30, 31, 32, 33};
+
+// ATOMIC = false: 16x16x64 MFMAs; the sums are aggregated in registers and written as T / L, to the matrix planes
+// (part 0) or to the part's slot of the raw buffer (parts z > 0 of a k split).
+// ATOMIC = true: unaggregated sums are added into the unit's raw slot with integer atomics (exact and order-free; the
+// host zeroes the slots before and aggregates them after): as many parts as one likes in the same memory, for
+// outputs of few units.  32x32x32 MFMAs there: a half-wave then adds to 128 contiguous bytes instead of 64, and
+// such launches are bound by the atomics, not by power.
+//
+// A workgroup takes units slot, slot + stride, ... of its XCD's range (one only where the launch has a workgroup per
+// unit); the stream of tiles runs on into the next unit, so neither the first tiles' latency nor the drain
+// of the last sums is waited for.
+template <bool ATOMIC>
+__global__ __launch_bounds__(256) void gemm_i8_kernel(const int8_t* __restrict__ As, const int8_t* __restrict__ Bs,
                                                       int32_t* __restrict__ T, int8_t* __restrict__ L,
-                                                      int32_t* __restrict__ raw, int raw_slots,
-                                                      int64_t mp, int64_t np, int64_t kp, int s_cap,
-                                                      Record* rec, int full_chip, int zsplit,
-                                                      int tile_begin, int tile_count,
+                                                      int32_t* __restrict__ raw, int raw_units, int64_t mp, int64_t np,
+                                                      int64_t kp, int s_cap, Record* rec, GemmGrid g,
                                                       const int32_t* __restrict__ tile_S) {
+    constexpr int D = ATOMIC ? kDiagAtomic : kDiag;
+    constexpr int TAIL = D - 1;          // last steps of a 64 of k: D-1 .. 1 accumulator sets
     extern __shared__ __align__(16) uint8_t lds[];
     if (rec->res.fallback) return;
     const int S_all = rec->res.slices_used;
     // k-range one int32 accumulator can take with S slices (S*kblk digit products of at most 2^14);
-    // the k-blocks are those of the call's largest slice count, whatever this tile's own count is
+    // the k-blocks are those of the call's largest slice count, whatever this block's own count is
     const int64_t kblk = k_block_length(S_all);
-    const int nkb = int((kp + kblk - 1) / kblk);
+    // per-block mode: the table of slice counts is followed by the order the blocks are dealt in
+    const int32_t* order = tile_S ? tile_S + g.nti * g.ntj : nullptr;
 
-    int ti, tj, z, xcd, slot, xcd_tiles, unit_tile;   // unit_tile: this tile's position in the tile order
-    // per-tile mode: the table of slice counts is followed by the order the tiles are dealt in
-    const int32_t* order = tile_S ? tile_S + int(mp / kBM) * int(np / kBN) : nullptr;
-    tile_of(blockIdx.x, int(mp / kBM), int(np / kBN), tile_begin, tile_count, zsplit, order, ti, tj, z, xcd, slot,
-            xcd_tiles, unit_tile);
-    // slice count of this tile of C: its own (per-tile mode: the first S digit planes of the operands
-    // and the pairs s + t <= S - 1) or the call's
-    const int S = tile_S ? min(tile_S[tj * int(mp / kBM) + ti], S_all) : S_all;
-
-    // This workgroup's share of the K steps: part z of zsplit equal parts of the whole k range (one
-    // part = everything when the call has enough tiles to fill the chip).  Parts of the same k-block
-    // add their unaggregated anti-diagonal sums into the tile's slot of the raw buffer with integer
-    // atomics: exact and order-free.  The host zeroes the slots before such a launch and aggregates
-    // them afterwards (aggregate_raw_kernel) into the same T / L form the unsplit tiles write.
-    const int kt_total = int(kp / kBK);
-    const int kt_first = int(int64_t(kt_total) * z / zsplit);
-    const int kt_end = int(int64_t(kt_total) * (z + 1) / zsplit);
-    const int kt_per_block = int(kblk / kBK);
-    const int kb_first = kt_first / kt_per_block, kb_last = (kt_end - 1) / kt_per_block;
+    const int xcd = int(blockIdx.x) & 7, stride = int(gridDim.x) >> 3;
+    int slot = int(blockIdx.x) >> 3;
+    int ui, uj, z, local, xcd_units;
+    if (!unit_of(xcd, slot, g, order, ui, uj, z, local, xcd_units)) return;
 
     // Keep the workgroups that share panels in step.  An XCD runs 32 workgroups at a time (one
-    // per CU) and its tiles are ordered so that each such round is one 4x8 block.  The workgroups
-    // of a round wait for each other at the start of the tile and, when k is long, after every
-    // anti-diagonal, because workgroups that have drifted apart never fall back into step by
-    // themselves and then miss in L2 what their neighbours loaded (measured at 16384^3 without
-    // this: hit rate 49 % instead of 81 %, 10 % more time; at k = 8192 the start of the tile is
-    // enough and the extra waits would cost 1 %).  Arrival number q of a workgroup of round r waits
-    // for 32*r*steps + (q+1)*members arrivals on the XCD's counter (earlier rounds are full rounds).
-    const int sync_steps = (kp >= kMidSyncMinK && !SPLIT) ? nkb * S_all : 1;
-    const int sync_round = slot / kRoundTiles;
-    const int sync_members = min(kRoundTiles, xcd_tiles - sync_round * kRoundTiles);
-    const int sync_base = sync_round * kRoundTiles * sync_steps;
-    const bool sync_on = full_chip && xcd_tiles > kRoundTiles && sync_members > 1;
+    // per CU) and its units are ordered so that each such round is one 4x8 block.  Where a unit is long, the
+    // workgroups of a round wait for each other at its start and, when k is very long, after every
+    // group of anti-diagonals, because workgroups that have drifted apart never fall back into step by
+    // themselves and then miss in L2 what their neighbours loaded (measured: 2 % at 8192^3, 6 % at 16384^3).
+    // Arrival number q of a workgroup of round r waits for 32*r*steps + (q+1)*members arrivals on the XCD's
+    // counter (earlier rounds are full).  The wait also drains the wave's stores, so short units go without.
+    const int sync_steps = kp >= kMidSyncMinK ? int((kp + kblk - 1) / kblk) * ((S_all + D - 1) / D) : 1;
+    const bool sync_on = !ATOMIC && g.full_chip && g.zsplit == 1 && xcd_units > kRoundUnits && kp >= kSyncMinK &&
+                         (stride == kRoundUnits || stride >= xcd_units);
     int sync_q = 0;
-    bool sync_wait = true;
-    if (sync_on) sync_wait = round_sync(&rec->tile_sync[xcd], sync_base + (++sync_q) * sync_members, sync_wait);
+    bool sync_wait = true;               // thread 0: stop waiting once the others were not met in time
+    auto arrive = [&]() {
+        const int round = slot / kRoundUnits;
+        const int members = min(kRoundUnits, xcd_units - round * kRoundUnits);
+        ++sync_q;
+        round_sync(&rec->tile_sync[xcd], round * kRoundUnits * sync_steps + sync_q * members, sync_wait);
+    };
+    // a quadrant of an edge block that holds padding only: nothing to do but the arrivals it owes its round
+    auto skip_padding = [&]() -> bool {
+        while (ui >= g.um || uj >= g.un) {
+            if (sync_on && threadIdx.x == 0) atomicAdd(&rec->tile_sync[xcd], sync_steps);
+            slot += stride;
+            if (!unit_of(xcd, slot, g, order, ui, uj, z, local, xcd_units)) return false;
+        }
+        return true;
+    };
+    if (!skip_padding()) return;
+    // slice count of a unit: its block's own (per-block mode: the first S digit planes of the operands
+    // and the pairs s + t <= S - 1) or the call's
+    auto slices_of = [&](int i, int j) -> int { return tile_S ? min(tile_S[(j >> 1) * g.nti + (i >> 1)], S_all) : S_all; };
+    int S = slices_of(ui, uj);
 
-    const int64_t i0 = int64_t(ti) * kBM, j0 = int64_t(tj) * kBN;
+    // this workgroup's share of k, in steps of 64: part z of zsplit equal parts of the whole range
+    const int kt_total = int(kp / kBK);
+    const int kt_first = int(int64_t(kt_total) * z / g.zsplit);
+    const int kt_end = int(int64_t(kt_total) * (z + 1) / g.zsplit);
+    const int kt_per_block = int(kblk / kBK);
+    const int kb_first = kt_first / kt_per_block, kb_last = (kt_end - 1) / kt_per_block;
+    // 64s of k [kt_lo(kb), kt_lo(kb) + kt_count(kb)) of k-block kb belong to this workgroup
+    auto kt_lo = [&](int kb) -> int { return max(kb * kt_per_block, kt_first); };
+    auto kt_count = [&](int kb) -> int { return min((kb + 1) * kt_per_block, kt_end) - kt_lo(kb); };
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wi = wave & 1, wj = wave >> 1;
 
-    v16i acc[4][4];   // [fj][fi]
-    const v16i zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = zero;
-
-    // K steps [kt_lo(kb), kt_lo(kb) + kt_count(kb)) of k-block kb belong to this workgroup
-    auto kt_lo = [&](int kb) -> int { return max(kb * kt_per_block, kt_first); };
-    auto kt_count = [&](int kb) -> int { return min((kb + 1) * kt_per_block, kt_end) - kt_lo(kb); };
-
-    // (nkb_, nd, ns, nkt) walks the (k-block, anti-diagonal, pair, K step) sequence ahead of the
-    // compute, so the prefetch runs across pair and anti-diagonal boundaries without a bubble.
-    // After the last tile it stays put: the surplus transfers land in stages nobody reads again.
-    int nkb_ = kb_first, nd = S - 1, ns = 0, nkt = 0;
-    int nxt_ktc = kt_count(kb_first);
-    int issue_stage = 0;
-    const uint32_t lds_base = uint32_t(uintptr_t((__attribute__((address_space(3))) uint8_t*)lds));
-    const uint8_t* gA = reinterpret_cast<const uint8_t*>(As) + (i0 + wave * 64) * 16;   // wave-uniform
-    const uint8_t* gB = reinterpret_cast<const uint8_t*>(Bs) + (j0 + wave * 64) * 16;
+    // ---- the streams of tiles -----------------------------------------------------------------
+    // Entry e of the A (B) stream: for each unit, k-block, group and 64 of k, slice s = 0..d_hi of A (t = d_hi..0 of B).
+    // Item x is entry x of A and entry x+2 of B; it goes to LDS stage x mod 10.  Wave w fetches k chunk w of both
+    // tiles: four transfers of 1 KB.
+    struct Stream {
+        const uint8_t* p;                // next entry
+        int64_t wrap;                    // from the last slice of a 64 of k to the first of the next
+        int r, n;                        // entries left of this 64 of k; entries per 64 of k
+        int c;                           // 64s of k left in this group of this k-block
+        int kb;
+        bool ahead;                      // already on the next unit
+    };
+    const int64_t planeA = kp * mp, planeB = kp * np;                     // bytes per slice plane
+    const int64_t stepA = int64_t(kBK) * mp, stepB = int64_t(kBK) * np;   // bytes per 64 of k
+    auto base_of = [&](const int8_t* X, int64_t rows, int unit) -> const uint8_t* {
+        return reinterpret_cast<const uint8_t*>(X) + (int64_t(wave) * rows + int64_t(unit) * kUnit) * 16;
+    };
+    bool has_next = false;               // the unit after this one, for the streams to run on into
+    int nui = 0, nuj = 0, nS = 0, nslot = 0;
+    auto find_next = [&]() {
+        const int cui = ui, cuj = uj, cslot = slot;
+        slot += stride;
+        has_next = unit_of(xcd, slot, g, order, ui, uj, z, local, xcd_units) && skip_padding();
+        nui = ui; nuj = uj; nslot = slot;
+        if (has_next) nS = slices_of(nui, nuj);
+        ui = cui; uj = cuj; slot = cslot;
+    };
+    auto group_start = [&](Stream& s, bool is_b) {       // s.n and s.kb are set
+        s.r = s.n;
+        s.c = kt_count(s.kb);
+        const int64_t kt = kt_lo(s.kb);
+        if (is_b) {
+            s.p = base_of(Bs, np, s.ahead ? nuj : uj) + int64_t(s.n - 1) * planeB + kt * stepB;
+            s.wrap = stepB + int64_t(s.n - 1) * planeB;
+        } else {
+            s.p = base_of(As, mp, s.ahead ? nui : ui) + kt * stepA;
+            s.wrap = stepA - int64_t(s.n - 1) * planeA;
+        }
+    };
+    // past the last entry of a group: the next group, k-block or unit; at the very end the last group
+    // once more (surplus entries that land in stages nobody reads)
+    auto group_end = [&](Stream& s, bool is_b) {
+        if (s.n > D) {
+            s.n -= D;
+        } else if (s.kb < kb_last) {
+            ++s.kb;
+            s.n = s.ahead ? nS : S;
+        } else if (has_next && !s.ahead) {
+            s.ahead = true;
+            s.kb = kb_first;
+            s.n = nS;
+        } else {
+            s.n = (s.ahead ? nS : S) % D == 0 ? D : (s.ahead ? nS : S) % D;
+        }
+        group_start(s, is_b);
+    };
+    Stream sa, sb;
+    const int64_t downB = -planeB;
+    // The next entry: `wrap` bytes on after the last slice of a 64 of k, else a plane on (A) or back (B).  Without a
+    // branch but for the end of a group, and in assembly so that it stays at eight scalar instructions: they fit the
+    // gaps between the matrix instructions, while a taken branch leaves the matrix unit idle for tens of cycles.
+    int64_t by = 0;
+    auto next_by = [&](Stream& s, bool is_b) {
+        asm volatile("s_sub_u32 %[r], %[r], 1\n\ts_cmp_eq_u32 %[r], 0\n\ts_cselect_b64 %[by], %[wrap], %[plane]\n\t"
+                     "s_cselect_b32 %[r], %[n], %[r]\n\ts_subb_u32 %[c], %[c], 0"
+                     : [r] "+s"(s.r), [c] "+s"(s.c), [by] "=&s"(by)
+                     : [wrap] "s"(s.wrap), [plane] "s"(is_b ? downB : planeA), [n] "s"(s.n) : "scc");
+    };
+    auto next_check = [&]() {            // one branch for both streams
+        if (__builtin_expect(min(uint32_t(sa.c), uint32_t(sb.c)) == 0, 0)) {
+            if (sa.c == 0) group_end(sa, false);
+            if (sb.c == 0) group_end(sb, true);
+        }
+    };
     const uint32_t lane_off = uint32_t(lane) * 16;
-    // per-lane byte offsets of the four k chunks of a tile (chunk q is q*rows*16 bytes further on)
-    uint32_t offA[4], offB[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        offA[q] = lane_off + uint32_t(q) * uint32_t(mp) * 16u;
-        offB[q] = lane_off + uint32_t(q) * uint32_t(np) * 16u;
-    }
-    const int64_t planeA = kp * mp, planeB = kp * np;   // bytes per slice plane
+    const uint32_t lds_wave = uint32_t(uintptr_t((__attribute__((address_space(3))) uint8_t*)lds)) + uint32_t(wave) * (kUnit * 16);
+    // transfer x of an item into the stage at byte `stage` of the ring
+    auto dma = [&](uint32_t stage, int x) {
+        const uint32_t la = lds_wave + stage;
+        if (x == 0) dma16<0>(sa.p, lane_off, la);
+        else if (x == 1) dma16<kOperandBytes>(sb.p, lane_off, la);
+        else if (x == 2) dma16<1024>(sa.p, lane_off + 1024, la);
+        else dma16<kOperandBytes + 1024>(sb.p, lane_off + 1024, la);
+    };
 
-    // addresses of the next tile to fetch (8 transfers per wave: 4 k chunks of A, 4 of B).  The
-    // pointers advance by one K step per tile; only when the pair changes are they recomputed from
-    // the iterator (once per k-block length, outside the common path).
-    const uint8_t* pa = gA + int64_t(kt_first) * (kBK / 16) * mp * 16;
-    const uint8_t* pb = gB + int64_t(S - 1) * (kp * np) + int64_t(kt_first) * (kBK / 16) * np * 16;   // pair (0, S-1)
-    const int64_t stepA = int64_t(kBK) * mp, stepB = int64_t(kBK) * np;   // bytes per K step
-    uint32_t la;
-#define OZ_TILE_ADDR()                                                                           \
-    { la = lds_base + issue_stage * kStageBytes + wave * 1024; }
-// transfer number x (0..7) of the tile addressed by pa / pb / la
-#define OZ_DMA(x)                                                                                \
-    {                                                                                            \
-        switch (x) {                                                                             \
-            case 0: dma16<0 * (kBM * 16)>(pa, offA[0], la); break;                                   \
-            case 1: dma16<kBM * kBK + 0 * (kBN * 16)>(pb, offB[0], la); break;                       \
-            case 2: dma16<1 * (kBM * 16)>(pa, offA[1], la); break;                                   \
-            case 3: dma16<kBM * kBK + 1 * (kBN * 16)>(pb, offB[1], la); break;                       \
-            case 4: dma16<2 * (kBM * 16)>(pa, offA[2], la); break;                                   \
-            case 5: dma16<kBM * kBK + 2 * (kBN * 16)>(pb, offB[2], la); break;                       \
-            case 6: dma16<3 * (kBM * 16)>(pa, offA[3], la); break;                                   \
-            default: dma16<kBM * kBK + 3 * (kBN * 16)>(pb, offB[3], la); break;                      \
-        }                                                                                        \
-    }
-#define OZ_TILE_ADVANCE()                                                                        \
-    {                                                                                            \
-        issue_stage = (issue_stage + 1) & (kStages - 1);                                         \
-        if (++nkt == nxt_ktc) {                                                                  \
-            nkt = 0;                                                                             \
-            if (++ns > nd) {                                                                     \
-                ns = 0;                                                                          \
-                if (--nd < 0) {                                                                  \
-                    nd = S - 1;                                                                  \
-                    if (++nkb_ > kb_last) nkb_ = kb_last;                                        \
-                    nxt_ktc = kt_count(nkb_);                                                    \
-                }                                                                                \
-            }                                                                                    \
-            const int64_t kc = int64_t(kt_lo(nkb_)) * (kBK / 16);                                \
-            pa = gA + int64_t(ns) * planeA + kc * mp * 16;                                       \
-            pb = gB + int64_t(nd - ns) * planeB + kc * np * 16;                                  \
-        } else {                                                                                 \
-            pa += stepA;                                                                         \
-            pb += stepB;                                                                         \
-        }                                                                                        \
-    }
-#define OZ_ISSUE_TILE()                                                                          \
-    {                                                                                            \
-        OZ_TILE_ADDR();                                                                          \
-        _Pragma("unroll") for (int x = 0; x < 8; ++x) OZ_DMA(x);                                 \
-        OZ_TILE_ADVANCE();                                                                       \
-    }
-// operand fragment f of K sub-step kk (0 or 1) of the tile in LDS stage `stage`
-#define OZ_READ_A(dst, stage, kk, f)                                                             \
-    dst[f] = as_v4i((reinterpret_cast<const uint4*>(lds + (stage) * kStageBytes) + wi * 128 +    \
-                     (lane & 31) + ((kk) * 2 + (lane >> 5)) * kBM)[(f) * 32])
-#define OZ_READ_B(dst, stage, kk, f)                                                             \
-    dst[f] = as_v4i((reinterpret_cast<const uint4*>(lds + (stage) * kStageBytes + kBM * kBK) +   \
-                     wj * 128 + (lane & 31) + ((kk) * 2 + (lane >> 5)) * kBN)[(f) * 32])
-#define OZ_READ_FRAGS(dstA, dstB, stage, kk)                                                     \
-    _Pragma("unroll") for (int f = 0; f < 4; ++f) {                                              \
-        OZ_READ_A(dstA, stage, kk, f);                                                           \
-        OZ_READ_B(dstB, stage, kk, f);                                                           \
-    }
-#define OZ_MFMA(srcA, srcB, fj, fi)                                                              \
-    acc[fj][fi] = __builtin_amdgcn_mfma_i32_32x32x32_i8(srcB[fj], srcA[fi], acc[fj][fi], 0, 0, 0)
+    // ---- fragments ------------------------------------------------------------------------------
+    // 16x16x64: fragment f = rows 16f..16f+15, all 64 of k.  32x32x32: f = 2 * (rows 32(f/2)..) + (half of k).
+    const uint32_t rd_lane = ATOMIC ? uint32_t(lane >> 5) * (kUnit * 16) + uint32_t(lane & 31) * 16
+                                    : uint32_t(lane >> 4) * (kUnit * 16) + uint32_t(lane & 15) * 16;
+    const uint32_t rdA = rd_lane + uint32_t(wi) * 1024, rdB = rd_lane + uint32_t(wj) * 1024 + kOperandBytes;
+    constexpr int kFragImm[4] = {0, ATOMIC ? 4096 : 256, 512, ATOMIC ? 4608 : 768};
+    auto frag = [&](uint32_t off) -> v4i { return *reinterpret_cast<const v4i*>(lds + off); };
 
-    // prologue: three tiles in flight, then wait for the first, publish it, issue the fourth
-    OZ_ISSUE_TILE();
-    OZ_ISSUE_TILE();
-    OZ_ISSUE_TILE();
-    asm volatile("s_waitcnt vmcnt(16)\n\ts_barrier" ::: "memory");
-    OZ_TILE_ADDR();
+    v4i fa[3][4], fb[4][4];              // A: two in turn and one for the last step of a 64 of k; B: [slot][f]
+    constexpr int NT = ATOMIC ? 2 : 4;   // MFMA tiles per wave and direction
+    typedef typename std::conditional<ATOMIC, v16i, v4i>::type acc_t;
+    acc_t acc[D][NT][NT];                // [j][tj][ti]
+    // Cleared by matrix instructions with zero operands: written by the vector ALU, an accumulator would be kept in an
+    // ordinary vector register by the register allocator and moved in and out in every step.
+    const v4i zero4 = {0, 0, 0, 0};
+    auto clear = [&](int from) {
 #pragma unroll
-    for (int x = 0; x < 8; ++x) OZ_DMA(x);   // the iterator moves on in the first half of the loop body
-    v4i fa0[4], fb0[4], fa1[4], fb1[4];
-    int stage = 0;
-    OZ_READ_FRAGS(fa0, fb0, stage, 0);
-
-    for (int kb = kb_first; kb <= kb_last; ++kb) {
-        const int ktc = kt_count(kb);
-        for (int d = S - 1; d >= 0; --d) {
-            const int n_iter = (d + 1) * ktc;
-            for (int it = 0; it < n_iter; ++it) {
-                // invariant here: transfers of the next three tiles are in flight (24 per wave);
-                // fragments of sub-step 0 of the current tile are in fa0/fb0
-                // first half: MFMAs of sub-step 0; the LDS reads of sub-step 1 ride along
-                // first half: MFMAs of sub-step 0 (16); one LDS read of sub-step 1 after each of the
-                // first eight, so that all have returned well before the barrier
+        for (int j = 0; j < D; ++j)
 #pragma unroll
-                for (int q = 0; q < 12; ++q) {
-                    OZ_MFMA(fa0, fb0, q >> 2, q & 3);
-                    __builtin_amdgcn_sched_barrier(0);
-                    if (q < 8) {
-                        if (q & 1) { OZ_READ_B(fb1, stage, 1, q >> 1); } else { OZ_READ_A(fa1, stage, 1, q >> 1); }
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                    if (q == 9) {   // a gap without memory work: move the iterator past the tile issued last
-                        OZ_TILE_ADVANCE();
-                        __builtin_amdgcn_sched_barrier(0);
+            for (int a = 0; a < NT; ++a)
+#pragma unroll
+                for (int b = 0; b < NT; ++b) {
+                    if (j < from) continue;
+                    if constexpr (ATOMIC) {
+                        const v16i none = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+                        acc[j][a][b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(zero4, zero4, none, 0, 0, 0);
+                    } else {
+                        acc[j][a][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(zero4, zero4, zero4, 0, 0, 0);
                     }
                 }
-                // next tile landed (own transfers), every LDS read of this tile returned; after the
-                // barrier that holds for all waves, so this stage may be overwritten.  The last four
-                // MFMAs of the first half cover the barrier.
-                asm volatile("s_waitcnt vmcnt(16) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-                const int next_stage = (stage + 1) & (kStages - 1);
-                OZ_TILE_ADDR();
+    };
+    clear(0);
+    constexpr int kSetMfma = ATOMIC ? 8 : 16;
+    // MFMA number q of accumulator set j; consecutive ones share an operand
+    auto mfma = [&](int j, const v4i (&xb)[4], const v4i (&xa)[4], int q) {
+        if constexpr (ATOMIC) {
+            const int ks = q >> 2, tj = (q >> 1) & 1, ti = tj ? 1 - (q & 1) : (q & 1);
+            acc[j][tj][ti] = __builtin_amdgcn_mfma_i32_32x32x32_i8(xb[2 * tj + ks], xa[2 * ti + ks], acc[j][tj][ti], 0, 0, 0);
+        } else {
+            const int tj = q >> 2, ti = (tj & 1) ? 3 - (q & 3) : (q & 3);
+            acc[j][tj][ti] = __builtin_amdgcn_mfma_i32_16x16x64_i8(xb[tj], xa[ti], acc[j][tj][ti], 0, 0, 0);
+        }
+    };
+
+    // ---- one step ---------------------------------------------------------------------------------
+    // Step a multiplies entry a of A with entries a .. a+sets-1 of B.  Before it, items up to a+2 have landed, and no wave
+    // reads item a-3 any more, so item a+7 may overwrite that stage.
+    //
+    // Register slots.  Within a 64 of k with n entries, entry s of B lies in slot (s + o) mod 4 with o such that the
+    // last TAIL steps always start at slot 0: o = (TAIL - n) mod 4.  So the tail is straight code, and the steps
+    // before it (all with D sets, step u serving slots u, u+1, .. mod 4) are a loop unrolled by four behind up to
+    // three single ones: a few branches per 64 of k.  (With a test per accumulator set, seven branches a step kept
+    // the matrix unit idle a quarter of the time: 16x16x64 leaves 16 cycles to fetch what comes next.)
+    //   step u        reads entry a+3 of B into slot u+3, which step u-1 gave up
+    //   tail 0        reads no B
+    //   tail TAIL-2   reads what the next 64 of k starts with in the two slots that are free by then
+    //   tail TAIL-1   the same for the slot that tail TAIL-2 gave up
+    //   next step     the same for the last one
+    // Which entries those are depends on the next o: entry j of the next 64 of k goes to slot (j + o) mod 4, it lies in
+    // item c1 + j - 2 when c1 is the first step of that 64 (j = 3 is read again by that step itself: harmless).
+    //
+    // The memory work is spread over the MFMAs: four waves' LDS reads take 32 cycles, their transfers 64.
+    uint32_t cur = 0, nxt = 0, put = 0;  // ring offsets of the stages of items a, a+1 and a+7
+    uint32_t oa = 0, ob = 0;             // where this lane reads A and B of item a+1 (computed in the step before)
+    auto ring = [&](uint32_t off) -> uint32_t { return off >= uint32_t(kRingBytes) ? off - kRingBytes : off; };
+    uint32_t pre_base = 0;               // ring offset of item c1 - 2
+    int o_next = 0;
+    auto preload = [&](int sl, int f) {  // fragment f of what slot `sl` starts the next 64 of k with
+        const uint32_t st = ring(pre_base + uint32_t((sl - o_next) & 3) * kStageBytes);
+        fb[sl][f] = frag(rdB + st + kFragImm[f]);
+    };
+    // SETS accumulator sets, first B slot SLOT, A in fa[AR], next A into fa[AW]; B(x) = x-th of NB further pieces
+    auto step = [&](auto SETS, auto SLOT, auto AR, auto AW, auto NB, auto WAITLDS, auto&& more) {
+        constexpr int sets = decltype(SETS)::v, first = decltype(SLOT)::v, ar = decltype(AR)::v, aw = decltype(AW)::v;
+        uint32_t oa_next = 0, ob_next = 0;
+        constexpr int nb = decltype(NB)::v, pieces = kOwnPieces + nb, gaps = sets * kSetMfma;
 #pragma unroll
-                for (int q = 12; q < 16; ++q) {
-                    OZ_MFMA(fa0, fb0, q >> 2, q & 3);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                // second half: MFMAs of sub-step 1; after each one either an LDS read of the next
-                // tile's sub-step 0 or a transfer of the tile three stages ahead
+        for (int j = 0; j < sets; ++j)
 #pragma unroll
-                for (int g = 0; g < 8; ++g) {
-                    OZ_MFMA(fa1, fb1, g >> 1, (g & 1) * 2);
-                    __builtin_amdgcn_sched_barrier(0);
-                    if (g & 1) { OZ_READ_B(fb0, next_stage, 0, g >> 1); } else { OZ_READ_A(fa0, next_stage, 0, g >> 1); }
-                    __builtin_amdgcn_sched_barrier(0);
-                    OZ_MFMA(fa1, fb1, g >> 1, (g & 1) * 2 + 1);
-                    __builtin_amdgcn_sched_barrier(0);
-                    OZ_DMA(g);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                stage = next_stage;
+            for (int q = 0; q < kSetMfma; ++q) {
+                mfma(j, fb[(first + j) & 3], fa[ar], q);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int x = 0; x < pieces; ++x)
+                    if (x * gaps / pieces == j * kSetMfma + q) {
+                        const int w = kPieces<nb>[x];
+                        if (w < 10) fa[aw][w] = frag(oa + kFragImm[w]);
+                        else if (w < 20) more(w - 10);
+                        else if (w < 30) dma(put, w - 20);
+                        else if (w == 30) next_by(sa, false);
+                        else if (w == 31) sa.p += by;
+                        else if (w == 32) next_by(sb, true);
+                        else if (w == 33) { sb.p += by; next_check(); }
+                        else if (w == 34) { asm volatile("" : "+s"(cur)); cur = ring(cur + kStageBytes); nxt = ring(cur + kStageBytes); }
+                        else { asm volatile("" : "+s"(nxt)); oa_next = rdA + nxt; ob_next = rdB + nxt; }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
             }
+        put = ring(put + kStageBytes);
+        oa = oa_next;
+        ob = ob_next;
+        // The wait as a builtin: the compiler then knows which LDS reads have returned.
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0x4070 | (decltype(WAITLDS)::v ? 0x0000 : 0x0F00));       // vmcnt(16), lgkmcnt(0) or none
+        asm volatile("s_barrier" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto none = [](int) {};
+    auto head = [&](auto UU) {           // step u: all D sets
+        constexpr int u = decltype(UU)::v;
+        step(Int<D>{}, Int<u>{}, Int<(u & 1)>{}, Int<((u + 1) & 1)>{}, Int<4>{}, Int<1>{},
+             [&](int x) { fb[(u + 3) & 3][x] = frag(ob + kFragImm[x]); });
+    };
 
-            // anti-diagonal d of k-block kb is complete.
-            // result register r of MFMA tile (fj, fi): j = fj*32 + 8*(r/4) + 4*(lane/32) + r%4,
-            // i = fi*32 + lane%32.  Every address below is a wave-uniform pointer (scalar arithmetic)
-            // plus one per-lane 32-bit element offset that is the same for all stores of a kind.
-            // the row stride as a value the compiler cannot trace out of this iteration: otherwise the row
-            // addresses of all stores (loop-invariant offsets) are hoisted out of the anti-diagonal loop
-            // and kept alive, several hundred registers' worth, across the MFMA loop
-            int64_t mp_here = mp;
-            asm volatile("" : "+s"(mp_here));
-            if (SPLIT) {
-                // this workgroup holds a part of the k range: add the partial sums into the tile's raw slot
-                int32_t* dst = raw + ((int64_t(kb) * s_cap + d) * raw_slots + (unit_tile - tile_begin)) * (kBM * kBN) +
-                               (wj * 128) * kBM + wi * 128;
-                const uint32_t lane_raw = uint32_t(4 * (lane >> 5)) * kBM + uint32_t(lane & 31);
+    // prologue: the first two entries of B, seven items; what the first step starts with; then on
+    sa = Stream{nullptr, 0, 0, S, 0, kb_first, false};
+    sb = sa;
+    if (g.persistent) find_next();
+    group_start(sa, false);
+    group_start(sb, true);
+    if (sync_on) arrive();
 #pragma unroll
-                for (int fj = 0; fj < 4; ++fj)
+    for (int e = 0; e < 2; ++e) {        // into stages 8 and 9, where items -2 and -1 would lie
+        dma(uint32_t(8 + e) * kStageBytes, 1);
+        dma(uint32_t(8 + e) * kStageBytes, 3);
+        next_by(sb, true);
+        sb.p += by;
+        next_check();
+    }
+    for (int x = 0; x < 7; ++x) {
+        const uint32_t st = uint32_t(x) * kStageBytes;
+        dma(st, 0); dma(st, 1); dma(st, 2); dma(st, 3);
+        next_by(sa, false);
+        sa.p += by;
+        next_by(sb, true);
+        sb.p += by;
+        next_check();
+    }
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x4070);          // vmcnt(16): items up to 2 have landed
+    asm volatile("s_barrier" ::: "memory");
+    pre_base = uint32_t(8) * kStageBytes;
+    o_next = (TAIL - S) & 3;
 #pragma unroll
-                    for (int fi = 0; fi < 4; ++fi) {
+    for (int x = 0; x < 4; ++x) {
+        fa[0][x] = frag(rdA + kFragImm[x]);
 #pragma unroll
-                        for (int r = 0; r < 16; ++r)
-                            atomicAdd(dst + ((fj * 32 + 8 * (r >> 2) + (r & 3)) * kBM + fi * 32) + lane_raw, acc[fj][fi][r]);
-                        acc[fj][fi] = zero;
-                    }
-            } else if (d > 0) {
-                // balanced digit out (the low byte of T is its two's-complement form), carry stays: four
-                // consecutive j of one i make a dword, so the lanes of a half-wave write 128 contiguous bytes
-                uint32_t* dst = reinterpret_cast<uint32_t*>(L) +
-                                ((int64_t(kb) * (s_cap - 1) + (d - 1)) * (np / 4) + (j0 + wj * 128) / 4) * mp + i0 + wi * 128;
-                const uint32_t lane_L = (uint32_t(lane >> 5) * uint32_t(mp) + uint32_t(lane & 31)) * 4u;   // bytes
-                const v4i zero4 = {0, 0, 0, 0};
+        for (int sl = 0; sl < 4; ++sl) preload(sl, x);
+    }
+    nxt = kStageBytes;
+    put = 7 * kStageBytes;
+    oa = rdA + nxt;
+    ob = rdB + nxt;
+
+    int kb = kb_first, d_hi = S - 1;
+    for (;;) {
+        // ---- group d_hi of k-block kb of unit (ui, uj) ----
+        const int n = d_hi + 1, nd = min(D, n), heads = n - TAIL;
+        const int o = (TAIL - n) & 3;
+        const bool last = d_hi < D && kb == kb_last;             // of the unit
+        const int n_after = d_hi >= D ? n - D : (kb < kb_last ? S : nS);      // entries of the next group's 64s of k
+        const int o_after = (TAIL - n_after) & 3;
+        for (int c = kt_count(kb); c > 0; --c) {
+            // the slot that the last tail step gave up, and the A tile where a first step that is not step 0 expects it
 #pragma unroll
-                for (int fj = 0; fj < 4; ++fj)
+            for (int x = 0; x < 4; ++x) preload((D - 2) & 3, x);
+            if (o != 0) {
 #pragma unroll
-                    for (int fi = 0; fi < 4; ++fi) {
-                        const v16i t = acc[fj][fi];
-                        v16i carry;
-#pragma unroll
-                        for (int rq = 0; rq < 4; ++rq) {
-                            const uint32_t w = (uint32_t(t[4 * rq]) & 255u) | ((uint32_t(t[4 * rq + 1]) & 255u) << 8) |
-                                               ((uint32_t(t[4 * rq + 2]) & 255u) << 16) | (uint32_t(t[4 * rq + 3]) << 24);
-                            store_lane_dword(dst + (int64_t(fj * 8 + 2 * rq) * mp_here + fi * 32), lane_L, w);
-                        }
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) carry[r] = (t[r] + 128) >> 8;
-                        // The carries go back into the accumulator tile as the result of a matrix instruction
-                        // with zero operands (0*0 + carry).  Written by the vector ALU instead, the tile
-                        // would be kept in the ordinary vector registers by the register allocator, and
-                        // sixteen such tiles do not fit there beside the loop's own registers.
-                        acc[fj][fi] = __builtin_amdgcn_mfma_i32_32x32x32_i8(zero4, zero4, carry, 0, 0, 0);
-                    }
+                for (int x = 0; x < 4; ++x) {
+                    fa[1][x] = fa[0][x];
+                    fa[2][x] = fa[0][x];
+                }
+            }
+            // a first round of the loop that starts at step o
+            for (int h = -o; h < heads; h += 4) {
+                if (__builtin_expect(h >= 0, 1)) head(Int<0>{});
+                if (__builtin_expect(h >= -1, 1)) head(Int<1>{});
+                if (__builtin_expect(h >= -2, 1)) head(Int<2>{});
+                head(Int<3>{});
+            }
+            o_next = c == 1 ? o_after : o;
+            if constexpr (D > 3) {
+                if (__builtin_expect(n > 2, 1)) step(Int<3>{}, Int<0>{}, Int<0>{}, Int<1>{}, Int<0>{}, Int<1>{}, none);
+            }
+            if (__builtin_expect(n > 1, 1)) {
+                pre_base = cur;          // this is step c1 - 2
+                step(Int<2>{}, Int<D - 3>{}, Int<(D - 3)>{}, Int<2>{}, Int<8>{}, Int<0>{},
+                     [&](int x) { preload(x < 4 ? (D & 3) : ((D - 1) & 3), x & 3); });
             } else {
-                // the leading word; the next k-block starts from zero
-                int32_t* dst = T + (int64_t(kb) * np + j0 + wj * 128) * mp + i0 + wi * 128;
-                const uint32_t lane_T = (uint32_t(4 * (lane >> 5)) * uint32_t(mp) + uint32_t(lane & 31)) * 4u;   // bytes
+                pre_base = cur >= uint32_t(kStageBytes) ? cur - kStageBytes : cur + (kRingBytes - kStageBytes);
 #pragma unroll
-                for (int fj = 0; fj < 4; ++fj)
-#pragma unroll
-                    for (int fi = 0; fi < 4; ++fi) {
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) {
-                            store_lane_dword(dst + (int64_t(fj * 32 + 8 * (r >> 2) + (r & 3)) * mp_here + fi * 32), lane_T,
-                                             uint32_t(acc[fj][fi][r]));
-                        }
-                        acc[fj][fi] = zero;
-                    }
+                for (int x = 0; x < 4; ++x) {
+                    preload(D & 3, x);
+                    preload((D - 1) & 3, x);
+                }
             }
-            if (sync_on && sync_q < sync_steps)
-                sync_wait = round_sync(&rec->tile_sync[xcd], sync_base + (++sync_q) * sync_members, sync_wait);
-            // The operand fragments of the next K step were read during the last one, as in every K
-            // step; reading them again here (eight LDS reads per anti-diagonal) ends their lifetime
-            // before the epilogue above, which needs the registers to pass the accumulators through.
-            OZ_READ_FRAGS(fa0, fb0, stage, 0);
+            step(Int<1>{}, Int<D - 2>{}, Int<2>{}, Int<0>{}, Int<4>{}, Int<0>{}, [&](int x) { preload((D - 3) & 3, x); });
+        }
+
+        // anti-diagonals d_hi .. d_hi-nd+1 of k-block kb are complete in acc[0 .. nd-1].
+        // Every address below is a wave-uniform pointer (scalar arithmetic) plus one per-lane 32-bit offset that
+        // is the same for all stores of a kind.
+        if constexpr (ATOMIC) {
+            // result register r of MFMA tile (tj, ti): j = tj*32 + 8*(r/4) + 4*(lane/32) + r%4, i = ti*32 + lane%32
+            const uint32_t lane_raw = uint32_t(wj * 64 + 4 * (lane >> 5)) * kUnit + uint32_t(wi * 64 + (lane & 31));
+#pragma unroll
+            for (int j = 0; j < D; ++j) {
+                if (j < nd) {
+                    int32_t* dst = raw + ((int64_t(kb) * s_cap + (d_hi - j)) * raw_units + local) * (kUnit * kUnit) + lane_raw;
+#pragma unroll
+                    for (int tj = 0; tj < NT; ++tj)
+#pragma unroll
+                        for (int ti = 0; ti < NT; ++ti)
+#pragma unroll
+                            for (int q = 0; q < 16; ++q)
+                                atomicAdd(dst + (tj * 32 + 8 * (q >> 2) + (q & 3)) * kUnit + ti * 32, acc[j][tj][ti][q]);
+                }
+            }
+            clear(0);
+        } else {
+            // where T / L go: the matrix planes, or (parts z > 0) the unit's own slots in the raw buffer.
+            // row: elements between neighbouring j of T, j/4 of L
+            int64_t row = mp, planeL = np * mp;
+            uint8_t* wT = reinterpret_cast<uint8_t*>(T) + ((int64_t(kb) * np + int64_t(uj) * kUnit) * mp + int64_t(ui) * kUnit) * 4;
+            uint8_t* wL = reinterpret_cast<uint8_t*>(L) + int64_t(kb) * (s_cap - 1) * planeL +
+                          (int64_t(uj) * (kUnit / 4) * mp + int64_t(ui) * kUnit) * 4;
+            if (z > 0) {
+                const int units = order ? 4 * g.count : g.count;
+                row = kUnit;
+                planeL = kUnit * kUnit;
+                wT = reinterpret_cast<uint8_t*>(raw) +
+                     ((int64_t(z - 1) * units + local) * g.nkb_part + (kb - kb_first)) * part_slot_bytes(s_cap);
+                wL = wT + kUnit * kUnit * 4;
+            }
+            wT += (int64_t(wj) * 64 * row + wi * 64) * 4;
+            wL += (int64_t(wj) * 16 * row + wi * 64) * 4;
+            // Result register r of MFMA tile (tj, ti): j = tj*16 + 4*(lane/16) + r, i = ti*16 + lane%16.  A lane's dwords
+            // for four ti are 16 apart in i; they change places through LDS (in the part of the stage that this
+            // wave alone fills next, free until then), so that a lane stores 16 bytes and 16 lanes 256 in a row.
+            const uint32_t lq = uint32_t(lane >> 4), lx = uint32_t(lane & 15);
+            const uint32_t lane_L = (lq * uint32_t(row) + lx * 4) * 4u, lane_T = (4 * lq * uint32_t(row) + lx * 4) * 4u;
+            constexpr uint32_t kScratchRow = 320;        // 64 dwords, and 64 bytes that move the next row to other banks
+            uint8_t* const scratch = lds + put + wave * (kUnit * 16) + lq * kScratchRow;
+            auto regroup = [&](int half, const uint32_t (&w)[NT]) -> v4i {
+                uint8_t* const sc = scratch + half * kOperandBytes;
+#pragma unroll
+                for (int ti = 0; ti < NT; ++ti) *reinterpret_cast<uint32_t*>(sc + (ti * 16 + lx) * 4) = w[ti];
+                asm volatile("" ::: "memory");
+                const v4i out = *reinterpret_cast<const v4i*>(sc + lx * 16);
+                asm volatile("" ::: "memory");
+                return out;
+            };
+            v4i carry[NT][NT];
+#pragma unroll
+            for (int a = 0; a < NT; ++a)
+#pragma unroll
+                for (int b = 0; b < NT; ++b) carry[a][b] = zero4;
+            auto put = [&](auto JJ) {
+                constexpr int j = decltype(JJ)::v;
+                const int d = d_hi - j;
+                int64_t row_here = row;
+                asm volatile("" : "+s"(row_here));
+                if (d > 0) {
+                    // balanced digit out (the low byte of the sum is its two's-complement form), carry stays
+                    uint8_t* dst = wL + int64_t(d - 1) * planeL;
+#pragma unroll
+                    for (int tj = 0; tj < NT; ++tj) {
+                        uint32_t w[NT];
+#pragma unroll
+                        for (int ti = 0; ti < NT; ++ti) {
+                            const v4i t = acc[j][tj][ti] + carry[tj][ti];
+                            w[ti] = (uint32_t(t[0]) & 255u) | ((uint32_t(t[1]) & 255u) << 8) |
+                                    ((uint32_t(t[2]) & 255u) << 16) | (uint32_t(t[3]) << 24);
+                            carry[tj][ti] = (t + 128) >> 8;
+                        }
+                        store_lane_16(dst + int64_t(tj * 4) * row_here * 4, lane_L, regroup(tj & 1, w));
+                    }
+                } else {
+                    // the leading word; the next k-block starts from zero
+#pragma unroll
+                    for (int tj = 0; tj < NT; ++tj)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            uint32_t w[NT];
+#pragma unroll
+                            for (int ti = 0; ti < NT; ++ti) w[ti] = uint32_t(acc[j][tj][ti][q] + carry[tj][ti][q]);
+                            store_lane_16(wT + int64_t(tj * 16 + q) * row_here * 4, lane_T, regroup(q & 1, w));
+                        }
+#pragma unroll
+                    for (int tj = 0; tj < NT; ++tj)
+#pragma unroll
+                        for (int ti = 0; ti < NT; ++ti) carry[tj][ti] = zero4;
+                }
+            };
+            put(Int<0>{});
+            if (nd > 1) {
+                put(Int<1>{});
+                if (nd > 2) {
+                    put(Int<2>{});
+                    if (nd > 3) put(Int<3>{});
+                }
+            }
+            clear(1);
+            // The carries enter the next group's first accumulator set as the result of a matrix instruction
+            // with zero operands (0*0 + carry), for the same reason as in clear().
+#pragma unroll
+            for (int tj = 0; tj < NT; ++tj)
+#pragma unroll
+                for (int ti = 0; ti < NT; ++ti)
+                    acc[0][tj][ti] = __builtin_amdgcn_mfma_i32_16x16x64_i8(zero4, zero4, carry[tj][ti], 0, 0, 0);
+        }
+
+        if (!last) {
+            if (d_hi >= D) {
+                d_hi -= D;
+            } else {
+                ++kb;
+                d_hi = S - 1;
+            }
+            if (sync_on && sync_q < sync_steps) arrive();
+        } else {
+            // a unit with fewer groups than the call's largest count still owes the round its
+            // remaining arrivals: the workgroups that walk more of them count on every member
+            if (sync_on && sync_q < sync_steps && threadIdx.x == 0) atomicAdd(&rec->tile_sync[xcd], sync_steps - sync_q);
+            if (!has_next) break;
+            ui = nui; uj = nuj; S = nS; slot = nslot;
+            kb = kb_first;
+            d_hi = S - 1;
+            sa.ahead = sb.ahead = false;
+            find_next();
+            sync_q = 0;
+            if (sync_on) arrive();
         }
     }
-    // a tile with fewer anti-diagonals than the call's largest count still owes the round its
-    // remaining arrivals: the workgroups that walk more of them count on every member
-    if (sync_on && sync_q < sync_steps && threadIdx.x == 0) atomicAdd(&rec->tile_sync[xcd], sync_steps - sync_q);
     // drain the surplus transfers before the workgroup's LDS is released
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-#undef OZ_ISSUE_TILE
-#undef OZ_READ_FRAGS
-#undef OZ_MFMA
-#undef OZ_DMA
-#undef OZ_TILE_ADDR
-#undef OZ_TILE_ADVANCE
-#undef OZ_READ_A
-#undef OZ_READ_B
-
 // raw = 0 on the slots of a launch whose workgroups add their parts of the k range into them.
-// grid (tiles of the launch, planes); a workgroup clears one 256 x 256 slot of one plane.
-__global__ __launch_bounds__(256) void zero_raw_kernel(int32_t* __restrict__ raw, int raw_slots, const Record* rec) {
-    if (rec->res.fallback) return;
-    int4* base = reinterpret_cast<int4*>(raw + (int64_t(blockIdx.y) * raw_slots + blockIdx.x) * (kBM * kBN));
-    for (int v = threadIdx.x; v < kBM * kBN / 4; v += 256) base[v] = make_int4(0, 0, 0, 0);
+// grid (units of the launch, planes); a workgroup clears one 128 x 128 slot of one plane.
+__global__ __launch_bounds__(256) void zero_raw_kernel(int32_t* __restrict__ raw, int raw_units, int s_cap, const Record* rec) {
+    if (rec->res.fallback || int(blockIdx.y) % s_cap >= rec->res.slices_used) return;
+    int4* base = reinterpret_cast<int4*>(raw + (int64_t(blockIdx.y) * raw_units + blockIdx.x) * (kUnit * kUnit));
+#pragma unroll 4
+    for (int v = threadIdx.x; v < kUnit * kUnit / 4; v += 256) base[v] = make_int4(0, 0, 0, 0);
 }
 
-// Aggregates the raw anti-diagonal sums of the split tiles of a launch into the T / L form the unsplit
-// tiles write directly: the same integer carry chain, least significant anti-diagonal first.
-// grid (tiles of the launch, k-blocks); thread = one i of the tile, walking j four at a time.
-__global__ __launch_bounds__(256) void aggregate_raw_kernel(const int32_t* __restrict__ raw, int raw_slots,
+// Unit `local` of a launch, and its slice count, for the kernels that follow a split launch.
+__device__ __forceinline__ int split_unit(const GemmGrid& g, int local, const int32_t* __restrict__ tile_S, int S_all, int& ui,
+                                          int& uj) {
+    if (tile_S) {
+        int ti, tj;
+        const int q = local / g.count;
+        lin_to_tile(tile_S[g.nti * g.ntj + g.begin + local - q * g.count], g.nti, g.ntj, ti, tj);
+        ui = 2 * ti + (q & 1);
+        uj = 2 * tj + (q >> 1);
+        return min(tile_S[tj * g.nti + ti], S_all);
+    }
+    lin_to_tile(g.begin + local, g.um, g.un, ui, uj);
+    return S_all;
+}
+
+constexpr int kSplitRows = 4;     // j/4 rows of a unit per workgroup of the two kernels below (32 rows in all)
+
+// Aggregates the raw anti-diagonal sums of the units of an atomic launch into the T / L form the other
+// launches write directly: the same integer carry chain, least significant anti-diagonal first.
+// grid (units of the launch, k-blocks, 32 / kSplitRows); thread = one i of the unit and half of the rows.
+__global__ __launch_bounds__(256) void aggregate_raw_kernel(const int32_t* __restrict__ raw, int raw_units,
                                                             int32_t* __restrict__ T, int8_t* __restrict__ L,
-                                                            int64_t mp, int64_t np, int64_t kp, int s_cap, int nti,
-                                                            int ntj, int tile_begin, const Record* rec,
-                                                            const int32_t* __restrict__ tile_S) {
+                                                            int64_t mp, int64_t np, int64_t kp, int s_cap, GemmGrid g,
+                                                            const Record* rec, const int32_t* __restrict__ tile_S) {
     if (rec->res.fallback) return;
     const int S_all = rec->res.slices_used;
     const int nkb = int((kp + k_block_length(S_all) - 1) / k_block_length(S_all));
-    const int kb = blockIdx.y;
+    const int kb = blockIdx.y, local = blockIdx.x;
     if (kb >= nkb) return;
-    int ti, tj;
-    const int pos = tile_begin + int(blockIdx.x);
-    lin_to_tile(tile_S ? tile_S[nti * ntj + pos] : pos, nti, ntj, ti, tj);
-    const int S = tile_S ? min(tile_S[tj * nti + ti], S_all) : S_all;
-    const int il = threadIdx.x;
-    const int64_t i = int64_t(ti) * kBM + il, j0 = int64_t(tj) * kBN;
-    const int32_t* src = raw + (int64_t(kb) * s_cap * raw_slots + blockIdx.x) * (kBM * kBN) + il;
-    const int64_t plane = int64_t(raw_slots) * (kBM * kBN);
-    for (int jl4 = 0; jl4 < kBN / 4; ++jl4) {
+    int ui, uj;
+    const int S = split_unit(g, local, tile_S, S_all, ui, uj);
+    if (ui >= g.um || uj >= g.un) return;
+    const int il = threadIdx.x & (kUnit - 1);
+    const int64_t i = int64_t(ui) * kUnit + il, j0 = int64_t(uj) * kUnit;
+    const int32_t* src = raw + (int64_t(kb) * s_cap * raw_units + local) * (kUnit * kUnit) + il;
+    const int64_t plane = int64_t(raw_units) * (kUnit * kUnit);
+    for (int jl4 = blockIdx.z * kSplitRows + (threadIdx.x >> 7); jl4 < int(blockIdx.z + 1) * kSplitRows; jl4 += 2) {
         int carry[4] = {0, 0, 0, 0};
         for (int d = S - 1; d >= 1; --d) {
             uint32_t w = 0;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int t = src[d * plane + (jl4 * 4 + q) * kBM] + carry[q];
+                const int t = src[d * plane + (jl4 * 4 + q) * kUnit] + carry[q];
                 w |= (uint32_t(t) & 255u) << (8 * q);
                 carry[q] = (t + 128) >> 8;
             }
@@ -485,7 +769,70 @@ __global__ __launch_bounds__(256) void aggregate_raw_kernel(const int32_t* __res
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            T[(int64_t(kb) * np + j0 + jl4 * 4 + q) * mp + i] = src[(jl4 * 4 + q) * kBM] + carry[q];
+            T[(int64_t(kb) * np + j0 + jl4 * 4 + q) * mp + i] = src[(jl4 * 4 + q) * kUnit] + carry[q];
+    }
+}
+
+// Adds the parts of a split launch: part 0 lies in the matrix planes, the others in their slots, every one as leading
+// word and balanced digits of its own exact integer.  Digits are added plane by plane with the same carry chain
+// (at most zsplit * 128 per digit), which gives the digits of the whole integer.  Only the parts that have k in
+// k-block kb count (the planes of the others hold nothing).
+// grid (units of the launch, k-blocks, 32 / kSplitRows); thread = one i of the unit and half of the rows.
+__global__ __launch_bounds__(256) void add_parts_kernel(const int32_t* __restrict__ raw, int32_t* __restrict__ T,
+                                                        int8_t* __restrict__ L, int64_t mp, int64_t np, int64_t kp, int s_cap,
+                                                        GemmGrid g, const Record* rec, const int32_t* __restrict__ tile_S) {
+    if (rec->res.fallback) return;
+    const int S_all = rec->res.slices_used;
+    const int64_t kblk = k_block_length(S_all);
+    const int nkb = int((kp + kblk - 1) / kblk);
+    const int kb = blockIdx.y, local = blockIdx.x;
+    if (kb >= nkb) return;
+    int ui, uj;
+    const int S = split_unit(g, local, tile_S, S_all, ui, uj);
+    if (ui >= g.um || uj >= g.un) return;
+    const int units = tile_S ? 4 * g.count : g.count;
+    const int kt_total = int(kp / kBK), kt_per_block = int(kblk / kBK);
+    const int il = threadIdx.x & (kUnit - 1);
+    const int64_t i = int64_t(ui) * kUnit + il, j0 = int64_t(uj) * kUnit;
+    const int64_t bytes = part_slot_bytes(s_cap);
+    // the parts that touch this k-block
+    auto first_kt = [&](int z) { return int(int64_t(kt_total) * z / g.zsplit); };
+    int z_lo = 0;
+    while (z_lo + 1 < g.zsplit && first_kt(z_lo + 1) <= kb * kt_per_block) ++z_lo;
+    int z_hi = z_lo;
+    while (z_hi + 1 < g.zsplit && first_kt(z_hi + 1) < (kb + 1) * kt_per_block) ++z_hi;
+    if (z_lo == 0 && z_hi == 0) return;     // all of it came from part 0: already in place
+    for (int jl4 = blockIdx.z * kSplitRows + (threadIdx.x >> 7); jl4 < int(blockIdx.z + 1) * kSplitRows; jl4 += 2) {
+        int carry[4] = {0, 0, 0, 0};
+        for (int d = S - 1; d >= 0; --d) {
+            int t[4] = {carry[0], carry[1], carry[2], carry[3]};
+            uint32_t* const lw = reinterpret_cast<uint32_t*>(L) + ((int64_t(kb) * (s_cap - 1) + (d - 1)) * (np / 4) + j0 / 4 + jl4) * mp + i;
+            int32_t* const tw = T + (int64_t(kb) * np + j0 + jl4 * 4) * mp + i;
+            for (int z = z_lo; z <= z_hi; ++z) {
+                const int32_t* sT = raw + ((int64_t(z - 1) * units + local) * g.nkb_part + (kb - first_kt(z) / kt_per_block)) * (bytes / 4);
+                if (d > 0) {
+                    const uint32_t w = z == 0 ? *lw
+                                              : reinterpret_cast<const uint32_t*>(sT + kUnit * kUnit)[((d - 1) * (kUnit / 4) + jl4) * kUnit + il];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) t[q] += int(w << (24 - 8 * q)) >> 24;
+                } else {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) t[q] += z == 0 ? tw[q * mp] : sT[(jl4 * 4 + q) * kUnit + il];
+                }
+            }
+            if (d > 0) {
+                uint32_t w = 0;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    w |= (uint32_t(t[q]) & 255u) << (8 * q);
+                    carry[q] = (t[q] + 128) >> 8;
+                }
+                *lw = w;
+            } else {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) tw[q * mp] = t[q];
+            }
+        }
     }
 }
 
@@ -539,21 +886,21 @@ __global__ __launch_bounds__(256) void tile_order_kernel(const int32_t* __restri
         }
     }
     __syncthreads();
-    const int per = first >> 3, rem = first & 7, rounds = first / (8 * kRoundTiles), dealt = rounds * 8 * kRoundTiles;
+    const int per = first >> 3, rem = first & 7, rounds = first / (8 * kRoundUnits), dealt = rounds * 8 * kRoundUnits;
     for (int lin = lo; lin < hi; ++lin) {
         const int k = key_of(lin);
         const int si = base[k] + cnt[k][tid]++;      // position in the sorted sequence
         int q = si;
         if (si < dealt) {
-            const int g = si / kRoundTiles, wpos = si % kRoundTiles, r = g >> 3, x = g & 7;
-            q = x * per + min(x, rem) + r * kRoundTiles + wpos;
+            const int g = si / kRoundUnits, wpos = si % kRoundUnits, r = g >> 3, x = g & 7;
+            q = x * per + min(x, rem) + r * kRoundUnits + wpos;
         } else if (si < first) {
             // what is left of the XCD ranges behind their dealt rounds, XCD by XCD
             int t = si - dealt;
             for (int x = 0; x < 8; ++x) {
-                const int left = per + (x < rem ? 1 : 0) - rounds * kRoundTiles;
+                const int left = per + (x < rem ? 1 : 0) - rounds * kRoundUnits;
                 if (t < left) {
-                    q = x * per + min(x, rem) + rounds * kRoundTiles + t;
+                    q = x * per + min(x, rem) + rounds * kRoundUnits + t;
                     break;
                 }
                 t -= left;
@@ -569,57 +916,105 @@ void launch_gemm_i8(hipStream_t st, const Workspace& w, const Problem& p) {
                               hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds);
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_i8_kernel<true>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds);
-    const int nti = int(p.mp / kBM), ntj = int(p.np / kBN);
-    const int tiles = nti * ntj;
-    const int64_t kt_total = p.kp / kBK;
-    const int planes = p.nkb * p.s_cap;
-    const int32_t* tile_S = p.tile_mode ? w.tile_S : nullptr;
+    GemmGrid g;
+    g.nti = int(p.mp / kTile);
+    g.ntj = int(p.np / kTile);
+    g.um = int((p.m + kUnit - 1) / kUnit);
+    g.un = int((p.n + kUnit - 1) / kUnit);
     // the workgroup-to-XCD reasoning behind the in-step waits holds for the whole chip only
     // (8 XCDs of 32 CUs); a partitioned device runs the same kernel without them
-    const int full_chip = p.num_cu == 8 * kRoundTiles ? 1 : 0;
-    // k split for `count` tiles that cannot fill the chip: about one workgroup per CU, each part
-    // keeping at least kMinSplitSteps K steps; the parts add into the raw buffer with integer atomics
-    auto split_for = [&](int count) -> int {
-        int zs = p.num_cu / count;
-        if (zs > kt_total / kMinSplitSteps) zs = int(kt_total / kMinSplitSteps);
-        if (count > p.raw_slots) zs = 1;      // cannot happen: a split launch has fewer tiles than CUs
-        return zs < 1 ? 1 : zs;
+    g.full_chip = p.num_cu == 8 * kRoundUnits ? 1 : 0;
+    const int32_t* tile_S = p.tile_mode ? w.tile_S : nullptr;
+    const int blocks = g.nti * g.ntj;
+    const int per_pos = p.tile_mode ? 4 : 1;                  // units per position of the launch order
+    const int positions = p.tile_mode ? blocks : g.um * g.un;
+    const int kt = int(p.kp / kBK);
+    const int raw_units = 4 * p.raw_slots;                    // 128 x 128 slots per plane of the raw buffer
+    const int64_t raw_bytes = int64_t(p.nkb) * p.s_cap * raw_units * (kUnit * kUnit * 4);
+
+    // stream entries per 64 of k of a unit with the fewest slices the call can come out with
+    int min_entries = 0;
+    for (int n = p.s_min; n > 0; n -= kDiag) min_entries += n;
+
+    // k split of a launch that cannot fill the chip.  Estimated time in ns for `units` units, seven slices assumed
+    // (the slice count is decided on the device): a 64 of k costs a unit about 4.2 us, a workgroup about 5 us to
+    // start and to write its sums, a further launch 6 us.  Parts with slots of their own move 10 bytes per
+    // element and part (60 ns per part and unit); atomics add 28 bytes per element and part (170 ns), zero and
+    // read the slots, but need no more memory for more parts.
+    struct Split { int z; bool atomic; };
+    // k-blocks a part can touch, whatever the slice count turns out to be (fewer slices: longer k-blocks)
+    auto nkb_part = [&](int z) -> int {
+        const int64_t len = (int64_t(kt) + z - 1) / z * kBK;
+        return p.nkb == 1 ? 1 : int(std::min<int64_t>(p.nkb, (len - 1) / p.kblk + 2));
     };
-    auto launch = [&](int begin, int count, int zs) {
-        if (zs > 1)
-            hipLaunchKernelGGL(zero_raw_kernel, dim3(unsigned(count), unsigned(planes)), dim3(256), 0, st, w.raw,
-                               p.raw_slots, w.rec);
-        if (zs > 1)
-            hipLaunchKernelGGL(gemm_i8_kernel<true>, dim3(unsigned(count) * unsigned(zs)), dim3(256), kGemmLds, st,
-                               w.As, w.Bs, w.T, w.L, w.raw, p.raw_slots, p.mp, p.np, p.kp, p.s_cap, w.rec, full_chip,
-                               zs, begin, count, tile_S);
-        else
-            hipLaunchKernelGGL(gemm_i8_kernel<false>, dim3(unsigned(count)), dim3(256), kGemmLds, st, w.As, w.Bs,
-                               w.T, w.L, w.raw, p.raw_slots, p.mp, p.np, p.kp, p.s_cap, w.rec, full_chip, 1, begin,
-                               count, tile_S);
-        if (zs > 1)
-            hipLaunchKernelGGL(aggregate_raw_kernel, dim3(unsigned(count), unsigned(p.nkb)), dim3(256), 0, st, w.raw,
-                               p.raw_slots, w.T, w.L, p.mp, p.np, p.kp, p.s_cap, nti, ntj, begin, w.rec, tile_S);
+    auto parts_fit = [&](int units, int z) -> bool {
+        return int64_t(z - 1) * units * nkb_part(z) * part_slot_bytes(p.s_cap) <= raw_bytes;
     };
-    // Tiles are dealt in rounds of one per CU.  A call with less than three quarters of a round is
-    // split along k as a whole; otherwise the full rounds run unsplit and a last round that would
-    // be less than three quarters full is split along k in a launch of its own.
+    auto plan = [&](int units) -> Split {
+        auto waves = [&](int64_t items) -> int64_t { return (items + p.num_cu - 1) / p.num_cu; };
+        Split best{1, false};
+        int64_t best_ns = waves(units) * (int64_t(kt) * 4200 + 5000) * 95 / 100;     // a split has to gain 5 %
+        for (int z = 2; z <= kt && int64_t(units) * z <= p.num_cu; ++z) {
+            const int64_t steps = (kt + z - 1) / z;
+            if (parts_fit(units, z)) {
+                const int64_t ns = steps * 4200 + 5000 + 6000 + int64_t(60) * units * z;
+                if (ns < best_ns) { best_ns = ns; best = Split{z, false}; }
+            }
+            if (units <= raw_units) {
+                const int64_t ns = steps * 4800 + 5000 + 12000 + int64_t(170) * units * z;
+                if (ns < best_ns) { best_ns = ns; best = Split{z, true}; }
+            }
+        }
+        return best;
+    };
+    auto launch = [&](int begin, int count, Split sp) {
+        const int units = count * per_pos;
+        g.begin = begin;
+        g.count = count;
+        g.zsplit = sp.z;
+        g.nkb_part = nkb_part(sp.z);
+        g.persistent = 0;
+        // unsplit launches in per-block order give every XCD whole blocks: the ranges differ by up to four units
+        unsigned grid = (p.tile_mode && sp.z == 1) ? unsigned(8 * 4 * ((count + 7) / 8)) : unsigned(units) * unsigned(sp.z);
+        // more units than CUs: one workgroup per CU that walks its share (eight equal ranges, one per XCD), if
+        // the units are long enough for the streams
+        const unsigned cus = unsigned(p.num_cu) & ~7u;
+        if (grid > cus && cus != 0 && kt * min_entries >= kMinUnitItems) {
+            grid = cus;
+            g.persistent = 1;
+        }
+        if (sp.atomic) {
+            hipLaunchKernelGGL(zero_raw_kernel, dim3(unsigned(units), unsigned(p.nkb * p.s_cap)), dim3(256), 0, st, w.raw,
+                               raw_units, p.s_cap, w.rec);
+            hipLaunchKernelGGL(gemm_i8_kernel<true>, dim3(grid), dim3(256), kGemmLds, st, w.As, w.Bs, w.T, w.L, w.raw,
+                               raw_units, p.mp, p.np, p.kp, p.s_cap, w.rec, g, tile_S);
+            hipLaunchKernelGGL(aggregate_raw_kernel, dim3(unsigned(units), unsigned(p.nkb), kUnit / 4 / kSplitRows), dim3(256),
+                               0, st, w.raw, raw_units, w.T, w.L, p.mp, p.np, p.kp, p.s_cap, g, w.rec, tile_S);
+        } else {
+            hipLaunchKernelGGL(gemm_i8_kernel<false>, dim3(grid), dim3(256), kGemmLds, st, w.As, w.Bs, w.T, w.L, w.raw,
+                               raw_units, p.mp, p.np, p.kp, p.s_cap, w.rec, g, tile_S);
+            if (sp.z > 1)
+                hipLaunchKernelGGL(add_parts_kernel, dim3(unsigned(units), unsigned(p.nkb), kUnit / 4 / kSplitRows), dim3(256),
+                                   0, st, w.raw, w.T, w.L, p.mp, p.np, p.kp, p.s_cap, g, w.rec, tile_S);
+        }
+    };
+    // Units are dealt in rounds of one per CU.  A call with less than a round may be split along k as a whole;
+    // otherwise the full rounds run unsplit and what is left may be split along k in a launch of its own.
+    // (Per-block order: a full round of the order table is one block per CU.)
     const int round = p.num_cu;
-    const int full = tiles / round * round, rest = tiles - full;
+    const int full = positions / round * round, rest = positions - full;
+    const Split sp = rest != 0 && rest * per_pos < round ? plan(rest * per_pos) : Split{1, false};
+    const bool two = full != 0 && sp.z > 1;
     if (p.tile_mode) {
-        const bool two_launches = full != 0 && rest != 0 && rest * 4 <= round * 3 && split_for(rest) != 1;
-        const int first = two_launches ? full : tiles;
-        const int deal = (full_chip && full != 0 && tiles <= (1 << 16)) ? 1 : 0;
-        hipLaunchKernelGGL(tile_order_kernel, dim3(1), dim3(256), 0, st, w.tile_S, w.tile_S + tiles, nti, ntj, first, deal,
-                           w.rec);
+        const int deal = (g.full_chip && full != 0 && blocks <= (1 << 16)) ? 1 : 0;
+        hipLaunchKernelGGL(tile_order_kernel, dim3(1), dim3(256), 0, st, w.tile_S, w.tile_S + blocks, g.nti, g.ntj,
+                           two ? full : blocks, deal, w.rec);
     }
-    if (full == 0) {
-        launch(0, tiles, rest * 4 <= round * 3 ? split_for(tiles) : 1);
-    } else if (rest == 0 || rest * 4 > round * 3 || split_for(rest) == 1) {
-        launch(0, tiles, 1);
+    if (two) {
+        launch(0, full, Split{1, false});
+        launch(full, rest, sp);
     } else {
-        launch(0, full, 1);
-        launch(full, rest, split_for(rest));
+        launch(0, positions, sp);
     }
 }
 

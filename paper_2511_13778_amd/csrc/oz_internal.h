@@ -50,6 +50,7 @@ struct Problem {
     int64_t m, n, k;
     int64_t mp, np, kp;    // padded sizes
     int32_t s_cap;         // slice planes the workspace holds
+    int32_t s_min;         // fewest slices an emulated block of C can come out with
     int32_t nkb;           // number of k-blocks (int32 accumulator headroom)
     int64_t kblk;          // k-block length (multiple of kKPad)
     int32_t esc_block;     // b

@@ -967,3 +967,32 @@ def test_argument_errors(lib):
     assert h.workspace_bytes("N", "N", (1 << 22) + 1, 64, 64, opts) == 0
     assert h.workspace_bytes("N", "N", 64, 64, 1 << 21, opts) > 0
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("m,n,k,S", [
+    (128, 128, 64, 1), (129, 127, 65, 2), (1, 257, 130, 3),          # one to three accumulator sets, 64 of k and one more
+    (127, 385, 200, 4), (257, 129, 700, 5), (300, 200, 1030, 6),     # every remainder of the window by four; parts of a k split
+    (640, 500, 2100, 7), (130, 140, 5000, 8), (200, 300, 9000, 9),   # more parts, few units (integer atomics)
+    (2100, 2050, 70, 7), (2176, 2300, 129, 2),                       # more units than CUs: several per workgroup, or one
+])
+def test_slice_gemm_units_and_splits(lib, m, n, k, S):
+    # the slice GEMM at the edges of its 128 x 128 units and of its 64s of k, for slice counts of every remainder modulo
+    # the four anti-diagonals it takes at a time, on each of its routes: whole, parts added afterwards, atomics,
+    # several units per workgroup.  Integers, so slices, digits and C are the oracle's bit for bit
+    g, h = lib
+    A, B = wl.lognormal_spread(m, k, n, 0.5, seed=1000 + S + k)
+    check_against_oracle(g, h, A, B, 1.0, 0.0, None, mode="unguarded", slices=S, bound=False)
+
+
+@pytest.mark.parametrize("m,n,k", [(700, 1300, 300), (2300, 2500, 100), (300, 500, 4000)])
+def test_slice_gemm_per_block_order(lib, m, n, k):
+    # the same in per-block order (quadrants of 256 x 256 blocks, some holding padding only), with different slice counts
+    # next to each other: fewer blocks than CUs, more units than CUs, a k split
+    g, h = lib
+    A, B = wl.wide_rows(m, k, n, seed=k, row_lo=m // 2, row_hi=m // 2 + 10, spread=24)
+    got, gm, res = run_gpu(g, h, A, B, 1.0, 0.0, None, "N", "T", mode=g.OZ_DYNAMIC, target_bits=53, max_bits=200, heuristic=0,
+                           tile_slices=1)
+    tr = oz.emulated_dgemm(A, B, 1.0, 0.0, None, mode=oz.MODE_DYNAMIC, target_bits=53, max_bits=200, per_tile=True)
+    assert (res.slices_used, res.slices_min, res.pair_tiles) == (tr.verdict.slices_used, tr.verdict.slices_min, tr.verdict.pair_tiles)
+    assert res.slices_min < res.slices_used
+    np.testing.assert_array_equal(got, tr.C)
