@@ -428,9 +428,9 @@ oz_status_t dgemm_impl(oz_handle_t h, void* stream, char transa, char transb, in
     launch_slice(st, A, a_sr, a_sl, m, p.mp, p, w.eA, w.As, w.rec);
     launch_slice(st, B, b_sr, b_sl, n, p.np, p, w.eB, w.Bs, w.rec);
     clk.done(3);
-    launch_gemm_i8(st, w, p);
+    const SplitPlan split = launch_gemm_i8(st, w, p);
     clk.done(4);
-    launch_recompose(st, w, p, alpha, beta, C, ldc);
+    launch_recompose(st, w, p, split, alpha, beta, C, ldc);
     clk.done(5);
     if (guarded) launch_dgemm_f64(st, w.rec, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, f64_scratch, f64_scratch_bytes);
     clk.done(6);

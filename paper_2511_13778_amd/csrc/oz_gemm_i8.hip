@@ -59,10 +59,8 @@ namespace oz {
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 
-constexpr int kUnit = 128;                       // edge of the unit of C a workgroup owns (four per kTile block)
 constexpr int kDiag = 4;                         // anti-diagonals accumulated side by side
 constexpr int kDiagAtomic = 3;                   // the same in the atomic variant (its 32x32 tiles need more registers in flight)
-constexpr int kBK = 64;                          // k per step (kKPad is a multiple)
 constexpr int kStages = 10;                      // LDS stages; the pipeline below counts on ten
 constexpr int kOperandBytes = kUnit * kBK;       // 8 KB: one operand's tile
 constexpr int kStageBytes = 2 * kOperandBytes;   // A tile, then B tile
@@ -79,21 +77,6 @@ constexpr int kMidSyncMinK = 24576;   // from this k on, workgroups also wait af
 // The streams of tiles run up to nine entries ahead of the multiplication: with at least this many per unit they never
 // need to know more than the next unit.
 constexpr int kMinUnitItems = 12;
-
-// What a launch of the slice GEMM covers.
-struct GemmGrid {
-    int nti, ntj;      // kTile x kTile blocks of the padded C
-    int um, un;        // units with at least one row / column of C
-    int begin, count;  // plain order: units [begin, begin + count); per-block order: as many positions of the order table
-    int zsplit;        // parts of the k range per unit
-    int nkb_part;      // k-blocks a part's slot has room for (parts other than the first)
-    int full_chip;     // 8 XCDs of 32 CUs: the in-step waits make sense
-    int persistent;    // a workgroup takes several units, and every unit has at least kMinUnitItems items
-};
-
-// Where part z > 0 of unit `local` of a launch leaves its aggregated sums: a slot of the raw buffer holding, per
-// k-block the part touches, T [128 j][128 i] int32 and L [s_cap-1][32][128 i][4 j] int8 of the unit alone.
-__host__ __device__ inline int64_t part_slot_bytes(int s_cap) { return int64_t(kUnit) * kUnit * (4 + (s_cap - 1)); }
 
 // Records this workgroup's arrival at *counter and, if `wait`, waits (bounded, about half a
 // millisecond) until `target` workgroups have arrived.  The wait only improves cache locality:
@@ -114,17 +97,6 @@ __device__ __forceinline__ void round_sync(int32_t* counter, int target, bool& w
         }
     }
     asm volatile("s_barrier" ::: "memory");
-}
-
-// position `lin` of the tile order -> tile coordinates: panels of 8 tile columns, inside a panel row by row,
-// so 32 consecutive tiles form a 4 (i) x 8 (j) block
-__device__ __forceinline__ void lin_to_tile(int lin, int nti, int ntj, int& ti, int& tj) {
-    constexpr int GW = 8;
-    const int panel = lin / (GW * nti);
-    const int in_panel = lin - panel * GW * nti;
-    const int w = min(GW, ntj - panel * GW);
-    ti = in_panel / w;
-    tj = panel * GW + in_panel % w;
 }
 
 // Position `slot` of an XCD's range -> unit of C.  Workgroup ids are dealt round-robin to the 8 XCDs by the hardware; each XCD is given a
@@ -734,50 +706,13 @@ __device__ __forceinline__ int split_unit(const GemmGrid& g, int local, const in
     return S_all;
 }
 
-constexpr int kSplitRows = 4;     // j/4 rows of a unit per workgroup of the two kernels below (32 rows in all)
-
-// Aggregates the raw anti-diagonal sums of the units of an atomic launch into the T / L form the other
-// launches write directly: the same integer carry chain, least significant anti-diagonal first.
-// grid (units of the launch, k-blocks, 32 / kSplitRows); thread = one i of the unit and half of the rows.
-__global__ __launch_bounds__(256) void aggregate_raw_kernel(const int32_t* __restrict__ raw, int raw_units,
-                                                            int32_t* __restrict__ T, int8_t* __restrict__ L,
-                                                            int64_t mp, int64_t np, int64_t kp, int s_cap, GemmGrid g,
-                                                            const Record* rec, const int32_t* __restrict__ tile_S) {
-    if (rec->res.fallback) return;
-    const int S_all = rec->res.slices_used;
-    const int nkb = int((kp + k_block_length(S_all) - 1) / k_block_length(S_all));
-    const int kb = blockIdx.y, local = blockIdx.x;
-    if (kb >= nkb) return;
-    int ui, uj;
-    const int S = split_unit(g, local, tile_S, S_all, ui, uj);
-    if (ui >= g.um || uj >= g.un) return;
-    const int il = threadIdx.x & (kUnit - 1);
-    const int64_t i = int64_t(ui) * kUnit + il, j0 = int64_t(uj) * kUnit;
-    const int32_t* src = raw + (int64_t(kb) * s_cap * raw_units + local) * (kUnit * kUnit) + il;
-    const int64_t plane = int64_t(raw_units) * (kUnit * kUnit);
-    for (int jl4 = blockIdx.z * kSplitRows + (threadIdx.x >> 7); jl4 < int(blockIdx.z + 1) * kSplitRows; jl4 += 2) {
-        int carry[4] = {0, 0, 0, 0};
-        for (int d = S - 1; d >= 1; --d) {
-            uint32_t w = 0;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int t = src[d * plane + (jl4 * 4 + q) * kUnit] + carry[q];
-                w |= (uint32_t(t) & 255u) << (8 * q);
-                carry[q] = (t + 128) >> 8;
-            }
-            reinterpret_cast<uint32_t*>(L)[((int64_t(kb) * (s_cap - 1) + (d - 1)) * (np / 4) + j0 / 4 + jl4) * mp + i] = w;
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            T[(int64_t(kb) * np + j0 + jl4 * 4 + q) * mp + i] = src[(jl4 * 4 + q) * kUnit] + carry[q];
-    }
-}
-
-// Adds the parts of a split launch: part 0 lies in the matrix planes, the others in their slots, every one as leading
-// word and balanced digits of its own exact integer.  Digits are added plane by plane with the same carry chain
-// (at most zsplit * 128 per digit), which gives the digits of the whole integer.  Only the parts that have k in
-// k-block kb count (the planes of the others hold nothing).
-// grid (units of the launch, k-blocks, 32 / kSplitRows); thread = one i of the unit and half of the rows.
+// Adds the parts of a launch that covers the last units of a product only (a product that is split as a whole is put
+// together by the recomposition): part 0 lies in the matrix planes, the others in their slots, every one as
+// leading word and balanced digits of its own exact integer.  Digits are added plane by plane with the carry chain
+// of the slice GEMM (at most zsplit * 128 per digit), which gives the digits of the whole integer.  Only the parts that
+// have k in k-block kb count (the planes of the others hold nothing).
+// Bound by latency: the loads of eight digits of a part are in flight together (one by one, a call of 7936 x 7936 x 256
+// spent 31 us here on four units).  grid (units of the launch, k-blocks, 16); thread = one i and one row j/4 of the unit.
 __global__ __launch_bounds__(256) void add_parts_kernel(const int32_t* __restrict__ raw, int32_t* __restrict__ T,
                                                         int8_t* __restrict__ L, int64_t mp, int64_t np, int64_t kp, int s_cap,
                                                         GemmGrid g, const Record* rec, const int32_t* __restrict__ tile_S) {
@@ -792,48 +727,56 @@ __global__ __launch_bounds__(256) void add_parts_kernel(const int32_t* __restric
     if (ui >= g.um || uj >= g.un) return;
     const int units = tile_S ? 4 * g.count : g.count;
     const int kt_total = int(kp / kBK), kt_per_block = int(kblk / kBK);
-    const int il = threadIdx.x & (kUnit - 1);
+    const int64_t slot_words = part_slot_bytes(s_cap) / 4;
+    int z_lo, z_hi;
+    parts_of_block(kt_total, kt_per_block, g.zsplit, kb, z_lo, z_hi);
+    if (z_hi == 0) return;                  // all of it came from part 0: already in place
+    const int il = threadIdx.x & (kUnit - 1), jl4 = int(blockIdx.z) * 2 + (threadIdx.x >> 7);
     const int64_t i = int64_t(ui) * kUnit + il, j0 = int64_t(uj) * kUnit;
-    const int64_t bytes = part_slot_bytes(s_cap);
-    // the parts that touch this k-block
-    auto first_kt = [&](int z) { return int(int64_t(kt_total) * z / g.zsplit); };
-    int z_lo = 0;
-    while (z_lo + 1 < g.zsplit && first_kt(z_lo + 1) <= kb * kt_per_block) ++z_lo;
-    int z_hi = z_lo;
-    while (z_hi + 1 < g.zsplit && first_kt(z_hi + 1) < (kb + 1) * kt_per_block) ++z_hi;
-    if (z_lo == 0 && z_hi == 0) return;     // all of it came from part 0: already in place
-    for (int jl4 = blockIdx.z * kSplitRows + (threadIdx.x >> 7); jl4 < int(blockIdx.z + 1) * kSplitRows; jl4 += 2) {
-        int carry[4] = {0, 0, 0, 0};
-        for (int d = S - 1; d >= 0; --d) {
-            int t[4] = {carry[0], carry[1], carry[2], carry[3]};
-            uint32_t* const lw = reinterpret_cast<uint32_t*>(L) + ((int64_t(kb) * (s_cap - 1) + (d - 1)) * (np / 4) + j0 / 4 + jl4) * mp + i;
-            int32_t* const tw = T + (int64_t(kb) * np + j0 + jl4 * 4) * mp + i;
-            for (int z = z_lo; z <= z_hi; ++z) {
-                const int32_t* sT = raw + ((int64_t(z - 1) * units + local) * g.nkb_part + (kb - first_kt(z) / kt_per_block)) * (bytes / 4);
-                if (d > 0) {
-                    const uint32_t w = z == 0 ? *lw
-                                              : reinterpret_cast<const uint32_t*>(sT + kUnit * kUnit)[((d - 1) * (kUnit / 4) + jl4) * kUnit + il];
+    uint32_t* const lw = reinterpret_cast<uint32_t*>(L) + (int64_t(kb) * (s_cap - 1) * (np / 4) + j0 / 4 + jl4) * mp + i;
+    const int64_t plane = (np / 4) * mp;    // dwords between digit planes
+    int32_t* const tw = T + (int64_t(kb) * np + j0 + jl4 * 4) * mp + i;
+    auto slot_of = [&](int z) -> const int32_t* {
+        return raw + ((int64_t(z - 1) * units + local) * g.nkb_part + (kb - part_first(kt_total, g.zsplit, z) / kt_per_block)) * slot_words;
+    };
+    int carry[4] = {0, 0, 0, 0};
+    constexpr int kBatch = 8;
+    for (int d_hi = S - 1; d_hi >= 1; d_hi -= kBatch) {
+        int t[kBatch][4];
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) t[q] += int(w << (24 - 8 * q)) >> 24;
-                } else {
+        for (int u = 0; u < kBatch; ++u)
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) t[q] += z == 0 ? tw[q * mp] : sT[(jl4 * 4 + q) * kUnit + il];
-                }
+            for (int q = 0; q < 4; ++q) t[u][q] = 0;
+        for (int z = z_lo; z <= z_hi; ++z) {
+            const uint32_t* src = z == 0 ? lw : reinterpret_cast<const uint32_t*>(slot_of(z) + kUnit * kUnit) + jl4 * kUnit + il;
+            const int64_t step = z == 0 ? plane : int64_t(kUnit / 4) * kUnit;
+            uint32_t w[kBatch];
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) w[u] = d_hi - u >= 1 ? src[(d_hi - u - 1) * step] : 0u;
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) t[u][q] += int(w[u] << (24 - 8 * q)) >> 24;
+        }
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            if (d_hi - u < 1) continue;
+            uint32_t w = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int v = t[u][q] + carry[q];
+                w |= (uint32_t(v) & 255u) << (8 * q);
+                carry[q] = (v + 128) >> 8;
             }
-            if (d > 0) {
-                uint32_t w = 0;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    w |= (uint32_t(t[q]) & 255u) << (8 * q);
-                    carry[q] = (t[q] + 128) >> 8;
-                }
-                *lw = w;
-            } else {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) tw[q * mp] = t[q];
-            }
+            lw[(d_hi - u - 1) * plane] = w;
         }
     }
+    for (int z = z_lo; z <= z_hi; ++z) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) carry[q] += z == 0 ? tw[q * mp] : slot_of(z)[(jl4 * 4 + q) * kUnit + il];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) tw[q * mp] = carry[q];
 }
 
 // Per-tile mode: the order in which the tiles of C are dealt to the workgroups.  An XCD runs its tiles in
@@ -910,7 +853,7 @@ __global__ __launch_bounds__(256) void tile_order_kernel(const int32_t* __restri
     }
 }
 
-void launch_gemm_i8(hipStream_t st, const Workspace& w, const Problem& p) {
+SplitPlan launch_gemm_i8(hipStream_t st, const Workspace& w, const Problem& p) {
     // the attribute is per device and cheap to set; no process-wide cache that a second device would miss
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_i8_kernel<false>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds);
@@ -960,7 +903,7 @@ void launch_gemm_i8(hipStream_t st, const Workspace& w, const Problem& p) {
                 const int64_t ns = steps * 4200 + 5000 + 6000 + int64_t(60) * units * z;
                 if (ns < best_ns) { best_ns = ns; best = Split{z, false}; }
             }
-            if (units <= raw_units) {
+            if (units == positions * per_pos) {      // (a product that is split as a whole)
                 const int64_t ns = steps * 4800 + 5000 + 12000 + int64_t(170) * units * z;
                 if (ns < best_ns) { best_ns = ns; best = Split{z, true}; }
             }
@@ -988,14 +931,11 @@ void launch_gemm_i8(hipStream_t st, const Workspace& w, const Problem& p) {
                                raw_units, p.s_cap, w.rec);
             hipLaunchKernelGGL(gemm_i8_kernel<true>, dim3(grid), dim3(256), kGemmLds, st, w.As, w.Bs, w.T, w.L, w.raw,
                                raw_units, p.mp, p.np, p.kp, p.s_cap, w.rec, g, tile_S);
-            hipLaunchKernelGGL(aggregate_raw_kernel, dim3(unsigned(units), unsigned(p.nkb), kUnit / 4 / kSplitRows), dim3(256),
-                               0, st, w.raw, raw_units, w.T, w.L, p.mp, p.np, p.kp, p.s_cap, g, w.rec, tile_S);
         } else {
             hipLaunchKernelGGL(gemm_i8_kernel<false>, dim3(grid), dim3(256), kGemmLds, st, w.As, w.Bs, w.T, w.L, w.raw,
                                raw_units, p.mp, p.np, p.kp, p.s_cap, w.rec, g, tile_S);
-            if (sp.z > 1)
-                hipLaunchKernelGGL(add_parts_kernel, dim3(unsigned(units), unsigned(p.nkb), kUnit / 4 / kSplitRows), dim3(256),
-                                   0, st, w.raw, w.T, w.L, p.mp, p.np, p.kp, p.s_cap, g, w.rec, tile_S);
+            if (sp.z > 1 && count < positions)
+                hipLaunchKernelGGL(add_parts_kernel, dim3(unsigned(units), unsigned(p.nkb), kUnit / 4 / 2), dim3(256), 0, st, w.raw, w.T, w.L, p.mp, p.np, p.kp, p.s_cap, g, w.rec, tile_S);
         }
     };
     // Units are dealt in rounds of one per CU.  A call with less than a round may be split along k as a whole;
@@ -1013,9 +953,10 @@ void launch_gemm_i8(hipStream_t st, const Workspace& w, const Problem& p) {
     if (two) {
         launch(0, full, Split{1, false});
         launch(full, rest, sp);
-    } else {
-        launch(0, positions, sp);
+        return SplitPlan{KSplit::kNone, g, raw_units};
     }
+    launch(0, positions, sp);
+    return SplitPlan{sp.z == 1 ? KSplit::kNone : (sp.atomic ? KSplit::kAtomic : KSplit::kParts), g, raw_units};
 }
 
 }  // namespace oz

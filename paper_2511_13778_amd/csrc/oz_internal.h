@@ -83,6 +83,59 @@ struct Workspace {
                            // entries again: the order in which the slice GEMM deals the tiles to its workgroups
 };
 
+// ---- geometry of the slice GEMM's launches, shared with the recomposition ----------------
+constexpr int kUnit = 128;            // edge of the unit of C a workgroup of the slice GEMM owns (four per kTile block)
+constexpr int kBK = 64;               // k per step (kKPad is a multiple)
+
+// What a launch of the slice GEMM covers.
+struct GemmGrid {
+    int nti, ntj;      // kTile x kTile blocks of the padded C
+    int um, un;        // units with at least one row / column of C
+    int begin, count;  // plain order: units [begin, begin + count); per-block order: as many positions of the order table
+    int zsplit;        // parts of the k range per unit
+    int nkb_part;      // k-blocks a part's slot has room for (parts other than the first)
+    int full_chip;     // 8 XCDs of 32 CUs: the in-step waits make sense
+    int persistent;    // a workgroup takes several units, and every unit has at least kMinUnitItems items
+};
+
+// How the whole product was split along k, for the recomposition to put together: not at all (the planes T / L are
+// complete), into parts that hold their own aggregated sums, or with integer atomics into raw sums.
+enum class KSplit { kNone, kParts, kAtomic };
+struct SplitPlan {
+    KSplit kind;
+    GemmGrid g;        // of the one launch that covered the product
+    int raw_units;     // 128 x 128 slots per plane of the raw buffer
+};
+
+// Where part z > 0 of unit `local` of a launch leaves its aggregated sums: a slot of the raw buffer holding, per
+// k-block the part touches, T [128 j][128 i] int32 and L [s_cap-1][32][128 i][4 j] int8 of the unit alone.
+__host__ __device__ inline int64_t part_slot_bytes(int s_cap) { return int64_t(kUnit) * kUnit * (4 + (s_cap - 1)); }
+
+// Position `lin` of the tile order -> tile coordinates, and back: panels of 8 tile columns, inside a panel row by row,
+// so 32 consecutive tiles form a 4 (i) x 8 (j) block.
+constexpr int kPanelTiles = 8;
+__host__ __device__ inline void lin_to_tile(int lin, int nti, int ntj, int& ti, int& tj) {
+    const int panel = lin / (kPanelTiles * nti);
+    const int in_panel = lin - panel * kPanelTiles * nti;
+    const int w = ntj - panel * kPanelTiles < kPanelTiles ? ntj - panel * kPanelTiles : kPanelTiles;
+    ti = in_panel / w;
+    tj = panel * kPanelTiles + in_panel % w;
+}
+__host__ __device__ inline int tile_to_lin(int ti, int tj, int nti, int ntj) {
+    const int panel = tj / kPanelTiles;
+    const int w = ntj - panel * kPanelTiles < kPanelTiles ? ntj - panel * kPanelTiles : kPanelTiles;
+    return panel * kPanelTiles * nti + ti * w + tj % kPanelTiles;
+}
+
+// k split: first 64 of k of part z, and the parts that have k in k-block kb
+__host__ __device__ inline int part_first(int kt_total, int zsplit, int z) { return int(int64_t(kt_total) * z / zsplit); }
+__host__ __device__ inline void parts_of_block(int kt_total, int kt_per_block, int zsplit, int kb, int& z_lo, int& z_hi) {
+    z_lo = 0;
+    while (z_lo + 1 < zsplit && part_first(kt_total, zsplit, z_lo + 1) <= kb * kt_per_block) ++z_lo;
+    z_hi = z_lo;
+    while (z_hi + 1 < zsplit && part_first(kt_total, zsplit, z_hi + 1) < (kb + 1) * kt_per_block) ++z_hi;
+}
+
 inline int64_t round_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
 
 // k-range one int32 accumulator can take: |digit product| <= 2^14, an anti-diagonal sums at most
@@ -108,8 +161,9 @@ void launch_verdict(hipStream_t st, const Workspace& w, const Problem& p, const 
 void launch_slice(hipStream_t st, const double* X, int64_t stride_r, int64_t stride_l,
                   int64_t rows, int64_t rows_p, const Problem& p, const int32_t* e_row,
                   int8_t* slices, const Record* rec);
-void launch_gemm_i8(hipStream_t st, const Workspace& w, const Problem& p);
-void launch_recompose(hipStream_t st, const Workspace& w, const Problem& p, double alpha,
+// returns what the recomposition still has to put together
+SplitPlan launch_gemm_i8(hipStream_t st, const Workspace& w, const Problem& p);
+void launch_recompose(hipStream_t st, const Workspace& w, const Problem& p, const SplitPlan& split, double alpha,
                       double beta, double* C, int64_t ldc);
 // rec == nullptr: run unconditionally; otherwise run only when rec->res.fallback != 0.
 // scratch (may be nullptr): device memory the kernel may use for partial products when it splits the

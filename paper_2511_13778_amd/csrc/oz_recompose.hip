@@ -15,6 +15,8 @@
 // added unscaled; the power of two applied last with ldexp; alpha*AB and beta*C rounded separately,
 // then added.
 // HBM-bound: (4 + S - 1) * nkb bytes read and 8 (+8 when beta != 0) bytes moved per element of C.
+#include <type_traits>
+
 #include "oz_internal.h"
 
 namespace oz {
@@ -22,8 +24,16 @@ namespace oz {
 constexpr int kRecI = 4;   // four consecutive i per thread: one 16-byte load of T per j, of L per digit
 constexpr int kRecJ = 4;   // four consecutive j per thread: the four bytes of an L dword
 
-__global__ __launch_bounds__(256) void recompose_kernel(const int32_t* __restrict__ T,
-                                                        const int8_t* __restrict__ L,
+// KIND: where the sums of a k-block come from.  kNone: the planes T / L, complete.  kParts: the planes hold part 0 of a
+// k split and the raw buffer the others, each with digits of its own; they are added digit by digit with the slice
+// GEMM's carry chain.  kAtomic: the raw buffer holds the unaggregated sums of every anti-diagonal, which go through
+// the same chain.  In both, the digits are those of the whole integer then; they are written back to T / L, and used
+// at once.  (A kernel of its own in between, with a thread walking its digits one load at a time, took 30-44 us of
+// a 1024^3 call's 180.)
+template <KSplit KIND>
+__global__ __launch_bounds__(256) void recompose_kernel(std::conditional_t<KIND == KSplit::kNone, const int32_t, int32_t>* __restrict__ T,
+                                                        std::conditional_t<KIND == KSplit::kNone, const int8_t, int8_t>* __restrict__ L,
+                                                        const int32_t* __restrict__ raw, SplitPlan split,
                                                         const int32_t* __restrict__ eA,
                                                         const int32_t* __restrict__ eB, int64_t m, int64_t n,
                                                         int64_t mp, int64_t np, int64_t kp, int s_cap,
@@ -44,8 +54,23 @@ __global__ __launch_bounds__(256) void recompose_kernel(const int32_t* __restric
     // (a 4 x 4 patch never straddles a block: kTile is a multiple of 4)
     const int S = tile_S ? min(tile_S[(j0 / kTile) * (mp / kTile) + i0 / kTile], S_all) : S_all;
     typedef int i32x4 __attribute__((ext_vector_type(4)));
-    const i32x4* t4 = reinterpret_cast<const i32x4*>(T);
-    const i32x4* l4 = reinterpret_cast<const i32x4*>(L);   // one dword = the four j of one i
+    typedef std::conditional_t<KIND == KSplit::kNone, const i32x4, i32x4> plane4;
+    plane4* t4 = reinterpret_cast<plane4*>(T);
+    plane4* l4 = reinterpret_cast<plane4*>(L);   // one dword = the four j of one i
+    // the unit of the slice GEMM this patch lies in (a patch never straddles units), and the patch inside it
+    int local = 0, units = 0;
+    const int il = int(i0) & (kUnit - 1), jl = int(j0) & (kUnit - 1);
+    if (KIND != KSplit::kNone) {
+        const GemmGrid& g = split.g;
+        const int ui = int(i0 / kUnit), uj = int(j0 / kUnit);
+        if (tile_S) {      // per-block order of a split product: position = block, quadrants one after the other
+            units = 4 * g.count;
+            local = ((ui & 1) + 2 * (uj & 1)) * g.count + tile_to_lin(ui >> 1, uj >> 1, g.nti, g.ntj);
+        } else {
+            units = g.count;
+            local = tile_to_lin(ui, uj, g.um, g.un);
+        }
+    }
     // C is requested first (when it is read at all), then the planes of each k-block in batches: all
     // loads of a batch are in flight together before the first digit is consumed
     double cin[kRecJ][kRecI];
@@ -72,43 +97,130 @@ __global__ __launch_bounds__(256) void recompose_kernel(const int32_t* __restric
 #pragma unroll
         for (int q = 0; q < kRecI; ++q) R[jj][q] = 0.0;
     constexpr int kBatch = 8;
+    const int kt_total = int(kp / kBK), kt_per_block = int(kblk / kBK);
     for (int kb = 0; kb < nkb; ++kb) {
         // the planes are read once: streaming loads keep them out of the way of C
+        const int64_t t_at = ((int64_t(kb) * np + j0) * mp + i0) / 4;                               // + jj * mp / 4
+        const int64_t l_at = ((int64_t(kb) * (s_cap - 1) * (np / 4) + j4) * mp + i0) / 4;           // + (d-1) * l_step
+        const int64_t l_step = (np / 4) * mp / 4;
+        int z_lo = 0, z_hi = 0;
+        if (KIND == KSplit::kParts) parts_of_block(kt_total, kt_per_block, split.g.zsplit, kb, z_lo, z_hi);
+        auto slot_of = [&](int z) -> const i32x4* {     // part z's T of this patch's unit
+            return reinterpret_cast<const i32x4*>(raw) +
+                   ((int64_t(z - 1) * units + local) * split.g.nkb_part + (kb - part_first(kt_total, split.g.zsplit, z) / kt_per_block)) *
+                       (part_slot_bytes(s_cap) / 16) + il / 4;
+        };
+        // raw sums of anti-diagonal d: element (j, i) of the unit's slot
+        auto raw_of = [&](int d) -> const i32x4* {
+            return reinterpret_cast<const i32x4*>(raw) +
+                   ((int64_t(kb) * s_cap + d) * split.raw_units + local) * (kUnit * kUnit / 4) + (jl * kUnit + il) / 4;
+        };
         i32x4 tv[kRecJ];
 #pragma unroll
-        for (int jj = 0; jj < kRecJ; ++jj)
-            tv[jj] = __builtin_nontemporal_load(&t4[((int64_t(kb) * np + j0 + jj) * mp + i0) / 4]);
-        double Rb[kRecJ][kRecI];
+        for (int jj = 0; jj < kRecJ; ++jj) {
+            if (KIND != KSplit::kNone) tv[jj] = i32x4{0, 0, 0, 0};
+            if (KIND == KSplit::kAtomic) tv[jj] = raw_of(0)[jj * (kUnit / 4)];
+            else if (KIND == KSplit::kNone || z_lo == 0)
+                tv[jj] = __builtin_nontemporal_load(&t4[((int64_t(kb) * np + j0 + jj) * mp + i0) / 4]);
+        }
+        if (KIND == KSplit::kParts)
+            for (int z = max(z_lo, 1); z <= z_hi; ++z)
 #pragma unroll
-        for (int jj = 0; jj < kRecJ; ++jj)
+                for (int jj = 0; jj < kRecJ; ++jj) tv[jj] += slot_of(z)[(jl + jj) * (kUnit / 4)];
+        double Rb[kRecJ][kRecI];
+        i32x4 carry[kRecJ];
+#pragma unroll
+        for (int jj = 0; jj < kRecJ; ++jj) {
+            carry[jj] = i32x4{0, 0, 0, 0};
 #pragma unroll
             for (int q = 0; q < kRecI; ++q) Rb[jj][q] = 0.0;
-        for (int d_hi = S - 1; d_hi >= 1; d_hi -= kBatch) {
-            i32x4 w[kBatch];
+        }
+        if constexpr (KIND == KSplit::kAtomic) {
+            for (int d = S - 1; d >= 1; --d) {
+                i32x4 w = {0, 0, 0, 0};
 #pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                const int d = d_hi - u;
-                if (d >= 1)
-                    w[u] = __builtin_nontemporal_load(
-                        &l4[(((int64_t(kb) * (s_cap - 1) + (d - 1)) * (np / 4) + j4) * mp + i0) / 4]);
+                for (int jj = 0; jj < kRecJ; ++jj) {
+                    const i32x4 v = raw_of(d)[jj * (kUnit / 4)] + carry[jj];
+                    carry[jj] = (v + 128) >> 8;
+                    w |= (v & 255) << (8 * jj);
+#pragma unroll
+                    for (int q = 0; q < kRecI; ++q) Rb[jj][q] = double((v[q] << 24) >> 24) + Rb[jj][q] * 0x1p-8;
+                }
+                l4[l_at + (d - 1) * l_step] = w;
             }
+        } else {
+            for (int d_hi = S - 1; d_hi >= 1; d_hi -= kBatch) {
+                i32x4 w[kBatch];
 #pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                if (d_hi - u >= 1) {
+                for (int u = 0; u < kBatch; ++u) {
+                    const int d = d_hi - u;
+                    if (KIND != KSplit::kNone) w[u] = i32x4{0, 0, 0, 0};
+                    if (d >= 1 && (KIND == KSplit::kNone || z_lo == 0))
+                        w[u] = __builtin_nontemporal_load(&l4[(((int64_t(kb) * (s_cap - 1) + (d - 1)) * (np / 4) + j4) * mp + i0) / 4]);
+                }
+                if constexpr (KIND == KSplit::kParts) {
+                    // the four digits of a dword are added as two pairs of 16-bit fields, biased so that no field borrows:
+                    // field = digit + 128 per part
+                    i32x4 even[kBatch], odd[kBatch];
+                    const bool main_counts = z_lo == 0;
 #pragma unroll
-                    for (int q = 0; q < kRecI; ++q)
+                    for (int u = 0; u < kBatch; ++u) {
+                        const i32x4 x = w[u] ^ int(0x80808080);
+                        even[u] = main_counts ? x & 0x00FF00FF : i32x4{0, 0, 0, 0};
+                        odd[u] = main_counts ? (x >> 8) & 0x00FF00FF : i32x4{0, 0, 0, 0};
+                    }
+                    for (int z = max(z_lo, 1); z <= z_hi; ++z) {
+                        const i32x4* src = slot_of(z) + kUnit * kUnit / 4 + (jl / 4) * (kUnit / 4);
+                        i32x4 y[kBatch];
+#pragma unroll
+                        for (int u = 0; u < kBatch; ++u)
+                            y[u] = d_hi - u >= 1 ? src[(d_hi - u - 1) * (kUnit / 4) * (kUnit / 4)] : i32x4{0, 0, 0, 0};
+#pragma unroll
+                        for (int u = 0; u < kBatch; ++u) {
+                            const i32x4 x = y[u] ^ int(0x80808080);
+                            even[u] += x & 0x00FF00FF;
+                            odd[u] += (x >> 8) & 0x00FF00FF;
+                        }
+                    }
+                    const int bias = 128 * (z_hi - z_lo + 1);
+#pragma unroll
+                    for (int u = 0; u < kBatch; ++u) {
+                        if (d_hi - u < 1) continue;
+                        i32x4 out = {0, 0, 0, 0};
 #pragma unroll
                         for (int jj = 0; jj < kRecJ; ++jj) {
-                            const int digit = (w[u][q] << (24 - 8 * jj)) >> 24;       // sign-extended byte jj
-                            Rb[jj][q] = double(digit) + Rb[jj][q] * 0x1p-8;
+                            const i32x4 f = (jj & 1) ? odd[u] : even[u];
+                            const i32x4 v = ((jj & 2) ? (f >> 16) & 0xFFFF : f & 0xFFFF) - bias + carry[jj];
+                            carry[jj] = (v + 128) >> 8;
+                            out |= (v & 255) << (8 * jj);
                         }
+                        w[u] = out;
+                        l4[l_at + (d_hi - u - 1) * l_step] = out;
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < kBatch; ++u) {
+                    if (d_hi - u >= 1) {
+#pragma unroll
+                        for (int q = 0; q < kRecI; ++q)
+#pragma unroll
+                            for (int jj = 0; jj < kRecJ; ++jj) {
+                                const int digit = (w[u][q] << (24 - 8 * jj)) >> 24;       // sign-extended byte jj
+                                Rb[jj][q] = double(digit) + Rb[jj][q] * 0x1p-8;
+                            }
+                    }
                 }
             }
         }
 #pragma unroll
-        for (int jj = 0; jj < kRecJ; ++jj)
+        for (int jj = 0; jj < kRecJ; ++jj) {
+            if constexpr (KIND != KSplit::kNone) {
+                tv[jj] += carry[jj];
+                t4[t_at + jj * (mp / 4)] = tv[jj];
+            }
 #pragma unroll
             for (int q = 0; q < kRecI; ++q) R[jj][q] = R[jj][q] + (double(tv[jj][q]) + Rb[jj][q] * 0x1p-8);
+        }
     }
     const int4 ea4 = *reinterpret_cast<const int4*>(eA + i0);
     const int ea[4] = {ea4.x, ea4.y, ea4.z, ea4.w};
@@ -146,15 +258,24 @@ __global__ __launch_bounds__(256) void scale_c_kernel(int64_t m, double beta, do
     C[j * ldc + i] = (beta == 0.0) ? 0.0 : __dmul_rn(beta, C[j * ldc + i]);
 }
 
-void launch_recompose(hipStream_t st, const Workspace& w, const Problem& p, double alpha, double beta,
+void launch_recompose(hipStream_t st, const Workspace& w, const Problem& p, const SplitPlan& split, double alpha, double beta,
                       double* C, int64_t ldc) {
     const unsigned gx = unsigned((p.m + 256 * kRecI - 1) / (256 * kRecI));
     const int64_t n4 = (p.n + kRecJ - 1) / kRecJ;
     const int c_vec = (reinterpret_cast<uintptr_t>(C) % 16 == 0 && ldc % 2 == 0) ? 1 : 0;
     for (int64_t j4 = 0; j4 < n4; j4 += 65535) {
         const unsigned gy = unsigned(n4 - j4 < 65535 ? n4 - j4 : 65535);
-        hipLaunchKernelGGL(recompose_kernel, dim3(gx, gy), dim3(256), 0, st, w.T, w.L, w.eA, w.eB, p.m, p.n, p.mp,
-                           p.np, p.kp, p.s_cap, alpha, beta, C, ldc, w.rec, p.tile_mode ? w.tile_S : nullptr, j4, c_vec);
+        const int32_t* tile_S = p.tile_mode ? w.tile_S : nullptr;
+        const dim3 grid(gx, gy), block(256);
+        if (split.kind == KSplit::kParts)
+            hipLaunchKernelGGL(recompose_kernel<KSplit::kParts>, grid, block, 0, st, w.T, w.L, w.raw, split, w.eA, w.eB, p.m,
+                               p.n, p.mp, p.np, p.kp, p.s_cap, alpha, beta, C, ldc, w.rec, tile_S, j4, c_vec);
+        else if (split.kind == KSplit::kAtomic)
+            hipLaunchKernelGGL(recompose_kernel<KSplit::kAtomic>, grid, block, 0, st, w.T, w.L, w.raw, split, w.eA, w.eB, p.m,
+                               p.n, p.mp, p.np, p.kp, p.s_cap, alpha, beta, C, ldc, w.rec, tile_S, j4, c_vec);
+        else
+            hipLaunchKernelGGL(recompose_kernel<KSplit::kNone>, grid, block, 0, st, w.T, w.L, w.raw, split, w.eA, w.eB, p.m,
+                               p.n, p.mp, p.np, p.kp, p.s_cap, alpha, beta, C, ldc, w.rec, tile_S, j4, c_vec);
     }
 }
 
