@@ -250,8 +250,8 @@ oz_status_t oz_dgemm_layout(oz_handle_t handle, char transa, char transb,
 /* Stage timing with HIP events on the call's own stream.  oz_profile_enable(h, n) makes the
  * next n oz_dgemm calls record an event after every stage; oz_profile_read(h, call, ms)
  * (after the stream has been synchronised by the caller) writes OZ_NUM_STAGES durations in
- * milliseconds.  Stages: 0 scan (Inf/NaN + exponent min/max), 1 ESC, 2 verdict,
- * 3 slicing, 4 slice-pair INT8 GEMMs, 5 FP64 recomposition, 6 native FP64 GEMM. */
+ * milliseconds.  Stages: 0 scan (Inf/NaN + exponent min/max), 1 ESC, 2 verdict (about 0: the ESC
+ * kernel's last workgroup gives it), 3 slicing, 4 slice-pair INT8 GEMMs, 5 FP64 recomposition, 6 native FP64 GEMM. */
 #define OZ_NUM_STAGES 7
 oz_status_t oz_profile_enable(oz_handle_t handle, int32_t max_calls);
 oz_status_t oz_profile_read(oz_handle_t handle, int32_t call, float* stage_ms);

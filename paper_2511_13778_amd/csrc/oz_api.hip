@@ -344,7 +344,7 @@ oz_status_t oz_native_dgemm(oz_handle_t h, void* stream, char transa, char trans
     if (!on_handle_device(*h)) return OZ_ERR_DEVICE;
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (k == 0 || alpha == 0.0) launch_scale_c(st, m, n, beta, C, ldc);
-    else launch_dgemm_f64(st, nullptr, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc);
+    else launch_dgemm_f64(st, nullptr, KnownRecord{}, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc);
     return hipGetLastError() == hipSuccess ? OZ_OK : OZ_ERR_HIP;
 }
 
@@ -383,7 +383,7 @@ oz_status_t dgemm_impl(oz_handle_t h, void* stream, char transa, char transb, in
 
     if (k == 0 || alpha == 0.0) {
         // BLAS convention: nothing to multiply
-        launch_verdict(st, w, p, *opts, h->hm, 2, result);
+        launch_known_record(st, KnownRecord{w.rec, result, known_verdict(p, *opts, 2)});
         launch_scale_c(st, m, n, beta, C, ldc);
         for (int s = 0; s < OZ_NUM_STAGES; ++s) clk.done(s);
         return hipGetLastError() == hipSuccess ? OZ_OK : OZ_ERR_HIP;
@@ -394,9 +394,8 @@ oz_status_t dgemm_impl(oz_handle_t h, void* stream, char transa, char transb, in
     const int64_t b_sr = tb ? 1 : ldb, b_sl = tb ? ldb : 1;
 
     if (opts->mode == OZ_NATIVE) {
-        launch_verdict(st, w, p, *opts, h->hm, 0, result);
         for (int s = 0; s <= 5; ++s) clk.done(s);
-        launch_dgemm_f64(st, nullptr, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, f64_scratch, f64_scratch_bytes);
+        launch_dgemm_f64(st, nullptr, KnownRecord{w.rec, result, known_verdict(p, *opts, 0)}, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, f64_scratch, f64_scratch_bytes);
         clk.done(6);
         return hipGetLastError() == hipSuccess ? OZ_OK : OZ_ERR_HIP;
     }
@@ -407,32 +406,28 @@ oz_status_t dgemm_impl(oz_handle_t h, void* stream, char transa, char transb, in
         int s_min = (opts->target_bits + 1 + 1 + kHeadroomBits + 7) / 8;
         if (s_min > kMaxSlices) s_min = kMaxSlices;
         if (emulation_slower(h->hm, s_min, m, n, k)) {
-            launch_verdict(st, w, p, *opts, h->hm, 3, result);
             for (int s = 0; s <= 5; ++s) clk.done(s);
-            launch_dgemm_f64(st, nullptr, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, f64_scratch, f64_scratch_bytes);
+            launch_dgemm_f64(st, nullptr, KnownRecord{w.rec, result, known_verdict(p, *opts, 3)}, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, f64_scratch, f64_scratch_bytes);
             clk.done(6);
             return hipGetLastError() == hipSuccess ? OZ_OK : OZ_ERR_HIP;
         }
     }
 
     const bool guarded = opts->mode != OZ_FIXED_UNGUARDED;
-    launch_init(st, w, p);
-    launch_scan(st, A, a_sr, a_sl, m, p.mp, p, w.U, /*max_first=*/true, w.eA, w.rec, guarded);
-    launch_scan(st, B, b_sr, b_sl, n, p.np, p, w.V, /*max_first=*/false, w.eB, w.rec, guarded);
+    const Operand oa{A, a_sr, a_sl, m, p.mp}, ob{B, b_sr, b_sl, n, p.np};
+    launch_init(st, w, p, guarded ? KnownRecord{} : KnownRecord{w.rec, result, known_verdict(p, *opts, 0)});
+    launch_scan(st, oa, ob, w, p, guarded);
     clk.done(0);
-    if (guarded) launch_esc(st, w, p);
+    if (guarded) launch_esc_verdict(st, w, p, *opts, h->hm, result);
     clk.done(1);
-    if (p.tile_mode) launch_tile_verdict(st, w, p, *opts);
-    launch_verdict(st, w, p, *opts, h->hm, guarded ? 1 : 0, result);
-    clk.done(2);
-    launch_slice(st, A, a_sr, a_sl, m, p.mp, p, w.eA, w.As, w.rec);
-    launch_slice(st, B, b_sr, b_sl, n, p.np, p, w.eB, w.Bs, w.rec);
+    clk.done(2);          // the verdict is given by the last workgroup of the ESC kernel
+    launch_slice(st, oa, ob, w, p);
     clk.done(3);
     const SplitPlan split = launch_gemm_i8(st, w, p);
     clk.done(4);
     launch_recompose(st, w, p, split, alpha, beta, C, ldc);
     clk.done(5);
-    if (guarded) launch_dgemm_f64(st, w.rec, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, f64_scratch, f64_scratch_bytes);
+    if (guarded) launch_dgemm_f64(st, w.rec, KnownRecord{}, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, f64_scratch, f64_scratch_bytes);
     clk.done(6);
     return hipGetLastError() == hipSuccess ? OZ_OK : OZ_ERR_HIP;
 }

@@ -107,7 +107,7 @@ __device__ __forceinline__ void dg_store(const double (&v)[T / 16], double* lds)
 // fit the 32-bit offsets of the fast loads).
 template <bool A_ROWS_CONTIG, bool B_ROWS_CONTIG, int MODE, int T>
 __global__ __launch_bounds__(256, 2) void dgemm_f64_kernel(
-    const Record* rec, int64_t m, int64_t n, int64_t k, double alpha, const double* __restrict__ A,
+    const Record* rec, KnownRecord known, int64_t m, int64_t n, int64_t k, double alpha, const double* __restrict__ A,
     int64_t a_sr, int64_t a_sl, const double* __restrict__ B, int64_t b_sr, int64_t b_sl, double beta,
     double* __restrict__ C, int64_t ldc, int ntm, int ntn, int zsplit, int64_t kpart, double* __restrict__ partial) {
     constexpr bool EDGE = MODE == 2;                       // bounds-checked loads in the K loop
@@ -120,6 +120,7 @@ __global__ __launch_bounds__(256, 2) void dgemm_f64_kernel(
     __shared__ double At[2][kDK * kDLd];
     __shared__ double Bt[2][kDK * kDLd];
     if (rec && !rec->res.fallback) return;
+    if (blockIdx.x == 0 && threadIdx.x == 0) write_known_record(known);
 
     // Workgroup ids are dealt round-robin to the 8 XCDs; each XCD gets a contiguous range of a tile
     // order in which 64 consecutive tiles (what an XCD runs at a time: 32 CUs, two workgroups each)
@@ -311,7 +312,7 @@ __global__ __launch_bounds__(256) void dgemm_f64_reduce_kernel(const Record* rec
     C[j * ldc + i] = out;
 }
 
-void launch_dgemm_f64(hipStream_t st, const Record* rec, bool ta, bool tb, int64_t m, int64_t n, int64_t k,
+void launch_dgemm_f64(hipStream_t st, const Record* rec, const KnownRecord& known, bool ta, bool tb, int64_t m, int64_t n, int64_t k,
                       double alpha, const double* A, int64_t lda, const double* B, int64_t ldb, double beta,
                       double* C, int64_t ldc, void* scratch, size_t scratch_bytes) {
     // op(A)(i,l): N -> A[i + l*lda] (rows contiguous), T -> A[l + i*lda]
@@ -377,7 +378,7 @@ void launch_dgemm_f64(hipStream_t st, const Record* rec, bool ta, bool tb, int64
     // k < 16: the fast loads always fetch a full K step, which such a matrix does not have
     const int mode = (wide_ld || k < kDK) ? 2 : (((m % T) || (n % T) || (k % kDK)) ? 1 : 0);
 #define OZ_DG_M(AC, BC, MODE, TT)                                                                              \
-    hipLaunchKernelGGL((dgemm_f64_kernel<AC, BC, MODE, TT>), grid, block, 0, st, rec, m, n, k, alpha, A, a_sr, \
+    hipLaunchKernelGGL((dgemm_f64_kernel<AC, BC, MODE, TT>), grid, block, 0, st, rec, known, m, n, k, alpha, A, a_sr, \
                        a_sl, B, b_sr, b_sl, beta, C, ldc, ntm, ntn, zsplit, kpart, partial)
 #define OZ_DG_T(AC, BC, TT)                                                                                    \
     {                                                                                                          \

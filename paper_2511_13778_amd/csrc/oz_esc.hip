@@ -7,8 +7,8 @@
 //   zt_ij = max_h ( U[h][i] + V[h][j] ),  U = [Max(xb); Min(xb)],  V = [Min(yb); Max(yb)],
 // followed by  span = max_ij ( eA_i + eB_j - zt_ij ).
 //
-// Two kernels compute it.
-//  * esc_mfma_kernel (always runs): the max-plus product mapped onto the BF16 matrix unit.
+// Two ways to compute it, in one kernel (esc_kernel), block of 128 x 128 pairs by block.
+//  * On the BF16 matrix unit.
 //    With u = U[h][i] - eA_i <= 0 and v = V[h][j] - eB_j <= 0 the table entries are encoded as
 //    the powers of two 2^(5u+61) and 2^(5v+61) (exact in BF16; entries below -37 and the "zero"
 //    sentinels become 0).  One MFMA sums 16 such products in FP32; all terms are non-negative, so
@@ -16,10 +16,14 @@
 //    order and rounding of the accumulation, and floor((exponent(sum) - 122) / 5) = t exactly.
 //    The running maximum over the chunks of 16 is kept on the raw FP32 bit patterns.  A pair
 //    whose result is below -37 (or has no candidate at all) may have lost candidates to the
-//    clamping, so it raises rec->esc_exact instead of contributing.
-//  * esc_kernel (runs only when that flag is set): the same product on the vector ALU with packed
-//    int16 add/max over the unencoded tables, one lane instruction per two (i,j) pairs.
+//    clamping, so its block is computed again the other way.
+//  * On the vector ALU with packed int16 add/max over the unencoded tables, one lane instruction per two
+//    (i,j) pairs: exact for every span, 8 times slower.
 // Both give the exact coarsened ESC; the first covers spans up to 37 bits at matrix-unit speed.
+// The last workgroup of the kernel gives the verdict and, in per-block mode, the slice counts of the blocks and the order
+// they are dealt in: what were up to four more launches of 4-5 us each, in which one workgroup did something or none.
+#include <algorithm>
+
 #include "oz_internal.h"
 
 namespace oz {
@@ -35,13 +39,18 @@ constexpr int kEncRange = 37;    // 5*(-37) + 61 >= -126: smallest encodable ent
 constexpr int kEncChunk = 16;    // inner steps per MFMA (K of v_mfma_f32_32x32x16_bf16)
 
 // enc[(h/8) * rows_p + r][h%8] = BF16 bits of 2^(5*(tab[h][r] - e[r]) + 61), or 0
-__global__ __launch_bounds__(256) void esc_encode_kernel(const int16_t* __restrict__ tab,
-                                                         const int32_t* __restrict__ e,
-                                                         int64_t rows_p, int H2,
-                                                         uint4* __restrict__ enc) {
-    const int64_t r = int64_t(blockIdx.x) * 256 + threadIdx.x;
+// grid (mp/256 + np/256, groups of 8 h): the first mp/256 workgroups along x encode U, the others V
+__global__ __launch_bounds__(256) void esc_encode_kernel(const int16_t* __restrict__ U, const int32_t* __restrict__ eA,
+                                                         int64_t mp, uint4* __restrict__ EU, const int16_t* __restrict__ V,
+                                                         const int32_t* __restrict__ eB, int64_t np, uint4* __restrict__ EV,
+                                                         int H2) {
+    const int64_t blocks_u = mp / 256;
+    const bool second = int64_t(blockIdx.x) >= blocks_u;
+    const int16_t* tab = second ? V : U;
+    const int64_t rows_p = second ? np : mp;
+    const int64_t r = (int64_t(blockIdx.x) - (second ? blocks_u : 0)) * 256 + threadIdx.x;
     const int hc = blockIdx.y;
-    const int er = e[r];
+    const int er = second ? eB[r] : eA[r];
     uint32_t w[4];
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
@@ -55,20 +64,177 @@ __global__ __launch_bounds__(256) void esc_encode_kernel(const int16_t* __restri
         }
         if (q & 1) w[q >> 1] |= bits << 16; else w[q >> 1] = bits;
     }
-    enc[int64_t(hc) * rows_p + r] = make_uint4(w[0], w[1], w[2], w[3]);
+    (second ? EV : EU)[int64_t(hc) * rows_p + r] = make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-// grid (mp/128, np/128); 4 waves of 64x64 pairs, 2x2 MFMA tiles of 32x32 each.
-__global__ __launch_bounds__(256) void esc_mfma_kernel(const uint4* __restrict__ EU,
-                                                       const uint4* __restrict__ EV, int64_t m,
-                                                       int64_t n, int64_t mp, int64_t np,
-                                                       int steps, Record* rec,
-                                                       int32_t* __restrict__ tile_span) {
-    if (rec->infnan) return;
+typedef short short2_t __attribute__((ext_vector_type(2)));
+typedef short short8_t __attribute__((ext_vector_type(8)));
+
+constexpr int kEscTile = 128;   // pairs (i,j) per workgroup and direction
+constexpr int kEscHChunk = 32;  // inner steps staged in LDS at a time (int16 way)
+constexpr short kEscPadValue = -16384;  // two of them add to the int16 minimum without wrapping
+static_assert(kTile == 2 * kEscTile, "four ESC blocks per block of C");
+
+struct EscLds {
+    union {
+        struct { short8_t Ut[kEscHChunk][kEscTile / 8], Vt[kEscHChunk][kEscTile / 8]; } exact;
+        struct { int cnt[kMaxSlices + 1][256]; int base[kMaxSlices + 1]; } order;
+    };
+    uint32_t least[4];
+    unsigned long long pairs[4];
+    int smin[4];
+    int last, stop;
+};
+
+// Largest span of a block of 128 x 128 pairs the exact way (16 x 16 threads of 8 x 8 pairs); of all threads.
+__device__ __forceinline__ int exact_span(EscLds& lds, const int16_t* __restrict__ U, const int16_t* __restrict__ V,
+                                          const int32_t* __restrict__ eA, const int32_t* __restrict__ eB, int64_t mp, int64_t np,
+                                          int H2, int64_t i0, int64_t j0) {
+    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+
+    short2_t acc[8][4];
+#pragma unroll
+    for (int a = 0; a < 8; ++a)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[a][c] = short2_t{-32768, -32768};
+
+    for (int h0 = 0; h0 < H2; h0 += kEscHChunk) {
+        __syncthreads();
+        // 32 x 128 int16 per table = 512 vectors of 8; two per thread
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int v = threadIdx.x + t * 256;
+            const int hh = v >> 4, col = v & 15;
+            short8_t uu, vv;
+            if (h0 + hh < H2) {
+                uu = *reinterpret_cast<const short8_t*>(U + int64_t(h0 + hh) * mp + i0 + col * 8);
+                vv = *reinterpret_cast<const short8_t*>(V + int64_t(h0 + hh) * np + j0 + col * 8);
+            } else {
+                uu = short8_t(kEscPadValue);
+                vv = short8_t(kEscPadValue);
+            }
+            lds.exact.Ut[hh][col] = uu;
+            lds.exact.Vt[hh][col] = vv;
+        }
+        __syncthreads();
+#pragma unroll 4
+        for (int hh = 0; hh < kEscHChunk; ++hh) {
+            const short8_t u = lds.exact.Ut[hh][ty];
+            const short8_t v = lds.exact.Vt[hh][tx];
+            const short2_t v2[4] = {short2_t{v[0], v[1]}, short2_t{v[2], v[3]},
+                                    short2_t{v[4], v[5]}, short2_t{v[6], v[7]}};
+#pragma unroll
+            for (int a = 0; a < 8; ++a) {
+                const short2_t ua = short2_t{u[a], u[a]};
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    acc[a][c] = __builtin_elementwise_max(acc[a][c], ua + v2[c]);
+            }
+        }
+    }
+
+    int best = 0;
+#pragma unroll
+    for (int a = 0; a < 8; ++a) {
+        const int ea = eA[i0 + ty * 8 + a];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int z = acc[a][c][q];
+                const int eb = eB[j0 + tx * 8 + c * 2 + q];
+                int span;
+                if (z >= kSumRealFloor) span = ea + eb - z;          // a real exponent sum
+                else if (z >= kSumDeadBelow) span = kEscCap;          // no candidate: unbounded
+                else span = 0;                                        // identically zero product
+                best = max(best, span);
+            }
+        }
+    }
+    return best;
+}
+
+// Per-tile mode: the order in which the tiles of C are dealt to the workgroups.  An XCD runs its tiles in
+// rounds of 32 that keep in step to share panels in L2; a round that mixes tiles of different slice counts
+// falls out of step when its light tiles finish (their successors wait in vain for the heavy ones and then
+// run alone: measured 18.0 ms instead of 13.9 ms for 64 ten-slice tiles lying in one block column).  So the
+// tiles are sorted by slice count, heaviest first and otherwise in the usual block order, and the sorted
+// groups of 32 are dealt to the XCDs in turn: group g is round g / 8 of XCD g % 8.  Rounds are then uniform
+// but for one per slice count, the heavy rounds are spread over the XCDs, and the lightest tiles end up in
+// the partial last round or the k-split launch.  `first` = tiles of the first launch (its XCD ranges are what
+// the groups are dealt into), of which the leading first / 256 * 256 sorted tiles are dealt; the others keep
+// the sorted order in the positions that remain.  order[position] = index of the tile in the block order.
+// One workgroup; a stable counting sort over the slice counts 0 .. kMaxSlices.
+constexpr int kOrderRound = 32;
+__device__ __forceinline__ void tile_order(EscLds& lds, const int32_t* tile_S, int32_t* order, int nti, int ntj, int first, int deal) {
+    const int tiles = nti * ntj, tid = threadIdx.x;
+    if (!deal) {
+        for (int lin = tid; lin < tiles; lin += 256) order[lin] = lin;
+        return;
+    }
+    int (*const cnt)[256] = lds.order.cnt;
+    int* const base = lds.order.base;
+    const int chunk = (tiles + 255) / 256;
+    const int lo = min(tiles, tid * chunk), hi = min(tiles, lo + chunk);
+    auto key_of = [&](int lin) -> int {
+        int ti, tj;
+        lin_to_tile(lin, nti, ntj, ti, tj);
+        return min(max(tile_S[tj * nti + ti], 0), kMaxSlices);
+    };
+    for (int k = 0; k <= kMaxSlices; ++k) cnt[k][tid] = 0;
+    for (int lin = lo; lin < hi; ++lin) ++cnt[key_of(lin)][tid];
+    __syncthreads();
+    if (tid <= kMaxSlices) {      // exclusive prefix over the threads' chunks, per key
+        int run = 0;
+        for (int t = 0; t < 256; ++t) {
+            const int c = cnt[tid][t];
+            cnt[tid][t] = run;
+            run += c;
+        }
+        base[tid] = run;
+    }
+    __syncthreads();
+    if (tid == 0) {               // keys in descending order
+        int run = 0;
+        for (int k = kMaxSlices; k >= 0; --k) {
+            const int c = base[k];
+            base[k] = run;
+            run += c;
+        }
+    }
+    __syncthreads();
+    const int per = first >> 3, rem = first & 7, rounds = first / (8 * kOrderRound), dealt = rounds * 8 * kOrderRound;
+    for (int lin = lo; lin < hi; ++lin) {
+        const int k = key_of(lin);
+        const int si = base[k] + cnt[k][tid]++;      // position in the sorted sequence
+        int q = si;
+        if (si < dealt) {
+            const int g = si / kOrderRound, wpos = si % kOrderRound, r = g >> 3, x = g & 7;
+            q = x * per + min(x, rem) + r * kOrderRound + wpos;
+        } else if (si < first) {
+            // what is left of the XCD ranges behind their dealt rounds, XCD by XCD
+            int t = si - dealt;
+            for (int x = 0; x < 8; ++x) {
+                const int left = per + (x < rem ? 1 : 0) - rounds * kOrderRound;
+                if (t < left) {
+                    q = x * per + min(x, rem) + rounds * kOrderRound + t;
+                    break;
+                }
+                t -= left;
+            }
+        }
+        order[q] = lin;
+    }
+}
+
+// Smallest of the block's chunk-maximum sums as FP32 bit patterns (0xFFFFFFFF: the block holds padding only); of
+// all threads.  4 waves of 64x64 pairs, 2x2 MFMA tiles of 32x32 each.
+__device__ __forceinline__ uint32_t least_sum(const uint4* __restrict__ EU, const uint4* __restrict__ EV, int64_t m,
+                                              int64_t n, int64_t mp, int64_t np, int steps, int64_t bi, int64_t bj) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int lr = lane & 31, lh = lane >> 5;
-    const int64_t i0 = int64_t(blockIdx.x) * 128 + (wave & 1) * 64;
-    const int64_t j0 = int64_t(blockIdx.y) * 128 + (wave >> 1) * 64;
+    const int64_t i0 = bi * kEscTile + (wave & 1) * 64;
+    const int64_t j0 = bj * kEscTile + (wave >> 1) * 64;
     const uint4* pa = EU + int64_t(lh) * mp + i0 + lr;
     const uint4* pb = EV + int64_t(lh) * np + j0 + lr;
 
@@ -145,178 +311,40 @@ __global__ __launch_bounds__(256) void esc_mfma_kernel(const uint4* __restrict__
                 const int64_t j = j0 + b * 32 + lr;
                 if (i < m && j < n) least = min(least, run[a][b][r]);
             }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) least = min(least, uint32_t(__shfl_xor(int(least), off)));
-    __shared__ uint32_t wave_least[4];
-    if (lane == 0) wave_least[wave] = least;
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-    least = min(min(wave_least[0], wave_least[1]), min(wave_least[2], wave_least[3]));
-    if (least == 0xFFFFFFFFu) return;               // the tile holds padding only
-    // exponent(sum) - 122 lies in [5t, 5t+4]; shifted by 5*64 so that the division is of a
-    // non-negative number
-    const int E = int(least >> 23) - 127 - 2 * kEncBias;
-    const int t = (E + kEncScale * 64) / kEncScale - 64;
-    if (t < -kEncRange) {
-        // Below the encodable range (or no candidate at all): the int16 kernel visits every pair,
-        // including the ones this tile resolved, so nothing else needs to be recorded here.
-        atomicOr(&rec->esc_exact, 1);
-    } else {
-        // this 128 x 128 block is resolved exactly: its largest span goes to the C block it lies in
-        // (four such blocks per kTile x kTile block) and to the global maximum
-        atomicMax(&tile_span[(blockIdx.y >> 1) * (mp / kTile) + (blockIdx.x >> 1)], -t);
-        // a stale read only costs a redundant atomic; the maximum is monotone
-        if (-t > *reinterpret_cast<volatile int32_t*>(&rec->span_max)) atomicMax(&rec->span_max, -t);
-    }
+    return least;
 }
 
-typedef short short2_t __attribute__((ext_vector_type(2)));
-typedef short short8_t __attribute__((ext_vector_type(8)));
+// What the host knows of the decision.
+struct VerdictArgs {
+    oz_opts_t o;
+    oz_heuristic_t hm;
+    int32_t s_cap, tile_mode;
+    int32_t nti, ntj, first, deal;       // per-block mode: the blocks, and how they are dealt (tile_order)
+    int32_t* tile_S;
+    oz_result_t* user;
+};
 
-constexpr int kEscTile = 128;   // (i,j) tile per workgroup, 16x16 threads of 8x8 pairs
-constexpr int kEscHChunk = 32;  // inner steps staged in LDS at a time
-constexpr short kEscPadValue = -16384;  // two of them add to the int16 minimum without wrapping
-
-__global__ __launch_bounds__(256) void esc_kernel(const int16_t* __restrict__ U,
-                                                  const int16_t* __restrict__ V,
-                                                  const int32_t* __restrict__ eA,
-                                                  const int32_t* __restrict__ eB, int64_t mp,
-                                                  int64_t np, int H2, Record* rec,
-                                                  int32_t* __restrict__ tile_span) {
-    __shared__ short8_t Ut[kEscHChunk][kEscTile / 8];
-    __shared__ short8_t Vt[kEscHChunk][kEscTile / 8];
-    // Inf/NaN already forces the native path; otherwise run only for what the MFMA kernel left open
-    if (rec->infnan || !rec->esc_exact) return;
-
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    const int64_t i0 = int64_t(blockIdx.x) * kEscTile, j0 = int64_t(blockIdx.y) * kEscTile;
-
-    short2_t acc[8][4];
-#pragma unroll
-    for (int a = 0; a < 8; ++a)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[a][c] = short2_t{-32768, -32768};
-
-    for (int h0 = 0; h0 < H2; h0 += kEscHChunk) {
-        __syncthreads();
-        // 32 x 128 int16 per table = 512 vectors of 8; two per thread
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int v = threadIdx.x + t * 256;
-            const int hh = v >> 4, col = v & 15;
-            short8_t uu, vv;
-            if (h0 + hh < H2) {
-                uu = *reinterpret_cast<const short8_t*>(U + int64_t(h0 + hh) * mp + i0 + col * 8);
-                vv = *reinterpret_cast<const short8_t*>(V + int64_t(h0 + hh) * np + j0 + col * 8);
-            } else {
-                uu = short8_t(kEscPadValue);
-                vv = short8_t(kEscPadValue);
-            }
-            Ut[hh][col] = uu;
-            Vt[hh][col] = vv;
-        }
-        __syncthreads();
-#pragma unroll 4
-        for (int hh = 0; hh < kEscHChunk; ++hh) {
-            const short8_t u = Ut[hh][ty];
-            const short8_t v = Vt[hh][tx];
-            const short2_t v2[4] = {short2_t{v[0], v[1]}, short2_t{v[2], v[3]},
-                                    short2_t{v[4], v[5]}, short2_t{v[6], v[7]}};
-#pragma unroll
-            for (int a = 0; a < 8; ++a) {
-                const short2_t ua = short2_t{u[a], u[a]};
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    acc[a][c] = __builtin_elementwise_max(acc[a][c], ua + v2[c]);
-            }
-        }
-    }
-
-    int best = 0;
-#pragma unroll
-    for (int a = 0; a < 8; ++a) {
-        const int ea = eA[i0 + ty * 8 + a];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const int z = acc[a][c][q];
-                const int eb = eB[j0 + tx * 8 + c * 2 + q];
-                int span;
-                if (z >= kSumRealFloor) span = ea + eb - z;          // a real exponent sum
-                else if (z >= kSumDeadBelow) span = kEscCap;          // no candidate: unbounded
-                else span = 0;                                        // identically zero product
-                best = max(best, span);
-            }
-        }
-    }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) best = max(best, __shfl_xor(best, off));
-    if ((threadIdx.x & 63) == 0) {
-        // this kernel visits every pair, so its block maxima complete the per-block table as well
-        // (kEscTile x kEscTile blocks, four per kTile x kTile block of C)
-        static_assert(kTile == 2 * kEscTile, "four ESC blocks per block of C");
-        atomicMax(&tile_span[(blockIdx.y >> 1) * (mp / kTile) + (blockIdx.x >> 1)], best);
-        // the maximum is monotone: a stale read only costs a redundant atomic
-        if (best > *reinterpret_cast<volatile int32_t*>(&rec->span_max)) atomicMax(&rec->span_max, best);
-    }
+// slice count of the fixed and forced modes
+__host__ __device__ inline int fixed_slices(const oz_opts_t& o) {
+    const int s = o.slices > 0 ? o.slices : (o.max_bits + 1 + 7) / 8;
+    return s < 1 ? 1 : (s > kMaxSlices ? kMaxSlices : s);
 }
 
-// Per-tile mode: slice count of every kTile x kTile block of C from the largest span inside it, plus
-// the two sums the verdict needs (pair products over all blocks, smallest count).
-__global__ __launch_bounds__(256) void tile_verdict_kernel(Record* rec, const int32_t* __restrict__ tile_span,
-                                                           int32_t* __restrict__ tile_S, int64_t tiles,
-                                                           int target_bits) {
-    const int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    unsigned long long pairs = 0;
-    int smin = kMaxSlices;
-    if (t < tiles) {
-        const int esc = min(tile_span[t] + 1, kEscCap);
-        int S = (target_bits + esc + 1 + kHeadroomBits + 7) / 8;
-        S = max(1, min(S, kMaxSlices));
-        tile_S[t] = S;
-        pairs = (unsigned long long)(S) * (S + 1) / 2;
-        smin = S;
-    }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        pairs += __shfl_xor(pairs, off);
-        smin = min(smin, __shfl_xor(smin, off));
-    }
-    if ((threadIdx.x & 63) == 0 && pairs) {
-        atomicAdd(&rec->pair_acc, pairs);
-        atomicMin(&rec->smin_acc, smin);
-    }
-}
-
-// One thread: slice count and fallback decision from the scan flag and the ESC.
-__global__ void verdict_kernel(Record* rec, oz_opts_t o, oz_heuristic_t hm, int kind,
-                               int64_t m, int64_t n, int64_t k, int s_cap, int tile_mode,
-                               oz_result_t* user_result) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// Slice count and fallback decision of a guarded call from the scan's flag and the ESC.  pairs, smin: per-block mode,
+// pair products over all blocks and the smallest count.
+__device__ oz_result_t verdict(const VerdictArgs& v, int infnan, int span_max, unsigned long long pairs_all, int smin, int64_t m,
+                               int64_t n, int64_t k) {
+    const oz_opts_t& o = v.o;
     oz_result_t r;
     r.fallback = 0; r.reason = 0; r.slices_used = 0; r.esc = -1; r.required_bits = 0; r.infnan = 0;
     r.slices_min = 0; r.reserved_ = 0; r.pair_tiles = 0;
     const int64_t tiles = ((m + kTile - 1) / kTile) * ((n + kTile - 1) / kTile);
-    bool per_tile = false;    // the blocks of C carry their own counts (tile_verdict_kernel ran)
-    if (kind == 2 || kind == 3) {
-        // 2: nothing to multiply (k == 0 or alpha == 0); 3: the host's cost model says that no slice
-        // count this call could get beats the native GEMM, so nothing was scanned
-        if (kind == 3) { r.fallback = 1; r.reason = 3; }
-        rec->res = r;
-        if (user_result) *user_result = r;
-        return;
-    }
-    int s_fixed = o.slices > 0 ? o.slices : (o.max_bits + 1 + 7) / 8;
-    s_fixed = max(1, min(s_fixed, kMaxSlices));
-    if (o.mode == OZ_NATIVE) {
-        r.fallback = 1; r.reason = 4;
-    } else if (o.mode == OZ_FIXED_UNGUARDED) {
-        r.slices_used = s_fixed;
-    } else if (rec->infnan) {
+    bool per_tile = false;    // the blocks of C carry their own counts
+    const int s_fixed = fixed_slices(o);
+    if (infnan) {
         r.fallback = 1; r.reason = 1; r.infnan = 1;
     } else {
-        const int esc = min(rec->span_max + 1, kEscCap);
+        const int esc = min(span_max + 1, kEscCap);
         r.esc = esc;
         r.required_bits = o.target_bits + esc;
         // slices that hold required_bits, the sign and the headroom bit
@@ -331,17 +359,17 @@ __global__ void verdict_kernel(Record* rec, oz_opts_t o, oz_heuristic_t hm, int 
             else r.slices_used = s_fixed;
         } else {
             S = max(1, min(S, kMaxSlices));
-            per_tile = tile_mode != 0;
+            per_tile = v.tile_mode != 0;
             bool slower = false;
             if (o.heuristic) {
                 const int64_t flops = 2 * m * n * k;
                 // pair products per block of C: S(S+1)/2, or the mean over the blocks, rounded up
-                const int64_t pairs = per_tile ? int64_t((rec->pair_acc + (unsigned long long)(tiles) - 1) /
+                const int64_t pairs = per_tile ? int64_t((pairs_all + (unsigned long long)(tiles) - 1) /
                                                          (unsigned long long)(tiles))
                                                : int64_t(S) * (S + 1) / 2;
                 const int64_t stream = (16 + S) * (m * k + k * n) + (2 * int64_t(S) + 22) * m * n;
-                const int64_t t_emu = hm.fixed_ns + (flops / hm.int8_ops_per_ns) * pairs + stream / hm.bytes_per_ns;
-                const int64_t t_f64 = flops / hm.fp64_flops_per_ns;
+                const int64_t t_emu = v.hm.fixed_ns + (flops / v.hm.int8_ops_per_ns) * pairs + stream / v.hm.bytes_per_ns;
+                const int64_t t_f64 = flops / v.hm.fp64_flops_per_ns;
                 slower = t_emu > t_f64;
             }
             if (slower) { r.fallback = 1; r.reason = 3; }
@@ -351,39 +379,148 @@ __global__ void verdict_kernel(Record* rec, oz_opts_t o, oz_heuristic_t hm, int 
     // The workspace holds s_cap slice planes and the host sized it for the largest count these options
     // can select, so this never binds; if it ever did, running with fewer slices would lose bits
     // silently, so the call goes native and says why.
-    if (!r.fallback && r.slices_used > s_cap) { r.fallback = 1; r.reason = 2; r.slices_used = 0; }
+    if (!r.fallback && r.slices_used > v.s_cap) { r.fallback = 1; r.reason = 2; r.slices_used = 0; }
     if (!r.fallback && r.slices_used > 0) {
-        r.slices_min = per_tile ? rec->smin_acc : r.slices_used;
-        r.pair_tiles = per_tile ? int64_t(rec->pair_acc) : tiles * (int64_t(r.slices_used) * (r.slices_used + 1) / 2);
+        r.slices_min = per_tile ? smin : r.slices_used;
+        r.pair_tiles = per_tile ? int64_t(pairs_all) : tiles * (int64_t(r.slices_used) * (r.slices_used + 1) / 2);
     }
-    rec->res = r;
-    if (user_result) *user_result = r;
+    return r;
 }
 
-void launch_esc(hipStream_t st, const Workspace& w, const Problem& p) {
+// A workgroup takes every gridDim.x-th block of 128 x 128 pairs: few enough workgroups (two per CU) that their arrivals
+// at one counter do not queue up (17 ns each: one per block took 70 us at 8192^3).
+__global__ __launch_bounds__(256) void esc_kernel(const uint4* __restrict__ EU, const uint4* __restrict__ EV,
+                                                  const int16_t* __restrict__ U, const int16_t* __restrict__ V,
+                                                  const int32_t* __restrict__ eA, const int32_t* __restrict__ eB, int64_t m,
+                                                  int64_t n, int64_t k, int64_t mp, int64_t np, int H2, int steps, Record* rec,
+                                                  int32_t* __restrict__ tile_span, VerdictArgs v) {
+    __shared__ EscLds lds;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int infnan = rec->infnan;
+    if (infnan) {
+        // the native path is decided: one workgroup says so, no span is needed
+        if (blockIdx.x != 0) return;
+    } else {
+        const int64_t nbi = mp / kEscTile, blocks = nbi * (np / kEscTile);
+        int widest = 0;
+        for (int64_t block = blockIdx.x; block < blocks; block += gridDim.x) {
+            const int64_t bj = block / nbi, bi = block - bj * nbi;
+            uint32_t least = least_sum(EU, EV, m, n, mp, np, steps, bi, bj);
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) least = min(least, uint32_t(__shfl_xor(int(least), off)));
+            __syncthreads();
+            if (lane == 0) lds.least[wave] = least;
+            __syncthreads();
+            least = min(min(lds.least[0], lds.least[1]), min(lds.least[2], lds.least[3]));
+            if (least == 0xFFFFFFFFu) continue;              // padding only
+            // exponent(sum) - 122 lies in [5t, 5t+4]; shifted by 5*64 so that the division is of a
+            // non-negative number
+            const int E = int(least >> 23) - 127 - 2 * kEncBias;
+            const int t = (E + kEncScale * 64) / kEncScale - 64;
+            int span = -t;
+            if (t < -kEncRange) {
+                // below the encodable range, or no candidate at all: this block once more, the exact way
+                int best = exact_span(lds, U, V, eA, eB, mp, np, H2, bi * kEscTile, bj * kEscTile);
+#pragma unroll
+                for (int off = 32; off >= 1; off >>= 1) best = max(best, __shfl_xor(best, off));
+                __syncthreads();
+                if (lane == 0) lds.least[wave] = uint32_t(best);
+                __syncthreads();
+                span = max(max(int(lds.least[0]), int(lds.least[1])), max(int(lds.least[2]), int(lds.least[3])));
+            }
+            widest = max(widest, span);
+            // the block's largest span goes to the C block it lies in (four such blocks per kTile x kTile block)
+            if (v.tile_mode && threadIdx.x == 0) atomicMax(&tile_span[(bj >> 1) * (mp / kTile) + (bi >> 1)], span);
+        }
+        // the last workgroup to get here has everybody's spans before it
+        if (threadIdx.x == 0) {
+            // a stale read only costs a redundant atomic, the maximum is monotone
+            if (widest > *reinterpret_cast<volatile int32_t*>(&rec->span_max)) atomicMax(&rec->span_max, widest);
+            // The spans are atomics of this thread, carried out where all XCDs see them: once they are done, so is this
+            // workgroup.  No fence: an agent-scope release writes the XCD's L2 back (150 us with one per block).
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            lds.last = __hip_atomic_fetch_add(&rec->esc_done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == int(gridDim.x) - 1;
+        }
+        __syncthreads();
+        if (!lds.last) return;
+    }
+
+    // ---- one workgroup from here on ----
+    auto read = [](const int32_t* p) -> int { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    unsigned long long pairs = 0;
+    int smin = kMaxSlices;
+    if (v.tile_mode) {
+        // slice count of every kTile x kTile block of C from the largest span inside it
+        for (int64_t t = threadIdx.x; t < int64_t(v.nti) * v.ntj; t += 256) {
+            const int esc = min(read(&tile_span[t]) + 1, kEscCap);
+            int S = (v.o.target_bits + esc + 1 + kHeadroomBits + 7) / 8;
+            S = max(1, min(S, kMaxSlices));
+            v.tile_S[t] = S;
+            pairs += (unsigned long long)(S) * (S + 1) / 2;
+            smin = min(smin, S);
+        }
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) {
+            pairs += __shfl_xor(pairs, off);
+            smin = min(smin, __shfl_xor(smin, off));
+        }
+        if (lane == 0) { lds.pairs[wave] = pairs; lds.smin[wave] = smin; }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        if (v.tile_mode) {
+            pairs = lds.pairs[0] + lds.pairs[1] + lds.pairs[2] + lds.pairs[3];
+            smin = min(min(lds.smin[0], lds.smin[1]), min(lds.smin[2], lds.smin[3]));
+        }
+        const oz_result_t r = verdict(v, infnan, read(&rec->span_max), pairs, smin, m, n, k);
+        rec->res = r;
+        if (v.user) *v.user = r;
+        lds.stop = r.fallback;
+    }
+    __threadfence_block();
+    __syncthreads();
+    if (!v.tile_mode || lds.stop) return;
+    tile_order(lds, v.tile_S, v.tile_S + v.nti * v.ntj, v.nti, v.ntj, v.first, v.deal);
+}
+
+__global__ void known_record_kernel(KnownRecord known) {
+    if (threadIdx.x == 0) write_known_record(known);
+}
+
+oz_result_t known_verdict(const Problem& p, const oz_opts_t& o, int kind) {
+    oz_result_t r = {};
+    r.esc = -1;
+    if (kind == 2) return r;
+    if (kind == 3) {
+        r.fallback = 1;
+        r.reason = 3;
+    } else if (o.mode == OZ_NATIVE) {
+        r.fallback = 1;
+        r.reason = 4;
+    } else {
+        r.slices_used = r.slices_min = fixed_slices(o);
+        r.pair_tiles = ((p.m + kTile - 1) / kTile) * ((p.n + kTile - 1) / kTile) * (int64_t(r.slices_used) * (r.slices_used + 1) / 2);
+    }
+    return r;
+}
+
+void launch_known_record(hipStream_t st, const KnownRecord& known) {
+    hipLaunchKernelGGL(known_record_kernel, dim3(1), dim3(64), 0, st, known);
+}
+
+void launch_esc_verdict(hipStream_t st, const Workspace& w, const Problem& p, const oz_opts_t& o, const oz_heuristic_t& hm,
+                        oz_result_t* user_result) {
     const int H2 = 2 * p.G;
     const int steps = (H2 + 2 * kEncChunk - 1) / (2 * kEncChunk);   // 32 inner steps (4 groups of 8) each
-    hipLaunchKernelGGL(esc_encode_kernel, dim3(unsigned(p.mp / 256), unsigned(steps * 4)), dim3(256), 0, st,
-                       w.U, w.eA, p.mp, H2, reinterpret_cast<uint4*>(w.EU));
-    hipLaunchKernelGGL(esc_encode_kernel, dim3(unsigned(p.np / 256), unsigned(steps * 4)), dim3(256), 0, st,
-                       w.V, w.eB, p.np, H2, reinterpret_cast<uint4*>(w.EV));
-    hipLaunchKernelGGL(esc_mfma_kernel, dim3(unsigned(p.mp / 128), unsigned(p.np / 128)), dim3(256), 0, st,
-                       reinterpret_cast<const uint4*>(w.EU), reinterpret_cast<const uint4*>(w.EV), p.m, p.n,
-                       p.mp, p.np, steps, w.rec, w.tile_span);
-    hipLaunchKernelGGL(esc_kernel, dim3(unsigned(p.mp / kEscTile), unsigned(p.np / kEscTile)), dim3(256), 0,
-                       st, w.U, w.V, w.eA, w.eB, p.mp, p.np, 2 * p.G, w.rec, w.tile_span);
-}
-
-void launch_tile_verdict(hipStream_t st, const Workspace& w, const Problem& p, const oz_opts_t& o) {
-    const int64_t tiles = (p.mp / kTile) * (p.np / kTile);
-    hipLaunchKernelGGL(tile_verdict_kernel, dim3(unsigned((tiles + 255) / 256)), dim3(256), 0, st, w.rec,
-                       w.tile_span, w.tile_S, tiles, o.target_bits);
-}
-
-void launch_verdict(hipStream_t st, const Workspace& w, const Problem& p, const oz_opts_t& o,
-                    const oz_heuristic_t& hm, int kind, oz_result_t* user_result) {
-    hipLaunchKernelGGL(verdict_kernel, dim3(1), dim3(64), 0, st, w.rec, o, hm, kind, p.m, p.n,
-                       p.k, p.s_cap, p.tile_mode, user_result);
+    uint4* const EU = reinterpret_cast<uint4*>(w.EU);
+    uint4* const EV = reinterpret_cast<uint4*>(w.EV);
+    hipLaunchKernelGGL(esc_encode_kernel, dim3(unsigned((p.mp + p.np) / 256), unsigned(steps * 4)), dim3(256), 0, st, w.U, w.eA,
+                       p.mp, EU, w.V, w.eB, p.np, EV, H2);
+    VerdictArgs v = {o, hm, p.s_cap, p.tile_mode, int(p.mp / kTile), int(p.np / kTile), 0, 0, w.tile_S, user_result};
+    if (p.tile_mode) tile_order_shape(p, v.first, v.deal);
+    const int64_t blocks = (p.mp / kEscTile) * (p.np / kEscTile);
+    hipLaunchKernelGGL(esc_kernel, dim3(unsigned(std::min<int64_t>(blocks, 2 * int64_t(p.num_cu)))), dim3(256), 0, st, EU, EV, w.U,
+                       w.V, w.eA, w.eB, p.m, p.n, p.k, p.mp, p.np, H2, steps, w.rec, w.tile_span, v);
 }
 
 }  // namespace oz

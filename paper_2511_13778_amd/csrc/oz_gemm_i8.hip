@@ -779,78 +779,83 @@ __global__ __launch_bounds__(256) void add_parts_kernel(const int32_t* __restric
     for (int q = 0; q < 4; ++q) tw[q * mp] = carry[q];
 }
 
-// Per-tile mode: the order in which the tiles of C are dealt to the workgroups.  An XCD runs its tiles in
-// rounds of 32 that keep in step to share panels in L2; a round that mixes tiles of different slice counts
-// falls out of step when its light tiles finish (their successors wait in vain for the heavy ones and then
-// run alone: measured 18.0 ms instead of 13.9 ms for 64 ten-slice tiles lying in one block column).  So the
-// tiles are sorted by slice count, heaviest first and otherwise in the usual block order, and the sorted
-// groups of 32 are dealt to the XCDs in turn: group g is round g / 8 of XCD g % 8.  Rounds are then uniform
-// but for one per slice count, the heavy rounds are spread over the XCDs, and the lightest tiles end up in
-// the partial last round or the k-split launch.  `first` = tiles of the first launch (its XCD ranges are what
-// the groups are dealt into), of which the leading first / 256 * 256 sorted tiles are dealt; the others keep
-// the sorted order in the positions that remain.  order[position] = index of the tile in the block order.
-// One workgroup; a stable counting sort over the slice counts 0 .. kMaxSlices.
-__global__ __launch_bounds__(256) void tile_order_kernel(const int32_t* __restrict__ tile_S, int32_t* __restrict__ order,
-                                                         int nti, int ntj, int first, int deal, const Record* rec) {
-    if (rec->res.fallback) return;
-    const int tiles = nti * ntj, tid = threadIdx.x;
-    if (!deal) {
-        for (int lin = tid; lin < tiles; lin += 256) order[lin] = lin;
-        return;
+namespace {
+
+struct Split { int z; bool atomic; };
+
+// How a call's units are dealt to launches.
+struct LaunchPlan {
+    GemmGrid g;
+    int per_pos;           // units per position of the launch order
+    int positions;
+    int kt;                // 64s of k
+    int raw_units;         // 128 x 128 slots per plane of the raw buffer
+    int min_entries;       // stream entries per 64 of k of a unit with the fewest slices the call can come out with
+    int full, rest;        // positions in full rounds, and left over
+    Split last;            // of the rest (of everything, if there is no full round)
+    bool two;              // the rest in a launch of its own
+
+    explicit LaunchPlan(const Problem& p) : g() {
+        g.nti = int(p.mp / kTile);
+        g.ntj = int(p.np / kTile);
+        g.um = int((p.m + kUnit - 1) / kUnit);
+        g.un = int((p.n + kUnit - 1) / kUnit);
+        // the workgroup-to-XCD reasoning behind the in-step waits holds for the whole chip only
+        // (8 XCDs of 32 CUs); a partitioned device runs the same kernel without them
+        g.full_chip = p.num_cu == 8 * kRoundUnits ? 1 : 0;
+        per_pos = p.tile_mode ? 4 : 1;
+        positions = p.tile_mode ? g.nti * g.ntj : g.um * g.un;
+        kt = int(p.kp / kBK);
+        raw_units = 4 * p.raw_slots;
+        min_entries = 0;
+        for (int n = p.s_min; n > 0; n -= kDiag) min_entries += n;
+        // Units are dealt in rounds of one per CU.  A call with less than a round may be split along k as a whole;
+        // otherwise the full rounds run unsplit and what is left may be split along k in a launch of its own.
+        // (Per-block order: a full round of the order table is one block per CU.)
+        const int round = p.num_cu;
+        full = positions / round * round;
+        rest = positions - full;
+        last = rest != 0 && rest * per_pos < round ? split(p, rest * per_pos) : Split{1, false};
+        two = full != 0 && last.z > 1;
     }
-    __shared__ int cnt[kMaxSlices + 1][256];
-    __shared__ int base[kMaxSlices + 1];
-    const int chunk = (tiles + 255) / 256;
-    const int lo = min(tiles, tid * chunk), hi = min(tiles, lo + chunk);
-    auto key_of = [&](int lin) -> int {
-        int ti, tj;
-        lin_to_tile(lin, nti, ntj, ti, tj);
-        return min(max(tile_S[tj * nti + ti], 0), kMaxSlices);
-    };
-    for (int k = 0; k <= kMaxSlices; ++k) cnt[k][tid] = 0;
-    for (int lin = lo; lin < hi; ++lin) ++cnt[key_of(lin)][tid];
-    __syncthreads();
-    if (tid <= kMaxSlices) {      // exclusive prefix over the threads' chunks, per key
-        int run = 0;
-        for (int t = 0; t < 256; ++t) {
-            const int c = cnt[tid][t];
-            cnt[tid][t] = run;
-            run += c;
-        }
-        base[tid] = run;
+
+    // k-blocks a part can touch, whatever the slice count turns out to be (fewer slices: longer k-blocks)
+    int nkb_part(const Problem& p, int z) const {
+        const int64_t len = (int64_t(kt) + z - 1) / z * kBK;
+        return p.nkb == 1 ? 1 : int(std::min<int64_t>(p.nkb, (len - 1) / p.kblk + 2));
     }
-    __syncthreads();
-    if (tid == 0) {               // keys in descending order
-        int run = 0;
-        for (int k = kMaxSlices; k >= 0; --k) {
-            const int c = base[k];
-            base[k] = run;
-            run += c;
-        }
-    }
-    __syncthreads();
-    const int per = first >> 3, rem = first & 7, rounds = first / (8 * kRoundUnits), dealt = rounds * 8 * kRoundUnits;
-    for (int lin = lo; lin < hi; ++lin) {
-        const int k = key_of(lin);
-        const int si = base[k] + cnt[k][tid]++;      // position in the sorted sequence
-        int q = si;
-        if (si < dealt) {
-            const int g = si / kRoundUnits, wpos = si % kRoundUnits, r = g >> 3, x = g & 7;
-            q = x * per + min(x, rem) + r * kRoundUnits + wpos;
-        } else if (si < first) {
-            // what is left of the XCD ranges behind their dealt rounds, XCD by XCD
-            int t = si - dealt;
-            for (int x = 0; x < 8; ++x) {
-                const int left = per + (x < rem ? 1 : 0) - rounds * kRoundUnits;
-                if (t < left) {
-                    q = x * per + min(x, rem) + rounds * kRoundUnits + t;
-                    break;
-                }
-                t -= left;
+
+    // k split of a launch that cannot fill the chip.  Estimated time in ns for `units` units, seven slices assumed
+    // (the slice count is decided on the device): a 64 of k costs a unit about 4.2 us, a workgroup about 5 us to
+    // start and to write its sums.  Parts with slots of their own move 10 bytes per element and part (60 ns per part and
+    // unit) and, for the rest of a larger product, need a launch to be added (6 us); atomics add 28 bytes per element
+    // and part (170 ns) and need the slots zeroed (8 us), but no more memory for more parts.
+    Split split(const Problem& p, int units) const {
+        const bool whole = units == positions * per_pos;     // the recomposition puts it together
+        const int64_t raw_bytes = int64_t(p.nkb) * p.s_cap * raw_units * (kUnit * kUnit * 4);
+        Split best{1, false};
+        int64_t best_ns = (int64_t(kt) * 4200 + 5000) * 95 / 100;     // a split has to gain 5 %
+        for (int z = 2; z <= kt && int64_t(units) * z <= p.num_cu; ++z) {
+            const int64_t steps = (kt + z - 1) / z;
+            if (int64_t(z - 1) * units * nkb_part(p, z) * part_slot_bytes(p.s_cap) <= raw_bytes) {
+                const int64_t ns = steps * 4200 + 5000 + (whole ? 1000 : 6000) + int64_t(60) * units * z;
+                if (ns < best_ns) { best_ns = ns; best = Split{z, false}; }
+            }
+            if (whole) {
+                const int64_t ns = steps * 4800 + 5000 + 8000 + int64_t(170) * units * z;
+                if (ns < best_ns) { best_ns = ns; best = Split{z, true}; }
             }
         }
-        order[q] = lin;
+        return best;
     }
+};
+
+}  // namespace
+
+void tile_order_shape(const Problem& p, int& first, int& deal) {
+    const LaunchPlan lp(p);
+    first = lp.two ? lp.full : lp.positions;
+    deal = (lp.g.full_chip && lp.full != 0 && lp.positions <= (1 << 16)) ? 1 : 0;
 }
 
 SplitPlan launch_gemm_i8(hipStream_t st, const Workspace& w, const Problem& p) {
@@ -859,104 +864,45 @@ SplitPlan launch_gemm_i8(hipStream_t st, const Workspace& w, const Problem& p) {
                               hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds);
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_i8_kernel<true>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds);
-    GemmGrid g;
-    g.nti = int(p.mp / kTile);
-    g.ntj = int(p.np / kTile);
-    g.um = int((p.m + kUnit - 1) / kUnit);
-    g.un = int((p.n + kUnit - 1) / kUnit);
-    // the workgroup-to-XCD reasoning behind the in-step waits holds for the whole chip only
-    // (8 XCDs of 32 CUs); a partitioned device runs the same kernel without them
-    g.full_chip = p.num_cu == 8 * kRoundUnits ? 1 : 0;
+    const LaunchPlan lp(p);
     const int32_t* tile_S = p.tile_mode ? w.tile_S : nullptr;
-    const int blocks = g.nti * g.ntj;
-    const int per_pos = p.tile_mode ? 4 : 1;                  // units per position of the launch order
-    const int positions = p.tile_mode ? blocks : g.um * g.un;
-    const int kt = int(p.kp / kBK);
-    const int raw_units = 4 * p.raw_slots;                    // 128 x 128 slots per plane of the raw buffer
-    const int64_t raw_bytes = int64_t(p.nkb) * p.s_cap * raw_units * (kUnit * kUnit * 4);
-
-    // stream entries per 64 of k of a unit with the fewest slices the call can come out with
-    int min_entries = 0;
-    for (int n = p.s_min; n > 0; n -= kDiag) min_entries += n;
-
-    // k split of a launch that cannot fill the chip.  Estimated time in ns for `units` units, seven slices assumed
-    // (the slice count is decided on the device): a 64 of k costs a unit about 4.2 us, a workgroup about 5 us to
-    // start and to write its sums, a further launch 6 us.  Parts with slots of their own move 10 bytes per
-    // element and part (60 ns per part and unit); atomics add 28 bytes per element and part (170 ns), zero and
-    // read the slots, but need no more memory for more parts.
-    struct Split { int z; bool atomic; };
-    // k-blocks a part can touch, whatever the slice count turns out to be (fewer slices: longer k-blocks)
-    auto nkb_part = [&](int z) -> int {
-        const int64_t len = (int64_t(kt) + z - 1) / z * kBK;
-        return p.nkb == 1 ? 1 : int(std::min<int64_t>(p.nkb, (len - 1) / p.kblk + 2));
-    };
-    auto parts_fit = [&](int units, int z) -> bool {
-        return int64_t(z - 1) * units * nkb_part(z) * part_slot_bytes(p.s_cap) <= raw_bytes;
-    };
-    auto plan = [&](int units) -> Split {
-        auto waves = [&](int64_t items) -> int64_t { return (items + p.num_cu - 1) / p.num_cu; };
-        Split best{1, false};
-        int64_t best_ns = waves(units) * (int64_t(kt) * 4200 + 5000) * 95 / 100;     // a split has to gain 5 %
-        for (int z = 2; z <= kt && int64_t(units) * z <= p.num_cu; ++z) {
-            const int64_t steps = (kt + z - 1) / z;
-            if (parts_fit(units, z)) {
-                const int64_t ns = steps * 4200 + 5000 + 6000 + int64_t(60) * units * z;
-                if (ns < best_ns) { best_ns = ns; best = Split{z, false}; }
-            }
-            if (units == positions * per_pos) {      // (a product that is split as a whole)
-                const int64_t ns = steps * 4800 + 5000 + 12000 + int64_t(170) * units * z;
-                if (ns < best_ns) { best_ns = ns; best = Split{z, true}; }
-            }
-        }
-        return best;
-    };
-    auto launch = [&](int begin, int count, Split sp) {
-        const int units = count * per_pos;
+    auto launch = [&](int begin, int count, Split sp) -> GemmGrid {
+        GemmGrid g = lp.g;
+        const int units = count * lp.per_pos;
         g.begin = begin;
         g.count = count;
         g.zsplit = sp.z;
-        g.nkb_part = nkb_part(sp.z);
+        g.nkb_part = lp.nkb_part(p, sp.z);
         g.persistent = 0;
         // unsplit launches in per-block order give every XCD whole blocks: the ranges differ by up to four units
         unsigned grid = (p.tile_mode && sp.z == 1) ? unsigned(8 * 4 * ((count + 7) / 8)) : unsigned(units) * unsigned(sp.z);
         // more units than CUs: one workgroup per CU that walks its share (eight equal ranges, one per XCD), if
         // the units are long enough for the streams
         const unsigned cus = unsigned(p.num_cu) & ~7u;
-        if (grid > cus && cus != 0 && kt * min_entries >= kMinUnitItems) {
+        if (grid > cus && cus != 0 && lp.kt * lp.min_entries >= kMinUnitItems) {
             grid = cus;
             g.persistent = 1;
         }
         if (sp.atomic) {
             hipLaunchKernelGGL(zero_raw_kernel, dim3(unsigned(units), unsigned(p.nkb * p.s_cap)), dim3(256), 0, st, w.raw,
-                               raw_units, p.s_cap, w.rec);
+                               lp.raw_units, p.s_cap, w.rec);
             hipLaunchKernelGGL(gemm_i8_kernel<true>, dim3(grid), dim3(256), kGemmLds, st, w.As, w.Bs, w.T, w.L, w.raw,
-                               raw_units, p.mp, p.np, p.kp, p.s_cap, w.rec, g, tile_S);
+                               lp.raw_units, p.mp, p.np, p.kp, p.s_cap, w.rec, g, tile_S);
         } else {
             hipLaunchKernelGGL(gemm_i8_kernel<false>, dim3(grid), dim3(256), kGemmLds, st, w.As, w.Bs, w.T, w.L, w.raw,
-                               raw_units, p.mp, p.np, p.kp, p.s_cap, w.rec, g, tile_S);
-            if (sp.z > 1 && count < positions)
-                hipLaunchKernelGGL(add_parts_kernel, dim3(unsigned(units), unsigned(p.nkb), kUnit / 4 / 2), dim3(256), 0, st, w.raw, w.T, w.L, p.mp, p.np, p.kp, p.s_cap, g, w.rec, tile_S);
+                               lp.raw_units, p.mp, p.np, p.kp, p.s_cap, w.rec, g, tile_S);
+            if (sp.z > 1 && count < lp.positions)
+                hipLaunchKernelGGL(add_parts_kernel, dim3(unsigned(units), unsigned(p.nkb), kUnit / 4 / 2), dim3(256), 0, st,
+                                   w.raw, w.T, w.L, p.mp, p.np, p.kp, p.s_cap, g, w.rec, tile_S);
         }
+        return g;
     };
-    // Units are dealt in rounds of one per CU.  A call with less than a round may be split along k as a whole;
-    // otherwise the full rounds run unsplit and what is left may be split along k in a launch of its own.
-    // (Per-block order: a full round of the order table is one block per CU.)
-    const int round = p.num_cu;
-    const int full = positions / round * round, rest = positions - full;
-    const Split sp = rest != 0 && rest * per_pos < round ? plan(rest * per_pos) : Split{1, false};
-    const bool two = full != 0 && sp.z > 1;
-    if (p.tile_mode) {
-        const int deal = (g.full_chip && full != 0 && blocks <= (1 << 16)) ? 1 : 0;
-        hipLaunchKernelGGL(tile_order_kernel, dim3(1), dim3(256), 0, st, w.tile_S, w.tile_S + blocks, g.nti, g.ntj,
-                           two ? full : blocks, deal, w.rec);
+    if (lp.two) {
+        launch(0, lp.full, Split{1, false});
+        return SplitPlan{KSplit::kNone, launch(lp.full, lp.rest, lp.last), lp.raw_units};
     }
-    if (two) {
-        launch(0, full, Split{1, false});
-        launch(full, rest, sp);
-        return SplitPlan{KSplit::kNone, g, raw_units};
-    }
-    launch(0, positions, sp);
-    return SplitPlan{sp.z == 1 ? KSplit::kNone : (sp.atomic ? KSplit::kAtomic : KSplit::kParts), g, raw_units};
+    const GemmGrid g = launch(0, lp.positions, lp.last);
+    return SplitPlan{lp.last.z == 1 ? KSplit::kNone : (lp.last.atomic ? KSplit::kAtomic : KSplit::kParts), g, lp.raw_units};
 }
 
 }  // namespace oz

@@ -37,14 +37,24 @@ constexpr int kTile = 256;            // edge of the blocks of C that can take t
 struct Record {
     int32_t infnan;        // set by the scan kernels (atomicOr)
     int32_t span_max;      // max_ij (eA_i + eB_j - zt_ij), set by the ESC kernels (atomicMax)
-    int32_t esc_exact;     // set by the MFMA ESC kernel when a pair needs the exact int16 kernel
+    int32_t esc_done;      // workgroups of the ESC kernel that have left their span (atomicAdd): the last one gives the verdict
     int32_t pad_;
     int32_t tile_sync[8];  // per-XCD arrival counters of the slice GEMM's workgroups
-    unsigned long long pair_acc;   // per-tile mode: sum over tiles of S_T(S_T+1)/2 (atomicAdd)
-    int32_t smin_acc;      // per-tile mode: smallest S_T (atomicMin)
-    int32_t pad2_;
-    oz_result_t res;       // written by the verdict kernel, read by every later kernel
+    oz_result_t res;       // the verdict, read by every later kernel
 };
+
+// A record that the host knows before anything runs (no guards, or the native GEMM chosen by the cost model), written
+// by the first kernel of the call.  rec == nullptr: nothing to write.
+struct KnownRecord {
+    Record* rec;
+    oz_result_t* user;     // may be nullptr
+    oz_result_t value;
+};
+__device__ inline void write_known_record(const KnownRecord& k) {
+    if (!k.rec) return;
+    k.rec->res = k.value;
+    if (k.user) *k.user = k.value;
+}
 
 struct Problem {
     int64_t m, n, k;
@@ -146,21 +156,24 @@ __host__ __device__ inline int64_t k_block_length(int S) {
 }
 
 // ---- stage launchers (each only enqueues) --------------------------------------------
-// element (r, l) of a k-by-rows operand is at base[r*stride_r + l*stride_l]
-void launch_init(hipStream_t st, const Workspace& w, const Problem& p);
-void launch_scan(hipStream_t st, const double* X, int64_t stride_r, int64_t stride_l,
-                 int64_t rows, int64_t rows_p, const Problem& p, int16_t* tab, bool max_first,
-                 int32_t* e_out, Record* rec, bool check_infnan);
-void launch_esc(hipStream_t st, const Workspace& w, const Problem& p);
-// per-tile mode: slice count of every block of C from its span, and the sums the verdict needs
-void launch_tile_verdict(hipStream_t st, const Workspace& w, const Problem& p, const oz_opts_t& o);
-// kind: 0 unguarded, 1 guarded, 2 nothing to multiply (record says "emulated, 0 slices"),
-// 3 native by the cost model alone (nothing scanned)
-void launch_verdict(hipStream_t st, const Workspace& w, const Problem& p, const oz_opts_t& o,
-                    const oz_heuristic_t& hm, int kind, oz_result_t* user_result);
-void launch_slice(hipStream_t st, const double* X, int64_t stride_r, int64_t stride_l,
-                  int64_t rows, int64_t rows_p, const Problem& p, const int32_t* e_row,
-                  int8_t* slices, const Record* rec);
+// element (r, l) of an operand (r: row of op(A) / column of op(B), l: along k) is at X[r*stride_r + l*stride_l]
+struct Operand {
+    const double* X;
+    int64_t stride_r, stride_l;
+    int64_t rows, rows_p;
+};
+void launch_init(hipStream_t st, const Workspace& w, const Problem& p, const KnownRecord& known);
+void launch_scan(hipStream_t st, const Operand& a, const Operand& b, const Workspace& w, const Problem& p, bool check_infnan);
+// coarsened ESC and the verdict (per-block mode: slice counts and dealing order of the blocks as well)
+void launch_esc_verdict(hipStream_t st, const Workspace& w, const Problem& p, const oz_opts_t& o, const oz_heuristic_t& hm,
+                        oz_result_t* user_result);
+// records that need no kernel's result.  kind: 0 unguarded or OZ_NATIVE, 2 nothing to multiply (record says "emulated,
+// 0 slices"), 3 native by the cost model alone (nothing scanned)
+oz_result_t known_verdict(const Problem& p, const oz_opts_t& o, int kind);
+void launch_known_record(hipStream_t st, const KnownRecord& known);
+void launch_slice(hipStream_t st, const Operand& a, const Operand& b, const Workspace& w, const Problem& p);
+// per-block mode: blocks of the slice GEMM's first launch, and whether they are sorted by slice count
+void tile_order_shape(const Problem& p, int& first, int& deal);
 // returns what the recomposition still has to put together
 SplitPlan launch_gemm_i8(hipStream_t st, const Workspace& w, const Problem& p);
 void launch_recompose(hipStream_t st, const Workspace& w, const Problem& p, const SplitPlan& split, double alpha,
@@ -168,7 +181,8 @@ void launch_recompose(hipStream_t st, const Workspace& w, const Problem& p, cons
 // rec == nullptr: run unconditionally; otherwise run only when rec->res.fallback != 0.
 // scratch (may be nullptr): device memory the kernel may use for partial products when it splits the
 // k range of a product with few tiles; nothing else may use it while the GEMM runs
-void launch_dgemm_f64(hipStream_t st, const Record* rec, bool ta, bool tb, int64_t m, int64_t n,
+// known: a record to write on the way
+void launch_dgemm_f64(hipStream_t st, const Record* rec, const KnownRecord& known, bool ta, bool tb, int64_t m, int64_t n,
                       int64_t k, double alpha, const double* A, int64_t lda, const double* B,
                       int64_t ldb, double beta, double* C, int64_t ldc, void* scratch = nullptr,
                       size_t scratch_bytes = 0);

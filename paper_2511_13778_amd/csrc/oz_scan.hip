@@ -40,14 +40,13 @@ struct BlockStat {
 
 // resets the control record and the row / column exponents (targets of atomicMax in the scans)
 __global__ __launch_bounds__(256) void init_kernel(Record* rec, int32_t* eA, int64_t mp, int32_t* eB, int64_t np,
-                                                   int32_t* tile_span, int64_t tiles) {
+                                                   int32_t* tile_span, int64_t tiles, KnownRecord known) {
     const int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x;
     if (t == 0) {
         rec->infnan = 0;
         rec->span_max = 0;
-        rec->esc_exact = 0;
-        rec->pair_acc = 0;
-        rec->smin_acc = kMaxSlices;
+        rec->esc_done = 0;
+        write_known_record(known);
     }
     if (t < tiles) tile_span[t] = 0;
     if (t < 8) {
@@ -57,56 +56,81 @@ __global__ __launch_bounds__(256) void init_kernel(Record* rec, int32_t* eA, int
     if (t < np) eB[t] = kExpAllZero;
 }
 
-// Rows contiguous in memory (stride_r == 1): one thread per row, lanes along the rows, so
-// every load instruction of a wave reads 512 contiguous bytes.
-// grid: (rows_p/256, ceil(G/kBlocksPerWg)); tab is [2G][rows_p].
-constexpr int kScanBlocksPerWg = 4;
+constexpr int kScanBlocksPerWg = 4;    // ESC blocks a workgroup covers (measured at 8192^3: 1, 2 or 8 are 4-13 % slower)
 
-__global__ __launch_bounds__(256) void scan_rows_contig_kernel(
-    const double* __restrict__ X, int64_t stride_l, int64_t rows, int64_t rows_p, int64_t k,
-    int b, int G, int16_t* __restrict__ tab, int max_half, int32_t* __restrict__ e_out, Record* rec,
-    int check) {
-    const int64_t r = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    const int g0 = blockIdx.y * kScanBlocksPerWg;
+struct ScanSide {
+    Operand o;
+    int16_t* tab;          // [2G][rows_p]
+    int max_half;          // 1: Max in the first half of the table, Min in the second; 0: the other way round
+    int32_t* e_out;
+    int64_t row_blocks;    // workgroups along the rows
+};
+
+__device__ __forceinline__ void scan_store(const ScanSide& s, int G, int g, int64_t r, int mx, int mn) {
+    s.tab[int64_t(s.max_half ? g : G + g) * s.o.rows_p + r] = int16_t(mx);
+    s.tab[int64_t(s.max_half ? G + g : g) * s.o.rows_p + r] = int16_t(mn);
+}
+
+// Rows contiguous in memory (stride_r == 1): lanes along 64 rows, so every load instruction of a wave reads 512
+// contiguous bytes; the four waves take every fourth k of a block, which keeps a thread's chain of loads short (a
+// thread per row for four whole blocks: 28 us for 2048 x 2048, now 10), and are combined through LDS.
+__device__ __forceinline__ int scan_rows(const ScanSide& s, int64_t rb, int g0, int64_t k, int b, int G) {
+    __shared__ int2 part[kScanBlocksPerWg][4][64];     // max; min, with bit 16 set when the part holds a zero
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t r = rb * 64 + lane;
     int bad = 0;
-    int row_max = kExpAllZero;
-    for (int g = g0; g < min(G, g0 + kScanBlocksPerWg); ++g) {
+#pragma unroll 1
+    for (int u = 0; u < kScanBlocksPerWg; ++u) {
+        const int g = g0 + u;
         BlockStat st;
         st.reset();
-        if (r < rows) {
-            const int64_t l0 = int64_t(g) * b;
-            const int64_t l1 = min(k, l0 + b);
-            const uint64_t* src = reinterpret_cast<const uint64_t*>(X) + r + l0 * stride_l;
-#pragma unroll 8
-            for (int64_t l = l0; l < l1; ++l, src += stride_l) st.add(*src, bad);
+        if (g < G && r < s.o.rows) {
+            const int64_t l0 = int64_t(g) * b, l1 = min(k, l0 + b);
+            const uint64_t* src = reinterpret_cast<const uint64_t*>(s.o.X) + r + (l0 + wave) * s.o.stride_l;
+#pragma unroll 16
+            for (int64_t l = l0 + wave; l < l1; l += 4, src += 4 * s.o.stride_l) st.add(*src, bad);
         }
-        tab[(int64_t(max_half ? g : G + g)) * rows_p + r] = st.table_max();
-        tab[(int64_t(max_half ? G + g : g)) * rows_p + r] = st.table_min();
-        row_max = max(row_max, int(st.table_max()));
+        part[u][wave][lane] = make_int2(st.mx, (st.mn & 0xFFFF) | (st.any_zero << 16));
     }
-    if (row_max > kExpAllZero) atomicMax(&e_out[r], row_max);
-    if (check && bad) atomicOr(&rec->infnan, 1);
+    __syncthreads();
+    // wave u finishes block g0 + u
+    BlockStat st;
+    st.reset();
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        const int2 x = part[wave][w][lane];
+        st.mx = max(st.mx, x.x);
+        st.mn = min(st.mn, int(int16_t(x.y & 0xFFFF)));
+        st.any_zero |= x.y >> 16;
+    }
+    st.any_nz = st.mx != -32768;
+    if (g0 + wave < G) scan_store(s, G, g0 + wave, r, st.table_max(), st.table_min());
+    __syncthreads();
+    int* const row_max = reinterpret_cast<int*>(part);
+    row_max[wave * 64 + lane] = g0 + wave < G ? int(st.table_max()) : kExpAllZero;
+    __syncthreads();
+    if (wave == 0) {
+        const int e = max(max(row_max[lane], row_max[64 + lane]), max(row_max[128 + lane], row_max[192 + lane]));
+        if (e > kExpAllZero) atomicMax(&s.e_out[r], e);
+    }
+    return bad;
 }
 
 // k contiguous in memory (stride_l == 1): 16 lanes share one row so that a load instruction
 // reads 128 contiguous bytes per row; partial results are combined across the 16 lanes.
-// A workgroup covers 16 rows; grid: (rows_p/16, ceil(G/kBlocksPerWg)).
-__global__ __launch_bounds__(256) void scan_k_contig_kernel(
-    const double* __restrict__ X, int64_t stride_r, int64_t rows, int64_t rows_p, int64_t k,
-    int b, int G, int16_t* __restrict__ tab, int max_half, int32_t* __restrict__ e_out, Record* rec,
-    int check) {
+// A workgroup covers 16 rows.
+__device__ __forceinline__ int scan_k(const ScanSide& s, int64_t rb, int g0, int64_t k, int b, int G) {
     int row_max = kExpAllZero;
     const int q = threadIdx.x & 15;
-    const int64_t r = int64_t(blockIdx.x) * 16 + (threadIdx.x >> 4);
-    const int g0 = blockIdx.y * kScanBlocksPerWg;
+    const int64_t r = rb * 16 + (threadIdx.x >> 4);
     int bad = 0;
     for (int g = g0; g < min(G, g0 + kScanBlocksPerWg); ++g) {
         BlockStat st;
         st.reset();
-        if (r < rows) {
+        if (r < s.o.rows) {
             const int64_t l0 = int64_t(g) * b;
             const int64_t l1 = min(k, l0 + b);
-            const uint64_t* src = reinterpret_cast<const uint64_t*>(X) + r * stride_r;
+            const uint64_t* src = reinterpret_cast<const uint64_t*>(s.o.X) + r * s.o.stride_r;
 #pragma unroll 4
             for (int64_t l = l0 + q; l < l1; l += 16) st.add(src[l], bad);
         }
@@ -118,36 +142,41 @@ __global__ __launch_bounds__(256) void scan_k_contig_kernel(
             st.any_zero |= __shfl_xor(st.any_zero, off);
         }
         if (q == 0) {
-            tab[(int64_t(max_half ? g : G + g)) * rows_p + r] = st.table_max();
-            tab[(int64_t(max_half ? G + g : g)) * rows_p + r] = st.table_min();
+            scan_store(s, G, g, r, st.table_max(), st.table_min());
             row_max = max(row_max, int(st.table_max()));
         }
     }
-    if (q == 0 && row_max > kExpAllZero) atomicMax(&e_out[r], row_max);
+    if (q == 0 && row_max > kExpAllZero) atomicMax(&s.e_out[r], row_max);
+    return bad;
+}
+
+// Both operands in one launch: the first blocks_a workgroups scan op(A), the others op(B).
+__global__ __launch_bounds__(256) void scan_kernel(ScanSide a, ScanSide b, int64_t blocks_a, int64_t k, int bl, int G,
+                                                   Record* rec, int check) {
+    const bool second = int64_t(blockIdx.x) >= blocks_a;
+    const ScanSide& s = second ? b : a;
+    const int64_t id = int64_t(blockIdx.x) - (second ? blocks_a : 0);
+    const int64_t rb = id % s.row_blocks;
+    const int g0 = int(id / s.row_blocks) * kScanBlocksPerWg;
+    const int bad = s.o.stride_r == 1 ? scan_rows(s, rb, g0, k, bl, G) : scan_k(s, rb, g0, k, bl, G);
     if (check && bad) atomicOr(&rec->infnan, 1);
 }
 
-void launch_init(hipStream_t st, const Workspace& w, const Problem& p) {
+void launch_init(hipStream_t st, const Workspace& w, const Problem& p, const KnownRecord& known) {
     const int64_t tiles = (p.mp / kTile) * (p.np / kTile);
     int64_t nmax = p.mp > p.np ? p.mp : p.np;
     if (tiles > nmax) nmax = tiles;
     hipLaunchKernelGGL(init_kernel, dim3(unsigned((nmax + 255) / 256)), dim3(256), 0, st, w.rec, w.eA, p.mp, w.eB, p.np,
-                       w.tile_span, tiles);
+                       w.tile_span, tiles, known);
 }
 
-void launch_scan(hipStream_t st, const double* X, int64_t stride_r, int64_t stride_l, int64_t rows,
-                 int64_t rows_p, const Problem& p, int16_t* tab, bool max_first, int32_t* e_out,
-                 Record* rec, bool check_infnan) {
-    const int gy = (p.G + kScanBlocksPerWg - 1) / kScanBlocksPerWg;
-    if (stride_r == 1) {
-        hipLaunchKernelGGL(scan_rows_contig_kernel, dim3(unsigned(rows_p / 256), gy), dim3(256), 0, st,
-                           X, stride_l, rows, rows_p, p.k, p.esc_block, p.G, tab, int(max_first), e_out, rec,
-                           int(check_infnan));
-    } else {
-        hipLaunchKernelGGL(scan_k_contig_kernel, dim3(unsigned(rows_p / 16), gy), dim3(256), 0, st, X,
-                           stride_r, rows, rows_p, p.k, p.esc_block, p.G, tab, int(max_first), e_out, rec,
-                           int(check_infnan));
-    }
+void launch_scan(hipStream_t st, const Operand& a, const Operand& b, const Workspace& w, const Problem& p, bool check_infnan) {
+    const int64_t gy = (p.G + kScanBlocksPerWg - 1) / kScanBlocksPerWg;
+    auto row_blocks = [](const Operand& o) { return o.rows_p / (o.stride_r == 1 ? 64 : 16); };
+    const ScanSide sa{a, w.U, 1, w.eA, row_blocks(a)}, sb{b, w.V, 0, w.eB, row_blocks(b)};
+    const int64_t blocks_a = sa.row_blocks * gy, blocks_b = sb.row_blocks * gy;
+    hipLaunchKernelGGL(scan_kernel, dim3(unsigned(blocks_a + blocks_b)), dim3(256), 0, st, sa, sb, blocks_a, p.k, p.esc_block,
+                       p.G, w.rec, int(check_infnan));
 }
 
 }  // namespace oz

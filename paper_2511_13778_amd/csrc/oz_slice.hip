@@ -142,57 +142,42 @@ __device__ __forceinline__ void emit(const uint64_t (&bits)[16], int e_row, int 
     }
 }
 
-constexpr int kSliceChunksPerWg = 1;
-constexpr int64_t kMaxGridY = 65535;   // grid.y limit the device reports
-
 // Rows contiguous in memory: thread = row, lanes along rows; loads coalesce across the wave.
-// grid: (rows_p/256, chunks of this launch / kSliceChunksPerWg); chunk0 = first 16-k chunk of the launch
-__global__ __launch_bounds__(256) void slice_rows_contig_kernel(
-    const double* __restrict__ X, int64_t stride_l, int64_t rows, int64_t rows_p, int64_t k,
-    int64_t kp, const int32_t* __restrict__ e_row, int8_t* __restrict__ out, const Record* rec,
-    int64_t chunk0) {
-    if (rec->res.fallback) return;
-    const int S = rec->res.slices_used;
-    const int64_t r = int64_t(blockIdx.x) * 256 + threadIdx.x;
+// A workgroup cuts 256 rows x 16 k (chunk c).
+__device__ __forceinline__ void slice_rows(const Operand& o, int64_t rb, int64_t c, int64_t k, int64_t kp,
+                                           const int32_t* __restrict__ e_row, int8_t* __restrict__ out, int S) {
+    const int64_t r = rb * 256 + threadIdx.x;
     const int er = e_row[r];
-    const int64_t slice_stride = kp * rows_p;      // bytes per slice plane
     // loads are unconditional at clamped addresses (rows >= 1 and k >= 1 here); out-of-range
     // elements are then replaced by zero, so the loop has no divergent branches
-    const bool row_ok = r < rows;
-    const uint64_t* src = reinterpret_cast<const uint64_t*>(X) + (row_ok ? r : rows - 1);
-    for (int cc = 0; cc < kSliceChunksPerWg; ++cc) {
-        const int64_t c = chunk0 + int64_t(blockIdx.y) * kSliceChunksPerWg + cc;
-        uint64_t bits[16];
+    const bool row_ok = r < o.rows;
+    const uint64_t* src = reinterpret_cast<const uint64_t*>(o.X) + (row_ok ? r : o.rows - 1);
+    uint64_t bits[16];
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const int64_t l = c * 16 + e;
-            const uint64_t x = __builtin_nontemporal_load(&src[(l < k ? l : k - 1) * stride_l]);
-            bits[e] = (row_ok && l < k) ? x : 0ull;
-        }
-        emit(bits, er, S, out + (c * rows_p + r) * 16, slice_stride);
+    for (int e = 0; e < 16; ++e) {
+        const int64_t l = c * 16 + e;
+        const uint64_t x = __builtin_nontemporal_load(&src[(l < k ? l : k - 1) * o.stride_l]);
+        bits[e] = (row_ok && l < k) ? x : 0ull;
     }
+    emit(bits, er, S, out + (c * o.rows_p + r) * 16, kp * o.rows_p);
 }
 
 // k contiguous in memory: a 64-row x 64-k tile is read with lanes along k (512 contiguous bytes
 // per wave load), transposed through LDS, then each thread owns (row, 16-k chunk).
-// grid: (rows_p/64, kp/64)
-__global__ __launch_bounds__(256) void slice_k_contig_kernel(
-    const double* __restrict__ X, int64_t stride_r, int64_t rows, int64_t rows_p, int64_t k,
-    int64_t kp, const int32_t* __restrict__ e_row, int8_t* __restrict__ out, const Record* rec) {
-    __shared__ uint64_t T[64][65];
-    if (rec->res.fallback) return;
-    const int S = rec->res.slices_used;
-    const int64_t r0 = int64_t(blockIdx.x) * 64, l0 = int64_t(blockIdx.y) * 64;
+__device__ __forceinline__ void slice_k(const Operand& o, int64_t rb, int64_t lb, int64_t k, int64_t kp,
+                                        const int32_t* __restrict__ e_row, int8_t* __restrict__ out, int S,
+                                        uint64_t (*T)[65]) {
+    const int64_t r0 = rb * 64, l0 = lb * 64;
     {
         const int ll = threadIdx.x & 63;
         const int rr0 = threadIdx.x >> 6;
-        const uint64_t* src = reinterpret_cast<const uint64_t*>(X);
+        const uint64_t* src = reinterpret_cast<const uint64_t*>(o.X);
 #pragma unroll
         for (int it = 0; it < 16; ++it) {
             const int rr = rr0 + it * 4;
             const int64_t r = r0 + rr, l = l0 + ll;
-            const uint64_t x = __builtin_nontemporal_load(&src[(r < rows ? r : rows - 1) * stride_r + (l < k ? l : k - 1)]);
-            T[rr][ll] = (r < rows && l < k) ? x : 0ull;
+            const uint64_t x = __builtin_nontemporal_load(&src[(r < o.rows ? r : o.rows - 1) * o.stride_r + (l < k ? l : k - 1)]);
+            T[rr][ll] = (r < o.rows && l < k) ? x : 0ull;
         }
     }
     __syncthreads();
@@ -203,23 +188,46 @@ __global__ __launch_bounds__(256) void slice_k_contig_kernel(
 #pragma unroll
     for (int e = 0; e < 16; ++e) bits[e] = T[rr][cc * 16 + e];
     const int64_t c = l0 / 16 + cc;
-    emit(bits, er, S, out + (c * rows_p + r) * 16, kp * rows_p);
+    emit(bits, er, S, out + (c * o.rows_p + r) * 16, kp * o.rows_p);
 }
 
-void launch_slice(hipStream_t st, const double* X, int64_t stride_r, int64_t stride_l, int64_t rows,
-                  int64_t rows_p, const Problem& p, const int32_t* e_row, int8_t* slices,
-                  const Record* rec) {
-    if (stride_r == 1) {
-        // k chunks ride on grid.y: the longest k (2^21) has 131072 of them, launched in slabs
-        const int64_t groups = p.kp / 16 / kSliceChunksPerWg;
-        for (int64_t g0 = 0; g0 < groups; g0 += kMaxGridY) {
-            const unsigned gy = unsigned(groups - g0 < kMaxGridY ? groups - g0 : kMaxGridY);
-            hipLaunchKernelGGL(slice_rows_contig_kernel, dim3(unsigned(rows_p / 256), gy), dim3(256), 0, st, X,
-                               stride_l, rows, rows_p, p.k, p.kp, e_row, slices, rec, g0 * kSliceChunksPerWg);
-        }
+struct SliceSide {
+    Operand o;
+    const int32_t* e_row;
+    int8_t* out;
+    int64_t row_blocks, blocks;      // workgroups along the rows, in all
+};
+
+// workgroups [0, a.blocks) cut a, the others b.  The LDS tile is dynamic: an operand with contiguous rows needs none
+__global__ __launch_bounds__(256) void slice_kernel(SliceSide a, SliceSide b, int64_t k, int64_t kp, const Record* rec) {
+    extern __shared__ uint64_t slice_lds[];
+    if (rec->res.fallback) return;
+    const int S = rec->res.slices_used;
+    const bool second = int64_t(blockIdx.x) >= a.blocks;
+    const SliceSide& s = second ? b : a;
+    const int64_t id = int64_t(blockIdx.x) - (second ? a.blocks : 0);
+    const int64_t rb = id % s.row_blocks, cb = id / s.row_blocks;
+    if (s.o.stride_r == 1) slice_rows(s.o, rb, cb, k, kp, s.e_row, s.out, S);
+    else slice_k(s.o, rb, cb, k, kp, s.e_row, s.out, S, reinterpret_cast<uint64_t (*)[65]>(slice_lds));
+}
+
+void launch_slice(hipStream_t st, const Operand& a, const Operand& b, const Workspace& w, const Problem& p) {
+    auto side = [&](const Operand& o, const int32_t* e, int8_t* out) {
+        const bool rows = o.stride_r == 1;
+        const int64_t rbs = o.rows_p / (rows ? 256 : 64);
+        return SliceSide{o, e, out, rbs, rbs * (p.kp / (rows ? 16 : 64))};
+    };
+    const SliceSide sa = side(a, w.eA, w.As), sb = side(b, w.eB, w.Bs);
+    constexpr size_t kLds = 64 * 65 * sizeof(uint64_t);
+    const size_t lds_a = a.stride_r == 1 ? 0 : kLds, lds_b = b.stride_r == 1 ? 0 : kLds;
+    // Both operands in one launch where they need the same LDS, or where the launch itself is what counts (fewer
+    // workgroups than 16 per CU); otherwise the LDS tile of the one would halve the occupancy of the other.
+    if (lds_a == lds_b || sa.blocks + sb.blocks < int64_t(16) * p.num_cu) {
+        hipLaunchKernelGGL(slice_kernel, dim3(unsigned(sa.blocks + sb.blocks)), dim3(256), lds_a > lds_b ? lds_a : lds_b, st, sa,
+                           sb, p.k, p.kp, w.rec);
     } else {
-        hipLaunchKernelGGL(slice_k_contig_kernel, dim3(unsigned(rows_p / 64), unsigned(p.kp / 64)), dim3(256),
-                           0, st, X, stride_r, rows, rows_p, p.k, p.kp, e_row, slices, rec);
+        hipLaunchKernelGGL(slice_kernel, dim3(unsigned(sa.blocks)), dim3(256), lds_a, st, sa, sb, p.k, p.kp, w.rec);
+        hipLaunchKernelGGL(slice_kernel, dim3(unsigned(sb.blocks)), dim3(256), lds_b, st, sb, sa, p.k, p.kp, w.rec);
     }
 }
 
