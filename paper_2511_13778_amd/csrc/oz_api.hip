@@ -344,7 +344,7 @@ oz_status_t oz_native_dgemm(oz_handle_t h, void* stream, char transa, char trans
     if (!on_handle_device(*h)) return OZ_ERR_DEVICE;
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (k == 0 || alpha == 0.0) launch_scale_c(st, m, n, beta, C, ldc);
-    else launch_dgemm_f64(st, nullptr, KnownRecord{}, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc);
+    else launch_dgemm_f64(st, nullptr, KnownRecord{}, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, h->num_cu);
     return hipGetLastError() == hipSuccess ? OZ_OK : OZ_ERR_HIP;
 }
 
@@ -395,7 +395,7 @@ oz_status_t dgemm_impl(oz_handle_t h, void* stream, char transa, char transb, in
 
     if (opts->mode == OZ_NATIVE) {
         for (int s = 0; s <= 5; ++s) clk.done(s);
-        launch_dgemm_f64(st, nullptr, KnownRecord{w.rec, result, known_verdict(p, *opts, 0)}, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, f64_scratch, f64_scratch_bytes);
+        launch_dgemm_f64(st, nullptr, KnownRecord{w.rec, result, known_verdict(p, *opts, 0)}, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, h->num_cu, f64_scratch, f64_scratch_bytes);
         clk.done(6);
         return hipGetLastError() == hipSuccess ? OZ_OK : OZ_ERR_HIP;
     }
@@ -407,7 +407,7 @@ oz_status_t dgemm_impl(oz_handle_t h, void* stream, char transa, char transb, in
         if (s_min > kMaxSlices) s_min = kMaxSlices;
         if (emulation_slower(h->hm, s_min, m, n, k)) {
             for (int s = 0; s <= 5; ++s) clk.done(s);
-            launch_dgemm_f64(st, nullptr, KnownRecord{w.rec, result, known_verdict(p, *opts, 3)}, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, f64_scratch, f64_scratch_bytes);
+            launch_dgemm_f64(st, nullptr, KnownRecord{w.rec, result, known_verdict(p, *opts, 3)}, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, h->num_cu, f64_scratch, f64_scratch_bytes);
             clk.done(6);
             return hipGetLastError() == hipSuccess ? OZ_OK : OZ_ERR_HIP;
         }
@@ -427,7 +427,7 @@ oz_status_t dgemm_impl(oz_handle_t h, void* stream, char transa, char transb, in
     clk.done(4);
     launch_recompose(st, w, p, split, alpha, beta, C, ldc);
     clk.done(5);
-    if (guarded) launch_dgemm_f64(st, w.rec, KnownRecord{}, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, f64_scratch, f64_scratch_bytes);
+    if (guarded) launch_dgemm_f64(st, w.rec, KnownRecord{}, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, h->num_cu, f64_scratch, f64_scratch_bytes);
     clk.done(6);
     return hipGetLastError() == hipSuccess ? OZ_OK : OZ_ERR_HIP;
 }

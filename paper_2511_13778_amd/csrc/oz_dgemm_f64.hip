@@ -297,10 +297,11 @@ __global__ __launch_bounds__(256, 2) void dgemm_f64_kernel(
 template <int T>
 __global__ __launch_bounds__(256) void dgemm_f64_reduce_kernel(const Record* rec, int64_t m, int64_t n, double alpha,
                                                                double beta, double* __restrict__ C, int64_t ldc, int ntm,
-                                                               int ntn, int zsplit, const double* __restrict__ partial) {
+                                                               int ntn, int zsplit, const double* __restrict__ partial,
+                                                               int64_t j_first) {
     if (rec && !rec->res.fallback) return;
     const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    const int64_t j = blockIdx.y;
+    const int64_t j = j_first + blockIdx.y;
     if (i >= m) return;
     const int64_t ti = i / T, tj = j / T;
     const double* src = partial + (tj * ntm + ti) * (T * T) + (j - tj * T) * T + (i - ti * T);
@@ -314,64 +315,52 @@ __global__ __launch_bounds__(256) void dgemm_f64_reduce_kernel(const Record* rec
 
 void launch_dgemm_f64(hipStream_t st, const Record* rec, const KnownRecord& known, bool ta, bool tb, int64_t m, int64_t n, int64_t k,
                       double alpha, const double* A, int64_t lda, const double* B, int64_t ldb, double beta,
-                      double* C, int64_t ldc, void* scratch, size_t scratch_bytes) {
+                      double* C, int64_t ldc, int num_cu, void* scratch, size_t scratch_bytes) {
     // op(A)(i,l): N -> A[i + l*lda] (rows contiguous), T -> A[l + i*lda]
     // op(B)(l,j): N -> B[l + j*ldb] (k contiguous),    T -> B[j + l*ldb] (rows contiguous)
     const int64_t a_sr = ta ? lda : 1, a_sl = ta ? 1 : lda;
     const int64_t b_sr = tb ? 1 : ldb, b_sl = tb ? ldb : 1;
     const bool ac = !ta, bc = tb;
-    // 64 x 64 tiles when 128 x 128 tiles would leave more than half of the 2 x 256 workgroup slots empty
-    const int64_t tiles128 = ((m + 127) / 128) * ((n + 127) / 128);
-    int device = 0, num_cu = 256;
-    if (hipGetDevice(&device) == hipSuccess) (void)hipDeviceGetAttribute(&num_cu, hipDeviceAttributeMultiprocessorCount, device);
     // the interior path keeps every offset inside a K step of a tile in 32 bits (a lane's own: at most
     // 15 leading dimensions plus a row of the tile; its elements: up to 7 x 16 leading dimensions
     // further on; in bytes); operands cut out of a very large parent matrix take the bounds-checked
     // path, which indexes in 64 bits
     const int64_t ld_max = lda > ldb ? lda : ldb;
     const bool wide_ld = (128 * ld_max + 256) * 8 >= (int64_t(1) << 32);
-    // Few tiles and a long k (a skinny or small output): with scratch memory at hand, the k range is split
-    // over zsplit workgroups per 128 x 128 tile so that the two workgroup slots of every CU are filled;
-    // the parts leave partial products in the scratch memory and a second kernel adds them in the order
-    // of the parts (deterministic) and applies alpha and beta.  Each part gets at least 512 of k.
+    // Tile edge T and number of parts of the k range zsplit.  With scratch memory at hand, k may be split over
+    // several workgroups per tile: they leave partial products in the scratch memory and a second kernel adds them in
+    // the order of the parts (deterministic) and applies alpha and beta.  Small tiles and splits fill the chip, large
+    // tiles need fewer bytes per flop.  Estimated time in us of a choice, with u = workgroups of the fullest CU:
+    //   a K step of 16   T = 128: 1.8 u from u = 2 on (the matrix unit's rate: two workgroups share a CU), 1.95 alone
+    //                    T = 64:  0.05 + 0.5 u from u = 2 on; one workgroup alone waits for its loads, 0.62 on an empty
+    //                             chip, 0.74 on a full one
+    //   start and end    8 (T = 128) or 6 (T = 64); a split adds a launch of 4 and zsplit + 2 passes over C at 4.5 TB/s.
+    // Measured against one choice by the number of tiles: 512^3 27.8 -> 16.9 us (T = 64, 4 parts), 500x300x700 39 -> 17
+    // (6 parts), 200x300x5000 86 -> 31 (12), 1000x1300x777 66 -> 54 (3), 3000x3000x400 150 -> 127 (T = 64, whole),
+    // 2000x1800x1000 138 -> 128 (T = 128, whole).
+    int T = ((m + 127) / 128) * ((n + 127) / 128) < num_cu ? 64 : 128;
     int zsplit = 1;
-    int64_t kpart = 0;
-    if (tiles128 < num_cu && !wide_ld && scratch != nullptr) {
-        int64_t z = (2 * int64_t(num_cu)) / tiles128;
-        if (z > 16) z = 16;
-        if (z > k / 512) z = k / 512;
-        const int64_t fit = int64_t(scratch_bytes / (size_t(tiles128) * 128 * 128 * 8));
-        if (z > fit) z = fit;
-        // A 64 x 64 tile's K step takes about 0.3 of a 128 x 128 tile's, so against the unsplit 64 x 64 path a
-        // split pays from four parts on, or from two if the parts give every CU a workgroup (measured:
-        // 512 x 512 x 8192 with 5 parts 0.20 ms against 0.40 ms; 1024^3 with 2 parts is slower than unsplit)
-        if (z >= 4 || (z >= 2 && z * tiles128 >= num_cu)) {
-            zsplit = int(z);
-            kpart = k / z / kDK * kDK;
+    if (!wide_ld && k >= kDK) {
+        double best = 0.0;
+        for (int t = 64; t <= 128; t += 64) {
+            const int64_t tiles = ((m + t - 1) / t) * ((n + t - 1) / t);
+            const int64_t k_least = t == 64 ? 64 : 256;      // what a part keeps at least
+            for (int64_t z = 1; z <= 16; ++z) {
+                if (z > 1 && (scratch == nullptr || k / z < k_least || size_t(tiles * z) * t * t * 8 > scratch_bytes)) break;
+                const double u = double((tiles * z + num_cu - 1) / num_cu), steps = double((k + z * kDK - 1) / (z * kDK));
+                const double alone = 0.62 + 0.12 * double(tiles * z) / num_cu;
+                const double us = (t == 128 ? 8.0 + (u > 1.0 ? 1.8 * u : 1.95) * steps : 6.0 + (u > 1.0 ? 0.05 + 0.5 * u : alone) * steps) +
+                                  (z > 1 ? 4.0 + double(z + 2) * double(m) * double(n) * 8.0 / 4.5e6 : 0.0);
+                if (best == 0.0 || us < best) {
+                    best = us;
+                    T = t;
+                    zsplit = int(z);
+                }
+            }
         }
     }
-    // Enough tiles for every CU, but not a whole number of rounds (a CU runs two 128 x 128 tiles at a time and
-    // a launch lasts as long as the CU with the most tiles): a k split makes the work units smaller, so the
-    // last round wastes less.  Estimate per part count z: ceil(tiles * z / CUs) units of 2 * 128 * 128 * k / z
-    // flops on a CU that sustains about 289 flops per ns, plus (z + 2) passes over C for the partial tiles at
-    // 4.5 TB/s.  Taken when it saves at least 5 % (3072^3: 3 rounds of 576 tiles become 9 / 4 with z = 4).
-    if (zsplit == 1 && tiles128 >= num_cu && !wide_ld && scratch != nullptr) {
-        auto estimate_ns = [&](int64_t z) -> double {
-            const int64_t units_per_cu = (tiles128 * z + num_cu - 1) / num_cu;
-            return double(units_per_cu) * (2.0 * 128 * 128 * double(k) / double(z)) / 289.0 +
-                   (z > 1 ? double(z + 2) * double(m) * double(n) * 8.0 / 4500.0 : 0.0);
-        };
-        const int64_t fit = int64_t(scratch_bytes / (size_t(tiles128) * 128 * 128 * 8));
-        int64_t best = 1;
-        for (int64_t z = 2; z <= 8 && z <= k / 512 && z <= fit; ++z)
-            if (estimate_ns(z) < estimate_ns(best)) best = z;
-        if (best > 1 && estimate_ns(best) < 0.95 * estimate_ns(1)) {
-            zsplit = int(best);
-            kpart = k / best / kDK * kDK;
-        }
-    }
-    const bool small = tiles128 < num_cu && zsplit == 1;
-    const int T = small ? 64 : 128;
+    const int64_t kpart = zsplit > 1 ? k / zsplit / kDK * kDK : 0;
+    const bool small = T == 64;
     const int ntm = int((m + T - 1) / T), ntn = int((n + T - 1) / T);
     const dim3 grid(unsigned(ntm) * unsigned(ntn) * unsigned(zsplit)), block(256);
     double* partial = static_cast<double*>(scratch);
@@ -399,9 +388,15 @@ void launch_dgemm_f64(hipStream_t st, const Record* rec, const KnownRecord& know
 #undef OZ_DG
     if (zsplit > 1) {
         const unsigned gx = unsigned((m + 255) / 256);
-        // n < 128 * 256 here (fewer than 256 tiles of 128 columns), so n fits grid.y
-        hipLaunchKernelGGL((dgemm_f64_reduce_kernel<128>), dim3(gx, unsigned(n)), dim3(256), 0, st, rec, m, n, alpha, beta,
-                           C, ldc, ntm, ntn, zsplit, partial);
+        for (int64_t j = 0; j < n; j += 65535) {
+            const dim3 rgrid(gx, unsigned(n - j < 65535 ? n - j : 65535));
+            if (small)
+                hipLaunchKernelGGL((dgemm_f64_reduce_kernel<64>), rgrid, dim3(256), 0, st, rec, m, n, alpha, beta, C, ldc, ntm,
+                                   ntn, zsplit, partial, j);
+            else
+                hipLaunchKernelGGL((dgemm_f64_reduce_kernel<128>), rgrid, dim3(256), 0, st, rec, m, n, alpha, beta, C, ldc, ntm,
+                                   ntn, zsplit, partial, j);
+        }
     }
 }
 

@@ -184,7 +184,7 @@ void launch_recompose(hipStream_t st, const Workspace& w, const Problem& p, cons
 // known: a record to write on the way
 void launch_dgemm_f64(hipStream_t st, const Record* rec, const KnownRecord& known, bool ta, bool tb, int64_t m, int64_t n,
                       int64_t k, double alpha, const double* A, int64_t lda, const double* B,
-                      int64_t ldb, double beta, double* C, int64_t ldc, void* scratch = nullptr,
+                      int64_t ldb, double beta, double* C, int64_t ldc, int num_cu, void* scratch = nullptr,
                       size_t scratch_bytes = 0);
 void launch_scale_c(hipStream_t st, int64_t m, int64_t n, double beta, double* C, int64_t ldc);
 // complex product by the 4M method: split an interleaved complex matrix into planar parts (conj negates

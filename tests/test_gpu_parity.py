@@ -996,3 +996,21 @@ def test_slice_gemm_per_block_order(lib, m, n, k):
     assert (res.slices_used, res.slices_min, res.pair_tiles) == (tr.verdict.slices_used, tr.verdict.slices_min, tr.verdict.pair_tiles)
     assert res.slices_min < res.slices_used
     np.testing.assert_array_equal(got, tr.C)
+
+
+@pytest.mark.parametrize("ta,tb,m,n,k", [("N", "N", 512, 512, 512), ("T", "N", 500, 301, 703), ("N", "T", 65, 130, 5000), ("T", "T", 1000, 1300, 777),
+                                         ("N", "N", 64, 64, 128), ("T", "N", 2000, 1799, 300)])
+def test_native_small_tiles_with_parts(lib, ta, tb, m, n, k):
+    # the FP64 GEMM on 64 x 64 tiles, whole and in parts of the k range (edges, k mod 16), through the call as shipped:
+    # inside the accumulation bound of any order of summation, the same twice
+    g, h = lib
+    rng = np.random.default_rng(m + n + k)
+    A, B, Cin = rng.standard_normal((m, k)), rng.standard_normal((k, n)), rng.standard_normal((m, n))
+    opts = dict(mode=g.OZ_DYNAMIC, max_bits=200, heuristic=1, tile_slices=1)
+    got, gm, res = run_gpu(g, h, A, B, 1.5, 0.5, Cin, ta, tb, pad=3, **opts)
+    assert (res.fallback, res.reason) == (1, oz.REASON_HEURISTIC)
+    # |computed - exact| <= (k + 3) * 2^-53 * (|alpha||A||B| + |beta||C|) for each of the two sides (gamma_k, three roundings behind it)
+    slack = 2.0 * (k + 3) * 2.0 ** -53 * (1.5 * (np.abs(A) @ np.abs(B)) + 0.5 * np.abs(Cin))
+    assert np.all(np.abs(got - (1.5 * (A @ B) + 0.5 * Cin)) <= slack)
+    again, _, _ = run_gpu(g, h, A, B, 1.5, 0.5, Cin, ta, tb, pad=3, **opts)
+    np.testing.assert_array_equal(got, again)
