@@ -246,7 +246,7 @@ __global__ __launch_bounds__(256) void gemm_i8_kernel(const int8_t* __restrict__
     int S = slices_of(ui, uj);
 
     // this workgroup's share of k, in steps of 64: part z of zsplit equal parts of the whole range
-    const int kt_total = int(kp / kBK);
+    const int kt_total = g.kt_total;
     const int kt_first = int(int64_t(kt_total) * z / g.zsplit);
     const int kt_end = int(int64_t(kt_total) * (z + 1) / g.zsplit);
     const int kt_per_block = int(kblk / kBK);
@@ -726,7 +726,7 @@ __global__ __launch_bounds__(256) void add_parts_kernel(const int32_t* __restric
     const int S = split_unit(g, local, tile_S, S_all, ui, uj);
     if (ui >= g.um || uj >= g.un) return;
     const int units = tile_S ? 4 * g.count : g.count;
-    const int kt_total = int(kp / kBK), kt_per_block = int(kblk / kBK);
+    const int kt_total = g.kt_total, kt_per_block = int(kblk / kBK);
     const int64_t slot_words = part_slot_bytes(s_cap) / 4;
     int z_lo, z_hi;
     parts_of_block(kt_total, kt_per_block, g.zsplit, kb, z_lo, z_hi);
@@ -805,7 +805,8 @@ struct LaunchPlan {
         g.full_chip = p.num_cu == 8 * kRoundUnits ? 1 : 0;
         per_pos = p.tile_mode ? 4 : 1;
         positions = p.tile_mode ? g.nti * g.ntj : g.um * g.un;
-        kt = int(p.kp / kBK);
+        kt = int((p.k + kBK - 1) / kBK);
+        g.kt_total = kt;
         raw_units = 4 * p.raw_slots;
         min_entries = 0;
         for (int n = p.s_min; n > 0; n -= kDiag) min_entries += n;

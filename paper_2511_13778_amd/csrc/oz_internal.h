@@ -102,6 +102,7 @@ struct GemmGrid {
     int nti, ntj;      // kTile x kTile blocks of the padded C
     int um, un;        // units with at least one row / column of C
     int begin, count;  // plain order: units [begin, begin + count); per-block order: as many positions of the order table
+    int kt_total;      // 64s of k, the last one possibly part padding
     int zsplit;        // parts of the k range per unit
     int nkb_part;      // k-blocks a part's slot has room for (parts other than the first)
     int full_chip;     // 8 XCDs of 32 CUs: the in-step waits make sense

@@ -97,7 +97,7 @@ __global__ __launch_bounds__(256) void recompose_kernel(std::conditional_t<KIND 
 #pragma unroll
         for (int q = 0; q < kRecI; ++q) R[jj][q] = 0.0;
     constexpr int kBatch = 8;
-    const int kt_total = int(kp / kBK), kt_per_block = int(kblk / kBK);
+    const int kt_total = split.g.kt_total, kt_per_block = int(kblk / kBK);
     for (int kb = 0; kb < nkb; ++kb) {
         // the planes are read once: streaming loads keep them out of the way of C
         const int64_t t_at = ((int64_t(kb) * np + j0) * mp + i0) / 4;                               // + jj * mp / 4
