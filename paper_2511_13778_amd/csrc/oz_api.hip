@@ -236,7 +236,8 @@ oz_status_t oz_create(oz_handle_t* handle, int device) {
         int prev = -1;
         h->static_ws = nullptr;
         bool ok = hipGetDevice(&prev) == hipSuccess && hipSetDevice(device) == hipSuccess &&
-                  hipGetSymbolAddress(&h->static_ws, HIP_SYMBOL(scratch)) == hipSuccess && h->static_ws != nullptr;
+                  hipGetSymbolAddress(&h->static_ws, HIP_SYMBOL(scratch)) == hipSuccess && h->static_ws != nullptr &&
+                  prepare_gemm_i8();
         if (prev >= 0 && prev != device) ok = (hipSetDevice(prev) == hipSuccess) && ok;
         if (!ok) {
             delete h;

@@ -859,12 +859,14 @@ void tile_order_shape(const Problem& p, int& first, int& deal) {
     deal = (lp.g.full_chip && lp.full != 0 && lp.positions <= (1 << 16)) ? 1 : 0;
 }
 
+bool prepare_gemm_i8() {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_i8_kernel<false>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds) == hipSuccess &&
+           hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_i8_kernel<true>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds) == hipSuccess;
+}
+
 SplitPlan launch_gemm_i8(hipStream_t st, const Workspace& w, const Problem& p) {
-    // the attribute is per device and cheap to set; no process-wide cache that a second device would miss
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_i8_kernel<false>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds);
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_i8_kernel<true>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds);
     const LaunchPlan lp(p);
     const int32_t* tile_S = p.tile_mode ? w.tile_S : nullptr;
     auto launch = [&](int begin, int count, Split sp) -> GemmGrid {

@@ -175,6 +175,8 @@ void launch_known_record(hipStream_t st, const KnownRecord& known);
 void launch_slice(hipStream_t st, const Operand& a, const Operand& b, const Workspace& w, const Problem& p);
 // per-block mode: blocks of the slice GEMM's first launch, and whether they are sorted by slice count
 void tile_order_shape(const Problem& p, int& first, int& deal);
+// allows the slice GEMM its LDS on the current device (a property of the device: set when a handle is made for it)
+bool prepare_gemm_i8();
 // returns what the recomposition still has to put together
 SplitPlan launch_gemm_i8(hipStream_t st, const Workspace& w, const Problem& p);
 void launch_recompose(hipStream_t st, const Workspace& w, const Problem& p, const SplitPlan& split, double alpha,
