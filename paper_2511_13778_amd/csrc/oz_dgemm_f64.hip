@@ -335,6 +335,7 @@ void launch_dgemm_f64(hipStream_t st, const Record* rec, const KnownRecord& know
     //                    T = 64:  0.05 + 0.5 u from u = 2 on; one workgroup alone waits for its loads, 0.62 on an empty
     //                             chip, 0.74 on a full one
     //   start and end    8 (T = 128) or 6 (T = 64); a split adds a launch of 4 and zsplit + 2 passes over C at 4.5 TB/s.
+    //                    A guarded call pays that launch whether it falls back or not: 20 there.
     // Measured against one choice by the number of tiles: 512^3 27.8 -> 16.9 us (T = 64, 4 parts), 500x300x700 39 -> 17
     // (6 parts), 200x300x5000 86 -> 31 (12), 1000x1300x777 66 -> 54 (3), 3000x3000x400 150 -> 127 (T = 64, whole),
     // 2000x1800x1000 138 -> 128 (T = 128, whole).
@@ -350,7 +351,7 @@ void launch_dgemm_f64(hipStream_t st, const Record* rec, const KnownRecord& know
                 const double u = double((tiles * z + num_cu - 1) / num_cu), steps = double((k + z * kDK - 1) / (z * kDK));
                 const double alone = 0.62 + 0.12 * double(tiles * z) / num_cu;
                 const double us = (t == 128 ? 8.0 + (u > 1.0 ? 1.8 * u : 1.95) * steps : 6.0 + (u > 1.0 ? 0.05 + 0.5 * u : alone) * steps) +
-                                  (z > 1 ? 4.0 + double(z + 2) * double(m) * double(n) * 8.0 / 4.5e6 : 0.0);
+                                  (z > 1 ? (rec ? 20.0 : 4.0) + double(z + 2) * double(m) * double(n) * 8.0 / 4.5e6 : 0.0);
                 if (best == 0.0 || us < best) {
                     best = us;
                     T = t;
