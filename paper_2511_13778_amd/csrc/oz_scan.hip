@@ -74,13 +74,13 @@ __device__ __forceinline__ void scan_store(const ScanSide& s, int G, int g, int6
 // Rows contiguous in memory (stride_r == 1): lanes along 64 rows, so every load instruction of a wave reads 512
 // contiguous bytes; the four waves take every fourth k of a block, which keeps a thread's chain of loads short (a
 // thread per row for four whole blocks: 28 us for 2048 x 2048, now 10), and are combined through LDS.
-__device__ __forceinline__ int scan_rows(const ScanSide& s, int64_t rb, int g0, int64_t k, int b, int G) {
+__device__ __forceinline__ int scan_rows(const ScanSide& s, int64_t rb, int g0, int per, int64_t k, int b, int G) {
     __shared__ int2 part[kScanBlocksPerWg][4][64];     // max; min, with bit 16 set when the part holds a zero
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t r = rb * 64 + lane;
     int bad = 0;
 #pragma unroll 1
-    for (int u = 0; u < kScanBlocksPerWg; ++u) {
+    for (int u = 0; u < per; ++u) {
         const int g = g0 + u;
         BlockStat st;
         st.reset();
@@ -94,20 +94,21 @@ __device__ __forceinline__ int scan_rows(const ScanSide& s, int64_t rb, int g0, 
     }
     __syncthreads();
     // wave u finishes block g0 + u
+    const bool mine = wave < per && g0 + wave < G;
     BlockStat st;
     st.reset();
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-        const int2 x = part[wave][w][lane];
+        const int2 x = part[mine ? wave : 0][w][lane];
         st.mx = max(st.mx, x.x);
         st.mn = min(st.mn, int(int16_t(x.y & 0xFFFF)));
         st.any_zero |= x.y >> 16;
     }
     st.any_nz = st.mx != -32768;
-    if (g0 + wave < G) scan_store(s, G, g0 + wave, r, st.table_max(), st.table_min());
+    if (mine) scan_store(s, G, g0 + wave, r, st.table_max(), st.table_min());
     __syncthreads();
     int* const row_max = reinterpret_cast<int*>(part);
-    row_max[wave * 64 + lane] = g0 + wave < G ? int(st.table_max()) : kExpAllZero;
+    row_max[wave * 64 + lane] = mine ? int(st.table_max()) : kExpAllZero;
     __syncthreads();
     if (wave == 0) {
         const int e = max(max(row_max[lane], row_max[64 + lane]), max(row_max[128 + lane], row_max[192 + lane]));
@@ -119,12 +120,12 @@ __device__ __forceinline__ int scan_rows(const ScanSide& s, int64_t rb, int g0, 
 // k contiguous in memory (stride_l == 1): 16 lanes share one row so that a load instruction
 // reads 128 contiguous bytes per row; partial results are combined across the 16 lanes.
 // A workgroup covers 16 rows.
-__device__ __forceinline__ int scan_k(const ScanSide& s, int64_t rb, int g0, int64_t k, int b, int G) {
+__device__ __forceinline__ int scan_k(const ScanSide& s, int64_t rb, int g0, int per, int64_t k, int b, int G) {
     int row_max = kExpAllZero;
     const int q = threadIdx.x & 15;
     const int64_t r = rb * 16 + (threadIdx.x >> 4);
     int bad = 0;
-    for (int g = g0; g < min(G, g0 + kScanBlocksPerWg); ++g) {
+    for (int g = g0; g < min(G, g0 + per); ++g) {
         BlockStat st;
         st.reset();
         if (r < s.o.rows) {
@@ -151,14 +152,14 @@ __device__ __forceinline__ int scan_k(const ScanSide& s, int64_t rb, int g0, int
 }
 
 // Both operands in one launch: the first blocks_a workgroups scan op(A), the others op(B).
-__global__ __launch_bounds__(256) void scan_kernel(ScanSide a, ScanSide b, int64_t blocks_a, int64_t k, int bl, int G,
-                                                   Record* rec, int check) {
+__global__ __launch_bounds__(256) void scan_kernel(ScanSide a, ScanSide b, int64_t blocks_a, int per, int64_t k, int bl,
+                                                   int G, Record* rec, int check) {
     const bool second = int64_t(blockIdx.x) >= blocks_a;
     const ScanSide& s = second ? b : a;
     const int64_t id = int64_t(blockIdx.x) - (second ? blocks_a : 0);
     const int64_t rb = id % s.row_blocks;
-    const int g0 = int(id / s.row_blocks) * kScanBlocksPerWg;
-    const int bad = s.o.stride_r == 1 ? scan_rows(s, rb, g0, k, bl, G) : scan_k(s, rb, g0, k, bl, G);
+    const int g0 = int(id / s.row_blocks) * per;
+    const int bad = s.o.stride_r == 1 ? scan_rows(s, rb, g0, per, k, bl, G) : scan_k(s, rb, g0, per, k, bl, G);
     if (check && bad) atomicOr(&rec->infnan, 1);
 }
 
@@ -171,11 +172,15 @@ void launch_init(hipStream_t st, const Workspace& w, const Problem& p, const Kno
 }
 
 void launch_scan(hipStream_t st, const Operand& a, const Operand& b, const Workspace& w, const Problem& p, bool check_infnan) {
-    const int64_t gy = (p.G + kScanBlocksPerWg - 1) / kScanBlocksPerWg;
     auto row_blocks = [](const Operand& o) { return o.rows_p / (o.stride_r == 1 ? 64 : 16); };
     const ScanSide sa{a, w.U, 1, w.eA, row_blocks(a)}, sb{b, w.V, 0, w.eB, row_blocks(b)};
+    // ESC blocks per workgroup: four, or one where four would leave fewer than four workgroups per CU: such a call waits
+    // for the loads of one block after the other (200x300x260: 11.5 us with four, 4.5 with one), a larger one is bound
+    // by the bytes read and sets eA and eB with a quarter of the atomics
+    const int per = (sa.row_blocks + sb.row_blocks) * ((p.G + 3) / 4) < int64_t(4) * p.num_cu ? 1 : kScanBlocksPerWg;
+    const int64_t gy = (p.G + per - 1) / per;
     const int64_t blocks_a = sa.row_blocks * gy, blocks_b = sb.row_blocks * gy;
-    hipLaunchKernelGGL(scan_kernel, dim3(unsigned(blocks_a + blocks_b)), dim3(256), 0, st, sa, sb, blocks_a, p.k, p.esc_block,
+    hipLaunchKernelGGL(scan_kernel, dim3(unsigned(blocks_a + blocks_b)), dim3(256), 0, st, sa, sb, blocks_a, per, p.k, p.esc_block,
                        p.G, w.rec, int(check_infnan));
 }
 
