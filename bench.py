@@ -184,7 +184,7 @@ def main():
     roofline = None
     if S > 0 and gemm_ms > 0:
         achieved = pairs * flops / (gemm_ms * 1e-3) * 1e-12
-        roofline = {"bound": "mfma", "kernel": "gemm_i8_kernel (v_mfma_i32_32x32x32_i8)", "achieved": achieved,
+        roofline = {"bound": "mfma", "kernel": "gemm_i8_kernel (v_mfma_i32_16x16x64_i8)", "achieved": achieved,
                     "peak": INT8_PEAK_TOPS, "unit": "TFLOP/s", "frac": achieved / INT8_PEAK_TOPS,
                     "traffic": traffic, "traffic_source": "stored rocprofv3 --pmc measurement (profiles/hbm_traffic.json), "
                                                           "not taken in this run",
