@@ -258,9 +258,10 @@ oz_status_t oz_create(oz_handle_t* handle, int device) {
         }
         if (prev >= 0 && prev != device) (void)hipSetDevice(prev);
     }
-    // measured on MI355X: slice GEMM 2.6-2.9 POP/s at 8192^3 (2.65 is used), native FP64 GEMM 55-75 TFLOP/s
-    // between 2304^3 and 8192^3 (74, its rate where emulation competes, is used), streaming kernels about 4 TB/s, launch overhead of the ten
-    // kernels of a call
+    // measured on MI355X: native FP64 GEMM 55-75 TFLOP/s between 2304^3 and 8192^3 (74, its rate where emulation competes, is
+    // used), streaming kernels about 4 TB/s, start and launches of a guarded call.  The slice GEMM's 2.65 POP/s is what it
+    // reached on 256x256 units; on 128x128 units it reaches 2.9-3.0, and the line between the routes stays where it was
+    // until it is drawn anew with the route as the subject.
     h->hm.int8_ops_per_ns = 2650000;
     h->hm.fp64_flops_per_ns = 74000;
     h->hm.bytes_per_ns = 4000;

@@ -15,9 +15,9 @@
 // on the 32-bank store path (the counters show exactly 4 extra cycles per store); other row lengths
 // (129, 131, 133) give the same run time, so it is left as it is.
 // Tile loads go through a buffer descriptor (no vector address arithmetic in the K loop); ragged sizes
-// run the same loop with clamped rows and a short first K step; products with few tiles, or with a number
-// of tiles that is not a whole number of rounds, may split k over several workgroups per tile when the
-// caller provides scratch memory (partial tiles added in a fixed order by dgemm_f64_reduce_kernel).
+// run the same loop with clamped rows and a short first K step; where the caller provides scratch memory, k may be
+// split over several workgroups per tile (partial tiles added in a fixed order by dgemm_f64_reduce_kernel).  The tile edge
+// (128, or 64 with waves of 32x32) and the number of parts are chosen together by an estimated time.
 // The kernel is launched on every call and returns at once unless the verdict selected it.
 #include "oz_internal.h"
 

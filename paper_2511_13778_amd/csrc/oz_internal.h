@@ -67,7 +67,7 @@ struct Problem {
     int32_t G;             // ceil(k / b)
     int32_t num_cu;        // compute units of the device
     int32_t tile_mode;     // 1: every kTile x kTile block of C takes its own slice count (OZ_DYNAMIC + tile_slices)
-    int32_t raw_slots;     // tiles the raw buffer holds (a launch splits the k range of fewer tiles than there are CUs)
+    int32_t raw_slots;     // kTile blocks the raw buffer holds, four units each (a launch of fewer units than CUs may split k)
 };
 
 struct Workspace {
@@ -86,8 +86,8 @@ struct Workspace {
     int32_t* T;            // [nkb][np][mp]                   leading word (anti-diagonal 0 plus the carry from below)
     int8_t* L;             // [nkb][s_cap-1][np/4][mp][4]     balanced digit of anti-diagonal d >= 1 at plane d-1; four
                            //                                 consecutive j of one i share a dword
-    int32_t* raw;          // [nkb][s_cap][raw_slots][kTile][kTile]  unaggregated sums of the tiles whose k range is split
-                           //                                 over several workgroups (integer atomics), tile-local [j][i]
+    int32_t* raw;          // [nkb][s_cap][raw_slots][kTile][kTile]  what the parts of a k split leave (see KSplit), in
+                           //                                 slots of one 128 x 128 unit
     int32_t* tile_span;    // [np/kTile][mp/kTile] largest coarsened span of the block's dot products (atomicMax)
     int32_t* tile_S;       // [np/kTile][mp/kTile] slice count of the block (per-tile mode), followed by as many
                            // entries again: the order in which the slice GEMM deals the tiles to its workgroups
