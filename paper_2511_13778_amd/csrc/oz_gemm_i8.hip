@@ -49,17 +49,15 @@
 //    other (bounded) so that they stay within what L2 holds.
 //  * One wave per SIMD, so nothing hides an instruction that delays the next MFMA: LDS reads, transfers and scalar
 //    work are spread over the gaps between a step's MFMAs, and the loops are laid out for few branches.
-#include <algorithm>
 #include <type_traits>
 
-#include "oz_internal.h"
+#include "oz_gemm_plan.h"
 
 namespace oz {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 
-constexpr int kDiag = 4;                         // anti-diagonals accumulated side by side
 constexpr int kDiagAtomic = 3;                   // the same in the atomic variant (its 32x32 tiles need more registers in flight)
 constexpr int kStages = 10;                      // LDS stages; the pipeline below counts on ten
 constexpr int kOperandBytes = kUnit * kBK;       // 8 KB: one operand's tile
@@ -69,14 +67,9 @@ constexpr int kGemmLds = kRingBytes;             // 160 KB: all of the CU's LDS
 static_assert(kKPad % kBK == 0, "k padding must cover whole steps");
 static_assert(kTile == 2 * kUnit, "a block of C with its own slice count is two by two units");
 
-constexpr int kRoundUnits = 32;       // workgroups an XCD runs at a time: 32 CUs, one workgroup each
 constexpr int kMaxSyncSpins = 384;    // upper bound of the wait for the other workgroups of a round
 constexpr int kSyncMinK = 2048;       // units of a shorter k run without the in-step waits
 constexpr int kMidSyncMinK = 24576;   // from this k on, workgroups also wait after every group of anti-diagonals
-
-// The streams of tiles run up to nine entries ahead of the multiplication: with at least this many per unit they never
-// need to know more than the next unit.
-constexpr int kMinUnitItems = 12;
 
 // Records this workgroup's arrival at *counter and, if `wait`, waits (bounded, about half a
 // millisecond) until `target` workgroups have arrived.  The wait only improves cache locality:
@@ -97,50 +90,6 @@ __device__ __forceinline__ void round_sync(int32_t* counter, int target, bool& w
         }
     }
     asm volatile("s_barrier" ::: "memory");
-}
-
-// Position `slot` of an XCD's range -> unit of C.  Workgroup ids are dealt round-robin to the 8 XCDs by the hardware; each XCD is given a
-// contiguous range.  With a k split (zsplit > 1) a work item is (unit, part of the k range), ordered part by
-// part, so the items an XCD runs together still are neighbours on the same k range.
-// Plain order: the units themselves in the 4 x 8 order of lin_to_tile.  Per-block order (`order` maps a position
-// to a kTile block): an XCD's blocks are taken in groups of 32, and a group in four rounds, one per quadrant, so a
-// round touches one 128-row half of each panel: as many panel bytes as a 4 x 8 block of units.
-// Returns false past the end of the range.
-__device__ __forceinline__ bool unit_of(int xcd, int slot, const GemmGrid& g, const int32_t* __restrict__ order, int& ui,
-                                        int& uj, int& z, int& local, int& xcd_units) {
-    z = 0;
-    if (order && g.zsplit == 1) {
-        const int per = g.count >> 3, rem = g.count & 7;
-        const int blocks = per + (xcd < rem ? 1 : 0);
-        xcd_units = 4 * blocks;
-        local = 0;
-        if (slot >= xcd_units) return false;
-        const int grp = slot / (4 * kRoundUnits), in = slot - grp * 4 * kRoundUnits;
-        const int gsz = min(kRoundUnits, blocks - grp * kRoundUnits);
-        const int q = in / gsz;
-        int ti, tj;
-        lin_to_tile(order[g.begin + xcd * per + min(xcd, rem) + grp * kRoundUnits + in - q * gsz], g.nti, g.ntj, ti, tj);
-        ui = 2 * ti + (q & 1);
-        uj = 2 * tj + (q >> 1);
-        return true;
-    }
-    const int units = order ? 4 * g.count : g.count, total = units * g.zsplit;
-    const int per = total >> 3, rem = total & 7;
-    xcd_units = per + (xcd < rem ? 1 : 0);
-    if (slot >= xcd_units) return false;
-    const int item = xcd * per + min(xcd, rem) + slot;
-    z = item / units;
-    local = item - z * units;
-    if (order) {
-        const int q = local / g.count;
-        int ti, tj;
-        lin_to_tile(order[g.begin + local - q * g.count], g.nti, g.ntj, ti, tj);
-        ui = 2 * ti + (q & 1);
-        uj = 2 * tj + (q >> 1);
-    } else {
-        lin_to_tile(g.begin + local, g.um, g.un, ui, uj);
-    }
-    return true;
 }
 
 // 64 lanes x 16 B from global memory into LDS: lane l's 16 bytes land at lds_addr + LDS_IMM + 16*l.
@@ -231,15 +180,12 @@ __global__ __launch_bounds__(256) void gemm_i8_kernel(const int8_t* __restrict__
         round_sync(&rec->tile_sync[xcd], round * kRoundUnits * sync_steps + sync_q * members, sync_wait);
     };
     // a quadrant of an edge block that holds padding only: nothing to do but the arrivals it owes its round
-    auto skip_padding = [&]() -> bool {
-        while (ui >= g.um || uj >= g.un) {
+    auto pass_padding = [&]() -> bool {
+        return skip_padding(xcd, stride, slot, g, order, ui, uj, z, local, xcd_units, [&]() {
             if (sync_on && threadIdx.x == 0) atomicAdd(&rec->tile_sync[xcd], sync_steps);
-            slot += stride;
-            if (!unit_of(xcd, slot, g, order, ui, uj, z, local, xcd_units)) return false;
-        }
-        return true;
+        });
     };
-    if (!skip_padding()) return;
+    if (!pass_padding()) return;
     // slice count of a unit: its block's own (per-block mode: the first S digit planes of the operands
     // and the pairs s + t <= S - 1) or the call's
     auto slices_of = [&](int i, int j) -> int { return tile_S ? min(tile_S[(j >> 1) * g.nti + (i >> 1)], S_all) : S_all; };
@@ -281,7 +227,7 @@ __global__ __launch_bounds__(256) void gemm_i8_kernel(const int8_t* __restrict__
     auto find_next = [&]() {
         const int cui = ui, cuj = uj, cslot = slot;
         slot += stride;
-        has_next = unit_of(xcd, slot, g, order, ui, uj, z, local, xcd_units) && skip_padding();
+        has_next = unit_of(xcd, slot, g, order, ui, uj, z, local, xcd_units) && pass_padding();
         nui = ui; nuj = uj; nslot = slot;
         if (has_next) nS = slices_of(nui, nuj);
         ui = cui; uj = cuj; slot = cslot;
@@ -792,80 +738,6 @@ __global__ __launch_bounds__(256) void add_parts_kernel(const int32_t* __restric
     for (int q = 0; q < 4; ++q) tw[q * mp] = carry[q];
 }
 
-namespace {
-
-struct Split { int z; bool atomic; };
-
-// How a call's units are dealt to launches.
-struct LaunchPlan {
-    GemmGrid g;
-    int per_pos;           // units per position of the launch order
-    int positions;
-    int kt;                // 64s of k
-    int raw_units;         // 128 x 128 slots per plane of the raw buffer
-    int min_entries;       // stream entries per 64 of k of a unit with the fewest slices the call can come out with
-    int full, rest;        // positions in full rounds, and left over
-    Split last;            // of the rest (of everything, if there is no full round)
-    bool two;              // the rest in a launch of its own
-
-    explicit LaunchPlan(const Problem& p) : g() {
-        g.nti = int(p.mp / kTile);
-        g.ntj = int(p.np / kTile);
-        g.um = int((p.m + kUnit - 1) / kUnit);
-        g.un = int((p.n + kUnit - 1) / kUnit);
-        // the workgroup-to-XCD reasoning behind the in-step waits holds for the whole chip only
-        // (8 XCDs of 32 CUs); a partitioned device runs the same kernel without them
-        g.full_chip = p.num_cu == 8 * kRoundUnits ? 1 : 0;
-        per_pos = p.tile_mode ? 4 : 1;
-        positions = p.tile_mode ? g.nti * g.ntj : g.um * g.un;
-        kt = int((p.k + kBK - 1) / kBK);
-        g.kt_total = kt;
-        raw_units = 4 * p.raw_slots;
-        min_entries = 0;
-        for (int n = p.s_min; n > 0; n -= kDiag) min_entries += n;
-        // Units are dealt in rounds of one per CU.  A call with less than a round may be split along k as a whole;
-        // otherwise the full rounds run unsplit and what is left may be split along k in a launch of its own.
-        // (Per-block order: a full round of the order table is one block per CU.)
-        const int round = p.num_cu;
-        full = positions / round * round;
-        rest = positions - full;
-        last = rest != 0 && rest * per_pos < round ? split(p, rest * per_pos) : Split{1, false};
-        two = full != 0 && last.z > 1;
-    }
-
-    // k-blocks a part can touch, whatever the slice count turns out to be (fewer slices: longer k-blocks)
-    int nkb_part(const Problem& p, int z) const {
-        const int64_t len = (int64_t(kt) + z - 1) / z * kBK;
-        return p.nkb == 1 ? 1 : int(std::min<int64_t>(p.nkb, (len - 1) / p.kblk + 2));
-    }
-
-    // k split of a launch that cannot fill the chip.  Estimated time in ns for `units` units, seven slices assumed
-    // (the slice count is decided on the device): a 64 of k costs a unit about 4.2 us, a workgroup about 5 us to
-    // start and to write its sums.  Parts with slots of their own move 10 bytes per element and part (60 ns per part and
-    // unit) and, for the rest of a larger product, need a launch to be added (6 us); atomics add 28 bytes per element
-    // and part (170 ns) and need the slots zeroed (8 us), but no more memory for more parts.
-    Split split(const Problem& p, int units) const {
-        const bool whole = units == positions * per_pos;     // the recomposition puts it together
-        const int64_t raw_bytes = int64_t(p.nkb) * p.s_cap * raw_units * (kUnit * kUnit * 4);
-        Split best{1, false};
-        int64_t best_ns = (int64_t(kt) * 4200 + 5000) * 95 / 100;     // a split has to gain 5 %
-        for (int z = 2; z <= kt && int64_t(units) * z <= p.num_cu; ++z) {
-            const int64_t steps = (kt + z - 1) / z;
-            if (int64_t(z - 1) * units * nkb_part(p, z) * part_slot_bytes(p.s_cap) <= raw_bytes) {
-                const int64_t ns = steps * 4200 + 5000 + (whole ? 1000 : 6000) + int64_t(60) * units * z;
-                if (ns < best_ns) { best_ns = ns; best = Split{z, false}; }
-            }
-            if (whole) {
-                const int64_t ns = steps * 4800 + 5000 + 8000 + int64_t(170) * units * z;
-                if (ns < best_ns) { best_ns = ns; best = Split{z, true}; }
-            }
-        }
-        return best;
-    }
-};
-
-}  // namespace
-
 void tile_order_shape(const Problem& p, int& first, int& deal) {
     const LaunchPlan lp(p);
     first = lp.two ? lp.full : lp.positions;
@@ -883,22 +755,9 @@ SplitPlan launch_gemm_i8(hipStream_t st, const Workspace& w, const Problem& p) {
     const LaunchPlan lp(p);
     const int32_t* tile_S = p.tile_mode ? w.tile_S : nullptr;
     auto launch = [&](int begin, int count, Split sp) -> GemmGrid {
-        GemmGrid g = lp.g;
+        unsigned grid;
+        const GemmGrid g = lp.launch(p, begin, count, sp, grid);
         const int units = count * lp.per_pos;
-        g.begin = begin;
-        g.count = count;
-        g.zsplit = sp.z;
-        g.nkb_part = lp.nkb_part(p, sp.z);
-        g.persistent = 0;
-        // unsplit launches in per-block order give every XCD whole blocks: the ranges differ by up to four units
-        unsigned grid = (p.tile_mode && sp.z == 1) ? unsigned(8 * 4 * ((count + 7) / 8)) : unsigned(units) * unsigned(sp.z);
-        // more units than CUs: one workgroup per CU that walks its share (eight equal ranges, one per XCD), if
-        // the units are long enough for the streams
-        const unsigned cus = unsigned(p.num_cu) & ~7u;
-        if (grid > cus && cus != 0 && lp.kt * lp.min_entries >= kMinUnitItems) {
-            grid = cus;
-            g.persistent = 1;
-        }
         if (sp.atomic) {
             hipLaunchKernelGGL(zero_raw_kernel, dim3(unsigned(units), unsigned(p.nkb * p.s_cap)), dim3(256), 0, st, w.raw,
                                lp.raw_units, p.s_cap, w.rec);

@@ -1,0 +1,169 @@
+// Which workgroup of the slice GEMM takes which unit of C and which part of k: the split of a call into launches (host) and
+// the walk of a workgroup over its units (device), kept apart from the kernel so that a host program can follow both.
+#pragma once
+
+#include <algorithm>
+
+#include "oz_internal.h"
+
+namespace oz {
+
+constexpr int kDiag = 4;              // anti-diagonals accumulated side by side
+constexpr int kRoundUnits = 32;       // workgroups an XCD runs at a time: 32 CUs, one workgroup each
+
+// The streams of tiles run up to nine entries ahead of the multiplication: with at least this many per unit they never
+// need to know more than the next unit.
+constexpr int kMinUnitItems = 12;
+
+// Position `slot` of an XCD's range -> unit of C.  Workgroup ids are dealt round-robin to the 8 XCDs by the hardware; each XCD is given a
+// contiguous range.  With a k split (zsplit > 1) a work item is (unit, part of the k range), ordered part by
+// part, so the items an XCD runs together still are neighbours on the same k range.
+// Plain order: the units themselves in the 4 x 8 order of lin_to_tile.  Per-block order (`order` maps a position
+// to a kTile block): an XCD's blocks are taken in groups of 32, and a group in four rounds, one per quadrant, so a
+// round touches one 128-row half of each panel: as many panel bytes as a 4 x 8 block of units.
+// Returns false past the end of the range.
+__host__ __device__ inline bool unit_of(int xcd, int slot, const GemmGrid& g, const int32_t* __restrict__ order, int& ui,
+                                        int& uj, int& z, int& local, int& xcd_units) {
+    z = 0;
+    if (order && g.zsplit == 1) {
+        const int per = g.count >> 3, rem = g.count & 7;
+        const int blocks = per + (xcd < rem ? 1 : 0);
+        xcd_units = 4 * blocks;
+        local = 0;
+        if (slot >= xcd_units) return false;
+        const int grp = slot / (4 * kRoundUnits), in = slot - grp * 4 * kRoundUnits;
+        const int gsz = blocks - grp * kRoundUnits < kRoundUnits ? blocks - grp * kRoundUnits : kRoundUnits;
+        const int q = in / gsz;
+        int ti, tj;
+        lin_to_tile(order[g.begin + xcd * per + (xcd < rem ? xcd : rem) + grp * kRoundUnits + in - q * gsz], g.nti, g.ntj, ti, tj);
+        ui = 2 * ti + (q & 1);
+        uj = 2 * tj + (q >> 1);
+        return true;
+    }
+    const int units = order ? 4 * g.count : g.count, total = units * g.zsplit;
+    const int per = total >> 3, rem = total & 7;
+    xcd_units = per + (xcd < rem ? 1 : 0);
+    if (slot >= xcd_units) return false;
+    const int item = xcd * per + (xcd < rem ? xcd : rem) + slot;
+    z = item / units;
+    local = item - z * units;
+    if (order) {
+        const int q = local / g.count;
+        int ti, tj;
+        lin_to_tile(order[g.begin + local - q * g.count], g.nti, g.ntj, ti, tj);
+        ui = 2 * ti + (q & 1);
+        uj = 2 * tj + (q >> 1);
+    } else {
+        lin_to_tile(g.begin + local, g.um, g.un, ui, uj);
+    }
+    return true;
+}
+
+// A unit that is a padding-only quadrant of an edge block is passed over: `owed` is called for it (what its round still
+// expects of it), and a persistent workgroup moves on to the next unit of its share.  One that is not persistent has no
+// next one: every other position belongs to another workgroup, also where the range of its XCD is one longer than
+// gridDim.x / 8.  Returns false when nothing is left.
+template <class Owed>
+__host__ __device__ inline bool skip_padding(int xcd, int stride, int& slot, const GemmGrid& g, const int32_t* __restrict__ order,
+                                             int& ui, int& uj, int& z, int& local, int& xcd_units, Owed&& owed) {
+    while (ui >= g.um || uj >= g.un) {
+        owed();
+        if (!g.persistent) return false;
+        slot += stride;
+        if (!unit_of(xcd, slot, g, order, ui, uj, z, local, xcd_units)) return false;
+    }
+    return true;
+}
+
+struct Split { int z; bool atomic; };
+
+// How a call's units are dealt to launches.
+struct LaunchPlan {
+    GemmGrid g;
+    int per_pos;           // units per position of the launch order
+    int positions;
+    int kt;                // 64s of k
+    int raw_units;         // 128 x 128 slots per plane of the raw buffer
+    int min_entries;       // stream entries per 64 of k of a unit with the fewest slices the call can come out with
+    int full, rest;        // positions in full rounds, and left over
+    Split last;            // of the rest (of everything, if there is no full round)
+    bool two;              // the rest in a launch of its own
+
+    explicit LaunchPlan(const Problem& p) : g() {
+        g.nti = int(p.mp / kTile);
+        g.ntj = int(p.np / kTile);
+        g.um = int((p.m + kUnit - 1) / kUnit);
+        g.un = int((p.n + kUnit - 1) / kUnit);
+        // the workgroup-to-XCD reasoning behind the in-step waits holds for the whole chip only
+        // (8 XCDs of 32 CUs); a partitioned device runs the same kernel without them
+        g.full_chip = p.num_cu == 8 * kRoundUnits ? 1 : 0;
+        per_pos = p.tile_mode ? 4 : 1;
+        positions = p.tile_mode ? g.nti * g.ntj : g.um * g.un;
+        kt = int((p.k + kBK - 1) / kBK);
+        g.kt_total = kt;
+        raw_units = 4 * p.raw_slots;
+        min_entries = 0;
+        for (int n = p.s_min; n > 0; n -= kDiag) min_entries += n;
+        // Units are dealt in rounds of one per CU.  A call with less than a round may be split along k as a whole;
+        // otherwise the full rounds run unsplit and what is left may be split along k in a launch of its own.
+        // (Per-block order: a full round of the order table is one block per CU.)
+        const int round = p.num_cu;
+        full = positions / round * round;
+        rest = positions - full;
+        last = rest != 0 && rest * per_pos < round ? split(p, rest * per_pos) : Split{1, false};
+        two = full != 0 && last.z > 1;
+    }
+
+    // k-blocks a part can touch, whatever the slice count turns out to be (fewer slices: longer k-blocks)
+    int nkb_part(const Problem& p, int z) const {
+        const int64_t len = (int64_t(kt) + z - 1) / z * kBK;
+        return p.nkb == 1 ? 1 : int(std::min<int64_t>(p.nkb, (len - 1) / p.kblk + 2));
+    }
+
+    // k split of a launch that cannot fill the chip.  Estimated time in ns for `units` units, seven slices assumed
+    // (the slice count is decided on the device): a 64 of k costs a unit about 4.2 us, a workgroup about 5 us to
+    // start and to write its sums.  Parts with slots of their own move 10 bytes per element and part (60 ns per part and
+    // unit) and, for the rest of a larger product, need a launch to be added (6 us); atomics add 28 bytes per element
+    // and part (170 ns) and need the slots zeroed (8 us), but no more memory for more parts.
+    Split split(const Problem& p, int units) const {
+        const bool whole = units == positions * per_pos;     // the recomposition puts it together
+        const int64_t raw_bytes = int64_t(p.nkb) * p.s_cap * raw_units * (kUnit * kUnit * 4);
+        Split best{1, false};
+        int64_t best_ns = (int64_t(kt) * 4200 + 5000) * 95 / 100;     // a split has to gain 5 %
+        for (int z = 2; z <= kt && int64_t(units) * z <= p.num_cu; ++z) {
+            const int64_t steps = (kt + z - 1) / z;
+            if (int64_t(z - 1) * units * nkb_part(p, z) * part_slot_bytes(p.s_cap) <= raw_bytes) {
+                const int64_t ns = steps * 4200 + 5000 + (whole ? 1000 : 6000) + int64_t(60) * units * z;
+                if (ns < best_ns) { best_ns = ns; best = Split{z, false}; }
+            }
+            if (whole) {
+                const int64_t ns = steps * 4800 + 5000 + 8000 + int64_t(170) * units * z;
+                if (ns < best_ns) { best_ns = ns; best = Split{z, true}; }
+            }
+        }
+        return best;
+    }
+
+    // geometry of the launch of positions [begin, begin + count), and its workgroups
+    GemmGrid launch(const Problem& p, int begin, int count, Split sp, unsigned& workgroups) const {
+        GemmGrid l = g;
+        const int units = count * per_pos;
+        l.begin = begin;
+        l.count = count;
+        l.zsplit = sp.z;
+        l.nkb_part = nkb_part(p, sp.z);
+        l.persistent = 0;
+        // unsplit launches in per-block order give every XCD whole blocks: the ranges differ by up to four units
+        workgroups = (p.tile_mode && sp.z == 1) ? unsigned(8 * 4 * ((count + 7) / 8)) : unsigned(units) * unsigned(sp.z);
+        // more units than CUs: one workgroup per CU that walks its share (eight equal ranges, one per XCD), if
+        // the units are long enough for the streams
+        const unsigned cus = unsigned(p.num_cu) & ~7u;
+        if (workgroups > cus && cus != 0 && kt * min_entries >= kMinUnitItems) {
+            workgroups = cus;
+            l.persistent = 1;
+        }
+        return l;
+    }
+};
+
+}  // namespace oz

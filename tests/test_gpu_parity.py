@@ -998,6 +998,19 @@ def test_slice_gemm_per_block_order(lib, m, n, k):
     np.testing.assert_array_equal(got, tr.C)
 
 
+@pytest.mark.parametrize("m,n,k", [(100, 100, 4000), (600, 600, 7500), (200, 100, 4000), (600, 100, 3500)])
+def test_per_block_split_with_padding_quadrants(lib, m, n, k):
+    # per-block order, all parts added with integer atomics, an odd number of blocks times parts (so the eight XCDs do not
+    # get equal shares) and quadrants that hold padding only: each part of each unit is added exactly once
+    g, h = lib
+    A, B = wl.lognormal_spread(m, k, n, 0.5, seed=m + k)
+    got, gm, res = run_gpu(g, h, A, B, 1.0, 0.0, None, "N", "T", mode=g.OZ_DYNAMIC, target_bits=53, max_bits=200, heuristic=0,
+                           tile_slices=1)
+    tr = oz.emulated_dgemm(A, B, 1.0, 0.0, None, mode=oz.MODE_DYNAMIC, target_bits=53, max_bits=200, per_tile=True)
+    assert (res.slices_used, res.slices_min, res.pair_tiles) == (tr.verdict.slices_used, tr.verdict.slices_min, tr.verdict.pair_tiles)
+    np.testing.assert_array_equal(got, tr.C)
+
+
 @pytest.mark.parametrize("ta,tb,m,n,k", [("N", "N", 512, 512, 512), ("T", "N", 500, 301, 703), ("N", "T", 65, 130, 5000), ("T", "T", 1000, 1300, 777),
                                          ("N", "N", 64, 64, 128), ("T", "N", 2000, 1799, 300)])
 def test_native_small_tiles_with_parts(lib, ta, tb, m, n, k):

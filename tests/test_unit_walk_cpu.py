@@ -1,0 +1,49 @@
+"""The walk of the slice GEMM's workgroups over the units of C, followed on the host (no GPU): every unit that holds a row
+and a column of C is multiplied over every 64 of k exactly once, whatever the order, the split along k and the padding."""
+import itertools
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def walk(tmp_path_factory):
+    exe = tmp_path_factory.mktemp("walk") / "walk"
+    cmd = ["g++", "-std=c++17", "-O1", "-Wno-attributes", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+           "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(ROOT, "paper_2511_13778_amd", "csrc"),
+           os.path.join(ROOT, "tests", "host_unit_walk.cpp"), "-o", str(exe)]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+
+    def run(cases):
+        out = subprocess.run([str(exe)], input="\n".join(" ".join(map(str, c)) for c in cases), capture_output=True,
+                             text=True, check=True).stdout.split("\n")[:-1]
+        assert len(out) == len(cases)
+        return [tuple(map(int, ln.split())) for ln in out]
+    return run
+
+
+def test_every_unit_and_part_is_taken_exactly_once(walk):
+    # odd and even numbers of blocks, padding-only quadrants on either edge, odd and even numbers of parts, small and large
+    # workspaces (which decide between parts with slots and atomics), more units than CUs, a split last round
+    mn = [1, 100, 128, 129, 200, 256, 300, 500, 513, 600, 700, 1300, 2300, 2500]
+    cases = [(m, n, k, s_cap, tile_mode, 256) for m, n in itertools.product(mn, mn)
+             for k in (1, 64, 65, 700, 1000, 3500, 4000, 7500, 20000) for s_cap in (2, 9, 26) for tile_mode in (0, 1)]
+    got = walk(cases)
+    odd_atomic = 0
+    for c, (kind, z, missed, repeated, mixed) in zip(cases, got):
+        assert (missed, repeated, mixed) == (0, 0, 0), (c, kind, z, missed, repeated, mixed)
+        blocks = -(-c[0] // 256) * -(-c[1] // 256)
+        odd_atomic += c[4] == 1 and kind == 2 and blocks * z % 2 == 1
+    assert odd_atomic > 50        # per-block order, atomics, items that do not divide by the eight XCDs
+
+
+@pytest.mark.parametrize("m,n,k", [(100, 100, 4000), (600, 600, 7500), (200, 100, 4000), (600, 100, 3500)])
+def test_shapes_of_the_gpu_test_take_the_atomic_route(walk, m, n, k):
+    # what test_per_block_split_with_padding_quadrants multiplies on the GPU
+    (kind, z, missed, repeated, mixed), = walk([(m, n, k, 26, 1, 256)])
+    assert kind == 2 and -(-m // 256) * -(-n // 256) * z % 2 == 1
+    assert (missed, repeated, mixed) == (0, 0, 0)
