@@ -156,9 +156,10 @@ struct LaunchPlan {
         // unsplit launches in per-block order give every XCD whole blocks: the ranges differ by up to four units
         workgroups = (p.tile_mode && sp.z == 1) ? unsigned(8 * 4 * ((count + 7) / 8)) : unsigned(units) * unsigned(sp.z);
         // more units than CUs: one workgroup per CU that walks its share (eight equal ranges, one per XCD), if
-        // the units are long enough for the streams
+        // the units are long enough for the streams.  Parts of k never: a workgroup keeps its part (a split fills at most one
+        // round of all CUs, which is more than `cus` where their number is no multiple of eight).
         const unsigned cus = unsigned(p.num_cu) & ~7u;
-        if (workgroups > cus && cus != 0 && kt * min_entries >= kMinUnitItems) {
+        if (sp.z == 1 && workgroups > cus && cus != 0 && kt * min_entries >= kMinUnitItems) {
             workgroups = cus;
             l.persistent = 1;
         }

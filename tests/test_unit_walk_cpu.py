@@ -47,3 +47,14 @@ def test_shapes_of_the_gpu_test_take_the_atomic_route(walk, m, n, k):
     (kind, z, missed, repeated, mixed), = walk([(m, n, k, 26, 1, 256)])
     assert kind == 2 and -(-m // 256) * -(-n // 256) * z % 2 == 1
     assert (missed, repeated, mixed) == (0, 0, 0)
+
+
+@pytest.mark.parametrize("num_cu", [4, 12, 36, 100, 250, 304])
+def test_other_numbers_of_compute_units(walk, num_cu):
+    # a device that shows some of its units only: not always a multiple of eight.  A workgroup keeps its part of k while it
+    # walks several units, so it must not meet units of different parts
+    mn = [100, 129, 300, 513, 700, 1300]
+    cases = [(m, n, k, s_cap, tile_mode, num_cu) for m, n in itertools.product(mn, mn)
+             for k in (64, 700, 3500, 7500, 20000) for s_cap in (2, 9, 26) for tile_mode in (0, 1)]
+    for c, (kind, z, missed, repeated, mixed) in zip(cases, walk(cases)):
+        assert (missed, repeated, mixed) == (0, 0, 0), (c, kind, z, missed, repeated, mixed)
