@@ -156,6 +156,34 @@ __host__ __device__ inline int64_t k_block_length(int S) {
     return ((int64_t(1) << 17) - (int64_t(1) << 9) - 1) / S / 256 * 256;
 }
 
+// ---- geometry of the scan's launches --------------------------------------------------
+constexpr int kScanBlocksPerWg = 4;    // ESC blocks a workgroup covers (measured at 8192^3: 1, 2 or 8 are 4-13 % slower)
+constexpr int64_t kMaxGridThreads = (int64_t(1) << 32) - 1;   // of one launch along x
+
+// Workgroups of the scan: row blocks of op(A), then of op(B), for `groups` groups of `per` ESC blocks along k.  One launch
+// takes `slab` groups: all of them, unless a launch would have too many threads (k-contiguous operands of 2^34 elements
+// with ESC blocks of 16).
+struct ScanGrid {
+    int64_t row_blocks_a, row_blocks_b;
+    int per;
+    int64_t groups, slab;
+};
+// rows_contig: stride_r == 1, a workgroup of 256 threads covers 64 rows, otherwise 16
+inline ScanGrid scan_grid(const Problem& p, bool a_rows_contig, bool b_rows_contig) {
+    ScanGrid s;
+    s.row_blocks_a = p.mp / (a_rows_contig ? 64 : 16);
+    s.row_blocks_b = p.np / (b_rows_contig ? 64 : 16);
+    const int64_t row_blocks = s.row_blocks_a + s.row_blocks_b;
+    // ESC blocks per workgroup: four, or one where four would leave fewer than four workgroups per CU: such a call waits
+    // for the loads of one block after the other (200x300x260: 11.5 us with four, 4.5 with one), a larger one is bound
+    // by the bytes read and sets eA and eB with a quarter of the atomics
+    s.per = row_blocks * ((p.G + kScanBlocksPerWg - 1) / kScanBlocksPerWg) < int64_t(4) * p.num_cu ? 1 : kScanBlocksPerWg;
+    s.groups = (p.G + s.per - 1) / s.per;
+    const int64_t fit = kMaxGridThreads / 256 / row_blocks;
+    s.slab = s.groups < fit ? s.groups : fit;
+    return s;
+}
+
 // ---- stage launchers (each only enqueues) --------------------------------------------
 // element (r, l) of an operand (r: row of op(A) / column of op(B), l: along k) is at X[r*stride_r + l*stride_l]
 struct Operand {

@@ -56,8 +56,6 @@ __global__ __launch_bounds__(256) void init_kernel(Record* rec, int32_t* eA, int
     if (t < np) eB[t] = kExpAllZero;
 }
 
-constexpr int kScanBlocksPerWg = 4;    // ESC blocks a workgroup covers (measured at 8192^3: 1, 2 or 8 are 4-13 % slower)
-
 struct ScanSide {
     Operand o;
     int16_t* tab;          // [2G][rows_p]
@@ -151,14 +149,14 @@ __device__ __forceinline__ int scan_k(const ScanSide& s, int64_t rb, int g0, int
     return bad;
 }
 
-// Both operands in one launch: the first blocks_a workgroups scan op(A), the others op(B).
-__global__ __launch_bounds__(256) void scan_kernel(ScanSide a, ScanSide b, int64_t blocks_a, int per, int64_t k, int bl,
-                                                   int G, Record* rec, int check) {
+// Both operands in one launch: the first blocks_a workgroups scan op(A), the others op(B), from ESC block g_first on.
+__global__ __launch_bounds__(256) void scan_kernel(ScanSide a, ScanSide b, int64_t blocks_a, int g_first, int per, int64_t k,
+                                                   int bl, int G, Record* rec, int check) {
     const bool second = int64_t(blockIdx.x) >= blocks_a;
     const ScanSide& s = second ? b : a;
     const int64_t id = int64_t(blockIdx.x) - (second ? blocks_a : 0);
     const int64_t rb = id % s.row_blocks;
-    const int g0 = int(id / s.row_blocks) * per;
+    const int g0 = g_first + int(id / s.row_blocks) * per;
     const int bad = s.o.stride_r == 1 ? scan_rows(s, rb, g0, per, k, bl, G) : scan_k(s, rb, g0, per, k, bl, G);
     if (check && bad) atomicOr(&rec->infnan, 1);
 }
@@ -172,16 +170,13 @@ void launch_init(hipStream_t st, const Workspace& w, const Problem& p, const Kno
 }
 
 void launch_scan(hipStream_t st, const Operand& a, const Operand& b, const Workspace& w, const Problem& p, bool check_infnan) {
-    auto row_blocks = [](const Operand& o) { return o.rows_p / (o.stride_r == 1 ? 64 : 16); };
-    const ScanSide sa{a, w.U, 1, w.eA, row_blocks(a)}, sb{b, w.V, 0, w.eB, row_blocks(b)};
-    // ESC blocks per workgroup: four, or one where four would leave fewer than four workgroups per CU: such a call waits
-    // for the loads of one block after the other (200x300x260: 11.5 us with four, 4.5 with one), a larger one is bound
-    // by the bytes read and sets eA and eB with a quarter of the atomics
-    const int per = (sa.row_blocks + sb.row_blocks) * ((p.G + 3) / 4) < int64_t(4) * p.num_cu ? 1 : kScanBlocksPerWg;
-    const int64_t gy = (p.G + per - 1) / per;
-    const int64_t blocks_a = sa.row_blocks * gy, blocks_b = sb.row_blocks * gy;
-    hipLaunchKernelGGL(scan_kernel, dim3(unsigned(blocks_a + blocks_b)), dim3(256), 0, st, sa, sb, blocks_a, per, p.k, p.esc_block,
-                       p.G, w.rec, int(check_infnan));
+    const ScanGrid g = scan_grid(p, a.stride_r == 1, b.stride_r == 1);
+    const ScanSide sa{a, w.U, 1, w.eA, g.row_blocks_a}, sb{b, w.V, 0, w.eB, g.row_blocks_b};
+    for (int64_t y = 0; y < g.groups; y += g.slab) {
+        const int64_t gy = g.groups - y < g.slab ? g.groups - y : g.slab;
+        hipLaunchKernelGGL(scan_kernel, dim3(unsigned((g.row_blocks_a + g.row_blocks_b) * gy)), dim3(256), 0, st, sa, sb,
+                           g.row_blocks_a * gy, int(y) * g.per, g.per, p.k, p.esc_block, p.G, w.rec, int(check_infnan));
+    }
 }
 
 }  // namespace oz

@@ -1,5 +1,6 @@
-"""The walk of the slice GEMM's workgroups over the units of C, followed on the host (no GPU): every unit that holds a row
-and a column of C is multiplied over every 64 of k exactly once, whatever the order, the split along k and the padding."""
+"""Launch geometry followed on the host (no GPU).  The walk of the slice GEMM's workgroups over the units of C: every unit
+that holds a row and a column of C is multiplied over every 64 of k exactly once, whatever the order, the split along
+k and the padding.  The scan's launches: none has more threads than a launch may have."""
 import itertools
 import os
 import subprocess
@@ -9,12 +10,11 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-@pytest.fixture(scope="module")
-def walk(tmp_path_factory):
-    exe = tmp_path_factory.mktemp("walk") / "walk"
+def host_program(tmp_path_factory, source):
+    exe = tmp_path_factory.mktemp("host") / "program"
     cmd = ["g++", "-std=c++17", "-O1", "-Wno-attributes", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
            "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(ROOT, "paper_2511_13778_amd", "csrc"),
-           os.path.join(ROOT, "tests", "host_unit_walk.cpp"), "-o", str(exe)]
+           os.path.join(ROOT, "tests", source), "-o", str(exe)]
     r = subprocess.run(cmd, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
 
@@ -24,6 +24,16 @@ def walk(tmp_path_factory):
         assert len(out) == len(cases)
         return [tuple(map(int, ln.split())) for ln in out]
     return run
+
+
+@pytest.fixture(scope="module")
+def walk(tmp_path_factory):
+    return host_program(tmp_path_factory, "host_unit_walk.cpp")
+
+
+@pytest.fixture(scope="module")
+def scan_grid(tmp_path_factory):
+    return host_program(tmp_path_factory, "host_scan_grid.cpp")
 
 
 def test_every_unit_and_part_is_taken_exactly_once(walk):
@@ -58,3 +68,18 @@ def test_other_numbers_of_compute_units(walk, num_cu):
              for k in (64, 700, 3500, 7500, 20000) for s_cap in (2, 9, 26) for tile_mode in (0, 1)]
     for c, (kind, z, missed, repeated, mixed) in zip(cases, walk(cases)):
         assert (missed, repeated, mixed) == (0, 0, 0), (c, kind, z, missed, repeated, mixed)
+
+
+def test_scan_launches_stay_within_the_grid_limit(scan_grid):
+    # HIP refuses a launch of 2^32 threads or more.  k-contiguous operands of 2^34 elements (137 GB) with ESC blocks of 16
+    # come to that in one launch; every size the library accepts must be scanned whole
+    sizes = [(1, 1, 1), (256, 300, 65), (8192, 8192, 8192), (8192, 1, 1 << 21), (1 << 15, 1 << 14, 1 << 20), (1 << 22, 1, 1 << 14),
+             (1 << 22, 1 << 22, 256), (4000001, 17, 8191), (1, 1 << 21, 1 << 21)]
+    cases = [(*s, b, ar, br) for s in sizes for b in (16, 32, 64, 1024) for ar in (0, 1) for br in (0, 1)]
+    slabs = 0
+    for c, (launches, most, covered, needed) in zip(cases, scan_grid(cases)):
+        assert most < 1 << 32 and covered >= needed and covered - needed < 4, (c, launches, most, covered, needed)
+        slabs += launches > 1
+    assert slabs
+    (launches, *_), = scan_grid([(8192, 8192, 8192, 16, 0, 0)])
+    assert launches == 1
