@@ -69,6 +69,8 @@ static_assert(kTile == 2 * kUnit, "a block of C with its own slice count is two 
 
 constexpr int kMaxSyncSpins = 384;    // upper bound of the wait for the other workgroups of a round
 constexpr int kSyncMinK = 2048;       // units of a shorter k run without the in-step waits
+constexpr int kSyncMinItems = 320;    // nor one of fewer steps than seven slices have there (8192 x 8192 x 2048: one slice
+                                      // 681 -> 630 us, two 845 -> 807, three 1055 -> 1005, four 1388 -> 1350)
 constexpr int kMidSyncMinK = 24576;   // from this k on, workgroups also wait after every group of anti-diagonals
 
 // Records this workgroup's arrival at *counter and, if `wait`, waits (bounded, about half a
@@ -169,7 +171,7 @@ __global__ __launch_bounds__(256) void gemm_i8_kernel(const int8_t* __restrict__
     // Arrival number q of a workgroup of round r waits for 32*r*steps + (q+1)*members arrivals on the XCD's
     // counter (earlier rounds are full).  The wait also drains the wave's stores, so short units go without.
     const int sync_steps = kp >= kMidSyncMinK ? int((kp + kblk - 1) / kblk) * ((S_all + D - 1) / D) : 1;
-    const bool sync_on = !ATOMIC && g.full_chip && g.zsplit == 1 && xcd_units > kRoundUnits && kp >= kSyncMinK &&
+    const bool sync_on = !ATOMIC && g.full_chip && g.zsplit == 1 && xcd_units > kRoundUnits && kp >= kSyncMinK && g.kt_total * unit_items(S_all) >= kSyncMinItems &&
                          (stride == kRoundUnits || stride >= xcd_units);
     int sync_q = 0;
     bool sync_wait = true;               // thread 0: stop waiting once the others were not met in time

@@ -15,6 +15,12 @@ constexpr int kRoundUnits = 32;       // workgroups an XCD runs at a time: 32 CU
 // need to know more than the next unit.
 constexpr int kMinUnitItems = 12;
 
+// steps per 64 of k of a unit with S slices: S for the first group of anti-diagonals, kDiag fewer for each further one
+__host__ __device__ inline int unit_items(int S) {
+    const int groups = (S + kDiag - 1) / kDiag;
+    return groups * S - kDiag * groups * (groups - 1) / 2;
+}
+
 // Position `slot` of an XCD's range -> unit of C.  Workgroup ids are dealt round-robin to the 8 XCDs by the hardware; each XCD is given a
 // contiguous range.  With a k split (zsplit > 1) a work item is (unit, part of the k range), ordered part by
 // part, so the items an XCD runs together still are neighbours on the same k range.
@@ -102,8 +108,7 @@ struct LaunchPlan {
         kt = int((p.k + kBK - 1) / kBK);
         g.kt_total = kt;
         raw_units = 4 * p.raw_slots;
-        min_entries = 0;
-        for (int n = p.s_min; n > 0; n -= kDiag) min_entries += n;
+        min_entries = unit_items(p.s_min);
         // Units are dealt in rounds of one per CU.  A call with less than a round may be split along k as a whole;
         // otherwise the full rounds run unsplit and what is left may be split along k in a launch of its own.
         // (Per-block order: a full round of the order table is one block per CU.)
