@@ -404,7 +404,8 @@ __global__ __launch_bounds__(256) void esc_kernel(const uint4* __restrict__ EU, 
         const int64_t nbi = mp / kEscTile, blocks = nbi * (np / kEscTile);
         int widest = 0;
         for (int64_t block = blockIdx.x; block < blocks; block += gridDim.x) {
-            const int64_t bj = block / nbi, bi = block - bj * nbi;
+            int64_t bi, bj;
+            esc_block_at(block, nbi, np / kEscTile, gridDim.x, bi, bj);
             uint32_t least = least_sum(EU, EV, m, n, mp, np, steps, bi, bj);
 #pragma unroll
             for (int off = 32; off >= 1; off >>= 1) least = min(least, uint32_t(__shfl_xor(int(least), off)));

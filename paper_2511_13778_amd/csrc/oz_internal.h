@@ -184,6 +184,27 @@ inline ScanGrid scan_grid(const Problem& p, bool a_rows_contig, bool b_rows_cont
     return s;
 }
 
+// ---- walk of the ESC kernel ------------------------------------------------------------
+// Position -> block of 128 x 128 pairs (nbi x nbj of them), for `workgroups` that take every workgroups-th position; as many
+// workgroups as blocks take them as they come, fewer share them out.  A row of A or a column of B
+// that is wide or zero leaves a whole row or column of blocks open, to be computed again the long way, and neither may meet
+// the same few workgroups.  So block columns come one after the other, each turned against the last, and once more per walk
+// over all workgroups; by eight blocks at a time where that leaves enough places, so that an XCD (every eighth workgroup)
+// keeps to an eighth of the rows' tables for eight such walks.  (Straight, with `workgroups` a multiple of nbi, one zero row at 8192^3 was 64
+// open blocks for 8 workgroups: 666 us for the ESC, now 149.  Turned by one block, with all rows' tables in every XCD's L2,
+// a call without open blocks took 84 us; straight 75, now 78, and at 4096^3 38 -> 35.)
+__host__ __device__ inline void esc_block_at(int64_t position, int64_t nbi, int64_t nbj, int64_t workgroups, int64_t& bi,
+                                             int64_t& bj) {
+    bj = position / nbi;
+    if (nbi * nbj <= workgroups) {
+        bi = position - bj * nbi;
+        return;
+    }
+    const int64_t walk = bj * nbi / workgroups, turn = bj + walk;
+    const int64_t by_xcd = nbi / 8 % 2 == 0 ? 8 : 16;      // with nbi itself, an odd number of eights from column to column
+    bi = (position + (nbi % 8 == 0 && nbi >= 64 ? by_xcd * turn + walk / 8 : turn)) % nbi;
+}
+
 // ---- stage launchers (each only enqueues) --------------------------------------------
 // element (r, l) of an operand (r: row of op(A) / column of op(B), l: along k) is at X[r*stride_r + l*stride_l]
 struct Operand {

@@ -984,6 +984,19 @@ def test_slice_gemm_units_and_splits(lib, m, n, k, S):
     check_against_oracle(g, h, A, B, 1.0, 0.0, None, mode="unguarded", slices=S, bound=False)
 
 
+@pytest.mark.parametrize("m,n,k,S", [
+    (2100, 2050, 192, 1), (2100, 2050, 250, 1), (2100, 2050, 330, 2), (2100, 2050, 400, 2), (2100, 2050, 321, 5), (2100, 2050, 190, 6),
+    (600, 700, 2000, 1), (600, 700, 2100, 2), (600, 700, 2200, 5), (600, 700, 2300, 9), (600, 700, 2400, 10),
+    (130, 140, 140000, 1), (130, 140, 70000, 2),
+])
+def test_slice_gemm_groups_of_one_or_two(lib, m, n, k, S):
+    # slice counts that leave one or two anti-diagonals in a group, which take most of k two 64s at a time: an even and an
+    # odd number of 64s, into and out of a larger group, from unit to unit, in parts of k, across a k-block
+    g, h = lib
+    A, B = wl.lognormal_spread(m, k, n, 0.5, seed=2000 + S + k)
+    check_against_oracle(g, h, A, B, 1.0, 0.0, None, mode="unguarded", slices=S, bound=False)
+
+
 @pytest.mark.parametrize("m,n,k", [(700, 1300, 300), (2300, 2500, 100), (300, 500, 4000)])
 def test_slice_gemm_per_block_order(lib, m, n, k):
     # the same in per-block order (quadrants of 256 x 256 blocks, some holding padding only), with different slice counts
@@ -1009,6 +1022,20 @@ def test_per_block_split_with_padding_quadrants(lib, m, n, k):
     tr = oz.emulated_dgemm(A, B, 1.0, 0.0, None, mode=oz.MODE_DYNAMIC, target_bits=53, max_bits=200, per_tile=True)
     assert (res.slices_used, res.slices_min, res.pair_tiles) == (tr.verdict.slices_used, tr.verdict.slices_min, tr.verdict.pair_tiles)
     np.testing.assert_array_equal(got, tr.C)
+
+
+@pytest.mark.parametrize("m,n,k", [(3000, 3100, 70), (2200, 4500, 90)])
+def test_esc_of_several_blocks_per_workgroup(lib, m, n, k):
+    # more 128 x 128 blocks of pairs than the ESC kernel has workgroups: a workgroup meets blocks that its matrix-unit pass
+    # resolves and blocks that it has to compute again on int16 (a band of wide rows, a zero row, a zero column)
+    g, h = lib
+    A, B = wl.wide_rows(m, k, n, seed=m, row_lo=m // 3, row_hi=m // 3 + 140, spread=60)
+    A[m - 7] = 0.0
+    B[:, n // 2] = 0.0
+    _, gm, res = run_gpu(g, h, A, B, 1.0, 0.0, None, mode=g.OZ_DYNAMIC, target_bits=40, max_bits=200, heuristic=0, tile_slices=1)
+    span = oz.esc_coarse_tiles(A, B)
+    assert (res.fallback, res.esc) == (0, span.max()) and res.esc > 60 and span.min() < 30
+    np.testing.assert_array_equal(gm.tile_slice_counts(), oz.tile_slices(40, span))
 
 
 @pytest.mark.parametrize("ta,tb,m,n,k", [("N", "N", 512, 512, 512), ("T", "N", 500, 301, 703), ("N", "T", 65, 130, 5000), ("T", "T", 1000, 1300, 777),

@@ -1,6 +1,7 @@
 """Launch geometry followed on the host (no GPU).  The walk of the slice GEMM's workgroups over the units of C: every unit
 that holds a row and a column of C is multiplied over every 64 of k exactly once, whatever the order, the split along
-k and the padding.  The scan's launches: none has more threads than a launch may have."""
+k and the padding.  The scan's launches: none has more threads than a launch may have.  The ESC kernel's blocks: those
+that one row or column of the operands leaves open meet as many workgroups as there are."""
 import itertools
 import os
 import subprocess
@@ -83,3 +84,15 @@ def test_scan_launches_stay_within_the_grid_limit(scan_grid):
     assert slabs
     (launches, *_), = scan_grid([(8192, 8192, 8192, 16, 0, 0)])
     assert launches == 1
+
+
+def test_blocks_of_one_row_or_column_are_spread_over_the_workgroups(tmp_path_factory):
+    run = host_program(tmp_path_factory, "host_esc_walk.cpp")
+    sizes = [(64, 64), (32, 32), (16, 512), (512, 16), (128, 128), (33, 47), (2, 300), (300, 2), (1, 700), (256, 256), (8, 4096),
+             (72, 72), (96, 96), (80, 200), (64, 1000), (512, 512), (1024, 1024)]
+    cases = [(a, b, min(a * b, 512)) for a, b in sizes]
+    for c, (wrong, most_row, most_col) in zip(cases, run(cases)):
+        nbi, nbj, grid = c
+        assert wrong == 0, c
+        # a block row has nbj blocks, a block column nbi: not far from an even share of either, for each workgroup
+        assert most_row <= 3 * -(-nbj // grid) + 1 and most_col <= -(-nbi // grid), (c, most_row, most_col)
