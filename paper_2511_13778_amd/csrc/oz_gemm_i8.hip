@@ -51,12 +51,9 @@
 //    work are spread over the gaps between a step's MFMAs, and the loops are laid out for few branches.
 #include <type_traits>
 
-#include "oz_gemm_plan.h"
+#include "oz_gemm_device.h"
 
 namespace oz {
-
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
 
 constexpr int kDiagAtomic = 3;                   // the same in the atomic variant (its 32x32 tiles need more registers in flight)
 constexpr int kStages = 10;                      // LDS stages; the pipeline below counts on ten
@@ -67,42 +64,9 @@ constexpr int kGemmLds = kRingBytes;             // 160 KB: all of the CU's LDS
 static_assert(kKPad % kBK == 0, "k padding must cover whole steps");
 static_assert(kTile == 2 * kUnit, "a block of C with its own slice count is two by two units");
 
-constexpr int kMaxSyncSpins = 384;    // upper bound of the wait for the other workgroups of a round
 constexpr int kSyncMinK = 2048;       // units of a shorter k run without the in-step waits
 constexpr int kSyncMinItems = 320;    // nor one of fewer steps than seven slices have there (8192 x 8192 x 2048: one slice
                                       // 681 -> 630 us, two 845 -> 807, three 1055 -> 1005, four 1388 -> 1350)
-constexpr int kMidSyncMinK = 24576;   // from this k on, workgroups also wait after every group of anti-diagonals
-
-// Records this workgroup's arrival at *counter and, if `wait`, waits (bounded, about half a
-// millisecond) until `target` workgroups have arrived.  The wait only improves cache locality:
-// correctness does not depend on it, and every wave gets past it whatever the other workgroups do.
-// A workgroup that did not meet the others in time (the chip is shared with another kernel, or workgroups are not
-// placed as assumed) keeps counting its arrivals, which the others rely on, but stops waiting (`wait` of thread 0
-// becomes false), so the cost of a wrong assumption is paid once.
-__device__ __forceinline__ void round_sync(int32_t* counter, int target, bool& wait) {
-    if (threadIdx.x == 0) {
-        atomicAdd(counter, 1);
-        if (wait) {
-            bool met = false;
-            for (int spin = 0; spin < kMaxSyncSpins && !met; ++spin) {
-                met = __hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= target;
-                if (!met) __builtin_amdgcn_s_sleep(8);
-            }
-            wait = met;
-        }
-    }
-    asm volatile("s_barrier" ::: "memory");
-}
-
-// 64 lanes x 16 B from global memory into LDS: lane l's 16 bytes land at lds_addr + LDS_IMM + 16*l.
-// The LDS byte address travels in M0 (set by the scalar add).  The compiler does not see this as a
-// memory access, so completion is awaited with explicit s_waitcnt vmcnt(...) below.
-// The global address is a wave-uniform base (scalar registers) plus a per-lane byte offset.
-template <int LDS_IMM>
-__device__ __forceinline__ void dma16(const uint8_t* gbase, uint32_t lane_off, uint32_t lds_addr) {
-    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :: "s"(lds_addr), "v"(lane_off), "s"(gbase), "n"(LDS_IMM) : "memory", "scc");
-}
 
 // 16 bytes per lane to a wave-uniform base (scalar register pair) plus a 32-bit per-lane byte offset.
 // Written as assembly so that the address stays in this form: left to itself the compiler builds a
@@ -750,11 +714,16 @@ bool prepare_gemm_i8() {
     return hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_i8_kernel<false>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds) == hipSuccess &&
            hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_i8_kernel<true>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds) == hipSuccess;
+                               hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds) == hipSuccess &&
+           prepare_gemm_i8_few();
 }
 
 SplitPlan launch_gemm_i8(hipStream_t st, const Workspace& w, const Problem& p) {
     const LaunchPlan lp(p);
+    if (lp.few) {
+        launch_gemm_i8_few(st, w, p, lp);
+        return SplitPlan{KSplit::kNone, lp.g, lp.raw_units};
+    }
     const int32_t* tile_S = p.tile_mode ? w.tile_S : nullptr;
     auto launch = [&](int begin, int count, Split sp) -> GemmGrid {
         unsigned grid;

@@ -94,6 +94,7 @@ struct LaunchPlan {
     int full, rest;        // positions in full rounds, and left over
     Split last;            // of the rest (of everything, if there is no full round)
     bool two;              // the rest in a launch of its own
+    bool few;              // at most two slices, on 256 x 256 blocks (gemm_i8_few_kernel) instead of all that
 
     explicit LaunchPlan(const Problem& p) : g() {
         g.nti = int(p.mp / kTile);
@@ -117,6 +118,22 @@ struct LaunchPlan {
         rest = positions - full;
         last = rest != 0 && rest * per_pos < round ? split(p, rest * per_pos) : Split{1, false};
         two = full != 0 && last.z > 1;
+        few = few_slices(p);
+    }
+
+    // At most two slices, whatever the device finds: 256 x 256 blocks, where their estimated time is the shorter one.  In us:
+    // T and L written at 4.5 TB/s, 12 to finish the first of two anti-diagonals, and per round of all CUs 8 and 0.75 per
+    // pair and 64 of k; 128 x 128 units take, per round and all in all, 5.3 and 0.425 per 64 of k with one slice, 8.1 and
+    // 0.67 with two.  (Blocks / units measured: one slice 3000^3 43 / 91, 8192^3 462 / 955; two slices 4096 x 4096 x 512 60 / 54,
+    // 5000 x 5000 x 1000 116 / 134, 8192^3 1236 / 1493.)
+    bool few_slices(const Problem& p) const {
+        if (p.s_cap > 2 || p.tile_mode) return false;
+        const int64_t blocks = int64_t(g.nti) * g.ntj, pairs = p.s_cap * (p.s_cap + 1) / 2;
+        const int64_t blocks_ns = blocks * kTile * kTile * (3 + p.s_cap) / 4500 + 12000 * (p.s_cap - 1) +
+                                  (blocks + p.num_cu - 1) / p.num_cu * (8000 + 750 * pairs * kt);
+        const int64_t units_ns = (int64_t(g.um) * g.un + p.num_cu - 1) / p.num_cu *
+                                 (p.s_cap == 1 ? 5300 + int64_t(425) * kt : 8100 + int64_t(670) * kt);
+        return blocks_ns < units_ns;
     }
 
     // k-blocks a part can touch, whatever the slice count turns out to be (fewer slices: longer k-blocks)
@@ -171,5 +188,9 @@ struct LaunchPlan {
         return l;
     }
 };
+
+// the slice GEMM of a plan with `few` set, and what it needs before its first launch on a device
+bool prepare_gemm_i8_few();
+void launch_gemm_i8_few(hipStream_t st, const Workspace& w, const Problem& p, const LaunchPlan& lp);
 
 }  // namespace oz

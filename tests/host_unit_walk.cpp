@@ -1,7 +1,7 @@
 // Follows every workgroup of the slice GEMM's launches on the host, with the library's own launch plan and walk, and
 // counts how often each (unit of C, part of k) is taken.  Reads lines "m n k s_cap tile_mode num_cu"; prints per line
-// "kind zsplit missed repeated mixed" with kind 0 whole, 1 parts, 2 atomics (of the launch that may be split), mixed =
-// workgroups that take units of different parts.
+// "kind zsplit missed repeated mixed few" with kind 0 whole, 1 parts, 2 atomics (of the launch that may be split), mixed =
+// workgroups that take units of different parts, few = the call goes to the 256 x 256 blocks instead.
 #include <cstdio>
 #include <vector>
 
@@ -64,7 +64,7 @@ int main() {
                 missed += c == 0;
                 repeated += c > 1;
             }
-        std::printf("%d %d %lld %lld %lld\n", lp.last.z == 1 ? 0 : (lp.last.atomic ? 2 : 1), lp.last.z, missed, repeated, mixed);
+        std::printf("%d %d %lld %lld %lld %d\n", lp.last.z == 1 ? 0 : (lp.last.atomic ? 2 : 1), lp.last.z, missed, repeated, mixed, int(lp.few));
     }
     return 0;
 }

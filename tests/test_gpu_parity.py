@@ -1038,6 +1038,41 @@ def test_esc_of_several_blocks_per_workgroup(lib, m, n, k):
     np.testing.assert_array_equal(gm.tile_slice_counts(), oz.tile_slices(40, span))
 
 
+@pytest.mark.parametrize("m,n,k,S", [(3700, 3900, 1, 1), (3840, 3840, 64, 1), (3700, 3900, 200, 1), (4900, 5100, 130, 2), (4900, 5100, 320, 2)])
+def test_slice_gemm_of_one_or_two_slices(lib, m, n, k, S):
+    # at most two slices on outputs that fill the chip: 256 x 256 blocks, whole and padded, one step per pair and several,
+    # one round of workgroups and several.  Slices, digits and C are the oracle's bit for bit
+    g, h = lib
+    A, B = wl.lognormal_spread(m, k, n, 0.5, seed=3000 + S + k)
+    check_against_oracle(g, h, A, B, 1.0, 0.0, None, mode="unguarded", slices=S, bound=False)
+
+
+def test_slice_gemm_of_two_slices_long_k(lib):
+    # the same over two k-blocks, with the waits after every anti-diagonal (k of 24576 and more); C against the slices that the device cut, multiplied
+    # as FP64 matrices: whole numbers below 2^53, exact in any order
+    g, h = lib
+    m, n, k, S = 3700, 3900, 66000, 2
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    A = torch.rand((k, m), generator=gen, dtype=torch.float64, device="cuda") - 0.5
+    B = torch.rand((n, k), generator=gen, dtype=torch.float64, device="cuda") - 0.5
+    C = torch.empty((n, m), dtype=torch.float64, device="cuda")
+    gm = g.Gemm(h, m, n, k, g.make_opts(mode=g.OZ_FIXED_UNGUARDED, slices=S), "N", "N")
+    gm.run(A, m, B, k, C, m)
+    torch.cuda.synchronize()
+    # |X| < 2^(8S-2): X = floor(a 2^(8S-3-e)) = 256 d_0 + d_1; the pairs (0,1), (1,0), (0,0)
+    def digits(X, dim):
+        e = torch.floor(torch.log2(X.abs().amax(dim=dim, keepdim=True)))
+        x = torch.floor(X * torch.exp2(8 * S - 3 - e))
+        low = torch.remainder(x + 128, 256) - 128
+        return (x - low) / 256, low, e
+    a0, a1, ea = digits(A, 0)
+    b0, b1, eb = digits(B, 1)
+    want = torch.exp2(ea + eb - 10) * (b0 @ a0 + (b0 @ a1 + b1 @ a0) / 256)
+    torch.cuda.synchronize()
+    assert torch.equal(C, want)
+
+
 @pytest.mark.parametrize("ta,tb,m,n,k", [("N", "N", 512, 512, 512), ("T", "N", 500, 301, 703), ("N", "T", 65, 130, 5000), ("T", "T", 1000, 1300, 777),
                                          ("N", "N", 64, 64, 128), ("T", "N", 2000, 1799, 300)])
 def test_native_small_tiles_with_parts(lib, ta, tb, m, n, k):

@@ -45,7 +45,7 @@ def test_every_unit_and_part_is_taken_exactly_once(walk):
              for k in (1, 64, 65, 700, 1000, 3500, 4000, 7500, 20000) for s_cap in (2, 9, 26) for tile_mode in (0, 1)]
     got = walk(cases)
     odd_atomic = 0
-    for c, (kind, z, missed, repeated, mixed) in zip(cases, got):
+    for c, (kind, z, missed, repeated, mixed, few) in zip(cases, got):
         assert (missed, repeated, mixed) == (0, 0, 0), (c, kind, z, missed, repeated, mixed)
         blocks = -(-c[0] // 256) * -(-c[1] // 256)
         odd_atomic += c[4] == 1 and kind == 2 and blocks * z % 2 == 1
@@ -55,9 +55,19 @@ def test_every_unit_and_part_is_taken_exactly_once(walk):
 @pytest.mark.parametrize("m,n,k", [(100, 100, 4000), (600, 600, 7500), (200, 100, 4000), (600, 100, 3500)])
 def test_shapes_of_the_gpu_test_take_the_atomic_route(walk, m, n, k):
     # what test_per_block_split_with_padding_quadrants multiplies on the GPU
-    (kind, z, missed, repeated, mixed), = walk([(m, n, k, 26, 1, 256)])
+    (kind, z, missed, repeated, mixed, _), = walk([(m, n, k, 26, 1, 256)])
     assert kind == 2 and -(-m // 256) * -(-n // 256) * z % 2 == 1
     assert (missed, repeated, mixed) == (0, 0, 0)
+
+
+def test_which_calls_take_the_256_blocks(walk):
+    # at most two slices and enough blocks to fill the chip; among them what
+    # test_slice_gemm_of_one_or_two_slices multiplies on the GPU
+    yes = [(3700, 3900, 1, 1), (3840, 3840, 64, 1), (3700, 3900, 200, 1), (4900, 5100, 130, 2), (4900, 5100, 320, 2), (8192, 8192, 256, 2),
+           (3700, 3900, 66000, 2)]
+    no = [(3700, 3900, 130, 3), (8192, 8192, 8192, 7), (2048, 2048, 2048, 1), (300, 300, 300, 2)]
+    got = walk([(*c, 0, 256) for c in yes + no] + [(*c, 1, 256) for c in yes])
+    assert [r[5] for r in got] == [1] * len(yes) + [0] * (len(no) + len(yes))
 
 
 @pytest.mark.parametrize("num_cu", [4, 12, 36, 100, 250, 304])
@@ -67,7 +77,7 @@ def test_other_numbers_of_compute_units(walk, num_cu):
     mn = [100, 129, 300, 513, 700, 1300]
     cases = [(m, n, k, s_cap, tile_mode, num_cu) for m, n in itertools.product(mn, mn)
              for k in (64, 700, 3500, 7500, 20000) for s_cap in (2, 9, 26) for tile_mode in (0, 1)]
-    for c, (kind, z, missed, repeated, mixed) in zip(cases, walk(cases)):
+    for c, (kind, z, missed, repeated, mixed, few) in zip(cases, walk(cases)):
         assert (missed, repeated, mixed) == (0, 0, 0), (c, kind, z, missed, repeated, mixed)
 
 
