@@ -1,4 +1,4 @@
-"""Static checks on the generated gfx950 code of the slice GEMM and of the FP64 fallback GEMM (no GPU needed:
+"""Static checks on the generated gfx950 code of the slice GEMM's kernels and of the FP64 fallback GEMM (no GPU needed:
 hipcc cross-compiles).
 
 The kernel issues its tile transfers and epilogue stores from asm blocks whose base address is a
@@ -22,50 +22,108 @@ WAIT_STATES = 5
 @pytest.fixture(scope="module")
 def gemm_asm(tmp_path_factory):
     from paper_2511_13778_amd.build import FLAGS
-    out = tmp_path_factory.mktemp("isa") / "oz_gemm_i8.s"
-    cmd = ["hipcc", *FLAGS, "-S", "--cuda-device-only", os.path.join(CSRC, "oz_gemm_i8.hip"), "-o", str(out)]
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    assert r.returncode == 0, r.stderr
-    return [ln for ln in open(out).read().splitlines() if ln.strip() and not ln.strip().startswith(";")]
+    lines = []
+    for name in ("oz_gemm_i8", "oz_gemm_few"):
+        out = tmp_path_factory.mktemp("isa") / (name + ".s")
+        cmd = ["hipcc", *FLAGS, "-S", "--cuda-device-only", os.path.join(CSRC, name + ".hip"), "-o", str(out)]
+        r = subprocess.run(cmd, capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr
+        lines += [ln for ln in open(out).read().splitlines() if ln.strip() and not ln.strip().startswith(";")]
+    return lines
 
 
-def test_asm_memory_ops_never_read_a_freshly_valu_written_scalar(gemm_asm):
+def function_body(asm, mangled_prefix):
+    start = next(i for i, ln in enumerate(asm) if ln.startswith(mangled_prefix) and ":" in ln)
+    end = next(i for i in range(start, len(asm)) if asm[i].startswith(".Lfunc_end"))
+    return asm[start:end]
+
+
+def too_close(asm):
+    """(memory instructions with a scalar base by opcode, those that read it within WAIT_STATES of a vector-ALU write)."""
     written = {}           # scalar register -> wait-state position of its last vector-ALU write
     pos = 0
-    checked = 0
-    for ln in gemm_asm:
+    seen, bad = {}, []
+    for ln in asm:
         pos += 1
         t = ln.split()
         if t[0] in ("v_readlane_b32", "v_readfirstlane_b32"):
             written[t[1].rstrip(",")] = pos
         elif t[0] == "s_nop":
             pos += int(t[1])
-        elif t[0] in ("global_store_dword", "global_load_lds_dwordx4"):
+        elif t[0].startswith(("global_store", "global_load", "global_atomic")):
             m = re.search(r"s\[(\d+):(\d+)\]", ln)
             if not m:
                 continue
-            checked += 1
+            seen[t[0]] = seen.get(t[0], 0) + 1
             for x in range(int(m.group(1)), int(m.group(2)) + 1):
-                reg = "s%d" % x
-                assert pos - written.get(reg, -10 ** 9) > WAIT_STATES, "%s read %d wait states after a vector-ALU write: %s" % (
-                    reg, pos - written[reg], ln)
-    assert checked > 100          # the kernel's transfers and stores were actually seen
+                if pos - written.get("s%d" % x, -10 ** 9) <= WAIT_STATES:
+                    bad.append(ln)
+    return seen, bad
 
 
-def test_mfma_loop_has_no_spills(gemm_asm):
-    # basic blocks (label to label) that hold the K-step MFMAs must not touch scratch memory
+def basic_blocks(asm):
     block, blocks = [], []
-    for ln in gemm_asm:
+    for ln in asm:
         if re.match(r"^\.LBB\d+_\d+:", ln):
             blocks.append(block)
             block = []
         block.append(ln)
     blocks.append(block)
-    hot = [b for b in blocks if sum("v_mfma_i32_32x32x32_i8" in ln for ln in b) >= 8
-           and any("global_load_lds" in ln or "ds_read_b128" in ln for ln in b)]
-    assert hot
+    return blocks
+
+
+# the slice GEMM's kernels: the MFMA each issues, how its asm blocks write results, and how many basic blocks hold steps
+# with transfers and LDS reads at least
+FORMS = {"_ZN2oz14gemm_i8_kernelILb0EE": ("v_mfma_i32_16x16x64_i8", "global_store_dwordx4", 7),
+         "_ZN2oz14gemm_i8_kernelILb1EE": ("v_mfma_i32_32x32x32_i8", None, 6),
+         "_ZN2oz18gemm_i8_few_kernel": ("v_mfma_i32_32x32x32_i8", "global_store_dword", 1)}
+
+
+@pytest.mark.parametrize("kernel", FORMS)
+def test_asm_memory_ops_never_read_a_freshly_valu_written_scalar(gemm_asm, kernel):
+    seen, bad = too_close(function_body(gemm_asm, kernel))
+    assert not bad, bad
+    # the kernel's transfers, and the epilogue's stores where it has them, were actually looked at
+    assert seen.get("global_load_lds_dwordx4", 0) >= 40
+    store = FORMS[kernel][1]
+    assert store is None or seen.get(store, 0) >= 60
+    assert store is None or not any(op.startswith("global_store") and op != store for op in seen)
+
+
+def test_the_check_sees_a_store_that_is_too_early():
+    for op in ("global_store_dwordx4 v1, v[2:5], s[6:7]", "global_load_lds_dwordx4 v1, s[6:7]"):
+        for nops, bad in ((3, 1), (4, 0)):
+            seen, found = too_close(["\tv_readlane_b32 s7, v0, 1", "\ts_nop %d" % nops, "\t" + op])
+            assert len(found) == bad and sum(seen.values()) == 1
+
+
+def step_blocks(body, mfma):
+    return [b for b in basic_blocks(body) if sum(mfma in ln for ln in b) >= 8
+            and any("global_load_lds" in ln for ln in b) and any("ds_read_b128" in ln for ln in b)]
+
+
+@pytest.mark.parametrize("kernel", FORMS)
+def test_mfma_loop_has_no_spills(gemm_asm, kernel):
+    # basic blocks (label to label) that hold the steps' MFMAs must not touch scratch memory, bring spilled scalars back or
+    # move accumulators between the register files
+    mfma, _, least = FORMS[kernel]
+    body = function_body(gemm_asm, kernel)
+    other = [m for m, _, _ in FORMS.values() if m != mfma][0]
+    assert not any(other in ln for ln in body)          # each kernel is looked at through the MFMA it issues
+    hot = step_blocks(body, mfma)
+    assert len(hot) >= least
     for b in hot:
-        assert not any("scratch_" in ln for ln in b)
+        assert not any("scratch_" in ln or "v_readlane" in ln or "v_writelane" in ln or "v_accvgpr" in ln for ln in b)
+
+
+@pytest.mark.parametrize("kernel", FORMS)
+def test_mfma_loop_waits_for_no_transfer_too_early(gemm_asm, kernel):
+    # The transfers are invisible to the compiler.  A wait of its own for some earlier load (a reload of a spilled register,
+    # say) that falls inside a step waits for the transfers in flight as well: with vmcnt below the sixteen that the steps
+    # themselves wait for, this kernel lost 30 % of its rate.
+    body = function_body(gemm_asm, kernel)
+    waits = [int(n) for b in step_blocks(body, FORMS[kernel][0]) for ln in b for n in re.findall(r"vmcnt\((\d+)\)", ln)]
+    assert all(n >= 16 for n in waits), waits
 
 
 @pytest.fixture(scope="module")
@@ -78,30 +136,17 @@ def dgemm_asm(tmp_path_factory):
     return [ln for ln in open(out).read().splitlines() if ln.strip() and not ln.strip().startswith(";")]
 
 
-def _kernel_body(asm, mangled_prefix):
-    start = next(i for i, ln in enumerate(asm) if ln.startswith(mangled_prefix) and ":" in ln)
-    end = next(i for i in range(start, len(asm)) if asm[i].split()[0] == "s_endpgm")
-    return asm[start:end]
-
-
 @pytest.mark.parametrize("mode", [0, 1])
 def test_fp64_gemm_k_loop_has_no_vector_address_arithmetic(dgemm_asm, mode):
     # The K loop of the FP64 fallback GEMM (128 x 128 tiles, interior and ragged modes) loads its tiles
     # through a buffer descriptor: 16 buffer loads and 64 MFMAs per K step, and no 64-bit vector adds.  With
     # plain pointer loads the compiler rebuilt sixteen 64-bit per-lane addresses in every K step, which
     # cost the matrix unit 4 % of its issue slots; this guards the code generation the speed depends on.
-    body = _kernel_body(dgemm_asm, "_ZN2oz16dgemm_f64_kernelILb1ELb0ELi%dELi128EEE" % mode)
-    block, blocks = [], []
-    for ln in body:
-        if re.match(r"^\.LBB\d+_\d+:", ln):
-            blocks.append(block)
-            block = []
-        block.append(ln)
-    blocks.append(block)
+    body = function_body(dgemm_asm, "_ZN2oz16dgemm_f64_kernelILb1ELb0ELi%dELi128EEE" % mode)
     # the K loop: the block that branches back to its own label (a peeled first K step may precede it);
     # what follows the back branch belongs to the code after the loop
     loops = []
-    for b in blocks:
+    for b in basic_blocks(body):
         label = b[0].split(":")[0] if b and b[0].startswith(".LBB") else None
         back = [i for i, ln in enumerate(b) if label and ln.split()[0].startswith("s_cbranch") and ln.split()[1] == label]
         if back:
