@@ -157,3 +157,49 @@ def test_fp64_gemm_k_loop_has_no_vector_address_arithmetic(dgemm_asm, mode):
     assert sum("buffer_load_dwordx2" in ln for ln in loop) == 16
     assert not any(ln.split()[0].startswith(("v_lshl_add_u64", "v_add_co_u32", "v_addc_co_u32", "global_load")) for ln in loop)
     assert not any("scratch_" in ln for ln in loop)
+
+
+def touched_in_flight(lines):
+    """Loads written as asm whose target is read or written before the next full wait: (loads seen, offending lines)."""
+    def registers(text):
+        out = set()
+        for m in re.finditer(r"\bv\[(\d+):(\d+)\]|\bv(\d+)\b", text):
+            lo, hi = (m.group(1), m.group(2)) if m.group(1) else (m.group(3), m.group(3))
+            out.update(range(int(lo), int(hi) + 1))
+        return out
+
+    loads, bad, flying, in_asm = 0, [], set(), False
+    for ln in lines:
+        t = ln.strip()
+        if t.startswith(";"):
+            in_asm = (in_asm or "#ASMSTART" in t) and "#ASMEND" not in t
+            continue
+        code = t.split(";")[0]
+        if re.search(r"s_waitcnt\b.*vmcnt\(0\)", code):
+            flying = set()
+        elif in_asm and code.startswith("global_load"):
+            target, rest = code.split(",", 1)
+            if registers(rest) & flying or registers(target) & flying:
+                bad.append(ln)
+            loads += 1
+            flying |= registers(target)
+        elif registers(code) & flying:
+            bad.append(ln)
+    return loads, bad
+
+
+def test_esc_loads_written_as_asm_are_not_touched_in_flight(tmp_path):
+    # The ESC kernel requests the operands of its next step in asm, so that they stay ahead of the arithmetic, and awaits them
+    # in a later asm statement.  To the compiler they have arrived at once: a copy or a spill in between would take what
+    # the registers held before, and a register freed in between would be overwritten when the data comes.
+    from paper_2511_13778_amd.build import FLAGS, SOURCE_FLAGS
+    out = tmp_path / "oz_esc.s"
+    cmd = ["hipcc", *FLAGS, *SOURCE_FLAGS["oz_esc.hip"], "-S", "--cuda-device-only", os.path.join(CSRC, "oz_esc.hip"), "-o", str(out)]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    loads, bad = touched_in_flight(function_body([ln for ln in open(out).read().splitlines() if ln.strip()], "_ZN2oz10esc_kernel"))
+    assert loads >= 24 and not bad, bad
+    # the check itself
+    load = ["\t;;#ASMSTART", "\tglobal_load_dwordx4 v[4:7], v[0:1], off", "\t;;#ASMEND"]
+    assert touched_in_flight(load + ["\tv_mov_b32_e32 v9, v5"])[1] and touched_in_flight(load + ["\tv_mov_b32_e32 v6, v9"])[1]
+    assert touched_in_flight(load + ["\ts_waitcnt vmcnt(0)", "\tv_mov_b32_e32 v9, v5"]) == (1, [])
