@@ -232,11 +232,13 @@ __global__ __launch_bounds__(256) void gemm_i8_kernel(const int8_t* __restrict__
     // The next entry: `wrap` bytes on after the last slice of a 64 of k, else a plane on (A) or back (B).  Without a
     // branch but for the end of a group, and in assembly so that it stays at eight scalar instructions: they fit the
     // gaps between the matrix instructions, while a taken branch leaves the matrix unit idle for tens of cycles.
+    // r is written before the other operands are read, hence its '&': without it the compiler may put n in the same register,
+    // being the same number whenever a 64 of k begins.
     int64_t by = 0;
     auto next_by = [&](Stream& s, bool is_b) {
         asm volatile("s_sub_u32 %[r], %[r], 1\n\ts_cmp_eq_u32 %[r], 0\n\ts_cselect_b64 %[by], %[wrap], %[plane]\n\t"
                      "s_cselect_b32 %[r], %[n], %[r]\n\ts_subb_u32 %[c], %[c], 0"
-                     : [r] "+s"(s.r), [c] "+s"(s.c), [by] "=&s"(by)
+                     : [r] "+&s"(s.r), [c] "+s"(s.c), [by] "=&s"(by)
                      : [wrap] "s"(s.wrap), [plane] "s"(is_b ? downB : planeA), [n] "s"(s.n) : "scc");
     };
     auto next_check = [&]() {            // one branch for both streams

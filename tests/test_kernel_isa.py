@@ -126,6 +126,30 @@ def test_mfma_loop_waits_for_no_transfer_too_early(gemm_asm, kernel):
     assert all(n >= 16 for n in waits), waits
 
 
+def shared_countdowns(asm):
+    """(countdowns of the tile streams seen, those that keep another operand in the register they count down first)."""
+    seen, bad = 0, []
+    for i, ln in enumerate(asm):
+        m = re.match(r"s_sub_u32 (s\d+), \1, 1$", ln.strip())
+        if not m or "s_cselect_b64" not in asm[i + 2]:
+            continue
+        seen += 1
+        r = int(m.group(1)[1:])
+        by = [int(x) for x in re.findall(r"\[(\d+):", asm[i + 2])]        # by, wrap, plane: pairs
+        n = re.match(r"s_cselect_b32 s\d+, s(\d+), s\d+", asm[i + 3].strip())
+        if int(n.group(1)) == r or any(r in (x, x + 1) for x in by):
+            bad.append(asm[i:i + 5])
+    return seen, bad
+
+
+def test_stream_countdown_has_its_register_to_itself(gemm_asm):
+    for kernel in list(FORMS)[:2]:
+        seen, bad = shared_countdowns(function_body(gemm_asm, kernel))
+        assert seen >= 16 and not bad, bad
+    alias = ["s_sub_u32 s4, s4, 1", "s_cmp_eq_u32 s4, 0", "s_cselect_b64 s[6:7], s[8:9], s[10:11]", "s_cselect_b32 s4, s4, s4"]
+    assert shared_countdowns(alias + ["s_subb_u32 s5, s5, 0"])[1]
+
+
 @pytest.fixture(scope="module")
 def dgemm_asm(tmp_path_factory):
     from paper_2511_13778_amd.build import FLAGS
