@@ -146,17 +146,21 @@ def main():
     ceilings = None
     if not args.no_ceilings:
         from paper_2511_13778_amd import ozprobe as pr
-        wgs, iters = 1024, 20000
+        wgs = 1024
         sink = torch.zeros(wgs * 256, dtype=torch.int32, device="cuda")
-        ops = float(wgs) * 4 * iters * pr.MFMA_OPS_PER_WAVE_ITER
         gen = torch.Generator(device="cpu").manual_seed(5)
         rnd = torch.randint(-128, 128, (pr.MFMA_OPERAND_BYTES,), dtype=torch.int8, generator=gen).cuda()
         const = torch.full((pr.MFMA_OPERAND_BYTES,), 1, dtype=torch.int8, device="cuda")
         rates = {}
-        for name, buf in (("constant_operands", const), ("random_operands", rnd)):
-            t = time_it(lambda: pr.launch_mfma_i8(st, buf.data_ptr(), sink.data_ptr(), iters, wgs), reps=2)
-            tops = ops / (t * 1e-3) * 1e-12
-            rates[name] = {"TOPS": tops, "implied_clock_GHz": tops * 1e12 / (CU_COUNT * SIMD_PER_CU * INT8_OPS_PER_CLK_SIMD) * 1e-9}
+        # 16x16x64 is what the slice GEMM issues, 32x32x32 its form for at most two slices
+        for shape, launch, per_iter, iters in (("16x16x64", pr.launch_mfma_i8_16x16x64, pr.MFMA_16X16X64_OPS_PER_WAVE_ITER, 10000),
+                                               ("32x32x32", pr.launch_mfma_i8, pr.MFMA_OPS_PER_WAVE_ITER, 20000)):
+            ops = float(wgs) * 4 * iters * per_iter
+            rates[shape] = {}
+            for name, buf in (("constant_operands", const), ("random_operands", rnd)):
+                t = time_it(lambda: launch(st, buf.data_ptr(), sink.data_ptr(), iters, wgs), reps=2)
+                tops = ops / (t * 1e-3) * 1e-12
+                rates[shape][name] = {"TOPS": tops, "implied_clock_GHz": tops * 1e12 / (CU_COUNT * SIMD_PER_CU * INT8_OPS_PER_CLK_SIMD) * 1e-9}
         nbytes = 1 << 30
         src = torch.empty(nbytes, dtype=torch.uint8, device="cuda").fill_(3)
         dst = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
@@ -166,7 +170,7 @@ def main():
         ceilings = {"mfma_i8_only": rates,
                     "copy_kernel_GBps": 2 * nbytes / (t_copy * 1e-3) * 1e-9,
                     "read_kernel_GBps": nbytes / (t_read * 1e-3) * 1e-9,
-                    "note": "MFMA-only loop: 1024 workgroups x 4 waves x 16 accumulators, no memory traffic; "
+                    "note": "MFMA-only loops: 1024 workgroups x 4 waves x 256 accumulation registers, no memory traffic; "
                             "implied clock = rate / (256 CU x 4 SIMD x 2048 int8 ops per clock); streaming kernels "
                             "move 1 GiB"}
         del src, dst, rnd, const, sink
@@ -191,7 +195,7 @@ def main():
                     "ops_per_launch": pairs * flops, "kernel_ms": gemm_ms,
                     "note": "int8 multiply-accumulate counted as 2 ops; peak is the published dense INT8 rate"}
         if ceilings:
-            rnd_tops = ceilings["mfma_i8_only"]["random_operands"]["TOPS"]
+            rnd_tops = ceilings["mfma_i8_only"]["16x16x64"]["random_operands"]["TOPS"]
             roofline["measured_mfma_only_ceiling"] = rnd_tops
             roofline["frac_of_measured_ceiling"] = achieved / rnd_tops
             roofline["implied_clock_GHz_if_mfma_always_busy"] = achieved * 1e12 / (CU_COUNT * SIMD_PER_CU * INT8_OPS_PER_CLK_SIMD) * 1e-9

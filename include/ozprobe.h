@@ -27,6 +27,11 @@ extern "C" {
  * workgroups*256 int32.  Work: workgroups * 4 * iters * 16 * 65536 int8 ops (multiply-add = 2). */
 int ozp_launch_mfma_i8(void* stream, const void* operands, void* sink, int iters, int workgroups);
 
+/* The same loop on the instruction and the register tile of the library's main slice GEMM: iters x 64
+ * v_mfma_i32_16x16x64_i8 on 64 independent accumulators, twenty operand fragments per lane.  Work:
+ * workgroups * 4 * iters * 64 * 32768 int8 ops. */
+int ozp_launch_mfma_i8_16x16x64(void* stream, const void* operands, void* sink, int iters, int workgroups);
+
 /* Plain streaming kernels of known size: dst[i] = src[i] over `bytes` (multiple of 16; reads and
  * writes `bytes` each), and a read-only pass that folds `bytes` of src into 8 bytes at sink.
  * They give the memory system's practical rate and the reference dispatches that the

@@ -8,9 +8,10 @@ import os
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "liboz_probe.so")
-EXPORTS = ("ozp_launch_mfma_i8", "ozp_launch_copy", "ozp_launch_read")
+EXPORTS = ("ozp_launch_mfma_i8", "ozp_launch_mfma_i8_16x16x64", "ozp_launch_copy", "ozp_launch_read")
 MFMA_OPERAND_BYTES = 65536
 MFMA_OPS_PER_WAVE_ITER = 16 * 65536          # 16 instructions of 32x32x32 multiply-adds, 2 ops each
+MFMA_16X16X64_OPS_PER_WAVE_ITER = 64 * 32768 # 64 instructions of 16x16x64
 
 _lib = None
 
@@ -27,6 +28,8 @@ def load_library() -> C.CDLL:
         lib = C.CDLL(LIB_PATH)
         lib.ozp_launch_mfma_i8.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int, C.c_int]
         lib.ozp_launch_mfma_i8.restype = C.c_int
+        lib.ozp_launch_mfma_i8_16x16x64.argtypes = lib.ozp_launch_mfma_i8.argtypes
+        lib.ozp_launch_mfma_i8_16x16x64.restype = C.c_int
         lib.ozp_launch_copy.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t]
         lib.ozp_launch_copy.restype = C.c_int
         lib.ozp_launch_read.argtypes = [C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]
@@ -42,6 +45,11 @@ def _check(rc: int, what: str):
 
 def launch_mfma_i8(stream_ptr, operands_ptr, sink_ptr, iters: int, workgroups: int):
     _check(load_library().ozp_launch_mfma_i8(stream_ptr, operands_ptr, sink_ptr, iters, workgroups), "ozp_launch_mfma_i8")
+
+
+def launch_mfma_i8_16x16x64(stream_ptr, operands_ptr, sink_ptr, iters: int, workgroups: int):
+    _check(load_library().ozp_launch_mfma_i8_16x16x64(stream_ptr, operands_ptr, sink_ptr, iters, workgroups),
+           "ozp_launch_mfma_i8_16x16x64")
 
 
 def launch_copy(stream_ptr, dst_ptr, src_ptr, nbytes: int):
