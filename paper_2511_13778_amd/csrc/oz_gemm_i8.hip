@@ -15,10 +15,13 @@
 // d = 0 is written as an int32 word.  So a k-block leaves the exact integer sum_d P_d 256^(S-1-d) in
 // 4 + (S-1) bytes per element instead of 4S, already aggregated.
 //
-// What bounds it: power.  An MFMA-only loop on random digits reaches 3.5 POP/s with 32x32x32 and 3.7-4.2
-// with 16x16x64 tiles (4.9 with constant operands, where the clock stays up); every byte moved on the way
-// takes its share of the same budget: one LDS read of 1 KB per two 32x32x32 MFMAs costs 8 %, one
-// direct-to-LDS transfer of 1 KB per four costs another 10 % (loops of the same shape as the one below).
+// What bounds it: the power limit and idle issue slots together.  At 8192^3 with seven slices it reaches 2.99 POP/s, the matrix
+// unit busy 76 % of the cycles at 1.88 GHz; an MFMA-only loop on the same register tile and random digits reaches 4.2 POP/s, busy
+// 99 % at 2.0 GHz (4.9 with constant operands at 2.35 GHz; 32x32x32 tiles on random digits 3.5 at 1.67 GHz).  The clock is
+// below its 2.4 GHz in all of them, so what the idle quarter is worth is open: schedules between 71 and 76 % busy differed by
+// 1.5 % in time.  Ends of groups, where sums are written and reloads of spilled registers wait for the transfers in flight,
+// are about 2 % at this size.  Every byte moved takes its share of the power: one LDS read of 1 KB per two 32x32x32 MFMAs 8 %,
+// one direct-to-LDS transfer of 1 KB per four another 10 % (loops of the same shape as the one below).
 // Hence the order of the loops.  Four anti-diagonals at a time means that an A fragment read from LDS
 // meets four B slices, and a B fragment that has been read stays in registers for four steps:
 //  * A step is one slice s of A for 64 of k.  With d_hi the group's first anti-diagonal, step s multiplies
@@ -30,8 +33,9 @@
 //  * v_mfma_i32_16x16x64_i8: per operation it moves a fifth less through the register file than
 //    32x32x32 (16x16 sums are read and written for 64 of k instead of 32).
 // Measured with seven slices, against one pair at a time on 256x256 tiles of 32x32x32: 8192^3 11.2 -> 10.3 ms
-// (2.75 -> 2.99 POP/s; matrix unit busy 75 % of the cycles at 1.83 GHz), 1024x1024x65536 1.85 -> 1.27 ms, and
-// where the quarter of the size lets more CUs work without a k split, 2048^3 0.53 -> 0.19 ms.
+// (2.75 -> 2.99 POP/s), 1024x1024x65536 1.85 -> 1.27 ms, and
+// where the quarter of the size lets more CUs work without a k split, 2048^3 0.53 -> 0.17 ms.  Calls of one or two slices that
+// fill the chip are better off on 256x256 blocks, pair by pair (oz_gemm_few.hip).
 //
 // Mapping to gfx950:
 //  * 4 waves per workgroup, each 64x64 x four anti-diagonals (256 accumulator registers per lane); one
@@ -100,7 +104,7 @@ constexpr int kPieces<8>[kOwnPieces + 8] = {0, 1, 2, 20, 3, 10, 11, 21, 12, 13, 
 // ATOMIC = true: unaggregated sums are added into the unit's raw slot with integer atomics (exact and order-free; the
 // host zeroes the slots before and aggregates them after): as many parts as one likes in the same memory, for
 // outputs of few units.  32x32x32 MFMAs there: a half-wave then adds to 128 contiguous bytes instead of 64, and
-// such launches are bound by the atomics, not by power.
+// such launches are bound by the atomics.
 //
 // A workgroup takes units slot, slot + stride, ... of its XCD's range (one only where the launch has a workgroup per
 // unit); the stream of tiles runs on into the next unit, so neither the first tiles' latency nor the drain

@@ -29,9 +29,9 @@ constexpr int kSumDeadBelow = -10000;
 
 // ---- tiling constants shared between kernels and the workspace layout --------------------
 constexpr int kRowPad = 256;          // rows of the slice panels are padded to this
-constexpr int kKPad = 128;            // k is padded to this (K tile of the INT8 GEMM)
-constexpr int kTile = 256;            // edge of the blocks of C that can take their own slice count
-                                      // (= the slice GEMM's workgroup tile; kRowPad is a multiple)
+constexpr int kKPad = 128;            // k is padded to this (a multiple of the slice GEMM's step of kBK)
+constexpr int kTile = 256;            // edge of the blocks of C that can take their own slice count (kRowPad is a multiple):
+                                      // two by two units of the slice GEMM, one workgroup's share at most two slices deep
 
 // ---- device-resident control record ---------------------------------------------------
 struct Record {
