@@ -1047,6 +1047,27 @@ def test_slice_gemm_of_one_or_two_slices(lib, m, n, k, S):
     check_against_oracle(g, h, A, B, 1.0, 0.0, None, mode="unguarded", slices=S, bound=False)
 
 
+def test_slice_gemm_of_two_slices_dynamic(lib):
+    # the same kernel where the device decides between two slices, one and the native product (max_bits allows no third)
+    g, h = lib
+    for target, nan in ((4, False), (4, True), (9, False)):
+        A, B = wl.lognormal_spread(4900, 130, 5100, 0.1, seed=77)
+        if nan:
+            A[1234, 56] = np.nan
+        got, _, res = run_gpu(g, h, A, B, mode=g.OZ_DYNAMIC, target_bits=target, max_bits=14, heuristic=0)
+        esc = None if nan else oz.esc_coarse(A, B)
+        if nan or target + esc > 14:
+            assert (res.fallback, res.reason) == (1, 1 if nan else 2)
+            assert np.array_equal(np.isnan(got).any(axis=1), np.isnan(A).any(axis=1))
+            # |computed - exact| <= (k + 2) * 2^-53 * |A||B| for each of the two sides
+            slack = 2.0 * (130 + 2) * 2.0 ** -53 * (np.abs(A[:1000]) @ np.abs(B))
+            assert np.all(np.abs(got[:1000] - A[:1000] @ B) <= slack)
+        else:
+            tr = oz.emulated_dgemm(A, B, 1.0, 0.0, None, mode=oz.MODE_DYNAMIC, target_bits=target, max_bits=14)
+            assert (res.fallback, res.slices_used, res.esc) == (0, tr.verdict.slices_used, esc) and res.slices_used <= 2
+            np.testing.assert_array_equal(got, tr.C)
+
+
 def test_slice_gemm_of_two_slices_long_k(lib):
     # the same over two k-blocks, with the waits after every anti-diagonal (k of 24576 and more); C against the slices that the device cut, multiplied
     # as FP64 matrices: whole numbers below 2^53, exact in any order
