@@ -31,7 +31,7 @@ constexpr int kSumDeadBelow = -10000;
 constexpr int kRowPad = 256;          // rows of the slice panels are padded to this
 constexpr int kKPad = 128;            // k is padded to this (a multiple of the slice GEMM's step of kBK)
 constexpr int kTile = 256;            // edge of the blocks of C that can take their own slice count (kRowPad is a multiple):
-                                      // two by two units of the slice GEMM, one workgroup's share at most two slices deep
+                                      // two by two units of gemm_i8_kernel, one workgroup's share in gemm_i8_few_kernel
 
 // ---- device-resident control record ---------------------------------------------------
 struct Record {
@@ -186,13 +186,13 @@ inline ScanGrid scan_grid(const Problem& p, bool a_rows_contig, bool b_rows_cont
 
 // ---- walk of the ESC kernel ------------------------------------------------------------
 // Position -> block of 128 x 128 pairs (nbi x nbj of them), for `workgroups` that take every workgroups-th position; as many
-// workgroups as blocks take them as they come, fewer share them out.  A row of A or a column of B
-// that is wide or zero leaves a whole row or column of blocks open, to be computed again the long way, and neither may meet
-// the same few workgroups.  So block columns come one after the other, each turned against the last, and once more per walk
-// over all workgroups; by eight blocks at a time where that leaves enough places, so that an XCD (every eighth workgroup)
-// keeps to an eighth of the rows' tables for eight such walks.  (Straight, with `workgroups` a multiple of nbi, one zero row at 8192^3 was 64
-// open blocks for 8 workgroups: 666 us for the ESC, now 149.  Turned by one block, with all rows' tables in every XCD's L2,
-// a call without open blocks took 84 us; straight 75, now 78, and at 4096^3 38 -> 35.)
+// workgroups as blocks take them as they come, fewer share them out.  A row of A or a column of B that is wide or zero
+// leaves a whole row or column of blocks open, to be computed again the long way, and neither may meet the same few
+// workgroups.  So block columns come one after the other, each turned against the last, and once more per walk over all
+// workgroups; by eight blocks at a time where that leaves enough places, so that an XCD (every eighth workgroup) keeps to
+// an eighth of the rows' tables for eight such walks.  (Straight, with `workgroups` a multiple of nbi, one zero row at
+// 8192^3 was 64 open blocks for 8 workgroups: 666 us for the ESC, now 149.  Turned by one block, with all rows' tables in
+// every XCD's L2, a call without open blocks took 84 us; straight 75, now 78, and at 4096^3 38 -> 35.)
 __host__ __device__ inline void esc_block_at(int64_t position, int64_t nbi, int64_t nbj, int64_t workgroups, int64_t& bi,
                                              int64_t& bj) {
     bj = position / nbi;
