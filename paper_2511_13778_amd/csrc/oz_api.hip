@@ -425,9 +425,9 @@ oz_status_t dgemm_impl(oz_handle_t h, void* stream, char transa, char transb, in
     clk.done(2);          // the verdict is given by the last workgroup of the ESC kernel
     launch_slice(st, oa, ob, w, p);
     clk.done(3);
-    const SplitPlan split = launch_gemm_i8(st, w, p);
+    const SplitPlan split = launch_gemm_i8(st, w, p, alpha, beta, C, ldc);
     clk.done(4);
-    launch_recompose(st, w, p, split, alpha, beta, C, ldc);
+    if (split.kind != KSplit::kDone) launch_recompose(st, w, p, split, alpha, beta, C, ldc);
     clk.done(5);
     if (guarded) launch_dgemm_f64(st, w.rec, KnownRecord{}, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, h->num_cu, f64_scratch, f64_scratch_bytes);
     clk.done(6);

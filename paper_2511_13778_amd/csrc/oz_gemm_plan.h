@@ -81,6 +81,10 @@ __host__ __device__ inline bool skip_padding(int xcd, int stride, int& slot, con
     return true;
 }
 
+// Tiles of C a workgroup of gemm_small_kernel owns.
+constexpr int kSmallTile = 32;
+constexpr int kSmallLdsMax = 160 * 1024;         // all of a CU's LDS
+
 struct Split { int z; bool atomic; };
 
 // How a call's units are dealt to launches.
@@ -95,6 +99,7 @@ struct LaunchPlan {
     Split last;            // of the rest (of everything, if there is no full round)
     bool two;              // the rest in a launch of its own
     bool few;              // at most two slices, on 256 x 256 blocks (gemm_i8_few_kernel) instead of all that
+    bool small;            // few units and short k, on 32 x 32 tiles with the recomposition (gemm_small_kernel) instead of all that
 
     explicit LaunchPlan(const Problem& p) : g() {
         g.nti = int(p.mp / kTile);
@@ -116,9 +121,36 @@ struct LaunchPlan {
         const int round = p.num_cu;
         full = positions / round * round;
         rest = positions - full;
-        last = rest != 0 && rest * per_pos < round ? split(p, rest * per_pos) : Split{1, false};
+        int64_t last_ns = 0;
+        last = rest != 0 && rest * per_pos < round ? split(p, rest * per_pos, last_ns) : Split{1, false};
         two = full != 0 && last.z > 1;
         few = few_slices(p);
+        small = small_call(p, last_ns);
+    }
+
+    int64_t small_tiles(const Problem& p) const {
+        return ((p.m + kSmallTile - 1) / kSmallTile) * ((p.n + kSmallTile - 1) / kSmallTile);
+    }
+
+    // Whether slice GEMM and recomposition take longer in their two launches than in the one of gemm_small_kernel.  Estimated
+    // in ns for S slices (one more than the fewest where the device decides):
+    //   one launch   8 us, and per 64 of k 0.4 us + 0.11 us per slice with a workgroup per CU at most; beyond that two share a
+    //                CU: per 512 tiles 4 us, and per 64 of k 0.25 us + 0.18 us per slice
+    //   two          10 us, and for seven slices 14 us, 5.5 us per million elements of C, 0.5 us per part of a k split, and
+    //                what split() estimates or 4.2 us per 64 of k and 5 us per round of units; (S+1)/8 of that for S
+    // Measured, the whole call with two launches / one, nine slices (dynamic) and three: 200x300x260 72 / 37 us and 37 / 21,
+    // 512^3 85 / 46 and 38 / 25, 700x700x1500 126 / 90 and 56 / 51, 1024^3 117 / 104 and 55 / 58, 256x256x4000 111 / 120 and
+    // 52 / 65, 1500x1500x128 86 / 68 and 47 / 40, 2000x2000x256 114 / 132 and 52 / 69.
+    bool small_call(const Problem& p, int64_t last_ns) const {
+        if (p.nkb != 1) return false;
+        const int64_t S = p.s_min == p.s_cap ? p.s_cap : p.s_min + 1;
+        const int64_t tiles = small_tiles(p);
+        const int64_t one = 8000 + (tiles <= p.num_cu ? kt * (400 + 110 * S)
+                                                      : std::max(tiles, int64_t(2) * p.num_cu) * (4000 + kt * (250 + 180 * S)) / (2 * p.num_cu));
+        const int64_t rounds = (int64_t(positions) * per_pos + p.num_cu - 1) / p.num_cu;
+        const int64_t gemm = full == 0 && last.z > 1 ? last_ns + int64_t(500) * last.z : rounds * (int64_t(4200) * kt + 5000);
+        const int64_t two_launches = 10000 + (14000 + p.m * p.n * 55 / 10000 + gemm) * (S + 1) / 8;
+        return one < two_launches * 95 / 100;
     }
 
     // At most two slices, whatever the device finds: 256 x 256 blocks, where their estimated time is the shorter one.  In us:
@@ -147,11 +179,11 @@ struct LaunchPlan {
     // start and to write its sums.  Parts with slots of their own move 10 bytes per element and part (60 ns per part and
     // unit) and, for the rest of a larger product, need a launch to be added (6 us); atomics add 28 bytes per element
     // and part (170 ns) and need the slots zeroed (8 us), but no more memory for more parts.
-    Split split(const Problem& p, int units) const {
+    Split split(const Problem& p, int units, int64_t& best_ns) const {
         const bool whole = units == positions * per_pos;     // the recomposition puts it together
         const int64_t raw_bytes = int64_t(p.nkb) * p.s_cap * raw_units * (kUnit * kUnit * 4);
         Split best{1, false};
-        int64_t best_ns = (int64_t(kt) * 4200 + 5000) * 95 / 100;     // a split has to gain 5 %
+        best_ns = (int64_t(kt) * 4200 + 5000) * 95 / 100;     // a split has to gain 5 %
         for (int z = 2; z <= kt && int64_t(units) * z <= p.num_cu; ++z) {
             const int64_t steps = (kt + z - 1) / z;
             if (int64_t(z - 1) * units * nkb_part(p, z) * part_slot_bytes(p.s_cap) <= raw_bytes) {
@@ -191,6 +223,10 @@ struct LaunchPlan {
 
 // the slice GEMM of a plan with `few` set, and what it needs before its first launch on a device
 bool prepare_gemm_i8_few();
+// the slice GEMM and the recomposition of a plan with `small` set
+bool prepare_gemm_small();
+void launch_gemm_small(hipStream_t st, const Workspace& w, const Problem& p, const LaunchPlan& lp, double alpha, double beta,
+                       double* C, int64_t ldc);
 void launch_gemm_i8_few(hipStream_t st, const Workspace& w, const Problem& p, const LaunchPlan& lp);
 
 }  // namespace oz

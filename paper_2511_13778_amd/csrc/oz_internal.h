@@ -110,8 +110,9 @@ struct GemmGrid {
 };
 
 // How the whole product was split along k, for the recomposition to put together: not at all (the planes T / L are
-// complete), into parts that hold their own aggregated sums, or with integer atomics into raw sums.
-enum class KSplit { kNone, kParts, kAtomic };
+// complete), into parts that hold their own aggregated sums, or with integer atomics into raw sums.  kDone: nothing is left to
+// do, C is written.
+enum class KSplit { kNone, kParts, kAtomic, kDone };
 struct SplitPlan {
     KSplit kind;
     GemmGrid g;        // of the one launch that covered the product
@@ -226,8 +227,8 @@ void launch_slice(hipStream_t st, const Operand& a, const Operand& b, const Work
 void tile_order_shape(const Problem& p, int& first, int& deal);
 // allows the slice GEMM its LDS on the current device (a property of the device: set when a handle is made for it)
 bool prepare_gemm_i8();
-// returns what the recomposition still has to put together
-SplitPlan launch_gemm_i8(hipStream_t st, const Workspace& w, const Problem& p);
+// returns what the recomposition still has to put together; small calls are recomposed in the same launch (kDone)
+SplitPlan launch_gemm_i8(hipStream_t st, const Workspace& w, const Problem& p, double alpha, double beta, double* C, int64_t ldc);
 void launch_recompose(hipStream_t st, const Workspace& w, const Problem& p, const SplitPlan& split, double alpha,
                       double beta, double* C, int64_t ldc);
 // rec == nullptr: run unconditionally; otherwise run only when rec->res.fallback != 0.
