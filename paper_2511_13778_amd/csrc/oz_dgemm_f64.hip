@@ -16,10 +16,13 @@
 // (129, 131, 133) give the same run time, so it is left as it is.
 // Tile loads go through a buffer descriptor (no vector address arithmetic in the K loop); ragged sizes
 // run the same loop with clamped rows and a short first K step; where the caller provides scratch memory, k may be
-// split over several workgroups per tile (partial tiles added in a fixed order by dgemm_f64_reduce_kernel).  The tile edge
-// (128, or 64 with waves of 32x32) and the number of parts are chosen together by an estimated time.
+// split over several workgroups per tile (partial products added in a fixed order by dgemm_f64_reduce_kernel).  The tile edge
+// (128, or 64 with waves of 32x32), the small tiles of dgemm_f64_direct_kernel and the number of parts are chosen together by
+// an estimated time.
 // The kernel is launched on every call and returns at once unless the verdict selected it.
-#include "oz_internal.h"
+#include <algorithm>
+
+#include "oz_f64.h"
 
 namespace oz {
 
@@ -122,35 +125,14 @@ __global__ __launch_bounds__(256, 2) void dgemm_f64_kernel(
     if (rec && !rec->res.fallback) return;
     if (blockIdx.x == 0 && threadIdx.x == 0) write_known_record(known);
 
-    // Workgroup ids are dealt round-robin to the 8 XCDs; each XCD gets a contiguous range of a tile
-    // order in which 64 consecutive tiles (what an XCD runs at a time: 32 CUs, two workgroups each)
-    // form an 8 x 8 block, so they share 16 panels in that XCD's L2.
-    // With a k split (zsplit > 1) a work unit is (tile, part of the k range), ordered part by part.
     int ti, tj, z;
-    {
-        const int tiles = ntm * ntn, total = tiles * zsplit;
-        const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-        const int per = total >> 3, rem = total & 7;
-        const int unit = xcd * per + min(xcd, rem) + slot;
-        z = unit / tiles;
-        const int lin = unit - z * tiles;
-        constexpr int GW = 8;
-        const int panel = lin / (GW * ntm);
-        const int in_panel = lin - panel * GW * ntm;
-        const int w = min(GW, ntn - panel * GW);
-        ti = in_panel / w;
-        tj = panel * GW + in_panel % w;
-    }
+    f64_tile_of(int(blockIdx.x), ntm, ntn, zsplit, ti, tj, z);
     const int64_t i0 = int64_t(ti) * T, j0 = int64_t(tj) * T;
-    // this unit's k range: part 0 is [0, k - (zsplit-1)*kpart) and carries k mod 16, the others have kpart
-    // (a multiple of 16) each; from here on A, B and k describe that range alone
-    if (zsplit > 1) {
-        const int64_t k0 = k - int64_t(zsplit - 1) * kpart;
-        const int64_t kb = z == 0 ? 0 : k0 + int64_t(z - 1) * kpart;
-        A += kb * a_sl;
-        B += kb * b_sl;
-        k = z == 0 ? k0 : kpart;
-    }
+    // from here on A, B and k describe this unit's k range alone
+    int64_t kb;
+    f64_k_part(zsplit, z, kpart, k, kb);
+    A += kb * a_sl;
+    B += kb * b_sl;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wi = wave & 1, wj = wave >> 1;
 
@@ -266,15 +248,16 @@ __global__ __launch_bounds__(256, 2) void dgemm_f64_kernel(
 
     // result register r of tile (fj, fi): j = fj*16 + 4*r + lane/16, i = fi*16 + lane%16
     if (zsplit > 1) {
-        // partial product of this part of the k range: tile (ti, tj) of part z, T x T doubles, i contiguous
-        double* dst = partial + ((int64_t(z) * ntn + tj) * ntm + ti) * (T * T);
+        // partial product of this part of the k range, at its place in a matrix of whole tiles
+        const int64_t ldp = int64_t(ntm) * T;
+        double* dst = partial + (int64_t(z) * ntn * T + j0) * ldp + i0;
 #pragma unroll
         for (int fj = 0; fj < MT; ++fj)
 #pragma unroll
             for (int fi = 0; fi < MT; ++fi)
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                    dst[(wj * WT + fj * 16 + 4 * r + (lane >> 4)) * T + wi * WT + fi * 16 + (lane & 15)] = acc[fj][fi][r];
+                    dst[(wj * WT + fj * 16 + 4 * r + (lane >> 4)) * ldp + wi * WT + fi * 16 + (lane & 15)] = acc[fj][fi][r];
         return;
     }
 #pragma unroll
@@ -294,18 +277,15 @@ __global__ __launch_bounds__(256, 2) void dgemm_f64_kernel(
 }
 
 // C = alpha * (sum of the parts' partial products, in the order of the parts) + beta * C
-template <int T>
 __global__ __launch_bounds__(256) void dgemm_f64_reduce_kernel(const Record* rec, int64_t m, int64_t n, double alpha,
-                                                               double beta, double* __restrict__ C, int64_t ldc, int ntm,
-                                                               int ntn, int zsplit, const double* __restrict__ partial,
-                                                               int64_t j_first) {
+                                                               double beta, double* __restrict__ C, int64_t ldc, int zsplit,
+                                                               const double* __restrict__ partial, int64_t ldp,
+                                                               int64_t part_stride, int64_t j_first) {
     if (rec && !rec->res.fallback) return;
     const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
     const int64_t j = j_first + blockIdx.y;
     if (i >= m) return;
-    const int64_t ti = i / T, tj = j / T;
-    const double* src = partial + (tj * ntm + ti) * (T * T) + (j - tj * T) * T + (i - ti * T);
-    const int64_t part_stride = int64_t(ntn) * ntm * (T * T);
+    const double* src = partial + j * ldp + i;
     double sum = src[0];
     for (int z = 1; z < zsplit; ++z) sum = __dadd_rn(sum, src[z * part_stride]);
     double out = __dmul_rn(alpha, sum);
@@ -313,63 +293,91 @@ __global__ __launch_bounds__(256) void dgemm_f64_reduce_kernel(const Record* rec
     C[j * ldc + i] = out;
 }
 
+namespace {
+
+// Tiles a call can be cut into and what they cost, in us: a workgroup start + round per round of all CUs, and step per MFMA step of a
+// round (16 k in dgemm_f64_kernel, 4 k of each of the four waves in dgemm_f64_direct_kernel); first: per step of the call, for
+// the operands' way to the first workgroup of a CU.  Operands come out of the caches at 9 TB/s at most (4096^3 and 6144^3 on tiles of
+// 64 and less).  Fitted to 5879 timings of 126 shapes (50 to 8000, k to 65000, all four transposes, every tile, 1 to 16 parts): the
+// choice by these numbers is 3 % off the best one on average, 19 % at most, and 1.18 times as fast as the best choice among
+// the two tiles of dgemm_f64_kernel (at most 10 % slower).
+struct F64Tile {
+    bool direct;
+    int ti, tj;
+    double start, round, step, first;
+};
+constexpr F64Tile kF64Tiles[] = {
+    {false, 128, 128, 0.0, 7.42, 1.717, 0.167}, {false, 64, 64, 2.51, 1.69, 0.433, 0.336},
+    {true, 16, 16, 3.26, 0.38, 0.075, 0.018},   {true, 32, 32, 3.53, 0.94, 0.169, 0.0},
+    {true, 32, 64, 4.07, 2.00, 0.273, 0.0},     {true, 64, 32, 3.31, 2.56, 0.262, 0.008},
+    {true, 48, 64, 3.10, 3.95, 0.341, 0.039},   {true, 64, 48, 3.46, 3.47, 0.361, 0.027},
+};
+constexpr double kF64CacheBytesPerUs = 9e6;
+
+// Tile and number of parts of the k range.  With scratch memory at hand, k may be split over several workgroups per tile:
+// they leave partial products in the scratch memory and a second kernel adds them in the order of the parts (deterministic)
+// and applies alpha and beta: a launch of 4.5 us and zsplit + 2 passes over C at 4.5 TB/s.  A guarded call pays that launch
+// whether it falls back or not: 20 there.
+F64Plan choose_f64(const F64Call& c, int num_cu, void* scratch, size_t scratch_bytes) {
+    F64Plan best{};
+    double best_us = 0.0;
+    const uint32_t m = uint32_t(c.m), n = uint32_t(c.n), cus = uint32_t(num_cu);
+    for (const F64Tile& t : kF64Tiles) {
+        if (!t.direct && c.k < kDK) continue;                // whose fast loads always fetch a full K step
+        const uint32_t ti = uint32_t(t.ti), tj = uint32_t(t.tj), ntm = (m + ti - 1) / ti, ntn = (n + tj - 1) / tj;
+        const uint64_t tiles64 = uint64_t(ntm) * ntn;
+        if (tiles64 > uint64_t(kMaxGridThreads) / 256) continue;
+        const uint32_t tiles = uint32_t(tiles64);
+        const double cache_us = double(tiles) * double(ti + tj) * double(c.k) * 8.0 / kF64CacheBytesPerUs;
+        const int64_t k_least = t.ti == 128 ? 256 : 64;      // what a part keeps at least
+        for (uint32_t z : {1u, 2u, 3u, 4u, 6u, 8u, 12u, 16u}) {
+            if (z > 1 && (scratch == nullptr || c.k < k_least * z || tiles * z > 4 * cus ||
+                          uint64_t(tiles) * z * ti * tj * 8 > scratch_bytes))
+                break;
+            const double rounds = double((tiles * z + cus - 1) / cus), steps = double(uint32_t(c.k + z * kDK - 1) / (z * kDK));
+            double us = std::max(t.start + rounds * (t.round + t.step * steps) + t.first * steps, cache_us);
+            if (z > 1) us += (c.rec ? 20.0 : 4.5) + double(z + 2) * double(m) * double(n) * 8.0 / 4.5e6;
+            if (best_us == 0.0 || us < best_us) {
+                best_us = us;
+                best = F64Plan{t.direct, t.ti, t.tj, int(ntm), int(ntn), int(z), z > 1 ? c.k / z / kDK * kDK : 0,
+                               static_cast<double*>(scratch)};
+            }
+        }
+    }
+    return best;
+}
+
+}  // namespace
+
 void launch_dgemm_f64(hipStream_t st, const Record* rec, const KnownRecord& known, bool ta, bool tb, int64_t m, int64_t n, int64_t k,
                       double alpha, const double* A, int64_t lda, const double* B, int64_t ldb, double beta,
                       double* C, int64_t ldc, int num_cu, void* scratch, size_t scratch_bytes) {
     // op(A)(i,l): N -> A[i + l*lda] (rows contiguous), T -> A[l + i*lda]
     // op(B)(l,j): N -> B[l + j*ldb] (k contiguous),    T -> B[j + l*ldb] (rows contiguous)
-    const int64_t a_sr = ta ? lda : 1, a_sl = ta ? 1 : lda;
-    const int64_t b_sr = tb ? 1 : ldb, b_sl = tb ? ldb : 1;
-    const bool ac = !ta, bc = tb;
-    // the interior path keeps every offset inside a K step of a tile in 32 bits (a lane's own: at most
+    const F64Call c{rec, known, m, n, k, alpha, A, ta ? lda : 1, ta ? 1 : lda, B, tb ? 1 : ldb, tb ? ldb : 1, beta, C, ldc, !ta, tb};
+    // the fast loads keep every offset inside a K step of a tile in 32 bits (a lane's own: at most
     // 15 leading dimensions plus a row of the tile; its elements: up to 7 x 16 leading dimensions
     // further on; in bytes); operands cut out of a very large parent matrix take the bounds-checked
     // path, which indexes in 64 bits
     const int64_t ld_max = lda > ldb ? lda : ldb;
     const bool wide_ld = (128 * ld_max + 256) * 8 >= (int64_t(1) << 32);
-    // Tile edge T and number of parts of the k range zsplit.  With scratch memory at hand, k may be split over
-    // several workgroups per tile: they leave partial products in the scratch memory and a second kernel adds them in
-    // the order of the parts (deterministic) and applies alpha and beta.  Small tiles and splits fill the chip, large
-    // tiles need fewer bytes per flop.  Estimated time in us of a choice, with u = workgroups of the fullest CU:
-    //   a K step of 16   T = 128: 1.8 u from u = 2 on (the matrix unit's rate: two workgroups share a CU), 1.95 alone
-    //                    T = 64:  0.05 + 0.5 u from u = 2 on; one workgroup alone waits for its loads, 0.62 on an empty
-    //                             chip, 0.74 on a full one
-    //   start and end    8 (T = 128) or 6 (T = 64); a split adds a launch of 4 and zsplit + 2 passes over C at 4.5 TB/s.
-    //                    A guarded call pays that launch whether it falls back or not: 20 there.
-    // Measured against one choice by the number of tiles: 512^3 27.8 -> 16.9 us (T = 64, 4 parts), 500x300x700 39 -> 17
-    // (6 parts), 200x300x5000 86 -> 31 (12), 1000x1300x777 66 -> 54 (3), 3000x3000x400 150 -> 127 (T = 64, whole),
-    // 2000x1800x1000 138 -> 128 (T = 128, whole).
-    int T = ((m + 127) / 128) * ((n + 127) / 128) < num_cu ? 64 : 128;
-    int zsplit = 1;
-    if (!wide_ld && k >= kDK) {
-        double best = 0.0;
-        for (int t = 64; t <= 128; t += 64) {
-            const int64_t tiles = ((m + t - 1) / t) * ((n + t - 1) / t);
-            const int64_t k_least = t == 64 ? 64 : 256;      // what a part keeps at least
-            for (int64_t z = 1; z <= 16; ++z) {
-                if (z > 1 && (scratch == nullptr || k / z < k_least || size_t(tiles * z) * t * t * 8 > scratch_bytes)) break;
-                const double u = double((tiles * z + num_cu - 1) / num_cu), steps = double((k + z * kDK - 1) / (z * kDK));
-                const double alone = 0.62 + 0.12 * double(tiles * z) / num_cu;
-                const double us = (t == 128 ? 8.0 + (u > 1.0 ? 1.8 * u : 1.95) * steps : 6.0 + (u > 1.0 ? 0.05 + 0.5 * u : alone) * steps) +
-                                  (z > 1 ? (rec ? 20.0 : 4.0) + double(z + 2) * double(m) * double(n) * 8.0 / 4.5e6 : 0.0);
-                if (best == 0.0 || us < best) {
-                    best = us;
-                    T = t;
-                    zsplit = int(z);
-                }
-            }
-        }
+    // (as does a size of 2^31 and more)
+    const bool wide = wide_ld || ((m | n | k) >> 31) != 0;
+    F64Plan p{};
+    if (!wide) p = choose_f64(c, num_cu, scratch, scratch_bytes);
+    if (p.ti == 0) {
+        const int T = ((m + 127) / 128) * ((n + 127) / 128) < num_cu ? 64 : 128;
+        p = F64Plan{false, T, T, int((m + T - 1) / T), int((n + T - 1) / T), 1, 0, nullptr};
     }
-    const int64_t kpart = zsplit > 1 ? k / zsplit / kDK * kDK : 0;
-    const bool small = T == 64;
-    const int ntm = int((m + T - 1) / T), ntn = int((n + T - 1) / T);
-    const dim3 grid(unsigned(ntm) * unsigned(ntn) * unsigned(zsplit)), block(256);
-    double* partial = static_cast<double*>(scratch);
-    // k < 16: the fast loads always fetch a full K step, which such a matrix does not have
-    const int mode = (wide_ld || k < kDK) ? 2 : (((m % T) || (n % T) || (k % kDK)) ? 1 : 0);
+    if (p.direct) {
+        launch_dgemm_f64_direct(st, c, p);
+    } else {
+        const bool ac = c.a_rows, bc = c.b_rows;
+        const dim3 grid(unsigned(p.ntm) * unsigned(p.ntn) * unsigned(p.zsplit)), block(256);
+        const int mode = wide ? 2 : (((m % p.ti) || (n % p.tj) || (k % kDK)) ? 1 : 0);
 #define OZ_DG_M(AC, BC, MODE, TT)                                                                              \
-    hipLaunchKernelGGL((dgemm_f64_kernel<AC, BC, MODE, TT>), grid, block, 0, st, rec, known, m, n, k, alpha, A, a_sr, \
-                       a_sl, B, b_sr, b_sl, beta, C, ldc, ntm, ntn, zsplit, kpart, partial)
+    hipLaunchKernelGGL((dgemm_f64_kernel<AC, BC, MODE, TT>), grid, block, 0, st, rec, known, m, n, k, alpha, A, c.a_sr, \
+                       c.a_sl, B, c.b_sr, c.b_sl, beta, C, ldc, p.ntm, p.ntn, p.zsplit, p.kpart, p.partial)
 #define OZ_DG_T(AC, BC, TT)                                                                                    \
     {                                                                                                          \
         if (mode == 2) OZ_DG_M(AC, BC, 2, TT);                                                                 \
@@ -378,25 +386,23 @@ void launch_dgemm_f64(hipStream_t st, const Record* rec, const KnownRecord& know
     }
 #define OZ_DG(AC, BC)                                                                                          \
     {                                                                                                          \
-        if (small) OZ_DG_T(AC, BC, 64) else OZ_DG_T(AC, BC, 128)                                               \
+        if (p.ti == 64) OZ_DG_T(AC, BC, 64) else OZ_DG_T(AC, BC, 128)                                          \
     }
-    if (ac && bc) OZ_DG(true, true)
-    else if (ac && !bc) OZ_DG(true, false)
-    else if (!ac && bc) OZ_DG(false, true)
-    else OZ_DG(false, false)
+        if (ac && bc) OZ_DG(true, true)
+        else if (ac && !bc) OZ_DG(true, false)
+        else if (!ac && bc) OZ_DG(false, true)
+        else OZ_DG(false, false)
 #undef OZ_DG_T
 #undef OZ_DG_M
 #undef OZ_DG
-    if (zsplit > 1) {
+    }
+    if (p.zsplit > 1) {
         const unsigned gx = unsigned((m + 255) / 256);
+        const int64_t ldp = int64_t(p.ntm) * p.ti, part_stride = ldp * p.ntn * p.tj;
         for (int64_t j = 0; j < n; j += 65535) {
             const dim3 rgrid(gx, unsigned(n - j < 65535 ? n - j : 65535));
-            if (small)
-                hipLaunchKernelGGL((dgemm_f64_reduce_kernel<64>), rgrid, dim3(256), 0, st, rec, m, n, alpha, beta, C, ldc, ntm,
-                                   ntn, zsplit, partial, j);
-            else
-                hipLaunchKernelGGL((dgemm_f64_reduce_kernel<128>), rgrid, dim3(256), 0, st, rec, m, n, alpha, beta, C, ldc, ntm,
-                                   ntn, zsplit, partial, j);
+            hipLaunchKernelGGL(dgemm_f64_reduce_kernel, rgrid, dim3(256), 0, st, rec, m, n, alpha, beta, C, ldc, p.zsplit,
+                               p.partial, ldp, part_stride, j);
         }
     }
 }

@@ -1,0 +1,41 @@
+"""The FP64 GEMM on small tiles straight from memory (dgemm_f64_direct_kernel) at the edges of its tiles, of its 16s of k and of the
+quarter of k each wave takes, alone and with k split over workgroups.  The oracle is the product in extended precision; an element
+may be off by the forward bound of any summation order."""
+import numpy as np
+import pytest
+
+from test_gpu_parity import lib, run_gpu  # noqa: F401  (lib: fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("m,n,k", [
+    (1, 1, 1), (1, 17, 3), (16, 16, 4), (17, 15, 5), (33, 31, 13), (64, 48, 16), (47, 65, 17), (100, 90, 63), (81, 79, 65),
+    (200, 300, 260), (512, 512, 512), (600, 700, 500), (530, 1290, 131),         # every tile form in turn
+    (1000, 1300, 777), (1280, 1000, 301), (2000, 33, 90), (33, 2000, 90),
+    (64, 64, 7001), (200, 300, 5000),                                           # k split over workgroups as well
+])
+@pytest.mark.parametrize("ta,tb", [("N", "N"), ("N", "T"), ("T", "N"), ("T", "T")])
+def test_small_tiles(lib, m, n, k, ta, tb):
+    g, h = lib
+    rng = np.random.default_rng(m + 7 * n + k)
+    A, B, C = rng.standard_normal((m, k)), rng.standard_normal((k, n)), rng.standard_normal((m, n))
+    got, _, res = run_gpu(g, h, A, B, -1.5, 0.5, C, ta, tb, pad=3, mode=g.OZ_NATIVE)
+    assert res.fallback == 1
+    L = np.longdouble
+    ref = (L(-1.5) * (A.astype(L) @ B.astype(L)) + L(0.5) * C.astype(L)) if m * n * k < 2e7 else -1.5 * (A @ B) + 0.5 * C
+    bound = (k + 3) * 2.0 ** -53 * (1.5 * (np.abs(A) @ np.abs(B)) + 0.5 * np.abs(C)) * (1 if m * n * k < 2e7 else 2)
+    assert np.all(np.abs(got - ref) <= bound)
+
+
+@pytest.mark.parametrize("m,n,k", [(50, 70, 21), (130, 100, 66)])
+def test_small_tiles_keep_inf_and_nan_in_their_row_and_column(lib, m, n, k):
+    # rows past the end are read from the last row and k past the end from the last k: neither may reach another element
+    g, h = lib
+    rng = np.random.default_rng(k)
+    A, B = rng.standard_normal((m, k)), rng.standard_normal((k, n))
+    A[m - 1, k - 1] = np.inf
+    B[k - 1, n - 1] = np.nan
+    for ta, tb in (("N", "N"), ("T", "T")):
+        got, _, _ = run_gpu(g, h, A, B, 1.0, 0.0, None, ta, tb, mode=g.OZ_NATIVE)
+        assert np.all(np.isfinite(got[:-1, :-1])) and np.all(np.isnan(got[:, -1])) and np.all(np.isinf(got[-1, :-1]))
