@@ -417,8 +417,8 @@ oz_status_t dgemm_impl(oz_handle_t h, void* stream, char transa, char transb, in
 
     const bool guarded = opts->mode != OZ_FIXED_UNGUARDED;
     const Operand oa{A, a_sr, a_sl, m, p.mp}, ob{B, b_sr, b_sl, n, p.np};
-    launch_init(st, w, p, guarded ? KnownRecord{} : KnownRecord{w.rec, result, known_verdict(p, *opts, 0)});
-    launch_scan(st, oa, ob, w, p, guarded);
+    launch_scan(st, oa, ob, w, p);
+    launch_exponents(st, oa, ob, w, p, guarded, guarded ? KnownRecord{} : KnownRecord{w.rec, result, known_verdict(p, *opts, 0)});
     clk.done(0);
     if (guarded) launch_esc_verdict(st, w, p, *opts, h->hm, result);
     clk.done(1);

@@ -38,33 +38,67 @@ constexpr int kEncBias = 61;     // 2*61 + 4 < 128: a chunk sum cannot overflow 
 constexpr int kEncRange = 37;    // 5*(-37) + 61 >= -126: smallest encodable entry (BF16 normal)
 constexpr int kEncChunk = 16;    // inner steps per MFMA (K of v_mfma_f32_32x32x16_bf16)
 
-// enc[(h/8) * rows_p + r][h%8] = BF16 bits of 2^(5*(tab[h][r] - e[r]) + 61), or 0
-// grid (mp/256 + np/256, groups of 8 h): the first mp/256 workgroups along x encode U, the others V
-__global__ __launch_bounds__(256) void esc_encode_kernel(const int16_t* __restrict__ U, const int32_t* __restrict__ eA,
-                                                         int64_t mp, uint4* __restrict__ EU, const int16_t* __restrict__ V,
-                                                         const int32_t* __restrict__ eB, int64_t np, uint4* __restrict__ EV,
-                                                         int H2) {
-    const int64_t blocks_u = mp / 256;
-    const bool second = int64_t(blockIdx.x) >= blocks_u;
-    const int16_t* tab = second ? V : U;
-    const int64_t rows_p = second ? np : mp;
-    const int64_t r = (int64_t(blockIdx.x) - (second ? blocks_u : 0)) * 256 + threadIdx.x;
-    const int hc = blockIdx.y;
-    const int er = second ? eB[r] : eA[r];
-    uint32_t w[4];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const int h = hc * 8 + q;
-        uint32_t bits = 0;
-        if (h < H2) {
-            const int x = tab[int64_t(h) * rows_p + r];
-            const int d = x - er;
-            if (x > kSumRealFloor / 2 && d >= -kEncRange && d <= 0)
-                bits = uint32_t(kEncScale * d + kEncBias + 127) << 7;
+struct ExponentSide {
+    const int16_t* group_max;     // [groups][rows_p]
+    int32_t* e;
+    const int16_t* tab;           // [H2][rows_p]
+    uint4* enc;
+    int64_t rows_p;
+};
+
+constexpr int kExpRows = 64;      // rows per workgroup, one per lane
+constexpr int kExpWaves = 16;
+
+// Between scan and ESC.  e[r]: the largest exponent of a row over the scan's groups of blocks (every workgroup of a row block finds
+// it for itself; 16 waves share the groups).  Then the encoded tables, 8 h of a row at a time (groups of 8 wave by wave,
+// over gridDim.y workgroups):
+//   enc[(h/8) * rows_p + r][h%8] = BF16 bits of 2^(5*(tab[h][r] - e[r]) + 61), or 0
+// And the control record is cleared on the way, for the ESC kernel and the slice GEMM.
+// Bound by latency (8192^3: 7.6 us, where clearing and encoding took 5 + 8 in launches of their own).
+__global__ __launch_bounds__(kExpRows * kExpWaves) void exponents_kernel(ExponentSide a, ExponentSide b, int blocks_a, int groups, int H2,
+                                                                         int chunks, Record* rec, int32_t* __restrict__ tile_span,
+                                                                         int64_t tiles, KnownRecord known) {
+    __shared__ int part[kExpWaves][kExpRows];
+    const bool second = int(blockIdx.x) >= blocks_a;
+    const ExponentSide& s = second ? b : a;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t r = int64_t(int(blockIdx.x) - (second ? blocks_a : 0)) * kExpRows + lane;
+    int e = kExpAllZero;
+#pragma unroll 16
+    for (int g = wave; g < groups; g += kExpWaves) e = max(e, int(s.group_max[int64_t(g) * s.rows_p + r]));
+    part[wave][lane] = e;
+    if (blockIdx.x == 0 && blockIdx.y == 0) {
+        if (threadIdx.x == 0) {
+            rec->span_max = 0;
+            rec->esc_done = 0;
+            write_known_record(known);
         }
-        if (q & 1) w[q >> 1] |= bits << 16; else w[q >> 1] = bits;
+        if (threadIdx.x < 8) rec->tile_sync[threadIdx.x] = 0;
     }
-    (second ? EV : EU)[int64_t(hc) * rows_p + r] = make_uint4(w[0], w[1], w[2], w[3]);
+    for (int64_t t = (int64_t(blockIdx.y) * gridDim.x + blockIdx.x) * (kExpRows * kExpWaves) + threadIdx.x; t < tiles;
+         t += int64_t(gridDim.x) * gridDim.y * (kExpRows * kExpWaves))
+        tile_span[t] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kExpWaves; ++w) e = max(e, part[w][lane]);
+    if (wave == 0 && blockIdx.y == 0) {
+        s.e[r] = e;
+        if (e == kExpInfNan) atomicOr(&rec->infnan, 1);      // the scan has cleared it
+    }
+    for (int hc = int(blockIdx.y) * kExpWaves + wave; hc < chunks; hc += int(gridDim.y) * kExpWaves) {
+        int x[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) x[q] = s.tab[int64_t(min(hc * 8 + q, H2 - 1)) * s.rows_p + r];      // all in flight at once
+        uint32_t w[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int d = x[q] - e;
+            const bool in_range = hc * 8 + q < H2 && x[q] > kSumRealFloor / 2 && d >= -kEncRange && d <= 0;
+            const uint32_t bits = in_range ? uint32_t(kEncScale * d + kEncBias + 127) << 7 : 0u;
+            w[q >> 1] |= bits << (16 * (q & 1));
+        }
+        s.enc[int64_t(hc) * s.rows_p + r] = make_uint4(w[0], w[1], w[2], w[3]);
+    }
 }
 
 typedef short short2_t __attribute__((ext_vector_type(2)));
@@ -509,14 +543,26 @@ void launch_known_record(hipStream_t st, const KnownRecord& known) {
     hipLaunchKernelGGL(known_record_kernel, dim3(1), dim3(64), 0, st, known);
 }
 
+void launch_exponents(hipStream_t st, const Operand& a, const Operand& b, const Workspace& w, const Problem& p, bool encode,
+                      const KnownRecord& known) {
+    const ScanGrid g = scan_grid(p, a.stride_r == 1, b.stride_r == 1);
+    const int H2 = 2 * p.G;
+    const int chunks = encode ? (H2 + 2 * kEncChunk - 1) / (2 * kEncChunk) * 4 : 0;
+    const int blocks_a = int(p.mp / kExpRows), blocks = int((p.mp + p.np) / kExpRows);
+    // several workgroups per row block while the CUs are not filled and each still has a chunk for every wave
+    const int y = std::max(1, std::min((p.num_cu + blocks - 1) / blocks, chunks / kExpWaves));
+    const ExponentSide sa{w.group_max_a(), w.eA, w.U, reinterpret_cast<uint4*>(w.EU), p.mp};
+    const ExponentSide sb{w.group_max_b(), w.eB, w.V, reinterpret_cast<uint4*>(w.EV), p.np};
+    hipLaunchKernelGGL(exponents_kernel, dim3(unsigned(blocks), unsigned(y)), dim3(kExpRows * kExpWaves), 0, st, sa, sb, blocks_a,
+                       int(g.groups), H2, chunks, w.rec, w.tile_span, (p.mp / kTile) * (p.np / kTile), known);
+}
+
 void launch_esc_verdict(hipStream_t st, const Workspace& w, const Problem& p, const oz_opts_t& o, const oz_heuristic_t& hm,
                         oz_result_t* user_result) {
     const int H2 = 2 * p.G;
     const int steps = (H2 + 2 * kEncChunk - 1) / (2 * kEncChunk);   // 32 inner steps (4 groups of 8) each
     uint4* const EU = reinterpret_cast<uint4*>(w.EU);
     uint4* const EV = reinterpret_cast<uint4*>(w.EV);
-    hipLaunchKernelGGL(esc_encode_kernel, dim3(unsigned((p.mp + p.np) / 256), unsigned(steps * 4)), dim3(256), 0, st, w.U, w.eA,
-                       p.mp, EU, w.V, w.eB, p.np, EV, H2);
     VerdictArgs v = {o, hm, p.s_cap, p.tile_mode, int(p.mp / kTile), int(p.np / kTile), 0, 0, w.tile_S, user_result};
     if (p.tile_mode) tile_order_shape(p, v.first, v.deal);
     const int64_t blocks = (p.mp / kEscTile) * (p.np / kEscTile);

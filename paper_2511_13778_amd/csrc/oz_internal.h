@@ -24,6 +24,7 @@ constexpr int64_t kMaxMnk = int64_t(1) << 52;    // largest m*n*k: the cost mode
 // [-10000, -4096) "no information", < -10000 "this block contributes nothing to the product".
 constexpr int kExpZeroInMin = -6144;
 constexpr int kExpAllZero = -12288;
+constexpr int kExpInfNan = 1024;      // exponent of Inf and NaN: their field is all ones, that of a number at most 1023 + 1023
 constexpr int kSumRealFloor = -4096;
 constexpr int kSumDeadBelow = -10000;
 
@@ -35,7 +36,7 @@ constexpr int kTile = 256;            // edge of the blocks of C that can take t
 
 // ---- device-resident control record ---------------------------------------------------
 struct Record {
-    int32_t infnan;        // set by the scan kernels (atomicOr)
+    int32_t infnan;        // cleared by the scan, set by exponents_kernel for a row or column exponent of kExpInfNan
     int32_t span_max;      // max_ij (eA_i + eB_j - zt_ij), set by the ESC kernels (atomicMax)
     int32_t esc_done;      // workgroups of the ESC kernel that have left their span (atomicAdd): the last one gives the verdict
     int32_t pad_;
@@ -91,6 +92,11 @@ struct Workspace {
     int32_t* tile_span;    // [np/kTile][mp/kTile] largest coarsened span of the block's dot products (atomicMax)
     int32_t* tile_S;       // [np/kTile][mp/kTile] slice count of the block (per-tile mode), followed by as many
                            // entries again: the order in which the slice GEMM deals the tiles to its workgroups
+
+    // largest exponent of every row in each group of blocks of the scan: in the slice planes, not yet written then and
+    // always larger (two bytes per row and at least one block of 16 k)
+    int16_t* group_max_a() const { return reinterpret_cast<int16_t*>(As); }
+    int16_t* group_max_b() const { return reinterpret_cast<int16_t*>(Bs); }
 };
 
 // ---- geometry of the slice GEMM's launches, shared with the recomposition ----------------
@@ -213,8 +219,10 @@ struct Operand {
     int64_t stride_r, stride_l;
     int64_t rows, rows_p;
 };
-void launch_init(hipStream_t st, const Workspace& w, const Problem& p, const KnownRecord& known);
-void launch_scan(hipStream_t st, const Operand& a, const Operand& b, const Workspace& w, const Problem& p, bool check_infnan);
+void launch_scan(hipStream_t st, const Operand& a, const Operand& b, const Workspace& w, const Problem& p);
+// row and column exponents, the cleared control record, and (encode) the BF16 tables of the ESC
+void launch_exponents(hipStream_t st, const Operand& a, const Operand& b, const Workspace& w, const Problem& p, bool encode,
+                      const KnownRecord& known);
 // coarsened ESC and the verdict (per-block mode: slice counts and dealing order of the blocks as well)
 void launch_esc_verdict(hipStream_t st, const Workspace& w, const Problem& p, const oz_opts_t& o, const oz_heuristic_t& hm,
                         oz_result_t* user_result);

@@ -1,6 +1,7 @@
 // Pre-pass over op(A) and op(B): Inf/NaN scan, per-block exponent Max/Min tables for the
-// coarsened ESC, and the row / column exponents the slicing aligns to (integer atomicMax over the
-// block maxima: order-free, hence deterministic).
+// coarsened ESC, and what the row / column exponents the slicing aligns to are made of: the largest exponent of each row
+// in every group of blocks a workgroup takes (exponents_kernel finishes them; with atomics on the exponents themselves, a
+// launch of its own had to clear them and the control record first: 4.8 us a call).
 // (paper: sections "Pre-processing and Safety Checks" and "Exponent Span Estimation";
 //  block Max/Min: section "ESC", the paragraph on blocks of length b.)
 //
@@ -9,58 +10,59 @@
 
 namespace oz {
 
-// exp(x) = floor(log2|x|) from the bit pattern; zero -> is_zero; all-ones field -> bad.
-__device__ __forceinline__ int exponent_of(uint64_t bits, bool& is_zero, bool& bad) {
-    const uint64_t mag = bits & 0x7FFFFFFFFFFFFFFFull;
-    const int field = int(mag >> 52);
-    is_zero = (mag == 0);
-    bad = (field == 0x7FF);
-    if (field != 0) return field - 1023;
-    // denormal: value = frac * 2^-1074, exponent = position of the leading one - 1074
-    return is_zero ? 0 : (63 - __builtin_clzll(mag)) - 1074;
-}
-
+// Exponents (floor(log2|x|)) of the entries that one thread has seen of a block, a batch of loaded entries at a time.  Kept on
+// the high words: the exponent field grows with the magnitude, so the largest and smallest word have the largest and
+// smallest exponent, and Inf and NaN come out as kExpInfNan.  Five instructions per entry and no branch, so the loads of a
+// batch are all in flight before the first is looked at; zeros and denormals, whose exponent lies elsewhere, are looked
+// for only in a batch that has one.  (Entry by entry, with branches for zeros, loads were waited for one by one: 200 x 300 x 260
+// 5.3 us, now 3.6; 1024 x 1024 x 65536 219, now 196; 8192^3 254, now 238.)
 struct BlockStat {
-    int mx;        // max exponent over non-zero entries
-    int mn;        // min exponent over non-zero entries
-    int any_nz;    // block has a non-zero entry
-    int any_zero;  // block has a zero entry
-    __device__ __forceinline__ void reset() { mx = -32768; mn = 32767; any_nz = 0; any_zero = 0; }
-    __device__ __forceinline__ void add(uint64_t bits, int& bad_acc) {
-        bool z, bad;
-        const int e = exponent_of(bits, z, bad);
-        bad_acc |= int(bad);
-        if (z) { any_zero = 1; } else { any_nz = 1; mx = max(mx, e); mn = min(mn, e); }
+    uint32_t mx, mn;       // largest high word (without sign), smallest of the normal numbers less kMinNormal
+    int mx_low, mn_low;    // exponents of the denormals: -32768 and 32767: none
+    int any_zero;
+    static constexpr uint32_t kMinNormal = 0x00100000u;
+    __device__ __forceinline__ void reset() { mx = 0; mn = ~0u; mx_low = -32768; mn_low = 32767; any_zero = 0; }
+    template <int N>
+    __device__ __forceinline__ void add(const uint64_t (&x)[N]) {
+        uint32_t least = ~0u;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const uint32_t hi = uint32_t(x[i] >> 32) & 0x7FFFFFFFu;
+            mx = max(mx, hi);
+            mn = min(mn, hi - kMinNormal);       // a word below kMinNormal wraps to more than any other
+            least = min(least, hi);
+        }
+        if (least < kMinNormal) {
+#pragma unroll 1
+            for (int i = 0; i < N; ++i) {
+                uint64_t mag = 0;
+#pragma unroll
+                for (int q = 0; q < N; ++q) mag = q == i ? x[q] & 0x7FFFFFFFFFFFFFFFull : mag;
+                if (mag == 0) {
+                    any_zero = 1;
+                } else if (uint32_t(mag >> 32) < kMinNormal) {
+                    const int e = (63 - __builtin_clzll(mag)) - 1074;
+                    mx_low = max(mx_low, e);
+                    mn_low = min(mn_low, e);
+                }
+            }
+        }
     }
-    __device__ __forceinline__ int16_t table_max() const { return int16_t(any_nz ? mx : kExpAllZero); }
-    __device__ __forceinline__ int16_t table_min() const {
-        return int16_t(!any_nz ? kExpAllZero : (any_zero ? kExpZeroInMin : mn));
-    }
+    // largest and smallest exponent of the non-zero entries; -32768 and 32767: none
+    __device__ __forceinline__ int max_exp() const { return mx >= kMinNormal ? int(mx >> 20) - 1023 : mx_low; }
+    __device__ __forceinline__ int min_exp() const { return min(mn_low, mn < 0x80000000u ? int((mn + kMinNormal) >> 20) - 1023 : 32767); }
 };
 
-// resets the control record and the row / column exponents (targets of atomicMax in the scans)
-__global__ __launch_bounds__(256) void init_kernel(Record* rec, int32_t* eA, int64_t mp, int32_t* eB, int64_t np,
-                                                   int32_t* tile_span, int64_t tiles, KnownRecord known) {
-    const int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    if (t == 0) {
-        rec->infnan = 0;
-        rec->span_max = 0;
-        rec->esc_done = 0;
-        write_known_record(known);
-    }
-    if (t < tiles) tile_span[t] = 0;
-    if (t < 8) {
-        rec->tile_sync[t] = 0;
-    }
-    if (t < mp) eA[t] = kExpAllZero;
-    if (t < np) eB[t] = kExpAllZero;
+__device__ __forceinline__ int table_max(int mx) { return mx == -32768 ? kExpAllZero : mx; }
+__device__ __forceinline__ int table_min(int mx, int mn, int any_zero) {
+    return mx == -32768 ? kExpAllZero : (any_zero ? kExpZeroInMin : mn);
 }
 
 struct ScanSide {
     Operand o;
     int16_t* tab;          // [2G][rows_p]
     int max_half;          // 1: Max in the first half of the table, Min in the second; 0: the other way round
-    int32_t* e_out;
+    int16_t* group_max;    // [groups][rows_p] largest exponent of a row in a group of blocks
     int64_t row_blocks;    // workgroups along the rows
 };
 
@@ -72,110 +74,116 @@ __device__ __forceinline__ void scan_store(const ScanSide& s, int G, int g, int6
 // Rows contiguous in memory (stride_r == 1): lanes along 64 rows, so every load instruction of a wave reads 512
 // contiguous bytes; the four waves take every fourth k of a block, which keeps a thread's chain of loads short (a
 // thread per row for four whole blocks: 28 us for 2048 x 2048, now 10), and are combined through LDS.
-__device__ __forceinline__ int scan_rows(const ScanSide& s, int64_t rb, int g0, int per, int64_t k, int b, int G) {
+__device__ __forceinline__ void scan_rows(const ScanSide& s, int64_t rb, int g0, int per, int64_t k, int b, int G) {
     __shared__ int2 part[kScanBlocksPerWg][4][64];     // max; min, with bit 16 set when the part holds a zero
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t r = rb * 64 + lane;
-    int bad = 0;
 #pragma unroll 1
     for (int u = 0; u < per; ++u) {
         const int g = g0 + u;
         BlockStat st;
         st.reset();
         if (g < G && r < s.o.rows) {
-            const int64_t l0 = int64_t(g) * b, l1 = min(k, l0 + b);
-            const uint64_t* src = reinterpret_cast<const uint64_t*>(s.o.X) + r + (l0 + wave) * s.o.stride_l;
-#pragma unroll 16
-            for (int64_t l = l0 + wave; l < l1; l += 4, src += 4 * s.o.stride_l) st.add(*src, bad);
+            // past the end of a block its last entry is read again: it changes neither maximum nor minimum
+            const int64_t l0 = int64_t(g) * b;
+            const int len = int(min(int64_t(b), k - l0));
+            const uint64_t* src = reinterpret_cast<const uint64_t*>(s.o.X) + r + l0 * s.o.stride_l;
+            for (int l = wave; l < len; l += 64) {
+                uint64_t x[16];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) x[i] = src[min(l + 4 * i, len - 1) * s.o.stride_l];
+                st.add(x);
+            }
         }
-        part[u][wave][lane] = make_int2(st.mx, (st.mn & 0xFFFF) | (st.any_zero << 16));
+        part[u][wave][lane] = make_int2(st.max_exp(), (st.min_exp() & 0xFFFF) | (st.any_zero << 16));
     }
     __syncthreads();
     // wave u finishes block g0 + u
     const bool mine = wave < per && g0 + wave < G;
-    BlockStat st;
-    st.reset();
+    int mx = -32768, mn = 32767, any_zero = 0;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
         const int2 x = part[mine ? wave : 0][w][lane];
-        st.mx = max(st.mx, x.x);
-        st.mn = min(st.mn, int(int16_t(x.y & 0xFFFF)));
-        st.any_zero |= x.y >> 16;
+        mx = max(mx, x.x);
+        mn = min(mn, int(int16_t(x.y & 0xFFFF)));
+        any_zero |= x.y >> 16;
     }
-    st.any_nz = st.mx != -32768;
-    if (mine) scan_store(s, G, g0 + wave, r, st.table_max(), st.table_min());
+    if (mine) scan_store(s, G, g0 + wave, r, table_max(mx), table_min(mx, mn, any_zero));
     __syncthreads();
     int* const row_max = reinterpret_cast<int*>(part);
-    row_max[wave * 64 + lane] = mine ? int(st.table_max()) : kExpAllZero;
+    row_max[wave * 64 + lane] = mine ? table_max(mx) : kExpAllZero;
     __syncthreads();
     if (wave == 0) {
         const int e = max(max(row_max[lane], row_max[64 + lane]), max(row_max[128 + lane], row_max[192 + lane]));
-        if (e > kExpAllZero) atomicMax(&s.e_out[r], e);
+        s.group_max[int64_t(g0 / per) * s.o.rows_p + r] = int16_t(e);
     }
-    return bad;
 }
 
 // k contiguous in memory (stride_l == 1): 16 lanes share one row so that a load instruction
 // reads 128 contiguous bytes per row; partial results are combined across the 16 lanes.
-// A workgroup covers 16 rows.
-__device__ __forceinline__ int scan_k(const ScanSide& s, int64_t rb, int g0, int per, int64_t k, int b, int G) {
-    int row_max = kExpAllZero;
+// A workgroup covers 16 rows.  The loads of all its blocks are in flight together.
+template <int PER>
+__device__ __forceinline__ void scan_k(const ScanSide& s, int64_t rb, int g0, int64_t k, int b, int G) {
     const int q = threadIdx.x & 15;
     const int64_t r = rb * 16 + (threadIdx.x >> 4);
-    int bad = 0;
-    for (int g = g0; g < min(G, g0 + per); ++g) {
-        BlockStat st;
-        st.reset();
-        if (r < s.o.rows) {
-            const int64_t l0 = int64_t(g) * b;
-            const int64_t l1 = min(k, l0 + b);
-            const uint64_t* src = reinterpret_cast<const uint64_t*>(s.o.X) + r * s.o.stride_r;
-#pragma unroll 4
-            for (int64_t l = l0 + q; l < l1; l += 16) st.add(src[l], bad);
-        }
+    BlockStat st[PER];
 #pragma unroll
-        for (int off = 8; off >= 1; off >>= 1) {
-            st.mx = max(st.mx, __shfl_xor(st.mx, off));
-            st.mn = min(st.mn, __shfl_xor(st.mn, off));
-            st.any_nz |= __shfl_xor(st.any_nz, off);
-            st.any_zero |= __shfl_xor(st.any_zero, off);
-        }
-        if (q == 0) {
-            scan_store(s, G, g, r, st.table_max(), st.table_min());
-            row_max = max(row_max, int(st.table_max()));
+    for (int u = 0; u < PER; ++u) st[u].reset();
+    if (r < s.o.rows) {
+        const uint64_t* src = reinterpret_cast<const uint64_t*>(s.o.X) + r * s.o.stride_r;
+        for (int l = q; l < b; l += 64) {
+            uint64_t x[PER][4];
+#pragma unroll
+            for (int u = 0; u < PER; ++u)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    // past the end of a block its last entry is read again, past the last block that block
+                    const int64_t l0 = int64_t(min(g0 + u, G - 1)) * b;
+                    x[u][i] = src[l0 + min(int64_t(l + 16 * i), min(int64_t(b), k - l0) - 1)];
+                }
+#pragma unroll
+            for (int u = 0; u < PER; ++u) st[u].add(x[u]);
         }
     }
-    if (q == 0 && row_max > kExpAllZero) atomicMax(&s.e_out[r], row_max);
-    return bad;
+    int row_max = kExpAllZero;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        int mx = st[u].max_exp(), mn = st[u].min_exp(), any_zero = st[u].any_zero;
+#pragma unroll
+        for (int off = 8; off >= 1; off >>= 1) {
+            mx = max(mx, __shfl_xor(mx, off));
+            mn = min(mn, __shfl_xor(mn, off));
+            any_zero |= __shfl_xor(any_zero, off);
+        }
+        if (q == 0 && g0 + u < G) {
+            scan_store(s, G, g0 + u, r, table_max(mx), table_min(mx, mn, any_zero));
+            row_max = max(row_max, table_max(mx));
+        }
+    }
+    if (q == 0) s.group_max[int64_t(g0 / PER) * s.o.rows_p + r] = int16_t(row_max);
 }
 
 // Both operands in one launch: the first blocks_a workgroups scan op(A), the others op(B), from ESC block g_first on.
 __global__ __launch_bounds__(256) void scan_kernel(ScanSide a, ScanSide b, int64_t blocks_a, int g_first, int per, int64_t k,
-                                                   int bl, int G, Record* rec, int check) {
+                                                   int bl, int G, Record* rec) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) rec->infnan = 0;        // the exponents tell (exponents_kernel)
     const bool second = int64_t(blockIdx.x) >= blocks_a;
     const ScanSide& s = second ? b : a;
     const int64_t id = int64_t(blockIdx.x) - (second ? blocks_a : 0);
     const int64_t rb = id % s.row_blocks;
     const int g0 = g_first + int(id / s.row_blocks) * per;
-    const int bad = s.o.stride_r == 1 ? scan_rows(s, rb, g0, per, k, bl, G) : scan_k(s, rb, g0, per, k, bl, G);
-    if (check && bad) atomicOr(&rec->infnan, 1);
+    if (s.o.stride_r == 1) scan_rows(s, rb, g0, per, k, bl, G);
+    else if (per == 1) scan_k<1>(s, rb, g0, k, bl, G);
+    else scan_k<kScanBlocksPerWg>(s, rb, g0, k, bl, G);
 }
 
-void launch_init(hipStream_t st, const Workspace& w, const Problem& p, const KnownRecord& known) {
-    const int64_t tiles = (p.mp / kTile) * (p.np / kTile);
-    int64_t nmax = p.mp > p.np ? p.mp : p.np;
-    if (tiles > nmax) nmax = tiles;
-    hipLaunchKernelGGL(init_kernel, dim3(unsigned((nmax + 255) / 256)), dim3(256), 0, st, w.rec, w.eA, p.mp, w.eB, p.np,
-                       w.tile_span, tiles, known);
-}
-
-void launch_scan(hipStream_t st, const Operand& a, const Operand& b, const Workspace& w, const Problem& p, bool check_infnan) {
+void launch_scan(hipStream_t st, const Operand& a, const Operand& b, const Workspace& w, const Problem& p) {
     const ScanGrid g = scan_grid(p, a.stride_r == 1, b.stride_r == 1);
-    const ScanSide sa{a, w.U, 1, w.eA, g.row_blocks_a}, sb{b, w.V, 0, w.eB, g.row_blocks_b};
+    const ScanSide sa{a, w.U, 1, w.group_max_a(), g.row_blocks_a}, sb{b, w.V, 0, w.group_max_b(), g.row_blocks_b};
     for (int64_t y = 0; y < g.groups; y += g.slab) {
         const int64_t gy = g.groups - y < g.slab ? g.groups - y : g.slab;
         hipLaunchKernelGGL(scan_kernel, dim3(unsigned((g.row_blocks_a + g.row_blocks_b) * gy)), dim3(256), 0, st, sa, sb,
-                           g.row_blocks_a * gy, int(y) * g.per, g.per, p.k, p.esc_block, p.G, w.rec, int(check_infnan));
+                           g.row_blocks_a * gy, int(y) * g.per, g.per, p.k, p.esc_block, p.G, w.rec);
     }
 }
 
