@@ -185,9 +185,10 @@ oz_status_t oz_dgemm_static(oz_handle_t handle, void* stream, char transa, char 
  * differ inside a batch (the paper's application runs show a distribution of slice counts over
  * the GEMMs of one factorisation: section "Application-Level Integration").
  * Concurrency follows the workspace: with room for q >= 2 times oz_dgemm_workspace_bytes(...)
- * (each rounded up to 256 bytes) the problems run q at a time, q <= OZ_BATCH_LANES, on streams the
- * handle owns, forked from and joined to `stream` with events (so the call still only enqueues,
- * and everything it enqueued is ordered before later work on `stream`); with room for one they
+ * (each rounded up to 256 bytes) the problems run q at a time, q <= OZ_BATCH_LANES: problems that leave much of
+ * the GPU idle share their launches on `stream` (native products of a whole batch where nothing is decided on the
+ * device), larger ones run on streams the handle owns, forked from and joined to `stream` with events (so the call
+ * still only enqueues, and everything it enqueued is ordered before later work on `stream`); with room for one they
  * run one after the other on `stream`.  Stage timing (oz_profile_*) records serial batches only.
  * Two batched calls on one handle must not overlap in time (they share the handle's streams).
  * batch_count == 0 is a no-op; errors are those of oz_dgemm, checked before anything is enqueued. */
@@ -204,13 +205,14 @@ oz_status_t oz_dgemm_strided_batched(oz_handle_t handle, void* stream, char tran
  * extend to ZGEMM via 4M): C = alpha * op(A) * op(B) + beta * C with complex matrices stored
  * interleaved (re, im), column-major, leading dimensions in complex elements; op is 'N', 'T' or
  * 'C' (conjugate transpose).  A and B are split into real and imaginary parts, the four real
- * products  Pr = Ar Br - Ai Bi,  Pi = Ar Bi + Ai Br  run through the emulated DGEMM one after the
- * other on `stream` (each with its own scan, ESC and verdict; the second of each pair accumulates
- * onto the first), and C = alpha (Pr + i Pi) + beta C is formed with every real product and sum
+ * products  Pr = Ar Br - Ai Bi,  Pi = Ar Bi + Ai Br  run through the emulated DGEMM on `stream` (each with its
+ * own scan, ESC and verdict; the second of each pair is added to the first), together where one alone would leave
+ * much of the GPU idle, else one after the other, and C = alpha (Pr + i Pi) + beta C is formed with every real product and sum
  * rounded separately.  alpha, beta: host pointers to (re, im).  C is not read when beta == 0.
  * results: device array of four records (Ar Br, Ai Bi, Ar Bi, Ai Br) or NULL.  workspace as for
- * oz_dgemm, at least oz_zgemm_workspace_bytes(...) (planar copies of A and B, the planar product,
- * one real call's workspace).  k == 0 gives C = beta C.  Errors as oz_dgemm. */
+ * oz_dgemm: oz_zgemm_workspace_bytes(...) has room for what the chosen way needs (planar copies of A and B, the planar
+ * products, the real calls' workspaces); with less, down to one planar product and one real call's workspace
+ * (oz_dgemm_workspace_bytes), they run one after the other.  Stage timing records those only.  k == 0 gives C = beta C.  Errors as oz_dgemm. */
 size_t oz_zgemm_workspace_bytes(oz_handle_t handle, char transa, char transb,
                                 int64_t m, int64_t n, int64_t k, const oz_opts_t* opts);
 oz_status_t oz_zgemm(oz_handle_t handle, void* stream, char transa, char transb,

@@ -20,7 +20,7 @@ struct oz_handle {
     int device;
     int num_cu;
     void* static_ws;      // device address of `scratch` on this handle's device
-    // lanes of oz_dgemm_strided_batched: streams (default priority) and the events that fork them
+    // lanes of oz_dgemm_strided_batched (problems too large to share launches): streams (default priority) and the events that fork them
     // from, and join them to, the caller's stream; created once in oz_create
     hipStream_t lane[OZ_BATCH_LANES];
     hipEvent_t lane_done[OZ_BATCH_LANES];
@@ -66,6 +66,13 @@ bool emulation_slower(const oz_heuristic_t& hm, int S, int64_t m, int64_t n, int
     const int64_t t_emu = hm.fixed_ns + (flops / hm.int8_ops_per_ns) * pairs + stream / hm.bytes_per_ns;
     const int64_t t_f64 = flops / hm.fp64_flops_per_ns;
     return t_emu > t_f64;
+}
+
+// The ESC is at least 1: no input gets fewer slices than this; if even that count is slower than the native GEMM by the cost
+// model, the operands need not be scanned at all.
+bool native_unscanned(const oz_handle& h, const oz_opts_t& o, int64_t m, int64_t n, int64_t k) {
+    if (o.mode != OZ_DYNAMIC || !o.heuristic) return false;
+    return emulation_slower(h.hm, std::min((o.target_bits + 1 + 1 + kHeadroomBits + 7) / 8, kMaxSlices), m, n, k);
 }
 
 // largest slice count a call with these options can select
@@ -357,12 +364,13 @@ namespace {
 oz_status_t dgemm_impl(oz_handle_t h, void* stream, char transa, char transb, int64_t m, int64_t n, int64_t k,
                        double alpha, const double* A, int64_t lda, const double* B, int64_t ldb, double beta,
                        double* C, int64_t ldc, const oz_opts_t* opts, void* workspace, size_t workspace_bytes,
-                       oz_result_t* result, bool timed = true) {
+                       oz_result_t* result, bool timed = true, const Batch& batch = Batch{}) {
     bool ta, tb;
     if (!h || !opts || !parse_trans(transa, ta) || !parse_trans(transb, tb)) return OZ_ERR_ARG;
     if (!valid_opts(*opts)) return OZ_ERR_ARG;
     Problem p;
     if (!make_problem(*h, *opts, m, n, k, p)) return OZ_ERR_ARG;
+    p.batch = batch;
     if (!check_dims(ta, tb, m, n, k, lda, ldb, ldc)) return OZ_ERR_ARG;
     if (m == 0 || n == 0) return OZ_OK;
     if (!C) return OZ_ERR_ARG;
@@ -381,7 +389,7 @@ oz_status_t dgemm_impl(oz_handle_t h, void* stream, char transa, char transb, in
     // what the native GEMM may use for the partial products of a k split: the slice planes, the
     // aggregated products and the raw sums, none of which a call that falls back reads or writes
     void* const f64_scratch = w.As;
-    const size_t f64_scratch_bytes = size_t(reinterpret_cast<uint8_t*>(w.tile_span) - reinterpret_cast<uint8_t*>(w.As));
+    const size_t f64_scratch_bytes = batch.count > batch.lanes ? 0 : size_t(reinterpret_cast<uint8_t*>(w.tile_span) - reinterpret_cast<uint8_t*>(w.As));
 
     if (k == 0 || alpha == 0.0) {
         // BLAS convention: nothing to multiply
@@ -397,22 +405,16 @@ oz_status_t dgemm_impl(oz_handle_t h, void* stream, char transa, char transb, in
 
     if (opts->mode == OZ_NATIVE) {
         for (int s = 0; s <= 5; ++s) clk.done(s);
-        launch_dgemm_f64(st, nullptr, KnownRecord{w.rec, result, known_verdict(p, *opts, 0)}, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, h->num_cu, f64_scratch, f64_scratch_bytes);
+        launch_dgemm_f64(st, nullptr, KnownRecord{w.rec, result, known_verdict(p, *opts, 0)}, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, h->num_cu, batch, f64_scratch, f64_scratch_bytes);
         clk.done(6);
         return hipGetLastError() == hipSuccess ? OZ_OK : OZ_ERR_HIP;
     }
 
-    if (opts->mode == OZ_DYNAMIC && opts->heuristic) {
-        // the ESC is at least 1: no input gets fewer slices than this; if even that count is slower
-        // than the native GEMM by the cost model, the operands need not be scanned at all
-        int s_min = (opts->target_bits + 1 + 1 + kHeadroomBits + 7) / 8;
-        if (s_min > kMaxSlices) s_min = kMaxSlices;
-        if (emulation_slower(h->hm, s_min, m, n, k)) {
-            for (int s = 0; s <= 5; ++s) clk.done(s);
-            launch_dgemm_f64(st, nullptr, KnownRecord{w.rec, result, known_verdict(p, *opts, 3)}, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, h->num_cu, f64_scratch, f64_scratch_bytes);
-            clk.done(6);
-            return hipGetLastError() == hipSuccess ? OZ_OK : OZ_ERR_HIP;
-        }
+    if (native_unscanned(*h, *opts, m, n, k)) {
+        for (int s = 0; s <= 5; ++s) clk.done(s);
+        launch_dgemm_f64(st, nullptr, KnownRecord{w.rec, result, known_verdict(p, *opts, 3)}, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, h->num_cu, batch, f64_scratch, f64_scratch_bytes);
+        clk.done(6);
+        return hipGetLastError() == hipSuccess ? OZ_OK : OZ_ERR_HIP;
     }
 
     const bool guarded = opts->mode != OZ_FIXED_UNGUARDED;
@@ -429,7 +431,7 @@ oz_status_t dgemm_impl(oz_handle_t h, void* stream, char transa, char transb, in
     clk.done(4);
     if (split.kind != KSplit::kDone) launch_recompose(st, w, p, split, alpha, beta, C, ldc);
     clk.done(5);
-    if (guarded) launch_dgemm_f64(st, w.rec, KnownRecord{}, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, h->num_cu, f64_scratch, f64_scratch_bytes);
+    if (guarded) launch_dgemm_f64(st, w.rec, KnownRecord{}, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, h->num_cu, batch, f64_scratch, f64_scratch_bytes);
     clk.done(6);
     return hipGetLastError() == hipSuccess ? OZ_OK : OZ_ERR_HIP;
 }
@@ -469,11 +471,24 @@ bool parse_ztrans(char c, bool& t, bool& conj) {
 struct ZLayout {
     size_t off_ar, off_ai, off_br, off_bi, off_pr, off_pi, off_ws, total;
     size_t real_ws;
+    int workspaces;
 };
 
-// planar copies of the stored A and B, the planar product, then the workspace of one real call
-// (the four real products run one after the other and share it)
-bool make_zlayout(oz_handle_t h, char ta_real, char tb_real, int64_t m, int64_t n, int64_t k, const oz_opts_t* opts,
+// Whether the four real products share their launches: each alone would leave much of the chip idle.  They need planes for four
+// products then and, emulated, a workspace each; 256 MiB bounds what that adds.  workspaces: how many.
+bool zgemm_shares(const oz_handle& h, const oz_opts_t& o, int64_t m, int64_t n, int64_t k, size_t real_ws, int& workspaces) {
+    workspaces = 1;
+    Problem p;
+    if (k == 0 || m == 0 || n == 0 || !make_problem(h, o, m, n, k, p)) return false;
+    if (o.mode == OZ_NATIVE || native_unscanned(h, o, m, n, k)) return ((m + 127) / 128) * ((n + 127) / 128) < h.num_cu;
+    workspaces = 4;
+    p.batch.count = 4;
+    return real_ws <= (size_t(256) << 20) && can_batch(p);
+}
+
+// Planar copies of the stored A and B, the planar product, then the workspace of one real call (the four real products run
+// one after the other and share it).  four: planes for the four real products instead, and their workspaces.
+bool make_zlayout(oz_handle_t h, char ta_real, char tb_real, int64_t m, int64_t n, int64_t k, const oz_opts_t* opts, bool four,
                   ZLayout& z) {
     const size_t real_ws = oz_dgemm_workspace_bytes(h, ta_real, tb_real, m, n, k, opts);
     if (real_ws == 0 && m > 0 && n > 0) return false;
@@ -484,8 +499,12 @@ bool make_zlayout(oz_handle_t h, char ta_real, char tb_real, int64_t m, int64_t 
     z.off_br = off; off += b;
     z.off_bi = off; off += b;
     z.off_pr = off; off += p;
+    if (four) off += p;                  // Ar Br, Ai Bi, Ar Bi, Ai Br
     z.off_pi = off; off += p;
-    z.off_ws = off; off += align_up(real_ws);
+    if (four) off += p;
+    z.workspaces = 1;
+    if (four && !zgemm_shares(*h, *opts, m, n, k, real_ws, z.workspaces)) return false;
+    z.off_ws = off; off += align_up(real_ws) * size_t(z.workspaces);
     z.real_ws = real_ws;
     z.total = off;
     return true;
@@ -498,7 +517,8 @@ size_t oz_zgemm_workspace_bytes(oz_handle_t h, char transa, char transb, int64_t
     bool ta, tb, ca, cb;
     if (!h || !opts || !parse_ztrans(transa, ta, ca) || !parse_ztrans(transb, tb, cb)) return 0;
     ZLayout z;
-    if (!make_zlayout(h, ta ? 'T' : 'N', tb ? 'T' : 'N', m, n, k, opts, z)) return 0;
+    if (make_zlayout(h, ta ? 'T' : 'N', tb ? 'T' : 'N', m, n, k, opts, true, z)) return z.total;
+    if (!make_zlayout(h, ta ? 'T' : 'N', tb ? 'T' : 'N', m, n, k, opts, false, z)) return 0;
     return z.total;
 }
 
@@ -514,7 +534,8 @@ oz_status_t oz_zgemm(oz_handle_t h, void* stream, char transa, char transb, int6
     if (!C || (k > 0 && (!A || !B))) return OZ_ERR_ARG;
     const char tra = ta ? 'T' : 'N', trb = tb ? 'T' : 'N';
     ZLayout z;
-    if (!make_zlayout(h, tra, trb, m, n, k, opts, z)) return OZ_ERR_ARG;
+    const bool four = workspace && h->prof_calls == 0 && make_zlayout(h, tra, trb, m, n, k, opts, true, z) && workspace_bytes >= z.total;
+    if (!four && !make_zlayout(h, tra, trb, m, n, k, opts, false, z)) return OZ_ERR_ARG;
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) % kAlign) != 0 || workspace_bytes < z.total)
         return OZ_ERR_WORKSPACE;
     if (!on_handle_device(*h)) return OZ_ERR_DEVICE;
@@ -531,6 +552,22 @@ oz_status_t oz_zgemm(oz_handle_t h, void* stream, char transa, char transb, int6
     launch_zsplit(st, A, lda, a_rows, a_cols, Ar, Ai, ca);
     launch_zsplit(st, B, ldb, b_rows, b_cols, Br, Bi, cb);
     const int64_t pa = a_rows > 1 ? a_rows : 1, pb = b_rows > 1 ? b_rows : 1, pm = m;
+    const int64_t plane = int64_t(align_up(size_t(m) * n * 8)) / 8;
+    if (four) {
+        Batch bt;
+        bt.count = 4;
+        bt.four = 1;
+        bt.lanes = z.workspaces;
+        bt.ws = int64_t(align_up(z.real_ws));
+        bt.a = Ai - Ar;
+        bt.b = Bi - Br;
+        bt.c = plane;
+        const oz_status_t s = dgemm_impl(h, stream, tra, trb, m, n, k, 1.0, Ar, pa, Br, pb, 0.0, Pr, pm, opts, w + z.off_ws, z.real_ws,
+                                         results, /*timed=*/false, bt);
+        if (s != OZ_OK) return s;
+        launch_zcombine(st, Pr, Pi, plane, m, n, alpha[0], alpha[1], beta[0], beta[1], C, ldc);
+        return hipGetLastError() == hipSuccess ? OZ_OK : OZ_ERR_HIP;
+    }
     struct Call { const double* a; const double* b; double alpha, beta; double* c; };
     const Call calls[4] = {{Ar, Br, 1.0, 0.0, Pr}, {Ai, Bi, -1.0, 1.0, Pr}, {Ar, Bi, 1.0, 0.0, Pi}, {Ai, Br, 1.0, 1.0, Pi}};
     for (int c = 0; c < 4; ++c) {
@@ -539,7 +576,7 @@ oz_status_t oz_zgemm(oz_handle_t h, void* stream, char transa, char transb, int6
                                          results ? results + c : nullptr);
         if (s != OZ_OK) return s;
     }
-    launch_zcombine(st, Pr, Pi, m, n, alpha[0], alpha[1], beta[0], beta[1], C, ldc);
+    launch_zcombine(st, Pr, Pi, 0, m, n, alpha[0], alpha[1], beta[0], beta[1], C, ldc);
     return hipGetLastError() == hipSuccess ? OZ_OK : OZ_ERR_HIP;
 }
 
@@ -567,6 +604,34 @@ oz_status_t oz_dgemm_strided_batched(oz_handle_t h, void* stream, char transa, c
         lanes = int(fit < size_t(OZ_BATCH_LANES) ? fit : size_t(OZ_BATCH_LANES));
         if (int64_t(lanes) > batch_count) lanes = int(batch_count);
         if (lanes < 1) lanes = 1;
+    }
+    // Problems that are small enough share their launches, as many as there are workspaces; native products that nothing is
+    // decided about on the device need none, only the k split does (not where there are 32 x 32 tiles for all CUs without).
+    if (lanes > 1 && k > 0 && alpha != 0.0) {
+        Problem p;
+        if (!make_problem(*h, *opts, m, n, k, p)) return OZ_ERR_ARG;
+        const bool native = opts->mode == OZ_NATIVE || native_unscanned(*h, *opts, m, n, k);
+        int64_t group = lanes;
+        if (native && ((m + 31) / 32) * ((n + 31) / 32) * batch_count >= h->num_cu) group = std::min<int64_t>(batch_count, 4096);
+        p.batch.count = int(std::min<int64_t>(group, batch_count));
+        if (native || can_batch(p)) {
+            oz_status_t status = OZ_OK;
+            for (int64_t b = 0; b < batch_count && status == OZ_OK; b += p.batch.count) {
+                p.batch.count = int(std::min<int64_t>(group, batch_count - b));
+                if (!native && p.batch.count > 1 && !can_batch(p)) p.batch.count = 1;
+                Batch bt;
+                bt.count = p.batch.count;
+                bt.lanes = lanes;
+                bt.ws = int64_t(need);
+                bt.a = stride_a;
+                bt.b = stride_b;
+                bt.c = stride_c;
+                status = dgemm_impl(h, stream, transa, transb, m, n, k, alpha, A ? A + b * stride_a : A, lda, B ? B + b * stride_b : B,
+                                    ldb, beta, C ? C + b * stride_c : C, ldc, opts, workspace, need, results ? results + b : nullptr,
+                                    /*timed=*/false, bt);
+            }
+            return status;
+        }
     }
     hipStream_t user = static_cast<hipStream_t>(stream);
     if (lanes > 1) {

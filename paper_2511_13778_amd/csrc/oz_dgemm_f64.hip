@@ -112,7 +112,7 @@ template <bool A_ROWS_CONTIG, bool B_ROWS_CONTIG, int MODE, int T>
 __global__ __launch_bounds__(256, 2) void dgemm_f64_kernel(
     const Record* rec, KnownRecord known, int64_t m, int64_t n, int64_t k, double alpha, const double* __restrict__ A,
     int64_t a_sr, int64_t a_sl, const double* __restrict__ B, int64_t b_sr, int64_t b_sl, double beta,
-    double* __restrict__ C, int64_t ldc, int ntm, int ntn, int zsplit, int64_t kpart, double* __restrict__ partial) {
+    double* __restrict__ C, int64_t ldc, int ntm, int ntn, int zsplit, int64_t kpart, double* __restrict__ partial, Batch bt) {
     constexpr bool EDGE = MODE == 2;                       // bounds-checked loads in the K loop
     constexpr bool RAGGED = MODE != 0;                     // bounds-checked stores of C
     constexpr bool A_PER_Q = MODE == 1 && !A_ROWS_CONTIG, B_PER_Q = MODE == 1 && !B_ROWS_CONTIG;
@@ -122,8 +122,9 @@ __global__ __launch_bounds__(256, 2) void dgemm_f64_kernel(
     constexpr int EPT = T / 16;          // elements per thread, operand and K step
     __shared__ double At[2][kDK * kDLd];
     __shared__ double Bt[2][kDK * kDLd];
+    f64_problem(bt, rec, A, B, C, partial);
     if (rec && !rec->res.fallback) return;
-    if (blockIdx.x == 0 && threadIdx.x == 0) write_known_record(known);
+    if (blockIdx.x == 0 && threadIdx.x == 0) write_known_record(known, bt, int(blockIdx.z));
 
     int ti, tj, z;
     f64_tile_of(int(blockIdx.x), ntm, ntn, zsplit, ti, tj, z);
@@ -280,7 +281,10 @@ __global__ __launch_bounds__(256, 2) void dgemm_f64_kernel(
 __global__ __launch_bounds__(256) void dgemm_f64_reduce_kernel(const Record* rec, int64_t m, int64_t n, double alpha,
                                                                double beta, double* __restrict__ C, int64_t ldc, int zsplit,
                                                                const double* __restrict__ partial, int64_t ldp,
-                                                               int64_t part_stride, int64_t j_first) {
+                                                               int64_t part_stride, int64_t j_first, Batch bt) {
+    if (rec) rec = at_bytes(rec, bt.ws_at(blockIdx.z));
+    partial = at_bytes(partial, bt.ws_at(blockIdx.z));
+    C += blockIdx.z * bt.c;
     if (rec && !rec->res.fallback) return;
     const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
     const int64_t j = j_first + blockIdx.y;
@@ -321,22 +325,23 @@ constexpr double kF64CacheBytesPerUs = 9e6;
 F64Plan choose_f64(const F64Call& c, int num_cu, void* scratch, size_t scratch_bytes) {
     F64Plan best{};
     double best_us = 0.0;
-    const uint32_t m = uint32_t(c.m), n = uint32_t(c.n), cus = uint32_t(num_cu);
+    const uint32_t m = uint32_t(c.m), n = uint32_t(c.n), cus = uint32_t(num_cu), problems = uint32_t(c.batch.count);
     for (const F64Tile& t : kF64Tiles) {
         if (!t.direct && c.k < kDK) continue;                // whose fast loads always fetch a full K step
         const uint32_t ti = uint32_t(t.ti), tj = uint32_t(t.tj), ntm = (m + ti - 1) / ti, ntn = (n + tj - 1) / tj;
         const uint64_t tiles64 = uint64_t(ntm) * ntn;
         if (tiles64 > uint64_t(kMaxGridThreads) / 256) continue;
-        const uint32_t tiles = uint32_t(tiles64);
-        const double cache_us = double(tiles) * double(ti + tj) * double(c.k) * 8.0 / kF64CacheBytesPerUs;
+        const uint32_t tiles = uint32_t(tiles64);            // of a problem
+        const uint64_t all = tiles64 * problems;
+        const double cache_us = double(all) * double(ti + tj) * double(c.k) * 8.0 / kF64CacheBytesPerUs;
         const int64_t k_least = t.ti == 128 ? 256 : 64;      // what a part keeps at least
         for (uint32_t z : {1u, 2u, 3u, 4u, 6u, 8u, 12u, 16u}) {
-            if (z > 1 && (scratch == nullptr || c.k < k_least * z || tiles * z > 4 * cus ||
+            if (z > 1 && (scratch == nullptr || c.k < k_least * z || all * z > 4 * cus ||
                           uint64_t(tiles) * z * ti * tj * 8 > scratch_bytes))
                 break;
-            const double rounds = double((tiles * z + cus - 1) / cus), steps = double(uint32_t(c.k + z * kDK - 1) / (z * kDK));
+            const double rounds = double((all * z + cus - 1) / cus), steps = double(uint32_t(c.k + z * kDK - 1) / (z * kDK));
             double us = std::max(t.start + rounds * (t.round + t.step * steps) + t.first * steps, cache_us);
-            if (z > 1) us += (c.rec ? 20.0 : 4.5) + double(z + 2) * double(m) * double(n) * 8.0 / 4.5e6;
+            if (z > 1) us += (c.rec ? 20.0 : 4.5) + double(z + 2) * double(m) * double(n) * double(problems) * 8.0 / 4.5e6;
             if (best_us == 0.0 || us < best_us) {
                 best_us = us;
                 best = F64Plan{t.direct, t.ti, t.tj, int(ntm), int(ntn), int(z), z > 1 ? c.k / z / kDK * kDK : 0,
@@ -351,10 +356,10 @@ F64Plan choose_f64(const F64Call& c, int num_cu, void* scratch, size_t scratch_b
 
 void launch_dgemm_f64(hipStream_t st, const Record* rec, const KnownRecord& known, bool ta, bool tb, int64_t m, int64_t n, int64_t k,
                       double alpha, const double* A, int64_t lda, const double* B, int64_t ldb, double beta,
-                      double* C, int64_t ldc, int num_cu, void* scratch, size_t scratch_bytes) {
+                      double* C, int64_t ldc, int num_cu, const Batch& batch, void* scratch, size_t scratch_bytes) {
     // op(A)(i,l): N -> A[i + l*lda] (rows contiguous), T -> A[l + i*lda]
     // op(B)(l,j): N -> B[l + j*ldb] (k contiguous),    T -> B[j + l*ldb] (rows contiguous)
-    const F64Call c{rec, known, m, n, k, alpha, A, ta ? lda : 1, ta ? 1 : lda, B, tb ? 1 : ldb, tb ? ldb : 1, beta, C, ldc, !ta, tb};
+    const F64Call c{rec, known, m, n, k, alpha, A, ta ? lda : 1, ta ? 1 : lda, B, tb ? 1 : ldb, tb ? ldb : 1, beta, C, ldc, !ta, tb, batch};
     // the fast loads keep every offset inside a K step of a tile in 32 bits (a lane's own: at most
     // 15 leading dimensions plus a row of the tile; its elements: up to 7 x 16 leading dimensions
     // further on; in bytes); operands cut out of a very large parent matrix take the bounds-checked
@@ -373,11 +378,11 @@ void launch_dgemm_f64(hipStream_t st, const Record* rec, const KnownRecord& know
         launch_dgemm_f64_direct(st, c, p);
     } else {
         const bool ac = c.a_rows, bc = c.b_rows;
-        const dim3 grid(unsigned(p.ntm) * unsigned(p.ntn) * unsigned(p.zsplit)), block(256);
+        const dim3 grid(unsigned(p.ntm) * unsigned(p.ntn) * unsigned(p.zsplit), 1, unsigned(batch.count)), block(256);
         const int mode = wide ? 2 : (((m % p.ti) || (n % p.tj) || (k % kDK)) ? 1 : 0);
 #define OZ_DG_M(AC, BC, MODE, TT)                                                                              \
     hipLaunchKernelGGL((dgemm_f64_kernel<AC, BC, MODE, TT>), grid, block, 0, st, rec, known, m, n, k, alpha, A, c.a_sr, \
-                       c.a_sl, B, c.b_sr, c.b_sl, beta, C, ldc, p.ntm, p.ntn, p.zsplit, p.kpart, p.partial)
+                       c.a_sl, B, c.b_sr, c.b_sl, beta, C, ldc, p.ntm, p.ntn, p.zsplit, p.kpart, p.partial, batch)
 #define OZ_DG_T(AC, BC, TT)                                                                                    \
     {                                                                                                          \
         if (mode == 2) OZ_DG_M(AC, BC, 2, TT);                                                                 \
@@ -400,9 +405,9 @@ void launch_dgemm_f64(hipStream_t st, const Record* rec, const KnownRecord& know
         const unsigned gx = unsigned((m + 255) / 256);
         const int64_t ldp = int64_t(p.ntm) * p.ti, part_stride = ldp * p.ntn * p.tj;
         for (int64_t j = 0; j < n; j += 65535) {
-            const dim3 rgrid(gx, unsigned(n - j < 65535 ? n - j : 65535));
+            const dim3 rgrid(gx, unsigned(n - j < 65535 ? n - j : 65535), unsigned(batch.count));
             hipLaunchKernelGGL(dgemm_f64_reduce_kernel, rgrid, dim3(256), 0, st, rec, m, n, alpha, beta, C, ldc, p.zsplit,
-                               p.partial, ldp, part_stride, j);
+                               p.partial, ldp, part_stride, j, batch);
         }
     }
 }

@@ -77,12 +77,13 @@ template <bool AC, bool BC, int NI, int NJ>
 __global__ __launch_bounds__(256, NI * NJ <= 4 ? 4 : 2) void dgemm_f64_direct_kernel(
     const Record* rec, KnownRecord known, int64_t m, int64_t n, int64_t k, double alpha, const double* __restrict__ A,
     int64_t a_sr, int64_t a_sl, const double* __restrict__ B, int64_t b_sr, int64_t b_sl, double beta,
-    double* __restrict__ C, int64_t ldc, int ntm, int ntn, int zsplit, int64_t kpart, double* __restrict__ partial) {
+    double* __restrict__ C, int64_t ldc, int ntm, int ntn, int zsplit, int64_t kpart, double* __restrict__ partial, Batch bt) {
     constexpr int TI = 16 * NI, TJ = 16 * NJ, NF = NI * NJ, NQ = (NF + 3) / 4;
     constexpr int kPerBatch = kSumBatch / 4;
     __shared__ double sums[3 * (NF < kSumBatch ? NQ * 4 : kSumBatch) * 4 * 64];
+    f64_problem(bt, rec, A, B, C, partial);
     if (rec && !rec->res.fallback) return;
-    if (blockIdx.x == 0 && threadIdx.x == 0) write_known_record(known);
+    if (blockIdx.x == 0 && threadIdx.x == 0) write_known_record(known, bt, int(blockIdx.z));
     int ti, tj, z;
     f64_tile_of(int(blockIdx.x), ntm, ntn, zsplit, ti, tj, z);
     const int64_t i0 = int64_t(ti) * TI, j0 = int64_t(tj) * TJ;
@@ -182,11 +183,11 @@ __global__ __launch_bounds__(256, NI * NJ <= 4 ? 4 : 2) void dgemm_f64_direct_ke
 }
 
 void launch_dgemm_f64_direct(hipStream_t st, const F64Call& c, const F64Plan& p) {
-    const dim3 grid(unsigned(p.ntm) * unsigned(p.ntn) * unsigned(p.zsplit)), block(256);
+    const dim3 grid(unsigned(p.ntm) * unsigned(p.ntn) * unsigned(p.zsplit), 1, unsigned(c.batch.count)), block(256);
 #define OZ_DIRECT(AC, BC, NI, NJ)                                                                                        \
     hipLaunchKernelGGL((dgemm_f64_direct_kernel<AC, BC, NI, NJ>), grid, block, 0, st, c.rec, c.known, c.m, c.n, c.k,      \
                        c.alpha, c.A, c.a_sr, c.a_sl, c.B, c.b_sr, c.b_sl, c.beta, c.C, c.ldc, p.ntm, p.ntn, p.zsplit, \
-                       p.kpart, p.partial)
+                       p.kpart, p.partial, c.batch)
 #define OZ_DIRECT_T(NI, NJ)                                                                                              \
     if (p.ti == 16 * NI && p.tj == 16 * NJ) {                                                                              \
         if (c.a_rows && c.b_rows) OZ_DIRECT(true, true, NI, NJ);                                                           \

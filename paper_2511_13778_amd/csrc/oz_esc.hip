@@ -57,10 +57,17 @@ constexpr int kExpWaves = 16;
 // Bound by latency (8192^3: 7.6 us, where clearing and encoding took 5 + 8 in launches of their own).
 __global__ __launch_bounds__(kExpRows * kExpWaves) void exponents_kernel(ExponentSide a, ExponentSide b, int blocks_a, int groups, int H2,
                                                                          int chunks, Record* rec, int32_t* __restrict__ tile_span,
-                                                                         int64_t tiles, KnownRecord known) {
+                                                                         int64_t tiles, KnownRecord known, Batch bt) {
     __shared__ int part[kExpWaves][kExpRows];
     const bool second = int(blockIdx.x) >= blocks_a;
-    const ExponentSide& s = second ? b : a;
+    const int64_t ws = bt.ws_at(blockIdx.z);
+    ExponentSide s = second ? b : a;
+    s.group_max = at_bytes(s.group_max, ws);
+    s.e = at_bytes(s.e, ws);
+    s.tab = at_bytes(s.tab, ws);
+    s.enc = at_bytes(s.enc, ws);
+    rec = at_bytes(rec, ws);
+    tile_span = at_bytes(tile_span, ws);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t r = int64_t(int(blockIdx.x) - (second ? blocks_a : 0)) * kExpRows + lane;
     int e = kExpAllZero;
@@ -71,7 +78,7 @@ __global__ __launch_bounds__(kExpRows * kExpWaves) void exponents_kernel(Exponen
         if (threadIdx.x == 0) {
             rec->span_max = 0;
             rec->esc_done = 0;
-            write_known_record(known);
+            write_known_record(known, bt, int(blockIdx.z));
         }
         if (threadIdx.x < 8) rec->tile_sync[threadIdx.x] = 0;
     }
@@ -427,9 +434,18 @@ __global__ __launch_bounds__(256) void esc_kernel(const uint4* __restrict__ EU, 
                                                   const int16_t* __restrict__ U, const int16_t* __restrict__ V,
                                                   const int32_t* __restrict__ eA, const int32_t* __restrict__ eB, int64_t m,
                                                   int64_t n, int64_t k, int64_t mp, int64_t np, int H2, int steps, Record* rec,
-                                                  int32_t* __restrict__ tile_span, VerdictArgs v) {
+                                                  int32_t* __restrict__ tile_span, VerdictArgs v, Batch bt) {
     __shared__ EscLds lds;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    {
+        const int64_t ws = bt.ws_at(blockIdx.z);
+        EU = at_bytes(EU, ws); EV = at_bytes(EV, ws);
+        U = at_bytes(U, ws); V = at_bytes(V, ws);
+        eA = at_bytes(eA, ws); eB = at_bytes(eB, ws);
+        rec = at_bytes(rec, ws);
+        tile_span = at_bytes(tile_span, ws);
+        v.tile_S = at_bytes(v.tile_S, ws);
+    }
     const int infnan = rec->infnan;
     if (infnan) {
         // the native path is decided: one workgroup says so, no span is needed
@@ -509,7 +525,7 @@ __global__ __launch_bounds__(256) void esc_kernel(const uint4* __restrict__ EU, 
         }
         const oz_result_t r = verdict(v, infnan, read(&rec->span_max), pairs, smin, m, n, k);
         rec->res = r;
-        if (v.user) *v.user = r;
+        if (v.user) v.user[blockIdx.z] = r;
         lds.stop = r.fallback;
     }
     __threadfence_block();
@@ -519,7 +535,7 @@ __global__ __launch_bounds__(256) void esc_kernel(const uint4* __restrict__ EU, 
 }
 
 __global__ void known_record_kernel(KnownRecord known) {
-    if (threadIdx.x == 0) write_known_record(known);
+    if (threadIdx.x == 0) write_known_record(known, Batch{}, 0);
 }
 
 oz_result_t known_verdict(const Problem& p, const oz_opts_t& o, int kind) {
@@ -550,11 +566,11 @@ void launch_exponents(hipStream_t st, const Operand& a, const Operand& b, const 
     const int chunks = encode ? (H2 + 2 * kEncChunk - 1) / (2 * kEncChunk) * 4 : 0;
     const int blocks_a = int(p.mp / kExpRows), blocks = int((p.mp + p.np) / kExpRows);
     // several workgroups per row block while the CUs are not filled and each still has a chunk for every wave
-    const int y = std::max(1, std::min((p.num_cu + blocks - 1) / blocks, chunks / kExpWaves));
+    const int y = std::max(1, std::min((p.num_cu + blocks * p.batch.count - 1) / (blocks * p.batch.count), chunks / kExpWaves));
     const ExponentSide sa{w.group_max_a(), w.eA, w.U, reinterpret_cast<uint4*>(w.EU), p.mp};
     const ExponentSide sb{w.group_max_b(), w.eB, w.V, reinterpret_cast<uint4*>(w.EV), p.np};
-    hipLaunchKernelGGL(exponents_kernel, dim3(unsigned(blocks), unsigned(y)), dim3(kExpRows * kExpWaves), 0, st, sa, sb, blocks_a,
-                       int(g.groups), H2, chunks, w.rec, w.tile_span, (p.mp / kTile) * (p.np / kTile), known);
+    hipLaunchKernelGGL(exponents_kernel, dim3(unsigned(blocks), unsigned(y), unsigned(p.batch.count)), dim3(kExpRows * kExpWaves), 0, st, sa, sb, blocks_a,
+                       int(g.groups), H2, chunks, w.rec, w.tile_span, (p.mp / kTile) * (p.np / kTile), known, p.batch);
 }
 
 void launch_esc_verdict(hipStream_t st, const Workspace& w, const Problem& p, const oz_opts_t& o, const oz_heuristic_t& hm,
@@ -566,8 +582,8 @@ void launch_esc_verdict(hipStream_t st, const Workspace& w, const Problem& p, co
     VerdictArgs v = {o, hm, p.s_cap, p.tile_mode, int(p.mp / kTile), int(p.np / kTile), 0, 0, w.tile_S, user_result};
     if (p.tile_mode) tile_order_shape(p, v.first, v.deal);
     const int64_t blocks = (p.mp / kEscTile) * (p.np / kEscTile);
-    hipLaunchKernelGGL(esc_kernel, dim3(unsigned(std::min<int64_t>(blocks, 2 * int64_t(p.num_cu)))), dim3(256), 0, st, EU, EV, w.U,
-                       w.V, w.eA, w.eB, p.m, p.n, p.k, p.mp, p.np, H2, steps, w.rec, w.tile_span, v);
+    hipLaunchKernelGGL(esc_kernel, dim3(unsigned(std::min<int64_t>(blocks, std::max(1, 2 * p.num_cu / p.batch.count))), 1, unsigned(p.batch.count)), dim3(256), 0, st, EU, EV, w.U,
+                       w.V, w.eA, w.eB, p.m, p.n, p.k, p.mp, p.np, H2, steps, w.rec, w.tile_span, v, p.batch);
 }
 
 }  // namespace oz

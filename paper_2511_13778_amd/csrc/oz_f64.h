@@ -18,6 +18,7 @@ struct F64Call {
     double* C;
     int64_t ldc;
     bool a_rows, b_rows;   // rows (not k) contiguous
+    Batch batch;
 };
 
 struct F64Plan {
@@ -56,6 +57,18 @@ __device__ __forceinline__ void f64_k_part(int zsplit, int z, int64_t kpart, int
         kb = z == 0 ? 0 : k0 + int64_t(z - 1) * kpart;
         k = z == 0 ? k0 : kpart;
     }
+}
+
+// problem p = blockIdx.z of a batch
+template <class Rec, class In, class Out>
+__device__ __forceinline__ void f64_problem(const Batch& bt, Rec& rec, In& A, In& B, Out& C, Out& partial) {
+    const int p = int(blockIdx.z);
+    const int64_t ws = bt.ws_at(p);        // not used by problems beyond the workspaces: no verdict to read, no partial products
+    if (rec) rec = at_bytes(rec, ws);
+    A += bt.a_at(p);
+    B += bt.b_at(p);
+    C += p * bt.c;
+    partial = at_bytes(partial, ws);
 }
 
 void launch_dgemm_f64_direct(hipStream_t st, const F64Call& c, const F64Plan& p);

@@ -110,11 +110,10 @@ constexpr int kPieces<8>[kOwnPieces + 8] = {0, 1, 2, 20, 3, 10, 11, 21, 12, 13, 
 // unit); the stream of tiles runs on into the next unit, so neither the first tiles' latency nor the drain
 // of the last sums is waited for.
 template <bool ATOMIC>
-__global__ __launch_bounds__(256) void gemm_i8_kernel(const int8_t* __restrict__ As, const int8_t* __restrict__ Bs,
-                                                      int32_t* __restrict__ T, int8_t* __restrict__ L,
-                                                      int32_t* __restrict__ raw, int raw_units, int64_t mp, int64_t np,
-                                                      int64_t kp, int s_cap, Record* rec, GemmGrid g,
-                                                      const int32_t* __restrict__ tile_S) {
+__device__ __forceinline__ void gemm_i8_body(const int8_t* __restrict__ As, const int8_t* __restrict__ Bs, int32_t* __restrict__ T,
+                                             int8_t* __restrict__ L, int32_t* __restrict__ raw, int raw_units, int64_t mp,
+                                             int64_t np, int64_t kp, int s_cap, Record* rec, const GemmGrid& g,
+                                             const int32_t* __restrict__ tile_S) {
     constexpr int D = ATOMIC ? kDiagAtomic : kDiag;
     constexpr int TAIL = D - 1;          // last steps of a 64 of k: D-1 .. 1 accumulator sets
     extern __shared__ __align__(16) uint8_t lds[];
@@ -613,6 +612,26 @@ __global__ __launch_bounds__(256) void gemm_i8_kernel(const int8_t* __restrict__
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
+template <bool ATOMIC>
+__global__ __launch_bounds__(256) void gemm_i8_kernel(const int8_t* __restrict__ As, const int8_t* __restrict__ Bs,
+                                                      int32_t* __restrict__ T, int8_t* __restrict__ L,
+                                                      int32_t* __restrict__ raw, int raw_units, int64_t mp, int64_t np,
+                                                      int64_t kp, int s_cap, Record* rec, GemmGrid g,
+                                                      const int32_t* __restrict__ tile_S) {
+    gemm_i8_body<ATOMIC>(As, Bs, T, L, raw, raw_units, mp, np, kp, s_cap, rec, g, tile_S);
+}
+
+// Several problems in one launch.  A kernel of its own: pointers that are computed take scalar registers from the other's steps.
+__global__ __launch_bounds__(256) void gemm_i8_batch_kernel(const int8_t* __restrict__ As, const int8_t* __restrict__ Bs,
+                                                            int32_t* __restrict__ T, int8_t* __restrict__ L,
+                                                            int32_t* __restrict__ raw, int raw_units, int64_t mp, int64_t np,
+                                                            int64_t kp, int s_cap, Record* rec, GemmGrid g,
+                                                            const int32_t* __restrict__ tile_S, Batch bt) {
+    const int64_t ws = bt.ws_at(blockIdx.z);
+    gemm_i8_body<false>(at_bytes(As, ws), at_bytes(Bs, ws), at_bytes(T, ws), at_bytes(L, ws), at_bytes(raw, ws), raw_units, mp, np, kp,
+                        s_cap, at_bytes(rec, ws), g, tile_S ? at_bytes(tile_S, ws) : nullptr);
+}
+
 // raw = 0 on the slots of a launch whose workgroups add their parts of the k range into them.
 // grid (units of the launch, planes); a workgroup clears one 128 x 128 slot of one plane.
 __global__ __launch_bounds__(256) void zero_raw_kernel(int32_t* __restrict__ raw, int raw_units, int s_cap, const Record* rec) {
@@ -716,10 +735,14 @@ void tile_order_shape(const Problem& p, int& first, int& deal) {
     deal = (lp.g.full_chip && lp.full != 0 && lp.positions <= (1 << 16)) ? 1 : 0;
 }
 
+bool can_batch(const Problem& p) { return LaunchPlan(p).can_batch(p); }
+
 bool prepare_gemm_i8() {
     return hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_i8_kernel<false>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds) == hipSuccess &&
            hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_i8_kernel<true>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds) == hipSuccess &&
+           hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_i8_batch_kernel),
                                hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds) == hipSuccess &&
            prepare_gemm_i8_few() && prepare_gemm_small();
 }
@@ -756,6 +779,13 @@ SplitPlan launch_gemm_i8(hipStream_t st, const Workspace& w, const Problem& p, d
     if (lp.two) {
         launch(0, lp.full, Split{1, false});
         return SplitPlan{KSplit::kNone, launch(lp.full, lp.rest, lp.last), lp.raw_units};
+    }
+    if (p.batch.count > 1) {             // can_batch: one launch, no more units than CUs
+        unsigned grid;
+        const GemmGrid g = lp.launch(p, 0, lp.positions, lp.last, grid);
+        hipLaunchKernelGGL(gemm_i8_batch_kernel, dim3(grid, 1, unsigned(p.batch.count)), dim3(256), kGemmLds, st, w.As, w.Bs, w.T, w.L,
+                           w.raw, lp.raw_units, p.mp, p.np, p.kp, p.s_cap, w.rec, g, tile_S, p.batch);
+        return SplitPlan{lp.last.z == 1 ? KSplit::kNone : KSplit::kParts, g, lp.raw_units};
     }
     const GemmGrid g = launch(0, lp.positions, lp.last);
     return SplitPlan{lp.last.z == 1 ? KSplit::kNone : (lp.last.atomic ? KSplit::kAtomic : KSplit::kParts), g, lp.raw_units};

@@ -118,8 +118,9 @@ struct LaunchPlan {
         // Units are dealt in rounds of one per CU.  A call with less than a round may be split along k as a whole;
         // otherwise the full rounds run unsplit and what is left may be split along k in a launch of its own.
         // (Per-block order: a full round of the order table is one block per CU.)
-        const int round = p.num_cu;
-        full = positions / round * round;
+        // Problems that share a launch (p.batch) are counted together; they share one only with less than a round in all.
+        const int round = p.num_cu / p.batch.count;
+        full = round != 0 ? positions / round * round : positions;
         rest = positions - full;
         int64_t last_ns = 0;
         last = rest != 0 && rest * per_pos < round ? split(p, rest * per_pos, last_ns) : Split{1, false};
@@ -128,6 +129,12 @@ struct LaunchPlan {
         small = small_call(p, last_ns);
     }
 
+    // whether the problems of p.batch can share the launches
+    bool can_batch(const Problem& p) const {
+        return small || (!few && int64_t(positions) * per_pos * p.batch.count <= p.num_cu);
+    }
+
+    // tiles of one problem
     int64_t small_tiles(const Problem& p) const {
         return ((p.m + kSmallTile - 1) / kSmallTile) * ((p.n + kSmallTile - 1) / kSmallTile);
     }
@@ -144,12 +151,12 @@ struct LaunchPlan {
     bool small_call(const Problem& p, int64_t last_ns) const {
         if (p.nkb != 1) return false;
         const int64_t S = p.s_min == p.s_cap ? p.s_cap : p.s_min + 1;
-        const int64_t tiles = small_tiles(p);
+        const int64_t tiles = small_tiles(p) * p.batch.count;
         const int64_t one = 8000 + (tiles <= p.num_cu ? kt * (400 + 110 * S)
                                                       : std::max(tiles, int64_t(2) * p.num_cu) * (4000 + kt * (250 + 180 * S)) / (2 * p.num_cu));
-        const int64_t rounds = (int64_t(positions) * per_pos + p.num_cu - 1) / p.num_cu;
+        const int64_t rounds = (int64_t(positions) * per_pos * p.batch.count + p.num_cu - 1) / p.num_cu;
         const int64_t gemm = full == 0 && last.z > 1 ? last_ns + int64_t(500) * last.z : rounds * (int64_t(4200) * kt + 5000);
-        const int64_t two_launches = 10000 + (14000 + p.m * p.n * 55 / 10000 + gemm) * (S + 1) / 8;
+        const int64_t two_launches = 10000 + (14000 + p.m * p.n * p.batch.count * 55 / 10000 + gemm) * (S + 1) / 8;
         return one < two_launches * 95 / 100;
     }
 
@@ -181,16 +188,17 @@ struct LaunchPlan {
     // and part (170 ns) and need the slots zeroed (8 us), but no more memory for more parts.
     Split split(const Problem& p, int units, int64_t& best_ns) const {
         const bool whole = units == positions * per_pos;     // the recomposition puts it together
+        const int64_t all = int64_t(units) * p.batch.count;
         const int64_t raw_bytes = int64_t(p.nkb) * p.s_cap * raw_units * (kUnit * kUnit * 4);
         Split best{1, false};
         best_ns = (int64_t(kt) * 4200 + 5000) * 95 / 100;     // a split has to gain 5 %
-        for (int z = 2; z <= kt && int64_t(units) * z <= p.num_cu; ++z) {
+        for (int z = 2; z <= kt && all * z <= p.num_cu; ++z) {
             const int64_t steps = (kt + z - 1) / z;
             if (int64_t(z - 1) * units * nkb_part(p, z) * part_slot_bytes(p.s_cap) <= raw_bytes) {
-                const int64_t ns = steps * 4200 + 5000 + (whole ? 1000 : 6000) + int64_t(60) * units * z;
+                const int64_t ns = steps * 4200 + 5000 + (whole ? 1000 : 6000) + int64_t(60) * all * z;
                 if (ns < best_ns) { best_ns = ns; best = Split{z, false}; }
             }
-            if (whole) {
+            if (whole && p.batch.count == 1) {
                 const int64_t ns = steps * 4800 + 5000 + 8000 + int64_t(170) * units * z;
                 if (ns < best_ns) { best_ns = ns; best = Split{z, true}; }
             }

@@ -40,8 +40,17 @@ __global__ __launch_bounds__(64 * kSmallWaves, 4) void gemm_small_kernel(
     const int8_t* __restrict__ As, const int8_t* __restrict__ Bs, int32_t* __restrict__ T, int8_t* __restrict__ L,
     const int32_t* __restrict__ eA, const int32_t* __restrict__ eB, int64_t m, int64_t n, int64_t mp, int64_t np, int64_t kp,
     int kt_total, int lds_bytes, double alpha, double beta, double* __restrict__ C, int64_t ldc, const Record* rec,
-    const int32_t* __restrict__ tile_S) {
+    const int32_t* __restrict__ tile_S, Batch bt) {
     extern __shared__ __align__(16) uint8_t lds[];
+    {
+        const int64_t ws = bt.ws_at(blockIdx.z);
+        As = at_bytes(As, ws); Bs = at_bytes(Bs, ws);
+        T = at_bytes(T, ws); L = at_bytes(L, ws);
+        eA = at_bytes(eA, ws); eB = at_bytes(eB, ws);
+        rec = at_bytes(rec, ws);
+        if (tile_S) tile_S = at_bytes(tile_S, ws);
+        C += int64_t(blockIdx.z) * bt.c;
+    }
     if (rec->res.fallback) return;
     const int S_all = rec->res.slices_used;
     const int ntm = int((m + kSmallTile - 1) / kSmallTile);
@@ -229,9 +238,9 @@ void launch_gemm_small(hipStream_t st, const Workspace& w, const Problem& p, con
                        double* C, int64_t ldc) {
     const int64_t tiles = lp.small_tiles(p);
     // two workgroups per CU where there are that many and the largest slice count leaves room for both
-    const int lds = tiles > p.num_cu && p.s_cap * kSumPlane <= kSmallLdsMax / 2 ? kSmallLdsMax / 2 : kSmallLdsMax;
-    hipLaunchKernelGGL(gemm_small_kernel, dim3(unsigned(tiles)), dim3(64 * kSmallWaves), lds, st, w.As, w.Bs, w.T, w.L, w.eA,
-                       w.eB, p.m, p.n, p.mp, p.np, p.kp, lp.kt, lds, alpha, beta, C, ldc, w.rec, p.tile_mode ? w.tile_S : nullptr);
+    const int lds = tiles * p.batch.count > p.num_cu && p.s_cap * kSumPlane <= kSmallLdsMax / 2 ? kSmallLdsMax / 2 : kSmallLdsMax;
+    hipLaunchKernelGGL(gemm_small_kernel, dim3(unsigned(tiles), 1, unsigned(p.batch.count)), dim3(64 * kSmallWaves), lds, st, w.As, w.Bs, w.T, w.L, w.eA,
+                       w.eB, p.m, p.n, p.mp, p.np, p.kp, lp.kt, lds, alpha, beta, C, ldc, w.rec, p.tile_mode ? w.tile_S : nullptr, p.batch);
 }
 
 }  // namespace oz

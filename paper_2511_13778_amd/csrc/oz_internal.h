@@ -51,10 +51,28 @@ struct KnownRecord {
     oz_result_t* user;     // may be nullptr
     oz_result_t value;
 };
-__device__ inline void write_known_record(const KnownRecord& k) {
+
+// Problems of one shape that share every launch of a call: problem p = blockIdx.z finds its workspace p * ws bytes further on, its
+// operands and result p * a, b, c elements.  A chain of dependent launches costs 4 to 5 us a launch, whatever it computes,
+// so several small problems take little more than one.
+struct Batch {
+    int32_t count = 1;
+    int32_t four = 0;      // the four real products of a complex one: A of problem p is number p & 1, B number (p & 1) ^ (p >> 1)
+    int32_t lanes = 1;     // workspaces; only native products without a k split, which need none, may be more
+    int32_t pad_ = 0;
+    int64_t ws = 0, a = 0, b = 0, c = 0;
+    __device__ int64_t ws_at(int p) const { return p * ws; }
+    __device__ int64_t a_at(int p) const { return (four ? p & 1 : p) * a; }
+    __device__ int64_t b_at(int p) const { return (four ? (p & 1) ^ (p >> 1) : p) * b; }
+};
+template <class T>
+__device__ inline T* at_bytes(T* x, int64_t bytes) {
+    return (T*)((const char*)x + bytes);
+}
+__device__ inline void write_known_record(const KnownRecord& k, const Batch& bt, int p) {
     if (!k.rec) return;
-    k.rec->res = k.value;
-    if (k.user) *k.user = k.value;
+    if (p < bt.lanes) at_bytes(k.rec, bt.ws_at(p))->res = k.value;
+    if (k.user) k.user[p] = k.value;
 }
 
 struct Problem {
@@ -68,6 +86,7 @@ struct Problem {
     int32_t G;             // ceil(k / b)
     int32_t num_cu;        // compute units of the device
     int32_t tile_mode;     // 1: every kTile x kTile block of C takes its own slice count (OZ_DYNAMIC + tile_slices)
+    Batch batch;           // problems that share the launches
     int32_t raw_slots;     // kTile blocks the raw buffer holds, four units each (a launch of fewer units than CUs may split k)
 };
 
@@ -184,7 +203,7 @@ inline ScanGrid scan_grid(const Problem& p, bool a_rows_contig, bool b_rows_cont
     // ESC blocks per workgroup: four, or one where four would leave fewer than four workgroups per CU: such a call waits
     // for the loads of one block after the other (200x300x260: 11.5 us with four, 4.5 with one), a larger one is bound
     // by the bytes read and sets eA and eB with a quarter of the atomics
-    s.per = row_blocks * ((p.G + kScanBlocksPerWg - 1) / kScanBlocksPerWg) < int64_t(4) * p.num_cu ? 1 : kScanBlocksPerWg;
+    s.per = p.batch.count * row_blocks * ((p.G + kScanBlocksPerWg - 1) / kScanBlocksPerWg) < int64_t(4) * p.num_cu ? 1 : kScanBlocksPerWg;
     s.groups = (p.G + s.per - 1) / s.per;
     const int64_t fit = kMaxGridThreads / 256 / row_blocks;
     s.slab = s.groups < fit ? s.groups : fit;
@@ -230,6 +249,9 @@ void launch_esc_verdict(hipStream_t st, const Workspace& w, const Problem& p, co
 // 0 slices"), 3 native by the cost model alone (nothing scanned)
 oz_result_t known_verdict(const Problem& p, const oz_opts_t& o, int kind);
 void launch_known_record(hipStream_t st, const KnownRecord& known);
+// whether the problems of p.batch can share the launches of an emulated call: few enough units of C for all of them, or small
+// calls (LaunchPlan)
+bool can_batch(const Problem& p);
 void launch_slice(hipStream_t st, const Operand& a, const Operand& b, const Workspace& w, const Problem& p);
 // per-block mode: blocks of the slice GEMM's first launch, and whether they are sorted by slice count
 void tile_order_shape(const Problem& p, int& first, int& deal);
@@ -245,14 +267,15 @@ void launch_recompose(hipStream_t st, const Workspace& w, const Problem& p, cons
 // known: a record to write on the way
 void launch_dgemm_f64(hipStream_t st, const Record* rec, const KnownRecord& known, bool ta, bool tb, int64_t m, int64_t n,
                       int64_t k, double alpha, const double* A, int64_t lda, const double* B,
-                      int64_t ldb, double beta, double* C, int64_t ldc, int num_cu, void* scratch = nullptr,
-                      size_t scratch_bytes = 0);
+                      int64_t ldb, double beta, double* C, int64_t ldc, int num_cu, const Batch& batch = Batch{},
+                      void* scratch = nullptr, size_t scratch_bytes = 0);
 void launch_scale_c(hipStream_t st, int64_t m, int64_t n, double beta, double* C, int64_t ldc);
 // complex product by the 4M method: split an interleaved complex matrix into planar parts (conj negates
 // the imaginary part), and combine the planar product with alpha, beta and the interleaved C
 void launch_zsplit(hipStream_t st, const void* Z, int64_t ld, int64_t rows, int64_t cols, double* re, double* im,
                    bool conj);
-void launch_zcombine(hipStream_t st, const double* Pr, const double* Pi, int64_t m, int64_t n, double ar, double ai,
+// p_step: 0, or elements to the products that are still to be subtracted from Pr and added to Pi
+void launch_zcombine(hipStream_t st, const double* Pr, const double* Pi, int64_t p_step, int64_t m, int64_t n, double ar, double ai,
                      double br, double bi, void* C, int64_t ldc);
 
 }  // namespace oz

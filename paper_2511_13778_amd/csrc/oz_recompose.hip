@@ -41,7 +41,16 @@ __global__ __launch_bounds__(256) void recompose_kernel(std::conditional_t<KIND 
                                                         double* __restrict__ C, int64_t ldc,
                                                         const Record* rec,
                                                         const int32_t* __restrict__ tile_S, int64_t j4_first,
-                                                        int c_vec) {
+                                                        int c_vec, Batch bt) {
+    {
+        const int64_t ws = bt.ws_at(blockIdx.z);
+        T = at_bytes(T, ws); L = at_bytes(L, ws);
+        raw = at_bytes(raw, ws);
+        eA = at_bytes(eA, ws); eB = at_bytes(eB, ws);
+        rec = at_bytes(rec, ws);
+        if (tile_S) tile_S = at_bytes(tile_S, ws);
+        C += int64_t(blockIdx.z) * bt.c;
+    }
     if (rec->res.fallback) return;
     const int S_all = rec->res.slices_used;
     const int64_t kblk = k_block_length(S_all);             // k-blocks of the call's largest count
@@ -282,20 +291,20 @@ void launch_recompose(hipStream_t st, const Workspace& w, const Problem& p, cons
                       double* C, int64_t ldc) {
     const unsigned gx = unsigned((p.m + 256 * kRecI - 1) / (256 * kRecI));
     const int64_t n4 = (p.n + kRecJ - 1) / kRecJ;
-    const int c_vec = (reinterpret_cast<uintptr_t>(C) % 16 == 0 && ldc % 2 == 0) ? 1 : 0;
+    const int c_vec = (reinterpret_cast<uintptr_t>(C) % 16 == 0 && ldc % 2 == 0 && p.batch.c % 2 == 0) ? 1 : 0;
     for (int64_t j4 = 0; j4 < n4; j4 += 65535) {
         const unsigned gy = unsigned(n4 - j4 < 65535 ? n4 - j4 : 65535);
         const int32_t* tile_S = p.tile_mode ? w.tile_S : nullptr;
-        const dim3 grid(gx, gy), block(256);
+        const dim3 grid(gx, gy, unsigned(p.batch.count)), block(256);
         if (split.kind == KSplit::kParts)
             hipLaunchKernelGGL(recompose_kernel<KSplit::kParts>, grid, block, 0, st, w.T, w.L, w.raw, split, w.eA, w.eB, p.m,
-                               p.n, p.mp, p.np, p.kp, p.s_cap, alpha, beta, C, ldc, w.rec, tile_S, j4, c_vec);
+                               p.n, p.mp, p.np, p.kp, p.s_cap, alpha, beta, C, ldc, w.rec, tile_S, j4, c_vec, p.batch);
         else if (split.kind == KSplit::kAtomic)
             hipLaunchKernelGGL(recompose_kernel<KSplit::kAtomic>, grid, block, 0, st, w.T, w.L, w.raw, split, w.eA, w.eB, p.m,
-                               p.n, p.mp, p.np, p.kp, p.s_cap, alpha, beta, C, ldc, w.rec, tile_S, j4, c_vec);
+                               p.n, p.mp, p.np, p.kp, p.s_cap, alpha, beta, C, ldc, w.rec, tile_S, j4, c_vec, p.batch);
         else
             hipLaunchKernelGGL(recompose_kernel<KSplit::kNone>, grid, block, 0, st, w.T, w.L, w.raw, split, w.eA, w.eB, p.m,
-                               p.n, p.mp, p.np, p.kp, p.s_cap, alpha, beta, C, ldc, w.rec, tile_S, j4, c_vec);
+                               p.n, p.mp, p.np, p.kp, p.s_cap, alpha, beta, C, ldc, w.rec, tile_S, j4, c_vec, p.batch);
     }
 }
 

@@ -165,10 +165,14 @@ __device__ __forceinline__ void scan_k(const ScanSide& s, int64_t rb, int g0, in
 
 // Both operands in one launch: the first blocks_a workgroups scan op(A), the others op(B), from ESC block g_first on.
 __global__ __launch_bounds__(256) void scan_kernel(ScanSide a, ScanSide b, int64_t blocks_a, int g_first, int per, int64_t k,
-                                                   int bl, int G, Record* rec) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) rec->infnan = 0;        // the exponents tell (exponents_kernel)
+                                                   int bl, int G, Record* rec, Batch bt) {
+    const int64_t ws = bt.ws_at(blockIdx.z);
+    if (blockIdx.x == 0 && threadIdx.x == 0) at_bytes(rec, ws)->infnan = 0;        // the exponents tell (exponents_kernel)
     const bool second = int64_t(blockIdx.x) >= blocks_a;
-    const ScanSide& s = second ? b : a;
+    ScanSide s = second ? b : a;
+    s.o.X += second ? bt.b_at(blockIdx.z) : bt.a_at(blockIdx.z);
+    s.tab = at_bytes(s.tab, ws);
+    s.group_max = at_bytes(s.group_max, ws);
     const int64_t id = int64_t(blockIdx.x) - (second ? blocks_a : 0);
     const int64_t rb = id % s.row_blocks;
     const int g0 = g_first + int(id / s.row_blocks) * per;
@@ -182,8 +186,8 @@ void launch_scan(hipStream_t st, const Operand& a, const Operand& b, const Works
     const ScanSide sa{a, w.U, 1, w.group_max_a(), g.row_blocks_a}, sb{b, w.V, 0, w.group_max_b(), g.row_blocks_b};
     for (int64_t y = 0; y < g.groups; y += g.slab) {
         const int64_t gy = g.groups - y < g.slab ? g.groups - y : g.slab;
-        hipLaunchKernelGGL(scan_kernel, dim3(unsigned((g.row_blocks_a + g.row_blocks_b) * gy)), dim3(256), 0, st, sa, sb,
-                           g.row_blocks_a * gy, int(y) * g.per, g.per, p.k, p.esc_block, p.G, w.rec);
+        hipLaunchKernelGGL(scan_kernel, dim3(unsigned((g.row_blocks_a + g.row_blocks_b) * gy), 1, unsigned(p.batch.count)), dim3(256), 0, st, sa, sb,
+                           g.row_blocks_a * gy, int(y) * g.per, g.per, p.k, p.esc_block, p.G, w.rec, p.batch);
     }
 }
 

@@ -224,11 +224,16 @@ struct SliceSide {
     int64_t row_blocks, blocks;      // workgroups along the rows, in all
 };
 
-// workgroups [0, a.blocks) cut a, the others b.  The LDS tile is dynamic: an operand with contiguous rows needs none
-__global__ __launch_bounds__(256) void slice_kernel(SliceSide a, SliceSide b, int64_t k, int64_t kp, const Record* rec) {
+// workgroups [0, a.blocks) cut a, the others b (swapped: a is op(B)).  The LDS tile is dynamic: an operand with contiguous rows needs none
+__global__ __launch_bounds__(256) void slice_kernel(SliceSide a, SliceSide b, int64_t k, int64_t kp, const Record* rec, Batch bt, int swapped) {
     extern __shared__ uint64_t slice_lds[];
     const bool second = int64_t(blockIdx.x) >= a.blocks;
-    const SliceSide& s = second ? b : a;
+    const int64_t ws = bt.ws_at(blockIdx.z);
+    SliceSide s = second ? b : a;
+    s.o.X += (second != bool(swapped)) ? bt.b_at(blockIdx.z) : bt.a_at(blockIdx.z);
+    s.e_row = at_bytes(s.e_row, ws);
+    s.out = at_bytes(s.out, ws);
+    rec = at_bytes(rec, ws);
     const int64_t id = int64_t(blockIdx.x) - (second ? a.blocks : 0);
     const int64_t rb = id % s.row_blocks, cb = id / s.row_blocks;
     const bool rows = s.o.stride_r == 1;
@@ -252,12 +257,13 @@ void launch_slice(hipStream_t st, const Operand& a, const Operand& b, const Work
     const size_t lds_a = a.stride_r == 1 ? 0 : kLds, lds_b = b.stride_r == 1 ? 0 : kLds;
     // Both operands in one launch where they need the same LDS, or where the launch itself is what counts (fewer
     // workgroups than 16 per CU); otherwise the LDS tile of the one would halve the occupancy of the other.
-    if (lds_a == lds_b || sa.blocks + sb.blocks < int64_t(16) * p.num_cu) {
-        hipLaunchKernelGGL(slice_kernel, dim3(unsigned(sa.blocks + sb.blocks)), dim3(256), lds_a > lds_b ? lds_a : lds_b, st, sa,
-                           sb, p.k, p.kp, w.rec);
+    const unsigned z = unsigned(p.batch.count);
+    if (lds_a == lds_b || (sa.blocks + sb.blocks) * z < int64_t(16) * p.num_cu) {
+        hipLaunchKernelGGL(slice_kernel, dim3(unsigned(sa.blocks + sb.blocks), 1, z), dim3(256), lds_a > lds_b ? lds_a : lds_b, st, sa,
+                           sb, p.k, p.kp, w.rec, p.batch, 0);
     } else {
-        hipLaunchKernelGGL(slice_kernel, dim3(unsigned(sa.blocks)), dim3(256), lds_a, st, sa, sb, p.k, p.kp, w.rec);
-        hipLaunchKernelGGL(slice_kernel, dim3(unsigned(sb.blocks)), dim3(256), lds_b, st, sb, sa, p.k, p.kp, w.rec);
+        hipLaunchKernelGGL(slice_kernel, dim3(unsigned(sa.blocks), 1, z), dim3(256), lds_a, st, sa, sb, p.k, p.kp, w.rec, p.batch, 0);
+        hipLaunchKernelGGL(slice_kernel, dim3(unsigned(sb.blocks), 1, z), dim3(256), lds_b, st, sb, sa, p.k, p.kp, w.rec, p.batch, 1);
     }
 }
 
