@@ -76,7 +76,8 @@ __device__ __forceinline__ void scan_store(const ScanSide& s, int G, int g, int6
 // thread per row for four whole blocks: 28 us for 2048 x 2048, now 10), and are combined through LDS.
 __device__ __forceinline__ void scan_rows(const ScanSide& s, int64_t rb, int g0, int per, int64_t k, int b, int G) {
     __shared__ int2 part[kScanBlocksPerWg][4][64];     // max; min, with bit 16 set when the part holds a zero
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);        // addresses are scalar but for the lane
     const int64_t r = rb * 64 + lane;
 #pragma unroll 1
     for (int u = 0; u < per; ++u) {
@@ -87,11 +88,11 @@ __device__ __forceinline__ void scan_rows(const ScanSide& s, int64_t rb, int g0,
             // past the end of a block its last entry is read again: it changes neither maximum nor minimum
             const int64_t l0 = int64_t(g) * b;
             const int len = int(min(int64_t(b), k - l0));
-            const uint64_t* src = reinterpret_cast<const uint64_t*>(s.o.X) + r + l0 * s.o.stride_l;
+            const uint64_t* src = reinterpret_cast<const uint64_t*>(s.o.X) + rb * 64 + l0 * s.o.stride_l;
             for (int l = wave; l < len; l += 64) {
                 uint64_t x[16];
 #pragma unroll
-                for (int i = 0; i < 16; ++i) x[i] = src[min(l + 4 * i, len - 1) * s.o.stride_l];
+                for (int i = 0; i < 16; ++i) x[i] = (src + min(l + 4 * i, len - 1) * s.o.stride_l)[lane];
                 st.add(x);
             }
         }
@@ -121,50 +122,55 @@ __device__ __forceinline__ void scan_rows(const ScanSide& s, int64_t rb, int g0,
 
 // k contiguous in memory (stride_l == 1): 16 lanes share one row so that a load instruction
 // reads 128 contiguous bytes per row; partial results are combined across the 16 lanes.
-// A workgroup covers 16 rows.  The loads of all its blocks are in flight together.
+// A workgroup covers 16 rows.  The loads of two blocks are in flight together (of four: 77 registers, and six workgroups to a CU
+// instead of eight: 4224 x 3008 x 1792 32 us against 25).
 template <int PER>
 __device__ __forceinline__ void scan_k(const ScanSide& s, int64_t rb, int g0, int64_t k, int b, int G) {
+    constexpr int PAIR = PER < 2 ? PER : 2;
     const int q = threadIdx.x & 15;
     const int64_t r = rb * 16 + (threadIdx.x >> 4);
-    BlockStat st[PER];
+    const uint64_t* const row = reinterpret_cast<const uint64_t*>(s.o.X) + r * s.o.stride_r;
+    int row_max = kExpAllZero;
+#pragma unroll 1
+    for (int g = g0; g < min(g0 + PER, G); g += PAIR) {
+        BlockStat st[PAIR];
 #pragma unroll
-    for (int u = 0; u < PER; ++u) st[u].reset();
-    if (r < s.o.rows) {
-        const uint64_t* src = reinterpret_cast<const uint64_t*>(s.o.X) + r * s.o.stride_r;
-        for (int l = q; l < b; l += 64) {
-            uint64_t x[PER][4];
+        for (int u = 0; u < PAIR; ++u) st[u].reset();
+        if (r < s.o.rows) {
+            for (int l = q; l < b; l += 64) {
+                uint64_t x[PAIR][4];
 #pragma unroll
-            for (int u = 0; u < PER; ++u)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
+                for (int u = 0; u < PAIR; ++u) {
                     // past the end of a block its last entry is read again, past the last block that block
-                    const int64_t l0 = int64_t(min(g0 + u, G - 1)) * b;
-                    x[u][i] = src[l0 + min(int64_t(l + 16 * i), min(int64_t(b), k - l0) - 1)];
+                    const int64_t l0 = int64_t(min(g + u, G - 1)) * b;
+                    const int len = int(min(int64_t(b), k - l0));
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) x[u][i] = (row + l0)[min(l + 16 * i, len - 1)];
                 }
 #pragma unroll
-            for (int u = 0; u < PER; ++u) st[u].add(x[u]);
+                for (int u = 0; u < PAIR; ++u) st[u].add(x[u]);
+            }
         }
-    }
-    int row_max = kExpAllZero;
 #pragma unroll
-    for (int u = 0; u < PER; ++u) {
-        int mx = st[u].max_exp(), mn = st[u].min_exp(), any_zero = st[u].any_zero;
+        for (int u = 0; u < PAIR; ++u) {
+            int mx = st[u].max_exp(), mn = st[u].min_exp(), any_zero = st[u].any_zero;
 #pragma unroll
-        for (int off = 8; off >= 1; off >>= 1) {
-            mx = max(mx, __shfl_xor(mx, off));
-            mn = min(mn, __shfl_xor(mn, off));
-            any_zero |= __shfl_xor(any_zero, off);
-        }
-        if (q == 0 && g0 + u < G) {
-            scan_store(s, G, g0 + u, r, table_max(mx), table_min(mx, mn, any_zero));
-            row_max = max(row_max, table_max(mx));
+            for (int off = 8; off >= 1; off >>= 1) {
+                mx = max(mx, __shfl_xor(mx, off));
+                mn = min(mn, __shfl_xor(mn, off));
+                any_zero |= __shfl_xor(any_zero, off);
+            }
+            if (q == 0 && g + u < G) {
+                scan_store(s, G, g + u, r, table_max(mx), table_min(mx, mn, any_zero));
+                row_max = max(row_max, table_max(mx));
+            }
         }
     }
     if (q == 0) s.group_max[int64_t(g0 / PER) * s.o.rows_p + r] = int16_t(row_max);
 }
 
 // Both operands in one launch: the first blocks_a workgroups scan op(A), the others op(B), from ESC block g_first on.
-__global__ __launch_bounds__(256) void scan_kernel(ScanSide a, ScanSide b, int64_t blocks_a, int g_first, int per, int64_t k,
+__global__ __launch_bounds__(256, 8) void scan_kernel(ScanSide a, ScanSide b, int64_t blocks_a, int g_first, int per, int64_t k,
                                                    int bl, int G, Record* rec, Batch bt) {
     const int64_t ws = bt.ws_at(blockIdx.z);
     if (blockIdx.x == 0 && threadIdx.x == 0) at_bytes(rec, ws)->infnan = 0;        // the exponents tell (exponents_kernel)
