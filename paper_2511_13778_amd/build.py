@@ -12,7 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liboz_mi355x.so")
 PROBE_LIB = os.path.join(HERE, "liboz_probe.so")      # measurement probes: separate from the product library
 PROBE_SOURCES = ["oz_probe.hip"]
-SOURCES = ["oz_api.hip", "oz_scan.hip", "oz_esc.hip", "oz_slice.hip", "oz_gemm_i8.hip", "oz_gemm_few.hip", "oz_gemm_small.hip",
+SOURCES = ["oz_api.hip", "oz_scan.hip", "oz_esc.hip", "oz_slice.hip", "oz_gemm_i8.hip", "oz_gemm_few.hip", "oz_gemm_small.hip", "oz_gemm_mid.hip",
            "oz_recompose.hip", "oz_dgemm_f64.hip", "oz_dgemm_f64_direct.hip", "oz_complex.hip"]
 # packed FP32 instructions are switched off for all device code (known-bad on the test machines)
 # -ffp-contract=off: the FP64 epilogues round every product and sum separately, as the header specifies;

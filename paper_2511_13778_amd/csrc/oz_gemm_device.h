@@ -42,4 +42,28 @@ __device__ __forceinline__ void dma16(const uint8_t* gbase, uint32_t lane_off, u
                  :: "s"(lds_addr), "v"(lane_off), "s"(gbase), "n"(LDS_IMM) : "memory", "scc");
 }
 
+// Waits until at most n of this wave's transfers are in flight, n rounded down to one of a few values.  The decision is a
+// tree of three to four scalar branches: eighteen in a row cost the kernels on small tiles a tenth of a 64 of k.
+__device__ __forceinline__ void wait_transfers(int n) {
+#define OZ_WAIT(N) asm volatile("s_waitcnt vmcnt(" #N ")" ::: "memory")
+    if (n < 4) {
+        if (n <= 0) OZ_WAIT(0);
+        else if (n < 2) OZ_WAIT(1);
+        else OZ_WAIT(2);
+    } else if (n < 12) {
+        if (n < 6) OZ_WAIT(4);
+        else if (n < 8) OZ_WAIT(6);
+        else if (n < 10) OZ_WAIT(8);
+        else OZ_WAIT(10);
+    } else if (n < 24) {
+        if (n < 16) OZ_WAIT(12);
+        else OZ_WAIT(16);
+    } else {
+        if (n < 32) OZ_WAIT(24);
+        else if (n < 48) OZ_WAIT(32);
+        else OZ_WAIT(48);
+    }
+#undef OZ_WAIT
+}
+
 }  // namespace oz

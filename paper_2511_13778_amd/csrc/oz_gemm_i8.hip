@@ -744,13 +744,17 @@ bool prepare_gemm_i8() {
                                hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds) == hipSuccess &&
            hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_i8_batch_kernel),
                                hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds) == hipSuccess &&
-           prepare_gemm_i8_few() && prepare_gemm_small();
+           prepare_gemm_i8_few() && prepare_gemm_small() && prepare_gemm_mid();
 }
 
 SplitPlan launch_gemm_i8(hipStream_t st, const Workspace& w, const Problem& p, double alpha, double beta, double* C, int64_t ldc) {
     const LaunchPlan lp(p);
     if (lp.small) {
         launch_gemm_small(st, w, p, lp, alpha, beta, C, ldc);
+        return SplitPlan{KSplit::kDone, lp.g, lp.raw_units};
+    }
+    if (lp.mid) {
+        launch_gemm_mid(st, w, p, lp, alpha, beta, C, ldc);
         return SplitPlan{KSplit::kDone, lp.g, lp.raw_units};
     }
     if (lp.few) {

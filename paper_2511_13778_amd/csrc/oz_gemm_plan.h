@@ -85,6 +85,11 @@ __host__ __device__ inline bool skip_padding(int xcd, int stride, int& slot, con
 constexpr int kSmallTile = 32;
 constexpr int kSmallLdsMax = 160 * 1024;         // all of a CU's LDS
 
+// The same of gemm_mid_kernel, the most slices it holds, and the most with which two workgroups share a CU.
+constexpr int kMidTile = 64;
+constexpr int kMidMaxSlices = 16;
+constexpr int kMidPairSlices = 8;
+
 struct Split { int z; bool atomic; };
 
 // How a call's units are dealt to launches.
@@ -99,7 +104,9 @@ struct LaunchPlan {
     Split last;            // of the rest (of everything, if there is no full round)
     bool two;              // the rest in a launch of its own
     bool few;              // at most two slices, on 256 x 256 blocks (gemm_i8_few_kernel) instead of all that
-    bool small;            // few units and short k, on 32 x 32 tiles with the recomposition (gemm_small_kernel) instead of all that
+    // slice GEMM and recomposition in one launch instead of all that:
+    bool small;            // on 32 x 32 tiles (gemm_small_kernel)
+    bool mid, mid_pair;    // on 64 x 64 tiles (gemm_mid_kernel), two workgroups to a CU
 
     explicit LaunchPlan(const Problem& p) : g() {
         g.nti = int(p.mp / kTile);
@@ -126,12 +133,12 @@ struct LaunchPlan {
         last = rest != 0 && rest * per_pos < round ? split(p, rest * per_pos, last_ns) : Split{1, false};
         two = full != 0 && last.z > 1;
         few = few_slices(p);
-        small = small_call(p, last_ns);
+        fuse(p, last_ns);
     }
 
     // whether the problems of p.batch can share the launches
     bool can_batch(const Problem& p) const {
-        return small || (!few && int64_t(positions) * per_pos * p.batch.count <= p.num_cu);
+        return small || mid || (!few && int64_t(positions) * per_pos * p.batch.count <= p.num_cu);
     }
 
     // tiles of one problem
@@ -139,25 +146,61 @@ struct LaunchPlan {
         return ((p.m + kSmallTile - 1) / kSmallTile) * ((p.n + kSmallTile - 1) / kSmallTile);
     }
 
-    // Whether slice GEMM and recomposition take longer in their two launches than in the one of gemm_small_kernel.  Estimated
-    // in ns for S slices (one more than the fewest where the device decides):
-    //   one launch   8 us, and per 64 of k 0.4 us + 0.11 us per slice with a workgroup per CU at most; beyond that two share a
-    //                CU: per 512 tiles 4 us, and per 64 of k 0.25 us + 0.18 us per slice
-    //   two          10 us, and for seven slices 14 us, 5.5 us per million elements of C, 0.5 us per part of a k split, and
-    //                what split() estimates or 4.2 us per 64 of k and 5 us per round of units; (S+1)/8 of that for S
-    // Measured, the whole call with two launches / one, nine slices (dynamic) and three: 200x300x260 72 / 37 us and 37 / 21,
-    // 512^3 85 / 46 and 38 / 25, 700x700x1500 126 / 90 and 56 / 51, 1024^3 117 / 104 and 55 / 58, 256x256x4000 111 / 120 and
-    // 52 / 65, 1500x1500x128 86 / 68 and 47 / 40, 2000x2000x256 114 / 132 and 52 / 69.
-    bool small_call(const Problem& p, int64_t last_ns) const {
-        if (p.nkb != 1) return false;
-        const int64_t S = p.s_min == p.s_cap ? p.s_cap : p.s_min + 1;
-        const int64_t tiles = small_tiles(p) * p.batch.count;
-        const int64_t one = 8000 + (tiles <= p.num_cu ? kt * (400 + 110 * S)
-                                                      : std::max(tiles, int64_t(2) * p.num_cu) * (4000 + kt * (250 + 180 * S)) / (2 * p.num_cu));
-        const int64_t rounds = (int64_t(positions) * per_pos * p.batch.count + p.num_cu - 1) / p.num_cu;
-        const int64_t gemm = full == 0 && last.z > 1 ? last_ns + int64_t(500) * last.z : rounds * (int64_t(4200) * kt + 5000);
-        const int64_t two_launches = 10000 + (14000 + p.m * p.n * p.batch.count * 55 / 10000 + gemm) * (S + 1) / 8;
-        return one < two_launches * 95 / 100;
+    // Whether slice GEMM and recomposition take longer in their two launches than in one, and in which: estimated in ns for S
+    // slices (one more than the fewest where the device decides).  What a tile costs beside its products is its start and
+    // its end, its sums and the digits it writes: with many slices and a long k the 128 x 128 units, which read fewer bytes
+    // per product, win; otherwise the larger of the small tiles that still gives every CU one.
+    //   units       10 us, and for seven slices 14 us, 5.5 us per million elements of C, 0.5 us per part of a k split, and what
+    //               split() estimates or 4.2 us per 64 of k and 5 us per round of units; (S+1)/8 of that for S; 0.925 of it
+    //               all, and 0.32 us per slice and million elements
+    //   64 x 64     a workgroup per CU: per round 1.07 us + 0.60 per slice, and per 64 of k 0.36 us + 37 ns per pair of slices; 2.8 us
+    //               per million elements.  Two to a CU (a stage of one 64 of k each; the slice count must be known): 0.81, 0.85, 0.45
+    //               and 66, per round of twice as many, one alone 0.95, 0.52 and 54; 2.6 us per million elements
+    //   32 x 32     a workgroup per CU at most: 2.5 us, and per 64 of k 0.42 us + 19 ns per slice + 12 per pair; beyond that, per
+    //               round of two to a CU: 2.8 us + 0.28 per slice, and per 64 of k 0.55 us + 4 ns per slice + 16 per pair
+    // Rounds are whole up to four, beyond that workgroups end at different times.
+    // Fitted to 1770 timings of 499 calls of 1 to 16 slices (60 to 8000, k to 6000, one to four problems): the choice is 1 % off the
+    // best on average, and against the better of units and 32 x 32 tiles 7 % faster on average (29 % slower at most).  The 64 x 64
+    // tiles have to be 12 % better than the others: on a full chip and a long k, at a lower clock, they are worse than estimated (2048^3
+    // and 4224 x 3008 x 1792, seven slices, 4 %).
+    // Whole calls, units / 32 x 32 / 64 x 64: 200x300x260 nine slices 69 / 36 / 44 us, 512^3 nine 84 / 45 / 58, 1000^3 seven 95 / 86 /
+    // 71, 1500x1700x1000 seven 142 / - / 130, 2048^3 seven 246 / 435 / 257, 7936x7936 seven: k = 64 573 / - / 378, k = 256 850 / - / 740,
+    // k = 1024 1660 / - / 1730.
+    void fuse(const Problem& p, int64_t last_ns) {
+        small = mid = mid_pair = false;
+        if (p.nkb != 1) return;
+        const int64_t S = p.s_min == p.s_cap ? p.s_cap : p.s_min + 1, pairs = S * (S + 1) / 2, cus = p.num_cu;
+        const int64_t area = p.m * p.n * p.batch.count;
+        // workgroups, per round, ns of a round
+        auto rounds_ns = [](int64_t all, int64_t per, int64_t ns) { return all < 4 * per ? (all + per - 1) / per * ns : all * ns / per; };
+        const int64_t whole = (int64_t(full) * per_pos * p.batch.count + cus - 1) / cus, unit_ns = int64_t(4200) * kt + 5000;
+        int64_t gemm = whole * unit_ns;
+        if (rest != 0) gemm += last.z > 1 ? last_ns + int64_t(500) * last.z : (int64_t(rest) * per_pos * p.batch.count + cus - 1) / cus * unit_ns;
+        int64_t best = (10000 + (14000 + area * 55 / 10000 + gemm) * (S + 1) / 8) * 925 / 1000 + area * S * 32 / 100000;
+        const int64_t small_all = small_tiles(p) * p.batch.count;
+        const int64_t small_ns = small_all <= cus ? 2540 + kt * (416 + 19 * S + 12 * pairs)
+                                                  : rounds_ns(small_all, 2 * cus, 2770 + 278 * S + kt * (550 + 4 * S + 16 * pairs));
+        if (small_ns < best) {
+            best = small_ns;
+            small = true;
+        }
+        best = best * 88 / 100;
+        if (p.s_cap > kMidMaxSlices) return;
+        const int64_t mid_all = ((p.m + kMidTile - 1) / kMidTile) * ((p.n + kMidTile - 1) / kMidTile) * p.batch.count;
+        const int64_t mid_ns = rounds_ns(mid_all, cus, 1070 + 600 * S + kt * (357 + 37 * pairs)) + area * 279 / 100000;
+        if (mid_ns < best) {
+            best = mid_ns;
+            small = false;
+            mid = true;
+        }
+        if (p.s_min != p.s_cap || p.s_cap > kMidPairSlices) return;
+        const int64_t pair_ns = 810 + 850 * S + kt * (449 + 66 * pairs), alone_ns = 952 * S + kt * (519 + 54 * pairs);
+        const int64_t on_cu = (mid_all + cus - 1) / cus;          // workgroups of the fullest CU
+        const int64_t two_ns = (mid_all < 8 * cus ? on_cu / 2 * pair_ns + on_cu % 2 * alone_ns : mid_all * pair_ns / (2 * cus)) + area * 262 / 100000;
+        if (two_ns < best) {
+            small = false;
+            mid = mid_pair = true;
+        }
     }
 
     // At most two slices, whatever the device finds: 256 x 256 blocks, where their estimated time is the shorter one.  In us:
@@ -236,5 +279,9 @@ bool prepare_gemm_small();
 void launch_gemm_small(hipStream_t st, const Workspace& w, const Problem& p, const LaunchPlan& lp, double alpha, double beta,
                        double* C, int64_t ldc);
 void launch_gemm_i8_few(hipStream_t st, const Workspace& w, const Problem& p, const LaunchPlan& lp);
+// the same of a plan with `mid` set
+bool prepare_gemm_mid();
+void launch_gemm_mid(hipStream_t st, const Workspace& w, const Problem& p, const LaunchPlan& lp, double alpha, double beta,
+                     double* C, int64_t ldc);
 
 }  // namespace oz

@@ -8,7 +8,7 @@
 // is walked once and every anti-diagonal grows at the same time, in the registers of the wave it is dealt to; the carry
 // chain, the powers of two and alpha / beta follow from LDS in the same launch.  Up to 16 times as many workgroups as units.
 // The price is LDS bandwidth: four MFMAs per four fragments read, twice what the matrix unit's rate allows.  So
-// it is the shorter way only while the units would leave the chip idle (LaunchPlan::small).
+// it is the shorter way only while the units would leave the chip idle (LaunchPlan::fuse).
 // 200 x 300 x 260 with nine slices: slice GEMM and recomposition 33 + 14 us, now 10 (the call 72 -> 37).
 #include "oz_gemm_device.h"
 
@@ -25,15 +25,6 @@ static_assert(kMaxSlices * kSumPlane <= kSmallLdsMax && kMaxSlices * 2 * kSliceB
 
 template <int N>
 struct Count { static constexpr int v = N; };
-
-// waits until at most n of this wave's transfers are in flight (rounded down to what the instruction can be given here)
-__device__ __forceinline__ void wait_transfers(int n) {
-#define OZ_WAIT(N) if (n >= N) { asm volatile("s_waitcnt vmcnt(" #N ")" ::: "memory"); return; }
-    OZ_WAIT(48) OZ_WAIT(32) OZ_WAIT(24) OZ_WAIT(16) OZ_WAIT(12) OZ_WAIT(10) OZ_WAIT(8) OZ_WAIT(6) OZ_WAIT(5) OZ_WAIT(4)
-    OZ_WAIT(3) OZ_WAIT(2)
-#undef OZ_WAIT
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-}
 
 // grid (32 x 32 tiles of C, i fastest); one k-block.
 __global__ __launch_bounds__(64 * kSmallWaves, 4) void gemm_small_kernel(

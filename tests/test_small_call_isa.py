@@ -1,19 +1,23 @@
-"""Static check on the generated gfx950 code of the small calls' slice GEMM (no GPU needed): its transfers take a scalar base in
+"""Static check on the generated gfx950 code of the slice GEMMs on small tiles (no GPU needed): their transfers take a scalar base in
 an asm block, where the compiler does not keep the distance to a vector-ALU write of that register."""
 import os
 import subprocess
 
+import pytest
+
 from test_kernel_isa import CSRC, function_body, gemm_asm, shared_countdowns, step_blocks, too_close  # noqa: F401
 
 
-def test_transfers_never_read_a_freshly_valu_written_scalar(tmp_path):
+@pytest.mark.parametrize("source,kernel", [("oz_gemm_small", "_ZN2oz17gemm_small_kernel"), ("oz_gemm_mid", "_ZN2oz15gemm_mid_kernelILi1EE"),
+                                           ("oz_gemm_mid", "_ZN2oz15gemm_mid_kernelILi2EE")])
+def test_transfers_never_read_a_freshly_valu_written_scalar(tmp_path, source, kernel):
     from paper_2511_13778_amd.build import FLAGS
-    out = tmp_path / "oz_gemm_small.s"
-    r = subprocess.run(["hipcc", *FLAGS, "-S", "--cuda-device-only", os.path.join(CSRC, "oz_gemm_small.hip"), "-o", str(out)],
+    out = tmp_path / (source + ".s")
+    r = subprocess.run(["hipcc", *FLAGS, "-S", "--cuda-device-only", os.path.join(CSRC, source + ".hip"), "-o", str(out)],
                        capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
     asm = [ln for ln in open(out).read().splitlines() if ln.strip() and not ln.strip().startswith(";")]
-    body = function_body(asm, "_ZN2oz17gemm_small_kernel")
+    body = function_body(asm, kernel)
     seen, bad = too_close(body)
     assert seen.get("global_load_lds_dwordx4", 0) >= 2 and not bad, bad
     assert not any("scratch_" in ln for ln in body)
