@@ -8,7 +8,7 @@
 #include <new>
 #include <vector>
 
-#include "oz_internal.h"
+#include "oz_f64_direct.h"
 
 // Workspace of oz_dgemm_static: device memory owned by the library, one copy per GPU that loads
 // it, held until the process ends.  In host code this name is only a handle for
@@ -427,11 +427,13 @@ oz_status_t dgemm_impl(oz_handle_t h, void* stream, char transa, char transb, in
     clk.done(2);          // the verdict is given by the last workgroup of the ESC kernel
     launch_slice(st, oa, ob, w, p);
     clk.done(3);
-    const SplitPlan split = launch_gemm_i8(st, w, p, alpha, beta, C, ldc);
+    bool fell_back = false;
+    const Fallback fallback{guarded ? A : nullptr, a_sr, a_sl, B, b_sr, b_sl, k, !ta, tb};
+    const SplitPlan split = launch_gemm_i8(st, w, p, alpha, beta, C, ldc, fallback, fell_back);
     clk.done(4);
     if (split.kind != KSplit::kDone) launch_recompose(st, w, p, split, alpha, beta, C, ldc);
     clk.done(5);
-    if (guarded) launch_dgemm_f64(st, w.rec, KnownRecord{}, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, h->num_cu, batch, f64_scratch, f64_scratch_bytes);
+    if (guarded && !fell_back) launch_dgemm_f64(st, w.rec, KnownRecord{}, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, h->num_cu, batch, f64_scratch, f64_scratch_bytes);
     clk.done(6);
     return hipGetLastError() == hipSuccess ? OZ_OK : OZ_ERR_HIP;
 }

@@ -322,7 +322,7 @@ constexpr double kF64CacheBytesPerUs = 9e6;
 // they leave partial products in the scratch memory and a second kernel adds them in the order of the parts (deterministic)
 // and applies alpha and beta: a launch of 4.5 us and zsplit + 2 passes over C at 4.5 TB/s.  A guarded call pays that launch
 // whether it falls back or not: 20 there.
-F64Plan choose_f64(const F64Call& c, int num_cu, void* scratch, size_t scratch_bytes) {
+F64Plan choose_f64(const F64Call& c, int num_cu, void* scratch, size_t scratch_bytes, double* us_of = nullptr) {
     F64Plan best{};
     double best_us = 0.0;
     const uint32_t m = uint32_t(c.m), n = uint32_t(c.n), cus = uint32_t(num_cu), problems = uint32_t(c.batch.count);
@@ -349,10 +349,31 @@ F64Plan choose_f64(const F64Call& c, int num_cu, void* scratch, size_t scratch_b
             }
         }
     }
+    if (us_of) *us_of = best_us;
     return best;
 }
 
+// operands cut out of a very large parent matrix, or a size of 2^31 and more: offsets inside a tile may not fit 32 bits (a lane's
+// own: at most 15 leading dimensions plus a row of the tile; its elements: up to 7 x 16 leading dimensions further on; in bytes)
+bool wide_offsets(int64_t m, int64_t n, int64_t k, int64_t ld_max) {
+    return (128 * ld_max + 256) * 8 >= (int64_t(1) << 32) || ((m | n | k) >> 31) != 0;
+}
+
 }  // namespace
+
+bool f64_folds(const Problem& p, int64_t ld_max, int edge) {
+    if (wide_offsets(p.m, p.n, p.k, ld_max)) return false;
+    F64Call c{};
+    c.m = p.m; c.n = p.n; c.k = p.k;
+    c.batch = p.batch;
+    double best_us = 0.0;
+    choose_f64(c, p.num_cu, nullptr, 0, &best_us);
+    const double tiles = double((p.m + edge - 1) / edge) * double((p.n + edge - 1) / edge) * p.batch.count, steps = double((p.k + kDK - 1) / kDK);
+    const double rounds = double(int64_t((tiles + p.num_cu - 1) / p.num_cu)), cache_us = tiles * (2 * edge) * double(p.k) * 8.0 / kF64CacheBytesPerUs;
+    // 32 x 32 as in the table; 64 x 64 fitted to the same timings
+    const double us = edge == 32 ? 3.53 + rounds * (0.94 + 0.169 * steps) : 3.79 + rounds * (4.10 + 0.465 * steps) + 0.023 * steps;
+    return std::max(us, cache_us) <= best_us + 4.5;
+}
 
 void launch_dgemm_f64(hipStream_t st, const Record* rec, const KnownRecord& known, bool ta, bool tb, int64_t m, int64_t n, int64_t k,
                       double alpha, const double* A, int64_t lda, const double* B, int64_t ldb, double beta,
@@ -360,14 +381,8 @@ void launch_dgemm_f64(hipStream_t st, const Record* rec, const KnownRecord& know
     // op(A)(i,l): N -> A[i + l*lda] (rows contiguous), T -> A[l + i*lda]
     // op(B)(l,j): N -> B[l + j*ldb] (k contiguous),    T -> B[j + l*ldb] (rows contiguous)
     const F64Call c{rec, known, m, n, k, alpha, A, ta ? lda : 1, ta ? 1 : lda, B, tb ? 1 : ldb, tb ? ldb : 1, beta, C, ldc, !ta, tb, batch};
-    // the fast loads keep every offset inside a K step of a tile in 32 bits (a lane's own: at most
-    // 15 leading dimensions plus a row of the tile; its elements: up to 7 x 16 leading dimensions
-    // further on; in bytes); operands cut out of a very large parent matrix take the bounds-checked
-    // path, which indexes in 64 bits
-    const int64_t ld_max = lda > ldb ? lda : ldb;
-    const bool wide_ld = (128 * ld_max + 256) * 8 >= (int64_t(1) << 32);
-    // (as does a size of 2^31 and more)
-    const bool wide = wide_ld || ((m | n | k) >> 31) != 0;
+    // the fast loads keep every offset inside a K step of a tile in 32 bits; where they may not fit, the bounds-checked path indexes in 64
+    const bool wide = wide_offsets(m, n, k, lda > ldb ? lda : ldb);
     F64Plan p{};
     if (!wide) p = choose_f64(c, num_cu, scratch, scratch_bytes);
     if (p.ti == 0) {

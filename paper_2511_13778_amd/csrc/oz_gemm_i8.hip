@@ -55,6 +55,7 @@
 //    work are spread over the gaps between a step's MFMAs, and the loops are laid out for few branches.
 #include <type_traits>
 
+#include "oz_f64_direct.h"
 #include "oz_gemm_device.h"
 
 namespace oz {
@@ -747,14 +748,19 @@ bool prepare_gemm_i8() {
            prepare_gemm_i8_few() && prepare_gemm_small() && prepare_gemm_mid();
 }
 
-SplitPlan launch_gemm_i8(hipStream_t st, const Workspace& w, const Problem& p, double alpha, double beta, double* C, int64_t ldc) {
+SplitPlan launch_gemm_i8(hipStream_t st, const Workspace& w, const Problem& p, double alpha, double beta, double* C, int64_t ldc,
+                         const Fallback& fallback, bool& fell_back) {
     const LaunchPlan lp(p);
+    Fallback fb = fallback;
+    if (fb.A && (lp.small || lp.mid))
+        fell_back = f64_folds(p, std::max(std::max(fb.a_sr, fb.a_sl), std::max(fb.b_sr, fb.b_sl)), lp.small ? kSmallTile : kMidTile);
+    if (!fell_back) fb.A = nullptr;
     if (lp.small) {
-        launch_gemm_small(st, w, p, lp, alpha, beta, C, ldc);
+        launch_gemm_small(st, w, p, lp, alpha, beta, C, ldc, fb);
         return SplitPlan{KSplit::kDone, lp.g, lp.raw_units};
     }
     if (lp.mid) {
-        launch_gemm_mid(st, w, p, lp, alpha, beta, C, ldc);
+        launch_gemm_mid(st, w, p, lp, alpha, beta, C, ldc, fb);
         return SplitPlan{KSplit::kDone, lp.g, lp.raw_units};
     }
     if (lp.few) {

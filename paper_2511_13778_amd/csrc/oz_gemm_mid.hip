@@ -13,6 +13,7 @@
 // What bounds it at a short k is memory: digits, leading words and C are 26 bytes per element (7936 x 7936, seven slices: 280 us
 // plus 95 per 64 of k; units 500 plus 73).  At a long one the load of a stage, which only the other workgroup covers.
 // Measured, whole calls: 7936x7936x256 814 -> 716 us, 16 problems of 512^3 271 -> 235, 1000^3 (seven slices) 86 -> 71.
+#include "oz_f64_direct.h"
 #include "oz_gemm_device.h"
 
 namespace oz {
@@ -32,7 +33,7 @@ __global__ __launch_bounds__(256 * SETS, 2) void gemm_mid_kernel(
     const int8_t* __restrict__ As, const int8_t* __restrict__ Bs, int32_t* __restrict__ T, int8_t* __restrict__ L,
     const int32_t* __restrict__ eA, const int32_t* __restrict__ eB, int64_t m, int64_t n, int64_t mp, int64_t np, int64_t kp,
     int ntm, int ntn, int kt_total, int lds_bytes, double alpha, double beta, double* __restrict__ C, int64_t ldc, const Record* rec,
-    const int32_t* __restrict__ tile_S, Batch bt) {
+    const int32_t* __restrict__ tile_S, Batch bt, Fallback fb) {
     constexpr int WAVES = 4 * SETS, D = 4;
     constexpr int GROUPS = (SETS == 1 ? kMidPairSlices : kMidMaxSlices) / D / SETS;     // of four anti-diagonals per wave
     extern __shared__ __align__(16) uint8_t lds[];
@@ -45,8 +46,7 @@ __global__ __launch_bounds__(256 * SETS, 2) void gemm_mid_kernel(
         if (tile_S) tile_S = at_bytes(tile_S, ws);
         C += int64_t(blockIdx.z) * bt.c;
     }
-    if (rec->res.fallback) return;
-    const int S_all = rec->res.slices_used;
+    const int fallback = rec->res.fallback, S_all = rec->res.slices_used;
     int ti, tj;
     {
         const int total = ntm * ntn, xcd = int(blockIdx.x) & 7, slot = int(blockIdx.x) >> 3;
@@ -54,6 +54,10 @@ __global__ __launch_bounds__(256 * SETS, 2) void gemm_mid_kernel(
         lin_to_tile(xcd * per + min(xcd, rem) + slot, ntm, ntn, ti, tj);
     }
     const int64_t i0 = int64_t(ti) * kMidTile, j0 = int64_t(tj) * kMidTile;
+    if (fallback) {
+        if (fb.A) fall_back<4, 4, WAVES>(fb, bt, int(blockIdx.z), reinterpret_cast<double*>(lds), m, n, i0, j0, alpha, beta, C, ldc);
+        return;
+    }
     const int S = tile_S ? min(tile_S[(j0 / kTile) * (mp / kTile) + i0 / kTile], S_all) : S_all;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -252,16 +256,16 @@ bool prepare_gemm_mid() {
 }
 
 void launch_gemm_mid(hipStream_t st, const Workspace& w, const Problem& p, const LaunchPlan& lp, double alpha, double beta,
-                     double* C, int64_t ldc) {
+                     double* C, int64_t ldc, const Fallback& fb) {
     const int ntm = int((p.m + kMidTile - 1) / kMidTile), ntn = int((p.n + kMidTile - 1) / kMidTile);
     const int32_t* tile_S = p.tile_mode ? w.tile_S : nullptr;
     const dim3 grid(unsigned(ntm) * unsigned(ntn), 1, unsigned(p.batch.count));
     if (lp.mid_pair)
         hipLaunchKernelGGL(gemm_mid_kernel<1>, grid, dim3(256), kSmallLdsMax / 2, st, w.As, w.Bs, w.T, w.L, w.eA, w.eB, p.m, p.n, p.mp,
-                           p.np, p.kp, ntm, ntn, lp.kt, kSmallLdsMax / 2, alpha, beta, C, ldc, w.rec, tile_S, p.batch);
+                           p.np, p.kp, ntm, ntn, lp.kt, kSmallLdsMax / 2, alpha, beta, C, ldc, w.rec, tile_S, p.batch, fb);
     else
         hipLaunchKernelGGL(gemm_mid_kernel<2>, grid, dim3(512), kSmallLdsMax, st, w.As, w.Bs, w.T, w.L, w.eA, w.eB, p.m, p.n, p.mp,
-                           p.np, p.kp, ntm, ntn, lp.kt, kSmallLdsMax, alpha, beta, C, ldc, w.rec, tile_S, p.batch);
+                           p.np, p.kp, ntm, ntn, lp.kt, kSmallLdsMax, alpha, beta, C, ldc, w.rec, tile_S, p.batch, fb);
 }
 
 }  // namespace oz

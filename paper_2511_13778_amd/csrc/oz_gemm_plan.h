@@ -277,11 +277,11 @@ bool prepare_gemm_i8_few();
 // the slice GEMM and the recomposition of a plan with `small` set
 bool prepare_gemm_small();
 void launch_gemm_small(hipStream_t st, const Workspace& w, const Problem& p, const LaunchPlan& lp, double alpha, double beta,
-                       double* C, int64_t ldc);
+                       double* C, int64_t ldc, const Fallback& fb);
 void launch_gemm_i8_few(hipStream_t st, const Workspace& w, const Problem& p, const LaunchPlan& lp);
 // the same of a plan with `mid` set
 bool prepare_gemm_mid();
 void launch_gemm_mid(hipStream_t st, const Workspace& w, const Problem& p, const LaunchPlan& lp, double alpha, double beta,
-                     double* C, int64_t ldc);
+                     double* C, int64_t ldc, const Fallback& fb);
 
 }  // namespace oz

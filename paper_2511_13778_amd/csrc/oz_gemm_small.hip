@@ -10,6 +10,7 @@
 // The price is LDS bandwidth: four MFMAs per four fragments read, twice what the matrix unit's rate allows.  So
 // it is the shorter way only while the units would leave the chip idle (LaunchPlan::fuse).
 // 200 x 300 x 260 with nine slices: slice GEMM and recomposition 33 + 14 us, now 10 (the call 72 -> 37).
+#include "oz_f64_direct.h"
 #include "oz_gemm_device.h"
 
 namespace oz {
@@ -21,6 +22,7 @@ constexpr int kSumRow = kSmallTile + 4;                     // words between row
 constexpr int kSumPlane = kSmallTile * kSumRow * 4;         // bytes per anti-diagonal
 constexpr int kSmallDiags = (kMaxSlices + kSmallWaves - 1) / kSmallWaves;     // anti-diagonals per wave
 static_assert(kSmallTile == 32 && kBK == 64, "the transfers below move 2 x 32 rows of 16 bytes, the waves 2 x 2 MFMA tiles");
+static_assert(f64_direct_lds(2, 2, kSmallWaves) <= kSmallLdsMax / 2, "the fallback shares the LDS");
 static_assert(kMaxSlices * kSumPlane <= kSmallLdsMax && kMaxSlices * 2 * kSliceBytes <= kSmallLdsMax, "one stage must fit");
 
 template <int N>
@@ -31,7 +33,7 @@ __global__ __launch_bounds__(64 * kSmallWaves, 4) void gemm_small_kernel(
     const int8_t* __restrict__ As, const int8_t* __restrict__ Bs, int32_t* __restrict__ T, int8_t* __restrict__ L,
     const int32_t* __restrict__ eA, const int32_t* __restrict__ eB, int64_t m, int64_t n, int64_t mp, int64_t np, int64_t kp,
     int kt_total, int lds_bytes, double alpha, double beta, double* __restrict__ C, int64_t ldc, const Record* rec,
-    const int32_t* __restrict__ tile_S, Batch bt) {
+    const int32_t* __restrict__ tile_S, Batch bt, Fallback fb) {
     extern __shared__ __align__(16) uint8_t lds[];
     {
         const int64_t ws = bt.ws_at(blockIdx.z);
@@ -42,11 +44,14 @@ __global__ __launch_bounds__(64 * kSmallWaves, 4) void gemm_small_kernel(
         if (tile_S) tile_S = at_bytes(tile_S, ws);
         C += int64_t(blockIdx.z) * bt.c;
     }
-    if (rec->res.fallback) return;
-    const int S_all = rec->res.slices_used;
+    const int fallback = rec->res.fallback, S_all = rec->res.slices_used;
     const int ntm = int((m + kSmallTile - 1) / kSmallTile);
     const int tj = int(blockIdx.x) / ntm, ti = int(blockIdx.x) - tj * ntm;
     const int64_t i0 = int64_t(ti) * kSmallTile, j0 = int64_t(tj) * kSmallTile;
+    if (fallback) {
+        if (fb.A) fall_back<2, 2, kSmallWaves>(fb, bt, int(blockIdx.z), reinterpret_cast<double*>(lds), m, n, i0, j0, alpha, beta, C, ldc);
+        return;
+    }
     const int S = tile_S ? min(tile_S[(j0 / kTile) * (mp / kTile) + i0 / kTile], S_all) : S_all;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -226,12 +231,12 @@ bool prepare_gemm_small() {
 }
 
 void launch_gemm_small(hipStream_t st, const Workspace& w, const Problem& p, const LaunchPlan& lp, double alpha, double beta,
-                       double* C, int64_t ldc) {
+                       double* C, int64_t ldc, const Fallback& fb) {
     const int64_t tiles = lp.small_tiles(p);
     // two workgroups per CU where there are that many and the largest slice count leaves room for both
     const int lds = tiles * p.batch.count > p.num_cu && p.s_cap * kSumPlane <= kSmallLdsMax / 2 ? kSmallLdsMax / 2 : kSmallLdsMax;
     hipLaunchKernelGGL(gemm_small_kernel, dim3(unsigned(tiles), 1, unsigned(p.batch.count)), dim3(64 * kSmallWaves), lds, st, w.As, w.Bs, w.T, w.L, w.eA,
-                       w.eB, p.m, p.n, p.mp, p.np, p.kp, lp.kt, lds, alpha, beta, C, ldc, w.rec, p.tile_mode ? w.tile_S : nullptr, p.batch);
+                       w.eB, p.m, p.n, p.mp, p.np, p.kp, lp.kt, lds, alpha, beta, C, ldc, w.rec, p.tile_mode ? w.tile_S : nullptr, p.batch, fb);
 }
 
 }  // namespace oz

@@ -257,8 +257,15 @@ void launch_slice(hipStream_t st, const Operand& a, const Operand& b, const Work
 void tile_order_shape(const Problem& p, int& first, int& deal);
 // allows the slice GEMM its LDS on the current device (a property of the device: set when a handle is made for it)
 bool prepare_gemm_i8();
-// returns what the recomposition still has to put together; small calls are recomposed in the same launch (kDone)
-SplitPlan launch_gemm_i8(hipStream_t st, const Workspace& w, const Problem& p, double alpha, double beta, double* C, int64_t ldc);
+// Returns what the recomposition still has to put together; small calls are recomposed in the same launch (kDone).  fallback: what
+// such a launch needs to be the native product as well, if the verdict says so (A == nullptr: it has a launch of its own);
+// fell_back: it is.
+struct Fallback;
+SplitPlan launch_gemm_i8(hipStream_t st, const Workspace& w, const Problem& p, double alpha, double beta, double* C, int64_t ldc,
+                         const Fallback& fallback, bool& fell_back);
+// whether the native product of a guarded call is as fast on square tiles of this edge (32 or 64) in the last launch of the
+// emulated one as in its own, that launch counted
+bool f64_folds(const Problem& p, int64_t ld_max, int edge);
 void launch_recompose(hipStream_t st, const Workspace& w, const Problem& p, const SplitPlan& split, double alpha,
                       double beta, double* C, int64_t ldc);
 // rec == nullptr: run unconditionally; otherwise run only when rec->res.fallback != 0.

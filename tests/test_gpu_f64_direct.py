@@ -39,3 +39,24 @@ def test_small_tiles_keep_inf_and_nan_in_their_row_and_column(lib, m, n, k):
     for ta, tb in (("N", "N"), ("T", "T")):
         got, _, _ = run_gpu(g, h, A, B, 1.0, 0.0, None, ta, tb, mode=g.OZ_NATIVE)
         assert np.all(np.isfinite(got[:-1, :-1])) and np.all(np.isnan(got[:, -1])) and np.all(np.isinf(got[-1, :-1]))
+
+
+@pytest.mark.parametrize("m,n,k,opts", [
+    (1, 1, 1, dict(mode=1, max_bits=55)), (31, 33, 65, dict(mode=1, max_bits=55)), (200, 300, 261, dict(mode=0, heuristic=0)),
+    (512, 512, 512, dict(mode=0, heuristic=0, max_bits=103)), (64, 1500, 130, dict(mode=1, slices=12)),       # 32 x 32 tiles
+    (700, 800, 130, dict(mode=1, max_bits=55)), (705, 770, 66, dict(mode=0, heuristic=0, max_bits=103, tile_slices=1)),
+    (1100, 1030, 129, dict(mode=1, max_bits=55)), (2300, 2500, 70, dict(mode=1, max_bits=55)),               # 64 x 64; a launch of its own
+])
+@pytest.mark.parametrize("ta,tb", [("N", "N"), ("N", "T"), ("T", "N"), ("T", "T")])
+def test_guarded_call_falls_back_in_its_last_launch(lib, m, n, k, opts, ta, tb):
+    g, h = lib
+    rng = np.random.default_rng(m + k)
+    A, B, C = rng.standard_normal((m, k)), rng.standard_normal((k, n)), rng.standard_normal((m, n))
+    A[m // 2, k // 2] = np.nan
+    got, _, res = run_gpu(g, h, A, B, -1.5, 0.5, C, ta, tb, pad=3, **opts)
+    assert (res.fallback, res.reason, res.infnan) == (1, 1, 1)
+    rest = np.arange(m) != m // 2
+    assert np.all(np.isnan(got[m // 2]))
+    ref = -1.5 * (A[rest] @ B) + 0.5 * C[rest]
+    bound = 2 * (k + 3) * 2.0 ** -53 * (1.5 * (np.abs(A[rest]) @ np.abs(B)) + 0.5 * np.abs(C[rest]))
+    assert np.all(np.abs(got[rest] - ref) <= bound)
