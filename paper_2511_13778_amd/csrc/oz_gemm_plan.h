@@ -180,12 +180,12 @@ struct LaunchPlan {
         const int64_t small_all = small_tiles(p) * p.batch.count;
         const int64_t small_ns = small_all <= cus ? 2540 + kt * (416 + 19 * S + 12 * pairs)
                                                   : rounds_ns(small_all, 2 * cus, 2770 + 278 * S + kt * (550 + 4 * S + 16 * pairs));
-        if (small_ns < best) {
+        if (small_ns < best && small_tiles(p) * 512 <= kMaxGridThreads) {
             best = small_ns;
             small = true;
         }
         best = best * 88 / 100;
-        if (p.s_cap > kMidMaxSlices) return;
+        if (p.s_cap > kMidMaxSlices || p.m * p.n / (kMidTile * kMidTile) > kMaxGridThreads / 1024) return;
         const int64_t mid_all = ((p.m + kMidTile - 1) / kMidTile) * ((p.n + kMidTile - 1) / kMidTile) * p.batch.count;
         const int64_t mid_ns = rounds_ns(mid_all, cus, 1070 + 600 * S + kt * (357 + 37 * pairs)) + area * 279 / 100000;
         if (mid_ns < best) {
