@@ -19,7 +19,8 @@
 // split over several workgroups per tile (partial products added in a fixed order by dgemm_f64_reduce_kernel).  The tile edge
 // (128, or 64 with waves of 32x32), the small tiles of dgemm_f64_direct_kernel and the number of parts are chosen together by
 // an estimated time.
-// The kernel is launched on every call and returns at once unless the verdict selected it.
+// Behind a guarded call it is launched on every call and returns at once unless the verdict selected it; calls that are recomposed
+// on small tiles hold a direct tile in that launch instead where it is as fast (f64_folds).
 #include <algorithm>
 
 #include "oz_f64.h"
