@@ -17,30 +17,26 @@ namespace oz {
 
 // Tile of 16 NI x 16 NJ; grid: tiles x zsplit, part 0 of k carries k mod kpart as in dgemm_f64_kernel.
 template <bool AC, bool BC, int NI, int NJ>
-__global__ __launch_bounds__(256, NI * NJ <= 4 ? 4 : 2) void dgemm_f64_direct_kernel(
-    const Record* rec, KnownRecord known, int64_t m, int64_t n, int64_t k, double alpha, const double* __restrict__ A,
-    int64_t a_sr, int64_t a_sl, const double* __restrict__ B, int64_t b_sr, int64_t b_sl, double beta,
-    double* __restrict__ C, int64_t ldc, int ntm, int ntn, int zsplit, int64_t kpart, double* __restrict__ partial, Batch bt) {
+__global__ __launch_bounds__(256, NI * NJ <= 4 ? 4 : 2) void dgemm_f64_direct_kernel(F64Call c, F64Plan p) {
     constexpr int TI = 16 * NI, TJ = 16 * NJ;
     __shared__ double sums[f64_direct_lds(NI, NJ, 4) / 8];
-    f64_problem(bt, rec, A, B, C, partial);
-    if (rec && !rec->res.fallback) return;
-    if (blockIdx.x == 0 && threadIdx.x == 0) write_known_record(known, bt, int(blockIdx.z));
+    f64_problem(c.batch, c.rec, c.A, c.B, c.C, p.partial);
+    if (c.rec && !c.rec->res.fallback) return;
+    if (blockIdx.x == 0 && threadIdx.x == 0) write_known_record(c.known, c.batch, int(blockIdx.z));
     int ti, tj, z;
-    f64_tile_of(int(blockIdx.x), ntm, ntn, zsplit, ti, tj, z);
+    f64_tile_of(int(blockIdx.x), p.ntm, p.ntn, p.zsplit, ti, tj, z);
     int64_t kb;
-    f64_k_part(zsplit, z, kpart, k, kb);
-    const int64_t ldp = int64_t(ntm) * TI;
-    f64_direct_tile<AC, BC, NI, NJ, 4>(sums, m, n, k, kb, int64_t(ti) * TI, int64_t(tj) * TJ, alpha, A, a_sr, a_sl, B, b_sr, b_sl,
-                                       beta, C, ldc, zsplit > 1 ? partial + int64_t(z) * ntn * TJ * ldp : nullptr, ldp);
+    f64_k_part(p.zsplit, z, p.kpart, c.k, kb);
+    const int64_t ldp = int64_t(p.ntm) * TI;
+    f64_direct_tile<AC, BC, NI, NJ, 4>(sums, c.m, c.n, c.k, kb, int64_t(ti) * TI, int64_t(tj) * TJ, c.alpha, c.A, c.a_sr, c.a_sl, c.B,
+                                       c.b_sr, c.b_sl, c.beta, c.C, c.ldc,
+                                       p.zsplit > 1 ? p.partial + int64_t(z) * p.ntn * TJ * ldp : nullptr, ldp);
 }
 
 void launch_dgemm_f64_direct(hipStream_t st, const F64Call& c, const F64Plan& p) {
     const dim3 grid(unsigned(p.ntm) * unsigned(p.ntn) * unsigned(p.zsplit), 1, unsigned(c.batch.count)), block(256);
 #define OZ_DIRECT(AC, BC, NI, NJ)                                                                                        \
-    hipLaunchKernelGGL((dgemm_f64_direct_kernel<AC, BC, NI, NJ>), grid, block, 0, st, c.rec, c.known, c.m, c.n, c.k,      \
-                       c.alpha, c.A, c.a_sr, c.a_sl, c.B, c.b_sr, c.b_sl, c.beta, c.C, c.ldc, p.ntm, p.ntn, p.zsplit, \
-                       p.kpart, p.partial, c.batch)
+    hipLaunchKernelGGL((dgemm_f64_direct_kernel<AC, BC, NI, NJ>), grid, block, 0, st, c, p)
 #define OZ_DIRECT_T(NI, NJ)                                                                                              \
     if (p.ti == 16 * NI && p.tj == 16 * NJ) {                                                                              \
         if (c.a_rows && c.b_rows) OZ_DIRECT(true, true, NI, NJ);                                                           \
