@@ -3,64 +3,18 @@
 #pragma once
 
 #include "oz_f64.h"
+#include "oz_f64_walk.h"
 
 namespace oz {
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
-typedef double f64x2u __attribute__((ext_vector_type(2), aligned(8)));
 
-constexpr int kChunkK = 16;          // k per loop iteration: four MFMA steps
 constexpr int kSumBatch = 8;         // fragments whose sums are in LDS at a time
 
-// One operand of a wave: NF fragments of 16 rows.  MFMA step s of a chunk multiplies k = 4g + s for lane group g (the same set for
-// both operands), so a lane of a k-contiguous operand reads 16 bytes for two steps and four lanes 128 in a row.
-// The address is a wave-uniform base plus a 32-bit lane offset that never changes.
-template <bool ROWS_CONTIG, int NF>
-struct DirectSide {
-    const char* u;           // wave-uniform: row r0 of the operand at the k that is loaded next
-    uint32_t off[NF];        // this lane's row of fragment f and its k inside a chunk, bytes
-    int64_t sl;              // bytes from one k to the next
-    double v[4][NF];         // fragments of the four MFMA steps of a chunk
-
-    __device__ __forceinline__ void init(const double* X, int64_t stride_r, int64_t stride_l, int64_t r0, int64_t rows, int64_t k0) {
-        u = reinterpret_cast<const char*>(X + r0 * stride_r + k0 * stride_l);
-        sl = stride_l * 8;
-        const int lane = threadIdx.x & 63, g = lane >> 4;
-#pragma unroll
-        for (int f = 0; f < NF; ++f) {         // rows past the end are read from the last one; what they give is never stored
-            const int64_t r = min(int64_t(f * 16 + (lane & 15)), rows - 1 - r0);
-            off[f] = uint32_t(r * stride_r + int64_t(4 * g) * stride_l) * 8u;
-        }
-    }
-    // the first chunk: `len` (1..16) k, in the last ceil(len / 4) steps, four k a step
-    __device__ __forceinline__ void load_first(int len) {
-        const int g = (threadIdx.x & 63) >> 4, skip = 4 - (len + 3) / 4;
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const int kk = 4 * (s - skip) + g;                     // this lane's k, read at the nearest one there is
-            const int64_t at = int64_t(min(max(kk, 0), len - 1) - 4 * g) * sl;
-#pragma unroll
-            for (int f = 0; f < NF; ++f) {
-                const double x = *reinterpret_cast<const double*>(u + off[f] + at);
-                v[s][f] = kk >= 0 && kk < len ? x : 0.0;
-            }
-        }
-    }
-    // step s of the chunk at u; k-contiguous operands come two steps at a time
-    __device__ __forceinline__ void load(int s) {
-        if (ROWS_CONTIG) {
-            const char* us = u + s * sl;
-#pragma unroll
-            for (int f = 0; f < NF; ++f) v[s][f] = *reinterpret_cast<const double*>(us + off[f]);
-        } else if (s & 1) {
-#pragma unroll
-            for (int f = 0; f < NF; ++f) {
-                const f64x2u x = *reinterpret_cast<const f64x2u*>(u + (s - 1) * 8 + off[f]);
-                v[s - 1][f] = x[0];
-                v[s][f] = x[1];
-            }
-        }
-    }
+// What walk_share asks of the compiler on the device.
+struct KeepOrder {
+    __device__ __forceinline__ void order() const { __builtin_amdgcn_sched_barrier(0); }
+    __device__ __forceinline__ void scalar(int64_t& x) const { asm volatile("" : "+s"(x)); }
 };
 
 // bytes of LDS a tile needs
@@ -78,44 +32,22 @@ __device__ __forceinline__ void f64_direct_tile(double* sums, int64_t m, int64_t
     constexpr int NF = NI * NJ, NQ = (NF + WAVES - 1) / WAVES;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // this wave's share of k, in units of four
-    const int64_t quads = (k + 3) / 4;
-    const int64_t k_lo = quads * wave / WAVES * 4, k_hi = min(quads * (wave + 1) / WAVES * 4, k);
     f64x4 acc[NF];
 #pragma unroll
     for (int f = 0; f < NF; ++f) acc[f] = f64x4{0.0, 0.0, 0.0, 0.0};
-    if (k_lo < k_hi) {
-        const int first = int((k_hi - k_lo - 1) % kChunkK) + 1;
+    const WaveShare share = wave_share(k, wave, WAVES);
+    if (share.first > 0) {
         DirectSide<AC, NI> a;
         DirectSide<BC, NJ> b;
-        a.init(A, a_sr, a_sl, i0, m, kb + k_lo);
-        b.init(B, b_sr, b_sl, j0, n, kb + k_lo);
-        a.load_first(first);
-        b.load_first(first);
-        int64_t adv = first;
-        int skip = 4 - (first + 3) / 4;  // MFMA steps the first chunk does not need
-        for (int left = int((k_hi - k_lo - first) / kChunkK);; --left) {
-            if (left > 0) {              // otherwise the chunk is loaded again, for nobody
-                a.u += adv * a.sl;
-                b.u += adv * b.sl;
-            }
-            adv = kChunkK;
+        a.init(A, a_sr, a_sl, i0, m, kb + share.lo, lane);
+        b.init(B, b_sr, b_sl, j0, n, kb + share.lo, lane);
+        walk_share(share, a, b, lane, [&](int s) {
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                if (s >= skip) {
+            for (int fj = 0; fj < NJ; ++fj)
 #pragma unroll
-                    for (int fj = 0; fj < NJ; ++fj)
-#pragma unroll
-                        for (int fi = 0; fi < NI; ++fi)
-                            acc[fj * NI + fi] = __builtin_amdgcn_mfma_f64_16x16x4f64(b.v[s][fj], a.v[s][fi], acc[fj * NI + fi], 0, 0, 0);
-                }
-                a.load(s);
-                b.load(s);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            skip = 0;
-            if (left == 0) break;
-        }
+                for (int fi = 0; fi < NI; ++fi)
+                    acc[fj * NI + fi] = __builtin_amdgcn_mfma_f64_16x16x4f64(b.v[s][fj], a.v[s][fi], acc[fj * NI + fi], 0, 0, 0);
+        }, KeepOrder{});
     }
 
     // result register r of fragment f: j = (f / NI) * 16 + 4r + lane / 16, i = (f % NI) * 16 + lane % 16.  Fragment f is finished by wave

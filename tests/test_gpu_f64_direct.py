@@ -30,7 +30,8 @@ def test_small_tiles(lib, m, n, k, ta, tb):
 
 @pytest.mark.parametrize("m,n,k", [(50, 70, 21), (130, 100, 66)])
 def test_small_tiles_keep_inf_and_nan_in_their_row_and_column(lib, m, n, k):
-    # rows past the end are read from the last row and k past the end from the last k: neither may reach another element
+    # rows past the end are read from the last row; of k past the end (a first 16 that is not full, the only such) nothing is kept.
+    # Neither may reach another element.  That no load lies outside the operands is test_fp64_tiles_stay_inside_their_operands's.
     g, h = lib
     rng = np.random.default_rng(k)
     A, B = rng.standard_normal((m, k)), rng.standard_normal((k, n))

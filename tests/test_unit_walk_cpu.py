@@ -1,7 +1,8 @@
 """Launch geometry followed on the host (no GPU).  The walk of the slice GEMM's workgroups over the units of C: every unit
 that holds a row and a column of C is multiplied over every 64 of k exactly once, whatever the order, the split along
 k and the padding.  The scan's launches: none has more threads than a launch may have.  The ESC kernel's blocks: those
-that one row or column of the operands leaves open meet as many workgroups as there are."""
+that one row or column of the operands leaves open meet as many workgroups as there are.  The FP64 tiles straight from
+memory: no load lies outside the operands, and every k is multiplied once."""
 import itertools
 import os
 import subprocess
@@ -106,3 +107,20 @@ def test_blocks_of_one_row_or_column_are_spread_over_the_workgroups(tmp_path_fac
         assert wrong == 0, c
         # a block row has nbj blocks, a block column nbi: not far from an even share of either, for each workgroup
         assert most_row <= 3 * -(-nbj // grid) + 1 and most_col <= -(-nbi // grid), (c, most_row, most_col)
+
+
+@pytest.mark.parametrize("ar,br", list(itertools.product((0, 1), (0, 1))))
+def test_fp64_tiles_stay_inside_their_operands(tmp_path_factory, ar, br):
+    # the last tile of either side, whose rows end with the operand; a share of a wave may be empty, less than a 16 of k, one, more
+    run = host_program(tmp_path_factory, "host_f64_walk.cpp")
+    cases = [(m, n, k, 0, k, waves, ar, br, pad) for m, n, pad in ((1, 17, 0), (33, 31, 0), (48, 64, 5)) for k in range(1, 201) for waves in (4, 8)]
+    # parts of a split: the first carries the remainder, the others have a multiple of 16 each
+    for kt in (128, 129, 135, 200, 1000, 1033):
+        for parts in (2, 3):
+            per = kt // parts // 16 * 16
+            first = kt - (parts - 1) * per
+            for z in range(parts):
+                kb, k = (0, first) if z == 0 else (first + (z - 1) * per, per)
+                cases.append((33, 31, k, kb, kt, 4, ar, br, 0))
+    bad = [(c, r) for c, r in zip(cases, run(cases)) if r != (0, 0)]
+    assert not bad, (len(bad), len(cases), bad[:10])
