@@ -29,7 +29,6 @@ namespace oz {
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 
-constexpr int kDK = 16;
 constexpr int kDPad = 2;                        // doubles of padding per LDS row (see the bank note above)
 // The tile is T x T with T = 128 (the fast path) or T = 64 (outputs too small to give 128-tiles to
 // every CU).  Per thread and operand a K step has T/16 elements; a wave owns (T/2) x (T/2).
@@ -108,7 +107,7 @@ __device__ __forceinline__ void dg_store(const double (&v)[T / 16], double* lds)
 // rows in the (loop-invariant) lane offsets and k % 16 is taken as a short first K step, loaded by the
 // bounds-checked loader once per tile; the K loop itself is the same as in MODE 0.  MODE 2: the
 // bounds-checked loader with 64-bit indexing everywhere (operands whose leading dimension does not
-// fit the 32-bit offsets of the fast loads).
+// fit the 32-bit offsets of the fast loads, and k < 16, which has no full K step).
 template <bool A_ROWS_CONTIG, bool B_ROWS_CONTIG, int MODE, int T>
 __global__ __launch_bounds__(256, 2) void dgemm_f64_kernel(
     const Record* rec, KnownRecord known, int64_t m, int64_t n, int64_t k, double alpha, const double* __restrict__ A,
@@ -298,77 +297,10 @@ __global__ __launch_bounds__(256) void dgemm_f64_reduce_kernel(const Record* rec
     C[j * ldc + i] = out;
 }
 
-namespace {
-
-// Tiles a call can be cut into and what they cost, in us: a workgroup start + round per round of all CUs, and step per MFMA step of a
-// round (16 k in dgemm_f64_kernel, 4 k of each of the four waves in dgemm_f64_direct_kernel); first: per step of the call, for
-// the operands' way to the first workgroup of a CU.  Operands come out of the caches at 9 TB/s at most (4096^3 and 6144^3 on tiles of
-// 64 and less).  Fitted to 5879 timings of 126 shapes (50 to 8000, k to 65000, all four transposes, every tile, 1 to 16 parts): the
-// choice by these numbers is 3 % off the best one on average, 19 % at most, and 1.18 times as fast as the best choice among
-// the two tiles of dgemm_f64_kernel (at most 10 % slower).
-struct F64Tile {
-    bool direct;
-    int ti, tj;
-    double start, round, step, first;
-};
-constexpr F64Tile kF64Tiles[] = {
-    {false, 128, 128, 0.0, 7.42, 1.717, 0.167}, {false, 64, 64, 2.51, 1.69, 0.433, 0.336},
-    {true, 16, 16, 3.26, 0.38, 0.075, 0.018},   {true, 32, 32, 3.53, 0.94, 0.169, 0.0},
-    {true, 32, 64, 4.07, 2.00, 0.273, 0.0},     {true, 64, 32, 3.31, 2.56, 0.262, 0.008},
-    {true, 48, 64, 3.10, 3.95, 0.341, 0.039},   {true, 64, 48, 3.46, 3.47, 0.361, 0.027},
-};
-constexpr double kF64CacheBytesPerUs = 9e6;
-
-// Tile and number of parts of the k range.  With scratch memory at hand, k may be split over several workgroups per tile:
-// they leave partial products in the scratch memory and a second kernel adds them in the order of the parts (deterministic)
-// and applies alpha and beta: a launch of 4.5 us and zsplit + 2 passes over C at 4.5 TB/s.  A guarded call pays that launch
-// whether it falls back or not: 20 there.
-F64Plan choose_f64(const F64Call& c, int num_cu, void* scratch, size_t scratch_bytes, double* us_of = nullptr) {
-    F64Plan best{};
-    double best_us = 0.0;
-    const uint32_t m = uint32_t(c.m), n = uint32_t(c.n), cus = uint32_t(num_cu), problems = uint32_t(c.batch.count);
-    for (const F64Tile& t : kF64Tiles) {
-        if (!t.direct && c.k < kDK) continue;                // whose fast loads always fetch a full K step
-        const uint32_t ti = uint32_t(t.ti), tj = uint32_t(t.tj), ntm = (m + ti - 1) / ti, ntn = (n + tj - 1) / tj;
-        const uint64_t tiles64 = uint64_t(ntm) * ntn;
-        if (tiles64 > uint64_t(kMaxGridThreads) / 256) continue;
-        const uint32_t tiles = uint32_t(tiles64);            // of a problem
-        const uint64_t all = tiles64 * problems;
-        const double cache_us = double(all) * double(ti + tj) * double(c.k) * 8.0 / kF64CacheBytesPerUs;
-        const int64_t k_least = t.ti == 128 ? 256 : 64;      // what a part keeps at least
-        for (uint32_t z : {1u, 2u, 3u, 4u, 6u, 8u, 12u, 16u}) {
-            if (z > 1 && (scratch == nullptr || c.k < k_least * z || all * z > 4 * cus ||
-                          uint64_t(tiles) * z * ti * tj * 8 > scratch_bytes))
-                break;
-            const double rounds = double((all * z + cus - 1) / cus), steps = double(uint32_t(c.k + z * kDK - 1) / (z * kDK));
-            double us = std::max(t.start + rounds * (t.round + t.step * steps) + t.first * steps, cache_us);
-            if (z > 1) us += (c.rec ? 20.0 : 4.5) + double(z + 2) * double(m) * double(n) * double(problems) * 8.0 / 4.5e6;
-            if (best_us == 0.0 || us < best_us) {
-                best_us = us;
-                best = F64Plan{t.direct, t.ti, t.tj, int(ntm), int(ntn), int(z), z > 1 ? c.k / z / kDK * kDK : 0,
-                               static_cast<double*>(scratch)};
-            }
-        }
-    }
-    if (us_of) *us_of = best_us;
-    return best;
-}
-
-// operands cut out of a very large parent matrix, or a size of 2^31 and more: offsets inside a tile may not fit 32 bits (a lane's
-// own: at most 15 leading dimensions plus a row of the tile; its elements: up to 7 x 16 leading dimensions further on; in bytes)
-bool wide_offsets(int64_t m, int64_t n, int64_t k, int64_t ld_max) {
-    return (128 * ld_max + 256) * 8 >= (int64_t(1) << 32) || ((m | n | k) >> 31) != 0;
-}
-
-}  // namespace
-
 bool f64_folds(const Problem& p, int64_t ld_max, int edge) {
     if (wide_offsets(p.m, p.n, p.k, ld_max)) return false;
-    F64Call c{};
-    c.m = p.m; c.n = p.n; c.k = p.k;
-    c.batch = p.batch;
     double best_us = 0.0;
-    choose_f64(c, p.num_cu, nullptr, 0, &best_us);
+    choose_f64(F64Size{p.m, p.n, p.k, p.batch.count, false}, p.num_cu, nullptr, 0, &best_us);
     const double tiles = double((p.m + edge - 1) / edge) * double((p.n + edge - 1) / edge) * p.batch.count, steps = double((p.k + kDK - 1) / kDK);
     const double rounds = double(int64_t((tiles + p.num_cu - 1) / p.num_cu)), cache_us = tiles * (2 * edge) * double(p.k) * 8.0 / kF64CacheBytesPerUs;
     // 32 x 32 as in the table; 64 x 64 fitted to the same timings
@@ -385,7 +317,7 @@ void launch_dgemm_f64(hipStream_t st, const Record* rec, const KnownRecord& know
     // the fast loads keep every offset inside a K step of a tile in 32 bits; where they may not fit, the bounds-checked path indexes in 64
     const bool wide = wide_offsets(m, n, k, lda > ldb ? lda : ldb);
     F64Plan p{};
-    if (!wide) p = choose_f64(c, num_cu, scratch, scratch_bytes);
+    if (!wide) p = choose_f64(F64Size{m, n, k, batch.count, rec != nullptr}, num_cu, scratch, scratch_bytes);
     if (p.ti == 0) {
         const int T = ((m + 127) / 128) * ((n + 127) / 128) < num_cu ? 64 : 128;
         p = F64Plan{false, T, T, int((m + T - 1) / T), int((n + T - 1) / T), 1, 0, nullptr};
@@ -395,7 +327,7 @@ void launch_dgemm_f64(hipStream_t st, const Record* rec, const KnownRecord& know
     } else {
         const bool ac = c.a_rows, bc = c.b_rows;
         const dim3 grid(unsigned(p.ntm) * unsigned(p.ntn) * unsigned(p.zsplit), 1, unsigned(batch.count)), block(256);
-        const int mode = wide ? 2 : (((m % p.ti) || (n % p.tj) || (k % kDK)) ? 1 : 0);
+        const int mode = f64_mode(wide, m, n, k, p.ti, p.tj);
 #define OZ_DG_M(AC, BC, MODE, TT)                                                                              \
     hipLaunchKernelGGL((dgemm_f64_kernel<AC, BC, MODE, TT>), grid, block, 0, st, rec, known, m, n, k, alpha, A, c.a_sr, \
                        c.a_sl, B, c.b_sr, c.b_sl, beta, C, ldc, p.ntm, p.ntn, p.zsplit, p.kpart, p.partial, batch)

@@ -1,7 +1,7 @@
 // What the kernels of the native FP64 GEMM share: the call, how it is cut into workgroups, and which of them a workgroup is.
 #pragma once
 
-#include "oz_internal.h"
+#include "oz_f64_plan.h"
 
 namespace oz {
 
@@ -19,15 +19,6 @@ struct F64Call {
     int64_t ldc;
     bool a_rows, b_rows;   // rows (not k) contiguous
     Batch batch;
-};
-
-struct F64Plan {
-    bool direct;           // dgemm_f64_direct_kernel, otherwise dgemm_f64_kernel
-    int ti, tj;            // tile
-    int ntm, ntn;          // tiles
-    int zsplit;            // parts of k over workgroups
-    int64_t kpart;         // length of every part but the first
-    double* partial;       // [zsplit][ntn * tj][ntm * ti] partial products of a split
 };
 
 // Workgroup ids are dealt round-robin to the 8 XCDs; each XCD gets a contiguous range of a tile order in which 64 consecutive

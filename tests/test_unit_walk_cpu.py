@@ -124,3 +124,13 @@ def test_fp64_tiles_stay_inside_their_operands(tmp_path_factory, ar, br):
                 cases.append((33, 31, k, kb, kt, 4, ar, br, 0))
     bad = [(c, r) for c, r in zip(cases, run(cases)) if r != (0, 0)]
     assert not bad, (len(bad), len(cases), bad[:10])
+
+
+def test_fp64_product_of_less_than_a_k_step_never_loads_a_full_one(tmp_path_factory):
+    # through LDS only the bounds-checked loop takes k < 16; chosen are the tiles straight from memory, unless none fits the grid
+    run = host_program(tmp_path_factory, "host_f64_plan.cpp")
+    sizes = [(1, 1), (64, 64), (100, 3000), (7000, 7000), (1 << 20, 3), (1 << 22, 1 << 22)]
+    got = run([(m, n, k) for m, n in sizes for k in range(1, 16)])
+    assert {g[0] for g in got} == {2}
+    assert all(direct or ti == 0 for _, direct, ti in got) and got[0][1] == 1 and got[-1][2] == 0
+    assert [g[0] for g in run([(64, 64, 16), (64, 64, 17), (65, 64, 32), (1 << 22, 1, 16)])] == [0, 1, 1, 2]
