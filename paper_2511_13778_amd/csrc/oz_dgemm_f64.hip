@@ -300,7 +300,7 @@ __global__ __launch_bounds__(256) void dgemm_f64_reduce_kernel(const Record* rec
 bool f64_folds(const Problem& p, int64_t ld_max, int edge) {
     if (wide_offsets(p.m, p.n, p.k, ld_max)) return false;
     double best_us = 0.0;
-    choose_f64(F64Size{p.m, p.n, p.k, p.batch.count, false}, p.num_cu, nullptr, 0, &best_us);
+    choose_f64(F64Size{p.m, p.n, p.k, p.batch.count, false, false, 0, 0.0}, p.num_cu, 0, &best_us);
     const double tiles = double((p.m + edge - 1) / edge) * double((p.n + edge - 1) / edge) * p.batch.count, steps = double((p.k + kDK - 1) / kDK);
     const double rounds = double(int64_t((tiles + p.num_cu - 1) / p.num_cu)), cache_us = tiles * (2 * edge) * double(p.k) * 8.0 / kF64CacheBytesPerUs;
     // 32 x 32 as in the table; 64 x 64 fitted to the same timings
@@ -317,11 +317,12 @@ void launch_dgemm_f64(hipStream_t st, const Record* rec, const KnownRecord& know
     // the fast loads keep every offset inside a K step of a tile in 32 bits; where they may not fit, the bounds-checked path indexes in 64
     const bool wide = wide_offsets(m, n, k, lda > ldb ? lda : ldb);
     F64Plan p{};
-    if (!wide) p = choose_f64(F64Size{m, n, k, batch.count, rec != nullptr}, num_cu, scratch, scratch_bytes);
+    if (!wide) p = choose_f64(f64_size(m, n, k, batch.count, rec != nullptr, beta != 0.0, !ta, lda, tb, ldb), num_cu, scratch ? scratch_bytes : 0);
     if (p.ti == 0) {
         const int T = ((m + 127) / 128) * ((n + 127) / 128) < num_cu ? 64 : 128;
         p = F64Plan{false, T, T, int((m + T - 1) / T), int((n + T - 1) / T), 1, 0, nullptr};
     }
+    p.partial = static_cast<double*>(scratch);
     if (p.direct) {
         launch_dgemm_f64_direct(st, c, p);
     } else {

@@ -10,12 +10,19 @@ namespace oz {
 
 constexpr int kDK = 16;                         // K step of dgemm_f64_kernel
 
-// What the choice depends on.  guarded: behind a verdict that may not select the product.
+// What the choice depends on.
 struct F64Size {
     int64_t m, n, k;
     int problems;
-    bool guarded;
+    bool guarded;          // behind a verdict that may not select the product
+    bool beta;             // C is read
+    int k_contig;          // operands with k contiguous (0 to 2), and how many of them have their rows at addresses that share the
+    double near;           // caches' sets: 1 each for rows a multiple of 512 bytes apart, 0.7 of 128
 };
+inline F64Size f64_size(int64_t m, int64_t n, int64_t k, int problems, bool guarded, bool beta, bool a_rows, int64_t lda, bool b_rows, int64_t ldb) {
+    auto near = [](bool rows, int64_t ld) { return rows ? 0.0 : (ld % 64 == 0 ? 1.0 : (ld % 16 == 0 ? 0.7 : 0.0)); };
+    return F64Size{m, n, k, problems, guarded, beta, int(!a_rows) + int(!b_rows), near(a_rows, lda) + near(b_rows, ldb)};
+}
 
 struct F64Plan {
     bool direct;           // dgemm_f64_direct_kernel, otherwise dgemm_f64_kernel
@@ -26,53 +33,65 @@ struct F64Plan {
     double* partial;       // [zsplit][ntn * tj][ntm * ti] partial products of a split
 };
 
-// Tiles a call can be cut into and what they cost, in us: a workgroup start + round per round of all CUs, and step per MFMA step of a
-// round (16 k in dgemm_f64_kernel, 4 k of each of the four waves in dgemm_f64_direct_kernel); first: per step of the call, for
-// the operands' way to the first workgroup of a CU.  Operands come out of the caches at 9 TB/s at most (4096^3 and 6144^3 on tiles of
-// 64 and less).  Fitted to 5879 timings of 126 shapes (50 to 8000, k to 65000, all four transposes, every tile, 1 to 16 parts): the
-// choice by these numbers is 3 % off the best one on average, 19 % at most, and 1.18 times as fast as the best choice among
-// the two tiles of dgemm_f64_kernel (at most 10 % slower).
+// Tiles a call can be cut into and what they cost, in us: start, and per round of all CUs: round, more with beta, step per MFMA step
+// (16 k in dgemm_f64_kernel, 4 k of each of the four waves in dgemm_f64_direct_kernel); first: per step of the call, for the operands'
+// way to the first workgroup of a CU; c per million elements of C, more with beta.  Tiles straight from memory: per step and round
+// more for each operand with k contiguous, and for its rows near each other in the caches' sets, and so per round.  Tiles through LDS:
+// more where an edge is ragged, and per round where k has a short first step.  Operands come out of the caches at 9 TB/s at most.
+// A split of k costs a launch and 0.33 us a part (the sums are added one after the other), and passes over C.
+// Fitted to 9406 calls (2 to 8000, k 1 to 50000, all four transposes, beta zero and not), each timed on every tile, from k = 64 on with
+// 1 to 16 parts: the choice is 1.6 % off the best on average (a model without beta, layout and ragged edges, fitted to k of 50 and
+// more, was 4.7 % off; 1261 x 2649 x 18 with beta took 31.9 us on 128 x 128 tiles, now 17; 7732 x 2885 x 14 66.9 us, now 36).
 struct F64Tile {
     bool direct;
     int ti, tj;
-    double start, round, step, first;
+    double start, round, round_beta, step, first, c, c_beta;
+    double k_step, near_step, near_round;      // straight from memory
+    double ragged, short_round;                // through LDS
 };
 constexpr F64Tile kF64Tiles[] = {
-    {false, 128, 128, 0.0, 7.42, 1.717, 0.167}, {false, 64, 64, 2.51, 1.69, 0.433, 0.336},
-    {true, 16, 16, 3.26, 0.38, 0.075, 0.018},   {true, 32, 32, 3.53, 0.94, 0.169, 0.0},
-    {true, 32, 64, 4.07, 2.00, 0.273, 0.0},     {true, 64, 32, 3.31, 2.56, 0.262, 0.008},
-    {true, 48, 64, 3.10, 3.95, 0.341, 0.039},   {true, 64, 48, 3.46, 3.47, 0.361, 0.027},
+    {false, 128, 128, 4.70, 0.0, 1.055, 1.666, 0.238, 1.37, 3.38, 0.0, 0.0, 0.0, 0.58, 0.662},
+    {false, 64, 64, 3.95, 0.0, 0.773, 0.449, 0.296, 0.92, 0.91, 0.0, 0.0, 0.0, 0.56, 0.264},
+    {true, 16, 16, 4.61, 0.181, 0.053, 0.050, 0.007, 2.12, 0.0, 0.004, 0.018, 0.051, 0.0, 0.0},
+    {true, 32, 32, 4.43, 0.379, 0.065, 0.139, 0.0, 0.41, 0.23, 0.003, 0.014, 0.238, 0.0, 0.0},
+    {true, 32, 64, 4.49, 0.461, 0.179, 0.273, 0.0, 1.25, 0.25, 0.0, 0.006, 0.442, 0.0, 0.0},
+    {true, 64, 32, 4.46, 0.545, 0.159, 0.276, 0.0, 1.11, 0.23, 0.0, 0.004, 0.465, 0.0, 0.0},
+    {true, 48, 64, 4.65, 0.803, 0.414, 0.398, 0.0, 1.70, 0.17, 0.0, 0.0, 0.564, 0.0, 0.0},
+    {true, 64, 48, 4.61, 0.833, 0.369, 0.398, 0.0, 1.66, 0.12, 0.0, 0.0, 0.553, 0.0, 0.0},
 };
 constexpr double kF64CacheBytesPerUs = 9e6;
 
 // Tile and number of parts of the k range.  With scratch memory at hand, k may be split over several workgroups per tile:
 // they leave partial products in the scratch memory and a second kernel adds them in the order of the parts (deterministic)
-// and applies alpha and beta: a launch of 4.5 us and zsplit + 2 passes over C at 4.5 TB/s.  A guarded call pays that launch
-// whether it falls back or not: 20 there.
-inline F64Plan choose_f64(const F64Size& c, int num_cu, void* scratch, size_t scratch_bytes, double* us_of = nullptr) {
+// and applies alpha and beta.  A guarded call pays that launch whether it falls back or not: 15.5 us more there.
+// scratch_bytes 0: none.  The caller sets where the partial products go.
+inline F64Plan choose_f64(const F64Size& c, int num_cu, size_t scratch_bytes, double* us_of = nullptr) {
     F64Plan best{};
     double best_us = 0.0;
     const uint32_t m = uint32_t(c.m), n = uint32_t(c.n), cus = uint32_t(num_cu), problems = uint32_t(c.problems);
+    const double area = double(c.m) * double(c.n) * double(problems) * 1e-6;
     for (const F64Tile& t : kF64Tiles) {
-        if (!t.direct && c.k < kDK) continue;                // whose fast loads always fetch a full K step
         const uint32_t ti = uint32_t(t.ti), tj = uint32_t(t.tj), ntm = (m + ti - 1) / ti, ntn = (n + tj - 1) / tj;
         const uint64_t tiles64 = uint64_t(ntm) * ntn;
         if (tiles64 > uint64_t(kMaxGridThreads) / 256) continue;
         const uint32_t tiles = uint32_t(tiles64);            // of a problem
         const uint64_t all = tiles64 * problems;
+        const bool short_first = c.k % kDK != 0, ragged = short_first || m % ti != 0 || n % tj != 0;
         const double cache_us = double(all) * double(ti + tj) * double(c.k) * 8.0 / kF64CacheBytesPerUs;
+        const double per_call = t.start + (ragged ? t.ragged : 0.0) + area * (t.c + (c.beta ? t.c_beta : 0.0));
+        const double per_round = t.round + (c.beta ? t.round_beta : 0.0) + t.near_round * c.near + (short_first ? t.short_round : 0.0);
+        const double per_step = t.step + t.k_step * c.k_contig + t.near_step * c.near;
         const int64_t k_least = t.ti == 128 ? 256 : 64;      // what a part keeps at least
         for (uint32_t z : {1u, 2u, 3u, 4u, 6u, 8u, 12u, 16u}) {
-            if (z > 1 && (scratch == nullptr || c.k < k_least * z || all * z > 4 * cus ||
+            if (z > 1 && (scratch_bytes == 0 || c.k < k_least * z || all * z > 4 * cus ||
                           uint64_t(tiles) * z * ti * tj * 8 > scratch_bytes))
                 break;
             const double rounds = double((all * z + cus - 1) / cus), steps = double(uint32_t(c.k + z * kDK - 1) / (z * kDK));
-            double us = std::max(t.start + rounds * (t.round + t.step * steps) + t.first * steps, cache_us);
-            if (z > 1) us += (c.guarded ? 20.0 : 4.5) + double(z + 2) * double(m) * double(n) * double(problems) * 8.0 / 4.5e6;
+            double us = std::max(per_call + rounds * (per_round + per_step * steps) + t.first * steps, cache_us);
+            if (z > 1) us += (c.guarded ? 17.0 : 1.5) + 0.33 * double(z) + 2.5 * double(z + 2) * area;
             if (best_us == 0.0 || us < best_us) {
                 best_us = us;
-                best = F64Plan{t.direct, t.ti, t.tj, int(ntm), int(ntn), int(z), z > 1 ? c.k / z / kDK * kDK : 0,
-                               static_cast<double*>(scratch)};
+                best = F64Plan{t.direct, t.ti, t.tj, int(ntm), int(ntn), int(z), z > 1 ? c.k / z / kDK * kDK : 0, nullptr};
             }
         }
     }

@@ -38,6 +38,11 @@ def scan_grid(tmp_path_factory):
     return host_program(tmp_path_factory, "host_scan_grid.cpp")
 
 
+@pytest.fixture(scope="module")
+def f64_plan(tmp_path_factory):
+    return host_program(tmp_path_factory, "host_f64_plan.cpp")
+
+
 def test_every_unit_and_part_is_taken_exactly_once(walk):
     # odd and even numbers of blocks, padding-only quadrants on either edge, odd and even numbers of parts, small and large
     # workspaces (which decide between parts with slots and atomics), more units than CUs, a split last round
@@ -126,11 +131,20 @@ def test_fp64_tiles_stay_inside_their_operands(tmp_path_factory, ar, br):
     assert not bad, (len(bad), len(cases), bad[:10])
 
 
-def test_fp64_product_of_less_than_a_k_step_never_loads_a_full_one(tmp_path_factory):
-    # through LDS only the bounds-checked loop takes k < 16; chosen are the tiles straight from memory, unless none fits the grid
-    run = host_program(tmp_path_factory, "host_f64_plan.cpp")
-    sizes = [(1, 1), (64, 64), (100, 3000), (7000, 7000), (1 << 20, 3), (1 << 22, 1 << 22)]
-    got = run([(m, n, k) for m, n in sizes for k in range(1, 16)])
-    assert {g[0] for g in got} == {2}
-    assert all(direct or ti == 0 for _, direct, ti in got) and got[0][1] == 1 and got[-1][2] == 0
-    assert [g[0] for g in run([(64, 64, 16), (64, 64, 17), (65, 64, 32), (1 << 22, 1, 16)])] == [0, 1, 1, 2]
+def test_fp64_product_of_less_than_a_k_step_never_loads_a_full_one(f64_plan):
+    # tiles through LDS take k < 16 in the bounds-checked loop only
+    sizes = [(1, 1), (64, 64), (100, 3000), (7000, 7000), (4000, 4000), (1 << 20, 3), (1 << 22, 1 << 22)]
+    got = f64_plan([(m, n, k, 1, 0, beta, 0) for m, n in sizes for k in range(1, 16) for beta in (0, 1)])
+    assert {mode for direct, _, _, mode in got} == {2}
+    assert {direct for direct, *_ in got} == {0, 1} and got[-1][1] == 0
+    assert [mode for *_, mode in f64_plan([(64, 64, 16, 1, 1, 0, 0), (64, 64, 17, 1, 1, 0, 0), (65, 64, 32, 1, 1, 0, 0), (64, 64, 64, 1, 1, 0, 1 << 22)])][1:] == [1, 1, 2]
+
+
+def test_fp64_tile_is_near_the_fastest_measured(f64_plan):
+    # a hundred calls timed on every tile; among them those on which a choice that knew neither beta nor the operands' layout, and
+    # nothing of k below 50, took the wrong one
+    forms = [(0, 128, 128), (0, 64, 64), (1, 16, 16), (1, 32, 32), (1, 32, 64), (1, 64, 32), (1, 48, 64), (1, 64, 48)]
+    rows = [ln.split() for ln in open(os.path.join(ROOT, "tests", "golden", "f64_tile_times.txt")) if not ln.startswith("#")]
+    got = f64_plan([(*r[:3], int(r[3] == "N"), int(r[4] == "T"), int(float(r[5]) != 0), 0) for r in rows])
+    off = [float(r[6 + forms.index(g[:3])]) / min(map(float, r[6:])) for r, g in zip(rows, got)]
+    assert max(off) < 1.4 and sum(off) / len(off) < 1.05, (max(off), sum(off) / len(off))
