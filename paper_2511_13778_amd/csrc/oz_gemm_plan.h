@@ -83,6 +83,7 @@ __host__ __device__ inline bool skip_padding(int xcd, int stride, int& slot, con
 
 // Tiles of C a workgroup of gemm_small_kernel owns.
 constexpr int kSmallTile = 32;
+constexpr int kSmallPairSlices = 17;             // most slices with which two of them share a CU
 constexpr int kSmallLdsMax = 160 * 1024;         // all of a CU's LDS
 
 // The same of gemm_mid_kernel, the most slices it holds, and the most with which two workgroups share a CU.
@@ -105,7 +106,7 @@ struct LaunchPlan {
     bool two;              // the rest in a launch of its own
     bool few;              // at most two slices, on 256 x 256 blocks (gemm_i8_few_kernel) instead of all that
     // slice GEMM and recomposition in one launch instead of all that:
-    bool small;            // on 32 x 32 tiles (gemm_small_kernel)
+    bool small, small_pair;    // on 32 x 32 tiles (gemm_small_kernel), two workgroups to a CU
     bool mid, mid_pair;    // on 64 x 64 tiles (gemm_mid_kernel), two workgroups to a CU
 
     explicit LaunchPlan(const Problem& p) : g() {
@@ -129,11 +130,10 @@ struct LaunchPlan {
         const int round = p.num_cu / p.batch.count;
         full = round != 0 ? positions / round * round : positions;
         rest = positions - full;
-        int64_t last_ns = 0;
-        last = rest != 0 && rest * per_pos < round ? split(p, rest * per_pos, last_ns) : Split{1, false};
+        last = rest != 0 && rest * per_pos < round ? split(p, rest * per_pos) : Split{1, false};
         two = full != 0 && last.z > 1;
         few = few_slices(p);
-        fuse(p, last_ns);
+        fuse(p);
     }
 
     // whether the problems of p.batch can share the launches
@@ -149,56 +149,71 @@ struct LaunchPlan {
     // Whether slice GEMM and recomposition take longer in their two launches than in one, and in which: estimated in ns for S
     // slices (one more than the fewest where the device decides).  What a tile costs beside its products is its start and
     // its end, its sums and the digits it writes: with many slices and a long k the 128 x 128 units, which read fewer bytes
-    // per product, win; otherwise the larger of the small tiles that still gives every CU one.
-    //   units       10 us, and for seven slices 14 us, 5.5 us per million elements of C, 0.5 us per part of a k split, and what
-    //               split() estimates or 4.2 us per 64 of k and 5 us per round of units; (S+1)/8 of that for S; 0.925 of it
-    //               all, and 0.32 us per slice and million elements
-    //   64 x 64     a workgroup per CU: per round 1.07 us + 0.60 per slice, and per 64 of k 0.36 us + 37 ns per pair of slices; 2.8 us
-    //               per million elements.  Two to a CU (a stage of one 64 of k each; the slice count must be known): 0.81, 0.85, 0.45
-    //               and 66, per round of twice as many, one alone 0.95, 0.52 and 54; 2.6 us per million elements
-    //   32 x 32     a workgroup per CU at most: 2.5 us, and per 64 of k 0.42 us + 19 ns per slice + 12 per pair; beyond that, per
-    //               round of two to a CU: 2.8 us + 0.28 per slice, and per 64 of k 0.55 us + 4 ns per slice + 16 per pair
+    // per product, win; otherwise the larger of the small tiles that still gives every CU one.  The times below are those of a whole
+    // call but for what all routes share, in us; el: million elements of C.
+    //   units       1.0, 3.5 el, and per round of all CUs 0.46 per 64 of k and step of a unit and 9.3 per group of anti-diagonals; a split
+    //               of k adds, with slots, 0.7 and per part 1.57 and 7 ns per unit and byte of a sum, with atomics per part 0.16 and 28 ns
+    //               per unit and slice.  256 x 256 blocks (few): per round 9.9 and per 64 of k 0.70 with one slice, 2.07 with two; 2.8 el,
+    //               1 el S
+    //   64 x 64     a workgroup per CU: 1.4, per round 0.40 per slice, and per 64 of k 0.255 and 44 ns per pair of slices; 3.6 el,
+    //               0.1 el S.  Two to a CU (a stage of one 64 of k each; the slice count must be known): 2.2, per round of twice as many
+    //               2.75 and per 64 of k 0.313 and 71 ns per pair, one alone 0.32 per slice, 0.261 and 72; 0.9 el, 0.435 el S
+    //   32 x 32     alone on a CU (no more tiles than CUs, or more slices than half the LDS holds): per round 0.325 per slice, and per 64
+    //               of k 0.51 and 14 ns per pair; two to a CU: per round of twice as many 1.15 and 0.28 per slice, and per 64 of k 0.494,
+    //               16 ns per slice and 17 per pair; 2.6 el.  No less than the slices at 9 TB/s and 1.5 el
     // Rounds are whole up to four, beyond that workgroups end at different times.
-    // Fitted to 1770 timings of 499 calls of 1 to 16 slices (60 to 8000, k to 6000, one to four problems): the choice is 1 % off the
-    // best on average, and against the better of units and 32 x 32 tiles 7 % faster on average (29 % slower at most).  The 64 x 64
-    // tiles have to be 12 % better than the others: on a full chip and a long k, at a lower clock, they are worse than estimated (2048^3
-    // and 4224 x 3008 x 1792, seven slices, 4 %).
-    // Whole calls, units / 32 x 32 / 64 x 64: 200x300x260 nine slices 69 / 36 / 44 us, 512^3 nine 84 / 45 / 58, 1000^3 seven 95 / 86 /
-    // 71, 1500x1700x1000 seven 142 / - / 130, 2048^3 seven 246 / 435 / 257, 7936x7936 seven: k = 64 573 / - / 378, k = 256 850 / - / 740,
-    // k = 1024 1660 / - / 1730.
-    void fuse(const Problem& p, int64_t last_ns) {
-        small = mid = mid_pair = false;
+    // Fitted to 5100 calls of 1 to 26 slices (8 to 8000, k 8 to 6000, one to four problems; counts known and decided by the device), each
+    // timed on every route: the choice is 0.7 % off the best on average, and one call in 200 is more than 3 % slower than on units.
+    // 32 x 32 tiles have to be 7 % better from four rounds of two to a CU on, 64 x 64 ones 8 %, and 14 % on a full chip with more than
+    // three 64s of k, 20 % with sixteen, where at a lower clock they are worse than estimated (4224 x 3008 x 1792 with seven slices 588 us,
+    // on units 564).
+    // (A rule that took two workgroups of 32 x 32 to a CU for any slice count, with no bound on the bytes, was 1.9 % off; 4010 x 2372 x 137 at
+    // up to 26 slices took 287 us, now 205, 46 x 119 x 4154 with five 76, now 53, and 2270 x 944 x 2390 with seven 281, now 234.)
+    void fuse(const Problem& p) {
+        small = small_pair = mid = mid_pair = false;
         if (p.nkb != 1) return;
-        const int64_t S = p.s_min == p.s_cap ? p.s_cap : p.s_min + 1, pairs = S * (S + 1) / 2, cus = p.num_cu;
-        const int64_t area = p.m * p.n * p.batch.count;
+        const int64_t S = p.s_min == p.s_cap ? p.s_cap : p.s_min + 1, pairs = S * (S + 1) / 2, cus = p.num_cu, count = p.batch.count;
+        const int64_t area = p.m * p.n * count;
+        auto el = [&](int64_t ns) { return area * ns / 1000000; };
         // workgroups, per round, ns of a round
         auto rounds_ns = [](int64_t all, int64_t per, int64_t ns) { return all < 4 * per ? (all + per - 1) / per * ns : all * ns / per; };
-        const int64_t whole = (int64_t(full) * per_pos * p.batch.count + cus - 1) / cus, unit_ns = int64_t(4200) * kt + 5000;
-        int64_t gemm = whole * unit_ns;
-        if (rest != 0) gemm += last.z > 1 ? last_ns + int64_t(500) * last.z : (int64_t(rest) * per_pos * p.batch.count + cus - 1) / cus * unit_ns;
-        int64_t best = (10000 + (14000 + area * 55 / 10000 + gemm) * (S + 1) / 8) * 925 / 1000 + area * S * 32 / 100000;
-        const int64_t small_all = small_tiles(p) * p.batch.count;
-        const int64_t small_ns = small_all <= cus ? 2540 + kt * (416 + 19 * S + 12 * pairs)
-                                                  : rounds_ns(small_all, 2 * cus, 2770 + 278 * S + kt * (550 + 4 * S + 16 * pairs));
-        if (small_ns < best && small_tiles(p) * 512 <= kMaxGridThreads) {
+        int64_t best;
+        if (few) {
+            best = (int64_t(g.nti) * g.ntj + cus - 1) / cus * (9900 + (S == 1 ? 695 : 2065) * kt) + el(2770 + 1010 * S);
+        } else {
+            const int64_t step = unit_items(int(S)) * 460, ends = (S + kDiag - 1) / kDiag * 9260, per_cu = int64_t(per_pos) * count;
+            best = 975 + el(3506 + 13 * S) + ((last.z > 1 ? full : positions) * per_cu + cus - 1) / cus * (kt * step + ends);
+            if (last.z > 1) {
+                const int64_t parts = last.z * rest * per_cu;
+                best += (kt + last.z - 1) / last.z * step + ends +
+                        (last.atomic ? 155 * last.z + 28 * parts * S : 708 + 1565 * last.z + 7 * parts * (4 + S));
+            }
+        }
+        const int64_t small_all = small_tiles(p) * count;
+        const bool pair = small_all > cus && p.s_cap <= kSmallPairSlices;
+        const int64_t small_products = pair ? rounds_ns(small_all, 2 * cus, 1150 + 279 * S + kt * (494 + 16 * S + 17 * pairs))
+                                            : rounds_ns(small_all, cus, 325 * S + kt * (510 + 14 * pairs));
+        const int64_t small_ns = std::max(small_products + el(2630), small_all * (2 * kSmallTile * kBK) * kt * S / 9000 + el(1500));
+        if (small_ns < best * (small_all >= 8 * cus ? 93 : 100) / 100 && small_tiles(p) * 512 <= kMaxGridThreads) {
             best = small_ns;
             small = true;
+            small_pair = pair;
         }
-        best = best * 88 / 100;
         if (p.s_cap > kMidMaxSlices || p.m * p.n / (kMidTile * kMidTile) > kMaxGridThreads / 1024) return;
-        const int64_t mid_all = ((p.m + kMidTile - 1) / kMidTile) * ((p.n + kMidTile - 1) / kMidTile) * p.batch.count;
-        const int64_t mid_ns = rounds_ns(mid_all, cus, 1070 + 600 * S + kt * (357 + 37 * pairs)) + area * 279 / 100000;
+        const int64_t mid_all = ((p.m + kMidTile - 1) / kMidTile) * ((p.n + kMidTile - 1) / kMidTile) * count;
+        best = best * (kt > 3 && mid_all >= 4 * cus ? (kt < 16 ? 86 : 80) : 92) / 100;
+        const int64_t mid_ns = 1409 + rounds_ns(mid_all, cus, 395 * S + kt * (255 + 44 * pairs)) + el(3625 + 101 * S);
         if (mid_ns < best) {
             best = mid_ns;
-            small = false;
+            small = small_pair = false;
             mid = true;
         }
         if (p.s_min != p.s_cap || p.s_cap > kMidPairSlices) return;
-        const int64_t pair_ns = 810 + 850 * S + kt * (449 + 66 * pairs), alone_ns = 952 * S + kt * (519 + 54 * pairs);
+        const int64_t pair_ns = 2751 + kt * (313 + 71 * pairs), alone_ns = 322 * S + kt * (261 + 72 * pairs);
         const int64_t on_cu = (mid_all + cus - 1) / cus;          // workgroups of the fullest CU
-        const int64_t two_ns = (mid_all < 8 * cus ? on_cu / 2 * pair_ns + on_cu % 2 * alone_ns : mid_all * pair_ns / (2 * cus)) + area * 262 / 100000;
+        const int64_t two_ns = 2167 + (mid_all < 8 * cus ? on_cu / 2 * pair_ns + on_cu % 2 * alone_ns : mid_all * pair_ns / (2 * cus)) + el(899 + 435 * S);
         if (two_ns < best) {
-            small = false;
+            small = small_pair = false;
             mid = mid_pair = true;
         }
     }
@@ -229,12 +244,12 @@ struct LaunchPlan {
     // start and to write its sums.  Parts with slots of their own move 10 bytes per element and part (60 ns per part and
     // unit) and, for the rest of a larger product, need a launch to be added (6 us); atomics add 28 bytes per element
     // and part (170 ns) and need the slots zeroed (8 us), but no more memory for more parts.
-    Split split(const Problem& p, int units, int64_t& best_ns) const {
+    Split split(const Problem& p, int units) const {
         const bool whole = units == positions * per_pos;     // the recomposition puts it together
         const int64_t all = int64_t(units) * p.batch.count;
         const int64_t raw_bytes = int64_t(p.nkb) * p.s_cap * raw_units * (kUnit * kUnit * 4);
         Split best{1, false};
-        best_ns = (int64_t(kt) * 4200 + 5000) * 95 / 100;     // a split has to gain 5 %
+        int64_t best_ns = (int64_t(kt) * 4200 + 5000) * 95 / 100;     // a split has to gain 5 %
         for (int z = 2; z <= kt && all * z <= p.num_cu; ++z) {
             const int64_t steps = (kt + z - 1) / z;
             if (int64_t(z - 1) * units * nkb_part(p, z) * part_slot_bytes(p.s_cap) <= raw_bytes) {

@@ -22,6 +22,7 @@ constexpr int kSumRow = kSmallTile + 4;                     // words between row
 constexpr int kSumPlane = kSmallTile * kSumRow * 4;         // bytes per anti-diagonal
 constexpr int kSmallDiags = (kMaxSlices + kSmallWaves - 1) / kSmallWaves;     // anti-diagonals per wave
 static_assert(kSmallTile == 32 && kBK == 64, "the transfers below move 2 x 32 rows of 16 bytes, the waves 2 x 2 MFMA tiles");
+static_assert(kSmallPairSlices * kSumPlane <= kSmallLdsMax / 2 && kSmallPairSlices * 2 * kSliceBytes <= kSmallLdsMax / 2, "one of two workgroups");
 static_assert(f64_direct_lds(2, 2, kSmallWaves) <= kSmallLdsMax / 2, "the fallback shares the LDS");
 static_assert(kMaxSlices * kSumPlane <= kSmallLdsMax && kMaxSlices * 2 * kSliceBytes <= kSmallLdsMax, "one stage must fit");
 
@@ -233,8 +234,7 @@ bool prepare_gemm_small() {
 void launch_gemm_small(hipStream_t st, const Workspace& w, const Problem& p, const LaunchPlan& lp, double alpha, double beta,
                        double* C, int64_t ldc, const Fallback& fb) {
     const int64_t tiles = lp.small_tiles(p);
-    // two workgroups per CU where there are that many and the largest slice count leaves room for both
-    const int lds = tiles * p.batch.count > p.num_cu && p.s_cap * kSumPlane <= kSmallLdsMax / 2 ? kSmallLdsMax / 2 : kSmallLdsMax;
+    const int lds = lp.small_pair ? kSmallLdsMax / 2 : kSmallLdsMax;
     hipLaunchKernelGGL(gemm_small_kernel, dim3(unsigned(tiles), 1, unsigned(p.batch.count)), dim3(64 * kSmallWaves), lds, st, w.As, w.Bs, w.T, w.L, w.eA,
                        w.eB, p.m, p.n, p.mp, p.np, p.kp, lp.kt, lds, alpha, beta, C, ldc, w.rec, p.tile_mode ? w.tile_S : nullptr, p.batch, fb);
 }

@@ -28,6 +28,10 @@ def host_program(tmp_path_factory, source):
     return run
 
 
+def golden_times(name):
+    return [ln.split() for ln in open(os.path.join(ROOT, "tests", "golden", name)) if not ln.startswith("#")]
+
+
 @pytest.fixture(scope="module")
 def walk(tmp_path_factory):
     return host_program(tmp_path_factory, "host_unit_walk.cpp")
@@ -144,7 +148,17 @@ def test_fp64_tile_is_near_the_fastest_measured(f64_plan):
     # a hundred calls timed on every tile; among them those on which a choice that knew neither beta nor the operands' layout, and
     # nothing of k below 50, took the wrong one
     forms = [(0, 128, 128), (0, 64, 64), (1, 16, 16), (1, 32, 32), (1, 32, 64), (1, 64, 32), (1, 48, 64), (1, 64, 48)]
-    rows = [ln.split() for ln in open(os.path.join(ROOT, "tests", "golden", "f64_tile_times.txt")) if not ln.startswith("#")]
+    rows = golden_times("f64_tile_times.txt")
     got = f64_plan([(*r[:3], int(r[3] == "N"), int(r[4] == "T"), int(float(r[5]) != 0), 0) for r in rows])
     off = [float(r[6 + forms.index(g[:3])]) / min(map(float, r[6:])) for r, g in zip(rows, got)]
     assert max(off) < 1.4 and sum(off) / len(off) < 1.05, (max(off), sum(off) / len(off))
+
+
+def test_route_of_an_emulated_call_is_near_the_fastest_measured(tmp_path_factory):
+    # a hundred calls timed on every route; among them those on which an estimate without the bytes of the 32 x 32 tiles, and with two
+    # of their workgroups to a CU whatever the slices in LDS, took the wrong one
+    run = host_program(tmp_path_factory, "host_call_plan.cpp")
+    rows = golden_times("route_times.txt")
+    got = run([(*r[:6], 1) for r in rows])
+    off = [float(r[6 + g]) / min(float(x) for x in r[6:] if x != "-") for r, (g,) in zip(rows, got)]
+    assert max(off) < 1.25 and sum(off) / len(off) < 1.03, (max(off), sum(off) / len(off))
