@@ -297,17 +297,6 @@ __global__ __launch_bounds__(256) void dgemm_f64_reduce_kernel(const Record* rec
     C[j * ldc + i] = out;
 }
 
-bool f64_folds(const Problem& p, int64_t ld_max, int edge) {
-    if (wide_offsets(p.m, p.n, p.k, ld_max)) return false;
-    double best_us = 0.0;
-    choose_f64(F64Size{p.m, p.n, p.k, p.batch.count, false, false, 0, 0.0}, p.num_cu, 0, &best_us);
-    const double tiles = double((p.m + edge - 1) / edge) * double((p.n + edge - 1) / edge) * p.batch.count, steps = double((p.k + kDK - 1) / kDK);
-    const double rounds = double(int64_t((tiles + p.num_cu - 1) / p.num_cu)), cache_us = tiles * (2 * edge) * double(p.k) * 8.0 / kF64CacheBytesPerUs;
-    // 32 x 32 as in the table; 64 x 64 fitted to the same timings
-    const double us = edge == 32 ? 3.53 + rounds * (0.94 + 0.169 * steps) : 3.79 + rounds * (4.10 + 0.465 * steps) + 0.023 * steps;
-    return std::max(us, cache_us) <= best_us + 4.5;
-}
-
 void launch_dgemm_f64(hipStream_t st, const Record* rec, const KnownRecord& known, bool ta, bool tb, int64_t m, int64_t n, int64_t k,
                       double alpha, const double* A, int64_t lda, const double* B, int64_t ldb, double beta,
                       double* C, int64_t ldc, int num_cu, const Batch& batch, void* scratch, size_t scratch_bytes) {

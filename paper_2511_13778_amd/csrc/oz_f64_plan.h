@@ -105,6 +105,30 @@ inline bool wide_offsets(int64_t m, int64_t n, int64_t k, int64_t ld_max) {
     return (128 * ld_max + 256) * 8 >= (int64_t(1) << 32) || ((m | n | k) >> 31) != 0;
 }
 
+// Whether the native product of a guarded call is as fast on square tiles of this edge (32: gemm_small_kernel, 64: gemm_mid_kernel) in the
+// last launch of the emulated call as in launches of its own: whatever choose_f64 takes for it, with the call's scratch memory.
+// alone: the emulated kernel's LDS leaves one workgroup to a CU.
+// In us: launches of its own take 1.6, 0.9 of choose_f64's estimate and 4.6 for the sums of a split; tiles as below, and no less than the
+// operands at the rate of the caches.  Fitted to 2250 calls that fall back (16 to 8000, k 20 to 6000), timed with either: half of
+// them fold, 0.4 % slower than the better one on average, and fifteen by more than 5 % than in launches of their own.  (Against the
+// unsplit product alone, without the layout and with two workgroups to a CU throughout, 519 x 123 x 4328 took 72 us, now 41, and
+// 811 x 1516 x 101 36, now 26.)
+inline bool f64_folds(const F64Size& c, int num_cu, size_t scratch_bytes, int edge, bool alone) {
+    double own_us = 0.0;
+    const F64Plan own = choose_f64(c, num_cu, scratch_bytes, &own_us);
+    if (own.zsplit > 1) own_us -= 15.5;                  // what a guarded call is charged beyond the launch
+    own_us = 1.6 + 0.9 * own_us + (own.zsplit > 1 ? 4.6 : 0.0);
+    const int64_t tiles = ((c.m + edge - 1) / edge) * ((c.n + edge - 1) / edge) * c.problems;
+    const int64_t per_round = edge == 64 || alone ? num_cu : 2 * num_cu;
+    const double rounds = double((tiles + per_round - 1) / per_round), steps = double((c.k + kDK - 1) / kDK);
+    const double area = double(c.m) * double(c.n) * double(c.problems) * 1e-6, beta = c.beta ? 1.0 : 0.0;
+    double us;
+    if (edge == 64) us = rounds * (4.87 + 0.458 * steps + 0.46 * beta + 1.01 * c.near) + 2.17 * area;
+    else if (alone) us = 0.82 + rounds * (2.23 + (0.118 + 0.017 * c.k_contig) * steps + 0.30 * beta + 0.93 * c.near) + 2.82 * area;
+    else us = 0.60 + 0.045 * steps + rounds * ((0.224 + 0.053 * c.k_contig) * steps + 0.42 * beta + 0.71 * c.near) + 5.90 * area;
+    return std::max(us, double(tiles) * (2 * edge) * double(c.k) * 8.0 / kF64CacheBytesPerUs) <= own_us;
+}
+
 // Form of dgemm_f64_kernel's K loop: 0 and 1 load full K steps through 32-bit offsets (1: edge tiles, and a short first step),
 // 2 checks bounds with 64-bit indexing in every step.  k < 16 has no full step to load.
 inline int f64_mode(bool wide, int64_t m, int64_t n, int64_t k, int ti, int tj) {

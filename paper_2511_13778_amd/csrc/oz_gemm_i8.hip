@@ -752,8 +752,13 @@ SplitPlan launch_gemm_i8(hipStream_t st, const Workspace& w, const Problem& p, d
                          const Fallback& fallback, bool& fell_back) {
     const LaunchPlan lp(p);
     Fallback fb = fallback;
-    if (fb.A && (lp.small || lp.mid))
-        fell_back = f64_folds(p, std::max(std::max(fb.a_sr, fb.a_sl), std::max(fb.b_sr, fb.b_sl)), lp.small ? kSmallTile : kMidTile);
+    if (fb.A && (lp.small || lp.mid)) {
+        const int64_t lda = std::max(fb.a_sr, fb.a_sl), ldb = std::max(fb.b_sr, fb.b_sl);       // one of either is 1
+        const F64Size size = f64_size(p.m, p.n, p.k, p.batch.count, true, beta != 0.0, fb.a_rows, lda, fb.b_rows, ldb);
+        const size_t scratch = size_t(reinterpret_cast<uint8_t*>(w.tile_span) - reinterpret_cast<uint8_t*>(w.As));
+        fell_back = !wide_offsets(p.m, p.n, p.k, std::max(lda, ldb)) &&
+                    f64_folds(size, p.num_cu, scratch, lp.small ? kSmallTile : kMidTile, lp.small && !lp.small_pair);
+    }
     if (!fell_back) fb.A = nullptr;
     if (lp.small) {
         launch_gemm_small(st, w, p, lp, alpha, beta, C, ldc, fb);

@@ -263,9 +263,6 @@ bool prepare_gemm_i8();
 struct Fallback;
 SplitPlan launch_gemm_i8(hipStream_t st, const Workspace& w, const Problem& p, double alpha, double beta, double* C, int64_t ldc,
                          const Fallback& fallback, bool& fell_back);
-// whether the native product of a guarded call is as fast on square tiles of this edge (32 or 64) in the last launch of the
-// emulated one as in its own, that launch counted
-bool f64_folds(const Problem& p, int64_t ld_max, int edge);
 void launch_recompose(hipStream_t st, const Workspace& w, const Problem& p, const SplitPlan& split, double alpha,
                       double beta, double* C, int64_t ldc);
 // rec == nullptr: run unconditionally; otherwise run only when rec->res.fallback != 0.

@@ -46,7 +46,8 @@ def test_small_tiles_keep_inf_and_nan_in_their_row_and_column(lib, m, n, k):
     (1, 1, 1, dict(mode=1, max_bits=55)), (31, 33, 65, dict(mode=1, max_bits=55)), (200, 300, 261, dict(mode=0, heuristic=0)),
     (512, 512, 512, dict(mode=0, heuristic=0, max_bits=103)), (64, 1500, 130, dict(mode=1, slices=12)),       # 32 x 32 tiles
     (700, 800, 130, dict(mode=1, max_bits=55)), (705, 770, 66, dict(mode=0, heuristic=0, max_bits=103, tile_slices=1)),
-    (1100, 1030, 129, dict(mode=1, max_bits=55)), (2300, 2500, 70, dict(mode=1, max_bits=55)),               # 64 x 64; a launch of its own
+    (1100, 1030, 129, dict(mode=1, max_bits=55)), (2300, 2500, 70, dict(mode=1, max_bits=55)),       # 64 x 64 (the second); launches of their own
+    (700, 750, 100, dict(mode=1, max_bits=55)), (1127, 501, 18, dict(mode=1, slices=4)), (1180, 768, 236, dict(mode=1, slices=1)),     # 64 x 64, one and two to a CU
 ])
 @pytest.mark.parametrize("ta,tb", [("N", "N"), ("N", "T"), ("T", "N"), ("T", "T")])
 def test_guarded_call_falls_back_in_its_last_launch(lib, m, n, k, opts, ta, tb):

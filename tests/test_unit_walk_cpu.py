@@ -162,3 +162,18 @@ def test_route_of_an_emulated_call_is_near_the_fastest_measured(tmp_path_factory
     got = run([(*r[:6], 1) for r in rows])
     off = [float(r[6 + g]) / min(float(x) for x in r[6:] if x != "-") for r, (g,) in zip(rows, got)]
     assert max(off) < 1.25 and sum(off) / len(off) < 1.03, (max(off), sum(off) / len(off))
+
+
+def test_fallback_is_where_it_is_near_the_fastest_measured(tmp_path_factory):
+    # guarded calls that fall back, timed with the FP64 product in its own launch and in the last launch of the emulated call; among
+    # them those where a rule that knew no split of k and no workgroup alone on its CU took the wrong one
+    run = host_program(tmp_path_factory, "host_f64_fold.cpp")
+    cases, times = [], []
+    for r in golden_times("fold_times.txt"):
+        for edge, t in ((32, r[8]), (64, r[9])):
+            if t != "-":
+                cases.append((*r[:3], int(r[3] == "N"), int(r[4] == "T"), int(float(r[5]) != 0), r[6], edge, 1 << 26))
+                times.append((float(r[7]), float(t)))
+    off = [t[g] / min(t) for t, (g,) in zip(times, run(cases))]
+    assert max(off) < 1.25 and sum(off) / len(off) < 1.02, (max(off), sum(off) / len(off))
+    assert 0.1 < sum(g for g, in run(cases)) / len(cases) < 0.9
