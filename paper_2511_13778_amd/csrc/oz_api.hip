@@ -146,6 +146,13 @@ void make_layout(const Problem& p, oz_layout_t& L) {
     L.total_bytes = off;
 }
 
+// What the native GEMM may use for the partial products of a k split: the slice planes, the aggregated products and the raw sums, none
+// of which a call that falls back reads or writes.  They lie behind each other from off_As on.
+size_t f64_scratch_bytes(const Problem& p, const oz_layout_t& L) {
+    const size_t off_raw = align_up(L.off_L + size_t(p.nkb) * (p.s_cap - 1) * p.np * p.mp);
+    return align_up(off_raw + size_t(p.nkb) * p.s_cap * p.raw_slots * kTile * kTile * 4) - L.off_As;
+}
+
 Workspace bind(void* base, const Problem& p, const oz_layout_t& L) {
     uint8_t* b = static_cast<uint8_t*>(base);
     Workspace w;
@@ -166,7 +173,7 @@ Workspace bind(void* base, const Problem& p, const oz_layout_t& L) {
     w.L = reinterpret_cast<int8_t*>(b + L.off_L);
     const size_t off_raw = align_up(L.off_L + size_t(p.nkb) * (p.s_cap - 1) * p.np * p.mp);
     w.raw = reinterpret_cast<int32_t*>(b + off_raw);
-    w.tile_span = reinterpret_cast<int32_t*>(b + align_up(off_raw + size_t(p.nkb) * p.s_cap * p.raw_slots * kTile * kTile * 4));
+    w.tile_span = reinterpret_cast<int32_t*>(b + L.off_As + f64_scratch_bytes(p, L));
     w.tile_S = reinterpret_cast<int32_t*>(b + L.off_tileS);
     return w;
 }
@@ -386,10 +393,8 @@ oz_status_t dgemm_impl(oz_handle_t h, void* stream, char transa, char transb, in
     hipStream_t st = static_cast<hipStream_t>(stream);
     const Workspace w = bind(workspace, p, L);
     StageClock clk(h, st, timed);
-    // what the native GEMM may use for the partial products of a k split: the slice planes, the
-    // aggregated products and the raw sums, none of which a call that falls back reads or writes
     void* const f64_scratch = w.As;
-    const size_t f64_scratch_bytes = batch.count > batch.lanes ? 0 : size_t(reinterpret_cast<uint8_t*>(w.tile_span) - reinterpret_cast<uint8_t*>(w.As));
+    const size_t f64_bytes = batch.count > batch.lanes ? 0 : f64_scratch_bytes(p, L);
 
     if (k == 0 || alpha == 0.0) {
         // BLAS convention: nothing to multiply
@@ -405,14 +410,14 @@ oz_status_t dgemm_impl(oz_handle_t h, void* stream, char transa, char transb, in
 
     if (opts->mode == OZ_NATIVE) {
         for (int s = 0; s <= 5; ++s) clk.done(s);
-        launch_dgemm_f64(st, nullptr, KnownRecord{w.rec, result, known_verdict(p, *opts, 0)}, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, h->num_cu, batch, f64_scratch, f64_scratch_bytes);
+        launch_dgemm_f64(st, nullptr, KnownRecord{w.rec, result, known_verdict(p, *opts, 0)}, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, h->num_cu, batch, f64_scratch, f64_bytes);
         clk.done(6);
         return hipGetLastError() == hipSuccess ? OZ_OK : OZ_ERR_HIP;
     }
 
     if (native_unscanned(*h, *opts, m, n, k)) {
         for (int s = 0; s <= 5; ++s) clk.done(s);
-        launch_dgemm_f64(st, nullptr, KnownRecord{w.rec, result, known_verdict(p, *opts, 3)}, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, h->num_cu, batch, f64_scratch, f64_scratch_bytes);
+        launch_dgemm_f64(st, nullptr, KnownRecord{w.rec, result, known_verdict(p, *opts, 3)}, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, h->num_cu, batch, f64_scratch, f64_bytes);
         clk.done(6);
         return hipGetLastError() == hipSuccess ? OZ_OK : OZ_ERR_HIP;
     }
@@ -433,7 +438,7 @@ oz_status_t dgemm_impl(oz_handle_t h, void* stream, char transa, char transb, in
     clk.done(4);
     if (split.kind != KSplit::kDone) launch_recompose(st, w, p, split, alpha, beta, C, ldc);
     clk.done(5);
-    if (guarded && !fell_back) launch_dgemm_f64(st, w.rec, KnownRecord{}, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, h->num_cu, batch, f64_scratch, f64_scratch_bytes);
+    if (guarded && !fell_back) launch_dgemm_f64(st, w.rec, KnownRecord{}, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, h->num_cu, batch, f64_scratch, f64_bytes);
     clk.done(6);
     return hipGetLastError() == hipSuccess ? OZ_OK : OZ_ERR_HIP;
 }
@@ -476,13 +481,19 @@ struct ZLayout {
     int workspaces;
 };
 
-// Whether the four real products share their launches: each alone would leave much of the chip idle.  They need planes for four
-// products then and, emulated, a workspace each; 256 MiB bounds what that adds.  workspaces: how many.
-bool zgemm_shares(const oz_handle& h, const oz_opts_t& o, int64_t m, int64_t n, int64_t k, size_t real_ws, int& workspaces) {
+// Whether the four real products share their launches: each alone would leave much of the chip idle.  They need two more planes then
+// and, emulated, three more workspaces, of up to 256 MiB each.  workspaces: how many in all.  Native ones have no room for a split of k
+// then, and share where they take no longer without one than four launches with it (661 x 426 x 19376: 1010 us shared, 937 split).
+bool zgemm_shares(const oz_handle& h, const oz_opts_t& o, bool ta, bool tb, int64_t m, int64_t n, int64_t k, size_t real_ws, int& workspaces) {
     workspaces = 1;
     Problem p;
     if (k == 0 || m == 0 || n == 0 || !make_problem(h, o, m, n, k, p)) return false;
-    if (o.mode == OZ_NATIVE || native_unscanned(h, o, m, n, k)) return ((m + 127) / 128) * ((n + 127) / 128) < h.num_cu;
+    if (o.mode == OZ_NATIVE || native_unscanned(h, o, m, n, k)) {
+        if (((m + 127) / 128) * ((n + 127) / 128) >= h.num_cu) return false;
+        oz_layout_t L;
+        make_layout(p, L);
+        return f64_together(f64_size(m, n, k, 1, false, false, !ta, ta ? k : m, tb, tb ? n : k), 4, 1, h.num_cu, f64_scratch_bytes(p, L));
+    }
     workspaces = 4;
     p.batch.count = 4;
     return real_ws <= (size_t(256) << 20) && can_batch(p);
@@ -505,7 +516,7 @@ bool make_zlayout(oz_handle_t h, char ta_real, char tb_real, int64_t m, int64_t 
     z.off_pi = off; off += p;
     if (four) off += p;
     z.workspaces = 1;
-    if (four && !zgemm_shares(*h, *opts, m, n, k, real_ws, z.workspaces)) return false;
+    if (four && !zgemm_shares(*h, *opts, ta_real == 'T', tb_real == 'T', m, n, k, real_ws, z.workspaces)) return false;
     z.off_ws = off; off += align_up(real_ws) * size_t(z.workspaces);
     z.real_ws = real_ws;
     z.total = off;
@@ -608,13 +619,19 @@ oz_status_t oz_dgemm_strided_batched(oz_handle_t h, void* stream, char transa, c
         if (lanes < 1) lanes = 1;
     }
     // Problems that are small enough share their launches, as many as there are workspaces; native products that nothing is
-    // decided about on the device need none, only the k split does (not where there are 32 x 32 tiles for all CUs without).
+    // decided about on the device need none, only a split of k does: a launch for all of them, unless groups that split take less time
+    // (319 x 588 x 11522, twelve problems, room for four: 1114 us in one launch, 986 in groups).
     if (lanes > 1 && k > 0 && alpha != 0.0) {
         Problem p;
         if (!make_problem(*h, *opts, m, n, k, p)) return OZ_ERR_ARG;
         const bool native = opts->mode == OZ_NATIVE || native_unscanned(*h, *opts, m, n, k);
         int64_t group = lanes;
-        if (native && ((m + 31) / 32) * ((n + 31) / 32) * batch_count >= h->num_cu) group = std::min<int64_t>(batch_count, 4096);
+        if (native && batch_count > lanes) {
+            oz_layout_t L;
+            make_layout(p, L);
+            const int64_t all = std::min<int64_t>(batch_count, 4096);
+            if (f64_together(f64_size(m, n, k, 1, false, beta != 0.0, !ta, lda, tb, ldb), int(all), lanes, h->num_cu, f64_scratch_bytes(p, L))) group = all;
+        }
         p.batch.count = int(std::min<int64_t>(group, batch_count));
         if (native || can_batch(p)) {
             oz_status_t status = OZ_OK;

@@ -129,6 +129,18 @@ inline bool f64_folds(const F64Size& c, int num_cu, size_t scratch_bytes, int ed
     return std::max(us, double(tiles) * (2 * edge) * double(c.k) * 8.0 / kF64CacheBytesPerUs) <= own_us;
 }
 
+// Whether `all` products of one shape go into one launch, without scratch memory, or `at_once` at a time with a split of k for each
+// where that pays.  A launch that cannot split has to be 15 % better: whole-k tiles of one workgroup each end far apart (524 x 591 x 27591,
+// four products: 1799 us in one launch, estimated 1381; 1594 split, one after the other).
+inline bool f64_together(F64Size c, int all, int at_once, int num_cu, size_t scratch_bytes) {
+    double one_us = 0.0, group_us = 0.0;
+    c.problems = all;
+    choose_f64(c, num_cu, 0, &one_us);
+    c.problems = at_once;
+    const F64Plan group = choose_f64(c, num_cu, scratch_bytes, &group_us);
+    return one_us <= group_us * double((all + at_once - 1) / at_once) * (group.zsplit > 1 ? 0.85 : 1.0);
+}
+
 // Form of dgemm_f64_kernel's K loop: 0 and 1 load full K steps through 32-bit offsets (1: edge tiles, and a short first step),
 // 2 checks bounds with 64-bit indexing in every step.  k < 16 has no full step to load.
 inline int f64_mode(bool wide, int64_t m, int64_t n, int64_t k, int ti, int tj) {

@@ -177,3 +177,13 @@ def test_fallback_is_where_it_is_near_the_fastest_measured(tmp_path_factory):
     off = [t[g] / min(t) for t, (g,) in zip(times, run(cases))]
     assert max(off) < 1.25 and sum(off) / len(off) < 1.02, (max(off), sum(off) / len(off))
     assert 0.1 < sum(g for g, in run(cases)) / len(cases) < 0.9
+
+
+def test_native_products_share_a_launch_unless_a_split_of_k_is_faster(tmp_path_factory):
+    # one launch for more products than workspaces has no memory for a split.  Measured in one launch and split: 12 of 319x588x11522, four at
+    # a time, 1114 and 986 us; the four of a complex 661x426x19376 1010 and 937, of 524x591x27591 1799 and 1594
+    run = host_program(tmp_path_factory, "host_f64_together.cpp")
+    split = [(319, 588, 11522, 1, 1, 12, 4, 36 << 20), (661, 426, 19376, 1, 0, 4, 1, 40 << 20), (524, 591, 27591, 0, 0, 4, 1, 46 << 20)]
+    whole = [(96, 80, 112, 1, 0, 9, 4, 4 << 20), (500, 400, 300, 1, 0, 16, 2, 8 << 20), (100, 100, 2000, 1, 1, 24, 2, 6 << 20),
+             (1000, 900, 700, 0, 0, 4, 1, 16 << 20)]
+    assert [r for r, in run(split + whole)] == [0] * 3 + [1] * 4
