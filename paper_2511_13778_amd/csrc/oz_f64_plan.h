@@ -51,7 +51,7 @@ struct F64Tile {
 };
 constexpr F64Tile kF64Tiles[] = {
     {false, 128, 128, 4.70, 0.0, 1.055, 1.666, 0.238, 1.37, 3.38, 0.0, 0.0, 0.0, 0.58, 0.662},
-    {false, 64, 64, 3.95, 0.0, 0.773, 0.449, 0.296, 0.92, 0.91, 0.0, 0.0, 0.0, 0.56, 0.264},
+    {false, 64, 64, 3.95, 0.0, 0.45, 0.449, 0.296, 0.92, 0.91, 0.0, 0.0, 0.0, 0.56, 0.264},
     {true, 16, 16, 4.61, 0.181, 0.053, 0.050, 0.007, 2.12, 0.0, 0.004, 0.018, 0.051, 0.0, 0.0},
     {true, 32, 32, 4.43, 0.379, 0.065, 0.139, 0.0, 0.41, 0.23, 0.003, 0.014, 0.238, 0.0, 0.0},
     {true, 32, 64, 4.49, 0.461, 0.179, 0.273, 0.0, 1.25, 0.25, 0.0, 0.006, 0.442, 0.0, 0.0},
@@ -60,10 +60,11 @@ constexpr F64Tile kF64Tiles[] = {
     {true, 64, 48, 4.61, 0.833, 0.369, 0.398, 0.0, 1.66, 0.12, 0.0, 0.0, 0.553, 0.0, 0.0},
 };
 constexpr double kF64CacheBytesPerUs = 9e6;
+constexpr double kGuardedSplitUs = 15.5;        // charged for a split where the launch that adds its parts is paid by calls that do not fall back
 
 // Tile and number of parts of the k range.  With scratch memory at hand, k may be split over several workgroups per tile:
 // they leave partial products in the scratch memory and a second kernel adds them in the order of the parts (deterministic)
-// and applies alpha and beta.  A guarded call pays that launch whether it falls back or not: 15.5 us more there.
+// and applies alpha and beta.
 // scratch_bytes 0: none.  The caller sets where the partial products go.
 inline F64Plan choose_f64(const F64Size& c, int num_cu, size_t scratch_bytes, double* us_of = nullptr) {
     F64Plan best{};
@@ -86,9 +87,14 @@ inline F64Plan choose_f64(const F64Size& c, int num_cu, size_t scratch_bytes, do
             if (z > 1 && (scratch_bytes == 0 || c.k < k_least * z || all * z > 4 * cus ||
                           uint64_t(tiles) * z * ti * tj * 8 > scratch_bytes))
                 break;
-            const double rounds = double((all * z + cus - 1) / cus), steps = double(uint32_t(c.k + z * kDK - 1) / (z * kDK));
+            // 128 x 128, no operand with k contiguous: the two workgroups of a CU keep step, and where the last rounds are an odd one the
+            // pairs that start together leave half of the CUs without any (513 to 768 tiles take as long as 1024: 2703 x 4171 x 3943 1842 us,
+            // on 64 x 64 tiles 1560)
+            uint64_t rounds_whole = (all * z + cus - 1) / cus;
+            if (t.ti == 128 && c.k_contig == 0 && rounds_whole > 1) rounds_whole += rounds_whole & 1;
+            const double rounds = double(rounds_whole), steps = double(uint32_t(c.k + z * kDK - 1) / (z * kDK));
             double us = std::max(per_call + rounds * (per_round + per_step * steps) + t.first * steps, cache_us);
-            if (z > 1) us += (c.guarded ? 17.0 : 1.5) + 0.33 * double(z) + 2.5 * double(z + 2) * area;
+            if (z > 1) us += 1.5 + (c.guarded ? kGuardedSplitUs : 0.0) + 0.33 * double(z) + 2.5 * double(z + 2) * area;
             if (best_us == 0.0 || us < best_us) {
                 best_us = us;
                 best = F64Plan{t.direct, t.ti, t.tj, int(ntm), int(ntn), int(z), z > 1 ? c.k / z / kDK * kDK : 0, nullptr};
@@ -99,8 +105,10 @@ inline F64Plan choose_f64(const F64Size& c, int num_cu, size_t scratch_bytes, do
     return best;
 }
 
-// operands cut out of a very large parent matrix, or a size of 2^31 and more: offsets inside a tile may not fit 32 bits (a lane's
-// own: at most 15 leading dimensions plus a row of the tile; its elements: up to 7 x 16 leading dimensions further on; in bytes)
+// operands cut out of a very large parent matrix, or a size of 2^31 and more: offsets inside a tile may not fit 32 bits, in bytes.
+// Tiles through LDS: a lane's own is at most 15 leading dimensions plus a row of the tile, its elements lie up to 7 x 16 leading
+// dimensions further on.  Tiles straight from memory: a lane's own is at most 63 leading dimensions (the last row of 64, k contiguous)
+// plus 12 of k, or 12 leading dimensions plus a row; what a step adds is kept in 64 bits.
 inline bool wide_offsets(int64_t m, int64_t n, int64_t k, int64_t ld_max) {
     return (128 * ld_max + 256) * 8 >= (int64_t(1) << 32) || ((m | n | k) >> 31) != 0;
 }
@@ -116,7 +124,7 @@ inline bool wide_offsets(int64_t m, int64_t n, int64_t k, int64_t ld_max) {
 inline bool f64_folds(const F64Size& c, int num_cu, size_t scratch_bytes, int edge, bool alone) {
     double own_us = 0.0;
     const F64Plan own = choose_f64(c, num_cu, scratch_bytes, &own_us);
-    if (own.zsplit > 1) own_us -= 15.5;                  // what a guarded call is charged beyond the launch
+    if (own.zsplit > 1) own_us -= kGuardedSplitUs;
     own_us = 1.6 + 0.9 * own_us + (own.zsplit > 1 ? 4.6 : 0.0);
     const int64_t tiles = ((c.m + edge - 1) / edge) * ((c.n + edge - 1) / edge) * c.problems;
     const int64_t per_round = edge == 64 || alone ? num_cu : 2 * num_cu;

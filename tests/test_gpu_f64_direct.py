@@ -28,6 +28,19 @@ def test_small_tiles(lib, m, n, k, ta, tb):
     assert np.all(np.abs(got - ref) <= bound)
 
 
+@pytest.mark.parametrize("m,n,k", [(705, 800, 1), (710, 801, 5), (768, 832, 15), (1900, 1700, 13)])
+@pytest.mark.parametrize("ta,tb", [("N", "N"), ("N", "T"), ("T", "N"), ("T", "T")])
+def test_less_than_a_k_step_through_lds(lib, m, n, k, ta, tb):
+    # outputs of this size and a k below 16 take, without beta, 64 x 64 tiles through LDS in the bounds-checked loop
+    g, h = lib
+    rng = np.random.default_rng(m + k)
+    A, B = rng.standard_normal((m, k)), rng.standard_normal((k, n))
+    got, _, res = run_gpu(g, h, A, B, -1.5, 0.0, None, ta, tb, pad=3, mode=g.OZ_NATIVE)
+    assert res.fallback == 1
+    bound = 2 * (k + 3) * 2.0 ** -53 * 1.5 * (np.abs(A) @ np.abs(B))
+    assert np.all(np.abs(got + 1.5 * (A @ B)) <= bound)
+
+
 @pytest.mark.parametrize("m,n,k", [(50, 70, 21), (130, 100, 66)])
 def test_small_tiles_keep_inf_and_nan_in_their_row_and_column(lib, m, n, k):
     # rows past the end are read from the last row; of k past the end (a first 16 that is not full, the only such) nothing is kept.
