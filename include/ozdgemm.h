@@ -187,7 +187,7 @@ oz_status_t oz_dgemm_static(oz_handle_t handle, void* stream, char transa, char 
  * Concurrency follows the workspace: with room for q >= 2 times oz_dgemm_workspace_bytes(...)
  * (each rounded up to 256 bytes) the problems run q at a time, q <= OZ_BATCH_LANES: problems that leave much of
  * the GPU idle share their launches on `stream` (native products of a whole batch where nothing is decided on the
- * device), larger ones run on streams the handle owns, forked from and joined to `stream` with events (so the call
+ * device, unless q at a time with k split are faster), larger ones run on streams the handle owns, forked from and joined to `stream` with events (so the call
  * still only enqueues, and everything it enqueued is ordered before later work on `stream`); with room for one they
  * run one after the other on `stream`.  Stage timing (oz_profile_*) records serial batches only.
  * Two batched calls on one handle must not overlap in time (they share the handle's streams).

@@ -18,7 +18,7 @@
 // run the same loop with clamped rows and a short first K step; where the caller provides scratch memory, k may be
 // split over several workgroups per tile (partial products added in a fixed order by dgemm_f64_reduce_kernel).  The tile edge
 // (128, or 64 with waves of 32x32), the small tiles of dgemm_f64_direct_kernel and the number of parts are chosen together by
-// an estimated time.
+// an estimated time (choose_f64).
 // Behind a guarded call it is launched on every call and returns at once unless the verdict selected it; calls that are recomposed
 // on small tiles hold a direct tile in that launch instead where it is as fast (f64_folds).
 #include <algorithm>

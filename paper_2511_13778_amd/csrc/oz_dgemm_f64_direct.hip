@@ -8,14 +8,14 @@
 // in the loop, the loads of a chunk have three MFMA steps to arrive, and the tile edges can be any multiples of 16: the form
 // whose tiles come out even on the CUs is taken.  The four waves' sums meet in LDS at the end and are added in wave order
 // (deterministic), so k is split four ways without a second launch and without a pass over partial products.
-// Whole calls, against LDS tiles of 64 with k split over workgroups: 1000 x 1300 x 777 53 -> 44 us, 512^3 17 -> 10,
-// 600 x 700 x 500 29 -> 14, 200 x 300 x 5000 45 -> 29, 64 x 64 x 7000 35 -> 13.  Large products stay on the LDS tiles (4096^3
+// Whole calls, against LDS tiles with k split over workgroups: 1000 x 1300 x 777 63 -> 44 us, 512^3 27 -> 10,
+// 600 x 700 x 500 28 -> 15, 200 x 300 x 5000 45 -> 24, 64 x 64 x 7000 34 -> 11.  Large products stay on the LDS tiles (4096^3
 // 1866 us, here 1918): an operand fragment is read by four waves there, here by one.
 #include "oz_f64_direct.h"
 
 namespace oz {
 
-// Tile of 16 NI x 16 NJ; grid: tiles x zsplit, part 0 of k carries k mod kpart as in dgemm_f64_kernel.
+// Tile of 16 NI x 16 NJ; grid: tiles x zsplit, the parts of k as in dgemm_f64_kernel (f64_k_part).
 template <bool AC, bool BC, int NI, int NJ>
 __global__ __launch_bounds__(256, NI * NJ <= 4 ? 4 : 2) void dgemm_f64_direct_kernel(F64Call c, F64Plan p) {
     constexpr int TI = 16 * NI, TJ = 16 * NJ;

@@ -12,7 +12,8 @@
 //   SETS = 2   8 waves (two sets share the groups), up to 16 slices, all of the LDS: more than one stage up to 10 slices
 // What bounds it at a short k is memory: digits, leading words and C are 26 bytes per element (7936 x 7936, seven slices: 280 us
 // plus 95 per 64 of k; units 500 plus 73).  At a long one the load of a stage, which only the other workgroup covers.
-// Measured, whole calls: 7936x7936x256 814 -> 716 us, 16 problems of 512^3 271 -> 235, 1000^3 (seven slices) 86 -> 71.
+// Measured, whole calls, against units: 7936x7936x256 814 -> 717 us, 1000^3 (seven slices, no guards) 86 -> 53; 16 problems of 512^3, which
+// also share their launches, 540 -> 229.
 #include "oz_f64_direct.h"
 #include "oz_gemm_device.h"
 

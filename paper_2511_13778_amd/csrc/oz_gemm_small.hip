@@ -9,7 +9,8 @@
 // chain, the powers of two and alpha / beta follow from LDS in the same launch.  Up to 16 times as many workgroups as units.
 // The price is LDS bandwidth: four MFMAs per four fragments read, twice what the matrix unit's rate allows.  So
 // it is the shorter way only while the units would leave the chip idle (LaunchPlan::fuse).
-// 200 x 300 x 260 with nine slices: slice GEMM and recomposition 33 + 14 us, now 10 (the call 72 -> 37).
+// 200 x 300 x 260 with nine slices: slice GEMM and recomposition 33 + 14 us, now 10 (the call 72 -> 31 us, with the
+// fallback in the same launch and one launch less before it).
 #include "oz_f64_direct.h"
 #include "oz_gemm_device.h"
 

@@ -183,7 +183,7 @@ __host__ __device__ inline int64_t k_block_length(int S) {
 }
 
 // ---- geometry of the scan's launches --------------------------------------------------
-constexpr int kScanBlocksPerWg = 4;    // ESC blocks a workgroup covers (measured at 8192^3: 1, 2 or 8 are 4-13 % slower)
+constexpr int kScanBlocksPerWg = 4;    // ESC blocks a workgroup covers (one, at 8192^3: scan and exponents 267 us against 249)
 constexpr int64_t kMaxGridThreads = (int64_t(1) << 32) - 1;   // of one launch along x
 
 // Workgroups of the scan: row blocks of op(A), then of op(B), for `groups` groups of `per` ESC blocks along k.  One launch
@@ -201,8 +201,9 @@ inline ScanGrid scan_grid(const Problem& p, bool a_rows_contig, bool b_rows_cont
     s.row_blocks_b = p.np / (b_rows_contig ? 64 : 16);
     const int64_t row_blocks = s.row_blocks_a + s.row_blocks_b;
     // ESC blocks per workgroup: four, or one where four would leave fewer than four workgroups per CU: such a call waits
-    // for the loads of one block after the other (200x300x260: 11.5 us with four, 4.5 with one), a larger one is bound
-    // by the bytes read and sets eA and eB with a quarter of the atomics
+    // for the loads of one block after the other, a larger one is bound by the bytes read, and four blocks leave a quarter of
+    // the group maxima to write and to read again (scan and exponents with four and with one: 200x300x260 11.6 us and 9.9,
+    // 1000^3 14.3 and 12.1, 2048^3 21.4 and 22.5, 8192^3 249 and 267)
     s.per = p.batch.count * row_blocks * ((p.G + kScanBlocksPerWg - 1) / kScanBlocksPerWg) < int64_t(4) * p.num_cu ? 1 : kScanBlocksPerWg;
     s.groups = (p.G + s.per - 1) / s.per;
     const int64_t fit = kMaxGridThreads / 256 / row_blocks;
