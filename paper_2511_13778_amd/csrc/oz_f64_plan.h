@@ -35,32 +35,35 @@ struct F64Plan {
 
 // Tiles a call can be cut into and what they cost, in us: start, and per round of all CUs: round, more with beta, step per MFMA step
 // (16 k in dgemm_f64_kernel, 4 k of each of the four waves in dgemm_f64_direct_kernel); first: per step of the call, for the operands'
-// way to the first workgroup of a CU; c per million elements of C, more with beta.  Tiles straight from memory: per step and round
-// more for each operand with k contiguous, and for its rows near each other in the caches' sets, and so per round.  Tiles through LDS:
-// more where an edge is ragged, and per round where k has a short first step.  Operands come out of the caches at 9 TB/s at most.
-// A split of k costs a launch and 0.33 us a part (the sums are added one after the other), and passes over C.
+// way to the first workgroup of a CU, and far, where they are more than an XCD's L2 holds; c per million elements of C, more with
+// beta.  Tiles straight from memory: per step and round more for each operand with k contiguous, and for its rows near each other in
+// the caches' sets, and so per round.  Tiles through LDS: more where an edge is ragged, and per round where k has a short first step.  Operands come out of the caches at 9 TB/s at most; of two
+// cuts they bound alike, the one with less else to do.
+// A split of k costs a launch and 0.31 us a part (the sums are added one after the other), and passes over C.
 // Fitted to 9406 calls (2 to 8000, k 1 to 50000, all four transposes, beta zero and not), each timed on every tile, from k = 64 on with
-// 1 to 16 parts: the choice is 1.6 % off the best on average (a model without beta, layout and ragged edges, fitted to k of 50 and
+// 1 to 16 parts: the choice is 1.2 % off the best on average (a model without beta, layout and ragged edges, fitted to k of 50 and
 // more, was 4.7 % off; 1261 x 2649 x 18 with beta took 31.9 us on 128 x 128 tiles, now 17; 7732 x 2885 x 14 66.9 us, now 36).
 struct F64Tile {
     bool direct;
     int ti, tj;
-    double start, round, round_beta, step, first, c, c_beta;
+    double start, round, round_beta, step, first, far, c, c_beta;
     double k_step, near_step, near_round;      // straight from memory
     double ragged, short_round;                // through LDS
 };
 constexpr F64Tile kF64Tiles[] = {
-    {false, 128, 128, 4.70, 0.0, 1.055, 1.666, 0.238, 1.37, 3.38, 0.0, 0.0, 0.0, 0.58, 0.662},
-    {false, 64, 64, 3.95, 0.0, 0.45, 0.449, 0.296, 0.92, 0.91, 0.0, 0.0, 0.0, 0.56, 0.264},
-    {true, 16, 16, 4.61, 0.181, 0.053, 0.050, 0.007, 2.12, 0.0, 0.004, 0.018, 0.051, 0.0, 0.0},
-    {true, 32, 32, 4.43, 0.379, 0.065, 0.139, 0.0, 0.41, 0.23, 0.003, 0.014, 0.238, 0.0, 0.0},
-    {true, 32, 64, 4.49, 0.461, 0.179, 0.273, 0.0, 1.25, 0.25, 0.0, 0.006, 0.442, 0.0, 0.0},
-    {true, 64, 32, 4.46, 0.545, 0.159, 0.276, 0.0, 1.11, 0.23, 0.0, 0.004, 0.465, 0.0, 0.0},
-    {true, 48, 64, 4.65, 0.803, 0.414, 0.398, 0.0, 1.70, 0.17, 0.0, 0.0, 0.564, 0.0, 0.0},
-    {true, 64, 48, 4.61, 0.833, 0.369, 0.398, 0.0, 1.66, 0.12, 0.0, 0.0, 0.553, 0.0, 0.0},
+    {false, 128, 128, 4.68, 0.0, 0.812, 1.610, 0.332, 0.0, 1.42, 2.81, 0.0, 0.0, 0.0, 0.66, 0.451},
+    {false, 64, 64, 4.13, 0.0, 0.790, 0.446, 0.225, 0.088, 0.96, 0.59, 0.0, 0.0, 0.0, 0.75, 0.204},
+    {true, 16, 16, 4.08, 0.215, 0.065, 0.048, 0.0, 0.035, 2.03, 0.14, 0.005, 0.015, 0.051, 0.0, 0.0},
+    {true, 32, 32, 4.39, 0.423, 0.080, 0.140, 0.0, 0.006, 0.18, 0.27, 0.001, 0.013, 0.280, 0.0, 0.0},
+    {true, 32, 64, 4.61, 0.596, 0.153, 0.288, 0.0, 0.0, 1.33, 0.32, 0.0, 0.009, 0.408, 0.0, 0.0},
+    {true, 64, 32, 4.59, 0.492, 0.189, 0.285, 0.0, 0.0, 1.22, 0.30, 0.0, 0.004, 0.604, 0.0, 0.0},
+    {true, 48, 64, 5.11, 0.804, 0.557, 0.391, 0.0, 0.0, 1.33, 0.19, 0.0, 0.0, 0.449, 0.0, 0.0},
+    {true, 64, 48, 5.06, 1.188, 0.361, 0.409, 0.0, 0.0, 1.66, 0.11, 0.0, 0.0, 0.540, 0.0, 0.0},
 };
 constexpr double kF64CacheBytesPerUs = 9e6;
-constexpr double kGuardedSplitUs = 15.5;        // charged for a split where the launch that adds its parts is paid by calls that do not fall back
+constexpr double kF64NearBytes = 4e6;
+constexpr double kGuardedSplitUs = 7.5;         // charged for a split where calls that do not fall back pay 3 to 4 for the launch that adds its parts
+                                                // (at 15.5 58 x 32 x 4432 took 53.8 us falling back, now 33)
 
 // Tile and number of parts of the k range.  With scratch memory at hand, k may be split over several workgroups per tile:
 // they leave partial products in the scratch memory and a second kernel adds them in the order of the parts (deterministic)
@@ -71,7 +74,9 @@ inline F64Plan choose_f64(const F64Size& c, int num_cu, size_t scratch_bytes, do
     double best_us = 0.0;
     const uint32_t m = uint32_t(c.m), n = uint32_t(c.n), cus = uint32_t(num_cu), problems = uint32_t(c.problems);
     const double area = double(c.m) * double(c.n) * double(problems) * 1e-6;
+    const bool far = double(c.m + c.n) * double(c.k) * double(c.problems) * 8.0 > kF64NearBytes;
     for (const F64Tile& t : kF64Tiles) {
+        const double first = t.first + (far ? t.far : 0.0);
         const uint32_t ti = uint32_t(t.ti), tj = uint32_t(t.tj), ntm = (m + ti - 1) / ti, ntn = (n + tj - 1) / tj;
         const uint64_t tiles64 = uint64_t(ntm) * ntn;
         if (tiles64 > uint64_t(kMaxGridThreads) / 256) continue;
@@ -93,8 +98,12 @@ inline F64Plan choose_f64(const F64Size& c, int num_cu, size_t scratch_bytes, do
             uint64_t rounds_whole = (all * z + cus - 1) / cus;
             if (t.ti == 128 && c.k_contig == 0 && rounds_whole > 1) rounds_whole += rounds_whole & 1;
             const double rounds = double(rounds_whole), steps = double(uint32_t(c.k + z * kDK - 1) / (z * kDK));
-            double us = std::max(per_call + rounds * (per_round + per_step * steps) + t.first * steps, cache_us);
-            if (z > 1) us += 1.5 + (c.guarded ? kGuardedSplitUs : 0.0) + 0.33 * double(z) + 2.5 * double(z + 2) * area;
+            double us = per_call + rounds * (per_round + per_step * steps) + first * steps;
+            if (z > 1) us += 1.4 + 0.31 * double(z) + 2.0 * double(z + 2) * area;
+            us = std::max(us, 0.7 * cache_us + 0.3 * us);
+            if (z > 1 && c.guarded) us += kGuardedSplitUs;
+            // sums in four parts have half the error: tiles straight from memory where they are as fast
+            if (!t.direct && z == 1 && c.k >= 128) us *= 1.03;
             if (best_us == 0.0 || us < best_us) {
                 best_us = us;
                 best = F64Plan{t.direct, t.ti, t.tj, int(ntm), int(ntn), int(z), z > 1 ? c.k / z / kDK * kDK : 0, nullptr};
@@ -138,7 +147,7 @@ inline bool f64_folds(const F64Size& c, int num_cu, size_t scratch_bytes, int ed
 }
 
 // Whether `all` products of one shape go into one launch, without scratch memory, or `at_once` at a time with a split of k for each
-// where that pays.  A launch that cannot split has to be 15 % better: whole-k tiles of one workgroup each end far apart (524 x 591 x 27591,
+// where that pays.  A launch that cannot split has to be 3 % better: whole-k tiles of one workgroup each end far apart (524 x 591 x 27591,
 // four products: 1799 us in one launch, estimated 1381; 1594 split, one after the other).
 inline bool f64_together(F64Size c, int all, int at_once, int num_cu, size_t scratch_bytes) {
     double one_us = 0.0, group_us = 0.0;
@@ -146,7 +155,7 @@ inline bool f64_together(F64Size c, int all, int at_once, int num_cu, size_t scr
     choose_f64(c, num_cu, 0, &one_us);
     c.problems = at_once;
     const F64Plan group = choose_f64(c, num_cu, scratch_bytes, &group_us);
-    return one_us <= group_us * double((all + at_once - 1) / at_once) * (group.zsplit > 1 ? 0.85 : 1.0);
+    return one_us <= group_us * double((all + at_once - 1) / at_once) * (group.zsplit > 1 ? 0.97 : 1.0);
 }
 
 // Form of dgemm_f64_kernel's K loop: 0 and 1 load full K steps through 32-bit offsets (1: edge tiles, and a short first step),

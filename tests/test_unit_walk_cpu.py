@@ -186,4 +186,14 @@ def test_native_products_share_a_launch_unless_a_split_of_k_is_faster(tmp_path_f
     split = [(319, 588, 11522, 1, 1, 12, 4, 36 << 20), (661, 426, 19376, 1, 0, 4, 1, 40 << 20), (524, 591, 27591, 0, 0, 4, 1, 46 << 20)]
     whole = [(96, 80, 112, 1, 0, 9, 4, 4 << 20), (500, 400, 300, 1, 0, 16, 2, 8 << 20), (100, 100, 2000, 1, 1, 24, 2, 6 << 20),
              (1000, 900, 700, 0, 0, 4, 1, 16 << 20)]
-    assert [r for r, in run(split + whole)] == [0] * 3 + [1] * 4
+    # in one launch and split: the four of a complex 202x275x6305 91 and 116 us, of 534x109x3204 72 and 90, of 52x1197x3094 81 and 97
+    whole += [(202, 275, 6305, 0, 0, 4, 1, 64 << 20), (534, 109, 3204, 0, 1, 4, 1, 64 << 20), (52, 1197, 3094, 0, 0, 4, 1, 64 << 20)]
+    assert [r for r, in run(split + whole)] == [0] * 3 + [1] * 7
+
+
+def test_small_outputs_with_a_long_k_are_split(tmp_path_factory):
+    # 58x32x4432 behind a verdict that falls back takes 54 us unsplit and 33 in parts, 30x69x4823 41 and 30; 39x235x54713 59 us in twelve
+    # parts on 32x32 tiles, which leave every fourth CU idle, and 48 in sixteen.  A short k stays whole
+    run = host_program(tmp_path_factory, "host_f64_split.cpp")
+    (*_, a), (*_, b), c, (*_, d) = run([(58, 32, 4432, 0, 0, 0, 1), (30, 69, 4823, 0, 0, 0, 1), (39, 235, 54713, 0, 1, 1, 0), (58, 32, 600, 0, 0, 0, 1)])
+    assert a > 1 and b > 1 and list(c) == [32, 32, 16] and d == 1
