@@ -91,6 +91,8 @@ constexpr int kMidTile = 64;
 constexpr int kMidMaxSlices = 16;
 constexpr int kMidPairSlices = 8;
 
+constexpr int64_t kCallStagesNs = 16000;         // stages that problems in launches of their own run once each, over the shared ones
+
 struct Split { int z; bool atomic; };
 
 // How a call's units are dealt to launches.
@@ -137,8 +139,9 @@ struct LaunchPlan {
     }
 
     // whether the problems of p.batch can share the launches
-    bool can_batch(const Problem& p) const {
-        return small || mid || (!few && int64_t(positions) * per_pos * p.batch.count <= p.num_cu);
+    bool can_batch(const Problem& p) const { return small || mid || units_batch(p); }
+    bool units_batch(const Problem& p) const {
+        return !few && int64_t(positions) * per_pos * p.batch.count <= p.num_cu;
     }
 
     // tiles of one problem
@@ -167,6 +170,9 @@ struct LaunchPlan {
     // 32 x 32 tiles have to be 7 % better from four rounds of two to a CU on, 64 x 64 ones 8 %, and 14 % on a full chip with more than
     // three 64s of k, 20 % with sixteen, where at a lower clock they are worse than estimated (4224 x 3008 x 1792 with seven slices 588 us,
     // on units 564).
+    // Units share launches only while a round holds all problems' (units_batch); otherwise each problem pays its rounds and stages.  Of 735
+    // complex products and 734 batches of 200 to 3500, about 200 take tiles for it, 11 % faster on average (1556 x 939 x 331 complex 317 us on
+    // units, now 192; 2006 x 1146 x 1529 967, now 617), and fifteen more than 3 % slower (1666 x 2989 x 1234 1171, now 1478).
     // (A rule that took two workgroups of 32 x 32 to a CU for any slice count, with no bound on the bytes, was 1.9 % off; 4010 x 2372 x 137 at
     // up to 26 slices took 287 us, now 205, 46 x 119 x 4154 with five 76, now 53, and 2270 x 944 x 2390 with seven 281, now 234.)
     void fuse(const Problem& p) {
@@ -177,18 +183,20 @@ struct LaunchPlan {
         auto el = [&](int64_t ns) { return area * ns / 1000000; };
         // workgroups, per round, ns of a round
         auto rounds_ns = [](int64_t all, int64_t per, int64_t ns) { return all < 4 * per ? (all + per - 1) / per * ns : all * ns / per; };
-        int64_t best;
-        if (few) {
-            best = (int64_t(g.nti) * g.ntj + cus - 1) / cus * (9900 + (S == 1 ? 695 : 2065) * kt) + el(2770 + 1010 * S);
-        } else {
-            const int64_t step = unit_items(int(S)) * 460, ends = (S + kDiag - 1) / kDiag * 9260, per_cu = int64_t(per_pos) * count;
-            best = 975 + el(3506 + 13 * S) + ((last.z > 1 ? full : positions) * per_cu + cus - 1) / cus * (kt * step + ends);
+        auto units_ns = [&](int64_t problems) -> int64_t {
+            const int64_t own = p.m * p.n * problems;
+            auto el_own = [&](int64_t ns) { return own * ns / 1000000; };
+            if (few) return (int64_t(g.nti) * g.ntj + cus - 1) / cus * (9900 + (S == 1 ? 695 : 2065) * kt) + el_own(2770 + 1010 * S);
+            const int64_t step = unit_items(int(S)) * 460, ends = (S + kDiag - 1) / kDiag * 9260, per_cu = int64_t(per_pos) * problems;
+            int64_t ns = 975 + el_own(3506 + 13 * S) + ((last.z > 1 ? full : positions) * per_cu + cus - 1) / cus * (kt * step + ends);
             if (last.z > 1) {
                 const int64_t parts = last.z * rest * per_cu;
-                best += (kt + last.z - 1) / last.z * step + ends +
-                        (last.atomic ? 155 * last.z + 28 * parts * S : 708 + 1565 * last.z + 7 * parts * (4 + S));
+                ns += (kt + last.z - 1) / last.z * step + ends +
+                      (last.atomic ? 155 * last.z + 28 * parts * S : 708 + 1565 * last.z + 7 * parts * (4 + S));
             }
-        }
+            return ns;
+        };
+        int64_t best = count == 1 || units_batch(p) ? units_ns(count) : count * units_ns(1) + (count - 1) * kCallStagesNs;
         const int64_t small_all = small_tiles(p) * count;
         const bool pair = small_all > cus && p.s_cap <= kSmallPairSlices;
         const int64_t small_products = pair ? rounds_ns(small_all, 2 * cus, 1150 + 279 * S + kt * (494 + 16 * S + 17 * pairs))

@@ -197,3 +197,10 @@ def test_small_outputs_with_a_long_k_are_split(tmp_path_factory):
     run = host_program(tmp_path_factory, "host_f64_split.cpp")
     (*_, a), (*_, b), c, (*_, d) = run([(58, 32, 4432, 0, 0, 0, 1), (30, 69, 4823, 0, 0, 0, 1), (39, 235, 54713, 0, 1, 1, 0), (58, 32, 600, 0, 0, 0, 1)])
     assert a > 1 and b > 1 and list(c) == [32, 32, 16] and d == 1
+
+
+def test_problems_that_cannot_share_units_take_tiles(tmp_path_factory):
+    # 104 units a problem: on units four calls one after the other.  The four of a complex 1556x939x331 with counts per block take 317 us so
+    # and 192 in one launch on tiles, of 2006x1146x1529 967 and 617
+    run = host_program(tmp_path_factory, "host_call_plan.cpp")
+    assert all(g != 0 for g, in run([(1556, 939, 331, 14, 7, 1, 4), (2006, 1146, 1529, 14, 7, 1, 4)]))
