@@ -127,7 +127,7 @@ inline bool wide_offsets(int64_t m, int64_t n, int64_t k, int64_t ld_max) {
 // alone: the emulated kernel's LDS leaves one workgroup to a CU.
 // In us: launches of its own take 1.6, 0.9 of choose_f64's estimate and 4.6 for the sums of a split; tiles as below, and no less than the
 // operands at the rate of the caches.  Fitted to 2250 calls that fall back (16 to 8000, k 20 to 6000), timed with either: half of
-// them fold, 0.4 % slower than the better one on average, and fifteen by more than 5 % than in launches of their own.  (Against the
+// them fold, 0.6 % slower than the better one on average, and sixteen by more than 5 % than in launches of their own.  (Against the
 // unsplit product alone, without the layout and with two workgroups to a CU throughout, 519 x 123 x 4328 took 72 us, now 41, and
 // 811 x 1516 x 101 36, now 26.)
 inline bool f64_folds(const F64Size& c, int num_cu, size_t scratch_bytes, int edge, bool alone) {
@@ -148,7 +148,7 @@ inline bool f64_folds(const F64Size& c, int num_cu, size_t scratch_bytes, int ed
 
 // Whether `all` products of one shape go into one launch, without scratch memory, or `at_once` at a time with a split of k for each
 // where that pays.  A launch that cannot split has to be 3 % better: whole-k tiles of one workgroup each end far apart (524 x 591 x 27591,
-// four products: 1799 us in one launch, estimated 1381; 1594 split, one after the other).
+// four products: 1799 us in one launch, estimated 1357; 1594 split, one after the other).
 inline bool f64_together(F64Size c, int all, int at_once, int num_cu, size_t scratch_bytes) {
     double one_us = 0.0, group_us = 0.0;
     c.problems = all;
