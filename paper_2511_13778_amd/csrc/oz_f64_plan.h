@@ -39,7 +39,8 @@ struct F64Plan {
 // beta.  Tiles straight from memory: per step and round more for each operand with k contiguous, and for its rows near each other in
 // the caches' sets, and so per round.  Tiles through LDS: more where an edge is ragged, and per round where k has a short first step.  Operands come out of the caches at 9 TB/s at most; of two
 // cuts they bound alike, the one with less else to do.
-// A split of k costs a launch and 0.31 us a part (the sums are added one after the other), and passes over C.
+// A split of k costs a launch and 0.31 us a part (the sums are added one after the other), and passes over C (2.6: with 2.0 the model takes
+// eight parts for 256 x 7936 x 8192, 508 us, and four take 494).
 // Fitted to 9406 calls (2 to 8000, k 1 to 50000, all four transposes, beta zero and not), each timed on every tile, from k = 64 on with
 // 1 to 16 parts: the choice is 1.2 % off the best on average (a model without beta, layout and ragged edges, fitted to k of 50 and
 // more, was 4.7 % off; 1261 x 2649 x 18 with beta took 31.9 us on 128 x 128 tiles, now 17; 7732 x 2885 x 14 66.9 us, now 36).
@@ -51,7 +52,7 @@ struct F64Tile {
     double ragged, short_round;                // through LDS
 };
 constexpr F64Tile kF64Tiles[] = {
-    {false, 128, 128, 4.68, 0.0, 0.812, 1.610, 0.332, 0.0, 1.42, 2.81, 0.0, 0.0, 0.0, 0.66, 0.451},
+    {false, 128, 128, 4.68, 0.0, 0.812, 1.610, 0.280, 0.0, 1.42, 2.81, 0.0, 0.0, 0.0, 0.66, 0.451},
     {false, 64, 64, 4.13, 0.0, 0.790, 0.446, 0.225, 0.088, 0.96, 0.59, 0.0, 0.0, 0.0, 0.75, 0.204},
     {true, 16, 16, 4.08, 0.215, 0.065, 0.048, 0.0, 0.035, 2.03, 0.14, 0.005, 0.015, 0.051, 0.0, 0.0},
     {true, 32, 32, 4.39, 0.423, 0.080, 0.140, 0.0, 0.006, 0.18, 0.27, 0.001, 0.013, 0.280, 0.0, 0.0},
@@ -99,7 +100,7 @@ inline F64Plan choose_f64(const F64Size& c, int num_cu, size_t scratch_bytes, do
             if (t.ti == 128 && c.k_contig == 0 && rounds_whole > 1) rounds_whole += rounds_whole & 1;
             const double rounds = double(rounds_whole), steps = double(uint32_t(c.k + z * kDK - 1) / (z * kDK));
             double us = per_call + rounds * (per_round + per_step * steps) + first * steps;
-            if (z > 1) us += 1.4 + 0.31 * double(z) + 2.0 * double(z + 2) * area;
+            if (z > 1) us += 1.4 + 0.31 * double(z) + 2.6 * double(z + 2) * area;
             us = std::max(us, 0.7 * cache_us + 0.3 * us);
             if (z > 1 && c.guarded) us += kGuardedSplitUs;
             // sums in four parts have half the error: tiles straight from memory where they are as fast
