@@ -194,11 +194,13 @@ struct ScanGrid {
     int per;
     int64_t groups, slab;
 };
-// rows_contig: stride_r == 1, a workgroup of 256 threads covers 64 rows, otherwise 16
+// rows_contig: stride_r == 1.  A workgroup of 256 threads covers 64 rows; 16 of an operand with k contiguous whose ESC blocks are not
+// whole 64s of k
 inline ScanGrid scan_grid(const Problem& p, bool a_rows_contig, bool b_rows_contig) {
     ScanGrid s;
-    s.row_blocks_a = p.mp / (a_rows_contig ? 64 : 16);
-    s.row_blocks_b = p.np / (b_rows_contig ? 64 : 16);
+    const bool whole = p.esc_block % 64 == 0;
+    s.row_blocks_a = p.mp / (a_rows_contig || whole ? 64 : 16);
+    s.row_blocks_b = p.np / (b_rows_contig || whole ? 64 : 16);
     const int64_t row_blocks = s.row_blocks_a + s.row_blocks_b;
     // ESC blocks per workgroup: four, or one where four would leave fewer than four workgroups per CU: such a call waits
     // for the loads of one block after the other, a larger one is bound by the bytes read, and four blocks leave a quarter of

@@ -5,7 +5,9 @@
 // (paper: sections "Pre-processing and Safety Checks" and "Exponent Span Estimation";
 //  block Max/Min: section "ESC", the paragraph on blocks of length b.)
 //
-// HBM-bound: every FP64 element is read once (8 B), two int16 are written per block of b.
+// HBM-bound: every FP64 element is read once (8 B), two int16 are written per block of b.  Scan and exponents at 8192^3 (1.07 GB) 178 us
+// with both operands' rows contiguous, 198 with k contiguous (231 and 276 with 128 bytes of a row per load there and without the streaming
+// hint; a read of 1 GiB with the hint takes 154).
 #include "oz_internal.h"
 
 namespace oz {
@@ -15,7 +17,7 @@ namespace oz {
 // smallest exponent, and Inf and NaN come out as kExpInfNan.  Five instructions per entry and no branch, so the loads of a
 // batch are all in flight before the first is looked at; zeros and denormals, whose exponent lies elsewhere, are looked
 // for only in a batch that has one.  (Entry by entry, with branches for zeros, loads were waited for one by one: 200 x 300 x 260
-// 5.3 us, now 3.6; 1024 x 1024 x 65536 219, now 196; 8192^3 254, now 238.)
+// 5.3 us, then 3.6; 1024 x 1024 x 65536 219, then 196; 8192^3 254, then 238.)
 struct BlockStat {
     uint32_t mx, mn;       // largest high word (without sign), smallest of the normal numbers less kMinNormal
     int mx_low, mn_low;    // exponents of the denormals: -32768 and 32767: none
@@ -71,9 +73,16 @@ __device__ __forceinline__ void scan_store(const ScanSide& s, int G, int g, int6
     s.tab[int64_t(s.max_half ? G + g : g) * s.o.rows_p + r] = int16_t(mn);
 }
 
+// NT: with the streaming hint (launch_scan)
+template <bool NT>
+__device__ __forceinline__ uint64_t load_entry(const uint64_t* p) {
+    return NT ? __builtin_nontemporal_load(p) : *p;
+}
+
 // Rows contiguous in memory (stride_r == 1): lanes along 64 rows, so every load instruction of a wave reads 512
 // contiguous bytes; the four waves take every fourth k of a block, which keeps a thread's chain of loads short (a
 // thread per row for four whole blocks: 28 us for 2048 x 2048, now 10), and are combined through LDS.
+template <bool NT>
 __device__ __forceinline__ void scan_rows(const ScanSide& s, int64_t rb, int g0, int per, int64_t k, int b, int G) {
     __shared__ int2 part[kScanBlocksPerWg][4][64];     // max; min, with bit 16 set when the part holds a zero
     const int lane = threadIdx.x & 63;
@@ -92,7 +101,7 @@ __device__ __forceinline__ void scan_rows(const ScanSide& s, int64_t rb, int g0,
             for (int l = wave; l < len; l += 64) {
                 uint64_t x[16];
 #pragma unroll
-                for (int i = 0; i < 16; ++i) x[i] = (src + min(l + 4 * i, len - 1) * s.o.stride_l)[lane];
+                for (int i = 0; i < 16; ++i) x[i] = load_entry<NT>(src + min(l + 4 * i, len - 1) * s.o.stride_l + lane);
                 st.add(x);
             }
         }
@@ -122,7 +131,7 @@ __device__ __forceinline__ void scan_rows(const ScanSide& s, int64_t rb, int g0,
 
 // k contiguous in memory (stride_l == 1): 16 lanes share one row so that a load instruction
 // reads 128 contiguous bytes per row; partial results are combined across the 16 lanes.
-// A workgroup covers 16 rows.  The loads of two blocks are in flight together (of four: 77 registers, and six workgroups to a CU
+// A workgroup covers 16 rows.  For ESC blocks that are no whole 64s of k (scan_k64 below).  The loads of two blocks are in flight together (of four: 77 registers, and six workgroups to a CU
 // instead of eight: 4224 x 3008 x 1792 32 us against 25).
 template <int PER>
 __device__ __forceinline__ void scan_k(const ScanSide& s, int64_t rb, int g0, int64_t k, int b, int G) {
@@ -169,8 +178,102 @@ __device__ __forceinline__ void scan_k(const ScanSide& s, int64_t rb, int g0, in
     if (q == 0) s.group_max[int64_t(g0 / PER) * s.o.rows_p + r] = int16_t(row_max);
 }
 
+// Blocks that are whole 64s of k: a load instruction of a wave reads 64 entries of one row, 512 contiguous bytes as in scan_rows,
+// with 16 rows in flight; the rows' partial results, one per lane, then fold into each other across the lanes.  A wave covers 16
+// rows, a workgroup 64.
+// A code of 16 bits stands for an entry: the top 16 bits of its magnitude (exponent field and four bits of the significand) plus
+// kLowCodes, the exponent of a denormal + 1075 (1 .. 52), 0 for a zero.  A word holds the largest code of a row and, in its high
+// half, the inverse of the smallest, so that one packed maximum takes both.
+constexpr uint32_t kLowCodes = 64;
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pk_max(uint32_t a, uint32_t b) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
+}
+template <int CTRL>
+__device__ __forceinline__ uint32_t pk_max_dpp(uint32_t x) {
+    return pk_max(x, uint32_t(__builtin_amdgcn_update_dpp(0, int(x), CTRL, 0xF, 0xF, false)));
+}
+__device__ __forceinline__ int code_exp(uint32_t code) {     // of a non-zero entry
+    return code >= kLowCodes ? int((code - kLowCodes) >> 4) - 1023 : int(code) - 1075;
+}
+template <bool NT>
+__device__ __forceinline__ void scan_k64(const ScanSide& s, int64_t rb, int g0, int per, int64_t k, int b, int G) {
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t r0 = rb * 64 + wave * 16;
+    const char* const base = reinterpret_cast<const char*>(s.o.X + r0 * s.o.stride_r);
+    const int64_t row_bytes = s.o.stride_r * 8;
+    const int last_row = int(max(min(int64_t(15), s.o.rows - 1 - r0), int64_t(-1)));     // -1: padding only
+    const int my_row = (lane >> 4) * 4 + (lane & 3);         // the row whose results this lane holds in the end
+    uint32_t row_max = 0;
+#pragma unroll 1
+    for (int g = g0; g < min(g0 + per, G); ++g) {
+        uint32_t stat[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) stat[i] = 0;
+        const int64_t l0 = int64_t(g) * b;
+        const int len = last_row < 0 ? 0 : int(min(int64_t(b), k - l0));
+#pragma unroll 1
+        for (int l = 0; l < len; l += 64) {
+            // past the end of a block its last entry is read again, past the last row that row
+            const uint32_t at = uint32_t(min(l + lane, len - 1)) * 8u;
+            const char* row = base + l0 * 8;
+            uint64_t x[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                x[i] = load_entry<NT>(reinterpret_cast<const uint64_t*>(row + at));
+                row += i < last_row ? row_bytes : 0;
+            }
+            uint32_t least = ~0u;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) least = min(least, uint32_t(x[i] >> 32) << 1);
+            if (!__any(least < 2 * BlockStat::kMinNormal)) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const uint32_t hi = uint32_t(x[i] >> 32);
+                    const u16x2 top = __builtin_bit_cast(u16x2, __builtin_amdgcn_perm(hi, hi, 0x07060706u) & 0x7FFF7FFFu);
+                    stat[i] = pk_max(stat[i], __builtin_bit_cast(uint32_t, top * u16x2{1, 0xFFFF} + u16x2{kLowCodes, 0xFFFF - kLowCodes}));
+                }
+            } else {                     // a zero or a denormal among them
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    uint32_t hi = uint32_t(x[i] >> 32);
+                    asm volatile("" : "+v"(hi));             // one entry at a time: registers
+                    hi &= 0x7FFFFFFFu;
+                    const uint32_t lo = uint32_t(x[i]);
+                    const uint32_t low = hi ? 64 - __builtin_clz(hi) : (lo ? 32 - __builtin_clz(lo) : 0u);
+                    const uint32_t code = hi >= BlockStat::kMinNormal ? (hi >> 16) + kLowCodes : low;
+                    stat[i] = pk_max(stat[i], code | ((0xFFFFu - code) << 16));
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const auto p = __builtin_amdgcn_permlane32_swap(stat[i], stat[i + 8], false, false);
+            stat[i] = pk_max(p[0], p[1]);                  // lanes 0 .. 31 row i, 32 .. 63 row i + 8
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const auto p = __builtin_amdgcn_permlane16_swap(stat[i], stat[i + 4], false, false);
+            uint32_t x = pk_max(p[0], p[1]);               // rows i, i + 4, i + 8, i + 12, in 16 lanes each
+            x = pk_max_dpp<0x128>(x);                      // row_ror 8, 4, 2, 1
+            x = pk_max_dpp<0x124>(x);
+            x = pk_max_dpp<0x122>(x);
+            stat[i] = pk_max_dpp<0x121>(x);
+        }
+        const uint32_t mine = (lane & 2) ? ((lane & 1) ? stat[3] : stat[2]) : ((lane & 1) ? stat[1] : stat[0]);
+        const uint32_t largest = my_row <= last_row ? mine & 0xFFFFu : 0u, smallest = 0xFFFFu - (mine >> 16);
+        if ((lane & 12) == 0)
+            scan_store(s, G, g, r0 + my_row, largest ? code_exp(largest) : kExpAllZero,
+                       largest ? (smallest ? code_exp(smallest) : kExpZeroInMin) : kExpAllZero);
+        row_max = max(row_max, largest);
+    }
+    if ((lane & 12) == 0) s.group_max[int64_t(g0 / per) * s.o.rows_p + r0 + my_row] = int16_t(row_max ? code_exp(row_max) : kExpAllZero);
+}
+
 // Both operands in one launch: the first blocks_a workgroups scan op(A), the others op(B), from ESC block g_first on.
-__global__ __launch_bounds__(256, 8) void scan_kernel(ScanSide a, ScanSide b, int64_t blocks_a, int g_first, int per, int64_t k,
+template <bool NT>
+__global__ __launch_bounds__(256, 6) void scan_kernel(ScanSide a, ScanSide b, int64_t blocks_a, int g_first, int per, int64_t k,
                                                    int bl, int G, Record* rec, Batch bt) {
     const int64_t ws = bt.ws_at(blockIdx.z);
     if (blockIdx.x == 0 && threadIdx.x == 0) at_bytes(rec, ws)->infnan = 0;        // the exponents tell (exponents_kernel)
@@ -182,17 +285,25 @@ __global__ __launch_bounds__(256, 8) void scan_kernel(ScanSide a, ScanSide b, in
     const int64_t id = int64_t(blockIdx.x) - (second ? blocks_a : 0);
     const int64_t rb = id % s.row_blocks;
     const int g0 = g_first + int(id / s.row_blocks) * per;
-    if (s.o.stride_r == 1) scan_rows(s, rb, g0, per, k, bl, G);
+    if (s.o.stride_r == 1) scan_rows<NT>(s, rb, g0, per, k, bl, G);
+    else if (bl % 64 == 0) scan_k64<NT>(s, rb, g0, per, k, bl, G);
     else if (per == 1) scan_k<1>(s, rb, g0, k, bl, G);
     else scan_k<kScanBlocksPerWg>(s, rb, g0, k, bl, G);
 }
 
+constexpr double kStreamBytes = 400e6;
+
 void launch_scan(hipStream_t st, const Operand& a, const Operand& b, const Workspace& w, const Problem& p) {
     const ScanGrid g = scan_grid(p, a.stride_r == 1, b.stride_r == 1);
     const ScanSide sa{a, w.U, 1, w.group_max_a(), g.row_blocks_a}, sb{b, w.V, 0, w.group_max_b(), g.row_blocks_b};
+    // The streaming hint keeps the operands out of the 256 MB Infinity Cache.  What fits there the slicing reads from it; of more it finds
+    // little, and the scan is the faster for it (scan and slicing, seven slices: 8192 x 8192 twice, 1.07 GB, 586 -> 543 us with rows
+    // contiguous, 679 -> 629 with k; 4096 x 4096 twice, 268 MB, 171 -> 185)
+    const bool stream = (double(p.m) + double(p.n)) * double(p.k) * 8.0 * p.batch.count > kStreamBytes;
+    const auto kernel = stream ? scan_kernel<true> : scan_kernel<false>;
     for (int64_t y = 0; y < g.groups; y += g.slab) {
         const int64_t gy = g.groups - y < g.slab ? g.groups - y : g.slab;
-        hipLaunchKernelGGL(scan_kernel, dim3(unsigned((g.row_blocks_a + g.row_blocks_b) * gy), 1, unsigned(p.batch.count)), dim3(256), 0, st, sa, sb,
+        hipLaunchKernelGGL(kernel, dim3(unsigned((g.row_blocks_a + g.row_blocks_b) * gy), 1, unsigned(p.batch.count)), dim3(256), 0, st, sa, sb,
                            g.row_blocks_a * gy, int(y) * g.per, g.per, p.k, p.esc_block, p.G, w.rec, p.batch);
     }
 }
