@@ -13,8 +13,8 @@
 //
 // Output layout (what the INT8 GEMM's tiles load with contiguous 16-byte pieces):
 //   slices[s][l/16][r][l%16]  for row r (padded to rows_p), k index l (padded to kp); padding = 0.
-// HBM-bound: 8 B read and S bytes written per element.  Operands and slices are touched once per call
-// here, so loads and stores carry the streaming (non-temporal) hint: measured 11 % faster.
+// HBM-bound: 8 B read and S bytes written per element; 8192^3 with seven slices 360 to 410 us by storage order, 4.9 to 5.6 TB/s (a copy
+// reaches 5.6).  Operands and slices are touched once per call here, so loads and stores carry the streaming (non-temporal) hint.
 #include "oz_internal.h"
 
 namespace oz {
@@ -52,22 +52,32 @@ __device__ __forceinline__ uint32_t byte_of(const Fixed& f, int b) {
     return 0u;
 }
 
-// Digits of 16 consecutive k of one row, least significant slice first; writes 16 bytes per slice.
-__device__ __forceinline__ void emit_slices(const Fixed (&f)[16], int S, int8_t* dst,
-                                            int64_t slice_stride) {
-    uint32_t carry[16];
+// N = 4 or 16 consecutive k of one row leave N bytes per slice.
+template <int N>
+__device__ __forceinline__ void store_digits(const uint32_t (&w)[N / 4], int8_t* plane, uint32_t lane_off) {
+    typedef uint32_t vec __attribute__((ext_vector_type(N / 4)));
+    vec v;
+    if constexpr (N == 4) v = w[0];
+    else v = vec{w[0], w[1], w[2], w[3]};
+    __builtin_nontemporal_store(v, reinterpret_cast<vec*>(plane + lane_off));
+}
+
+// Digits of N consecutive k of one row, least significant slice first.
+template <int N>
+__device__ __forceinline__ void emit_slices(const Fixed (&f)[N], int S, int8_t* plane0, uint32_t lane_off, int64_t slice_stride) {
+    uint32_t carry[N];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) carry[e] = 0;
+    for (int e = 0; e < N; ++e) carry[e] = 0;
     for (int s = S - 1; s >= 0; --s) {
         const int b = S - 1 - s;
-        uint32_t w[4] = {0, 0, 0, 0};
+        uint32_t w[N / 4] = {};
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
+        for (int e = 0; e < N; ++e) {
             const uint32_t u = byte_of(f[e], b) + carry[e];
             carry[e] = (u >= 128u) ? 1u : 0u;       // unused after the leading slice
             w[e >> 2] |= (u & 0xFFu) << (8 * (e & 3));
         }
-        *reinterpret_cast<uint4*>(dst + int64_t(s) * slice_stride) = make_uint4(w[0], w[1], w[2], w[3]);
+        store_digits<N>(w, plane0 + int64_t(s) * slice_stride, lane_off);
     }
 }
 
@@ -114,107 +124,185 @@ __device__ __forceinline__ void biased_fixed128(uint64_t bits, int q_minus_1075,
     hi = x_hi + bias_hi + (lo < x_lo ? 1ull : 0ull);
 }
 
-// Byte b of 16 values (NW dwords each, least significant first) is gathered into four dwords with byte permutes
-// (three per dword).
-template <int NW>
-__device__ __forceinline__ void emit_words(const uint32_t (&y)[NW][16], int S, int8_t* dst, int64_t slice_stride) {
+// X + BIAS for S <= 8 on the FP64 unit, in five instructions instead of 24: with the unit rounding toward -infinity, adding
+// 1.5 * 2^52 leaves floor(a * 2^(q-32)) in the low word, what that leaves over is in [0, 1), and 2^32 times that plus 2^52 leaves the
+// low word of X in the low word.  Rounding the rest (an entry far below its row's largest, negative) downwards changes no floor.  The
+// two constants carry the bias: its low word may carry into the upper word of the second sum, which is added to the first.
+// (Both operands of 8192^3, seven slices, rows contiguous: 447 us in integer arithmetic at 128 registers, now 360.)
+struct Fp64Cut {
+    double scale, magic_hi, magic_lo;
+    static constexpr uint32_t kTwo52 = 0x43300000u;          // upper word of 2^52
+    // q_minus_32 within the exponents of normal numbers
+    __device__ __forceinline__ Fp64Cut(int q_minus_32, uint64_t bias)
+        : scale(__builtin_bit_cast(double, uint64_t(q_minus_32 + 1023) << 52)),
+          magic_hi(__builtin_bit_cast(double, 0x4338000000000000ull | uint32_t(uint32_t(bias >> 32) - kTwo52))),
+          magic_lo(__builtin_bit_cast(double, uint64_t(kTwo52) << 32 | uint32_t(bias))) {}
+    __device__ __forceinline__ void cut(uint64_t bits, uint32_t& lo, uint32_t& hi) const {
+        const double a = __builtin_bit_cast(double, bits);
+        const double h = __builtin_fma(a, scale, magic_hi);
+        const double rest = __builtin_fma(a, scale, -(h - magic_hi));
+        const uint64_t l = __builtin_bit_cast(uint64_t, __builtin_fma(rest, 0x1p32, magic_lo));
+        lo = uint32_t(l);
+        hi = uint32_t(__builtin_bit_cast(uint64_t, h)) + uint32_t(l >> 32);
+    }
+};
+
+// Byte b of N values (NW dwords each, least significant first) goes to plane S - 1 - b, four values to a dword: transposes of four
+// dwords in two steps of byte permutes.
+template <int NW, int N>
+__device__ __forceinline__ void emit_words(const uint32_t (&y)[NW][N], int S, int8_t* plane0, uint32_t lane_off, int64_t slice_stride) {
 #pragma unroll
-    for (int v = NW - 1; v >= 0; --v)
-        for (int b = min(S - 1, 4 * v + 3); b >= 4 * v; --b) {
-            const uint32_t k = uint32_t(b) & 3u;
-            const uint32_t pick = k * 0x0101u + 0x0400u;            // result bytes: [second.k, first.k, -, -]
-            const uint32_t flip = (b == S - 1) ? 0u : 0x80808080u;  // the leading digit keeps its sign bit
-            uint32_t w[4];
+    for (int v = NW - 1; v >= 0; --v) {
+        if (4 * v >= S) continue;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint32_t t1 = __builtin_amdgcn_perm(y[v][4 * j + 1], y[v][4 * j], pick);
-                const uint32_t t2 = __builtin_amdgcn_perm(y[v][4 * j + 3], y[v][4 * j + 2], pick);
-                w[j] = __builtin_amdgcn_perm(t2, t1, 0x05040100u) ^ flip;
+        for (int half = 1; half >= 0; --half) {              // bytes 2, 3 and 0, 1
+            if (4 * v + 2 * half >= S) continue;
+            uint32_t w[2][N / 4];
+#pragma unroll
+            for (int j = 0; j < N / 4; ++j) {
+                const uint32_t pick = half ? 0x07030602u : 0x05010400u;
+                const uint32_t t01 = __builtin_amdgcn_perm(y[v][4 * j + 1], y[v][4 * j], pick);
+                const uint32_t t23 = __builtin_amdgcn_perm(y[v][4 * j + 3], y[v][4 * j + 2], pick);
+                w[0][j] = __builtin_amdgcn_perm(t23, t01, 0x05040100u);
+                w[1][j] = __builtin_amdgcn_perm(t23, t01, 0x07060302u);
             }
-            typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-            __builtin_nontemporal_store(u32x4{w[0], w[1], w[2], w[3]},
-                                        reinterpret_cast<u32x4*>(dst + int64_t(S - 1 - b) * slice_stride));
+#pragma unroll
+            for (int q = 1; q >= 0; --q) {
+                const int b = 4 * v + 2 * half + q;
+                if (b >= S) continue;
+                const uint32_t flip = b == S - 1 ? 0u : 0x80808080u;     // the leading digit keeps its sign bit
+#pragma unroll
+                for (int j = 0; j < N / 4; ++j) w[q][j] ^= flip;
+                store_digits<N>(w[q], plane0 + int64_t(S - 1 - b) * slice_stride, lane_off);
+            }
         }
+    }
 }
 
-__device__ __forceinline__ void emit(const uint64_t (&bits)[16], int e_row, int S, int8_t* dst,
+// plane0: where the first plane's entries of this wave lie (uniform), lane_off: bytes to this lane's
+template <int MAXS, int N>
+__device__ __forceinline__ void emit(const uint64_t (&bits)[N], int e_row, int S, int8_t* plane0, uint32_t lane_off,
                                      int64_t slice_stride) {
-    const int q = 8 * S - 2 - kHeadroomBits - (e_row > kExpAllZero ? e_row : 0) - 1075;
+    const int q = 8 * S - 2 - kHeadroomBits - (e_row > kExpAllZero ? e_row : 0);
     if (S <= 8) {
         const uint64_t bias = S >= 2 ? (0x8080808080808080ull >> (8 * (9 - S))) : 0ull;
-        uint32_t y[2][16];
+        uint32_t y[2][N];
+        // Inf and NaN (unguarded mode), and rows of 2^-960 and less, whose factor is no normal number: integer arithmetic
+        if (__all(e_row < kExpInfNan && q - 32 >= -1022 && q - 32 <= 1023)) {
+            const Fp64Cut c(q - 32, bias);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const uint64_t x = biased_fixed64(bits[e], q, bias);
-            y[0][e] = uint32_t(x);
-            y[1][e] = uint32_t(x >> 32);
+            for (int e = 0; e < N; ++e) c.cut(bits[e], y[0][e], y[1][e]);
+        } else {
+#pragma unroll
+            for (int e = 0; e < N; ++e) {
+                const uint64_t x = biased_fixed64(bits[e], q - 1075, bias);
+                y[0][e] = uint32_t(x);
+                y[1][e] = uint32_t(x >> 32);
+                __builtin_amdgcn_sched_barrier(0);           // one at a time: registers
+            }
         }
-        emit_words<2>(y, S, dst, slice_stride);
-    } else if (S <= 16) {
-        const uint64_t bias_hi = S >= 10 ? (0x8080808080808080ull >> (8 * (17 - S))) : 0ull;
-        uint32_t y[4][16];
+        emit_words<2, N>(y, S, plane0, lane_off, slice_stride);
+        return;
+    }
+    if constexpr (MAXS > 8) {
+        if (S <= 16) {
+            const uint64_t bias_hi = S >= 10 ? (0x8080808080808080ull >> (8 * (17 - S))) : 0ull;
+            uint32_t y[4][N];
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            uint64_t lo, hi;
-            biased_fixed128(bits[e], q, 0x8080808080808080ull, bias_hi, lo, hi);
-            y[0][e] = uint32_t(lo);
-            y[1][e] = uint32_t(lo >> 32);
-            y[2][e] = uint32_t(hi);
-            y[3][e] = uint32_t(hi >> 32);
+            for (int e = 0; e < N; ++e) {
+                uint64_t lo, hi;
+                biased_fixed128(bits[e], q - 1075, 0x8080808080808080ull, bias_hi, lo, hi);
+                y[0][e] = uint32_t(lo);
+                y[1][e] = uint32_t(lo >> 32);
+                y[2][e] = uint32_t(hi);
+                y[3][e] = uint32_t(hi >> 32);
+            }
+            emit_words<4, N>(y, S, plane0, lane_off, slice_stride);
+            return;
         }
-        emit_words<4>(y, S, dst, slice_stride);
-    } else {
-        Fixed f[16];
+    }
+    if constexpr (MAXS > 16) {
+        Fixed f[N];
 #pragma unroll
-        for (int e = 0; e < 16; ++e) f[e] = fixed_point(bits[e], e_row, S);
-        emit_slices(f, S, dst, slice_stride);
+        for (int e = 0; e < N; ++e) f[e] = fixed_point(bits[e], e_row, S);
+        emit_slices<N>(f, S, plane0, lane_off, slice_stride);
     }
 }
 
 // Rows contiguous in memory: thread = row, lanes along rows; loads coalesce across the wave.
 // A workgroup cuts 256 rows x 16 k (chunk c).
+template <int MAXS>
 __device__ __forceinline__ void slice_rows(const Operand& o, int64_t rb, int64_t c, int64_t k, int64_t kp, int er,
                                            int8_t* __restrict__ out, int S) {
-    const int64_t r = rb * 256 + threadIdx.x;
-    // loads are unconditional at clamped addresses (rows >= 1 and k >= 1 here); out-of-range
+    // loads are unconditional at clamped addresses (rows >= 1 and k >= 1 here, and every block of rows has one); out-of-range
     // elements are then replaced by zero, so the loop has no divergent branches
-    const bool row_ok = r < o.rows;
-    const uint64_t* src = reinterpret_cast<const uint64_t*>(o.X) + (row_ok ? r : o.rows - 1);
+    const int64_t rows_here = o.rows - rb * 256;
+    const bool row_ok = int64_t(threadIdx.x) < rows_here;
+    const uint32_t lane = uint32_t(min(int64_t(threadIdx.x), rows_here - 1)) * 8u;
+    const char* const src = reinterpret_cast<const char*>(o.X + rb * 256);
     uint64_t bits[16];
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
         const int64_t l = c * 16 + e;
-        const uint64_t x = __builtin_nontemporal_load(&src[(l < k ? l : k - 1) * o.stride_l]);
+        const uint64_t x = __builtin_nontemporal_load(reinterpret_cast<const uint64_t*>(src + (l < k ? l : k - 1) * o.stride_l * 8 + lane));
         bits[e] = (row_ok && l < k) ? x : 0ull;
     }
-    emit(bits, er, S, out + (c * o.rows_p + r) * 16, kp * o.rows_p);
+    emit<MAXS, 16>(bits, er, S, out + (c * o.rows_p + rb * 256) * 16, threadIdx.x * 16u, kp * o.rows_p);
 }
 
-// k contiguous in memory: a 64-row x 64-k tile is read with lanes along k (512 contiguous bytes
-// per wave load), transposed through LDS, then each thread owns (row, 16-k chunk).
-__device__ __forceinline__ void slice_k(const Operand& o, int64_t rb, int64_t lb, int64_t k, int64_t kp,
-                                        int er, int8_t* __restrict__ out, int S, uint64_t (*T)[65]) {
-    const int64_t r0 = rb * 64, l0 = lb * 64;
-    {
-        const int ll = threadIdx.x & 63;
-        const int rr0 = threadIdx.x >> 6;
-        const uint64_t* src = reinterpret_cast<const uint64_t*>(o.X);
+// k contiguous in memory: four lanes share 16 consecutive k of a row (128 bytes, 16 per load and lane), a wave takes 16 rows and, chunk
+// by chunk, 64 k; a lane's four k are a dword of every plane, and the 64 lanes' dwords lie behind each other.  (A 64 x 64 tile
+// transposed through LDS instead, so that a thread has 16 k: four workgroups to a CU that load and cut in turn, 8192 x 8192 with
+// seven slices 255 us.)
+template <int MAXS>
+__device__ __forceinline__ void slice_k(const Operand& o, int64_t rb, int64_t lb, int64_t k, int64_t kp, int er, int8_t* __restrict__ out,
+                                        int S) {
+    typedef uint64_t pair __attribute__((ext_vector_type(2), aligned(8)));
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t r0 = rb * 64 + wave * 16, l0 = lb * 64;
+    const int64_t rows_here = o.rows - r0;
+    const bool row_ok = (lane >> 2) < rows_here;
+    // rows past the end read the last one, and count as zero
+    const uint64_t* const src = reinterpret_cast<const uint64_t*>(o.X) + min(r0 + (lane >> 2), o.rows - 1) * o.stride_r + l0 + (lane & 3) * 4;
+    const bool whole = l0 + 64 <= k;
+    auto load = [&](int c, uint64_t (&x)[4]) {
+        if (whole) {
 #pragma unroll
-        for (int it = 0; it < 16; ++it) {
-            const int rr = rr0 + it * 4;
-            const int64_t r = r0 + rr, l = l0 + ll;
-            const uint64_t x = __builtin_nontemporal_load(&src[(r < o.rows ? r : o.rows - 1) * o.stride_r + (l < k ? l : k - 1)]);
-            T[rr][ll] = (r < o.rows && l < k) ? x : 0ull;
+            for (int h = 0; h < 2; ++h) {
+                const pair p = __builtin_nontemporal_load(reinterpret_cast<const pair*>(src + c * 16 + h * 2));
+                x[2 * h] = row_ok ? p[0] : 0ull;
+                x[2 * h + 1] = row_ok ? p[1] : 0ull;
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int64_t l = l0 + c * 16 + (lane & 3) * 4 + e;
+                const uint64_t y = src[(l < k ? l : k - 1) - (l0 + (lane & 3) * 4)];
+                x[e] = row_ok && l < k ? y : 0ull;
+            }
+        }
+    };
+    auto put = [&](int c, const uint64_t (&x)[4]) {
+        emit<MAXS, 4>(x, er, S, out + ((l0 / 16 + c) * o.rows_p + r0) * 16, uint32_t(lane) * 4u, kp * o.rows_p);
+    };
+    if constexpr (MAXS <= 8) {
+        uint64_t bits[4][4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) load(c, bits[c]);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) put(c, bits[c]);
+    } else {                             // the wider words leave registers for one chunk in work and one on its way
+        uint64_t now[4], next[4] = {};
+        load(0, now);
+#pragma unroll 1
+        for (int c = 0; c < 4; ++c) {
+            if (c < 3) load(c + 1, next);
+            put(c, now);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) now[e] = next[e];
         }
     }
-    __syncthreads();
-    const int rr = threadIdx.x & 63, cc = threadIdx.x >> 6;
-    const int64_t r = r0 + rr;
-    uint64_t bits[16];
-#pragma unroll
-    for (int e = 0; e < 16; ++e) bits[e] = T[rr][cc * 16 + e];
-    const int64_t c = l0 / 16 + cc;
-    emit(bits, er, S, out + (c * o.rows_p + r) * 16, kp * o.rows_p);
 }
 
 struct SliceSide {
@@ -224,13 +312,17 @@ struct SliceSide {
     int64_t row_blocks, blocks;      // workgroups along the rows, in all
 };
 
-// workgroups [0, a.blocks) cut a, the others b (swapped: a is op(B)).  The LDS tile is dynamic: an operand with contiguous rows needs none
-__global__ __launch_bounds__(256) void slice_kernel(SliceSide a, SliceSide b, int64_t k, int64_t kp, const Record* rec, Batch bt, int swapped) {
-    extern __shared__ uint64_t slice_lds[];
+// workgroups [0, a.blocks) cut a, the others b
+// MAXS: the most slices the call can come out with
+template <int MAXS>
+__global__ __launch_bounds__(256, MAXS <= 8 ? 6 : 4) void slice_kernel(SliceSide a, SliceSide b, int64_t k, int64_t kp, const Record* rec, Batch bt) {
+    // FP64 rounds toward -infinity in this kernel (Fp64Cut).  As assembly, and before the loads that all FP64 arithmetic waits for: the
+    // compiler sets the mode back before such arithmetic where it knows of a change.
+    asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 2, 2), 2\n\ts_nop 1" ::: "memory");
     const bool second = int64_t(blockIdx.x) >= a.blocks;
     const int64_t ws = bt.ws_at(blockIdx.z);
     SliceSide s = second ? b : a;
-    s.o.X += (second != bool(swapped)) ? bt.b_at(blockIdx.z) : bt.a_at(blockIdx.z);
+    s.o.X += second ? bt.b_at(blockIdx.z) : bt.a_at(blockIdx.z);
     s.e_row = at_bytes(s.e_row, ws);
     s.out = at_bytes(s.out, ws);
     rec = at_bytes(rec, ws);
@@ -239,11 +331,11 @@ __global__ __launch_bounds__(256) void slice_kernel(SliceSide a, SliceSide b, in
     const bool rows = s.o.stride_r == 1;
     // the row's exponent is requested together with the record: two loads in a row before the operand's is what a small
     // call waits for
-    const int er = s.e_row[rows ? rb * 256 + threadIdx.x : rb * 64 + (threadIdx.x & 63)];
+    const int er = s.e_row[rows ? rb * 256 + threadIdx.x : rb * 64 + (threadIdx.x >> 2)];
     const int fallback = rec->res.fallback, S = rec->res.slices_used;
     if (fallback) return;
-    if (rows) slice_rows(s.o, rb, cb, k, kp, er, s.out, S);
-    else slice_k(s.o, rb, cb, k, kp, er, s.out, S, reinterpret_cast<uint64_t (*)[65]>(slice_lds));
+    if (rows) slice_rows<MAXS>(s.o, rb, cb, k, kp, er, s.out, S);
+    else slice_k<MAXS>(s.o, rb, cb, k, kp, er, s.out, S);
 }
 
 void launch_slice(hipStream_t st, const Operand& a, const Operand& b, const Workspace& w, const Problem& p) {
@@ -253,18 +345,11 @@ void launch_slice(hipStream_t st, const Operand& a, const Operand& b, const Work
         return SliceSide{o, e, out, rbs, rbs * (p.kp / (rows ? 16 : 64))};
     };
     const SliceSide sa = side(a, w.eA, w.As), sb = side(b, w.eB, w.Bs);
-    constexpr size_t kLds = 64 * 65 * sizeof(uint64_t);
-    const size_t lds_a = a.stride_r == 1 ? 0 : kLds, lds_b = b.stride_r == 1 ? 0 : kLds;
-    // Both operands in one launch where they need the same LDS, or where the launch itself is what counts (fewer
-    // workgroups than 16 per CU); otherwise the LDS tile of the one would halve the occupancy of the other.
-    const unsigned z = unsigned(p.batch.count);
-    if (lds_a == lds_b || (sa.blocks + sb.blocks) * z < int64_t(16) * p.num_cu) {
-        hipLaunchKernelGGL(slice_kernel, dim3(unsigned(sa.blocks + sb.blocks), 1, z), dim3(256), lds_a > lds_b ? lds_a : lds_b, st, sa,
-                           sb, p.k, p.kp, w.rec, p.batch, 0);
-    } else {
-        hipLaunchKernelGGL(slice_kernel, dim3(unsigned(sa.blocks), 1, z), dim3(256), lds_a, st, sa, sb, p.k, p.kp, w.rec, p.batch, 0);
-        hipLaunchKernelGGL(slice_kernel, dim3(unsigned(sb.blocks), 1, z), dim3(256), lds_b, st, sb, sa, p.k, p.kp, w.rec, p.batch, 1);
-    }
+    // a kernel for up to 8 slices, one for up to 16 and one for all: what the wider words need in registers would halve the
+    // waves in flight of the others
+    const auto kernel = p.s_cap <= 8 ? slice_kernel<8> : p.s_cap <= 16 ? slice_kernel<16> : slice_kernel<kMaxSlices>;
+    hipLaunchKernelGGL(kernel, dim3(unsigned(sa.blocks + sb.blocks), 1, unsigned(p.batch.count)), dim3(256), 0, st, sa, sb, p.k, p.kp, w.rec,
+                       p.batch);
 }
 
 }  // namespace oz

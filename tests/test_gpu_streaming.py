@@ -1,4 +1,6 @@
-"""Scan of operands larger than the Infinity Cache: exponents and ESC are the oracle's bit for bit."""
+"""Scan and slicing where their kernels branch: entries at either end of what the FP64 unit cuts (far below their row's largest, of both
+signs, exact and inexact), rows beyond its range, whole and ragged 64s of k in either storage order, and operands larger than
+the Infinity Cache.  Exponents and slices are the oracle's bit for bit."""
 import numpy as np
 import pytest
 
@@ -6,6 +8,37 @@ from oracle import ozaki as oz
 from test_gpu_parity import lib, run_gpu  # noqa: F401  (lib: fixture)
 
 pytestmark = pytest.mark.gpu
+
+
+def operand(rng, rows, k, extreme):
+    """Rows of magnitudes 2^-300 .. 2^300, entries down to 2^-200 below their row's largest; some whole numbers, halves and their
+    negatives of the last digit, zeros; extreme: every 40th row, beyond a wave of 64 rows that has none, near either end of the exponents."""
+    x = rng.uniform(-1.0, 1.0, (rows, k)) * np.exp2(rng.integers(-200, 1, (rows, k)).astype(float))
+    x[:, ::7] = rng.integers(-128, 129, (rows, len(range(0, k, 7)))) * 2.0 ** -9
+    x[::3, k // 2] = -2.0 ** -180
+    x[1::3, k // 3] = 0.0
+    x[:, 0] = rng.choice([-1.0, 1.0, 0.75, -0.5], rows)
+    x = np.ldexp(x, rng.integers(-300, 300, (rows, 1)))
+    if extreme:
+        at = np.arange(70, rows, 40)
+        x[at] = np.ldexp(rng.uniform(-1.0, 1.0, (len(at), k)), rng.choice([-1073, -1030, -1000, -950, 990, 1023], (len(at), 1)))
+        x[at[::4]] = 0.0
+    return x
+
+
+@pytest.mark.parametrize("S", [1, 2, 3, 4, 5, 7, 8, 9, 16, 17])
+@pytest.mark.parametrize("rows,k,extreme", [(300, 70, True), (257, 128, False), (64, 15, True), (130, 64, True)])
+def test_slices_of_either_storage_order(lib, S, rows, k, extreme):
+    g, h = lib
+    rng = np.random.default_rng(S * 1000 + rows)
+    A, B = operand(rng, rows, k, extreme), operand(rng, rows + 9, k, extreme).T.copy()
+    eA, eB = oz.row_exponents(A), oz.col_exponents(B)
+    want = oz.slice_rows(A, eA, S), oz.slice_rows(np.ascontiguousarray(B.T), eB, S)
+    for ta, tb in (("N", "N"), ("T", "T")):                   # either order of either operand
+        for pad in (0, 3):
+            _, gm, _ = run_gpu(g, h, A, B, 1.0, 0.0, None, ta, tb, pad, mode=g.OZ_FIXED_UNGUARDED, slices=S)
+            for got, ref in zip(gm.slices(S), want):
+                np.testing.assert_array_equal(got, ref)
 
 
 @pytest.mark.parametrize("ta", ["N", "T"])
