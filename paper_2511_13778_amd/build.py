@@ -21,9 +21,9 @@ FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-Wall", "-Wno-u
          "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I" + os.path.join(ROOT, "include"), "-I" + CSRC]
-# per-source additions.  oz_esc.hip: MFMA results are consumed by the vector ALU right away, so they
+# per-source additions.  ESC: MFMA results are consumed by the vector ALU right away, so they
 # are kept in ordinary VGPRs (the default puts them in accumulation registers and copies them out).
-SOURCE_FLAGS = {"oz_esc.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+SOURCE_FLAGS = {name: ["-mllvm", "-amdgpu-mfma-vgpr-form"] for name in ("oz_esc.hip",)}
 
 
 def _compile(src: str, extra=()) -> str:

@@ -424,8 +424,13 @@ oz_status_t dgemm_impl(oz_handle_t h, void* stream, char transa, char transb, in
 
     const bool guarded = opts->mode != OZ_FIXED_UNGUARDED;
     const Operand oa{A, a_sr, a_sl, m, p.mp}, ob{B, b_sr, b_sl, n, p.np};
-    launch_scan(st, oa, ob, w, p);
-    launch_exponents(st, oa, ob, w, p, guarded, guarded ? KnownRecord{} : KnownRecord{w.rec, result, known_verdict(p, *opts, 0)});
+    const KnownRecord known = guarded ? KnownRecord{} : KnownRecord{w.rec, result, known_verdict(p, *opts, 0)};
+    if (scan_once(p)) {
+        launch_scan_exponents(st, oa, ob, w, p, guarded, known);
+    } else {
+        launch_scan(st, oa, ob, w, p);
+        launch_exponents(st, oa, ob, w, p, guarded, known);
+    }
     clk.done(0);
     if (guarded) launch_esc_verdict(st, w, p, *opts, h->hm, result);
     clk.done(1);

@@ -24,7 +24,7 @@
 // they are dealt in: what were up to four more launches of 4-5 us each, in which one workgroup did something or none.
 #include <algorithm>
 
-#include "oz_internal.h"
+#include "oz_verdict.h"
 
 namespace oz {
 
@@ -32,11 +32,6 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x16_t __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-
-constexpr int kEncScale = 5;     // exponent units per bit of span; 16 equal terms stay below 2^5
-constexpr int kEncBias = 61;     // 2*61 + 4 < 128: a chunk sum cannot overflow FP32
-constexpr int kEncRange = 37;    // 5*(-37) + 61 >= -126: smallest encodable entry (BF16 normal)
-constexpr int kEncChunk = 16;    // inner steps per MFMA (K of v_mfma_f32_32x32x16_bf16)
 
 struct ExponentSide {
     const int16_t* group_max;     // [groups][rows_p]
@@ -99,9 +94,7 @@ __global__ __launch_bounds__(kExpRows * kExpWaves) void exponents_kernel(Exponen
         uint32_t w[4] = {0, 0, 0, 0};
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
-            const int d = x[q] - e;
-            const bool in_range = hc * 8 + q < H2 && x[q] > kSumRealFloor / 2 && d >= -kEncRange && d <= 0;
-            const uint32_t bits = in_range ? uint32_t(kEncScale * d + kEncBias + 127) << 7 : 0u;
+            const uint32_t bits = hc * 8 + q < H2 ? enc_bits(x[q], e) : 0u;
             w[q >> 1] |= bits << (16 * (q & 1));
         }
         s.enc[int64_t(hc) * s.rows_p + r] = make_uint4(w[0], w[1], w[2], w[3]);
@@ -355,79 +348,6 @@ __device__ __forceinline__ uint32_t least_sum(const uint4* __restrict__ EU, cons
     return least;
 }
 
-// What the host knows of the decision.
-struct VerdictArgs {
-    oz_opts_t o;
-    oz_heuristic_t hm;
-    int32_t s_cap, tile_mode;
-    int32_t nti, ntj, first, deal;       // per-block mode: the blocks, and how they are dealt (tile_order)
-    int32_t* tile_S;
-    oz_result_t* user;
-};
-
-// slice count of the fixed and forced modes
-__host__ __device__ inline int fixed_slices(const oz_opts_t& o) {
-    const int s = o.slices > 0 ? o.slices : (o.max_bits + 1 + 7) / 8;
-    return s < 1 ? 1 : (s > kMaxSlices ? kMaxSlices : s);
-}
-
-// Slice count and fallback decision of a guarded call from the scan's flag and the ESC.  pairs, smin: per-block mode,
-// pair products over all blocks and the smallest count.
-__device__ oz_result_t verdict(const VerdictArgs& v, int infnan, int span_max, unsigned long long pairs_all, int smin, int64_t m,
-                               int64_t n, int64_t k) {
-    const oz_opts_t& o = v.o;
-    oz_result_t r;
-    r.fallback = 0; r.reason = 0; r.slices_used = 0; r.esc = -1; r.required_bits = 0; r.infnan = 0;
-    r.slices_min = 0; r.reserved_ = 0; r.pair_tiles = 0;
-    const int64_t tiles = ((m + kTile - 1) / kTile) * ((n + kTile - 1) / kTile);
-    bool per_tile = false;    // the blocks of C carry their own counts
-    const int s_fixed = fixed_slices(o);
-    if (infnan) {
-        r.fallback = 1; r.reason = 1; r.infnan = 1;
-    } else {
-        const int esc = min(span_max + 1, kEscCap);
-        r.esc = esc;
-        r.required_bits = o.target_bits + esc;
-        // slices that hold required_bits, the sign and the headroom bit
-        int S = (o.target_bits + esc + 1 + kHeadroomBits + 7) / 8;
-        if (o.mode == OZ_FORCED_GUARDED) {
-            r.slices_used = s_fixed;
-        } else if (r.required_bits > o.max_bits) {
-            r.fallback = 1; r.reason = 2;
-        } else if (o.mode == OZ_FIXED_GUARDED) {
-            // the fixed slices must really carry the bits (S slices carry 8S - 2: "55 bits" is 54)
-            if (S > s_fixed) { r.fallback = 1; r.reason = 2; }
-            else r.slices_used = s_fixed;
-        } else {
-            S = max(1, min(S, kMaxSlices));
-            per_tile = v.tile_mode != 0;
-            bool slower = false;
-            if (o.heuristic) {
-                const int64_t flops = 2 * m * n * k;
-                // pair products per block of C: S(S+1)/2, or the mean over the blocks, rounded up
-                const int64_t pairs = per_tile ? int64_t((pairs_all + (unsigned long long)(tiles) - 1) /
-                                                         (unsigned long long)(tiles))
-                                               : int64_t(S) * (S + 1) / 2;
-                const int64_t stream = (16 + S) * (m * k + k * n) + (2 * int64_t(S) + 22) * m * n;
-                const int64_t t_emu = v.hm.fixed_ns + (flops / v.hm.int8_ops_per_ns) * pairs + stream / v.hm.bytes_per_ns;
-                const int64_t t_f64 = flops / v.hm.fp64_flops_per_ns;
-                slower = t_emu > t_f64;
-            }
-            if (slower) { r.fallback = 1; r.reason = 3; }
-            else r.slices_used = S;
-        }
-    }
-    // The workspace holds s_cap slice planes and the host sized it for the largest count these options
-    // can select, so this never binds; if it ever did, running with fewer slices would lose bits
-    // silently, so the call goes native and says why.
-    if (!r.fallback && r.slices_used > v.s_cap) { r.fallback = 1; r.reason = 2; r.slices_used = 0; }
-    if (!r.fallback && r.slices_used > 0) {
-        r.slices_min = per_tile ? smin : r.slices_used;
-        r.pair_tiles = per_tile ? int64_t(pairs_all) : tiles * (int64_t(r.slices_used) * (r.slices_used + 1) / 2);
-    }
-    return r;
-}
-
 // A workgroup takes every gridDim.x-th block of 128 x 128 pairs: few enough workgroups (two per CU) that their arrivals
 // at one counter do not queue up (17 ns each: one per block took 70 us at 8192^3).
 __global__ __launch_bounds__(256) void esc_kernel(const uint4* __restrict__ EU, const uint4* __restrict__ EV,
@@ -446,7 +366,7 @@ __global__ __launch_bounds__(256) void esc_kernel(const uint4* __restrict__ EU, 
         tile_span = at_bytes(tile_span, ws);
         v.tile_S = at_bytes(v.tile_S, ws);
     }
-    const int infnan = rec->infnan;
+    const int infnan = any_infnan(rec, v.infnan_parts);
     if (infnan) {
         // the native path is decided: one workgroup says so, no span is needed
         if (blockIdx.x != 0) return;
@@ -503,9 +423,7 @@ __global__ __launch_bounds__(256) void esc_kernel(const uint4* __restrict__ EU, 
     if (v.tile_mode) {
         // slice count of every kTile x kTile block of C from the largest span inside it
         for (int64_t t = threadIdx.x; t < int64_t(v.nti) * v.ntj; t += 256) {
-            const int esc = min(read(&tile_span[t]) + 1, kEscCap);
-            int S = (v.o.target_bits + esc + 1 + kHeadroomBits + 7) / 8;
-            S = max(1, min(S, kMaxSlices));
+            const int S = span_slices(v.o, read(&tile_span[t]));
             v.tile_S[t] = S;
             pairs += (unsigned long long)(S) * (S + 1) / 2;
             smin = min(smin, S);
@@ -579,8 +497,7 @@ void launch_esc_verdict(hipStream_t st, const Workspace& w, const Problem& p, co
     const int steps = (H2 + 2 * kEncChunk - 1) / (2 * kEncChunk);   // 32 inner steps (4 groups of 8) each
     uint4* const EU = reinterpret_cast<uint4*>(w.EU);
     uint4* const EV = reinterpret_cast<uint4*>(w.EV);
-    VerdictArgs v = {o, hm, p.s_cap, p.tile_mode, int(p.mp / kTile), int(p.np / kTile), 0, 0, w.tile_S, user_result};
-    if (p.tile_mode) tile_order_shape(p, v.first, v.deal);
+    const VerdictArgs v = verdict_args(w, p, o, hm, user_result);
     const int64_t blocks = (p.mp / kEscTile) * (p.np / kEscTile);
     hipLaunchKernelGGL(esc_kernel, dim3(unsigned(std::min<int64_t>(blocks, std::max(1, 2 * p.num_cu / p.batch.count))), 1, unsigned(p.batch.count)), dim3(256), 0, st, EU, EV, w.U,
                        w.V, w.eA, w.eB, p.m, p.n, p.k, p.mp, p.np, H2, steps, w.rec, w.tile_span, v, p.batch);

@@ -34,6 +34,22 @@ constexpr int kKPad = 128;            // k is padded to this (a multiple of the 
 constexpr int kTile = 256;            // edge of the blocks of C that can take their own slice count (kRowPad is a multiple):
                                       // two by two units of gemm_i8_kernel, one workgroup's share in gemm_i8_few_kernel
 
+// ---- a scan whose workgroups hold all of k (scan_exponents_kernel) ----------------------
+constexpr int kOnceRows = 16;         // rows of a workgroup
+constexpr int kScanOnceParts = 128;   // most workgroups
+constexpr int kScanOnceBlocks = 32;   // most ESC blocks
+
+// ---- encoding of the block tables for the ESC on the matrix unit (oz_esc.hip) --------------
+constexpr int kEncScale = 5;     // exponent units per bit of span; 16 equal terms stay below 2^5
+constexpr int kEncBias = 61;     // 2*61 + 4 < 128: a chunk sum cannot overflow FP32
+constexpr int kEncRange = 37;    // 5*(-37) + 61 >= -126: smallest encodable entry (BF16 normal)
+constexpr int kEncChunk = 16;    // inner steps per MFMA (K of v_mfma_f32_32x32x16_bf16)
+// BF16 bits of 2^(5 (x - e) + 61), 0 for what the code does not hold
+__device__ __forceinline__ uint32_t enc_bits(int x, int e) {
+    const int d = x - e;
+    return x > kSumRealFloor / 2 && d >= -kEncRange && d <= 0 ? uint32_t(kEncScale * d + kEncBias + 127) << 7 : 0u;
+}
+
 // ---- device-resident control record ---------------------------------------------------
 struct Record {
     int32_t infnan;        // cleared by the scan, set by exponents_kernel for a row or column exponent of kExpInfNan
@@ -42,6 +58,7 @@ struct Record {
     int32_t pad_;
     int32_t tile_sync[8];  // per-XCD arrival counters of the slice GEMM's workgroups
     oz_result_t res;       // the verdict, read by every later kernel
+    uint8_t infnan_part[kScanOnceParts];   // of a call that is scanned in one launch: the flag of every workgroup, instead of infnan
 };
 
 // A record that the host knows before anything runs (no guards, or the native GEMM chosen by the cost model), written
@@ -242,6 +259,10 @@ struct Operand {
     int64_t rows, rows_p;
 };
 void launch_scan(hipStream_t st, const Operand& a, const Operand& b, const Workspace& w, const Problem& p);
+// both in one launch, where a workgroup can hold all of k of its rows
+bool scan_once(const Problem& p);
+void launch_scan_exponents(hipStream_t st, const Operand& a, const Operand& b, const Workspace& w, const Problem& p, bool encode,
+                           const KnownRecord& known);
 // row and column exponents, the cleared control record, and (encode) the BF16 tables of the ESC
 void launch_exponents(hipStream_t st, const Operand& a, const Operand& b, const Workspace& w, const Problem& p, bool encode,
                       const KnownRecord& known);
@@ -255,6 +276,10 @@ void launch_known_record(hipStream_t st, const KnownRecord& known);
 // whether the problems of p.batch can share the launches of an emulated call: few enough units of C for all of them, or small
 // calls (LaunchPlan)
 bool can_batch(const Problem& p);
+// ESC, verdict and slicing of a call so small that every workgroup of the slicing can decide for itself
+bool decide_in_slice(const Problem& p);
+void launch_esc_slice(hipStream_t st, const Operand& a, const Operand& b, const Workspace& w, const Problem& p, const oz_opts_t& o,
+                      const oz_heuristic_t& hm, oz_result_t* user_result);
 void launch_slice(hipStream_t st, const Operand& a, const Operand& b, const Workspace& w, const Problem& p);
 // per-block mode: blocks of the slice GEMM's first launch, and whether they are sorted by slice count
 void tile_order_shape(const Problem& p, int& first, int& deal);

@@ -196,6 +196,50 @@ __device__ __forceinline__ uint32_t pk_max_dpp(uint32_t x) {
 __device__ __forceinline__ int code_exp(uint32_t code) {     // of a non-zero entry
     return code >= kLowCodes ? int((code - kLowCodes) >> 4) - 1023 : int(code) - 1075;
 }
+// codes of 16 entries into 16 words
+__device__ __forceinline__ void add_codes(const uint64_t (&x)[16], uint32_t (&stat)[16]) {
+    uint32_t least = ~0u;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) least = min(least, uint32_t(x[i] >> 32) << 1);
+    if (!__any(least < 2 * BlockStat::kMinNormal)) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const uint32_t hi = uint32_t(x[i] >> 32);
+            const u16x2 top = __builtin_bit_cast(u16x2, __builtin_amdgcn_perm(hi, hi, 0x07060706u) & 0x7FFF7FFFu);
+            stat[i] = pk_max(stat[i], __builtin_bit_cast(uint32_t, top * u16x2{1, 0xFFFF} + u16x2{kLowCodes, 0xFFFF - kLowCodes}));
+        }
+    } else {                             // a zero or a denormal among them
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            uint32_t hi = uint32_t(x[i] >> 32);
+            asm volatile("" : "+v"(hi));             // one entry at a time: registers
+            hi &= 0x7FFFFFFFu;
+            const uint32_t lo = uint32_t(x[i]);
+            const uint32_t low = hi ? 64 - __builtin_clz(hi) : (lo ? 32 - __builtin_clz(lo) : 0u);
+            const uint32_t code = hi >= BlockStat::kMinNormal ? (hi >> 16) + kLowCodes : low;
+            stat[i] = pk_max(stat[i], code | ((0xFFFFu - code) << 16));
+        }
+    }
+}
+// 16 words of 64 lanes, a row each, to one word per row: row 4 (lane / 16) + lane % 4
+__device__ __forceinline__ uint32_t fold_rows(uint32_t (&stat)[16], int lane) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const auto p = __builtin_amdgcn_permlane32_swap(stat[i], stat[i + 8], false, false);
+        stat[i] = pk_max(p[0], p[1]);                      // lanes 0 .. 31 row i, 32 .. 63 row i + 8
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const auto p = __builtin_amdgcn_permlane16_swap(stat[i], stat[i + 4], false, false);
+        uint32_t x = pk_max(p[0], p[1]);                   // rows i, i + 4, i + 8, i + 12, in 16 lanes each
+        x = pk_max_dpp<0x128>(x);                          // row_ror 8, 4, 2, 1
+        x = pk_max_dpp<0x124>(x);
+        x = pk_max_dpp<0x122>(x);
+        stat[i] = pk_max_dpp<0x121>(x);
+    }
+    const uint32_t low = (lane & 1) ? stat[1] : stat[0], high = (lane & 1) ? stat[3] : stat[2];
+    return (lane & 2) ? high : low;
+}
 template <bool NT>
 __device__ __forceinline__ void scan_k64(const ScanSide& s, int64_t rb, int g0, int per, int64_t k, int b, int G) {
     const int lane = threadIdx.x & 63;
@@ -224,44 +268,9 @@ __device__ __forceinline__ void scan_k64(const ScanSide& s, int64_t rb, int g0, 
                 x[i] = load_entry<NT>(reinterpret_cast<const uint64_t*>(row + at));
                 row += i < last_row ? row_bytes : 0;
             }
-            uint32_t least = ~0u;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) least = min(least, uint32_t(x[i] >> 32) << 1);
-            if (!__any(least < 2 * BlockStat::kMinNormal)) {
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const uint32_t hi = uint32_t(x[i] >> 32);
-                    const u16x2 top = __builtin_bit_cast(u16x2, __builtin_amdgcn_perm(hi, hi, 0x07060706u) & 0x7FFF7FFFu);
-                    stat[i] = pk_max(stat[i], __builtin_bit_cast(uint32_t, top * u16x2{1, 0xFFFF} + u16x2{kLowCodes, 0xFFFF - kLowCodes}));
-                }
-            } else {                     // a zero or a denormal among them
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    uint32_t hi = uint32_t(x[i] >> 32);
-                    asm volatile("" : "+v"(hi));             // one entry at a time: registers
-                    hi &= 0x7FFFFFFFu;
-                    const uint32_t lo = uint32_t(x[i]);
-                    const uint32_t low = hi ? 64 - __builtin_clz(hi) : (lo ? 32 - __builtin_clz(lo) : 0u);
-                    const uint32_t code = hi >= BlockStat::kMinNormal ? (hi >> 16) + kLowCodes : low;
-                    stat[i] = pk_max(stat[i], code | ((0xFFFFu - code) << 16));
-                }
-            }
+            add_codes(x, stat);
         }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const auto p = __builtin_amdgcn_permlane32_swap(stat[i], stat[i + 8], false, false);
-            stat[i] = pk_max(p[0], p[1]);                  // lanes 0 .. 31 row i, 32 .. 63 row i + 8
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const auto p = __builtin_amdgcn_permlane16_swap(stat[i], stat[i + 4], false, false);
-            uint32_t x = pk_max(p[0], p[1]);               // rows i, i + 4, i + 8, i + 12, in 16 lanes each
-            x = pk_max_dpp<0x128>(x);                      // row_ror 8, 4, 2, 1
-            x = pk_max_dpp<0x124>(x);
-            x = pk_max_dpp<0x122>(x);
-            stat[i] = pk_max_dpp<0x121>(x);
-        }
-        const uint32_t mine = (lane & 2) ? ((lane & 1) ? stat[3] : stat[2]) : ((lane & 1) ? stat[1] : stat[0]);
+        const uint32_t mine = fold_rows(stat, lane);
         const uint32_t largest = my_row <= last_row ? mine & 0xFFFFu : 0u, smallest = 0xFFFFu - (mine >> 16);
         if ((lane & 12) == 0)
             scan_store(s, G, g, r0 + my_row, largest ? code_exp(largest) : kExpAllZero,
@@ -306,6 +315,142 @@ void launch_scan(hipStream_t st, const Operand& a, const Operand& b, const Works
         hipLaunchKernelGGL(kernel, dim3(unsigned((g.row_blocks_a + g.row_blocks_b) * gy), 1, unsigned(p.batch.count)), dim3(256), 0, st, sa, sb,
                            g.row_blocks_a * gy, int(y) * g.per, g.per, p.k, p.esc_block, p.G, w.rec, p.batch);
     }
+}
+
+// ---- scan and exponents of a small call in one launch --------------------------------------
+// A workgroup of 8 waves takes 16 rows and all of k.  Pieces of 64 k of a block, 16 loads a lane, go to the waves in turn and meet, as
+// codes, in LDS; then row exponents, tables, and their encoding.  What a small call waits for is the chain of its launches, and
+// this is one less.  16 rows, so that as many CUs read as there are: with 64 a call of 512 x 512 x 1024 had 16 workgroups and took
+// 5 us more than in two launches.
+constexpr int kOnceWaves = 8;
+static_assert(kOnceRows == 16, "four groups of 16 lanes");
+
+struct ScanOnceSide {
+    ScanSide s;
+    int32_t* e;
+    uint4* enc;
+};
+
+__global__ __launch_bounds__(64 * kOnceWaves) void scan_exponents_kernel(ScanOnceSide a, ScanOnceSide b, int blocks_a, int64_t k, int bl, int G,
+                                                                         int chunks, Record* rec, int32_t* __restrict__ tile_span, int64_t tiles,
+                                                                         KnownRecord known, Batch bt) {
+    __shared__ uint32_t most[kScanOnceBlocks][kOnceRows], least[kScanOnceBlocks][kOnceRows];       // largest and smallest code
+    const bool second = int(blockIdx.x) >= blocks_a;
+    const int64_t ws = bt.ws_at(blockIdx.z);
+    ScanOnceSide t = second ? b : a;
+    const Operand o = t.s.o;
+    const double* const X = o.X + (second ? bt.b_at(blockIdx.z) : bt.a_at(blockIdx.z));
+    rec = at_bytes(rec, ws);
+    tile_span = at_bytes(tile_span, ws);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int row = threadIdx.x & (kOnceRows - 1), place = threadIdx.x / kOnceRows;          // what a thread finishes
+    constexpr int kPlaces = 64 * kOnceWaves / kOnceRows;
+    const int64_t r0 = int64_t(int(blockIdx.x) - (second ? blocks_a : 0)) * kOnceRows;
+    for (int g = place; g < G; g += kPlaces) {
+        most[g][row] = 0;
+        least[g][row] = 0xFFFFu;
+    }
+    if (blockIdx.x == 0) {
+        if (threadIdx.x == 0) {
+            rec->span_max = 0;
+            rec->esc_done = 0;
+            write_known_record(known, bt, int(blockIdx.z));
+        }
+        if (threadIdx.x < 8) rec->tile_sync[threadIdx.x] = 0;
+        for (int64_t x = threadIdx.x; x < tiles; x += 64 * kOnceWaves) tile_span[x] = 0;
+    }
+    __syncthreads();
+    const int last_row = int(max(min(int64_t(kOnceRows), o.rows - r0), int64_t(0))) - 1;     // -1: padding only
+    const int per_block = (bl + 63) / 64, pieces = last_row < 0 ? 0 : G * per_block;
+    for (int piece = wave; piece < pieces; piece += kOnceWaves) {
+        const int g = piece / per_block, l = (piece - g * per_block) * 64;
+        const int64_t l0 = int64_t(g) * bl;
+        const int len = int(min(int64_t(bl), k - l0));
+        if (l >= len) continue;
+        // past the end of a block its last entry is read again, past the last row that row
+        uint64_t x[16];
+        uint32_t stat[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) stat[i] = 0;
+        uint32_t mine;
+        int my_row;
+        bool holds;
+        if (o.stride_r == 1) {           // a load: 16 rows of four k
+            const uint32_t at = uint32_t(min(lane & 15, last_row)) * 8u;
+            const char* const src = reinterpret_cast<const char*>(X + r0 + l0 * o.stride_l);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) x[i] = *reinterpret_cast<const uint64_t*>(src + min(l + 4 * i + (lane >> 4), len - 1) * o.stride_l * 8 + at);
+            add_codes(x, stat);
+#pragma unroll
+            for (int i = 1; i < 16; ++i) stat[0] = pk_max(stat[0], stat[i]);
+            mine = stat[0];
+            my_row = lane & 15;
+            holds = true;
+        } else {                         // a load: 64 k of a row
+            const uint32_t at = uint32_t(min(l + lane, len - 1)) * 8u;
+            const char* const src = reinterpret_cast<const char*>(X + r0 * o.stride_r + l0);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) x[i] = *reinterpret_cast<const uint64_t*>(src + min(i, last_row) * o.stride_r * 8 + at);
+            add_codes(x, stat);
+            mine = fold_rows(stat, lane);
+            my_row = (lane >> 4) * 4 + (lane & 3);
+            holds = (lane & 12) == 0;
+        }
+        if (holds && my_row <= last_row) {
+            atomicMax(&most[g][my_row], mine & 0xFFFFu);
+            atomicMin(&least[g][my_row], 0xFFFFu - (mine >> 16));
+        }
+    }
+    __syncthreads();
+    auto table = [&](bool largest, int g) -> int {
+        const uint32_t hi = most[g][row], lo = least[g][row];
+        if (hi == 0) return kExpAllZero;
+        return largest ? code_exp(hi) : (lo ? code_exp(lo) : kExpZeroInMin);
+    };
+    uint32_t top = 0;
+    for (int g = 0; g < G; ++g) top = max(top, most[g][row]);
+    const int e = top ? code_exp(top) : kExpAllZero;
+    if (wave == 0) {
+        if (place == 0) at_bytes(t.e, ws)[r0 + row] = e;
+        const bool bad = __any(e == kExpInfNan);
+        if (lane == 0) rec->infnan_part[blockIdx.x] = bad ? 1 : 0;
+    }
+    if (chunks == 0) return;                                 // no guards: nobody reads the tables
+    int16_t* const tab = at_bytes(t.s.tab, ws);
+    for (int h = place; h < 2 * G; h += kPlaces) {
+        const bool half = h >= G;
+        tab[int64_t(h) * o.rows_p + r0 + row] = int16_t(table(half != bool(t.s.max_half), half ? h - G : h));
+    }
+    uint4* const enc = at_bytes(t.enc, ws);
+    for (int hc = place; hc < chunks; hc += kPlaces) {
+        uint32_t w[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int h = hc * 8 + q;
+            if (h < 2 * G) {
+                const bool half = h >= G;
+                w[q >> 1] |= enc_bits(table(half != bool(t.s.max_half), half ? h - G : h), e) << (16 * (q & 1));
+            }
+        }
+        enc[int64_t(hc) * o.rows_p + r0 + row] = make_uint4(w[0], w[1], w[2], w[3]);
+    }
+}
+
+// Up to 1024 of k: one launch takes 2 to 4 us less (64 x 64 x 500 with seven slices 36.7 -> 30.5 us a call, 200 x 300 x 260 31.8 -> 30.2, 512^3
+// 41.4 -> 39.9, 1024^3 58.9 -> 56.6); beyond, the few workgroups are the slower way (512 x 512 x 2048 63.1 -> 64.4, 700 x 700 x 2000 79.7 -> 81.7).
+bool scan_once(const Problem& p) {
+    return p.k <= 1024 && p.G <= kScanOnceBlocks && (p.mp + p.np) / kOnceRows <= kScanOnceParts;
+}
+
+void launch_scan_exponents(hipStream_t st, const Operand& a, const Operand& b, const Workspace& w, const Problem& p, bool encode,
+                           const KnownRecord& known) {
+    const int chunks = encode ? (2 * p.G + 2 * kEncChunk - 1) / (2 * kEncChunk) * 4 : 0;
+    const int blocks_a = int(p.mp / kOnceRows), blocks = int((p.mp + p.np) / kOnceRows);
+    const ScanOnceSide sa{ScanSide{a, w.U, 1, nullptr, blocks_a}, w.eA, reinterpret_cast<uint4*>(w.EU)};
+    const ScanOnceSide sb{ScanSide{b, w.V, 0, nullptr, blocks - blocks_a}, w.eB, reinterpret_cast<uint4*>(w.EV)};
+    hipLaunchKernelGGL(scan_exponents_kernel, dim3(unsigned(blocks), 1, unsigned(p.batch.count)), dim3(64 * kOnceWaves), 0, st, sa, sb, blocks_a, p.k,
+                       p.esc_block, p.G, chunks, w.rec, w.tile_span, (p.mp / kTile) * (p.np / kTile), known, p.batch);
 }
 
 }  // namespace oz

@@ -4,306 +4,13 @@
 //  leading slice is rounded toward -infinity so that the remainder is non-negative, and every
 //  sub-leading u8 digit >= 128 is stored as digit-256 with a carry into the next higher digit.)
 //
-// For an entry a of a row with exponent e_row and S slices:
-//   X = floor(a * 2^q),  q = 8S - 3 - e_row,  |X| < 2^(8S-2)   (one headroom bit)
-//   X = sum_s d_s 256^(S-1-s),  d_s in [-128, 127].
-// a = sgn * M * 2^(E-1075) with the integer significand M, so X = (sgn*M) shifted by
-// E - 1075 + q: written here as a 64-bit window W at bit offset o (X = W * 2^o), which covers
-// any S up to 26 without multi-word arithmetic (up to 8 and up to 16 slices take one word of 64 or 128 bits instead).
-//
 // Output layout (what the INT8 GEMM's tiles load with contiguous 16-byte pieces):
 //   slices[s][l/16][r][l%16]  for row r (padded to rows_p), k index l (padded to kp); padding = 0.
 // HBM-bound: 8 B read and S bytes written per element; 8192^3 with seven slices 360 to 410 us by storage order, 4.9 to 5.6 TB/s (a copy
 // reaches 5.6).  Operands and slices are touched once per call here, so loads and stores carry the streaming (non-temporal) hint.
-#include "oz_internal.h"
+#include "oz_slice_device.h"
 
 namespace oz {
-
-struct Fixed {
-    int64_t W;
-    int o;
-};
-
-__device__ __forceinline__ Fixed fixed_point(uint64_t bits, int e_row, int S) {
-    const uint64_t mag = bits & 0x7FFFFFFFFFFFFFFFull;
-    Fixed f;
-    f.W = 0;
-    f.o = 0;
-    if (mag == 0 || e_row <= kExpAllZero) return f;
-    const int field = int(mag >> 52);
-    const uint64_t frac = mag & 0x000FFFFFFFFFFFFFull;
-    const int64_t M = int64_t(field ? (frac | 0x0010000000000000ull) : frac);
-    const int64_t sM = (bits >> 63) ? -M : M;
-    const int sh = max(field, 1) - 1075 + (8 * S - 2 - kHeadroomBits - e_row);
-    if (sh >= 0) {
-        f.W = sM;
-        f.o = min(sh, 8 * S);   // only Inf/NaN input (unguarded mode) can reach the clamp
-    } else {
-        f.W = sM >> min(-sh, 63);   // arithmetic shift: rounds toward -infinity
-    }
-    return f;
-}
-
-// bits [8b, 8b+8) of W * 2^o (two's complement, sign-extended), b = 0 least significant
-__device__ __forceinline__ uint32_t byte_of(const Fixed& f, int b) {
-    const int p = 8 * b - f.o;
-    if (p >= 0) return uint32_t(f.W >> min(p, 63)) & 0xFFu;
-    if (p > -8) return (uint32_t(f.W) << (-p)) & 0xFFu;
-    return 0u;
-}
-
-// N = 4 or 16 consecutive k of one row leave N bytes per slice.
-template <int N>
-__device__ __forceinline__ void store_digits(const uint32_t (&w)[N / 4], int8_t* plane, uint32_t lane_off) {
-    typedef uint32_t vec __attribute__((ext_vector_type(N / 4)));
-    vec v;
-    if constexpr (N == 4) v = w[0];
-    else v = vec{w[0], w[1], w[2], w[3]};
-    __builtin_nontemporal_store(v, reinterpret_cast<vec*>(plane + lane_off));
-}
-
-// Digits of N consecutive k of one row, least significant slice first.
-template <int N>
-__device__ __forceinline__ void emit_slices(const Fixed (&f)[N], int S, int8_t* plane0, uint32_t lane_off, int64_t slice_stride) {
-    uint32_t carry[N];
-#pragma unroll
-    for (int e = 0; e < N; ++e) carry[e] = 0;
-    for (int s = S - 1; s >= 0; --s) {
-        const int b = S - 1 - s;
-        uint32_t w[N / 4] = {};
-#pragma unroll
-        for (int e = 0; e < N; ++e) {
-            const uint32_t u = byte_of(f[e], b) + carry[e];
-            carry[e] = (u >= 128u) ? 1u : 0u;       // unused after the leading slice
-            w[e >> 2] |= (u & 0xFFu) << (8 * (e & 3));
-        }
-        store_digits<N>(w, plane0 + int64_t(s) * slice_stride, lane_off);
-    }
-}
-
-// Up to 8 slices the whole fixed-point value fits one 64-bit word, and the carry chain of the remap
-// collapses into one addition: with BIAS = 0x80 in every sub-leading byte, the digits are the bytes
-// of X + BIAS with the top bit of every sub-leading byte flipped.
-//
-// X for S <= 8 without branches: with sh = max(field,1) - 1075 + q (q = 8S - 3 - e_row) it is
-// sM << sh or sM >> -sh (arithmetic: rounds toward -infinity), both computed and one selected;
-// shift counts are clamped to 63 (a left shift beyond the word only happens for Inf/NaN input in
-// unguarded mode).  Zeros, all-zero rows and padding have sM = 0 and need no special case.
-__device__ __forceinline__ uint64_t biased_fixed64(uint64_t bits, int q_minus_1075, uint64_t bias) {
-    const uint64_t mag = bits & 0x7FFFFFFFFFFFFFFFull;
-    const int field = int(mag >> 52);
-    const uint64_t frac = mag & 0x000FFFFFFFFFFFFFull;
-    const uint64_t M = field ? (frac | 0x0010000000000000ull) : frac;
-    const uint64_t sgn = uint64_t(int64_t(bits) >> 63);              // all ones for negative entries
-    const int64_t sM = int64_t((M ^ sgn) - sgn);
-    const int sh = max(field, 1) + q_minus_1075;
-    const int64_t left = sM << min(max(sh, 0), 63);
-    const int64_t right = sM >> min(max(-sh, 0), 63);
-    return uint64_t(sh >= 0 ? left : right) + bias;
-}
-
-// The same for 9 to 16 slices on 128 bits.  sh beyond the word leaves zeros (only Inf/NaN input in unguarded mode).
-// (Digit by digit with a carry per element instead: 100 us for 4096 x 4096 with nine slices, now 58.)
-__device__ __forceinline__ void biased_fixed128(uint64_t bits, int q_minus_1075, uint64_t bias_lo, uint64_t bias_hi,
-                                                uint64_t& lo, uint64_t& hi) {
-    const uint64_t mag = bits & 0x7FFFFFFFFFFFFFFFull;
-    const int field = int(mag >> 52);
-    const uint64_t frac = mag & 0x000FFFFFFFFFFFFFull;
-    const uint64_t M = field ? (frac | 0x0010000000000000ull) : frac;
-    const uint64_t sgn = uint64_t(int64_t(bits) >> 63);
-    const int64_t sM = int64_t((M ^ sgn) - sgn);
-    const int sh = max(field, 1) + q_minus_1075;
-    const int up = min(max(sh, 0), 127), down = min(max(-sh, 0), 63);
-    const int64_t low = up < 64 ? int64_t(uint64_t(sM) << (up & 63)) : 0;
-    // bits 64.. of sM << up: for up < 64 what falls out at the top (with the sign above it)
-    const int64_t high = up < 64 ? (sM >> 1) >> (63 - (up & 63)) : int64_t(uint64_t(sM) << (up & 63));
-    const int64_t right = sM >> down;
-    const bool out = sh > 127;
-    const uint64_t x_lo = out ? 0ull : uint64_t(sh >= 0 ? low : right), x_hi = out ? 0ull : uint64_t(sh >= 0 ? high : right >> 63);
-    lo = x_lo + bias_lo;
-    hi = x_hi + bias_hi + (lo < x_lo ? 1ull : 0ull);
-}
-
-// X + BIAS for S <= 8 on the FP64 unit, in five instructions instead of 24: with the unit rounding toward -infinity, adding
-// 1.5 * 2^52 leaves floor(a * 2^(q-32)) in the low word, what that leaves over is in [0, 1), and 2^32 times that plus 2^52 leaves the
-// low word of X in the low word.  Rounding the rest (an entry far below its row's largest, negative) downwards changes no floor.  The
-// two constants carry the bias: its low word may carry into the upper word of the second sum, which is added to the first.
-// (Both operands of 8192^3, seven slices, rows contiguous: 447 us in integer arithmetic at 128 registers, now 360.)
-struct Fp64Cut {
-    double scale, magic_hi, magic_lo;
-    static constexpr uint32_t kTwo52 = 0x43300000u;          // upper word of 2^52
-    // q_minus_32 within the exponents of normal numbers
-    __device__ __forceinline__ Fp64Cut(int q_minus_32, uint64_t bias)
-        : scale(__builtin_bit_cast(double, uint64_t(q_minus_32 + 1023) << 52)),
-          magic_hi(__builtin_bit_cast(double, 0x4338000000000000ull | uint32_t(uint32_t(bias >> 32) - kTwo52))),
-          magic_lo(__builtin_bit_cast(double, uint64_t(kTwo52) << 32 | uint32_t(bias))) {}
-    __device__ __forceinline__ void cut(uint64_t bits, uint32_t& lo, uint32_t& hi) const {
-        const double a = __builtin_bit_cast(double, bits);
-        const double h = __builtin_fma(a, scale, magic_hi);
-        const double rest = __builtin_fma(a, scale, -(h - magic_hi));
-        const uint64_t l = __builtin_bit_cast(uint64_t, __builtin_fma(rest, 0x1p32, magic_lo));
-        lo = uint32_t(l);
-        hi = uint32_t(__builtin_bit_cast(uint64_t, h)) + uint32_t(l >> 32);
-    }
-};
-
-// Byte b of N values (NW dwords each, least significant first) goes to plane S - 1 - b, four values to a dword: transposes of four
-// dwords in two steps of byte permutes.
-template <int NW, int N>
-__device__ __forceinline__ void emit_words(const uint32_t (&y)[NW][N], int S, int8_t* plane0, uint32_t lane_off, int64_t slice_stride) {
-#pragma unroll
-    for (int v = NW - 1; v >= 0; --v) {
-        if (4 * v >= S) continue;
-#pragma unroll
-        for (int half = 1; half >= 0; --half) {              // bytes 2, 3 and 0, 1
-            if (4 * v + 2 * half >= S) continue;
-            uint32_t w[2][N / 4];
-#pragma unroll
-            for (int j = 0; j < N / 4; ++j) {
-                const uint32_t pick = half ? 0x07030602u : 0x05010400u;
-                const uint32_t t01 = __builtin_amdgcn_perm(y[v][4 * j + 1], y[v][4 * j], pick);
-                const uint32_t t23 = __builtin_amdgcn_perm(y[v][4 * j + 3], y[v][4 * j + 2], pick);
-                w[0][j] = __builtin_amdgcn_perm(t23, t01, 0x05040100u);
-                w[1][j] = __builtin_amdgcn_perm(t23, t01, 0x07060302u);
-            }
-#pragma unroll
-            for (int q = 1; q >= 0; --q) {
-                const int b = 4 * v + 2 * half + q;
-                if (b >= S) continue;
-                const uint32_t flip = b == S - 1 ? 0u : 0x80808080u;     // the leading digit keeps its sign bit
-#pragma unroll
-                for (int j = 0; j < N / 4; ++j) w[q][j] ^= flip;
-                store_digits<N>(w[q], plane0 + int64_t(S - 1 - b) * slice_stride, lane_off);
-            }
-        }
-    }
-}
-
-// plane0: where the first plane's entries of this wave lie (uniform), lane_off: bytes to this lane's
-template <int MAXS, int N>
-__device__ __forceinline__ void emit(const uint64_t (&bits)[N], int e_row, int S, int8_t* plane0, uint32_t lane_off,
-                                     int64_t slice_stride) {
-    const int q = 8 * S - 2 - kHeadroomBits - (e_row > kExpAllZero ? e_row : 0);
-    if (S <= 8) {
-        const uint64_t bias = S >= 2 ? (0x8080808080808080ull >> (8 * (9 - S))) : 0ull;
-        uint32_t y[2][N];
-        // Inf and NaN (unguarded mode), and rows of 2^-960 and less, whose factor is no normal number: integer arithmetic
-        if (__all(e_row < kExpInfNan && q - 32 >= -1022 && q - 32 <= 1023)) {
-            const Fp64Cut c(q - 32, bias);
-#pragma unroll
-            for (int e = 0; e < N; ++e) c.cut(bits[e], y[0][e], y[1][e]);
-        } else {
-#pragma unroll
-            for (int e = 0; e < N; ++e) {
-                const uint64_t x = biased_fixed64(bits[e], q - 1075, bias);
-                y[0][e] = uint32_t(x);
-                y[1][e] = uint32_t(x >> 32);
-                __builtin_amdgcn_sched_barrier(0);           // one at a time: registers
-            }
-        }
-        emit_words<2, N>(y, S, plane0, lane_off, slice_stride);
-        return;
-    }
-    if constexpr (MAXS > 8) {
-        if (S <= 16) {
-            const uint64_t bias_hi = S >= 10 ? (0x8080808080808080ull >> (8 * (17 - S))) : 0ull;
-            uint32_t y[4][N];
-#pragma unroll
-            for (int e = 0; e < N; ++e) {
-                uint64_t lo, hi;
-                biased_fixed128(bits[e], q - 1075, 0x8080808080808080ull, bias_hi, lo, hi);
-                y[0][e] = uint32_t(lo);
-                y[1][e] = uint32_t(lo >> 32);
-                y[2][e] = uint32_t(hi);
-                y[3][e] = uint32_t(hi >> 32);
-            }
-            emit_words<4, N>(y, S, plane0, lane_off, slice_stride);
-            return;
-        }
-    }
-    if constexpr (MAXS > 16) {
-        Fixed f[N];
-#pragma unroll
-        for (int e = 0; e < N; ++e) f[e] = fixed_point(bits[e], e_row, S);
-        emit_slices<N>(f, S, plane0, lane_off, slice_stride);
-    }
-}
-
-// Rows contiguous in memory: thread = row, lanes along rows; loads coalesce across the wave.
-// A workgroup cuts 256 rows x 16 k (chunk c).
-template <int MAXS>
-__device__ __forceinline__ void slice_rows(const Operand& o, int64_t rb, int64_t c, int64_t k, int64_t kp, int er,
-                                           int8_t* __restrict__ out, int S) {
-    // loads are unconditional at clamped addresses (rows >= 1 and k >= 1 here, and every block of rows has one); out-of-range
-    // elements are then replaced by zero, so the loop has no divergent branches
-    const int64_t rows_here = o.rows - rb * 256;
-    const bool row_ok = int64_t(threadIdx.x) < rows_here;
-    const uint32_t lane = uint32_t(min(int64_t(threadIdx.x), rows_here - 1)) * 8u;
-    const char* const src = reinterpret_cast<const char*>(o.X + rb * 256);
-    uint64_t bits[16];
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        const int64_t l = c * 16 + e;
-        const uint64_t x = __builtin_nontemporal_load(reinterpret_cast<const uint64_t*>(src + (l < k ? l : k - 1) * o.stride_l * 8 + lane));
-        bits[e] = (row_ok && l < k) ? x : 0ull;
-    }
-    emit<MAXS, 16>(bits, er, S, out + (c * o.rows_p + rb * 256) * 16, threadIdx.x * 16u, kp * o.rows_p);
-}
-
-// k contiguous in memory: four lanes share 16 consecutive k of a row (128 bytes, 16 per load and lane), a wave takes 16 rows and, chunk
-// by chunk, 64 k; a lane's four k are a dword of every plane, and the 64 lanes' dwords lie behind each other.  (A 64 x 64 tile
-// transposed through LDS instead, so that a thread has 16 k: four workgroups to a CU that load and cut in turn, 8192 x 8192 with
-// seven slices 255 us.)
-template <int MAXS>
-__device__ __forceinline__ void slice_k(const Operand& o, int64_t rb, int64_t lb, int64_t k, int64_t kp, int er, int8_t* __restrict__ out,
-                                        int S) {
-    typedef uint64_t pair __attribute__((ext_vector_type(2), aligned(8)));
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t r0 = rb * 64 + wave * 16, l0 = lb * 64;
-    const int64_t rows_here = o.rows - r0;
-    const bool row_ok = (lane >> 2) < rows_here;
-    // rows past the end read the last one, and count as zero
-    const uint64_t* const src = reinterpret_cast<const uint64_t*>(o.X) + min(r0 + (lane >> 2), o.rows - 1) * o.stride_r + l0 + (lane & 3) * 4;
-    const bool whole = l0 + 64 <= k;
-    auto load = [&](int c, uint64_t (&x)[4]) {
-        if (whole) {
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const pair p = __builtin_nontemporal_load(reinterpret_cast<const pair*>(src + c * 16 + h * 2));
-                x[2 * h] = row_ok ? p[0] : 0ull;
-                x[2 * h + 1] = row_ok ? p[1] : 0ull;
-            }
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int64_t l = l0 + c * 16 + (lane & 3) * 4 + e;
-                const uint64_t y = src[(l < k ? l : k - 1) - (l0 + (lane & 3) * 4)];
-                x[e] = row_ok && l < k ? y : 0ull;
-            }
-        }
-    };
-    auto put = [&](int c, const uint64_t (&x)[4]) {
-        emit<MAXS, 4>(x, er, S, out + ((l0 / 16 + c) * o.rows_p + r0) * 16, uint32_t(lane) * 4u, kp * o.rows_p);
-    };
-    if constexpr (MAXS <= 8) {
-        uint64_t bits[4][4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) load(c, bits[c]);
-#pragma unroll
-        for (int c = 0; c < 4; ++c) put(c, bits[c]);
-    } else {                             // the wider words leave registers for one chunk in work and one on its way
-        uint64_t now[4], next[4] = {};
-        load(0, now);
-#pragma unroll 1
-        for (int c = 0; c < 4; ++c) {
-            if (c < 3) load(c + 1, next);
-            put(c, now);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) now[e] = next[e];
-        }
-    }
-}
 
 struct SliceSide {
     Operand o;
@@ -315,10 +22,8 @@ struct SliceSide {
 // workgroups [0, a.blocks) cut a, the others b
 // MAXS: the most slices the call can come out with
 template <int MAXS>
-__global__ __launch_bounds__(256, MAXS <= 8 ? 6 : 4) void slice_kernel(SliceSide a, SliceSide b, int64_t k, int64_t kp, const Record* rec, Batch bt) {
-    // FP64 rounds toward -infinity in this kernel (Fp64Cut).  As assembly, and before the loads that all FP64 arithmetic waits for: the
-    // compiler sets the mode back before such arithmetic where it knows of a change.
-    asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 2, 2), 2\n\ts_nop 1" ::: "memory");
+__global__ __launch_bounds__(256, MAXS <= 8 ? 6 : MAXS <= 16 ? 4 : 3) void slice_kernel(SliceSide a, SliceSide b, int64_t k, int64_t kp, const Record* rec, Batch bt) {
+    round_down_fp64();
     const bool second = int64_t(blockIdx.x) >= a.blocks;
     const int64_t ws = bt.ws_at(blockIdx.z);
     SliceSide s = second ? b : a;
@@ -334,8 +39,31 @@ __global__ __launch_bounds__(256, MAXS <= 8 ? 6 : 4) void slice_kernel(SliceSide
     const int er = s.e_row[rows ? rb * 256 + threadIdx.x : rb * 64 + (threadIdx.x >> 2)];
     const int fallback = rec->res.fallback, S = rec->res.slices_used;
     if (fallback) return;
-    if (rows) slice_rows<MAXS>(s.o, rb, cb, k, kp, er, s.out, S);
-    else slice_k<MAXS>(s.o, rb, cb, k, kp, er, s.out, S);
+    if (rows) {                          // 256 rows x 16 k
+        uint64_t bits[16];
+        load_rows(s.o, rb, threadIdx.x, cb, k, bits);
+        put_rows<MAXS>(bits, s.o, rb, threadIdx.x, cb, kp, er, s.out, S);
+        return;
+    }
+    // 64 rows x 64 k
+    const int64_t r0 = rb * 64 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 16, c0 = cb * 4;
+    if constexpr (MAXS <= 8) {
+        uint64_t bits[4][4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) load_k(s.o, r0, c0 + c, k, bits[c]);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) put_k<MAXS>(bits[c], s.o, r0, c0 + c, kp, er, s.out, S);
+    } else {                             // the wider words leave registers for one chunk in work and one on its way
+        uint64_t now[4], next[4] = {};
+        load_k(s.o, r0, c0, k, now);
+#pragma unroll 1
+        for (int c = 0; c < 4; ++c) {
+            if (c < 3) load_k(s.o, r0, c0 + c + 1, k, next);
+            put_k<MAXS>(now, s.o, r0, c0 + c, kp, er, s.out, S);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) now[e] = next[e];
+        }
+    }
 }
 
 void launch_slice(hipStream_t st, const Operand& a, const Operand& b, const Workspace& w, const Problem& p) {
