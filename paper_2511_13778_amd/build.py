@@ -12,7 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liboz_mi355x.so")
 PROBE_LIB = os.path.join(HERE, "liboz_probe.so")      # measurement probes: separate from the product library
 PROBE_SOURCES = ["oz_probe.hip"]
-SOURCES = ["oz_api.hip", "oz_scan.hip", "oz_esc.hip", "oz_slice.hip", "oz_gemm_i8.hip", "oz_gemm_few.hip", "oz_gemm_small.hip", "oz_gemm_mid.hip",
+SOURCES = ["oz_api.hip", "oz_scan.hip", "oz_esc.hip", "oz_slice.hip", "oz_esc_slice.hip", "oz_gemm_i8.hip", "oz_gemm_few.hip", "oz_gemm_small.hip", "oz_gemm_mid.hip",
            "oz_recompose.hip", "oz_dgemm_f64.hip", "oz_dgemm_f64_direct.hip", "oz_complex.hip"]
 # packed FP32 instructions are switched off for all device code (known-bad on the test machines)
 # -ffp-contract=off: the FP64 epilogues round every product and sum separately, as the header specifies;
@@ -23,7 +23,7 @@ FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-Wall", "-Wno-u
          "-I" + os.path.join(ROOT, "include"), "-I" + CSRC]
 # per-source additions.  ESC: MFMA results are consumed by the vector ALU right away, so they
 # are kept in ordinary VGPRs (the default puts them in accumulation registers and copies them out).
-SOURCE_FLAGS = {name: ["-mllvm", "-amdgpu-mfma-vgpr-form"] for name in ("oz_esc.hip",)}
+SOURCE_FLAGS = {name: ["-mllvm", "-amdgpu-mfma-vgpr-form"] for name in ("oz_esc.hip", "oz_esc_slice.hip")}
 
 
 def _compile(src: str, extra=()) -> str:

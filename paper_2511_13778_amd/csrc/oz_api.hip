@@ -432,10 +432,12 @@ oz_status_t dgemm_impl(oz_handle_t h, void* stream, char transa, char transb, in
         launch_exponents(st, oa, ob, w, p, guarded, known);
     }
     clk.done(0);
-    if (guarded) launch_esc_verdict(st, w, p, *opts, h->hm, result);
+    const bool together = guarded && decide_in_slice(p);
+    if (guarded && !together) launch_esc_verdict(st, w, p, *opts, h->hm, result);
     clk.done(1);
     clk.done(2);          // the verdict is given by the last workgroup of the ESC kernel
-    launch_slice(st, oa, ob, w, p);
+    if (together) launch_esc_slice(st, oa, ob, w, p, *opts, h->hm, result);
+    else launch_slice(st, oa, ob, w, p);
     clk.done(3);
     bool fell_back = false;
     const Fallback fallback{guarded ? A : nullptr, a_sr, a_sl, B, b_sr, b_sl, k, !ta, tb};
