@@ -10,10 +10,14 @@
 // alpha and beta follow in the same launch.
 //   SETS = 1   4 waves, up to 8 slices, 80 KB: two workgroups to a CU, one ends or loads while the other multiplies
 //   SETS = 2   8 waves (two sets share the groups), up to 16 slices, all of the LDS: more than one stage up to 10 slices
-// What bounds it at a short k is memory: digits, leading words and C are 26 bytes per element (7936 x 7936, seven slices: 280 us
-// plus 95 per 64 of k; units 500 plus 73).  At a long one the load of a stage, which only the other workgroup covers.
-// Measured, whole calls, against units: 7936x7936x256 814 -> 717 us, 1000^3 (seven slices, no guards) 86 -> 53; 16 problems of 512^3, which
-// also share their launches, 540 -> 229.
+// Digits, leading words and C are 26 bytes per element, read and written once and streamed past L2, where the slices of the next tiles
+// live (plain stores, which drive those out, cost 85 us of 690 at 7936 x 7936 x 256).  What bounds it at a short k is the end of a tile:
+// memory, and the integer work of the carry chain, which the other workgroup's products only partly cover (7936 x 7936, seven
+// slices: 270 us plus 83 per 64 of k); at a long one LDS, from which a quadrant reads 42 KB per 64 of k and seven slices beside the 56 KB
+// that arrive (1750 cycles of 128 B for 1792 of MFMA).  Stages of 32 of k, twice as deep, gain 5 percent where they save half a stage (k = 200)
+// and lose 5 at 512; the first reads of a group during the group before gain nothing; nor do wave priorities.
+// Measured, whole calls, against units: 7936x7936x256 814 -> 600 us, 1000^3 (seven slices, no guards) 86 -> 51; 16 problems of 512^3, which
+// also share their launches, 540 -> 168.  The sums of one set through LDS and plain stores, before: 690, 53, 174.
 #include "oz_f64_direct.h"
 #include "oz_gemm_device.h"
 
@@ -24,7 +28,7 @@ constexpr int kMidRow = kMidTile + 4;                       // words between row
 constexpr int kMidPlane = kMidTile / 2 * kMidRow * 4;       // bytes per anti-diagonal of half a tile's sums
 static_assert(kMidTile == 64 && kBK == 64, "a transfer moves one k chunk of 64 rows, a wave owns a quadrant of 32 x 32");
 static_assert(kMidMaxSlices * 2 * kMidSlice <= kSmallLdsMax && kMidMaxSlices * kMidPlane <= kSmallLdsMax, "one stage must fit");
-static_assert(kMidPairSlices * 2 * kMidSlice <= kSmallLdsMax / 2 && kMidPairSlices * kMidPlane <= kSmallLdsMax / 2, "one of two workgroups");
+static_assert(kMidPairSlices * 2 * kMidSlice <= kSmallLdsMax / 2, "one of two workgroups");
 
 template <int N>
 struct MidInt { static constexpr int v = N; };
@@ -64,10 +68,11 @@ __global__ __launch_bounds__(256 * SETS, 2) void gemm_mid_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int set = wave >> 2, qi = wave & 1, qj = (wave >> 1) & 1;
 
-    // ---- elements this thread finishes: column i, in either half of the tile's rows 8 / WAVES times four j
+    // ---- elements this thread finishes.  One set: column i of its quadrant, rows of four j.
+    // Two sets: column i, in either half of the tile's rows 8 / WAVES times four j.
     constexpr int QUADS = 8 / WAVES;
-    const int64_t i = i0 + lane;
-    const int ea = eA[i];
+    const int64_t i = SETS == 1 ? i0 + qi * 32 + (lane & 31) : i0 + lane;
+    auto row_of = [&](int h, int u) -> int64_t { return SETS == 1 ? j0 + qj * 32 + h * 16 + (lane >> 5) * 8 + u * 4 : j0 + h * 32 + (u * WAVES + wave) * 4; };
     double cin[2][QUADS][4];
     if (beta != 0.0) {
 #pragma unroll
@@ -76,7 +81,7 @@ __global__ __launch_bounds__(256 * SETS, 2) void gemm_mid_kernel(
             for (int u = 0; u < QUADS; ++u)
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    cin[h][u][q] = C[min(j0 + h * 32 + (u * WAVES + wave) * 4 + q, n - 1) * ldc + min(i, m - 1)];
+                    cin[h][u][q] = C[min(row_of(h, u) + q, n - 1) * ldc + min(i, m - 1)];
     }
 
     // ---- transfers: a wave fetches k chunk (wave & 3) of every SETS-th slice, A's then B's
@@ -183,67 +188,135 @@ __global__ __launch_bounds__(256 * SETS, 2) void gemm_mid_kernel(
         stage = stage + 1 == stages ? 0 : stage + 1;
     }
 
-    // ---- half by half of the tile's columns j the sums meet in LDS
-    int32_t* const sums = reinterpret_cast<int32_t*>(lds);
+    // ---- carry chain and recomposition of columns i and, four at a time, rows j .. j + 3 of C.
+    const int ea = eA[i];
+    const int64_t planeL = np * mp / 4;      // in words
+    auto finish = [&](int t, double Rb, int eb, double c, int64_t j) {
+        __builtin_nontemporal_store(t, T + j * mp + i);
+        const double R = 0.0 + (double(t) + Rb * 0x1p-8);
+        const int sc = (ea > kExpAllZero ? ea : 0) + (eb > kExpAllZero ? eb : 0) + (2 * kHeadroomBits - 12);
+        double out = __dmul_rn(alpha, ldexp(R, sc));
+        if (beta != 0.0) out = __dadd_rn(out, __dmul_rn(beta, c));
+        if (i < m && j < n) __builtin_nontemporal_store(out, C + j * ldc + i);
+    };
+    if constexpr (SETS == 1) {
+        // A wave holds every anti-diagonal of its quadrant, so the sums stay in registers.  Rows of 16 lanes trade places so that 32 lanes
+        // hold 32 neighbouring columns: a line of 128 bytes leaves in one store (64 bytes at a time cost 7 percent of the call).
+        // VALU work bounds this part, so the chain runs on digits + 128: v = sum + 128 + (v before >> 8), the digit is its low byte less
+        // 128.  The six least digits are 48 bits, exact in a double in any grouping, and are converted four and two at a time
+        // (7936 x 7936 x 256: 724 us with a digit at a time, 675 so).  The exponents are fetched first: behind stores a load is only there
+        // when those have been accepted.
+        int4 eb4[2][QUADS];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        __syncthreads();
-        if (qj == h) {
+        for (int b = 0; b < 2; ++b)
 #pragma unroll
-            for (int gg = 0; gg < GROUPS; ++gg)
+            for (int u = 0; u < QUADS; ++u) eb4[b][u] = *reinterpret_cast<const int4*>(eB + row_of(b, u));
 #pragma unroll
-                for (int j = 0; j < D; ++j) {
-                    const int d = S - 1 - D * (set + SETS * gg) - j;
-                    if (d < 0) continue;
+        for (int b = 0; b < 2; ++b) {
+            int v[2][4] = {}, top[2][4] = {};
+            uint32_t w[2][kMidPairSlices - 1];
 #pragma unroll
-                    for (int b = 0; b < 2; ++b)
+            for (int t = 0; t < kMidPairSlices; ++t) {
+                if (t > S - 1) {
 #pragma unroll
-                        for (int a = 0; a < 2; ++a)
-#pragma unroll
-                            for (int r = 0; r < 4; ++r)
-                                sums[d * (kMidPlane / 4) + (b * 16 + 4 * (lane >> 4) + r) * kMidRow + qi * 32 + a * 16 + (lane & 15)] =
-                                    acc[gg][j][b][a][r];
+                    for (int u = 0; u < 2; ++u)
+                        if (t < kMidPairSlices - 1) w[u][t] = 0x80808080u;
+                    continue;
                 }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < QUADS; ++u) {
-            const int jq = (u * WAVES + wave) * 4;
-            const int64_t j = j0 + h * 32 + jq;
-            const int32_t* mine = sums + jq * kMidRow + lane;
-            uint32_t* const lw = reinterpret_cast<uint32_t*>(L + ((j >> 2) * mp + i) * 4);
-            const int64_t planeL = np * mp / 4;      // in words
-            int carry[4] = {0, 0, 0, 0};
-            double Rb[4] = {0.0, 0.0, 0.0, 0.0};
-            int p[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) p[q] = mine[(S - 1) * (kMidPlane / 4) + q * kMidRow];
-            for (int d = S - 1; d >= 1; --d) {
-                int next[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) next[q] = mine[(d - 1) * (kMidPlane / 4) + q * kMidRow];
-                uint32_t w = 0;
+                int p[2][4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const int v = p[q] + carry[q];
-                    carry[q] = (v + 128) >> 8;
-                    w |= (uint32_t(v) & 255u) << (8 * q);
-                    Rb[q] = double((v << 24) >> 24) + Rb[q] * 0x1p-8;
-                    p[q] = next[q];
+                    const auto two = __builtin_amdgcn_permlane16_swap(uint32_t(acc[t / D][t % D][b][0][q]), uint32_t(acc[t / D][t % D][b][1][q]), false, false);
+                    p[0][q] = int(two[0]);
+                    p[1][q] = int(two[1]);
                 }
-                lw[(d - 1) * planeL] = w;
-            }
-            const int4 eb4 = *reinterpret_cast<const int4*>(eB + j);
-            const int eb[4] = {eb4.x, eb4.y, eb4.z, eb4.w};
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int t = p[q] + carry[q];
-                T[(j + q) * mp + i] = t;
-                const double R = 0.0 + (double(t) + Rb[q] * 0x1p-8);
-                const int sc = (ea > kExpAllZero ? ea : 0) + (eb[q] > kExpAllZero ? eb[q] : 0) + (2 * kHeadroomBits - 12);
-                double out = __dmul_rn(alpha, ldexp(R, sc));
-                if (beta != 0.0) out = __dadd_rn(out, __dmul_rn(beta, cin[h][u][q]));
-                if (i < m && j + q < n) C[(j + q) * ldc + i] = out;
+                for (int u = 0; u < 2; ++u) {
+                    if (t == S - 1) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) top[u][q] = p[u][q] + (v[u][q] >> 8);
+                        if (t < kMidPairSlices - 1) w[u][t] = 0x80808080u;
+                    } else if (t < kMidPairSlices - 1) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) v[u][q] = p[u][q] + 128 + (v[u][q] >> 8);
+                        w[u][t] = __builtin_amdgcn_perm(v[u][1], v[u][0], 0x0c0c0400u) | __builtin_amdgcn_perm(v[u][3], v[u][2], 0x04000c0cu);
+                        __builtin_nontemporal_store(w[u][t] ^ 0x80808080u, reinterpret_cast<uint32_t*>(L + ((row_of(b, u) >> 2) * mp + i) * 4) + (S - 2 - t) * planeL);
+                    }
+                }
+            }
+            const double unit = ldexp(1.0, -8 * (min(S - 1, 6) - 1));
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const uint32_t lo01 = __builtin_amdgcn_perm(w[u][1], w[u][0], 0x05010400u), hi01 = __builtin_amdgcn_perm(w[u][1], w[u][0], 0x07030602u);
+                const uint32_t lo23 = __builtin_amdgcn_perm(w[u][3], w[u][2], 0x05010400u), hi23 = __builtin_amdgcn_perm(w[u][3], w[u][2], 0x07030602u);
+                const uint32_t x0[4] = {__builtin_amdgcn_perm(lo23, lo01, 0x05040100u), __builtin_amdgcn_perm(lo23, lo01, 0x07060302u),
+                                        __builtin_amdgcn_perm(hi23, hi01, 0x05040100u), __builtin_amdgcn_perm(hi23, hi01, 0x07060302u)};
+                const int eb[4] = {eb4[b][u].x, eb4[b][u].y, eb4[b][u].z, eb4[b][u].w};
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    double Rb = (double(x0[q]) - 0x80808080p0) * unit;
+                    if (S > 5) {
+                        const uint32_t x1 = __builtin_amdgcn_perm(w[u][5], w[u][4], 0x0c0c0400u + 0x0101u * q);
+                        Rb = Rb + (double(x1) - 0x8080p0) * (unit * 0x1p32);
+                        if (S > 7) Rb = double(int(w[u][6] >> (8 * q) & 255u) - 128) + Rb * 0x1p-8;
+                    }
+                    finish(top[u][q], Rb, eb[q], cin[b][u][q], row_of(b, u) + q);
+                }
+            }
+        }
+    } else {
+        // half by half of the tile's columns j the sums of both sets meet in LDS
+        int32_t* const sums = reinterpret_cast<int32_t*>(lds);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            __syncthreads();
+            if (qj == h) {
+#pragma unroll
+                for (int gg = 0; gg < GROUPS; ++gg)
+#pragma unroll
+                    for (int j = 0; j < D; ++j) {
+                        const int d = S - 1 - D * (set + SETS * gg) - j;
+                        if (d < 0) continue;
+#pragma unroll
+                        for (int b = 0; b < 2; ++b)
+#pragma unroll
+                            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                                for (int r = 0; r < 4; ++r)
+                                    sums[d * (kMidPlane / 4) + (b * 16 + 4 * (lane >> 4) + r) * kMidRow + qi * 32 + a * 16 + (lane & 15)] =
+                                        acc[gg][j][b][a][r];
+                    }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < QUADS; ++u) {
+                const int64_t j = row_of(h, u);
+                const int32_t* mine = sums + (u * WAVES + wave) * 4 * kMidRow + lane;
+                uint32_t* const lw = reinterpret_cast<uint32_t*>(L + ((j >> 2) * mp + i) * 4);
+                int carry[4] = {0, 0, 0, 0};
+                double Rb[4] = {0.0, 0.0, 0.0, 0.0};
+                int p[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) p[q] = mine[(S - 1) * (kMidPlane / 4) + q * kMidRow];
+                for (int d = S - 1; d >= 1; --d) {
+                    int next[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) next[q] = mine[(d - 1) * (kMidPlane / 4) + q * kMidRow];
+                    uint32_t w = 0;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int v = p[q] + carry[q];
+                        carry[q] = (v + 128) >> 8;
+                        w |= (uint32_t(v) & 255u) << (8 * q);
+                        Rb[q] = double((v << 24) >> 24) + Rb[q] * 0x1p-8;
+                        p[q] = next[q];
+                    }
+                    __builtin_nontemporal_store(w, lw + (d - 1) * planeL);
+                }
+                const int4 e4 = *reinterpret_cast<const int4*>(eB + j);
+                const int eb[4] = {e4.x, e4.y, e4.z, e4.w};
+#pragma unroll
+                for (int q = 0; q < 4; ++q) finish(p[q] + carry[q], Rb[q], eb[q], cin[h][u][q], j + q);
             }
         }
     }

@@ -36,3 +36,18 @@ def test_tiles_of_64_with_slice_counts_per_block(lib, m, n, k):
     tr = oz.emulated_dgemm(A, B, 1.0, 0.0, None, mode=oz.MODE_DYNAMIC, target_bits=53, max_bits=110, per_tile=True)
     assert (res.slices_used, res.slices_min, res.pair_tiles) == (tr.verdict.slices_used, tr.verdict.slices_min, tr.verdict.pair_tiles)
     np.testing.assert_array_equal(got, tr.C)
+
+
+@pytest.mark.parametrize("S", [1, 2, 4, 5, 6, 7, 8])
+def test_carries_at_their_extremes(lib, S):
+    """Entries of all-ones digits with one sign (the largest sums and carries, either way), rows of C that are zero because a row of A
+    is or because the halves of k cancel, and values of one low digit."""
+    g, h = lib
+    m, n, k = 1030, 1300, 96
+    A, B = np.full((m, k), 2.0 - 2.0 ** -52), np.full((k, n), -(2.0 - 2.0 ** -52))
+    B[:, ::3] *= -1.0
+    A[5::7] = 0.0
+    A[6::7, k // 2:] *= -1.0
+    A[1::7, 1:] = 2.0 ** -(8 * S - 4)
+    B[1:, 1::5] = -2.0 ** -(8 * S - 4)
+    check_against_oracle(g, h, A, B, mode="unguarded", slices=S, bound=False)
