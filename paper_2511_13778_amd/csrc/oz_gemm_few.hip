@@ -28,13 +28,16 @@ static_assert((kFewStages & (kFewStages - 1)) == 0, "stages are counted modulo a
 // One dword per lane to a wave-uniform base plus a 32-bit per-lane byte offset; as assembly, with the five wait states
 // between a vector-ALU write of a scalar register and its use as a base, so that no 64-bit per-lane address is built per
 // store.
+template <bool STREAM>
 __device__ __forceinline__ void store_lane_dword(void* uniform_base, uint32_t lane_byte_off, uint32_t data) {
-    asm volatile("s_nop 4\n\tglobal_store_dword %0, %1, %2" :: "v"(lane_byte_off), "v"(data), "s"(uniform_base) : "memory");
+    if (STREAM) asm volatile("s_nop 4\n\tglobal_store_dword %0, %1, %2 nt" :: "v"(lane_byte_off), "v"(data), "s"(uniform_base) : "memory");
+    else asm volatile("s_nop 4\n\tglobal_store_dword %0, %1, %2" :: "v"(lane_byte_off), "v"(data), "s"(uniform_base) : "memory");
 }
 
 __device__ __forceinline__ v4i as_v4i(const uint4& v) { return v4i{int(v.x), int(v.y), int(v.z), int(v.w)}; }
 
 // grid: one workgroup per block of C
+template <bool STREAM>
 __global__ __launch_bounds__(256) void gemm_i8_few_kernel(const int8_t* __restrict__ As, const int8_t* __restrict__ Bs,
                                                           int32_t* __restrict__ T, int8_t* __restrict__ L, int64_t mp, int64_t np,
                                                           int64_t kp, int s_cap, Record* rec, int kt_total, int full_chip) {
@@ -253,7 +256,7 @@ __global__ __launch_bounds__(256) void gemm_i8_few_kernel(const int8_t* __restri
                         for (int rq = 0; rq < 4; ++rq) {
                             const uint32_t w = (uint32_t(t[4 * rq]) & 255u) | ((uint32_t(t[4 * rq + 1]) & 255u) << 8) |
                                                ((uint32_t(t[4 * rq + 2]) & 255u) << 16) | (uint32_t(t[4 * rq + 3]) << 24);
-                            store_lane_dword(dst + (int64_t(fj * 8 + 2 * rq) * mp_here + fi * 32), lane_L, w);
+                            store_lane_dword<STREAM>(dst + (int64_t(fj * 8 + 2 * rq) * mp_here + fi * 32), lane_L, w);
                         }
 #pragma unroll
                         for (int r = 0; r < 16; ++r) carry[r] = (t[r] + 128) >> 8;
@@ -273,8 +276,8 @@ __global__ __launch_bounds__(256) void gemm_i8_few_kernel(const int8_t* __restri
                     for (int fi = 0; fi < 4; ++fi) {
 #pragma unroll
                         for (int r = 0; r < 16; ++r) {
-                            store_lane_dword(dst + (int64_t(fj * 32 + 8 * (r >> 2) + (r & 3)) * mp_here + fi * 32), lane_T,
-                                             uint32_t(acc[fj][fi][r]));
+                            store_lane_dword<STREAM>(dst + (int64_t(fj * 32 + 8 * (r >> 2) + (r & 3)) * mp_here + fi * 32), lane_T,
+                                                     uint32_t(acc[fj][fi][r]));
                         }
                         acc[fj][fi] = zero;
                     }
@@ -301,12 +304,15 @@ __global__ __launch_bounds__(256) void gemm_i8_few_kernel(const int8_t* __restri
 #undef OZ_READ_B
 
 bool prepare_gemm_i8_few() {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_i8_few_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_i8_few_kernel<false>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               kFewLds) == hipSuccess &&
+           hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_i8_few_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                kFewLds) == hipSuccess;
 }
 
 void launch_gemm_i8_few(hipStream_t st, const Workspace& w, const Problem& p, const LaunchPlan& lp) {
-    hipLaunchKernelGGL(gemm_i8_few_kernel, dim3(unsigned(lp.g.nti) * unsigned(lp.g.ntj)), dim3(256), kFewLds, st, w.As, w.Bs, w.T, w.L,
+    const auto kernel = results_stream(p) ? gemm_i8_few_kernel<true> : gemm_i8_few_kernel<false>;
+    hipLaunchKernelGGL(kernel, dim3(unsigned(lp.g.nti) * unsigned(lp.g.ntj)), dim3(256), kFewLds, st, w.As, w.Bs, w.T, w.L,
                        p.mp, p.np, p.kp, p.s_cap, w.rec, lp.kt, lp.g.full_chip);
 }
 

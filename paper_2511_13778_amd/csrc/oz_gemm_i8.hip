@@ -82,8 +82,9 @@ constexpr int kSyncMinItems = 320;    // nor one of fewer steps than seven slice
 // it as its base: inside an asm block the compiler does not insert them itself, and a store issued
 // too early takes the stale register value as its address.  The one behind it keeps the next instruction from
 // overwriting the data before the store has read all four registers.
+// Streamed past L2, where the slices are (four 900 x 1000 x 1500 234 -> 230 us, 6144 x 6144 x 1024 1040 -> 1031; level where k is long).
 __device__ __forceinline__ void store_lane_16(void* uniform_base, uint32_t lane_byte_off, v4i data) {
-    asm volatile("s_nop 4\n\tglobal_store_dwordx4 %0, %1, %2\n\ts_nop 1"
+    asm volatile("s_nop 4\n\tglobal_store_dwordx4 %0, %1, %2 nt\n\ts_nop 1"
                  :: "v"(lane_byte_off), "v"(data), "s"(uniform_base) : "memory");
 }
 

@@ -190,6 +190,11 @@ __host__ __device__ inline void parts_of_block(int kt_total, int kt_per_block, i
     while (z_hi + 1 < zsplit && part_first(kt_total, zsplit, z_hi + 1) < (kb + 1) * kt_per_block) ++z_hi;
 }
 
+// Whether what recomposition reads and writes (leading words, digits, C) is more than the 256 MB Infinity Cache: then C and, with few slices,
+// the leading words are streamed past it (8192 x 8192 x 2048 with two slices 719 -> 653 us, 6144 x 6144 x 1024 with seven 1040 -> 1015); what fits
+// there the next kernel or the next call's beta C finds (3000^3 with one slice 127 us, streamed 131).
+inline bool results_stream(const Problem& p) { return double(p.m) * double(p.n) * p.batch.count * (11 + p.s_cap) > 256e6; }
+
 inline int64_t round_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
 
 // k-range one int32 accumulator can take: |digit product| <= 2^14, an anti-diagonal sums at most

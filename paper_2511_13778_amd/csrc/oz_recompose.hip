@@ -23,6 +23,7 @@ namespace oz {
 
 constexpr int kRecI = 4;   // four consecutive i per thread: one 16-byte load of T per j, of L per digit
 constexpr int kRecJ = 4;   // four consecutive j per thread: the four bytes of an L dword
+constexpr int kVecC = 1, kStreamC = 2;       // c_flags
 
 // KIND: where the sums of a k-block come from.  kNone: the planes T / L, complete.  kParts: the planes hold part 0 of a
 // k split and the raw buffer the others, each with digits of its own; they are added digit by digit with the slice
@@ -41,7 +42,7 @@ __global__ __launch_bounds__(256) void recompose_kernel(std::conditional_t<KIND 
                                                         double* __restrict__ C, int64_t ldc,
                                                         const Record* rec,
                                                         const int32_t* __restrict__ tile_S, int64_t j4_first,
-                                                        int c_vec, Batch bt) {
+                                                        int c_flags, Batch bt) {
     {
         const int64_t ws = bt.ws_at(blockIdx.z);
         T = at_bytes(T, ws); L = at_bytes(L, ws);
@@ -84,8 +85,8 @@ __global__ __launch_bounds__(256) void recompose_kernel(std::conditional_t<KIND 
     // loads of a batch are in flight together before the first digit is consumed
     double cin[kRecJ][kRecI];
     const bool rows_full = i0 + kRecI <= m;
-    // c_vec: C and ldc allow 16-byte accesses (the host checked alignment); used for full groups of four rows
-    const bool vec = c_vec && rows_full;
+    // kVecC: C and ldc allow 16-byte accesses (the host checked alignment); used for full groups of four rows
+    const bool vec = (c_flags & kVecC) && rows_full;
     if (beta != 0.0) {
 #pragma unroll
         for (int jj = 0; jj < kRecJ; ++jj) {
@@ -267,9 +268,16 @@ __global__ __launch_bounds__(256) void recompose_kernel(std::conditional_t<KIND 
             if (beta != 0.0) out[q] = __dadd_rn(out[q], __dmul_rn(beta, cin[jj][q]));
         }
         if (vec) {
-            double2* dst = reinterpret_cast<double2*>(C + j * ldc + i0);
-            dst[0] = make_double2(out[0], out[1]);
-            dst[1] = make_double2(out[2], out[3]);
+            typedef double f64x2 __attribute__((ext_vector_type(2)));
+            f64x2* dst = reinterpret_cast<f64x2*>(C + j * ldc + i0);
+            const f64x2 lo = {out[0], out[1]}, hi = {out[2], out[3]};
+            if (c_flags & kStreamC) {
+                __builtin_nontemporal_store(lo, dst);
+                __builtin_nontemporal_store(hi, dst + 1);
+            } else {
+                dst[0] = lo;
+                dst[1] = hi;
+            }
         } else {
 #pragma unroll
             for (int q = 0; q < kRecI; ++q)
@@ -291,20 +299,21 @@ void launch_recompose(hipStream_t st, const Workspace& w, const Problem& p, cons
                       double* C, int64_t ldc) {
     const unsigned gx = unsigned((p.m + 256 * kRecI - 1) / (256 * kRecI));
     const int64_t n4 = (p.n + kRecJ - 1) / kRecJ;
-    const int c_vec = (reinterpret_cast<uintptr_t>(C) % 16 == 0 && ldc % 2 == 0 && p.batch.c % 2 == 0) ? 1 : 0;
+    const int c_flags = (reinterpret_cast<uintptr_t>(C) % 16 == 0 && ldc % 2 == 0 && p.batch.c % 2 == 0 ? kVecC : 0) |
+                        (results_stream(p) ? kStreamC : 0);
     for (int64_t j4 = 0; j4 < n4; j4 += 65535) {
         const unsigned gy = unsigned(n4 - j4 < 65535 ? n4 - j4 : 65535);
         const int32_t* tile_S = p.tile_mode ? w.tile_S : nullptr;
         const dim3 grid(gx, gy, unsigned(p.batch.count)), block(256);
         if (split.kind == KSplit::kParts)
             hipLaunchKernelGGL(recompose_kernel<KSplit::kParts>, grid, block, 0, st, w.T, w.L, w.raw, split, w.eA, w.eB, p.m,
-                               p.n, p.mp, p.np, p.kp, p.s_cap, alpha, beta, C, ldc, w.rec, tile_S, j4, c_vec, p.batch);
+                               p.n, p.mp, p.np, p.kp, p.s_cap, alpha, beta, C, ldc, w.rec, tile_S, j4, c_flags, p.batch);
         else if (split.kind == KSplit::kAtomic)
             hipLaunchKernelGGL(recompose_kernel<KSplit::kAtomic>, grid, block, 0, st, w.T, w.L, w.raw, split, w.eA, w.eB, p.m,
-                               p.n, p.mp, p.np, p.kp, p.s_cap, alpha, beta, C, ldc, w.rec, tile_S, j4, c_vec, p.batch);
+                               p.n, p.mp, p.np, p.kp, p.s_cap, alpha, beta, C, ldc, w.rec, tile_S, j4, c_flags, p.batch);
         else
             hipLaunchKernelGGL(recompose_kernel<KSplit::kNone>, grid, block, 0, st, w.T, w.L, w.raw, split, w.eA, w.eB, p.m,
-                               p.n, p.mp, p.np, p.kp, p.s_cap, alpha, beta, C, ldc, w.rec, tile_S, j4, c_vec, p.batch);
+                               p.n, p.mp, p.np, p.kp, p.s_cap, alpha, beta, C, ldc, w.rec, tile_S, j4, c_flags, p.batch);
     }
 }
 

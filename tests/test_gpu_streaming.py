@@ -1,6 +1,6 @@
 """Scan and slicing where their kernels branch: entries at either end of what the FP64 unit cuts (far below their row's largest, of both
 signs, exact and inexact), rows beyond its range, whole and ragged 64s of k in either storage order, and operands larger than
-the Infinity Cache.  Exponents and slices are the oracle's bit for bit."""
+the Infinity Cache, read or written.  Exponents, slices and C are the oracle's bit for bit."""
 import numpy as np
 import pytest
 
@@ -56,3 +56,16 @@ def test_scan_of_an_operand_larger_than_the_cache(lib, ta):
     got, _ = gm.row_exponents()
     np.testing.assert_array_equal(got, np.where(eA > oz.NEG_INF_BELOW, eA, -12288))
     assert res.esc == min(oz.esc_coarse(A, B, 64), 4096)
+
+
+@pytest.mark.parametrize("m,n,k,S,pad,beta", [(4801, 4810, 1500, 1, 0, 0.5), (4810, 4801, 1500, 2, 1, 0.0), (4801, 3902, 700, 7, 3, -1.5),
+                                              (4802, 3902, 700, 7, 0, 0.0)])
+def test_results_larger_than_the_cache(lib, m, n, k, S, pad, beta):
+    """Rows of C at either edge and scattered over it, bit for bit."""
+    g, h = lib
+    rng = np.random.default_rng(S)
+    A, B, Cin = rng.uniform(-1.0, 1.0, (m, k)), rng.uniform(-1.0, 1.0, (k, n)), rng.uniform(-1.0, 1.0, (m, n))
+    got, _, _ = run_gpu(g, h, A, B, 0.75, beta, Cin if beta else None, "N", "N", pad, mode=g.OZ_FIXED_UNGUARDED, slices=S)
+    at = np.r_[0:70, m // 2:m // 2 + 70, m - 70:m]
+    tr = oz.emulated_dgemm(A[at], B, 0.75, beta, Cin[at] if beta else None, mode=oz.MODE_FIXED_UNGUARDED, slices=S)
+    np.testing.assert_array_equal(got[at], tr.C)
