@@ -38,7 +38,7 @@ def test_tiles_of_64_with_slice_counts_per_block(lib, m, n, k):
     np.testing.assert_array_equal(got, tr.C)
 
 
-@pytest.mark.parametrize("S", [1, 2, 4, 5, 6, 7, 8])
+@pytest.mark.parametrize("S", [1, 2, 4, 5, 6, 7, 8, 9, 10, 13, 16])
 def test_carries_at_their_extremes(lib, S):
     """Entries of all-ones digits with one sign (the largest sums and carries, either way), rows of C that are zero because a row of A
     is or because the halves of k cancel, and values of one low digit."""
