@@ -90,6 +90,7 @@ constexpr int kSmallLdsMax = 160 * 1024;         // all of a CU's LDS
 constexpr int kMidTile = 64;
 constexpr int kMidMaxSlices = 16;
 constexpr int kMidPairSlices = 8;
+constexpr int kMidDoubleSlices = 10;             // most slices of which all of the LDS holds two stages
 
 constexpr int64_t kCallStagesNs = 16000;         // stages that problems in launches of their own run once each, over the shared ones
 
@@ -158,18 +159,20 @@ struct LaunchPlan {
     //               of k adds, with slots, 0.7 and per part 1.57 and 7 ns per unit and byte of a sum, with atomics per part 0.16 and 28 ns
     //               per unit and slice.  256 x 256 blocks (few): per round 9.9 and per 64 of k 0.70 with one slice, 2.07 with two; 2.8 el,
     //               1 el S
-    //   64 x 64     a workgroup per CU: 1.4, per round 0.40 per slice, and per 64 of k 0.255 and 44 ns per pair of slices; 3.6 el,
-    //               0.1 el S.  Two to a CU (a stage of one 64 of k each; the slice count must be known): 2.2, per round of twice as many
-    //               2.75 and per 64 of k 0.313 and 71 ns per pair, one alone 0.32 per slice, 0.261 and 72; 0.9 el, 0.435 el S
+    //   64 x 64     a workgroup per CU: 1.2, per round 0.375 per slice, and per 64 of k 0.18, 45 ns per pair of slices and, where the LDS holds
+    //               one stage only, 45 ns per slice; 0.195 el S, of few slices 2.7 el less 0.345 el S.  Two to a CU (a stage of one 64 of k each; the slice count must be
+    //               known): 1.23, per round of twice as many 1.72 and per 64 of k 0.25 and 68 ns per pair, one alone 0.36 per slice, 0.32 and
+    //               62; 2.1 el
     //   32 x 32     alone on a CU (no more tiles than CUs, or more slices than half the LDS holds): per round 0.325 per slice, and per 64
     //               of k 0.51 and 14 ns per pair; two to a CU: per round of twice as many 1.15 and 0.28 per slice, and per 64 of k 0.494,
     //               16 ns per slice and 17 per pair; 2.6 el.  No less than the slices at 9 TB/s and 1.5 el
     // Rounds are whole up to four, beyond that workgroups end at different times.
-    // Fitted to 5100 calls of 1 to 26 slices (8 to 8000, k 8 to 6000, one to four problems; counts known and decided by the device), each
-    // timed on every route: the choice is 0.7 % off the best on average, and one call in 200 is more than 3 % slower than on units.
-    // 32 x 32 tiles have to be 7 % better from four rounds of two to a CU on, 64 x 64 ones 8 %, and 14 % on a full chip with more than
-    // three 64s of k, 20 % with sixteen, where at a lower clock they are worse than estimated (4224 x 3008 x 1792 with seven slices 588 us,
-    // on units 564).
+    // Units and 32 x 32 tiles are fitted to 5100 calls of 1 to 26 slices (8 to 8000, k 8 to 6000, one to four problems; counts known and
+    // decided by the device), 64 x 64 tiles to 6900 (5 to 16 slices, 150 to 5000, k 40 to 3000), each timed on every route: of 2400 others
+    // (1 to 12 slices) the choice is 0.2 % off the best on average (1.6 % with the constants of the kernels before), one in 150 by more than 10 %.
+    // 32 x 32 tiles have to be 7 % better from four rounds of two to a CU on; 64 x 64 ones, on a full chip with more than three 64s of k,
+    // 5 %, from sixteen on 8 %, and two to a CU 14 and 28 %: in long runs the clock is lower and they are worse than estimated
+    // (4096 x 4096 x 1024 with seven slices 445 us, on units 437; 4096 x 4096 x 2048 841 and 776; 4096 x 4096 x 512 is the faster on tiles).
     // Units share launches only while a round holds all problems' (units_batch); otherwise each problem pays its rounds and stages.  Of 735
     // complex products and 734 batches of 200 to 3500, about 200 take tiles for it, 11 % faster on average (1556 x 939 x 331 complex 317 us on
     // units, now 192; 2006 x 1146 x 1529 967, now 617), and fifteen more than 3 % slower (1666 x 2989 x 1234 1171, now 1478).
@@ -209,21 +212,24 @@ struct LaunchPlan {
         }
         if (p.s_cap > kMidMaxSlices || p.m * p.n / (kMidTile * kMidTile) > kMaxGridThreads / 1024) return;
         const int64_t mid_all = ((p.m + kMidTile - 1) / kMidTile) * ((p.n + kMidTile - 1) / kMidTile) * count;
-        best = best * (kt > 3 && mid_all >= 4 * cus ? (kt < 16 ? 86 : 80) : 92) / 100;
-        const int64_t mid_ns = 1409 + rounds_ns(mid_all, cus, 395 * S + kt * (255 + 44 * pairs)) + el(3625 + 101 * S);
-        if (mid_ns < best) {
-            best = mid_ns;
-            small = small_pair = false;
-            mid = true;
+        // Two workgroups to a CU wherever there are more tiles than CUs: of 1900 such calls 1.13 times as fast (0.91 to 1.3), of 2350 with
+        // fewer tiles 0.92 (0.67 to 1.02).
+        const bool known = p.s_min == p.s_cap && p.s_cap <= kMidPairSlices, full_chip = kt > 3 && mid_all >= 4 * cus;
+        int64_t mid_ns, percent = 100;
+        if (known && mid_all > cus) {
+            const int64_t pair_ns = 1720 + kt * (250 + 68 * pairs), alone_ns = 360 * S + kt * (320 + 62 * pairs);
+            const int64_t on_cu = (mid_all + cus - 1) / cus;          // workgroups of the fullest CU
+            mid_ns = 1230 + (mid_all < 8 * cus ? on_cu / 2 * pair_ns + on_cu % 2 * alone_ns : mid_all * pair_ns / (2 * cus)) + el(2100);
+            if (full_chip) percent = kt < 16 ? 86 : 72;
+            mid_pair = true;
+        } else {
+            mid_ns = 1200 + rounds_ns(mid_all, cus, 375 * S + kt * (180 + 45 * pairs + (S > kMidDoubleSlices ? 45 * S : 0))) +
+                     el(std::max<int64_t>(195 * S, 2700 - 345 * S));
+            if (full_chip) percent = kt < 16 ? 95 : 92;
         }
-        if (p.s_min != p.s_cap || p.s_cap > kMidPairSlices) return;
-        const int64_t pair_ns = 2751 + kt * (313 + 71 * pairs), alone_ns = 322 * S + kt * (261 + 72 * pairs);
-        const int64_t on_cu = (mid_all + cus - 1) / cus;          // workgroups of the fullest CU
-        const int64_t two_ns = 2167 + (mid_all < 8 * cus ? on_cu / 2 * pair_ns + on_cu % 2 * alone_ns : mid_all * pair_ns / (2 * cus)) + el(899 + 435 * S);
-        if (two_ns < best) {
-            small = small_pair = false;
-            mid = mid_pair = true;
-        }
+        mid = mid_ns < best * percent / 100;
+        mid_pair = mid_pair && mid;
+        if (mid) small = small_pair = false;
     }
 
     // At most two slices, whatever the device finds: 256 x 256 blocks, where their estimated time is the shorter one.  In us:
