@@ -20,13 +20,7 @@ typedef short short8_t __attribute__((ext_vector_type(8)));
 typedef uint16_t ushort2_t __attribute__((ext_vector_type(2)));
 
 constexpr int kDecideThreads = 512, kDecideWaves = kDecideThreads / 64;
-constexpr int kDecidePairs = 64;             // edge of a wave's block of pairs
 constexpr int kDecideTiles = 32;             // most blocks of C that can take their own slice count
-constexpr int kDecideLds = 64 * 1024;        // most bytes of the encoded tables
-// Most blocks, and most blocks times table rows and four for their end: what every workgroup computes, and computes again on packed int16 if
-// all spans are wide.  Level then with the ESC kernel (300^3 34.1 -> 35.3 us falling back, 200 x 300 x 260 33.7 -> 30.3); with 64 blocks of two
-// rows (512 x 512 x 64) 32.3 -> 36.8.
-constexpr int kDecideBlocks = 32, kDecideWork = 400;
 
 struct DecideSide {
     Operand o;
@@ -277,15 +271,8 @@ __global__ __launch_bounds__(kDecideThreads, 2) void esc_slice_kernel(DecideSide
                   kp * s.o.rows_p);
 }
 
-// While all of it is one round of workgroups: 200 x 300 x 260 (nine slices) 30.2 us in four launches, 26.2 in three, 256^3 26.9 and 23.3,
-// 96 x 80 x 112 23.7 and 18.4.  With more (four problems of 200 x 300 x 260) what every workgroup computes is computed several times on a
-// CU: 38.7 and 39.0, and 70 instead of 39 where all spans are beyond the encoding.
 bool decide_in_slice(const Problem& p) {
-    const int64_t ru = round_up(p.m, 64), rv = round_up(p.n, 64), blocks = (ru / kDecidePairs) * (rv / kDecidePairs);
-    const int64_t chunks = (2 * p.G + kEncChunk - 1) / kEncChunk * 2;
-    if (!scan_once(p) || blocks > kDecideBlocks || blocks * (2 * p.G + 4) > kDecideWork || (ru + rv) * (chunks * 16 + 4) > kDecideLds ||
-        (p.mp + p.np) / 64 * (p.kp / 32) * p.batch.count > p.num_cu)
-        return false;
+    if (!decide_fits(p)) return false;
     if (!p.tile_mode) return true;
     int first, deal;
     tile_order_shape(p, first, deal);
@@ -302,7 +289,7 @@ void launch_esc_slice(hipStream_t st, const Operand& a, const Operand& b, const 
     const DecideSide sa = side(a, w.EU, w.U, w.eA, w.As), sb = side(b, w.EV, w.V, w.eB, w.Bs);
     const auto kernel = p.s_cap <= 8 ? esc_slice_kernel<8> : p.s_cap <= 16 ? esc_slice_kernel<16> : esc_slice_kernel<kMaxSlices>;
     hipLaunchKernelGGL(kernel, dim3(unsigned(sa.blocks + sb.blocks), 1, unsigned(p.batch.count)), dim3(kDecideThreads),
-                       size_t(sa.rows64 + sb.rows64) * (size_t(2 * steps) * 16 + 4), st, sa, sb, int(p.m), int(p.n), p.k, p.kp, H2, steps, w.rec,
+                       size_t(decide_table_bytes(p)), st, sa, sb, int(p.m), int(p.n), p.k, p.kp, H2, steps, w.rec,
                        verdict_args(w, p, o, hm, user_result), p.batch);
 }
 

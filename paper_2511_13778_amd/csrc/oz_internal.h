@@ -235,6 +235,36 @@ inline ScanGrid scan_grid(const Problem& p, bool a_rows_contig, bool b_rows_cont
     return s;
 }
 
+// ---- small calls, whose stages share launches ---------------------------------------------
+// Scan and exponents in one launch, where a workgroup can hold all of k of its rows.  Up to 1024 of k it takes 2 to 4 us less (64 x 64 x 500
+// with seven slices 36.7 -> 30.5 us a call, 200 x 300 x 260 31.8 -> 30.2, 512^3 41.4 -> 39.9, 1024^3 58.9 -> 56.6); beyond, the few workgroups
+// are the slower way (512 x 512 x 2048 63.1 -> 64.4, 700 x 700 x 2000 79.7 -> 81.7).
+inline bool scan_once(const Problem& p) {
+    return p.k <= 1024 && p.G <= kScanOnceBlocks && (p.mp + p.np) / kOnceRows <= kScanOnceParts;
+}
+
+constexpr int kDecidePairs = 64;             // edge of a wave's block of pairs
+// LDS of a workgroup that decides: 64 KB, of which the tables of both operands take what the kernel's own variables leave (432 bytes)
+constexpr int kDecideLds = 64 * 1024, kDecideOwnLds = 1024;
+// Most blocks, and most blocks times table rows and four for their end: what every workgroup computes, and computes again on packed int16 if
+// all spans are wide.  Level then with the ESC kernel (300^3 34.1 -> 35.3 us falling back, 200 x 300 x 260 33.7 -> 30.3); with 64 blocks of two
+// rows (512 x 512 x 64) 32.3 -> 36.8.
+constexpr int kDecideBlocks = 32, kDecideWork = 400;
+// bytes of the tables: encoded rows of eight, two operands, and an exponent per row
+inline int64_t decide_table_bytes(const Problem& p) {
+    const int64_t chunks = (2 * p.G + kEncChunk - 1) / kEncChunk * 2;
+    return (round_up(p.m, 64) + round_up(p.n, 64)) * (chunks * 16 + 4);
+}
+// ESC, verdict and slicing in one launch, as far as the sizes go (decide_in_slice): while all of it is one round of workgroups.  200 x 300 x
+// 260 (nine slices) 30.2 us in four launches, 26.2 in three, 256^3 26.9 and 23.3, 96 x 80 x 112 23.7 and 18.4.  With more (four problems of
+// 200 x 300 x 260) what every workgroup computes is computed several times on a CU: 38.7 and 39.0, and 70 instead of 39 where all spans are
+// beyond the encoding.
+inline bool decide_fits(const Problem& p) {
+    const int64_t blocks = ((p.m + kDecidePairs - 1) / kDecidePairs) * ((p.n + kDecidePairs - 1) / kDecidePairs);
+    return scan_once(p) && blocks <= kDecideBlocks && blocks * (2 * p.G + 4) <= kDecideWork &&
+           decide_table_bytes(p) <= kDecideLds - kDecideOwnLds && (p.mp + p.np) / 64 * (p.kp / 32) * p.batch.count <= p.num_cu;
+}
+
 // ---- walk of the ESC kernel ------------------------------------------------------------
 // Position -> block of 128 x 128 pairs (nbi x nbj of them), for `workgroups` that take every workgroups-th position; as many
 // workgroups as blocks take them as they come, fewer share them out.  A row of A or a column of B that is wide or zero
@@ -264,8 +294,7 @@ struct Operand {
     int64_t rows, rows_p;
 };
 void launch_scan(hipStream_t st, const Operand& a, const Operand& b, const Workspace& w, const Problem& p);
-// both in one launch, where a workgroup can hold all of k of its rows
-bool scan_once(const Problem& p);
+// both in one launch (scan_once)
 void launch_scan_exponents(hipStream_t st, const Operand& a, const Operand& b, const Workspace& w, const Problem& p, bool encode,
                            const KnownRecord& known);
 // row and column exponents, the cleared control record, and (encode) the BF16 tables of the ESC

@@ -437,12 +437,6 @@ __global__ __launch_bounds__(64 * kOnceWaves) void scan_exponents_kernel(ScanOnc
     }
 }
 
-// Up to 1024 of k: one launch takes 2 to 4 us less (64 x 64 x 500 with seven slices 36.7 -> 30.5 us a call, 200 x 300 x 260 31.8 -> 30.2, 512^3
-// 41.4 -> 39.9, 1024^3 58.9 -> 56.6); beyond, the few workgroups are the slower way (512 x 512 x 2048 63.1 -> 64.4, 700 x 700 x 2000 79.7 -> 81.7).
-bool scan_once(const Problem& p) {
-    return p.k <= 1024 && p.G <= kScanOnceBlocks && (p.mp + p.np) / kOnceRows <= kScanOnceParts;
-}
-
 void launch_scan_exponents(hipStream_t st, const Operand& a, const Operand& b, const Workspace& w, const Problem& p, bool encode,
                            const KnownRecord& known) {
     const int chunks = encode ? (2 * p.G + 2 * kEncChunk - 1) / (2 * kEncChunk) * 4 : 0;

@@ -34,7 +34,9 @@ def operands(kind, m, k, n, seed):
 
 SIZES = [(1, 1, 1, 0), (64, 64, 64, 0), (65, 63, 129, 0), (96, 80, 112, 16), (300, 200, 260, 0), (512, 256, 64, 0), (513, 256, 64, 0),
          (60, 70, 1024, 32), (60, 70, 1025, 64), (100, 90, 513, 16), (100, 90, 512, 16), (256, 1000, 30, 0), (1024, 1000, 70, 48),
-         (1025, 1000, 70, 0), (320, 300, 330, 128)]
+         (1025, 1000, 70, 0), (320, 300, 330, 128),
+         # the largest tables in LDS, and one block of pairs more than it holds
+         (64, 832, 320, 32), (832, 63, 192, 16), (64, 896, 320, 32), (833, 64, 190, 16)]
 
 
 @pytest.mark.parametrize("m,n,k,b", SIZES)
