@@ -33,7 +33,7 @@ def gemm_asm(tmp_path_factory):
 
 
 def function_body(asm, mangled_prefix):
-    start = next(i for i, ln in enumerate(asm) if ln.startswith(mangled_prefix) and ":" in ln)
+    (start,) = [i for i, ln in enumerate(asm) if ln.startswith(mangled_prefix) and ":" in ln]     # of several instances none is left out
     end = next(i for i in range(start, len(asm)) if asm[i].startswith(".Lfunc_end"))
     return asm[start:end]
 
@@ -76,7 +76,8 @@ def basic_blocks(asm):
 # with transfers and LDS reads at least
 FORMS = {"_ZN2oz14gemm_i8_kernelILb0EE": ("v_mfma_i32_16x16x64_i8", "global_store_dwordx4", 7),
          "_ZN2oz14gemm_i8_kernelILb1EE": ("v_mfma_i32_32x32x32_i8", None, 6),
-         "_ZN2oz18gemm_i8_few_kernel": ("v_mfma_i32_32x32x32_i8", "global_store_dword", 1)}
+         "_ZN2oz18gemm_i8_few_kernelILb0EE": ("v_mfma_i32_32x32x32_i8", "global_store_dword", 1),
+         "_ZN2oz18gemm_i8_few_kernelILb1EE": ("v_mfma_i32_32x32x32_i8", "global_store_dword", 1)}
 
 
 @pytest.mark.parametrize("kernel", FORMS)
