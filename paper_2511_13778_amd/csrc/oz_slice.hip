@@ -20,9 +20,10 @@ struct SliceSide {
 };
 
 // workgroups [0, a.blocks) cut a, the others b
-// MAXS: the most slices the call can come out with
+// MAXS: the most slices the call can come out with.  The widest form has the registers of the next, 115, and four workgroups to a CU: most
+// calls that may need more than 16 slices need fewer (with 137 and three 1024 x 1024 x 16000 with nine slices 106 to 115 us, now 93 to 97).
 template <int MAXS>
-__global__ __launch_bounds__(256, MAXS <= 8 ? 6 : MAXS <= 16 ? 4 : 3) void slice_kernel(SliceSide a, SliceSide b, int64_t k, int64_t kp, const Record* rec, Batch bt) {
+__global__ __launch_bounds__(256, MAXS <= 8 ? 6 : 4) void slice_kernel(SliceSide a, SliceSide b, int64_t k, int64_t kp, const Record* rec, Batch bt) {
     round_down_fp64();
     const bool second = int64_t(blockIdx.x) >= a.blocks;
     const int64_t ws = bt.ws_at(blockIdx.z);
@@ -45,25 +46,14 @@ __global__ __launch_bounds__(256, MAXS <= 8 ? 6 : MAXS <= 16 ? 4 : 3) void slice
         put_rows<MAXS>(bits, s.o, rb, threadIdx.x, cb, kp, er, s.out, S);
         return;
     }
-    // 64 rows x 64 k
+    // 64 rows x 64 k, all four chunks requested before the first is cut (one in work and one on its way, for wider words: 8192 x 8192
+    // twice at up to 26 slices, nine used, 507 to 528 us, now 423 to 485; 3000 x 3000 twice 81, now 75)
     const int64_t r0 = rb * 64 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 16, c0 = cb * 4;
-    if constexpr (MAXS <= 8) {
-        uint64_t bits[4][4];
+    uint64_t bits[4][4];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) load_k(s.o, r0, c0 + c, k, bits[c]);
+    for (int c = 0; c < 4; ++c) load_k(s.o, r0, c0 + c, k, bits[c]);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) put_k<MAXS>(bits[c], s.o, r0, c0 + c, kp, er, s.out, S);
-    } else {                             // the wider words leave registers for one chunk in work and one on its way
-        uint64_t now[4], next[4] = {};
-        load_k(s.o, r0, c0, k, now);
-#pragma unroll 1
-        for (int c = 0; c < 4; ++c) {
-            if (c < 3) load_k(s.o, r0, c0 + c + 1, k, next);
-            put_k<MAXS>(now, s.o, r0, c0 + c, kp, er, s.out, S);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) now[e] = next[e];
-        }
-    }
+    for (int c = 0; c < 4; ++c) put_k<MAXS>(bits[c], s.o, r0, c0 + c, kp, er, s.out, S);
 }
 
 void launch_slice(hipStream_t st, const Operand& a, const Operand& b, const Workspace& w, const Problem& p) {

@@ -5,8 +5,8 @@
 //   X = floor(a * 2^q),  q = 8S - 3 - e_row,  |X| < 2^(8S-2)   (one headroom bit)
 //   X = sum_s d_s 256^(S-1-s),  d_s in [-128, 127].
 // a = sgn * M * 2^(E-1075) with the integer significand M, so X = (sgn*M) shifted by
-// E - 1075 + q: written here as a 64-bit window W at bit offset o (X = W * 2^o), which covers
-// any S up to 26 without multi-word arithmetic (up to 8 and up to 16 slices take one word of 64 or 128 bits instead).
+// E - 1075 + q: beyond 16 slices a word of 64 bits at a byte of its own holds all digits that are not zero, up to 8 and up to 16 slices
+// one word of 64 or 128 bits holds all of X.
 //
 // Output layout (what the INT8 GEMM's tiles load with contiguous 16-byte pieces):
 //   slices[s][l/16][r][l%16]  for row r (padded to rows_p), k index l (padded to kp); padding = 0.
@@ -17,37 +17,33 @@
 namespace oz {
 
 
+// Digits of an entry for any slice count: those of a 64-bit word, eight of them, from bit o (a multiple of eight) on; the others are zero.
+// (53 bits shifted by at most seven: the leading one of the eight holds what is left with its sign, so no carry leaves them.  Byte
+// by byte with a carry a register more an entry, and 20 slices of 3000 x 3000 twice 175 to 179 us, now 116 to 134.)
 struct Fixed {
-    int64_t W;
+    uint64_t D;
     int o;
 };
 
 __device__ __forceinline__ Fixed fixed_point(uint64_t bits, int e_row, int S) {
     const uint64_t mag = bits & 0x7FFFFFFFFFFFFFFFull;
     Fixed f;
-    f.W = 0;
+    f.D = 0;
     f.o = 0;
     if (mag == 0 || e_row <= kExpAllZero) return f;
     const int field = int(mag >> 52);
     const uint64_t frac = mag & 0x000FFFFFFFFFFFFFull;
     const int64_t M = int64_t(field ? (frac | 0x0010000000000000ull) : frac);
     const int64_t sM = (bits >> 63) ? -M : M;
-    const int sh = max(field, 1) - 1075 + (8 * S - 2 - kHeadroomBits - e_row);
+    const int sh = min(max(field, 1) - 1075 + (8 * S - 2 - kHeadroomBits - e_row), 8 * S);   // only Inf/NaN input (unguarded mode) can reach the clamp
+    constexpr uint64_t kBias = 0x0080808080808080ull;
     if (sh >= 0) {
-        f.W = sM;
-        f.o = min(sh, 8 * S);   // only Inf/NaN input (unguarded mode) can reach the clamp
+        f.D = ((uint64_t(sM) << (sh & 7)) + kBias) ^ kBias;
+        f.o = sh & ~7;
     } else {
-        f.W = sM >> min(-sh, 63);   // arithmetic shift: rounds toward -infinity
+        f.D = (uint64_t(sM >> min(-sh, 63)) + kBias) ^ kBias;   // arithmetic shift: rounds toward -infinity
     }
     return f;
-}
-
-// bits [8b, 8b+8) of W * 2^o (two's complement, sign-extended), b = 0 least significant
-__device__ __forceinline__ uint32_t byte_of(const Fixed& f, int b) {
-    const int p = 8 * b - f.o;
-    if (p >= 0) return uint32_t(f.W >> min(p, 63)) & 0xFFu;
-    if (p > -8) return (uint32_t(f.W) << (-p)) & 0xFFu;
-    return 0u;
 }
 
 // N = 4 or 16 consecutive k of one row leave N bytes per slice.
@@ -60,20 +56,15 @@ __device__ __forceinline__ void store_digits(const uint32_t (&w)[N / 4], int8_t*
     __builtin_nontemporal_store(v, reinterpret_cast<vec*>(plane + lane_off));
 }
 
-// Digits of N consecutive k of one row, least significant slice first.
 template <int N>
 __device__ __forceinline__ void emit_slices(const Fixed (&f)[N], int S, int8_t* plane0, uint32_t lane_off, int64_t slice_stride) {
-    uint32_t carry[N];
-#pragma unroll
-    for (int e = 0; e < N; ++e) carry[e] = 0;
     for (int s = S - 1; s >= 0; --s) {
-        const int b = S - 1 - s;
         uint32_t w[N / 4] = {};
 #pragma unroll
         for (int e = 0; e < N; ++e) {
-            const uint32_t u = byte_of(f[e], b) + carry[e];
-            carry[e] = (u >= 128u) ? 1u : 0u;       // unused after the leading slice
-            w[e >> 2] |= (u & 0xFFu) << (8 * (e & 3));
+            const uint32_t p = uint32_t(8 * (S - 1 - s) - f[e].o);
+            w[e >> 2] |= (p < 64u ? uint32_t(f[e].D >> (p & 63u)) & 0xFFu : 0u) << (8 * (e & 3));
+            if (e % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
         store_digits<N>(w, plane0 + int64_t(s) * slice_stride, lane_off);
     }
@@ -222,7 +213,10 @@ __device__ __forceinline__ void emit(const uint64_t (&bits)[N], int e_row, int S
     if constexpr (MAXS > 16) {
         Fixed f[N];
 #pragma unroll
-        for (int e = 0; e < N; ++e) f[e] = fixed_point(bits[e], e_row, S);
+        for (int e = 0; e < N; ++e) {
+            f[e] = fixed_point(bits[e], e_row, S);
+            __builtin_amdgcn_sched_barrier(0);               // one at a time: registers
+        }
         emit_slices<N>(f, S, plane0, lane_off, slice_stride);
     }
 }

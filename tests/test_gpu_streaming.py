@@ -26,7 +26,7 @@ def operand(rng, rows, k, extreme):
     return x
 
 
-@pytest.mark.parametrize("S", [1, 2, 3, 4, 5, 7, 8, 9, 16, 17])
+@pytest.mark.parametrize("S", [1, 2, 3, 4, 5, 7, 8, 9, 16, 17, 21, 26])
 @pytest.mark.parametrize("rows,k,extreme", [(300, 70, True), (257, 128, False), (64, 15, True), (130, 64, True)])
 def test_slices_of_either_storage_order(lib, S, rows, k, extreme):
     g, h = lib
