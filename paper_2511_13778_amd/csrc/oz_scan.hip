@@ -281,8 +281,11 @@ __device__ __forceinline__ void scan_k64(const ScanSide& s, int64_t rb, int g0, 
 }
 
 // Both operands in one launch: the first blocks_a workgroups scan op(A), the others op(B), from ESC block g_first on.
-template <bool NT>
-__global__ __launch_bounds__(256, 6) void scan_kernel(ScanSide a, ScanSide b, int64_t blocks_a, int g_first, int per, int64_t k,
+// K64: some operand takes scan_k64, which needs 78 registers for its 16 rows in flight, six workgroups to a CU; calls without such an operand
+// have a kernel of 52 registers and eight to a CU (one kernel of 78 for all: ESC blocks of 16, 4096^3 with k contiguous 132 us, now 122, 2048^3 38,
+// now 35; scan_k64 with 63 registers, each 64 of k folded by itself: ESC blocks of 256, 4096^3 72 and then 77).
+template <bool NT, bool K64>
+__global__ __launch_bounds__(256, K64 ? 6 : 8) void scan_kernel(ScanSide a, ScanSide b, int64_t blocks_a, int g_first, int per, int64_t k,
                                                    int bl, int G, Record* rec, Batch bt) {
     const int64_t ws = bt.ws_at(blockIdx.z);
     if (blockIdx.x == 0 && threadIdx.x == 0) at_bytes(rec, ws)->infnan = 0;        // the exponents tell (exponents_kernel)
@@ -295,7 +298,7 @@ __global__ __launch_bounds__(256, 6) void scan_kernel(ScanSide a, ScanSide b, in
     const int64_t rb = id % s.row_blocks;
     const int g0 = g_first + int(id / s.row_blocks) * per;
     if (s.o.stride_r == 1) scan_rows<NT>(s, rb, g0, per, k, bl, G);
-    else if (bl % 64 == 0) scan_k64<NT>(s, rb, g0, per, k, bl, G);
+    else if constexpr (K64) scan_k64<NT>(s, rb, g0, per, k, bl, G);
     else if (per == 1) scan_k<1>(s, rb, g0, k, bl, G);
     else scan_k<kScanBlocksPerWg>(s, rb, g0, k, bl, G);
 }
@@ -309,7 +312,8 @@ void launch_scan(hipStream_t st, const Operand& a, const Operand& b, const Works
     // little, and the scan is the faster for it (scan and slicing, seven slices: 8192 x 8192 twice, 1.07 GB, 586 -> 543 us with rows
     // contiguous, 679 -> 629 with k; 4096 x 4096 twice, 268 MB, 171 -> 185)
     const bool stream = (double(p.m) + double(p.n)) * double(p.k) * 8.0 * p.batch.count > kStreamBytes;
-    const auto kernel = stream ? scan_kernel<true> : scan_kernel<false>;
+    const bool k64 = p.esc_block % 64 == 0 && (a.stride_r != 1 || b.stride_r != 1);
+    const auto kernel = stream ? (k64 ? scan_kernel<true, true> : scan_kernel<true, false>) : (k64 ? scan_kernel<false, true> : scan_kernel<false, false>);
     for (int64_t y = 0; y < g.groups; y += g.slab) {
         const int64_t gy = g.groups - y < g.slab ? g.groups - y : g.slab;
         hipLaunchKernelGGL(kernel, dim3(unsigned((g.row_blocks_a + g.row_blocks_b) * gy), 1, unsigned(p.batch.count)), dim3(256), 0, st, sa, sb,

@@ -9,6 +9,7 @@ import pytest
 from test_kernel_isa import CSRC
 
 # kernel: most vector registers (512 to a SIMD's lane: 64 are eight waves, 128 four)
+SCAN = {"scan_kernelILb0ELb0EE": 64, "scan_kernelILb1ELb0EE": 64, "scan_kernelILb0ELb1EE": 84, "scan_kernelILb1ELb1EE": 84}
 SLICING = {"slice_kernelILi8EE": 80, "slice_kernelILi16EE": 128, "slice_kernelILi26EE": 128}
 
 
@@ -28,3 +29,10 @@ def resources(source, tmp_path):
 def test_slicing_keeps_its_waves(tmp_path, kernel):
     (got,) = [v for name, v in resources("oz_slice", tmp_path).items() if kernel in name]
     assert got[0] <= SLICING[kernel] and got[1] == 0, got
+
+
+@pytest.mark.parametrize("kernel", SCAN)
+def test_scan_keeps_its_waves(tmp_path, kernel):
+    # eight workgroups of four waves to a CU where no operand has rows of 64 k a load, six otherwise
+    (got,) = [v for name, v in resources("oz_scan", tmp_path).items() if kernel in name]
+    assert got[0] <= SCAN[kernel] and got[1] == 0, got
