@@ -159,20 +159,22 @@ struct LaunchPlan {
     //               of k adds, with slots, 0.7 and per part 1.57 and 7 ns per unit and byte of a sum, with atomics per part 0.16 and 28 ns
     //               per unit and slice.  256 x 256 blocks (few): per round 9.9 and per 64 of k 0.70 with one slice, 2.07 with two; 2.8 el,
     //               1 el S
-    //   64 x 64     a workgroup per CU: 1.2, per round 0.375 per slice, and per 64 of k 0.18, 45 ns per pair of slices and, where the LDS holds
-    //               one stage only, 45 ns per slice; 0.195 el S, of few slices 2.7 el less 0.345 el S.  Two to a CU (a stage of one 64 of k each; the slice count must be
-    //               known): 1.23, per round of twice as many 1.72 and per 64 of k 0.25 and 68 ns per pair, one alone 0.36 per slice, 0.32 and
-    //               62; 2.1 el
-    //   32 x 32     alone on a CU (no more tiles than CUs, or more slices than half the LDS holds): per round 0.325 per slice, and per 64
-    //               of k 0.51 and 14 ns per pair; two to a CU: per round of twice as many 1.15 and 0.28 per slice, and per 64 of k 0.494,
-    //               16 ns per slice and 17 per pair; 2.6 el.  No less than the slices at 9 TB/s and 1.5 el
+    //   64 x 64     a workgroup per CU: 1.2, per round 0.40 per slice (and 0.47 per slice short of four), and per 64 of k 0.20 and 40 ns per pair
+    //               of slices, where the LDS holds one stage only 47 ns per slice besides, no less than 0.284 and 5 ns per slice for the
+    //               transfers; 3.47 el less 0.23 el S.  Two to a CU (the slice count must be known): per round of twice as many and per 64 of k
+    //               82 ns per pair, no less than 0.118 and 194 ns per slice, one alone 0.295 and 39 per pair; 5 el less 1.5 el S, 0.66 el at
+    //               least.  The products take longer on a chip full of tiles, up to 14 and 15 %, and with a long k, up to 12 and 20 %: the clock
+    //               is lower and fewer slices come from L2
+    //   32 x 32     alone on a CU (no more tiles than CUs, or more slices than half the LDS holds): per round 0.217 per slice, and per 64
+    //               of k 0.53 and 14 ns per pair; two to a CU: per round of twice as many 0.46 and 0.19 per slice, and per 64 of k 0.905
+    //               and 15 ns per pair; 3.9 el.  No less than the slices at 9 TB/s and 1.5 el
     // Rounds are whole up to four, beyond that workgroups end at different times.
-    // Units and 32 x 32 tiles are fitted to 5100 calls of 1 to 26 slices (8 to 8000, k 8 to 6000, one to four problems; counts known and
-    // decided by the device), 64 x 64 tiles to 6900 (5 to 16 slices, 150 to 5000, k 40 to 3000), each timed on every route: of 2400 others
-    // (1 to 12 slices) the choice is 0.2 % off the best on average (1.6 % with the constants of the kernels before), one in 150 by more than 10 %.
-    // 32 x 32 tiles have to be 7 % better from four rounds of two to a CU on; 64 x 64 ones, on a full chip with more than three 64s of k,
-    // 5 %, from sixteen on 8 %, and two to a CU 14 and 28 %: in long runs the clock is lower and they are worse than estimated
-    // (4096 x 4096 x 1024 with seven slices 445 us, on units 437; 4096 x 4096 x 2048 841 and 776; 4096 x 4096 x 512 is the faster on tiles).
+    // Units are fitted to 5100 calls, tiles to 2340 (1 to 26 slices, 40 to 8192, k 16 to 16000, one to four problems, counts known and decided by
+    // the device), each timed on every route for 10 to 150 ms on end: of 1593 others the choice is 0.3 % off the best on average, 53 are more
+    // than 3 % off and six more than 10 %.  (Constants of calls of 5 to 16 slices, and a margin of 14 to 28 % for two to a CU from four tiles
+    // to a CU on, were 0.7 % off, 117 and 27: 1061 x 4496 x 1016 with eight slices 241 us on units, 175 on tiles; 2417 x 1677 x 1383 with seven
+    // 219 and 195; 249 x 3425 x 2858 with twelve 303 and 265; 93 x 1321 x 378 with two 17.3 on 64 x 64 tiles, 15.9 on 32 x 32.)
+    // 32 x 32 tiles have to be 7 % better from four rounds of two to a CU on.
     // Units share launches only while a round holds all problems' (units_batch); otherwise each problem pays its rounds and stages.  Of 735
     // complex products and 734 batches of 200 to 3500, about 200 take tiles for it, 11 % faster on average (1556 x 939 x 331 complex 317 us on
     // units, now 192; 2006 x 1146 x 1529 967, now 617), and fifteen more than 3 % slower (1666 x 2989 x 1234 1171, now 1478).
@@ -202,9 +204,9 @@ struct LaunchPlan {
         int64_t best = count == 1 || units_batch(p) ? units_ns(count) : count * units_ns(1) + (count - 1) * kCallStagesNs;
         const int64_t small_all = small_tiles(p) * count;
         const bool pair = small_all > cus && p.s_cap <= kSmallPairSlices;
-        const int64_t small_products = pair ? rounds_ns(small_all, 2 * cus, 1150 + 279 * S + kt * (494 + 16 * S + 17 * pairs))
-                                            : rounds_ns(small_all, cus, 325 * S + kt * (510 + 14 * pairs));
-        const int64_t small_ns = std::max(small_products + el(2630), small_all * (2 * kSmallTile * kBK) * kt * S / 9000 + el(1500));
+        const int64_t small_products = pair ? rounds_ns(small_all, 2 * cus, 461 + 192 * S + kt * (905 + 15 * pairs))
+                                            : rounds_ns(small_all, cus, 217 * S + kt * (529 + 14 * pairs));
+        const int64_t small_ns = std::max(small_products + el(3931), small_all * (2 * kSmallTile * kBK) * kt * S / 9000 + el(1500));
         if (small_ns < best * (small_all >= 8 * cus ? 93 : 100) / 100 && small_tiles(p) * 512 <= kMaxGridThreads) {
             best = small_ns;
             small = true;
@@ -212,23 +214,24 @@ struct LaunchPlan {
         }
         if (p.s_cap > kMidMaxSlices || p.m * p.n / (kMidTile * kMidTile) > kMaxGridThreads / 1024) return;
         const int64_t mid_all = ((p.m + kMidTile - 1) / kMidTile) * ((p.n + kMidTile - 1) / kMidTile) * count;
-        // Two workgroups to a CU wherever there are more tiles than CUs: of 1900 such calls 1.13 times as fast (0.91 to 1.3), of 2350 with
-        // fewer tiles 0.92 (0.67 to 1.02).
-        const bool known = p.s_min == p.s_cap && p.s_cap <= kMidPairSlices, full_chip = kt > 3 && mid_all >= 4 * cus;
-        int64_t mid_ns, percent = 100;
-        if (known && mid_all > cus) {
-            const int64_t pair_ns = 1720 + kt * (250 + 68 * pairs), alone_ns = 360 * S + kt * (320 + 62 * pairs);
-            const int64_t on_cu = (mid_all + cus - 1) / cus;          // workgroups of the fullest CU
-            mid_ns = 1230 + (mid_all < 8 * cus ? on_cu / 2 * pair_ns + on_cu % 2 * alone_ns : mid_all * pair_ns / (2 * cus)) + el(2100);
-            if (full_chip) percent = kt < 16 ? 86 : 72;
-            mid_pair = true;
-        } else {
-            mid_ns = 1200 + rounds_ns(mid_all, cus, 375 * S + kt * (180 + 45 * pairs + (S > kMidDoubleSlices ? 45 * S : 0))) +
-                     el(std::max<int64_t>(195 * S, 2700 - 345 * S));
-            if (full_chip) percent = kt < 16 ? 95 : 92;
+        // thousandths by which the products take longer: on a chip full of tiles (from `first` rounds on, all of it four later) and for a long k (all
+        // of it from 128 64s on)
+        auto slower = [&](int64_t most, int64_t first, int64_t most_long) {
+            return 1000 + most * std::clamp<int64_t>(mid_all - first * cus, 0, 4 * cus) / (4 * cus) + most_long * std::min(kt, 128) / 128;
+        };
+        const int64_t alone_kt = std::max<int64_t>(200 + 40 * pairs + (S > kMidDoubleSlices ? 47 * S : 0), 284 + 5 * S);
+        const int64_t alone_ns = 1232 + el(std::max<int64_t>(3474 - 229 * S, 0)) +
+                                 rounds_ns(mid_all, cus, 400 * S + std::max<int64_t>(470 * (4 - S), 0) + kt * alone_kt * slower(137, 1, 123) / 1000);
+        if (alone_ns < best) {
+            best = alone_ns;
+            mid = true;
         }
-        mid = mid_ns < best * percent / 100;
-        mid_pair = mid_pair && mid;
+        if (p.s_min == p.s_cap && p.s_cap <= kMidPairSlices && mid_all > cus) {
+            const int64_t two = kt * std::max<int64_t>(82 * pairs, 118 + 194 * S), one = kt * (295 + 39 * pairs);
+            const int64_t on_cu = (mid_all + cus - 1) / cus;          // workgroups of the fullest CU
+            const int64_t products = mid_all < 8 * cus ? on_cu / 2 * two + on_cu % 2 * one : mid_all * two / (2 * cus);
+            if (products * slower(151, 2, 196) / 1000 + el(std::max<int64_t>(657, 5000 - 1500 * S)) < best) mid = mid_pair = true;
+        }
         if (mid) small = small_pair = false;
     }
 

@@ -1,6 +1,6 @@
 """GPU parity of the one-launch slice GEMM and recomposition on 64 x 64 tiles (gemm_mid_kernel): edges of its tiles and 64s of k, one
-and two workgroups to a CU, one to four groups of anti-diagonals, one stage in LDS and several; and of units next to it.  Digits,
-leading words and C are the oracle's bit for bit."""
+and two workgroups to a CU, one to four groups of anti-diagonals, one stage in LDS and several.  Digits, leading words and C
+are the oracle's bit for bit."""
 import numpy as np
 import pytest
 
@@ -15,9 +15,9 @@ pytestmark = pytest.mark.gpu
     (700, 800, 64, 1), (961, 1030, 300, 2), (1030, 1300, 70, 3), (1100, 1000, 200, 4), (1500, 1600, 50, 5), (1030, 1300, 450, 6),
     (65, 9000, 130, 5), (9000, 65, 130, 5), (1100, 1024, 129, 7), (1281, 1030, 65, 8),                 # two workgroups to a CU
     (700, 800, 64, 5), (640, 770, 300, 3), (900, 1000, 100, 8), (700, 800, 130, 9), (700, 810, 64, 10), (705, 800, 65, 12),
-    (900, 1000, 100, 13), (700, 800, 190, 16), (520, 530, 1000, 3),                                     # one (these three: 32 x 32 tiles)
+    (900, 1000, 100, 13), (700, 800, 190, 16), (520, 530, 1000, 3),                                     # one
     (1500, 1300, 64, 14), (1490, 1310, 130, 13), (300, 1650, 64, 16),                                   # one, four groups
-    (2100, 2200, 700, 9), (1100, 1200, 2000, 9), (600, 700, 3000, 12),                                  # units: two launches, parts
+    (2100, 2200, 700, 9), (1100, 1200, 2000, 9), (600, 700, 3000, 12),                                  # one, a long k (the last: 32 x 32 tiles)
 ])
 def test_tiles_of_64(lib, m, n, k, S):
     g, h = lib

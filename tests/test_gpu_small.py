@@ -38,7 +38,19 @@ def test_small_calls_with_slice_counts_per_block(lib, m, n, k):
 
 @pytest.mark.parametrize("m,n,k,S", [(2300, 2500, 200, 7), (2310, 2050, 190, 5), (1030, 1300, 900, 6), (1100, 1200, 2000, 9), (129, 300, 5000, 4)])
 def test_calls_just_beyond_them(lib, m, n, k, S):
-    # several units per workgroup, a split last round, parts put together by the recomposition
+    # 64 x 64 tiles, and parts of units (129 x 300 x 5000)
     g, h = lib
     A, B = wl.lognormal_spread(m, k, n, 0.5, seed=4100 + S + k)
     check_against_oracle(g, h, A, B, 1.0, 0.0, None, mode="unguarded", slices=S, bound=False)
+
+
+# calls on units, whatever the estimate of the tiles (tests/test_unit_walk_cpu.py holds them to it): whole, a split last round, parts put together by
+# the recomposition, sums by atomics
+UNITS = [(1500, 2200, 6000, 3), (2100, 2200, 6000, 3), (1500, 700, 6000, 3), (520, 530, 6000, 7), (130, 65, 3000, 3), (130, 300, 4500, 12)]
+
+
+@pytest.mark.parametrize("m,n,k,S", UNITS)
+def test_calls_on_units(lib, m, n, k, S):
+    g, h = lib
+    A, B, Cin = wl.lognormal_spread(m, k, n, 0.5, seed=4200 + S + k, with_c=True)
+    check_against_oracle(g, h, A, B, 1.5, 0.5, Cin, mode="unguarded", slices=S, bound=False, pad=1, transa="NT"[S & 1])

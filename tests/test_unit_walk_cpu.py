@@ -80,6 +80,13 @@ def test_which_calls_take_the_256_blocks(walk):
     assert [r[5] for r in got] == [1] * len(yes) + [0] * (len(no) + len(yes))
 
 
+def test_calls_of_the_gpu_test_of_units_take_them(walk, tmp_path_factory):
+    from test_gpu_small import UNITS
+    plan = host_program(tmp_path_factory, "host_call_plan.cpp")
+    assert [g for g, in plan([(m, n, k, S, S, 0, 1) for m, n, k, S in UNITS])] == [0] * len(UNITS)
+    assert [r[0] for r in walk([(*c, 0, 256) for c in UNITS])] == [0, 1, 1, 1, 2, 2]
+
+
 @pytest.mark.parametrize("num_cu", [4, 12, 36, 100, 250, 304])
 def test_other_numbers_of_compute_units(walk, num_cu):
     # a device that shows some of its units only: not always a multiple of eight.  A workgroup keeps its part of k while it
@@ -155,13 +162,22 @@ def test_fp64_tile_is_near_the_fastest_measured(f64_plan):
 
 
 def test_route_of_an_emulated_call_is_near_the_fastest_measured(tmp_path_factory):
-    # a hundred calls timed on every route; among them those on which an estimate without the bytes of the 32 x 32 tiles, and with two
-    # of their workgroups to a CU whatever the slices in LDS, took the wrong one
+    # calls timed on every route, 10 to 150 ms on end each; among them those on which an estimate that asked 64 x 64 tiles to be 14 to 28 %
+    # better from four to a CU on, and took the cost of few slices from that of many, was up to 38 % off (5 % on average over these)
     run = host_program(tmp_path_factory, "host_call_plan.cpp")
     rows = golden_times("route_times.txt")
     got = run([(*r[:6], 1) for r in rows])
     off = [float(r[6 + g]) / min(float(x) for x in r[6:] if x != "-") for r, (g,) in zip(rows, got)]
-    assert max(off) < 1.25 and sum(off) / len(off) < 1.03, (max(off), sum(off) / len(off))
+    assert max(off) < 1.2 and sum(off) / len(off) < 1.015, (max(off), sum(off) / len(off))
+
+
+def test_route_does_not_jump_where_the_times_do_not(tmp_path_factory):
+    # seven slices: both sides of the four tiles to a CU and of the 64s of k that the times do not step at (2048^3 215 us on units, 211 on tiles,
+    # 2500 x 2500 x 960 and 961 on tiles 175 and 189, on units 199 and 213); 4096^3 and 8192^3 are faster on units, by 6 to 7 %
+    run = host_program(tmp_path_factory, "host_call_plan.cpp")
+    tiles = [(1984, 1984, 2048), (2048, 2048, 2048), (2500, 2500, 960), (2500, 2500, 961), (3000, 3000, 1500)]
+    units = [(4096, 4096, 4096), (8192, 8192, 4096), (8192, 8192, 8192)]
+    assert [g for g, in run([(*s, 7, 7, 0, 1) for s in tiles + units])] == [3] * len(tiles) + [0] * len(units)
 
 
 def test_fallback_is_where_it_is_near_the_fastest_measured(tmp_path_factory):
