@@ -52,8 +52,21 @@ __global__ __launch_bounds__(256, MAXS <= 8 ? 6 : 4) void slice_kernel(SliceSide
     uint64_t bits[4][4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) load_k(s.o, r0, c0 + c, k, bits[c]);
+    if constexpr (MAXS <= 8) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) put_k<MAXS>(bits[c], s.o, r0, c0 + c, kp, er, s.out, S);
+        for (int c = 0; c < 4; ++c) put_k<MAXS>(bits[c], s.o, r0, c0 + c, kp, er, s.out, S);
+    } else {                             // one copy of the longer code
+#pragma unroll 1
+        for (int c = 0; c < 4; ++c) {
+            put_k<MAXS>(bits[0], s.o, r0, c0 + c, kp, er, s.out, S);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                bits[0][e] = bits[1][e];
+                bits[1][e] = bits[2][e];
+                bits[2][e] = bits[3][e];
+            }
+        }
+    }
 }
 
 void launch_slice(hipStream_t st, const Operand& a, const Operand& b, const Workspace& w, const Problem& p) {
