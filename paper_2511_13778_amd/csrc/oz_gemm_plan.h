@@ -151,7 +151,7 @@ struct LaunchPlan {
     }
 
     // Whether slice GEMM and recomposition take longer in their two launches than in one, and in which: estimated in ns for S
-    // slices (one more than the fewest where the device decides).  What a tile costs beside its products is its start and
+    // slices (two more than the fewest where the device decides).  What a tile costs beside its products is its start and
     // its end, its sums and the digits it writes: with many slices and a long k the 128 x 128 units, which read fewer bytes
     // per product, win; otherwise the larger of the small tiles that still gives every CU one.  The times below are those of a whole
     // call but for what all routes share, in us; el: million elements of C.
@@ -159,20 +159,20 @@ struct LaunchPlan {
     //               of k adds, with slots, 0.7 and per part 1.57 and 7 ns per unit and byte of a sum, with atomics per part 0.16 and 28 ns
     //               per unit and slice.  256 x 256 blocks (few): per round 9.9 and per 64 of k 0.70 with one slice, 2.07 with two; 2.8 el,
     //               1 el S
-    //   64 x 64     a workgroup per CU: 1.2, per round 0.40 per slice (and 0.47 per slice short of four), and per 64 of k 0.20 and 40 ns per pair
-    //               of slices, where the LDS holds one stage only 47 ns per slice besides, no less than 0.284 and 5 ns per slice for the
-    //               transfers; 3.47 el less 0.23 el S.  Two to a CU (the slice count must be known): per round of twice as many and per 64 of k
-    //               82 ns per pair, no less than 0.118 and 194 ns per slice, one alone 0.295 and 39 per pair; 5 el less 1.5 el S, 0.66 el at
-    //               least.  The products take longer on a chip full of tiles, up to 14 and 15 %, and with a long k, up to 12 and 20 %: the clock
-    //               is lower and fewer slices come from L2
-    //   32 x 32     alone on a CU (no more tiles than CUs, or more slices than half the LDS holds): per round 0.217 per slice, and per 64
-    //               of k 0.53 and 14 ns per pair; two to a CU: per round of twice as many 0.46 and 0.19 per slice, and per 64 of k 0.905
-    //               and 15 ns per pair; 3.9 el.  No less than the slices at 9 TB/s and 1.5 el
+    //   64 x 64     a workgroup per CU: 1.9, per round 0.37 per slice (and 0.51 per slice short of four), and per 64 of k 0.107 and 42 ns per
+    //               pair of slices, where the LDS holds one stage only 40 ns per slice besides, no less than 0.243 and 26 ns per slice for the
+    //               transfers; 4.7 el less 0.31 el S.  Two to a CU (the slice count must be known): per round of twice as many and per 64 of k
+    //               0.086 and 79 ns per pair, no less than 0.08 and 204 ns per slice, one alone 0.238 and 23 per pair; 5 el less 1.5 el S, 0.4 el
+    //               at least.  The products take longer on a chip full of tiles, up to 17 and 20 %, and with a long k, up to 10 and 12 %: the
+    //               clock is lower and fewer slices come from L2
+    //   32 x 32     alone on a CU (no more tiles than CUs, or more slices than half the LDS holds): per round 0.148 per slice, and per 64
+    //               of k 0.53 and 14 ns per pair; two to a CU: per round of twice as many 1.67 and 0.088 per slice, and per 64 of k 0.72
+    //               and 17 ns per pair; 5.2 el.  No less than the slices at 9 TB/s and 1.5 el
     // Rounds are whole up to four, beyond that workgroups end at different times.
-    // Units are fitted to 5100 calls, tiles to 2340 (1 to 26 slices, 40 to 8192, k 16 to 16000, one to four problems, counts known and decided by
-    // the device), each timed on every route for 10 to 150 ms on end: of 1593 others the choice is 0.3 % off the best on average, 53 are more
-    // than 3 % off and six more than 10 %.  (Constants of calls of 5 to 16 slices, and a margin of 14 to 28 % for two to a CU from four tiles
-    // to a CU on, were 0.7 % off, 117 and 27: 1061 x 4496 x 1016 with eight slices 241 us on units, 175 on tiles; 2417 x 1677 x 1383 with seven
+    // Units are fitted to 5100 calls, tiles to 3240 (1 to 26 slices, 40 to 8192, k 16 to 16000, one to four problems, counts known and decided by
+    // the device), each timed on every route for 10 to 150 ms on end: of 2150 others the choice is 0.3 % off the best on average, 66 are more
+    // than 3 % off and seven more than 10 %.  (Constants of calls of 5 to 16 slices, and a margin of 14 to 28 % for two to a CU from four tiles
+    // to a CU on, were 0.8 % off, 195 and 41: 1061 x 4496 x 1016 with eight slices 241 us on units, 175 on tiles; 2417 x 1677 x 1383 with seven
     // 219 and 195; 249 x 3425 x 2858 with twelve 303 and 265; 93 x 1321 x 378 with two 17.3 on 64 x 64 tiles, 15.9 on 32 x 32.)
     // 32 x 32 tiles have to be 7 % better from four rounds of two to a CU on.
     // Units share launches only while a round holds all problems' (units_batch); otherwise each problem pays its rounds and stages.  Of 735
@@ -183,7 +183,7 @@ struct LaunchPlan {
     void fuse(const Problem& p) {
         small = small_pair = mid = mid_pair = false;
         if (p.nkb != 1) return;
-        const int64_t S = p.s_min == p.s_cap ? p.s_cap : p.s_min + 1, pairs = S * (S + 1) / 2, cus = p.num_cu, count = p.batch.count;
+        const int64_t S = p.s_min == p.s_cap ? p.s_cap : std::min(p.s_cap, p.s_min + 2), pairs = S * (S + 1) / 2, cus = p.num_cu, count = p.batch.count;
         const int64_t area = p.m * p.n * count;
         auto el = [&](int64_t ns) { return area * ns / 1000000; };
         // workgroups, per round, ns of a round
@@ -204,9 +204,9 @@ struct LaunchPlan {
         int64_t best = count == 1 || units_batch(p) ? units_ns(count) : count * units_ns(1) + (count - 1) * kCallStagesNs;
         const int64_t small_all = small_tiles(p) * count;
         const bool pair = small_all > cus && p.s_cap <= kSmallPairSlices;
-        const int64_t small_products = pair ? rounds_ns(small_all, 2 * cus, 461 + 192 * S + kt * (905 + 15 * pairs))
-                                            : rounds_ns(small_all, cus, 217 * S + kt * (529 + 14 * pairs));
-        const int64_t small_ns = std::max(small_products + el(3931), small_all * (2 * kSmallTile * kBK) * kt * S / 9000 + el(1500));
+        const int64_t small_products = pair ? rounds_ns(small_all, 2 * cus, 1673 + 88 * S + kt * (720 + 17 * pairs))
+                                            : rounds_ns(small_all, cus, 148 * S + kt * (530 + 14 * pairs));
+        const int64_t small_ns = std::max(small_products + el(5236), small_all * (2 * kSmallTile * kBK) * kt * S / 9000 + el(1500));
         if (small_ns < best * (small_all >= 8 * cus ? 93 : 100) / 100 && small_tiles(p) * 512 <= kMaxGridThreads) {
             best = small_ns;
             small = true;
@@ -219,18 +219,18 @@ struct LaunchPlan {
         auto slower = [&](int64_t most, int64_t first, int64_t most_long) {
             return 1000 + most * std::clamp<int64_t>(mid_all - first * cus, 0, 4 * cus) / (4 * cus) + most_long * std::min(kt, 128) / 128;
         };
-        const int64_t alone_kt = std::max<int64_t>(200 + 40 * pairs + (S > kMidDoubleSlices ? 47 * S : 0), 284 + 5 * S);
-        const int64_t alone_ns = 1232 + el(std::max<int64_t>(3474 - 229 * S, 0)) +
-                                 rounds_ns(mid_all, cus, 400 * S + std::max<int64_t>(470 * (4 - S), 0) + kt * alone_kt * slower(137, 1, 123) / 1000);
+        const int64_t alone_kt = std::max<int64_t>(107 + 42 * pairs + (S > kMidDoubleSlices ? 40 * S : 0), 243 + 26 * S);
+        const int64_t alone_ns = 1905 + el(std::max<int64_t>(4663 - 310 * S, 0)) +
+                                 rounds_ns(mid_all, cus, 367 * S + std::max<int64_t>(512 * (4 - S), 0) + kt * alone_kt * slower(169, 1, 103) / 1000);
         if (alone_ns < best) {
             best = alone_ns;
             mid = true;
         }
         if (p.s_min == p.s_cap && p.s_cap <= kMidPairSlices && mid_all > cus) {
-            const int64_t two = kt * std::max<int64_t>(82 * pairs, 118 + 194 * S), one = kt * (295 + 39 * pairs);
+            const int64_t two = kt * std::max<int64_t>(86 + 79 * pairs, 80 + 204 * S), one = kt * (238 + 23 * pairs);
             const int64_t on_cu = (mid_all + cus - 1) / cus;          // workgroups of the fullest CU
             const int64_t products = mid_all < 8 * cus ? on_cu / 2 * two + on_cu % 2 * one : mid_all * two / (2 * cus);
-            if (products * slower(151, 2, 196) / 1000 + el(std::max<int64_t>(657, 5000 - 1500 * S)) < best) mid = mid_pair = true;
+            if (products * slower(203, 2, 123) / 1000 + el(std::max<int64_t>(435, 5000 - 1500 * S)) < best) mid = mid_pair = true;
         }
         if (mid) small = small_pair = false;
     }

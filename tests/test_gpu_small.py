@@ -46,7 +46,7 @@ def test_calls_just_beyond_them(lib, m, n, k, S):
 
 # calls on units, whatever the estimate of the tiles (tests/test_unit_walk_cpu.py holds them to it): whole, a split last round, parts put together by
 # the recomposition, sums by atomics
-UNITS = [(1500, 2200, 6000, 3), (2100, 2200, 6000, 3), (1500, 700, 6000, 3), (520, 530, 6000, 7), (130, 65, 3000, 3), (130, 300, 4500, 12)]
+UNITS = [(1500, 2200, 6000, 3), (2100, 2200, 9000, 3), (1500, 700, 9000, 3), (1500, 700, 3000, 8), (130, 65, 3000, 3), (130, 300, 9000, 12)]
 
 
 @pytest.mark.parametrize("m,n,k,S", UNITS)
