@@ -214,15 +214,22 @@ constexpr int64_t kMaxGridThreads = (int64_t(1) << 32) - 1;   // of one launch a
 struct ScanGrid {
     int64_t row_blocks_a, row_blocks_b;
     int per;
+    bool k64;
     int64_t groups, slab;
 };
-// rows_contig: stride_r == 1.  A workgroup of 256 threads covers 64 rows; 16 of an operand with k contiguous whose ESC blocks are not
-// whole 64s of k
+// rows_contig: stride_r == 1.  A workgroup of 256 threads covers 64 rows of such an operand, and of one with k contiguous where it reads
+// 64 k of a row per load (k64), otherwise 16.  k64: ESC blocks that are one 64 of k, and longer ones, through which a wave then walks, where there are
+// workgroups of 64 rows and a block for one and a half to a CU, or for half the CUs where the other operand has workgroups of its
+// kind anyway.  With fewer the walk is what a call waits for (scan and exponents with 64 and 16 rows: 1955 x 36 x 2987 in blocks of 1024 28.8 us and
+// 20.2, 160 x 1518 x 1783 of 256 15.0 and 12.5; beyond, 2000 x 2000 x 4096 of 512 31.3 and 36.8).  Over 3725 calls with blocks of 128 to 1024 the choice
+// is 0.9 % off the better one, 64 rows always 10 %, 16 always 2 %, and 21 calls are more than 5 % slower than with 64.
 inline ScanGrid scan_grid(const Problem& p, bool a_rows_contig, bool b_rows_contig) {
     ScanGrid s;
-    const bool whole = p.esc_block % 64 == 0;
-    s.row_blocks_a = p.mp / (a_rows_contig || whole ? 64 : 16);
-    s.row_blocks_b = p.np / (b_rows_contig || whole ? 64 : 16);
+    const bool one = a_rows_contig != b_rows_contig;
+    s.k64 = !(a_rows_contig && b_rows_contig) && p.esc_block % 64 == 0 &&
+            (p.esc_block == 64 || (p.m + p.n) * p.k * p.batch.count >= int64_t(one ? 1 : 3) * p.num_cu * 32 * p.esc_block);
+    s.row_blocks_a = p.mp / (a_rows_contig || s.k64 ? 64 : 16);
+    s.row_blocks_b = p.np / (b_rows_contig || s.k64 ? 64 : 16);
     const int64_t row_blocks = s.row_blocks_a + s.row_blocks_b;
     // ESC blocks per workgroup: four, or one where four would leave fewer than four workgroups per CU: such a call waits
     // for the loads of one block after the other, a larger one is bound by the bytes read, and four blocks leave a quarter of

@@ -131,8 +131,8 @@ __device__ __forceinline__ void scan_rows(const ScanSide& s, int64_t rb, int g0,
 
 // k contiguous in memory (stride_l == 1): 16 lanes share one row so that a load instruction
 // reads 128 contiguous bytes per row; partial results are combined across the 16 lanes.
-// A workgroup covers 16 rows.  For ESC blocks that are no whole 64s of k (scan_k64 below).  The loads of two blocks are in flight together (of four: 77 registers, and six workgroups to a CU
-// instead of eight: 4224 x 3008 x 1792 32 us against 25).
+// A workgroup covers 16 rows.  For calls that do not take scan_k64 below (scan_grid).  The loads of two blocks are in flight together (of
+// four: 77 registers, and six workgroups to a CU instead of eight: 4224 x 3008 x 1792 32 us against 25).
 template <int PER>
 __device__ __forceinline__ void scan_k(const ScanSide& s, int64_t rb, int g0, int64_t k, int b, int G) {
     constexpr int PAIR = PER < 2 ? PER : 2;
@@ -312,8 +312,7 @@ void launch_scan(hipStream_t st, const Operand& a, const Operand& b, const Works
     // little, and the scan is the faster for it (scan and slicing, seven slices: 8192 x 8192 twice, 1.07 GB, 586 -> 543 us with rows
     // contiguous, 679 -> 629 with k; 4096 x 4096 twice, 268 MB, 171 -> 185)
     const bool stream = (double(p.m) + double(p.n)) * double(p.k) * 8.0 * p.batch.count > kStreamBytes;
-    const bool k64 = p.esc_block % 64 == 0 && (a.stride_r != 1 || b.stride_r != 1);
-    const auto kernel = stream ? (k64 ? scan_kernel<true, true> : scan_kernel<true, false>) : (k64 ? scan_kernel<false, true> : scan_kernel<false, false>);
+    const auto kernel = stream ? (g.k64 ? scan_kernel<true, true> : scan_kernel<true, false>) : (g.k64 ? scan_kernel<false, true> : scan_kernel<false, false>);
     for (int64_t y = 0; y < g.groups; y += g.slab) {
         const int64_t gy = g.groups - y < g.slab ? g.groups - y : g.slab;
         hipLaunchKernelGGL(kernel, dim3(unsigned((g.row_blocks_a + g.row_blocks_b) * gy), 1, unsigned(p.batch.count)), dim3(256), 0, st, sa, sb,

@@ -20,7 +20,9 @@ def operand(rng, rows, k, along):
 
 
 @pytest.mark.parametrize("m,n,k,b", [(1, 1, 1, 16), (17, 65, 16, 16), (70, 33, 100, 48), (64, 80, 129, 64), (90, 130, 2100, 1024),
-                                     (300, 200, 700, 128), (65, 300, 9000, 16), (2100, 2300, 530, 64)])
+                                     (300, 200, 700, 128), (65, 300, 9000, 16), (2100, 2300, 530, 64),
+                                     # blocks of two and four 64s of k on either side of where a workgroup takes 64 rows
+                                     (600, 40, 1600, 128), (600, 40, 1700, 128), (40, 600, 3201, 256), (40, 600, 3301, 256)])
 @pytest.mark.parametrize("ta,tb", [("N", "N"), ("T", "T")])
 def test_exponents_of_mixed_blocks(lib, m, n, k, b, ta, tb):
     g, h = lib

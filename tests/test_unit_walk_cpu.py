@@ -113,6 +113,19 @@ def test_scan_launches_stay_within_the_grid_limit(scan_grid):
     assert launches == 1
 
 
+def test_scan_of_long_blocks_has_workgroups_for_the_chip(scan_grid):
+    # k contiguous, ESC blocks of several 64s of k: 64 rows to a workgroup only from one and a half workgroups to a CU on (half with
+    # one such operand), below that 16
+    up = lambda x: -(-x // 256) * 256
+    cases = [(*c, rows) for c, rows in (((2000, 40, 1500, 128, 0, 0), 16), ((2000, 40, 1600, 128, 0, 0), 64), ((155, 208, 4555, 1024, 0, 0), 16),
+                                        ((64, 64, 2000, 64, 0, 0), 64), ((6000, 3000, 4555, 48, 0, 0), 16), ((1955, 36, 2987, 1024, 0, 0), 16),
+                                        ((160, 1518, 1783, 256, 0, 0), 16), ((600, 40, 1600, 128, 0, 1), 16), ((600, 40, 1700, 128, 0, 1), 64),
+                                        ((40, 600, 3201, 256, 1, 0), 16), ((40, 600, 3301, 256, 1, 0), 64))]
+    for (m, n, k, b, ar, br, rows), (launches, most, *_) in zip(cases, scan_grid([c[:6] for c in cases])):
+        blocks, row_blocks = -(-k // b), up(m) // (64 if ar else rows) + up(n) // (64 if br else rows)
+        assert (launches, most // 256) == (1, row_blocks * (blocks if row_blocks * -(-blocks // 4) < 1024 else -(-blocks // 4))), (m, n, k, b)
+
+
 def test_blocks_of_one_row_or_column_are_spread_over_the_workgroups(tmp_path_factory):
     run = host_program(tmp_path_factory, "host_esc_walk.cpp")
     sizes = [(64, 64), (32, 32), (16, 512), (512, 16), (128, 128), (33, 47), (2, 300), (300, 2), (1, 700), (256, 256), (8, 4096),
