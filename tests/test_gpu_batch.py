@@ -13,9 +13,11 @@ torch = pytest.importorskip("torch")
 @pytest.mark.parametrize("m,n,k,nb,lanes,opts", [
     (150, 120, 300, 7, 4, dict(mode=0, max_bits=200, heuristic=0)),                      # small calls, remainder of three
     (300, 520, 130, 5, 2, dict(mode=0, max_bits=103, heuristic=0, tile_slices=1)),       # slice counts per block, remainder of one
-    (400, 300, 3000, 4, 4, dict(mode=1, max_bits=55)),                                   # units, k split into parts
-    (1000, 900, 2000, 3, 3, dict(mode=0, max_bits=103, heuristic=0)),                    # units, whole; more than CUs with all
+    (400, 300, 3000, 4, 4, dict(mode=1, max_bits=55)),                                   # 64 x 64 tiles, one and (the next but one) two to a CU
+    (1000, 900, 2000, 3, 3, dict(mode=0, max_bits=103, heuristic=0)),
     (700, 800, 700, 4, 4, dict(mode=3, max_bits=55)),                                    # no guards
+    (700, 600, 4000, 4, 3, dict(mode=0, max_bits=103, heuristic=0)),                     # units, k split into parts (tests/test_unit_walk_cpu.py
+    (1000, 1000, 3000, 4, 4, dict(mode=0, max_bits=103, heuristic=0)),                   # holds them to it), and whole, one to a CU
     (96, 80, 112, 9, 4, dict(mode=0)), (200, 100, 5000, 6, 4, dict(mode=4)), (50, 60, 4000, 5, 2, dict(mode=4)),      # native: shared workspace, k split
     (600, 700, 10, 3, 2, dict(mode=4)), (100, 90, 0, 3, 2, dict(mode=0)),
     (1500, 1400, 600, 3, 3, dict(mode=1, max_bits=55)),                                  # too large to share: streams

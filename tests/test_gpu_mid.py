@@ -11,14 +11,20 @@ from test_gpu_parity import check_against_oracle, lib, run_gpu  # noqa: F401  (l
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("m,n,k,S", [
-    (700, 800, 64, 1), (961, 1030, 300, 2), (1030, 1300, 70, 3), (1100, 1000, 200, 4), (1500, 1600, 50, 5), (1030, 1300, 450, 6),
-    (65, 9000, 130, 5), (9000, 65, 130, 5), (1100, 1024, 129, 7), (1281, 1030, 65, 8),                 # two workgroups to a CU
-    (700, 800, 64, 5), (640, 770, 300, 3), (900, 1000, 100, 8), (700, 800, 130, 9), (700, 810, 64, 10), (705, 800, 65, 12),
-    (900, 1000, 100, 13), (700, 800, 190, 16), (520, 530, 1000, 3),                                     # one
-    (1500, 1300, 64, 14), (1490, 1310, 130, 13), (300, 1650, 64, 16),                                   # one, four groups
-    (2100, 2200, 700, 9), (1100, 1200, 2000, 9), (600, 700, 3000, 12),                                  # one, a long k (the last: 32 x 32 tiles)
-])
+# calls on 64 x 64 tiles (tests/test_unit_walk_cpu.py holds them to it): two workgroups to a CU, and one
+TWO = [
+    (1030, 1290, 64, 1), (961, 1030, 300, 2), (1030, 1300, 70, 3), (1100, 1000, 200, 4), (1500, 1600, 50, 5), (1030, 1300, 450, 6),
+    (65, 9000, 130, 5), (9000, 65, 130, 5), (1100, 1024, 129, 7), (1281, 1030, 65, 8),
+]
+ONE = [
+    (700, 800, 64, 1), (700, 800, 64, 5), (640, 770, 300, 3), (900, 1000, 100, 8), (700, 800, 130, 9), (700, 810, 64, 10), (705, 800, 65, 12),
+    (900, 1000, 100, 13), (700, 800, 190, 16), (520, 530, 1000, 3),
+    (1500, 1300, 64, 14), (1490, 1310, 130, 13), (300, 1650, 64, 16),                                   # both groups of eight
+    (2100, 2200, 700, 9), (1100, 1200, 2000, 9),                                                        # a long k
+]
+
+
+@pytest.mark.parametrize("m,n,k,S", TWO + ONE + [(600, 700, 3000, 12)])
 def test_tiles_of_64(lib, m, n, k, S):
     g, h = lib
     A, B, Cin = wl.lognormal_spread(m, k, n, 0.5, seed=5000 + S + k, with_c=True)
@@ -38,12 +44,19 @@ def test_tiles_of_64_with_slice_counts_per_block(lib, m, n, k):
     np.testing.assert_array_equal(got, tr.C)
 
 
-@pytest.mark.parametrize("S", [1, 2, 4, 5, 6, 7, 8, 9, 10, 13, 16])
+CARRIES = [1, 2, 4, 5, 6, 7, 8, 9, 10, 13, 16]
+
+
+def carries_size(S):
+    return (1030, 1300, 96) if S <= 10 else (1100, 1400, 96)
+
+
+@pytest.mark.parametrize("S", CARRIES)
 def test_carries_at_their_extremes(lib, S):
     """Entries of all-ones digits with one sign (the largest sums and carries, either way), rows of C that are zero because a row of A
     is or because the halves of k cancel, and values of one low digit."""
     g, h = lib
-    m, n, k = 1030, 1300, 96
+    m, n, k = carries_size(S)
     A, B = np.full((m, k), 2.0 - 2.0 ** -52), np.full((k, n), -(2.0 - 2.0 ** -52))
     B[:, ::3] *= -1.0
     A[5::7] = 0.0

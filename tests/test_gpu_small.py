@@ -11,12 +11,17 @@ from test_gpu_parity import check_against_oracle, lib, run_gpu  # noqa: F401  (l
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("m,n,k,S", [
+# calls on 32 x 32 tiles (tests/test_unit_walk_cpu.py holds them to it), each form of the kernel
+TILES_32 = [
     (1, 1, 1, 1), (31, 33, 63, 2), (32, 32, 64, 8), (33, 31, 65, 9), (65, 96, 127, 16), (40, 70, 129, 17),      # one and two anti-diagonals per wave
     (100, 64, 300, 26), (64, 100, 320, 24),                         # the most slices: one 64 of k in LDS at a time
-    (200, 300, 1030, 7), (130, 90, 1500, 3),                        # more 64s of k than fit in LDS
-    (700, 600, 200, 5), (1100, 1000, 130, 10), (520, 530, 70, 18),  # more tiles than CUs: two workgroups per CU, and one
-])
+    (200, 300, 1030, 7), (129, 90, 1500, 12),                       # more 64s of k than fit in LDS
+    (520, 640, 200, 6), (1000, 450, 130, 10), (300, 900, 65, 17),   # more tiles than CUs: two workgroups per CU
+    (520, 530, 70, 18),                                             # and one
+]
+
+
+@pytest.mark.parametrize("m,n,k,S", TILES_32 + [(130, 90, 1500, 3), (700, 600, 200, 5), (1100, 1000, 130, 10)])
 @pytest.mark.parametrize("beta", [0.0, 0.5])
 def test_small_calls(lib, m, n, k, S, beta):
     g, h = lib

@@ -58,8 +58,11 @@ def test_scan_of_an_operand_larger_than_the_cache(lib, ta):
     assert res.esc == min(oz.esc_coarse(A, B, 64), 4096)
 
 
-@pytest.mark.parametrize("m,n,k,S,pad,beta", [(4801, 4810, 1500, 1, 0, 0.5), (4810, 4801, 1500, 2, 1, 0.0), (4801, 3902, 700, 7, 3, -1.5),
-                                              (4802, 3902, 700, 7, 0, 0.0)])
+# 256 x 256 blocks with one slice and with two, units (both: C at 16 bytes aligned and not), and 64 x 64 tiles, whose results are always streamed
+LARGE = [(4801, 4810, 1500, 1, 0, 0.5), (5000, 4990, 2000, 2, 0, 0.0), (4802, 3904, 6000, 7, 0, -1.5), (4801, 3904, 6000, 7, 0, 0.5)]
+
+
+@pytest.mark.parametrize("m,n,k,S,pad,beta", LARGE + [(4810, 4801, 1500, 2, 1, 0.0), (4801, 3902, 700, 7, 3, -1.5), (4802, 3902, 700, 7, 0, 0.0)])
 def test_results_larger_than_the_cache(lib, m, n, k, S, pad, beta):
     """Rows of C at either edge and scattered over it, bit for bit."""
     g, h = lib

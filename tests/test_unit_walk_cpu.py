@@ -87,6 +87,24 @@ def test_calls_of_the_gpu_test_of_units_take_them(walk, tmp_path_factory):
     assert [r[0] for r in walk([(*c, 0, 256) for c in UNITS])] == [0, 1, 1, 1, 2, 2]
 
 
+def test_calls_of_the_gpu_tests_of_tiles_take_them(walk, tmp_path_factory):
+    from test_gpu_mid import CARRIES, ONE, TWO, carries_size
+    from test_gpu_small import TILES_32
+    from test_gpu_streaming import LARGE
+    plan = host_program(tmp_path_factory, "host_call_plan.cpp")
+
+    def routes(calls):
+        return [g for g, in plan([(m, n, k, S, S, 0, 1) for m, n, k, S in calls])]
+    assert routes(TILES_32) == [1] * len(TILES_32)
+    assert routes(TWO) == [3] * len(TWO) and routes(ONE) == [2] * len(ONE)
+    assert routes([(*carries_size(S), S) for S in CARRIES]) == [3 if S <= 8 else 2 for S in CARRIES]
+    assert routes([c[:4] for c in LARGE]) == [0] * len(LARGE)
+    assert [r[5] for r in walk([(*c[:4], 0, 256) for c in LARGE])] == [1, 1, 0, 0]
+    # batches: tiles with one and two to a CU, units
+    assert [g for g, in plan([(400, 300, 3000, 7, 7, 0, 4), (700, 800, 700, 7, 7, 0, 4), (700, 600, 4000, 13, 7, 0, 3),
+                              (1000, 1000, 3000, 13, 7, 0, 4)])] == [2, 3, 0, 0]
+
+
 @pytest.mark.parametrize("num_cu", [4, 12, 36, 100, 250, 304])
 def test_other_numbers_of_compute_units(walk, num_cu):
     # a device that shows some of its units only: not always a multiple of eight.  A workgroup keeps its part of k while it
